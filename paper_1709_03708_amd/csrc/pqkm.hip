@@ -1258,11 +1258,28 @@ pqkm_status assign_indexed_impl(const IndexCarve& c, const uint8_t* codes, int64
     return launched();
 }
 
-template <int DS>
-void launch_encode(const float* vectors, int64_t N, int M, const float* codewords, uint8_t* codes, hipStream_t st)
+// Encoder: a workgroup holds the split codewords of G subspaces, as many as fit 128 KB of LDS, so that it reads whole
+// stretches of the vectors; with few vectors one subspace per workgroup, so that more workgroups share the work.
+template <int KS, int THREADS>
+void launch_encode(const float* vectors, int64_t N, int M, int Ds, const float* codewords, uint8_t* codes, hipStream_t st)
 {
-    hipLaunchKernelGGL((encode_kernel<DS, 256>), dim3((unsigned)((N + 255) / 256), (unsigned)M), dim3(256), 0, st,
-                       vectors, N, M, codewords, codes);
+    constexpr int WAVES = THREADS / 64;
+    int G = 8 / KS;
+    if (G > M) G = M;
+    const int64_t tiles = (N + 31) / 32;
+    const int64_t ncu = cu_count();
+    auto groups = [&](int g) { return (int64_t)((M + g - 1) / g); };
+    while (G > 1 && groups(G) * ((tiles + WAVES - 1) / WAVES) < ncu) G = (G + 1) / 2;
+    int64_t wpg = (tiles + WAVES - 1) / WAVES;
+    const int64_t most = (ncu + groups(G) - 1) / groups(G);      // about one workgroup per compute unit
+    if (wpg > most) wpg = most;
+    const dim3 grid((unsigned)(groups(G) * wpg));
+    if (Ds % 4 == 0 && ((uintptr_t)vectors & 15) == 0)
+        hipLaunchKernelGGL((encode_mfma_kernel<KS, THREADS, true>), grid, dim3(THREADS), 0, st, vectors, N, M, Ds, codewords,
+                           codes, G, (int)wpg);
+    else
+        hipLaunchKernelGGL((encode_mfma_kernel<KS, THREADS, false>), grid, dim3(THREADS), 0, st, vectors, N, M, Ds,
+                           codewords, codes, G, (int)wpg);
 }
 
 }  // namespace
@@ -1308,17 +1325,14 @@ pqkm_status pqkm_encode(const float* vectors, int64_t N, int32_t M, int32_t Ds, 
     if (s != PQKM_OK) return s;
     if (N == 0) return PQKM_OK;
     hipStream_t st = (hipStream_t)stream;
-    switch (Ds) {
-        case 4: launch_encode<4>(vectors, N, M, codewords, codes, st); break;
-        case 8: launch_encode<8>(vectors, N, M, codewords, codes, st); break;
-        case 16: launch_encode<16>(vectors, N, M, codewords, codes, st); break;
-        case 32: launch_encode<32>(vectors, N, M, codewords, codes, st); break;
-        case 64: launch_encode<64>(vectors, N, M, codewords, codes, st); break;
-        case 128: launch_encode<128>(vectors, N, M, codewords, codes, st); break;
-        default:
-            hipLaunchKernelGGL(encode_generic_kernel, dim3((unsigned)((N + 255) / 256), (unsigned)M), dim3(256), 0, st,
-                               vectors, N, M, Ds, codewords, codes);
-    }
+    const int ks = (Ds + 15) / 16;
+    if (ks == 1) launch_encode<1, 1024>(vectors, N, M, Ds, codewords, codes, st);
+    else if (ks == 2) launch_encode<2, 1024>(vectors, N, M, Ds, codewords, codes, st);
+    else if (ks <= 4) launch_encode<4, 512>(vectors, N, M, Ds, codewords, codes, st);
+    else if (ks <= 8) launch_encode<8, 512>(vectors, N, M, Ds, codewords, codes, st);
+    else
+        hipLaunchKernelGGL(encode_generic_kernel, dim3((unsigned)((N + 255) / 256), (unsigned)M), dim3(256), 0, st, vectors,
+                           N, M, Ds, codewords, codes);
     return launched();
 }
 

@@ -1,0 +1,86 @@
+"""Encoder and decoder against the oracle where their kernels can go wrong: every padding of the subvector length, the
+edges of the 32-vector tiles, ties, near ties, unaligned and non-finite inputs, extreme scales."""
+from __future__ import annotations
+
+import numpy as np
+import pytest
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def env():
+    import torch
+
+    import oracle
+    import paper_1709_03708_amd as pq
+
+    assert torch.cuda.is_available()
+    return pq, oracle, torch
+
+
+def _encode(env, vectors, cw, offset=0):
+    pq, _, torch = env
+    buf = torch.empty(vectors.size + offset, dtype=torch.float32, device="cuda")
+    v = buf[offset:].view(vectors.shape)
+    v.copy_(torch.from_numpy(vectors))
+    return pq.encode(v, torch.from_numpy(cw).cuda()).cpu().numpy()
+
+
+@pytest.mark.parametrize("M,Ds,N", [(1, 1, 1), (3, 3, 33), (16, 6, 65), (8, 12, 1000), (4, 16, 31), (5, 20, 97), (4, 24, 513),
+                                    (4, 32, 2049), (9, 33, 64), (3, 48, 100), (2, 64, 3000), (2, 100, 95), (32, 128, 70),
+                                    (2, 130, 40)])
+@pytest.mark.parametrize("offset", [0, 1])
+def test_encode_paddings_and_edges(env, M, Ds, N, offset):
+    oracle = env[1]
+    rng = np.random.default_rng(M * 1000 + Ds)
+    cw = np.abs(20 * rng.standard_normal((M, 256, Ds))).astype(np.float32)
+    vectors = np.abs(20 * rng.standard_normal((N, M * Ds))).astype(np.float32)
+    assert np.array_equal(_encode(env, vectors, cw, offset), oracle.encode(vectors, cw))
+
+
+@pytest.mark.parametrize("Ds", [4, 12, 32, 128])
+def test_encode_ties_and_near_ties(env, Ds):
+    """Duplicated codewords (the lower index wins), codewords one rounding apart, and vectors half-way between two."""
+    oracle = env[1]
+    rng = np.random.default_rng(Ds)
+    M, N = 2, 700
+    cw = rng.standard_normal((M, 256, Ds)).astype(np.float32)
+    cw[:, 128:192] = cw[:, :64]
+    cw[:, 192:224] = np.nextafter(cw[:, 64:96], np.float32(9))
+    cw[:, 224:240] = cw[:, 5:6]
+    vectors = rng.standard_normal((N, M, Ds)).astype(np.float32)
+    for n in range(0, N, 2):
+        a, b = rng.integers(0, 256, 2)
+        vectors[n] = (cw[:, a] + cw[:, b]) * np.float32(0.5)
+    for n in range(1, N, 4):
+        vectors[n] = cw[:, rng.integers(0, 256)]
+    vectors = vectors.reshape(N, M * Ds)
+    assert np.array_equal(_encode(env, vectors, cw), oracle.encode(vectors, cw))
+
+
+@pytest.mark.parametrize("scale", [1e-42, 1e-30, 1e-19, 1e-12, 1e12, 1e18, 3e37])
+@pytest.mark.parametrize("shift", [0.0, 1000.0])
+def test_encode_scales(env, scale, shift):
+    """Squares that underflow, products that overflow, and a common offset far larger than the distances."""
+    oracle = env[1]
+    rng = np.random.default_rng(3)
+    with np.errstate(over="ignore", under="ignore"):
+        cw = ((rng.standard_normal((2, 256, 16)) + shift) * scale).astype(np.float32)
+        vectors = ((rng.standard_normal((300, 32)) + shift) * scale).astype(np.float32)
+    assert np.array_equal(_encode(env, vectors, cw), oracle.encode(vectors, cw))
+
+
+def test_encode_non_finite(env):
+    oracle = env[1]
+    rng = np.random.default_rng(4)
+    cw = rng.standard_normal((3, 256, 24)).astype(np.float32)
+    vectors = rng.standard_normal((200, 72)).astype(np.float32)
+    vectors[3, 5] = np.nan
+    vectors[64, 30] = np.inf
+    vectors[65, 30] = -np.inf
+    vectors[199] = np.nan
+    cw[1, 7, 3] = np.inf
+    cw[2, 0] = np.nan
+    cw[2, 9, 1] = 3e38
+    assert np.array_equal(_encode(env, vectors, cw), oracle.encode(vectors, cw))
