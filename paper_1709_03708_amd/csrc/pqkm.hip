@@ -1346,8 +1346,16 @@ pqkm_status pqkm_decode(const uint8_t* codes, int64_t N, int32_t M, int32_t Ds, 
     if (N == 0) return PQKM_OK;
     const int64_t total = N * M * Ds;
     if ((total + 255) / 256 > (int64_t)0x7fffffff) return PQKM_ERR_SHAPE;
-    hipLaunchKernelGGL(decode_kernel, dim3((unsigned)((total + 255) / 256)), dim3(256), 0, (hipStream_t)stream, codes,
-                       total, M, Ds, codewords, vectors);
+    const unsigned wide = (unsigned)((total + 1024 * DECODE_PER - 1) / (1024 * DECODE_PER));
+    if ((((uintptr_t)vectors | (uintptr_t)codewords) & 15) != 0)
+        hipLaunchKernelGGL(decode_element_kernel, dim3((unsigned)((total + 255) / 256)), dim3(256), 0, (hipStream_t)stream,
+                           codes, total, M, Ds, codewords, vectors);
+    else if (Ds % 4 == 0)
+        hipLaunchKernelGGL((decode_kernel<true>), dim3(wide), dim3(256), 0, (hipStream_t)stream, codes, total, M, Ds,
+                           codewords, vectors);
+    else
+        hipLaunchKernelGGL((decode_kernel<false>), dim3(wide), dim3(256), 0, (hipStream_t)stream, codes, total, M, Ds,
+                           codewords, vectors);
     return launched();
 }
 

@@ -84,3 +84,18 @@ def test_encode_non_finite(env):
     cw[2, 0] = np.nan
     cw[2, 9, 1] = 3e38
     assert np.array_equal(_encode(env, vectors, cw), oracle.encode(vectors, cw))
+
+
+@pytest.mark.parametrize("M,Ds,N", [(1, 1, 1), (1, 1, 4099), (5, 3, 17), (16, 6, 1001), (8, 12, 999), (8, 16, 4096), (4, 32, 1),
+                                    (32, 128, 33), (3, 130, 50), (7, 7, 2048)])
+@pytest.mark.parametrize("offset", [0, 1])
+def test_decode_shapes(env, M, Ds, N, offset):
+    pq, oracle, torch = env
+    rng = np.random.default_rng(M + Ds)
+    cw = rng.standard_normal((M, 256, Ds)).astype(np.float32)
+    codes = rng.integers(0, 256, (N, M), dtype=np.uint8)
+    buf = torch.full((N * M * Ds + offset + 64,), -7.0, device="cuda")
+    out = buf[offset:offset + N * M * Ds].view(N, M * Ds)
+    pq.decode(torch.from_numpy(codes).cuda(), torch.from_numpy(cw).cuda(), vectors=out)
+    assert np.array_equal(out.cpu().numpy(), oracle.decode_f32(cw, codes))
+    assert bool((buf[offset + N * M * Ds:] == -7.0).all()) and bool((buf[:offset] == -7.0).all())
