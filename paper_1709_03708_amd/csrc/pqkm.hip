@@ -11,6 +11,7 @@
 #include <vector>
 
 #include "pqkm_kernels.h"
+#include "pqkm_filter.h"
 
 // Scratch of pqkm_assign_noalloc: one array per GPU, held from the moment the library is loaded on it until the
 // process ends.  In host code this name is only a handle for hipGetSymbolAddress, never an address to pass on.
@@ -92,7 +93,7 @@ inline bool tiled_M(int M) { return M == 4 || M == 8 || M == 16 || M == 32; }
 struct Carve {
     size_t img_off, img_bytes, hist_off, hist_bytes, counts_off, counts_bytes, parts_off, parts_bytes, gid_off,
         gid_bytes, gco_off, plan_off, rows_off, gc8_off, plan8_off, sidx_off, seg_off, pool_off, bseg_off, skew_off,
-        rank_off, tabt_off, rowoff_off, total;
+        rank_off, tabt_off, rowoff_off, state_off, total;
 };
 
 // The regrouped copy of the codes (M = 4 scan) covers one scan launch of at most this many codes.
@@ -120,6 +121,12 @@ HistPlan hist_plan(int64_t N, int M, int K)
     // every cluster group streams one byte per code: worth it while the groups fit a byte and that stays small
     p.cheap = p.groups <= 255 && (double)p.groups * (double)N <= 2.0e9;
     return p;
+}
+
+// does the histogram take the LDS-privatised owner path for this problem (and the call's options)?
+bool owner_histogram(const HistPlan& hp, int force)
+{
+    return hp.KT >= 1 && hp.groups <= 255 && force != 1 && force != 3 && (force == 2 || hp.cheap);
 }
 
 Carve carve(int64_t N, int M, int K)
@@ -170,15 +177,27 @@ Carve carve(int64_t N, int M, int K)
             off += align256((size_t)hp.groups * (size_t)(na / 2048 + 2) * sizeof(uint2));
         }
     }
-    // sorted-path histogram: code indices sorted by cluster (u32), cluster sizes, starts and cursors
-    c.sidx_off = c.seg_off = off;
+    // sorted-path histogram: code indices sorted by cluster (u32), every code's rank inside its cluster left by the scan
+    // (pqkm_fit), cluster sizes, starts and cursors
+    c.sidx_off = c.seg_off = c.state_off = off;
     if (N <= (int64_t)0xffffffff) {
         c.sidx_off = off;
         off += align256((size_t)N * sizeof(uint32_t));
+        c.rank_off = off;
+        off += align256((size_t)N * sizeof(uint32_t));
         c.seg_off = off;
         off += 3 * align256(((size_t)K + 1) * sizeof(uint32_t));
-        c.rank_off = off;                    // every code's rank inside its cluster, left by the scan (pqkm_fit)
-        off += align256((size_t)N * sizeof(uint32_t));
+    }
+    // keys of the lower-bound scans (8 bytes per code position of a launch): they live only while a scan runs.  Where the
+    // histogram of a fused iteration takes the owner path no ranks are handed over, and the keys share the room of the
+    // sorted path (the at most 30 padding positions reach into the cluster sizes, which are written after the scan).
+    if (M == 4) {
+        if (hp.cheap && N <= GROUP_CHUNK_MAX) {
+            c.state_off = c.sidx_off;
+        } else {
+            c.state_off = off;
+            off += align256((size_t)group_alloc(N < GROUP_CHUNK_MAX ? N : GROUP_CHUNK_MAX) * sizeof(uint64_t));
+        }
     }
     c.gc8_off = c.plan8_off = off;
     if (M == 8) {
@@ -620,6 +639,75 @@ int choose_scan4_large(int64_t n)
     return best;
 }
 
+// M = 4 scan through lower bounds (variants 60..64): codes per workgroup 512 R
+// Fewest centers, by iteration of a call.  What a code costs beside the scan of its tiles is candidates, four table lines
+// through the L2 each: about ten in the first iteration, less from the bound that the center of the iteration before
+// gives, less still once most centers no longer change.  Measured at N = 1e6 against the plain scans, ms per iteration:
+// first 0.30 / 0.26 at K = 1000, 0.35 / 0.32 at 1500; second and third 0.235 / 0.221 and 0.287 / 0.306; later
+// 0.148 / 0.149 at K = 500, 0.174 / 0.216 at 1000.  N = 3e6, K = 2500: 1.06 / 1.25, 0.90 / 1.26, 0.75 / 1.26.
+inline int filter4_min_k(int iteration) { return iteration == 0 ? 1700 : iteration < 3 ? 1200 : 600; }
+int filter4_codes_per_slot(int variant, int64_t n_alloc)
+{
+    switch (variant) {
+        case 61: return 16;
+        case 62: return 12;
+        case 63: return 8;
+        case 64: return 4;
+        default: break;
+    }
+    const int ncu = cu_count();
+    static const int cand[] = {16, 12, 8, 4};
+    int best = 16;
+    double best_cost = 1e300;
+    for (int R : cand) {
+        const int64_t wgs = (n_alloc + 512 * R - 1) / (512 * R);
+        const double cost = (double)((wgs + ncu - 1) / ncu) * (R + 1.0);
+        if (cost < best_cost) { best_cost = cost; best = R; }
+    }
+    return best;
+}
+
+template <int R>
+void launch_filter4_rounds(const uint2* gco, int64_t n_alloc, FilterIn f, int32_t* assign, float* dist, hipStream_t st,
+                           RankOut ro, int rounds_per_launch)
+{
+    // one kernel launch per rounds_per_launch rounds of workgroups (see launch_scan4q_rounds)
+    constexpr int64_t C = 512 * (int64_t)R;
+    const int64_t nwg = (n_alloc + C - 1) / C;
+    const int64_t per = rounds_per_launch > 0 ? (int64_t)rounds_per_launch * cu_count() : nwg;
+    unsigned long long* state = f.state;
+    for (int64_t w0 = 0; w0 < nwg; w0 += per) {
+        const int64_t cnt = nwg - w0 < per ? nwg - w0 : per;
+        f.state = state + w0 * C;
+        hipLaunchKernelGGL((assign_filter4_kernel<R, false>), dim3((unsigned)cnt), dim3(1024), 0, st, n_alloc - w0 * C,
+                           gco + w0 * C, f, assign, dist, ro, BucketOut{});
+        ++t_scan_kernels;
+    }
+}
+
+void launch_filter4(int variant, const uint2* gco, int64_t n_alloc, const FilterIn& f, int32_t* assign, float* dist,
+                    hipStream_t st, RankOut ro, int rounds_per_launch)
+{
+    switch (filter4_codes_per_slot(variant, n_alloc)) {
+        case 4: launch_filter4_rounds<4>(gco, n_alloc, f, assign, dist, st, ro, rounds_per_launch); break;
+        case 8: launch_filter4_rounds<8>(gco, n_alloc, f, assign, dist, st, ro, rounds_per_launch); break;
+        case 12: launch_filter4_rounds<12>(gco, n_alloc, f, assign, dist, st, ro, rounds_per_launch); break;
+        default: launch_filter4_rounds<16>(gco, n_alloc, f, assign, dist, st, ro, rounds_per_launch); break;
+    }
+}
+
+// the 4096-code shape, filing (code, center) records by cluster group for the histogram: all workgroups in one launch
+void launch_filter4_bucket(const uint2* gco, int64_t n_alloc, const FilterIn& f, int32_t* assign, float* dist,
+                           hipStream_t st, BucketOut bo, int* nwg_out)
+{
+    constexpr int64_t C = 512 * 8;
+    const int64_t nwg = (n_alloc + C - 1) / C;
+    hipLaunchKernelGGL((assign_filter4_kernel<8, true>), dim3((unsigned)nwg), dim3(1024), 0, st, n_alloc, gco, f, assign,
+                       dist, RankOut{}, bo);
+    ++t_scan_kernels;
+    *nwg_out = (int)nwg;
+}
+
 // M = 8 scans over regrouped codes: variants 70..79.  Variant 70 chooses the codes per lane-slot like the M = 4
 // scan does: rounds * (R + 9) with rounds = ceil(workgroups / CUs) (8e6 codes: 11 rounds of 2605 workgroups at
 // R = 24, 10 rounds of 2500 at R = 25, measured 12.2 ms against 11.4 ms at K = 4000).
@@ -846,7 +934,7 @@ inline int effective_variant(int M, int variant, int64_t N, int K, const uint8_t
     const int TK = 128 / M;
     const bool img32 = (int64_t)((K + TK - 1) / TK) * TILE_BYTES < (int64_t)0xfff00000;
     const bool special = (variant >= 40 && variant <= 49) || (variant >= 70 && variant <= 79) ||
-                         (M == 4 && variant >= 80 && variant <= 99) || (M == 8 && variant >= 80 && variant <= 84);
+                         (M == 4 && variant >= 60 && variant <= 64) || (M == 4 && variant >= 80 && variant <= 99) || (M == 8 && variant >= 80 && variant <= 84);
     if (M == 8) {
         const bool ok8 = img32 && ((uintptr_t)codes & 7) == 0;
         if (special && !ok8) return 0;
@@ -886,14 +974,16 @@ inline int effective_variant(int M, int variant, int64_t N, int K, const uint8_t
     }
     return 70;                            // regrouped half-plane scan, codes per lane-slot chosen per launch
 }
+inline bool variant_filter(int M, int variant) { return M == 4 && variant >= 60 && variant <= 64; }
 inline bool variant_grouped(int M, int variant)
 {
-    return ((M == 4 || M == 8) && variant >= 70 && variant <= 79) || (M == 4 && variant >= 80 && variant <= 99) ||
+    return variant_filter(M, variant) || ((M == 4 || M == 8) && variant >= 70 && variant <= 79) || (M == 4 && variant >= 80 && variant <= 99) ||
            (M == 8 && variant >= 80 && variant <= 84);
 }
 inline bool variant_two_lane(int M, int variant)
 {
-    return (M == 4 && variant >= 80 && variant <= 99) || (M == 8 && variant >= 80 && variant <= 84);
+    return variant_filter(M, variant) || (M == 4 && variant >= 80 && variant <= 99) ||
+           (M == 8 && variant >= 80 && variant <= 84);
 }
 inline bool variant_table_tiles(int M, int variant) { return M == 4 && variant >= 90 && variant <= 99; }
 inline bool variant_lds_loads(int M, int variant) { return M == 4 && variant >= 85 && variant <= 89; }
@@ -911,8 +1001,10 @@ struct BucketLink {
 template <int M>
 pqkm_status assign_tiled(const uint8_t* codes, int64_t N, const uint8_t* centers, int K, const float* tables,
                          int32_t* assign, float* dist, float* img, const Options& opt, const Carve& c, char* ws,
-                         bool reuse_groups, hipStream_t st, BucketLink* link = nullptr)
+                         int iteration, hipStream_t st, BucketLink* link = nullptr)
 {
+    // iteration > 0: a later iteration of the same call (same codes and tables, assign[] holds the result of the one before)
+    const bool reuse_groups = iteration > 0;
     constexpr int TK = 128 / M;
     int64_t ntiles = ((int64_t)K + TK - 1) / TK;
     int64_t total = ntiles * (int64_t)(TILE_BYTES / 4);
@@ -922,13 +1014,36 @@ pqkm_status assign_tiled(const uint8_t* codes, int64_t N, const uint8_t* centers
     // Records to file (the fused iteration at owner-path sizes): the same scan in its 4096-code shape, which files
     // them as the four-lane scan does.
     const bool files_records = M == 4 && link && link->wanted && N <= GROUP_CHUNK_MAX - 16384 && c.bseg_off != c.pool_off;
-    if (M == 4 && variant == 70 && opt.scan_variant == 0 && !files_records)
-        variant = choose_scan4_large(N);
-    else if (M == 4 && variant == 70 && opt.scan_variant == 0 && files_records)
-        variant = 89;
+    // the lower-bound scan addresses its byte tiles through one 32-bit buffer offset and reads centers as words
+    const bool filter_ok = M == 4 && ((uintptr_t)centers & 3) == 0 && ((int64_t)K + 63) / 64 * 65536 < (int64_t)0xfff00000;
+    if (M == 4 && variant == 70 && opt.scan_variant == 0)
+        variant = filter_ok && K >= filter4_min_k(iteration) ? (files_records ? 63 : 60)
+                  : files_records ? 89 : choose_scan4_large(N);
+    else if (variant_filter(M, variant) && !filter_ok)
+        variant = 85;
+    if (M == 4 && variant == 65) variant = files_records ? 89 : choose_scan4_large(N);      // the best of the plain scans
+    const bool filter = variant_filter(M, variant);
+    // the iteration before this one ran a plain scan: no statistics and no keys of it
+    const bool plain_before = iteration > 0 && opt.scan_variant == 0 && K < filter4_min_k(iteration - 1);
     const int layout = variant_layout(M, variant);
     const bool sliding = variant_sliding(M, variant);
-    if (sliding) {
+    FilterIn fin{};
+    if (filter) {
+        FilterStat* stat = reinterpret_cast<FilterStat*>(ws + c.rows_off);
+        const int nt = (K + FILTER_TK - 1) / FILTER_TK;
+        // statistics, the scale, then two copies of the centers (this iteration's, the one before) in the room of the
+        // row-ordered images
+        static_assert(M * FILTER_PARTS * sizeof(FilterStat) <= 4096, "statistics");
+        FilterScale* scale = reinterpret_cast<FilterScale*>(ws + c.rows_off + 4096);
+        uint8_t* copies = reinterpret_cast<uint8_t*>(ws + c.rows_off) + 4352;
+        const size_t copy_stride = align256((size_t)K * M);
+        if (iteration == 0 || plain_before)
+            hipLaunchKernelGGL(filter_stats_kernel, dim3(M * FILTER_PARTS), dim3(1024), 0, st, tables, stat);
+        hipLaunchKernelGGL((filter_image_kernel<M>), dim3((unsigned)(nt * M * 4)), dim3(256), 0, st, centers, K, tables, stat,
+                           reinterpret_cast<uint4*>(img), copies + (iteration & 1) * copy_stride, scale);
+        fin = FilterIn{reinterpret_cast<const uint4*>(img), tables, centers, scale,
+                       reinterpret_cast<unsigned long long*>(ws + c.state_off), K, nt, copies + ((iteration & 1) ^ 1) * copy_stride, 0};
+    } else if (sliding) {
         // tiles of 16 centers, plane-ordered: img[tile][m][x][16]
         ntiles = ((int64_t)K + 15) / 16;
         total = ntiles * (int64_t)16 * M * L;
@@ -949,11 +1064,19 @@ pqkm_status assign_tiled(const uint8_t* codes, int64_t N, const uint8_t* centers
     // a little below the limit: with its padding a launch of exactly 2^26 codes needs one workgroup more than
     // 64 full rounds of 4096-code workgroups, and that workgroup would run a round of its own
     if ((grouped || sliding) && per_launch > GROUP_CHUNK_MAX - 16384) per_launch = GROUP_CHUNK_MAX - 16384;
+    if (filter) {
+        const int64_t round = (int64_t)cu_count() * 512 * filter4_codes_per_slot(variant, group_alloc(N));
+        if (per_launch >= round) per_launch = per_launch / round * round - 32;
+    }
     if (variant_lds_loads(M, variant)) {
         // whole rounds of these large workgroups per stretch (the regrouped copy pads a stretch by less than 32 codes)
         const int64_t round = (int64_t)cu_count() * scan4h_codes_per_workgroup(variant);
         if (per_launch >= round) per_launch = per_launch / round * round - 32;
     }
+    // a later iteration starts from the center of the one before: by code position where the keys of one launch cover all
+    // codes and nothing has used their room since, else through assign[]
+    if (filter && reuse_groups)
+        fin.seeded = N <= per_launch && !plain_before && (c.state_off != c.sidx_off || owner_histogram(hist_plan(N, M, K), opt.hist_kernel)) ? 2 : 1;
     const float4* rows = reinterpret_cast<const float4*>(ws + c.rows_off);
     uint2* gco = reinterpret_cast<uint2*>(ws + c.gco_off);
     GroupPlan* plan = reinterpret_cast<GroupPlan*>(ws + c.plan_off);
@@ -974,7 +1097,7 @@ pqkm_status assign_tiled(const uint8_t* codes, int64_t N, const uint8_t* centers
     // ranks for the sorted-path histogram: from the scans that finish their codes one per lane (the regrouped scans
     // and the sliding-window scan), unless this iteration already hands records over by cluster group
     RankOut ro{};
-    if (link && link->rank_wanted && (grouped || sliding) && !(M == 4 && link->wanted && variant == 70 && N <= per_launch)) {
+    if (link && link->rank_wanted && (grouped || sliding) && !(M == 4 && link->wanted && (variant == 70 || filter) && N <= per_launch)) {
         ro.count = reinterpret_cast<uint32_t*>(ws + c.seg_off);
         ro.rank = reinterpret_cast<uint32_t*>(ws + c.rank_off);
         unsigned zb = (unsigned)((K + 255) / 256 < 1024 ? (K + 255) / 256 : 1024);
@@ -1000,7 +1123,15 @@ pqkm_status assign_tiled(const uint8_t* codes, int64_t N, const uint8_t* centers
                                       dist ? dist + n0 : nullptr, st, rl, opt.rounds_per_launch) != PQKM_OK)
                     return PQKM_ERR_DEVICE;
             }
-        } else if (M == 8 && variant_two_lane(M, variant))
+        } else if (filter && files_records && variant == 63 && N <= per_launch) {
+            BucketOut bo{reinterpret_cast<uint2*>(ws + c.pool_off), reinterpret_cast<uint2*>(ws + c.bseg_off), link->KT,
+                         link->ngroups};
+            launch_filter4_bucket(gco, group_alloc(cnt), fin, assign + n0, dist ? dist + n0 : nullptr, st, bo, &link->nwg);
+            link->produced = true;
+        } else if (filter)
+            launch_filter4(variant, gco, group_alloc(cnt), fin, assign + n0, dist ? dist + n0 : nullptr, st, rl,
+                           opt.rounds_per_launch);
+        else if (M == 8 && variant_two_lane(M, variant))
             launch_scan_grouped8_q(variant, gc8, group_alloc(cnt), reinterpret_cast<const float4*>(img), (int)ntiles,
                                    assign + n0, dist ? dist + n0 : nullptr, st, rl, opt.rounds_per_launch);
         else if (variant == 89 && files_records && N <= per_launch) {
@@ -1043,7 +1174,7 @@ pqkm_status assign_tiled(const uint8_t* codes, int64_t N, const uint8_t* centers
 
 pqkm_status assign_core(const Options& opt, const Carve& c, const uint8_t* codes, int64_t N, int M,
                         const uint8_t* centers, int K, const float* tables, int32_t* assign, float* dist, void* ws,
-                        hipStream_t st, bool reuse_groups, BucketLink* link)
+                        hipStream_t st, int iteration, BucketLink* link)
 {
     bool tiled = tiled_M(M) && opt.assign_kernel != 1 && ((uintptr_t)codes & 3) == 0;
     if (opt.assign_kernel == 2 && !tiled) return PQKM_ERR_SHAPE;
@@ -1055,22 +1186,22 @@ pqkm_status assign_core(const Options& opt, const Carve& c, const uint8_t* codes
     float* img = reinterpret_cast<float*>(static_cast<char*>(ws) + c.img_off);
     char* wsc = static_cast<char*>(ws);
     switch (M) {
-        case 4: return assign_tiled<4>(codes, N, centers, K, tables, assign, dist, img, opt, c, wsc, reuse_groups, st, link);
-        case 8: return assign_tiled<8>(codes, N, centers, K, tables, assign, dist, img, opt, c, wsc, reuse_groups, st, link);
-        case 16: return assign_tiled<16>(codes, N, centers, K, tables, assign, dist, img, opt, c, wsc, false, st, link);
-        default: return assign_tiled<32>(codes, N, centers, K, tables, assign, dist, img, opt, c, wsc, false, st, link);
+        case 4: return assign_tiled<4>(codes, N, centers, K, tables, assign, dist, img, opt, c, wsc, iteration, st, link);
+        case 8: return assign_tiled<8>(codes, N, centers, K, tables, assign, dist, img, opt, c, wsc, iteration, st, link);
+        case 16: return assign_tiled<16>(codes, N, centers, K, tables, assign, dist, img, opt, c, wsc, iteration, st, link);
+        default: return assign_tiled<32>(codes, N, centers, K, tables, assign, dist, img, opt, c, wsc, iteration, st, link);
     }
 }
 
 // one whole assignment step (tile images, regrouping where it is due, scan launches), optionally bracketed by events
 pqkm_status assign_impl(const Options& opt, const Carve& c, const uint8_t* codes, int64_t N, int M,
                         const uint8_t* centers, int K, const float* tables, int32_t* assign, float* dist, void* ws,
-                        hipStream_t st, bool reuse_groups = false, BucketLink* link = nullptr)
+                        hipStream_t st, int iteration = 0, BucketLink* link = nullptr)
 {
     if (N == 0) return PQKM_OK;
     EventPair ev{};
     const bool prof = (opt.profile & 2) && log_begin(g_step_log, st, &ev);
-    const pqkm_status s = assign_core(opt, c, codes, N, M, centers, K, tables, assign, dist, ws, st, reuse_groups, link);
+    const pqkm_status s = assign_core(opt, c, codes, N, M, centers, K, tables, assign, dist, ws, st, iteration, link);
     if (prof) hipEventRecord(ev.b, st);
     return s;
 }
@@ -1104,12 +1235,6 @@ void sort_by_cluster(const int32_t* assign, int64_t N, int K, const Carve& c, ch
     hipLaunchKernelGGL(seg_scatter_kernel, dim3(sb), dim3(256), 0, st, assign, N, K, start, cursor, sidx);
     *start_out = start;
     *sidx_out = sidx;
-}
-
-// does the histogram take the LDS-privatised owner path for this problem (and the call's options)?
-bool owner_histogram(const HistPlan& hp, int force)
-{
-    return hp.KT >= 1 && hp.groups <= 255 && force != 1 && force != 3 && (force == 2 || hp.cheap);
 }
 
 // what a fused iteration asks of its assignment step: records by cluster group, when the histogram would
@@ -1505,7 +1630,7 @@ pqkm_status pqkm_fit(const uint8_t* codes, int64_t N, int32_t M, const float* ta
     for (int it = 0; it < iters; ++it) {
         // the codes do not change between iterations: regroup them for the scan once
         BucketLink link = bucket_request(opt, N, M, K);
-        s = assign_impl(opt, c, codes, N, M, centers, K, tables, assign, nullptr, workspace, (hipStream_t)stream, it > 0,
+        s = assign_impl(opt, c, codes, N, M, centers, K, tables, assign, nullptr, workspace, (hipStream_t)stream, it,
                         &link);
         if (s != PQKM_OK) return s;
         s = update_impl(opt, c, codes, N, M, assign, K, tables, centers, hist, counts, workspace, (hipStream_t)stream,
@@ -1566,7 +1691,7 @@ pqkm_status pqkm_fit_until(const uint8_t* codes, int64_t N, int32_t M, const flo
     const Options opt = options_snapshot();
     for (int it = 0; it < max_iters; ++it) {
         BucketLink link = bucket_request(opt, N, M, K);
-        s = assign_impl(opt, c, codes, N, M, centers, K, tables, assign, dist, workspace, st, it > 0, &link);
+        s = assign_impl(opt, c, codes, N, M, centers, K, tables, assign, dist, workspace, st, it, &link);
         if (s != PQKM_OK) return s;
         hipLaunchKernelGGL(iter_assign_stats_kernel, dim3(STAT_BLOCKS), dim3(256), 0, st, assign, prev, dist, N, pa);
         s = update_impl(opt, c, codes, N, M, assign, K, tables, centers, hist, counts, workspace, st, &link);

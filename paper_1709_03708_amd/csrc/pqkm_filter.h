@@ -1,0 +1,602 @@
+// Assignment scans through a lower bound (Eq. 5 over Eq. 3, exact results).
+//
+// The LDS-tiled scans of pqkm_kernels.h form every fp32 distance: M four-byte look-ups and M - 1 adds per code and
+// center, and the LDS and the vector units are both near their limit doing so.  Nearly all of that work goes into
+// centers that are far from being the nearest.  Here the scan sums one-byte lower bounds of the table entries instead,
+// four centers per 32-bit register, and only the few centers whose bound does not exceed the code's best distance so far
+// get their fp32 distance, formed from the caller's tables in the order of Eq. 3.  The result is that of the plain
+// scan, bit for bit: a center that is skipped has an fp32 distance strictly above one that was formed.
+//
+// The bound.  With lo_m = the smallest finite entry of A^m, U = (A^m[x][c] - lo_m) * inv is an entry in units, and
+// q = min(31, floor(U (1 - 2^-20))) <= U.  Let s be the fp32 distance of (code, center) and b the code's best so far.
+// s <= b implies sum_m A <= b + err with err = (M + 2) 2^-23 sum_m max|A^m| (rounding of the fp32 sum, of lo_m and of
+// the differences), so sum_m q <= (b - sum_m lo_m + err) inv; the threshold is that, rounded up.  A NaN or +inf entry
+// takes q = 31: a distance that contains one is never selected, so skipping it is right.  A -inf entry, tables without
+// spread, or differences that overflow set inv = 0: every bound is 0 and passes, which is correct and then handled as
+// below.  inv = 31 / min(largest difference, 1.75 times the mean one): entries beyond are
+// capped, which only loosens the bound (between 1.5 and 2 the fewest centers pass on codes of clustered data).
+//
+// Where the bound selects too little (ties everywhere, tables without spread) forming the fp32 distances one by one
+// would be slower than the plain scan.  A workgroup counts the candidates it has formed, and when they exceed what the
+// plain scan would have cost it finishes its codes that way: fp32 tiles built in LDS from the tables.
+#pragma once
+#include "pqkm_kernels.h"
+
+namespace pqkm {
+
+constexpr int FILTER_Q = 31;              // largest bound of an entry
+constexpr int FILTER_TK = 64;             // centers per tile: a row of one subcode is 64 bytes
+constexpr uint32_t FILTER_PLANE = 16384;  // bytes per (tile, subspace): 256 subcodes x 64 centers
+constexpr int FILTER_QUEUE = 128;         // candidate entries a wave can hold (drained from 64 on)
+
+// statistics of the tables, FILTER_PARTS blocks per subspace; st[m * FILTER_PARTS + part]
+constexpr int FILTER_PARTS = 8;
+struct FilterStat { float lo, hi, mean, absmax; };       // finite entries; lo = -inf if there is a -inf entry
+
+__global__ __launch_bounds__(1024) void filter_stats_kernel(const float* __restrict__ tables, FilterStat* __restrict__ st)
+{
+    __shared__ float lo_s[16], hi_s[16], sum_s[16];
+    constexpr int PART = L * L / FILTER_PARTS;
+    const float* part = tables + (size_t)blockIdx.x * PART;
+    const float4* t = reinterpret_cast<const float4*>(part);
+    const bool aligned = ((uintptr_t)tables & 15) == 0;
+    float lo = INFINITY, hi = -INFINITY, sum = 0.0f;
+    auto take = [&](float v) {
+        if (v == -INFINITY) lo = v;
+        if (__builtin_fabsf(v) < INFINITY) {
+            lo = v < lo ? v : lo;
+            hi = v > hi ? v : hi;
+            sum += v;
+        }
+    };
+    if (aligned) {
+#pragma unroll
+        for (int i = threadIdx.x; i < PART / 4; i += 1024) {
+            const float4 v = t[i];
+            take(v.x); take(v.y); take(v.z); take(v.w);
+        }
+    } else {
+        for (int i = threadIdx.x; i < PART; i += 1024) take(part[i]);
+    }
+#pragma unroll
+    for (int off = 32; off; off >>= 1) {
+        lo = __builtin_fminf(lo, __shfl_xor(lo, off));
+        hi = __builtin_fmaxf(hi, __shfl_xor(hi, off));
+        sum += __shfl_xor(sum, off);
+    }
+    const int w = threadIdx.x >> 6;
+    if ((threadIdx.x & 63) == 0) { lo_s[w] = lo; hi_s[w] = hi; sum_s[w] = sum; }
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        for (int i = 1; i < 16; ++i) {
+            lo = __builtin_fminf(lo, lo_s[i]);
+            hi = __builtin_fmaxf(hi, hi_s[i]);
+            sum += sum_s[i];
+        }
+        st[blockIdx.x] = FilterStat{lo, hi, sum / (float)PART, __builtin_fmaxf(__builtin_fabsf(lo), __builtin_fabsf(hi))};
+    }
+}
+
+// the smallest finite entry of A^m (-inf if there is a -inf entry)
+__device__ __forceinline__ float filter_low(const FilterStat* __restrict__ st, int m)
+{
+    float lo = st[m * FILTER_PARTS].lo;
+#pragma unroll
+    for (int i = 1; i < FILTER_PARTS; ++i) lo = __builtin_fminf(lo, st[m * FILTER_PARTS + i].lo);
+    return lo;
+}
+
+// what the scan needs of the statistics: units = (value - base) * inv + slack
+struct FilterScale { float inv, base, slack; };
+
+template <int M>
+__device__ __forceinline__ FilterScale filter_scale(const FilterStat* __restrict__ st)
+{
+    float span = 0.0f, mean = 0.0f, base = 0.0f, absmax = 0.0f;
+#pragma unroll
+    for (int m = 0; m < M; ++m) {
+        FilterStat s = st[m * FILTER_PARTS];
+#pragma unroll
+        for (int i = 1; i < FILTER_PARTS; ++i) {
+            const FilterStat o = st[m * FILTER_PARTS + i];
+            s.lo = __builtin_fminf(s.lo, o.lo);
+            s.hi = __builtin_fmaxf(s.hi, o.hi);
+            s.mean += o.mean;
+            s.absmax = __builtin_fmaxf(s.absmax, o.absmax);
+        }
+        const float d = s.hi - s.lo;
+        span = (d > span || !(d == d)) ? d : span;
+        mean += s.mean / (float)FILTER_PARTS - s.lo;
+        base += s.lo;
+        absmax += s.absmax;
+    }
+    float cap = 1.75f * (mean / (float)M);
+    cap = span < cap ? span : cap;
+    FilterScale f;
+    f.inv = (float)FILTER_Q / cap;
+    // no spread, -inf or NaN anywhere, or an inverse out of range: everything passes
+    if (!(span > 0.0f && span < INFINITY) || !(cap > 0.0f) || !(f.inv > 0.0f && f.inv < 1e30f) || !(absmax < 1e30f)) f.inv = 0.0f;
+    f.base = f.inv > 0.0f ? base : 0.0f;
+    f.slack = f.inv > 0.0f ? 0.01f + (float)(M + 2) * 0x1p-23f * absmax * f.inv : 0.0f;
+    return f;
+}
+
+__device__ __forceinline__ uint32_t filter_quantise(float a, float lo, float inv)
+{
+    const float u = (a - lo) * inv * (1.0f - 0x1p-20f);
+    return u < (float)FILTER_Q ? (uint32_t)(u > 0.0f ? u : 0.0f) : (uint32_t)FILTER_Q;      // NaN and +inf: the cap
+}
+
+// largest sum of bounds a center may have, at most `tmax` (which passes everything); best = NaN or +inf: tmax
+__device__ __forceinline__ uint32_t filter_threshold(float best, const FilterScale& f, uint32_t tmax)
+{
+    const float u = (best - f.base) * f.inv * (1.0f + 0x1p-18f) + f.slack;
+    if (!(f.inv > 0.0f) || !(best < INFINITY)) return tmax;
+    return u < (float)tmax ? (uint32_t)(u > 0.0f ? u : 0.0f) : tmax;
+}
+
+// img[tile][m][x][64 centers]: block (tile, m, quarter of the subcodes), 256 threads of 16 bytes each.  Centers past K
+// take the cap; the scan drops them by their index.
+template <int M>
+__global__ __launch_bounds__(256) void filter_image_kernel(const uint8_t* __restrict__ centers, int K,
+                                                            const float* __restrict__ tables,
+                                                            const FilterStat* __restrict__ st, uint4* __restrict__ img,
+                                                            uint8_t* __restrict__ copy, FilterScale* __restrict__ scale)
+{
+    __shared__ uint32_t sub[FILTER_TK];
+    const int tile = (int)(blockIdx.x / (4 * M)), m = (int)(blockIdx.x / 4 % M), part = (int)(blockIdx.x % 4);
+    const FilterScale sc = filter_scale<M>(st);
+    if (blockIdx.x == 0 && threadIdx.x == 0) *scale = sc;            // for the scan
+    const float inv = sc.inv, lo = filter_low(st, m);
+    if (threadIdx.x < FILTER_TK) {
+        const int64_t k = (int64_t)tile * FILTER_TK + threadIdx.x;
+        sub[threadIdx.x] = k < K ? centers[k * M + m] : 256u;
+        if (part == 0 && k < K) copy[k * M + m] = centers[k * M + m];       // for the next iteration's comparison
+    }
+    __syncthreads();
+    const int x = part * 64 + (threadIdx.x >> 2), p = threadIdx.x & 3;
+    const float* row = tables + ((size_t)m * L + x) * L;
+    float v[16];
+#pragma unroll
+    for (int i = 0; i < 16; ++i) {
+        const uint32_t c = sub[p * 16 + i];
+        v[i] = c < 256u ? row[c] : INFINITY;
+    }
+    uint32_t w[4] = {0u, 0u, 0u, 0u};
+#pragma unroll
+    for (int i = 0; i < 16; ++i) w[i >> 2] |= filter_quantise(v[i], lo, inv) << (8 * (i & 3));
+    img[((size_t)tile * M + m) * 1024 + part * 256 + threadIdx.x] = make_uint4(w[0], w[1], w[2], w[3]);
+}
+
+// (distance, center) as one integer whose order is "smaller distance, then lower index"; -0 counts as +0
+__device__ __forceinline__ unsigned long long filter_key(float s, uint32_t k)
+{
+    const float z = s + 0.0f;
+    const uint32_t u = __builtin_bit_cast(uint32_t, z);
+    const uint32_t o = u ^ ((u >> 31) ? 0xffffffffu : 0x80000000u);
+    return ((unsigned long long)o << 32) | k;
+}
+__device__ __forceinline__ float filter_key_distance(unsigned long long key)
+{
+    const uint32_t o = (uint32_t)(key >> 32);
+    return __builtin_bit_cast(float, o ^ ((o >> 31) ? 0x80000000u : 0xffffffffu));
+}
+__device__ __forceinline__ float filter_next_up(float v)          // the next float above a finite v or -inf
+{
+    const int32_t b = __builtin_bit_cast(int32_t, v + 0.0f);
+    return v == 0.0f ? 0x1p-149f : __builtin_bit_cast(float, b < 0 ? b - 1 : b + 1);
+}
+constexpr unsigned long long FILTER_NONE = ~0ull;        // no center selected yet
+
+struct FilterIn {
+    const uint4* img;                // byte tiles
+    const float* tables;
+    const uint8_t* centers;          // 4-byte aligned
+    const FilterScale* scale;
+    unsigned long long* state;       // one key per code position of the launch
+    int K, ntiles;                   // ntiles = ceil(K / 64)
+    const uint8_t* before;           // the centers of the iteration whose keys `state` holds (seeded == 2)
+    int seeded;                      // 1: assign[] holds a center for every code (of the iteration before); 2: so does `state`
+};
+
+// 4 subcodes of a code or center packed in a word
+__device__ __forceinline__ float filter_distance4(const float* __restrict__ tables, uint32_t x, uint32_t c)
+{
+    const float a0 = tables[((x & 255u) << 8) | (c & 255u)];
+    const float a1 = tables[65536u + ((x & 0xff00u) | ((c >> 8) & 255u))];
+    const float a2 = tables[131072u + (((x >> 8) & 0xff00u) | ((c >> 16) & 255u))];
+    const float a3 = tables[196608u + (((x >> 16) & 0xff00u) | (c >> 24))];
+    return ((a0 + a1) + a2) + a3;
+}
+
+// ---------------------------------------------------------------------------------------------
+// M = 4: regrouped codes and two-lane slots of assign_scan4h_kernel, whose 64-byte rows of 16 fp32 centers are here rows
+// of 64 one-byte centers; the same conflict-free reads, the same half-ahead loads straight into LDS (a tile of 64
+// centers is 64 KB, two buffers).  Per code and tile a lane reads 2 x 16 bytes per subspace = 32 centers, and adds the
+// four bounds and 127 - threshold in every byte of a register (two three-operand adds; at most 4 * 31 + 128 = 252, no
+// byte carries into its neighbour): the high bit of a byte stays clear exactly when the center passes.  A code that
+// adds 128 passes nothing (the holes of the regrouped array).  The high bits of two codes are and'ed into one test per
+// wave; lanes with a clear one append (mask of 32 centers, code, tile) to a queue of their wave in LDS, and 64 entries are worked off
+// at a time, one lane each: subcodes of the center, four table entries through the L2, an atomic minimum of (distance,
+// index) on the code's key in global memory, the new threshold to LDS.  Thresholds are one byte per code in LDS, read 16
+// at a time when a tile begins.  Before the first tile every code needs a bound: the distance to its center of the
+// previous iteration, where there is one, else that to the center with the smallest sum of bounds in the first tile.
+// ---------------------------------------------------------------------------------------------
+template <int V> struct IntC { static constexpr int value = V; };
+
+typedef unsigned short v2us __attribute__((ext_vector_type(2)));
+
+__device__ __forceinline__ uint32_t pk_min_u16(uint32_t a, uint32_t b)
+{
+    return __builtin_bit_cast(uint32_t, __builtin_elementwise_min(__builtin_bit_cast(v2us, a), __builtin_bit_cast(v2us, b)));
+}
+
+template <int R, bool BUCKET>
+__global__ __launch_bounds__(1024) void assign_filter4_kernel(int64_t N, const uint2* __restrict__ gco, FilterIn f,
+                                                              int32_t* __restrict__ assign, float* __restrict__ dist,
+                                                              RankOut ro, BucketOut bo)
+{
+    constexpr int THREADS = 1024, SLOTS = 512, C = SLOTS * R, DEPTH = 3, TW = R / 4;
+    constexpr uint32_t ALL = 127u, DEAD = 128u;          // what passes everything; what is added for a hole
+    constexpr uint32_t HI = 0x80808080u;
+    static_assert(R % 4 == 0, "thresholds are read as words of four codes");
+    __shared__ float4 tile[TILE_F4];
+    __shared__ uint32_t thr_s[SLOTS * TW];
+    __shared__ uint2 queue_s[THREADS / 64][FILTER_QUEUE];
+    __shared__ uint32_t trips_s, bail_s[2];
+    __shared__ uint32_t gcnt[BUCKET ? 256 : 1], gbase[BUCKET ? 256 : 1];
+    const char* tb = reinterpret_cast<const char*>(tile);
+    uint8_t* thr_b = reinterpret_cast<uint8_t*>(thr_s);
+
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int q = tid & 1, c = tid >> 1;
+    const uint32_t hq = ((uint32_t)(c & 1) << 5) | ((uint32_t)q << 4);
+    const int64_t base = (int64_t)blockIdx.x * C;
+    const uint32_t low15 = 0x7fffu;
+    uint2* queue = queue_s[wave];
+
+    // tile t goes to buffer t & 1, plane m of buffer h at byte (2 m + h) * 16384
+    const uint64_t ip = reinterpret_cast<uint64_t>(f.img);
+    const v4i rs_img = {(int)(uint32_t)ip, (int)(uint32_t)(ip >> 32), (int)((uint32_t)f.ntiles * 65536u), 0x00020000};
+    const uint32_t lds0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) char*)tile;
+    const uint32_t wave_off = (uint32_t)wave * 1024u, lane_off = (uint32_t)tid * 16u;
+    auto fetch = [&](int t, int h, int m) {
+        buffer_to_lds16(lds0 + (uint32_t)(2 * m + h) * FILTER_PLANE + wave_off, rs_img, lane_off,
+                        (uint32_t)t * 65536u + (uint32_t)m * FILTER_PLANE);
+    };
+#pragma unroll
+    for (int m = 0; m < 4; ++m) fetch(0, 0, m);
+
+    const FilterScale sc = *f.scale;
+    const uint32_t* cen = reinterpret_cast<const uint32_t*>(f.centers);
+    if (tid == 0) trips_s = 0u;
+    if (tid < 2) bail_s[tid] = 0u;
+
+    // keys and thresholds of the workgroup's codes; the loads of four codes travel together
+    constexpr int SB = (R / 2) % 4 == 0 ? 4 : (R / 2) % 3 == 0 ? 3 : 2;
+    static_assert((R / 2) % SB == 0, "whole batches");
+#pragma unroll 1
+    for (int i0 = 0; i0 < R / 2; i0 += SB) {
+        uint2 g[SB];
+        uint32_t k[SB];
+        float s[SB];
+        unsigned long long old[SB];
+#pragma unroll
+        for (int i = 0; i < SB; ++i) {
+            const int64_t n = base + (i0 + i) * THREADS + tid, nc = n < N ? n : N - 1;
+            g[i] = gco[nc];
+            if (n >= N) g[i].y = ORIGIN_NONE;
+            old[i] = f.seeded == 2 ? f.state[nc] : FILTER_NONE;
+            k[i] = (uint32_t)old[i];
+        }
+        if (f.seeded) {
+#pragma unroll
+            for (int i = 0; i < SB; ++i) {
+                if (f.seeded == 1) k[i] = (uint32_t)assign[g[i].y == ORIGIN_NONE ? 0u : g[i].y];
+                k[i] = k[i] < (uint32_t)f.K ? k[i] : 0u;             // any center will do
+            }
+#pragma unroll
+            for (int i = 0; i < SB; ++i) {
+                // an unchanged center is as far as it was; table entries are fetched for the others only
+                const uint32_t now = cen[k[i]];
+                s[i] = filter_key_distance(old[i]);
+                if (f.seeded != 2 || old[i] == FILTER_NONE || reinterpret_cast<const uint32_t*>(f.before)[k[i]] != now)
+                    s[i] = filter_distance4(f.tables, g[i].x, now);
+            }
+        }
+#pragma unroll
+        for (int i = 0; i < SB; ++i) {
+            const int jj = (i0 + i) * THREADS + tid;
+            unsigned long long key = FILTER_NONE;
+            uint32_t t = g[i].y == ORIGIN_NONE ? DEAD : 0u;
+            if (f.seeded && g[i].y != ORIGIN_NONE && s[i] < INFINITY) {
+                key = filter_key(s[i], k[i]);
+                t = ALL - filter_threshold(s[i], sc, ALL);
+            }
+            if (base + jj < N) f.state[base + jj] = key;
+            thr_b[(jj % SLOTS) * R + jj / SLOTS] = (uint8_t)t;
+        }
+    }
+
+    uint32_t pa[R], pb[R];
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+        int64_t n = base + (int64_t)r * SLOTS + c;
+        if (n >= N) n = N - 1;
+        const uint32_t pk = gco[n].x;
+        const uint32_t f0 = ((pk & 255u) << 6) | hq;
+        const uint32_t f1 = (((pk >> 8) & 255u) << 6) | hq;
+        const uint32_t f2 = ((((pk >> 16) & 255u) << 6) | hq) + 65536u;
+        const uint32_t f3 = (((pk >> 24) << 6) | hq) + 65536u;
+        pa[r] = f0 | (f2 << 15);
+        pb[r] = f1 | (f3 << 15);
+    }
+
+    int qn = 0;                                  // entries in the wave's queue (the same in all lanes)
+
+    // up to 64 entries, one lane each
+    auto drain = [&]() __attribute__((always_inline)) {
+        const int cnt = qn < 64 ? qn : 64;
+        qn -= cnt;
+        __builtin_amdgcn_wave_barrier();
+        const uint2 e = queue[qn + (lane < cnt ? lane : 0)];
+        __builtin_amdgcn_wave_barrier();
+        uint32_t mask = lane < cnt ? e.x : 0u;
+        const uint32_t r = e.y & 31u, sl = (e.y >> 5) & 31u, eq = (e.y >> 10) & 1u, t = e.y >> 11;
+        const int slot = wave * 32 + (int)sl;
+        const int64_t n = base + (int64_t)r * SLOTS + slot;
+        const uint32_t piece = 2u * (sl & 1u) + eq;
+        const uint32_t x = gco[n].x;             // only positions below N ever pass
+        // the center the key names already (the bound a code starts with is often its answer) needs no second look
+        const unsigned long long known = __hip_atomic_load(&f.state[n], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        {
+            const uint32_t in = (uint32_t)known - t * FILTER_TK;           // its place in this tile, if it is here
+            if (known != FILTER_NONE && in < (uint32_t)FILTER_TK && ((in >> 4) & ~2u) == (piece & ~2u)) {
+                const uint32_t j = (((in >> 4) == piece) ? 0u : 4u) + ((in >> 2) & 3u);
+                mask &= ~(1u << (8u * (in & 3u) + 7u - j));
+            }
+        }
+        float sb = INFINITY;
+        uint32_t kb = 0xffffffffu;
+        int trips = 0;
+        while (__any(mask != 0u)) {
+            ++trips;
+            if (mask) {
+                const uint32_t bit = (uint32_t)__builtin_ctz(mask), j = 7u - (bit & 7u);
+                mask &= mask - 1u;
+                const uint32_t k = t * FILTER_TK + 16u * (piece ^ ((j >> 2) << 1)) + 4u * (j & 3u) + (bit >> 3);
+                if (k < (uint32_t)f.K) {
+                    const float s = filter_distance4(f.tables, x, cen[k]);
+                    if (s < INFINITY && (s < sb || (s == sb && k < kb))) { sb = s; kb = k; }
+                }
+            }
+        }
+        if (kb != 0xffffffffu) {                 // some distance below +inf
+            atomicMin(&f.state[n], filter_key(sb, kb));
+            const uint32_t nt = ALL - filter_threshold(sb, sc, ALL);
+            uint8_t* p = thr_b + slot * R + r;
+            if (nt > *p) *p = (uint8_t)nt;
+        }
+        if (lane == 0) atomicAdd(&trips_s, (uint32_t)trips);
+    };
+    // The lanes with a clear high bit in what they hold of code r0 (a0; n0 is the and of its registers) or r1 append
+    // their 32 centers: bit 8 b + 7 - j for byte b of register j.  A lane with both appends twice.
+    auto push = [&](const uint32_t (&a0)[8], const uint32_t (&a1)[8], uint32_t n0, uint32_t n1, int r0, int r1, int t)
+        __attribute__((always_inline)) {
+        bool p0 = (n0 & HI) != HI, p1 = (n1 & HI) != HI;
+#pragma unroll 1
+        while (true) {
+            const uint64_t who = __ballot(p0 || p1);
+            if (!who) break;
+            uint32_t m = 0u;
+#pragma unroll
+            for (int j = 7; j >= 0; --j) {
+                const uint32_t v = p0 ? a0[j] : a1[j];
+                m = j == 7 ? v : (v & HI) | ((m >> 1) & ~HI);
+            }
+            m = ~m;
+            const int at = qn + (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(who >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)who, 0u));
+            if (p0 || p1)
+                queue[at] = make_uint2(m, (uint32_t)(p0 ? r0 : r1) | ((uint32_t)(lane >> 1) << 5) | ((uint32_t)q << 10) | ((uint32_t)t << 11));
+            p1 = p0 && p1;
+            p0 = false;
+            qn += __builtin_popcountll(who);
+            if (qn >= 64) drain();
+        }
+    };
+
+    struct Pair { uint4 a, b; };
+    // one tile, in buffer h; SEED: instead of the thresholds, what comes closest in this tile passes
+    auto scan_tile = [&](auto hc, auto seed_c, int t, bool more) __attribute__((always_inline)) {
+        constexpr int h = decltype(hc)::value;
+        constexpr bool SEED = decltype(seed_c)::value;
+        uint32_t tw[TW];
+#pragma unroll
+        for (int i = 0; i < TW; ++i) tw[i] = thr_s[c * TW + i];
+        auto issue = [&](int step) -> Pair {
+            const int r = step / 4, m = step % 4;
+            const uint32_t ad = (m == 0) ? unpack_low15(low15, pa[r]) : (m == 1) ? unpack_low15(low15, pb[r])
+                              : (m == 2) ? unpack_high17(pa[r]) : unpack_high17(pb[r]);
+            const uint32_t po = ((m & 1) ? 2 * FILTER_PLANE : 0) + h * FILTER_PLANE;
+            Pair p;
+            p.a = *reinterpret_cast<const uint4*>(tb + ad + po);
+            p.b = *reinterpret_cast<const uint4*>(tb + (ad ^ 32u) + po);
+            return p;
+        };
+        Pair ring[DEPTH];
+#pragma unroll
+        for (int d = 0; d < DEPTH; ++d) ring[d] = issue(d);
+        uint32_t acc[2][8], all[2];
+#pragma unroll
+        for (int r = 0; r < R; ++r) {
+            if (!SEED) {
+#pragma unroll
+                for (int m = 0; m < 4; ++m)
+                    if ((m * R) / 8 == r && more) fetch(t + 1, h ^ 1, m);
+            }
+            uint32_t (&a)[8] = acc[r & 1];
+            const uint32_t ts = __builtin_amdgcn_perm(tw[r / 4], tw[r / 4], 0x01010101u * (uint32_t)(r & 3));
+            Pair v[4];
+#pragma unroll
+            for (int m = 0; m < 4; ++m) {
+                const int step = 4 * r + m;
+                v[m] = ring[step % DEPTH];
+                if (step + DEPTH < 4 * R) ring[step % DEPTH] = issue(step + DEPTH);
+            }
+            a[0] = v[0].a.x + v[1].a.x + v[2].a.x;  a[1] = v[0].a.y + v[1].a.y + v[2].a.y;
+            a[2] = v[0].a.z + v[1].a.z + v[2].a.z;  a[3] = v[0].a.w + v[1].a.w + v[2].a.w;
+            a[4] = v[0].b.x + v[1].b.x + v[2].b.x;  a[5] = v[0].b.y + v[1].b.y + v[2].b.y;
+            a[6] = v[0].b.z + v[1].b.z + v[2].b.z;  a[7] = v[0].b.w + v[1].b.w + v[2].b.w;
+            a[0] = a[0] + v[3].a.x + ts;  a[1] = a[1] + v[3].a.y + ts;  a[2] = a[2] + v[3].a.z + ts;  a[3] = a[3] + v[3].a.w + ts;
+            a[4] = a[4] + v[3].b.x + ts;  a[5] = a[5] + v[3].b.y + ts;  a[6] = a[6] + v[3].b.z + ts;  a[7] = a[7] + v[3].b.w + ts;
+            if (SEED) {
+                // bytes are sums of bounds (codes that have no distance yet) or at least 128 (holes)
+                uint32_t mn = 0xffffffffu;
+#pragma unroll
+                for (int j = 0; j < 8; ++j) {
+                    mn = pk_min_u16(mn, a[j] & 0x00ff00ffu);
+                    mn = pk_min_u16(mn, (a[j] >> 8) & 0x00ff00ffu);
+                }
+                uint32_t low = (mn & 0xffffu) < (mn >> 16) ? (mn & 0xffffu) : (mn >> 16);
+                const uint32_t other = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)low, 0xB1, 0xf, 0xf, true);
+                low = other < low ? other : low;
+                const uint32_t up = (low <= ALL ? ALL - low : 0u) * 0x01010101u;
+#pragma unroll
+                for (int j = 0; j < 8; ++j) a[j] += up;
+            }
+            all[r & 1] = (((a[0] & a[1] & a[2]) & (a[3] & a[4])) & (a[5] & a[6])) & a[7];
+            if ((r & 1) && __builtin_expect(__any((all[0] & all[1] & HI) != HI), 0)) push(acc[0], acc[1], all[0], all[1], r - 1, r, t);
+        }
+    };
+
+    if (!f.seeded) {
+        wait_vector_loads();
+        __syncthreads();
+        scan_tile(IntC<0>{}, IntC<1>{}, 0, false);
+        while (qn > 0) drain();
+    }
+    int t = 0;
+    bool bail = false;
+    for (; t < f.ntiles; ++t) {
+        wait_vector_loads();
+        // one thread decides for all whether the candidates cost more than the plain scan would; its verdict of this
+        // turn stays untouched until everybody has passed the next barrier
+        if (tid == 0) bail_s[t & 1] = trips_s * 64u > (uint32_t)C * (32u + (uint32_t)t + ((uint32_t)t >> 2)) ? 1u : 0u;
+        __syncthreads();
+        if (bail_s[t & 1]) { bail = true; break; }
+        const bool more = t + 1 < f.ntiles;
+        if (t & 1) scan_tile(IntC<1>{}, IntC<0>{}, t, more);
+        else scan_tile(IntC<0>{}, IntC<0>{}, t, more);
+    }
+    while (qn > 0) drain();
+
+    if (bail) {
+        // The plain scan of what is left: 16 centers at a time as fp32 rows in the first buffer's planes.  All loads
+        // into LDS have been waited for above.
+        float best[R];
+        __syncthreads();
+#pragma unroll
+        for (int r = 0; r < R; ++r) {
+            const int64_t n = base + (int64_t)r * SLOTS + c;
+            const unsigned long long key = n < N ? __hip_atomic_load(&f.state[n], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : FILTER_NONE;
+            // the next float up, so that an equal distance at a lower index (the bound may come from a later center) still counts
+            best[r] = key == FILTER_NONE ? INFINITY : filter_next_up(filter_key_distance(key));
+        }
+        for (int k0 = t * FILTER_TK; k0 < f.K; k0 += 16) {
+            __syncthreads();
+            for (int e = tid; e < 4 * L * 16; e += THREADS) {
+                const int kin = e & 15, x = (e >> 4) & 255, m = e >> 12;
+                const int k = k0 + kin;
+                const float v = k < f.K ? f.tables[((size_t)m * L + x) * L + f.centers[(size_t)k * 4 + m]] : INFINITY;
+                reinterpret_cast<float*>(tile)[m * 8192 + x * 16 + kin] = v;
+            }
+            __syncthreads();
+#pragma unroll
+            for (int r = 0; r < R; ++r) {
+                float v[8];
+#pragma unroll
+                for (int m = 0; m < 4; ++m) {
+                    const uint32_t ad = (m == 0) ? unpack_low15(low15, pa[r]) : (m == 1) ? unpack_low15(low15, pb[r])
+                                      : (m == 2) ? unpack_high17(pa[r]) : unpack_high17(pb[r]);
+                    const uint32_t po = (m & 1) ? 2 * FILTER_PLANE : 0;
+                    const float4 va = lds_read16(tb, ad + po), vb = lds_read16(tb, (ad ^ 32u) + po);
+                    const float w[8] = {va.x, va.y, va.z, va.w, vb.x, vb.y, vb.z, vb.w};
+#pragma unroll
+                    for (int j = 0; j < 8; ++j) v[j] = m == 0 ? w[j] : v[j] + w[j];
+                }
+                // lane's pieces of four centers: first read, second read
+                const uint32_t p0 = hq >> 4;
+                int kk = -1;
+#pragma unroll
+                for (int j = 0; j < 8; ++j) {
+                    const int k = k0 + 4 * (int)(j < 4 ? p0 : (p0 ^ 2u)) + (j & 3);
+                    if (v[j] < best[r] || (kk >= 0 && v[j] == best[r] && k < kk)) { best[r] = v[j]; kk = k; }
+                }
+                const int64_t n = base + (int64_t)r * SLOTS + c;
+                if (kk >= 0 && n < N) atomicMin(&f.state[n], filter_key(best[r], (uint32_t)kk));
+            }
+        }
+    }
+
+    // results: lane l finishes the codes l, l + THREADS, ...
+    if (BUCKET && tid < 256) gcnt[tid] = 0u;
+    wait_vector_loads();
+    __syncthreads();
+#pragma unroll 4
+    for (int i = 0; i < R / 2; ++i) {
+        const int jj = i * THREADS + tid;
+        const int64_t n = base + jj;
+        uint32_t pk = 0u, og = ORIGIN_NONE, k = 0u;
+        if (n < N) {
+            const uint2 g = gco[n];
+            const unsigned long long key = __hip_atomic_load(&f.state[n], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            pk = g.x;
+            og = g.y;
+            k = key == FILTER_NONE ? 0u : (uint32_t)key;
+            if (og != ORIGIN_NONE) {
+                assign[og] = (int32_t)k;
+                if (dist) {
+                    float s = key == FILTER_NONE ? INFINITY : filter_key_distance(key);
+                    if (s == 0.0f) s = filter_distance4(f.tables, pk, cen[k]);       // the sign of a zero
+                    dist[og] = s;
+                }
+                if (ro.count) ro.rank[og] = atomicAdd(&ro.count[k], 1u);
+            }
+        }
+        if (BUCKET) {
+            // the code, its center, its cluster group and its rank among the workgroup's codes of that group
+            uint32_t g = 0xffffffffu, rank = 0u;
+            if (og != ORIGIN_NONE) {
+                g = k / (uint32_t)bo.KT;
+                g = g < 255u ? g : 255u;
+                rank = atomicAdd(&gcnt[g], 1u);
+            }
+            reinterpret_cast<uint4*>(tile)[jj] = make_uint4(pk, k, g, rank);
+        }
+    }
+    if (BUCKET) {
+        static_assert(!BUCKET || C * 16 <= TILE_BYTES, "one 16-byte record per code");
+        __syncthreads();
+        if (tid < 64) {                                          // exclusive prefix over the groups: lane l owns 4l .. 4l+3
+            const uint32_t a0 = gcnt[4 * tid], a1 = gcnt[4 * tid + 1], a2 = gcnt[4 * tid + 2], a3 = gcnt[4 * tid + 3];
+            const uint32_t mine = a0 + a1 + a2 + a3;
+            const uint32_t e0 = wave_inclusive_scan(mine) - mine, e1 = e0 + a0, e2 = e1 + a1, e3 = e2 + a2;
+            gbase[4 * tid] = e0;  gbase[4 * tid + 1] = e1;  gbase[4 * tid + 2] = e2;  gbase[4 * tid + 3] = e3;
+            const size_t nw = gridDim.x;
+            uint2* sg = bo.seg + blockIdx.x;
+            if (4 * tid < bo.ngroups) sg[(size_t)(4 * tid) * nw] = make_uint2((uint32_t)(base + e0), a0);
+            if (4 * tid + 1 < bo.ngroups) sg[(size_t)(4 * tid + 1) * nw] = make_uint2((uint32_t)(base + e1), a1);
+            if (4 * tid + 2 < bo.ngroups) sg[(size_t)(4 * tid + 2) * nw] = make_uint2((uint32_t)(base + e2), a2);
+            if (4 * tid + 3 < bo.ngroups) sg[(size_t)(4 * tid + 3) * nw] = make_uint2((uint32_t)(base + e3), a3);
+        }
+        __syncthreads();
+#pragma unroll 2
+        for (int i = 0; i < R / 2; ++i) {
+            const uint4 r = reinterpret_cast<const uint4*>(tile)[i * THREADS + tid];
+            if (r.z != 0xffffffffu) bo.pool[base + gbase[r.z] + r.w] = make_uint2(r.x, r.y);
+        }
+    }
+}
+
+}  // namespace pqkm

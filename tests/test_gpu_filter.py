@@ -1,0 +1,170 @@
+"""The scans through lower bounds against the oracle, where the bound, the candidates or the fall-back to the plain scan
+can go wrong: edges of tiles and workgroups, ties, tables the bound says nothing about, non-finite and signed-zero entries,
+several iterations from the centers of the one before."""
+from __future__ import annotations
+
+import numpy as np
+import pytest
+
+from _util import progress, rand_tables, u32
+
+pytestmark = pytest.mark.gpu
+
+VARIANTS = {4: [60, 61, 62, 63, 64]}
+ALL = [(M, v) for M in VARIANTS for v in VARIANTS[M]]
+
+
+@pytest.fixture(scope="module")
+def env():
+    import torch
+
+    import oracle
+    import paper_1709_03708_amd as pq
+
+    assert torch.cuda.is_available()
+    return pq, oracle, torch
+
+
+class _Variant:
+    def __init__(self, pq, variant):
+        self.pq, self.variant = pq, variant
+
+    def __enter__(self):
+        self.pq.set_option("assign_kernel", 2)
+        self.pq.set_option("scan_variant", self.variant)
+
+    def __exit__(self, *exc):
+        self.pq.set_option("assign_kernel", 0)
+        self.pq.set_option("scan_variant", 0)
+
+
+def _check(env, codes, centers, tables, variant, offset=0):
+    """offset: floats by which the tables are moved off their 16-byte alignment"""
+    pq, oracle, torch = env
+    N, M = codes.shape
+    buf = torch.empty(tables.size + offset, dtype=torch.float32, device="cuda")
+    t = buf[offset:].view(tables.shape)
+    t.copy_(torch.from_numpy(tables))
+    a = torch.full((N,), -7, dtype=torch.int32, device="cuda")
+    d = torch.full((N,), float("nan"), dtype=torch.float32, device="cuda")
+    with _Variant(pq, variant):
+        pq.assign(torch.from_numpy(codes).cuda(), torch.from_numpy(centers).cuda(), t, assign=a, dist=d)
+    ra, rd = oracle.assign(codes, centers, tables)
+    np.testing.assert_array_equal(a.cpu().numpy(), ra)
+    np.testing.assert_array_equal(d.cpu().numpy().view(np.uint32), rd.view(np.uint32))
+
+
+def _metric_tables(rng, M):
+    cw = rng.standard_normal((M, 256, 6)).astype(np.float32)
+    return np.ascontiguousarray(((cw[:, :, None] - cw[:, None]) ** 2).sum(3, dtype=np.float32))
+
+
+@pytest.mark.parametrize("M,variant", ALL)
+@pytest.mark.parametrize("N,K", [(1, 1), (7, 64), (33, 63), (2047, 65), (2048, 128), (4097, 129), (20011, 640), (8191, 2000)])
+def test_edges(env, M, variant, N, K):
+    rng = np.random.default_rng(N + K + M)
+    centers = rng.integers(0, 256, (K, M), dtype=np.uint8)
+    near = centers[rng.integers(0, K, N)]
+    codes = np.where(rng.random((N, M)) < 0.3, rng.integers(0, 256, (N, M)), near).astype(np.uint8)
+    _check(env, codes, centers, _metric_tables(rng, M), variant, offset=N % 2)
+    _check(env, codes, centers, rand_tables(rng, M), variant)                    # non-symmetric, no zero diagonal
+
+
+def _special_tables(rng, M, kind):
+    t = _metric_tables(rng, M)
+    if kind == "constant":
+        t[:] = 2.5
+    elif kind == "zero":
+        t[:] = 0.0
+    elif kind == "signed zeros":
+        t[:] = np.where(rng.random(t.shape) < 0.5, np.float32(0.0), np.float32(-0.0))
+    elif kind == "hamming":
+        t[:] = 1.0
+        t[:, np.arange(256), np.arange(256)] = 0.0
+    elif kind == "negative":
+        t -= 40.0
+    elif kind == "offset":
+        t += np.float32(3e5)                       # spread far below the entries: sums tie by rounding
+    elif kind == "outlier":
+        t[0, 3, 5] = 1e30
+        t[1, 7, 7] = -1e25
+    elif kind == "huge":
+        t *= np.float32(1e37)
+    elif kind == "tiny":
+        t *= np.float32(1e-42)
+    elif kind == "non-finite":
+        t[rng.random(t.shape) < 0.02] = np.nan
+        t[rng.random(t.shape) < 0.02] = np.inf
+    elif kind == "minus inf":
+        t[rng.random(t.shape) < 0.001] = -np.inf
+    elif kind == "nothing selected":
+        t[0] = np.nan
+        t[1] = np.inf
+    return t
+
+
+KINDS = ["constant", "zero", "signed zeros", "hamming", "negative", "offset", "outlier", "huge", "tiny", "non-finite", "minus inf",
+         "nothing selected"]
+
+
+@pytest.mark.parametrize("M,variant", [(M, v) for M, v in ALL if v % 20 in (1, 4)])
+@pytest.mark.parametrize("kind", KINDS)
+def test_special_tables(env, M, variant, kind):
+    rng = np.random.default_rng(len(kind) + M)
+    N, K = 3001, 700
+    centers = rng.integers(0, 40, (K, M), dtype=np.uint8)            # many equal centers
+    codes = rng.integers(0, 40, (N, M), dtype=np.uint8)
+    with np.errstate(all="ignore"):
+        _check(env, codes, centers, _special_tables(rng, M, kind), variant)
+
+
+@pytest.mark.parametrize("M,variant", [(M, v) for M, v in ALL if v % 20 in (0, 4)])
+@pytest.mark.parametrize("N,K,kind", [(30_011, 300, "metric"), (5003, 90, "hamming"), (5003, 90, "non-finite"), (9001, 400, "offset"),
+                                      (3001, 200, "constant")])
+def test_iterations(env, M, variant, N, K, kind):
+    """Each iteration starts from the center of the one before; empty clusters, unchanged and changed centers among them."""
+    pq, oracle, torch = env
+    rng = np.random.default_rng(N + K)
+    T = rng.integers(0, 256, (2 * K, M), dtype=np.uint8)
+    codes = np.where(rng.random((N, M)) < 0.25, rng.integers(0, 256, (N, M)), T[rng.integers(0, 2 * K, N)]).astype(np.uint8)
+    centers = codes[rng.integers(0, N, K)].copy()
+    centers[K // 2] = centers[0]                                      # a center that stays empty
+    with np.errstate(all="ignore"):
+        tables = _metric_tables(rng, M) if kind == "metric" else _special_tables(rng, M, kind)
+    d = dict(codes=torch.from_numpy(codes).cuda(), tables=torch.from_numpy(tables).cuda())
+    for iters in (1, 2, 5):
+        progress(f"lower-bound scan, {iters} iterations: M={M} variant={variant} N={N} K={K} {kind}")
+        hist = torch.empty((K, M, 256), dtype=torch.int32, device="cuda")
+        counts = torch.empty((K,), dtype=torch.int32, device="cuda")
+        cent = torch.from_numpy(centers).cuda()
+        with _Variant(pq, variant), np.errstate(all="ignore"):
+            _, a = pq.fit(d["codes"], d["tables"], cent, iters, hist=hist, counts=counts)
+        rc, ra, rh, rcnt = oracle.fit(codes, tables, centers, iters)
+        np.testing.assert_array_equal(a.cpu().numpy(), ra)
+        np.testing.assert_array_equal(u32(hist), rh)
+        np.testing.assert_array_equal(u32(counts), rcnt)
+        np.testing.assert_array_equal(cent.cpu().numpy(), rc)
+
+
+@pytest.mark.parametrize("M,variant", [(M, v) for M, v in ALL if v % 20 == 4])
+def test_launch_stretches(env, M, variant):
+    """Several scan launches and rounds: keys by position serve one launch at a time, the bound then comes from assign[]."""
+    pq, oracle, torch = env
+    rng = np.random.default_rng(9)
+    N, K = 70_003, 200
+    centers = rng.integers(0, 256, (K, M), dtype=np.uint8)
+    codes = np.where(rng.random((N, M)) < 0.3, rng.integers(0, 256, (N, M)), centers[rng.integers(0, K, N)]).astype(np.uint8)
+    tables = _metric_tables(rng, M)
+    rc, ra, _, _ = oracle.fit(codes, tables, centers, 3)
+    try:
+        pq.set_option("launch_codes_log2", 14)
+        for forced in (0, 3):
+            pq.set_option("hist_kernel", forced)
+            cent = torch.from_numpy(centers).cuda()
+            with _Variant(pq, variant):
+                _, a = pq.fit(torch.from_numpy(codes).cuda(), torch.from_numpy(tables).cuda(), cent, 3)
+            np.testing.assert_array_equal(a.cpu().numpy(), ra)
+            np.testing.assert_array_equal(cent.cpu().numpy(), rc)
+    finally:
+        pq.set_option("launch_codes_log2", 26)
+        pq.set_option("hist_kernel", 0)
