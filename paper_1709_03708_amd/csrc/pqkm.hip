@@ -1172,16 +1172,68 @@ pqkm_status assign_tiled(const uint8_t* codes, int64_t N, const uint8_t* centers
     return PQKM_OK;
 }
 
+// Scan with one lane per center: from this many centers on the table rows of a block's codes are copied to LDS first
+// (measured, M = 4, per code: 0.64 ns without and 1.05 ns with the copies at K = 100, 4.4 and 1.5 ns at K = 1000)
+constexpr int GATHER_ROWS_MIN_K = 160;
+
+// Most codes for which it is faster than the tiled scans (M = 4, 8, 16, 32), whose time does not depend on N below one
+// round of their smallest workgroups: at M = 4 10 us + 74 ns K against 10 us + N (0.96 ns + 0.00062 ns K), equal at
+// 47000 codes for K = 1000 and 100000 for K = 8000, later for larger M; without rows equal at about 18000 codes.
+int64_t gather_max_codes(int K)
+{
+    return K < GATHER_ROWS_MIN_K ? 16384 : (int64_t)120000 * K / (1550 + (int64_t)K);
+}
+
+template <int MW, int CN>
+pqkm_status launch_gather(const uint8_t* codes, int64_t N, int M, const uint8_t* centers, int K, const float* tables,
+                          int32_t* assign, float* dist, NearRecord* part, size_t room, hipStream_t st)
+{
+    const int64_t per_launch = (int64_t)CN << 23;                  // 2^31 threads
+    for (int64_t n0 = 0; n0 < N; n0 += per_launch) {
+        const int64_t cnt = N - n0 < per_launch ? N - n0 : per_launch;
+        const int64_t blocks = (cnt + CN - 1) / CN;
+        // about eight blocks per compute unit, as long as each keeps 256 centers and the records fit their room
+        int64_t splits = 8 * (int64_t)cu_count() / blocks;
+        if (splits > ((int64_t)K + 255) / 256) splits = ((int64_t)K + 255) / 256;
+        if (splits > (int64_t)(room / sizeof(NearRecord)) / cnt) splits = (int64_t)(room / sizeof(NearRecord)) / cnt;
+        int per = K;
+        if (splits > 1) {
+            per = (int)((((int64_t)K + splits - 1) / splits + 255) / 256 * 256);
+            splits = ((int64_t)K + per - 1) / per;
+        }
+        if (splits < 1) splits = 1;
+        float* dn = dist ? dist + n0 : nullptr;
+        NearRecord* pn = splits > 1 ? part : nullptr;
+        const dim3 grid((unsigned)blocks, (unsigned)splits);
+        if (K >= GATHER_ROWS_MIN_K)
+            hipLaunchKernelGGL((assign_gather_kernel<MW, CN, true>), grid, dim3(256), 0, st, codes + n0 * M, cnt, M, centers, K,
+                               tables, assign + n0, dn, pn, per);
+        else
+            hipLaunchKernelGGL((assign_gather_kernel<MW, CN, false>), grid, dim3(256), 0, st, codes + n0 * M, cnt, M, centers, K,
+                               tables, assign + n0, dn, pn, per);
+        if (splits > 1)
+            hipLaunchKernelGGL(assign_merge_kernel, dim3((unsigned)((cnt + 3) / 4)), dim3(256), 0, st, pn, cnt, (int)splits,
+                               assign + n0, dn);
+    }
+    return launched();
+}
+
 pqkm_status assign_core(const Options& opt, const Carve& c, const uint8_t* codes, int64_t N, int M,
                         const uint8_t* centers, int K, const float* tables, int32_t* assign, float* dist, void* ws,
                         hipStream_t st, int iteration, BucketLink* link)
 {
     bool tiled = tiled_M(M) && opt.assign_kernel != 1 && ((uintptr_t)codes & 3) == 0;
     if (opt.assign_kernel == 2 && !tiled) return PQKM_ERR_SHAPE;
-    if (!tiled) {
-        hipLaunchKernelGGL(assign_generic_kernel, dim3((unsigned)((N + 255) / 256)), dim3(256), 0, st, codes, N, M,
-                           centers, K, tables, assign, dist);
-        return launched();
+    const bool few = opt.assign_kernel == 0 && opt.scan_variant == 0 && N <= gather_max_codes(K);
+    if (!tiled || few) {
+        const bool words = tiled_M(M) && (((uintptr_t)codes | (uintptr_t)centers) & 3) == 0;
+        NearRecord* part = tiled_M(M) ? reinterpret_cast<NearRecord*>(static_cast<char*>(ws) + c.img_off) : nullptr;
+        const size_t room = tiled_M(M) ? c.img_bytes : 0;
+        if (words && M == 4) return launch_gather<1, 8>(codes, N, M, centers, K, tables, assign, dist, part, room, st);
+        if (words && M == 8) return launch_gather<2, 4>(codes, N, M, centers, K, tables, assign, dist, part, room, st);
+        if (words && M == 16) return launch_gather<4, 2>(codes, N, M, centers, K, tables, assign, dist, part, room, st);
+        if (words && M == 32) return launch_gather<8, 1>(codes, N, M, centers, K, tables, assign, dist, part, room, st);
+        return launch_gather<0, 1>(codes, N, M, centers, K, tables, assign, dist, part, room, st);
     }
     float* img = reinterpret_cast<float*>(static_cast<char*>(ws) + c.img_off);
     char* wsc = static_cast<char*>(ws);

@@ -336,33 +336,152 @@ __global__ __launch_bounds__(256) void decode_element_kernel(const uint8_t* __re
 }
 
 // ---------------------------------------------------------------------------------------------
-// Generic assignment (any M): one lane per code, centers read wave-uniformly, table entries
-// gathered through the cache hierarchy.  Eq. 5 exactly as written: ascending k, strict <.
+// Assignment one lane per center (any M, any alignment; Eq. 5 as written): a block takes CN codes, copies their CN * M
+// table rows of 1 KB into LDS and walks over the centers, one lane per center, whose subcodes are the offsets of the
+// look-ups in every row: one four-byte LDS read and one add per look-up.  Needs no tile images and no regrouping, and
+// a handful of codes fills the chip: the fastest of the scans for few codes (bound by the bank conflicts of random
+// four-byte reads, the tiled scans by the tiles that too few workgroups walk one after the other), and for subspace counts
+// without a tiled scan the only one.  A lane sees its centers in ascending order and keeps the first minimum; lanes merge by
+// (distance, index).  With few blocks the centers are split over gridDim.y blocks, which leave (distance, index) records
+// for assign_merge_kernel.  MW = M / 4 with codes and centers read as words, or 0: any M, byte by byte.  With few centers
+// the copies of whole rows would cost more than the look-ups (ROWS false): those then go through the caches, a wave's 64
+// into the 8 lines of one row.
+// Measured, skewed tiled scan -> this, M = 4: 48 codes, K = 1000: 87 -> 13 us; 1e4 codes: 88 -> 23 us; 1e4 codes,
+// K = 8000: 610 -> 70 us; 1e4 codes, K = 100: 18 -> 12 us (17 us with rows).  M = 32, 1e4 codes, K = 1000: 676 -> 84 us.
 // ---------------------------------------------------------------------------------------------
-__global__ __launch_bounds__(256) void assign_generic_kernel(const uint8_t* __restrict__ codes, int64_t N, int M,
-                                                             const uint8_t* __restrict__ centers, int K,
-                                                             const float* __restrict__ tables,
-                                                             int32_t* __restrict__ assign, float* __restrict__ dist)
+struct NearRecord { float dist; int32_t index; };
+
+__device__ __forceinline__ void near_merge(float& s, int& k, float os, int ok)
 {
-    int64_t n = (int64_t)blockIdx.x * 256 + threadIdx.x;
-    if (n >= N) return;
-    const uint8_t* x = codes + n * M;
-    float best = INFINITY;
-    int bk = 0;
-    for (int k = 0; k < K; ++k) {
-        const uint8_t* mu = centers + (size_t)k * M;
-        float s = tables[((size_t)0 * L + x[0]) * L + mu[0]];
-        for (int m = 1; m < M; ++m) {
-            float a = tables[((size_t)m * L + x[m]) * L + mu[m]];
-            s = s + a;
+    if (os < s || (os == s && ok < k)) { s = os; k = ok; }
+}
+
+template <int MW, int CN, bool ROWS>
+__global__ __launch_bounds__(256) void assign_gather_kernel(const uint8_t* __restrict__ codes, int64_t N, int Mrt,
+                                                            const uint8_t* __restrict__ centers, int K,
+                                                            const float* __restrict__ tables,
+                                                            int32_t* __restrict__ assign, float* __restrict__ dist,
+                                                            NearRecord* __restrict__ part, int per)
+{
+    const int M = MW ? 4 * MW : Mrt;
+    __shared__ float row_s[ROWS ? (MW ? CN * 4 * MW : 64) * L : 1];
+    const int64_t n0 = (int64_t)blockIdx.x * CN;
+    const int k_begin = (int)blockIdx.y * per;
+    const int k_end = K - k_begin < per ? K : k_begin + per;
+    // row i * M + m: the entries of subspace m for the subcode of code i
+    if (ROWS && ((uintptr_t)tables & 15) == 0) {
+        for (int e = threadIdx.x; e < CN * M * (L / 4); e += 256) {
+            const int r = e / (L / 4), i = r / M, m = r % M;
+            const int64_t n = n0 + i < N ? n0 + i : N - 1;
+            const uint32_t x = codes[n * M + m];
+            reinterpret_cast<float4*>(row_s)[e] = reinterpret_cast<const float4*>(tables + ((size_t)m * L + x) * L)[e % (L / 4)];
         }
-        if (s < best) {
-            best = s;
-            bk = k;
+    } else if (ROWS) {
+        for (int e = threadIdx.x; e < CN * M * L; e += 256) {
+            const int r = e / L, i = r / M, m = r % M;
+            const int64_t n = n0 + i < N ? n0 + i : N - 1;
+            row_s[e] = tables[((size_t)m * L + codes[n * M + m]) * L + e % L];
         }
     }
-    assign[n] = bk;
-    if (dist) dist[n] = best;
+    if (ROWS) __syncthreads();
+    float best[CN];
+    int bk[CN];
+#pragma unroll
+    for (int i = 0; i < CN; ++i) { best[i] = INFINITY; bk[i] = IDX_NONE; }
+    for (int64_t k64 = k_begin + (int)threadIdx.x; k64 < k_end; k64 += 256) {
+        const int k = (int)k64;
+        float s[CN];
+        if (!ROWS) {
+            uint32_t c[MW ? MW : 1];
+#pragma unroll
+            for (int w = 0; w < MW; ++w) c[w] = reinterpret_cast<const uint32_t*>(centers)[(size_t)k * MW + w];
+#pragma unroll
+            for (int i = 0; i < CN; ++i) {
+                const int64_t n = n0 + i < N ? n0 + i : N - 1;                        // the same for all lanes
+                const uint8_t* x = codes + n * M;
+                float a[MW ? 4 * MW : 1];
+                if (MW) {
+#pragma unroll
+                    for (int m = 0; m < 4 * MW; ++m) {
+                        const uint32_t xm = (reinterpret_cast<const uint32_t*>(x)[m / 4] >> (8 * (m % 4))) & 255u;
+                        a[m] = tables[((size_t)m * L + xm) * L + ((c[m / 4] >> (8 * (m % 4))) & 255u)];
+                    }
+                    s[i] = a[0];
+#pragma unroll
+                    for (int m = 1; m < 4 * MW; ++m) s[i] = s[i] + a[m];
+                } else {
+                    const uint8_t* cb = centers + (size_t)k * M;
+                    s[i] = tables[(size_t)x[0] * L + cb[0]];
+#pragma unroll 4
+                    for (int m = 1; m < M; ++m) s[i] = s[i] + tables[((size_t)m * L + x[m]) * L + cb[m]];
+                }
+            }
+        } else if (MW) {
+            const float* at[MW ? 4 * MW : 1];
+#pragma unroll
+            for (int w = 0; w < MW; ++w) {
+                const uint32_t c = reinterpret_cast<const uint32_t*>(centers)[(size_t)k * MW + w];
+                at[4 * w] = row_s + (c & 255u);
+                at[4 * w + 1] = row_s + ((c >> 8) & 255u);
+                at[4 * w + 2] = row_s + ((c >> 16) & 255u);
+                at[4 * w + 3] = row_s + (c >> 24);
+            }
+#pragma unroll
+            for (int m = 0; m < 4 * MW; ++m)
+#pragma unroll
+                for (int i = 0; i < CN; ++i) {
+                    const float a = at[m][(i * 4 * MW + m) * L];
+                    s[i] = m == 0 ? a : s[i] + a;
+                }
+        } else {
+            const uint8_t* c = centers + (size_t)k * M;
+            s[0] = row_s[c[0]];
+#pragma unroll 4
+            for (int m = 1; m < M; ++m) s[0] = s[0] + row_s[m * L + c[m]];
+        }
+#pragma unroll
+        for (int i = 0; i < CN; ++i)
+            if (s[i] < best[i]) { best[i] = s[i]; bk[i] = k; }
+    }
+    static_assert(MW > 0 || CN == 1, "any M: one code");
+    __shared__ NearRecord rec[4][CN];
+#pragma unroll
+    for (int i = 0; i < CN; ++i) {
+#pragma unroll
+        for (int off = 32; off; off >>= 1) near_merge(best[i], bk[i], __shfl_xor(best[i], off), __shfl_xor(bk[i], off));
+        if ((threadIdx.x & 63) == 0) rec[threadIdx.x >> 6][i] = NearRecord{best[i], bk[i]};
+    }
+    __syncthreads();
+    if (threadIdx.x < CN && n0 + threadIdx.x < N) {
+        const int i = threadIdx.x;
+        float s = rec[0][i].dist;
+        int k = rec[0][i].index;
+        for (int w = 1; w < 4; ++w) near_merge(s, k, rec[w][i].dist, rec[w][i].index);
+        const int64_t n = n0 + i;
+        if (part) {
+            part[n * gridDim.y + blockIdx.y] = NearRecord{s, k};
+        } else {
+            assign[n] = k == IDX_NONE ? 0 : k;
+            if (dist) dist[n] = s;
+        }
+    }
+}
+
+// one wave per code: the records of its `splits` blocks
+__global__ __launch_bounds__(256) void assign_merge_kernel(const NearRecord* __restrict__ part, int64_t N, int splits,
+                                                           int32_t* __restrict__ assign, float* __restrict__ dist)
+{
+    const int64_t n = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
+    if (n >= N) return;
+    float s = INFINITY;
+    int k = IDX_NONE;
+    for (int i = threadIdx.x & 63; i < splits; i += 64) near_merge(s, k, part[n * splits + i].dist, part[n * splits + i].index);
+#pragma unroll
+    for (int off = 32; off; off >>= 1) near_merge(s, k, __shfl_xor(s, off), __shfl_xor(k, off));
+    if ((threadIdx.x & 63) == 0) {
+        assign[n] = k == IDX_NONE ? 0 : k;
+        if (dist) dist[n] = s;
+    }
 }
 
 // ---------------------------------------------------------------------------------------------
