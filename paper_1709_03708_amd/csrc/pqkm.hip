@@ -989,6 +989,22 @@ inline bool variant_table_tiles(int M, int variant) { return M == 4 && variant >
 inline bool variant_lds_loads(int M, int variant) { return M == 4 && variant >= 85 && variant <= 89; }
 inline bool variant_sliding(int M, int variant) { return (M == 16 || M == 32) && variant >= 50 && variant <= 59; }
 
+// Histogram with all clusters of G subspaces in a workgroup's LDS (G = 0: not taken): about one workgroup per compute unit,
+// slices of at least 2048 codes, at most the 16 partial arrays the vote adds, in the room of the sorted path.
+struct SubspaceHist { int G, S; };
+SubspaceHist subspace_hist(int64_t N, int M, int K, const Carve& c)
+{
+    SubspaceHist p{0, 1};
+    // below 65536 codes the owner path's more, smaller workgroups are faster (1e4 codes, K = 100: 11 us against 13 us)
+    if (N < 65536 || N > (int64_t)0xffffffff || (int64_t)K * L > SUBSPACE_HIST_WORDS) return p;
+    p.G = 1;
+    while (p.G < 4 && p.G * 2 <= M && (int64_t)K * L * p.G * 2 <= SUBSPACE_HIST_WORDS) p.G *= 2;
+    const int64_t room = (int64_t)(c.seg_off - c.sidx_off) / (int64_t)align256(c.hist_bytes);
+    const int64_t groups = (M + p.G - 1) / p.G;
+    while (p.S < 16 && p.S * 2 <= room && groups * p.S * 2 <= cu_count() && N / (p.S * 2) >= 2048) p.S *= 2;
+    return p;
+}
+
 // The fused iteration's hand-over from the scan to the histogram: filled in by the caller (wanted, KT, ngroups),
 // completed by the assignment (produced, nwg) when the scan that ran could file its codes by cluster group.
 struct BucketLink {
@@ -1073,10 +1089,12 @@ pqkm_status assign_tiled(const uint8_t* codes, int64_t N, const uint8_t* centers
         const int64_t round = (int64_t)cu_count() * scan4h_codes_per_workgroup(variant);
         if (per_launch >= round) per_launch = per_launch / round * round - 32;
     }
+    const bool keys_survive = c.state_off != c.sidx_off || (owner_histogram(hist_plan(N, M, K), opt.hist_kernel) &&
+                                                            (opt.hist_kernel != 0 || subspace_hist(N, M, K, c).G == 0));
     // a later iteration starts from the center of the one before: by code position where the keys of one launch cover all
     // codes and nothing has used their room since, else through assign[]
     if (filter && reuse_groups)
-        fin.seeded = N <= per_launch && !plain_before && (c.state_off != c.sidx_off || owner_histogram(hist_plan(N, M, K), opt.hist_kernel)) ? 2 : 1;
+        fin.seeded = N <= per_launch && !plain_before && keys_survive ? 2 : 1;
     const float4* rows = reinterpret_cast<const float4*>(ws + c.rows_off);
     uint2* gco = reinterpret_cast<uint2*>(ws + c.gco_off);
     GroupPlan* plan = reinterpret_cast<GroupPlan*>(ws + c.plan_off);
@@ -1284,7 +1302,11 @@ void sort_by_cluster(const int32_t* assign, int64_t N, int K, const Carve& c, ch
     if (cb < 1) cb = 1;
     hipLaunchKernelGGL(seg_count_kernel, dim3(cb), dim3(1024), 0, st, assign, N, K, cnt);
     hipLaunchKernelGGL(seg_prefix_kernel, dim3(1), dim3(1024), 0, st, cnt, K, start, cursor);
-    hipLaunchKernelGGL(seg_scatter_kernel, dim3(sb), dim3(256), 0, st, assign, N, K, start, cursor, sidx);
+    if (K <= SEG_BLOCK_MAX_K)
+        hipLaunchKernelGGL(seg_scatter_block_kernel, dim3((unsigned)((N + SEG_BLOCK - 1) / SEG_BLOCK)), dim3(1024), 0, st, assign,
+                           N, K, start, cursor, sidx);
+    else
+        hipLaunchKernelGGL(seg_scatter_kernel, dim3(sb), dim3(256), 0, st, assign, N, K, start, cursor, sidx);
     *start_out = start;
     *sidx_out = sidx;
 }
@@ -1351,6 +1373,15 @@ pqkm_status update_impl(const Options& opt, const Carve& c, const uint8_t* codes
         else
             hipLaunchKernelGGL((histogram_bucket_kernel<HIST_LDS_WORDS>), dim3((unsigned)(hp.groups * S)), dim3(1024),
                                0, st, pool, bseg, link->nwg, K, hp.KT, S, parts, part_stride);
+    } else if (owner && force == 0 && subspace_hist(N, M, K, c).G > 0) {
+        const SubspaceHist sh = subspace_hist(N, M, K, c);
+        S = sh.S;
+        if (S > 1) {
+            parts = reinterpret_cast<uint32_t*>(static_cast<char*>(ws) + c.sidx_off);
+            part_stride = align256(c.hist_bytes) / sizeof(uint32_t);
+        }
+        hipLaunchKernelGGL(histogram_subspace_kernel, dim3((unsigned)((M + sh.G - 1) / sh.G * S)), dim3(1024), 0, st, codes, N, M,
+                           assign, K, sh.G, S, parts, part_stride);
     } else if (owner) {
         S = hp.S;
         if (S > 1) {
@@ -1373,8 +1404,16 @@ pqkm_status update_impl(const Options& opt, const Carve& c, const uint8_t* codes
         sort_by_cluster(assign, N, K, c, static_cast<char*>(ws), &start, &sidx, st, link && link->ranked);
         int KT = (HIST_LDS_WORDS / L) / M;
         if (KT > 128) KT = 128;
-        hipLaunchKernelGGL(seg_hist_kernel, dim3((unsigned)((K + KT - 1) / KT)), dim3(1024), 0, st, codes, M, start, sidx,
-                           K, KT, hist);
+        // groups of more than twice the average of codes are shared by several workgroups
+        const int64_t ng = ((int64_t)K + KT - 1) / KT;
+        const int64_t twice = 2 * ((N + ng - 1) / ng);
+        const uint32_t most = (uint32_t)(twice > 8192 ? (twice < 0x40000000 ? twice : 0x40000000) : 8192);
+        int64_t shares = (N + most - 1) / most;
+        if (shares > 32) shares = 32;
+        if (shares > 1)
+            hipLaunchKernelGGL(seg_zero_kernel, dim3((unsigned)ng), dim3(256), 0, st, start, M, K, KT, most, hist);
+        hipLaunchKernelGGL(seg_hist_kernel, dim3((unsigned)ng, (unsigned)shares), dim3(1024), 0, st, codes, M, start, sidx, K, KT,
+                           shares > 1 ? most : 0xffffffffu, hist);
     } else {
         zero_hist();
         const int64_t per = (int64_t)1 << 30;
@@ -1750,7 +1789,7 @@ pqkm_status pqkm_fit_until(const uint8_t* codes, int64_t N, int32_t M, const flo
         if (s != PQKM_OK) return s;
         hipLaunchKernelGGL(iter_hist_stats_kernel, dim3(STAT_BLOCKS), dim3(256), 0, st, hist, (int64_t)K * M * L,
                            counts, K, ph);
-        hipLaunchKernelGGL(iter_stats_final_kernel, dim3(1), dim3(64), 0, st, pa, ph, out);
+        hipLaunchKernelGGL(iter_stats_final_kernel, dim3(1), dim3(1024), 0, st, pa, ph, out);
         unsigned long long h[4];
         if (hipMemcpyAsync(h, out, sizeof(h), hipMemcpyDeviceToHost, st) != hipSuccess) return PQKM_ERR_DEVICE;
         if (hipStreamSynchronize(st) != hipSuccess) return PQKM_ERR_DEVICE;

@@ -3336,6 +3336,39 @@ __global__ __launch_bounds__(256) void seg_scatter_kernel(const int32_t* __restr
     }
 }
 
+// The same with one global atomic per (block, cluster) instead of one per code, which clusters of uneven size slow down by
+// their contention: a block ranks its SEG_BLOCK codes inside their clusters in LDS, reserves their places, and writes.
+// Measured, 2e6 codes of a mixture, K = 5000: 615 us -> 22 us.
+constexpr int SEG_BLOCK_PER = 16, SEG_BLOCK = 1024 * SEG_BLOCK_PER;
+constexpr int SEG_BLOCK_MAX_K = 32768;
+
+__global__ __launch_bounds__(1024) void seg_scatter_block_kernel(const int32_t* __restrict__ assign, int64_t N, int K,
+                                                                 const uint32_t* __restrict__ start,
+                                                                 uint32_t* __restrict__ cursor, uint32_t* __restrict__ sidx)
+{
+    __shared__ uint32_t h[SEG_BLOCK_MAX_K];
+    const int64_t n0 = (int64_t)blockIdx.x * SEG_BLOCK + threadIdx.x;
+    int k[SEG_BLOCK_PER];
+    uint32_t r[SEG_BLOCK_PER];
+#pragma unroll
+    for (int i = 0; i < SEG_BLOCK_PER; ++i) {
+        const int64_t n = n0 + i * 1024;
+        k[i] = n < N ? assign[n] : -1;
+    }
+    for (int i = threadIdx.x; i < K; i += 1024) h[i] = 0u;
+    __syncthreads();
+#pragma unroll
+    for (int i = 0; i < SEG_BLOCK_PER; ++i)
+        if ((unsigned)k[i] < (unsigned)K) r[i] = atomicAdd(&h[k[i]], 1u);
+    __syncthreads();
+    for (int i = threadIdx.x; i < K; i += 1024)
+        if (h[i]) h[i] = start[i] + atomicAdd(&cursor[i], h[i]);
+    __syncthreads();
+#pragma unroll
+    for (int i = 0; i < SEG_BLOCK_PER; ++i)
+        if ((unsigned)k[i] < (unsigned)K) sidx[h[k[i]] + r[i]] = (uint32_t)(n0 + i * 1024);
+}
+
 // the scatter when the scan has left every code's rank inside its cluster: no atomics, one pass
 __global__ __launch_bounds__(256) void seg_place_kernel(const int32_t* __restrict__ assign,
                                                         const uint32_t* __restrict__ rank, int64_t N, int K,
@@ -3347,10 +3380,29 @@ __global__ __launch_bounds__(256) void seg_place_kernel(const int32_t* __restric
     }
 }
 
-// workgroup b owns clusters b*KT .. b*KT+KT-1; LDS holds KT*M*256 counters (at most HIST_LDS_WORDS)
+// Workgroup (b, p) owns clusters b*KT .. b*KT+KT-1; LDS holds KT*M*256 counters (at most HIST_LDS_WORDS).  Clusters are of
+// uneven size, and one workgroup with ten times the average of codes would be what the step takes: a group of more than
+// `most` codes is shared by up to gridDim.y workgroups, which add their counters to the result that seg_zero_kernel
+// cleared; any other group has one, which stores them.  Measured, 2e6 codes of a mixture, M = 8, K = 5000: 450 us -> 114 us.
+__device__ __forceinline__ uint32_t seg_shares(uint32_t codes, uint32_t most, uint32_t at_most)
+{
+    const uint32_t p = (codes + most - 1) / most;
+    return p < 1u ? 1u : p < at_most ? p : at_most;
+}
+
+__global__ __launch_bounds__(256) void seg_zero_kernel(const uint32_t* __restrict__ start, int M, int K, int KT, uint32_t most,
+                                                       uint32_t* __restrict__ hist)
+{
+    const int k0 = blockIdx.x * KT;
+    const int nk = K - k0 < KT ? K - k0 : KT;
+    if (start[k0 + nk] - start[k0] <= most) return;
+    uint32_t* out = hist + (size_t)k0 * M * L;
+    for (int i = threadIdx.x; i < nk * M * L; i += 256) out[i] = 0u;
+}
+
 __global__ __launch_bounds__(1024) void seg_hist_kernel(const uint8_t* __restrict__ codes, int M,
                                                         const uint32_t* __restrict__ start,
-                                                        const uint32_t* __restrict__ sidx, int K, int KT,
+                                                        const uint32_t* __restrict__ sidx, int K, int KT, uint32_t most,
                                                         uint32_t* __restrict__ hist)
 {
     __shared__ uint32_t lh[32768];
@@ -3359,34 +3411,108 @@ __global__ __launch_bounds__(1024) void seg_hist_kernel(const uint8_t* __restric
     const int k0 = blockIdx.x * KT;
     const int nk = K - k0 < KT ? K - k0 : KT;
     const int words = nk * M * L;
+    const uint32_t first = start[k0], last = start[k0 + nk];
+    const uint32_t shares = seg_shares(last - first, most, gridDim.y);
+    if (blockIdx.y >= shares) return;
     for (int i = tid; i < words; i += 1024) lh[i] = 0u;
     for (int i = tid; i <= nk; i += 1024) st[i] = start[k0 + i];
     __syncthreads();
-    const uint32_t p0 = st[0], p1 = st[nk];
+    const uint32_t share = (last - first + shares - 1) / shares;
+    const uint32_t p0 = first + blockIdx.y * share;
+    const uint32_t p1 = last - p0 < share ? last : p0 + share;
     const bool wordwise = (M & 3) == 0 && ((uintptr_t)codes & 3) == 0;
-    for (uint32_t p = p0 + tid; p < p1; p += 1024) {
-        // the cluster of position p: the last kk with st[kk] <= p
-        int kk = 0;
-        for (int step = 64; step >= 1; step >>= 1)
-            if (kk + step < nk && st[kk + step] <= p) kk += step;
-        const uint8_t* x = codes + (size_t)sidx[p] * M;
-        uint32_t* h = lh + kk * M * L;
-        if (wordwise) {
-            const uint32_t* xw = reinterpret_cast<const uint32_t*>(x);
-            for (int w = 0; w < M / 4; ++w) {
-                const uint32_t v = xw[w];
-                atomicAdd(&h[(4 * w + 0) * L + (v & 255u)], 1u);
-                atomicAdd(&h[(4 * w + 1) * L + ((v >> 8) & 255u)], 1u);
-                atomicAdd(&h[(4 * w + 2) * L + ((v >> 16) & 255u)], 1u);
-                atomicAdd(&h[(4 * w + 3) * L + (v >> 24)], 1u);
+    constexpr int PER = 4;                        // positions per thread whose loads travel together
+    for (uint64_t pb = (uint64_t)p0 + tid; pb < p1; pb += 1024 * PER) {
+        uint32_t n[PER];
+#pragma unroll
+        for (int i = 0; i < PER; ++i) n[i] = pb + i * 1024 < p1 ? sidx[pb + i * 1024] : 0xffffffffu;
+#pragma unroll
+        for (int i = 0; i < PER; ++i) {
+            const uint64_t p = pb + i * 1024;
+            if (p >= p1) break;
+            // the cluster of position p: the last kk with st[kk] <= p
+            int kk = 0;
+            for (int step = 64; step >= 1; step >>= 1)
+                if (kk + step < nk && st[kk + step] <= p) kk += step;
+            const uint8_t* x = codes + (size_t)n[i] * M;
+            uint32_t* h = lh + kk * M * L;
+            if (wordwise) {
+                const uint32_t* xw = reinterpret_cast<const uint32_t*>(x);
+                for (int w = 0; w < M / 4; ++w) {
+                    const uint32_t v = xw[w];
+                    atomicAdd(&h[(4 * w + 0) * L + (v & 255u)], 1u);
+                    atomicAdd(&h[(4 * w + 1) * L + ((v >> 8) & 255u)], 1u);
+                    atomicAdd(&h[(4 * w + 2) * L + ((v >> 16) & 255u)], 1u);
+                    atomicAdd(&h[(4 * w + 3) * L + (v >> 24)], 1u);
+                }
+            } else {
+                for (int m = 0; m < M; ++m) atomicAdd(&h[m * L + x[m]], 1u);
             }
-        } else {
-            for (int m = 0; m < M; ++m) atomicAdd(&h[m * L + x[m]], 1u);
         }
     }
     __syncthreads();
     uint32_t* out = hist + (size_t)k0 * M * L;
-    for (int i = tid; i < words; i += 1024) out[i] = lh[i];
+    if (shares == 1)
+        for (int i = tid; i < words; i += 1024) out[i] = lh[i];
+    else
+        for (int i = tid; i < words; i += 1024)
+            if (lh[i]) atomicAdd(&out[i], lh[i]);
+}
+
+// ---------------------------------------------------------------------------------------------
+// Eq. 7, few centers: the histograms of `G` subspaces of ALL clusters fit a workgroup's LDS (K * G KB <= 128 KB), so
+// workgroup (g, s) takes subspaces g*G .. g*G+G-1 and slice s of the codes, reads assignment and subcodes of each code
+// once and counts.  No pass that names cluster groups, no search for members, and heavy clusters are spread over the
+// slices.  Slices of S > 1 leave partial arrays that the vote adds.  Measured, 1.28e6 codes, M = 4, K = 100: 84 us (the
+// owner path below with its group bytes) -> 31 us.
+// ---------------------------------------------------------------------------------------------
+constexpr int SUBSPACE_HIST_WORDS = 32768;
+
+__global__ __launch_bounds__(1024) void histogram_subspace_kernel(const uint8_t* __restrict__ codes, int64_t N, int M,
+                                                                  const int32_t* __restrict__ assign, int K, int G, int S,
+                                                                  uint32_t* __restrict__ parts, size_t part_stride)
+{
+    __shared__ uint32_t h[SUBSPACE_HIST_WORDS];          // [k][subspace of the group][256]
+    const int tid = threadIdx.x;
+    const int g = (int)blockIdx.x / S, s = (int)blockIdx.x % S;
+    const int m0 = g * G, nm = M - m0 < G ? M - m0 : G;
+    for (int i = tid; i < K * G * L; i += 1024) h[i] = 0u;
+    __syncthreads();
+    const int64_t per = ((N + S - 1) / S + 1023) / 1024 * 1024;
+    const int64_t n_end = (s + 1) * per < N ? (s + 1) * per : N;
+    constexpr int PER = 12;                              // codes per thread whose loads travel together, a batch ahead
+    const bool word = (M & 3) == 0 && ((uintptr_t)codes & 3) == 0 && (m0 & 3) + nm <= 4;
+    int k[PER], kn[PER];
+    uint32_t v[PER], vn[PER];
+    auto load = [&](int64_t nb) {
+#pragma unroll
+        for (int i = 0; i < PER; ++i) {
+            const int64_t n = nb + i * 1024;
+            kn[i] = n < n_end ? assign[n] : -1;
+            vn[i] = word && n < n_end ? reinterpret_cast<const uint32_t*>(codes)[n * (M / 4) + m0 / 4] : 0u;
+        }
+    };
+    load(s * per + tid);
+    for (int64_t nb = s * per + tid; nb < n_end; nb += 1024 * PER) {
+#pragma unroll
+        for (int i = 0; i < PER; ++i) { k[i] = kn[i]; v[i] = vn[i] >> (8 * (m0 & 3)); }
+        load(nb + 1024 * PER);
+#pragma unroll
+        for (int i = 0; i < PER; ++i) {
+            if ((unsigned)k[i] >= (unsigned)K) continue;
+            uint32_t* hk = h + (size_t)k[i] * G * L;
+            for (int m = 0; m < nm; ++m) {
+                const uint32_t x = word ? (v[i] >> (8 * m)) & 255u : codes[(nb + i * 1024) * M + m0 + m];
+                atomicAdd(&hk[m * L + x], 1u);
+            }
+        }
+    }
+    __syncthreads();
+    uint32_t* out = parts + (size_t)s * part_stride;
+    for (int i = tid; i < K * nm * L; i += 1024) {
+        const int k = i / (nm * L), e = i % (nm * L);
+        out[((size_t)k * M + m0) * L + e] = h[k * G * L + e];
+    }
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -3998,13 +4124,15 @@ __global__ __launch_bounds__(256) void iter_hist_stats_kernel(const uint32_t* __
 }
 
 // out[0] = objective (as double bits), out[1] = changed, out[2] = nonzero bins, out[3] = nonempty
-__global__ __launch_bounds__(64) void iter_stats_final_kernel(const StatPartial* __restrict__ pa,
+__global__ __launch_bounds__(1024) void iter_stats_final_kernel(const StatPartial* __restrict__ pa,
                                                               const StatPartial* __restrict__ ph,
                                                               unsigned long long* __restrict__ out)
 {
+    __shared__ double sd[16];
+    __shared__ unsigned long long sc[3][16];
     double d = 0.0;
     unsigned long long ch = 0, nz = 0, ne = 0;
-    for (int i = threadIdx.x; i < STAT_BLOCKS; i += 64) {
+    for (int i = threadIdx.x; i < STAT_BLOCKS; i += 1024) {
         d += pa[i].dsum;
         ch += pa[i].cnt_a;
         nz += ph[i].cnt_a;
@@ -4017,6 +4145,11 @@ __global__ __launch_bounds__(64) void iter_stats_final_kernel(const StatPartial*
         nz += __shfl_xor(nz, o);
         ne += __shfl_xor(ne, o);
     }
+    const int w = threadIdx.x >> 6;
+    if ((threadIdx.x & 63) == 0) { sd[w] = d; sc[0][w] = ch; sc[1][w] = nz; sc[2][w] = ne; }
+    __syncthreads();
+    if (threadIdx.x == 0)
+        for (int i = 1; i < 16; ++i) { d += sd[i]; ch += sc[0][i]; nz += sc[1][i]; ne += sc[2][i]; }
     if (threadIdx.x == 0) {
         out[0] = (unsigned long long)__double_as_longlong(d);
         out[1] = ch;
