@@ -191,7 +191,7 @@ Carve carve(int64_t N, int M, int K)
     // keys of the lower-bound scans (8 bytes per code position of a launch): they live only while a scan runs.  Where the
     // histogram of a fused iteration takes the owner path no ranks are handed over, and the keys share the room of the
     // sorted path (the at most 30 padding positions reach into the cluster sizes, which are written after the scan).
-    if (M == 4) {
+    if (M == 4 || M == 8) {
         if (hp.cheap && N <= GROUP_CHUNK_MAX) {
             c.state_off = c.sidx_off;
         } else {
@@ -641,11 +641,11 @@ int choose_scan4_large(int64_t n)
 
 // M = 4 scan through lower bounds (variants 60..64): codes per workgroup 512 R
 // Fewest centers, by iteration of a call.  What a code costs beside the scan of its tiles is candidates, four table lines
-// through the L2 each: about ten in the first iteration, less from the bound that the center of the iteration before
-// gives, less still once most centers no longer change.  Measured at N = 1e6 against the plain scans, ms per iteration:
-// first 0.30 / 0.26 at K = 1000, 0.35 / 0.32 at 1500; second and third 0.235 / 0.221 and 0.287 / 0.306; later
-// 0.148 / 0.149 at K = 500, 0.174 / 0.216 at 1000.  N = 3e6, K = 2500: 1.06 / 1.25, 0.90 / 1.26, 0.75 / 1.26.
-inline int filter4_min_k(int iteration) { return iteration == 0 ? 1700 : iteration < 3 ? 1200 : 600; }
+// through the L2 each: several in the first iteration, less from the bound that the center of the iteration before gives,
+// less still once most centers no longer change.  Measured against the plain scans, ms per iteration, N = 1e6: first
+// 0.28 / 0.24 at K = 1000, 0.337 / 0.313 at 1500; second and third 0.181 / 0.180 at K = 700, 0.202 / 0.220 at 1000;
+// later 0.132 / 0.172 at K = 700.  N = 3e6, K = 2500: 1.02 / 1.27, 0.84 / 1.26, 0.69 / 1.26.
+inline int filter4_min_k(int iteration) { return iteration == 0 ? 1800 : iteration < 3 ? 900 : 500; }
 int filter4_codes_per_slot(int variant, int64_t n_alloc)
 {
     switch (variant) {
@@ -661,25 +661,26 @@ int filter4_codes_per_slot(int variant, int64_t n_alloc)
     double best_cost = 1e300;
     for (int R : cand) {
         const int64_t wgs = (n_alloc + 512 * R - 1) / (512 * R);
-        const double cost = (double)((wgs + ncu - 1) / ncu) * (R + 1.0);
+        // measured at K = 1e5 per round: 7.6, 5.9, 4.1 ms for R = 16, 12, 8
+        const double cost = (double)((wgs + ncu - 1) / ncu) * (R + 1.4);
         if (cost < best_cost) { best_cost = cost; best = R; }
     }
     return best;
 }
 
-template <int R>
-void launch_filter4_rounds(const uint2* gco, int64_t n_alloc, FilterIn f, int32_t* assign, float* dist, hipStream_t st,
+template <int M, int R, int THREADS = 1024, int DEPTH = 3>
+void launch_filter_rounds(const typename FilterCode<M>::Raw* gco, int64_t n_alloc, FilterIn f, int32_t* assign, float* dist, hipStream_t st,
                            RankOut ro, int rounds_per_launch)
 {
     // one kernel launch per rounds_per_launch rounds of workgroups (see launch_scan4q_rounds)
-    constexpr int64_t C = 512 * (int64_t)R;
+    constexpr int64_t C = THREADS / 2 * (int64_t)R;
     const int64_t nwg = (n_alloc + C - 1) / C;
     const int64_t per = rounds_per_launch > 0 ? (int64_t)rounds_per_launch * cu_count() : nwg;
     unsigned long long* state = f.state;
     for (int64_t w0 = 0; w0 < nwg; w0 += per) {
         const int64_t cnt = nwg - w0 < per ? nwg - w0 : per;
         f.state = state + w0 * C;
-        hipLaunchKernelGGL((assign_filter4_kernel<R, false>), dim3((unsigned)cnt), dim3(1024), 0, st, n_alloc - w0 * C,
+        hipLaunchKernelGGL((assign_filter_kernel<M, R, THREADS, DEPTH, false>), dim3((unsigned)cnt), dim3(THREADS), 0, st, n_alloc - w0 * C,
                            gco + w0 * C, f, assign, dist, ro, BucketOut{});
         ++t_scan_kernels;
     }
@@ -689,10 +690,46 @@ void launch_filter4(int variant, const uint2* gco, int64_t n_alloc, const Filter
                     hipStream_t st, RankOut ro, int rounds_per_launch)
 {
     switch (filter4_codes_per_slot(variant, n_alloc)) {
-        case 4: launch_filter4_rounds<4>(gco, n_alloc, f, assign, dist, st, ro, rounds_per_launch); break;
-        case 8: launch_filter4_rounds<8>(gco, n_alloc, f, assign, dist, st, ro, rounds_per_launch); break;
-        case 12: launch_filter4_rounds<12>(gco, n_alloc, f, assign, dist, st, ro, rounds_per_launch); break;
-        default: launch_filter4_rounds<16>(gco, n_alloc, f, assign, dist, st, ro, rounds_per_launch); break;
+        case 4: launch_filter_rounds<4, 4>(gco, n_alloc, f, assign, dist, st, ro, rounds_per_launch); break;
+        case 8: launch_filter_rounds<4, 8>(gco, n_alloc, f, assign, dist, st, ro, rounds_per_launch); break;
+        case 12: launch_filter_rounds<4, 12>(gco, n_alloc, f, assign, dist, st, ro, rounds_per_launch); break;
+        default: launch_filter_rounds<4, 16>(gco, n_alloc, f, assign, dist, st, ro, rounds_per_launch); break;
+    }
+}
+
+// Centers from which the bound of a first iteration comes from the pair tables: K >= 400 leaves room for them (1 MB) behind
+// the byte tiles in either case
+constexpr int FILTER_PAIRS_MIN_K = 500;
+// the same for M = 8, N = 4.2e6: first 4.2 / 4.1 at K = 1500, 5.8 / 7.3 at 4000; second and third 1.53 / 1.35 at K = 600,
+// 1.94 / 2.64 at 1500; later 0.93 / 1.35 at K = 600
+inline int filter8_min_k(int iteration) { return iteration == 0 ? 1800 : iteration < 3 ? 900 : 500; }
+
+// M = 8 (variants 60..63): codes per workgroup 256 R, 512 threads (with 1024 and half the registers the loop spills)
+int filter8_codes_per_slot(int variant, int64_t n_alloc)
+{
+    if (variant == 61) return 24;
+    if (variant == 62) return 16;
+    if (variant == 63) return 8;
+    const int ncu = cu_count();
+    static const int cand[] = {24, 16, 8};
+    int best = 24;
+    double best_cost = 1e300;
+    for (int R : cand) {
+        const int64_t wgs = (n_alloc + 256 * R - 1) / (256 * R);
+        // measured at K = 1e4 per round: 1.67, 1.23, 0.77 ms for R = 24, 16, 8
+        const double cost = (double)((wgs + ncu - 1) / ncu) * (R + 6.4);
+        if (cost < best_cost) { best_cost = cost; best = R; }
+    }
+    return best;
+}
+
+void launch_filter8(int variant, const uint4* gc8, int64_t n_alloc, const FilterIn& f, int32_t* assign, float* dist,
+                    hipStream_t st, RankOut ro, int rounds_per_launch)
+{
+    switch (filter8_codes_per_slot(variant, n_alloc)) {
+        case 8: launch_filter_rounds<8, 8, 512, 4>(gc8, n_alloc, f, assign, dist, st, ro, rounds_per_launch); break;
+        case 16: launch_filter_rounds<8, 16, 512, 4>(gc8, n_alloc, f, assign, dist, st, ro, rounds_per_launch); break;
+        default: launch_filter_rounds<8, 24, 512, 4>(gc8, n_alloc, f, assign, dist, st, ro, rounds_per_launch); break;
     }
 }
 
@@ -702,7 +739,7 @@ void launch_filter4_bucket(const uint2* gco, int64_t n_alloc, const FilterIn& f,
 {
     constexpr int64_t C = 512 * 8;
     const int64_t nwg = (n_alloc + C - 1) / C;
-    hipLaunchKernelGGL((assign_filter4_kernel<8, true>), dim3((unsigned)nwg), dim3(1024), 0, st, n_alloc, gco, f, assign,
+    hipLaunchKernelGGL((assign_filter_kernel<4, 8, 1024, 3, true>), dim3((unsigned)nwg), dim3(1024), 0, st, n_alloc, gco, f, assign,
                        dist, RankOut{}, bo);
     ++t_scan_kernels;
     *nwg_out = (int)nwg;
@@ -928,20 +965,24 @@ void launch_scan_M<32>(int variant, const uint8_t* codes, int64_t N, const float
 
 // Which scan runs: for M = 4 with the default variant, the regrouped half-plane scan when there is enough work
 // to pay for regrouping (a pass over the codes) and the subspace-skewed scan otherwise.
-inline int effective_variant(int M, int variant, int64_t N, int K, const uint8_t* codes)
+inline int effective_variant(int M, int variant, int64_t N, int K, const uint8_t* codes, const uint8_t* centers)
 {
     // the regrouped scans address the tile images through one 32-bit buffer offset: below 4 GB of images only
     const int TK = 128 / M;
     const bool img32 = (int64_t)((K + TK - 1) / TK) * TILE_BYTES < (int64_t)0xfff00000;
     const bool special = (variant >= 40 && variant <= 49) || (variant >= 70 && variant <= 79) ||
-                         (M == 4 && variant >= 60 && variant <= 64) || (M == 4 && variant >= 80 && variant <= 99) || (M == 8 && variant >= 80 && variant <= 84);
+                         (M == 4 && variant >= 60 && variant <= 64) || (M == 8 && variant >= 60 && variant <= 63) || (M == 4 && variant >= 80 && variant <= 99) || (M == 8 && variant >= 80 && variant <= 84);
     if (M == 8) {
         const bool ok8 = img32 && ((uintptr_t)codes & 7) == 0;
         if (special && !ok8) return 0;
         // 65536 residue classes: regrouping pays once most classes hold a few dozen codes; then two lanes per code
         // (an LDS access holds two groups of four codes, so the left-over groups cost it more than the four-lane scan
         // 70, but a tile fill serves twice the codes: 0.63 against 0.60 of the LDS peak at N = 1e7, K = 1e4)
-        if (variant == 0 && ok8 && K >= 256 && N >= ((int64_t)1 << 22)) return choose_scan8_large(N, K);
+        // with enough centers for the lower-bound scan fewer codes pay for the regrouping as well (N = 1e6, K = 5000: 2.4 ms
+        // with it against 2.6 ms of the skewed scan in a first iteration, 0.9 ms in later ones)
+        if (variant == 0 && ok8 && ((K >= 256 && N >= ((int64_t)1 << 22)) ||
+                                    (K >= filter8_min_k(0) && N >= ((int64_t)1 << 19) && (double)N * K >= 6e9 && ((uintptr_t)centers & 3) == 0)))
+            return choose_scan8_large(N, K);
         if (variant == 0) {
             // skewed scan: while one round of workgroups covers the codes, the smallest shape that does so (measured
             // per round at K = 1000: 139, 172, 220, 263 us for 512, 1024, 1536, 2048 codes per workgroup)
@@ -974,7 +1015,10 @@ inline int effective_variant(int M, int variant, int64_t N, int K, const uint8_t
     }
     return 70;                            // regrouped half-plane scan, codes per lane-slot chosen per launch
 }
-inline bool variant_filter(int M, int variant) { return M == 4 && variant >= 60 && variant <= 64; }
+inline bool variant_filter(int M, int variant)
+{
+    return (M == 4 && variant >= 60 && variant <= 64) || (M == 8 && variant >= 60 && variant <= 63);
+}
 inline bool variant_grouped(int M, int variant)
 {
     return variant_filter(M, variant) || ((M == 4 || M == 8) && variant >= 70 && variant <= 79) || (M == 4 && variant >= 80 && variant <= 99) ||
@@ -1024,41 +1068,51 @@ pqkm_status assign_tiled(const uint8_t* codes, int64_t N, const uint8_t* centers
     constexpr int TK = 128 / M;
     int64_t ntiles = ((int64_t)K + TK - 1) / TK;
     int64_t total = ntiles * (int64_t)(TILE_BYTES / 4);
-    int variant = effective_variant(M, opt.scan_variant, N, K, codes);
+    int variant = effective_variant(M, opt.scan_variant, N, K, codes, centers);
     // No records to file for the histogram: the four-lane scan or the scan with two-lane slots whose tiles are loaded
     // straight into LDS, half a tile ahead, in the shape that the rounds favour
     // Records to file (the fused iteration at owner-path sizes): the same scan in its 4096-code shape, which files
     // them as the four-lane scan does.
     const bool files_records = M == 4 && link && link->wanted && N <= GROUP_CHUNK_MAX - 16384 && c.bseg_off != c.pool_off;
     // the lower-bound scan addresses its byte tiles through one 32-bit buffer offset and reads centers as words
-    const bool filter_ok = M == 4 && ((uintptr_t)centers & 3) == 0 && ((int64_t)K + 63) / 64 * 65536 < (int64_t)0xfff00000;
+    const bool filter_ok = (M == 4 || (M == 8 && K > 16)) && ((uintptr_t)centers & 3) == 0 && ((int64_t)K + 63) / 64 * (M * 16384) < (int64_t)0xfff00000;
     if (M == 4 && variant == 70 && opt.scan_variant == 0)
         variant = filter_ok && K >= filter4_min_k(iteration) ? (files_records ? 63 : 60)
                   : files_records ? 89 : choose_scan4_large(N);
     else if (variant_filter(M, variant) && !filter_ok)
-        variant = 85;
+        variant = M == 4 ? 85 : 80;
+    if (M == 8 && opt.scan_variant == 0 && variant_grouped(8, variant) && filter_ok && K >= filter8_min_k(iteration)) variant = 60;
     if (M == 4 && variant == 65) variant = files_records ? 89 : choose_scan4_large(N);      // the best of the plain scans
     const bool filter = variant_filter(M, variant);
     // the iteration before this one ran a plain scan: no statistics and no keys of it
-    const bool plain_before = iteration > 0 && opt.scan_variant == 0 && K < filter4_min_k(iteration - 1);
+    const bool plain_before = iteration > 0 && opt.scan_variant == 0 && K < (M == 4 ? filter4_min_k(iteration - 1) : filter8_min_k(iteration - 1));
     const int layout = variant_layout(M, variant);
     const bool sliding = variant_sliding(M, variant);
     FilterIn fin{};
     if (filter) {
-        FilterStat* stat = reinterpret_cast<FilterStat*>(ws + c.rows_off);
+        // (M = 8: behind the byte tiles, which take a quarter of the images' room)
+        char* const side = M == 4 ? ws + c.rows_off : ws + c.img_off + align256((size_t)((K + FILTER_TK - 1) / FILTER_TK) * M * FILTER_PLANE);
+        FilterStat* stat = reinterpret_cast<FilterStat*>(side);
         const int nt = (K + FILTER_TK - 1) / FILTER_TK;
         // statistics, the scale, then two copies of the centers (this iteration's, the one before) in the room of the
         // row-ordered images
         static_assert(M * FILTER_PARTS * sizeof(FilterStat) <= 4096, "statistics");
-        FilterScale* scale = reinterpret_cast<FilterScale*>(ws + c.rows_off + 4096);
-        uint8_t* copies = reinterpret_cast<uint8_t*>(ws + c.rows_off) + 4352;
+        FilterScale* scale = reinterpret_cast<FilterScale*>(side + 4096);
+        uint8_t* copies = reinterpret_cast<uint8_t*>(side) + 4352;
         const size_t copy_stride = align256((size_t)K * M);
+        uint32_t* pairs = reinterpret_cast<uint32_t*>(copies + 2 * copy_stride);     // at most 1 MB
         if (iteration == 0 || plain_before)
             hipLaunchKernelGGL(filter_stats_kernel, dim3(M * FILTER_PARTS), dim3(1024), 0, st, tables, stat);
         hipLaunchKernelGGL((filter_image_kernel<M>), dim3((unsigned)(nt * M * 4)), dim3(256), 0, st, centers, K, tables, stat,
                            reinterpret_cast<uint4*>(img), copies + (iteration & 1) * copy_stride, scale);
         fin = FilterIn{reinterpret_cast<const uint4*>(img), tables, centers, scale,
-                       reinterpret_cast<unsigned long long*>(ws + c.state_off), K, nt, copies + ((iteration & 1) ^ 1) * copy_stride, 0};
+                       reinterpret_cast<unsigned long long*>(ws + c.state_off), K, nt, copies + ((iteration & 1) ^ 1) * copy_stride,
+                       pairs, 0};
+        if (iteration == 0 && K >= FILTER_PAIRS_MIN_K) {
+            hipLaunchKernelGGL(fill_i32_kernel, dim3(256), dim3(256), 0, st, reinterpret_cast<int32_t*>(pairs), (int64_t)(M / 2) * 65536, (int32_t)-1);
+            hipLaunchKernelGGL((filter_pairs_kernel<M>), dim3((unsigned)((K + 255) / 256)), dim3(256), 0, st, centers, K, pairs);
+            fin.seeded = 3;
+        }
     } else if (sliding) {
         // tiles of 16 centers, plane-ordered: img[tile][m][x][16]
         ntiles = ((int64_t)K + 15) / 16;
@@ -1081,7 +1135,8 @@ pqkm_status assign_tiled(const uint8_t* codes, int64_t N, const uint8_t* centers
     // 64 full rounds of 4096-code workgroups, and that workgroup would run a round of its own
     if ((grouped || sliding) && per_launch > GROUP_CHUNK_MAX - 16384) per_launch = GROUP_CHUNK_MAX - 16384;
     if (filter) {
-        const int64_t round = (int64_t)cu_count() * 512 * filter4_codes_per_slot(variant, group_alloc(N));
+        const int64_t round = (int64_t)cu_count() *
+                              (M == 4 ? 512 * filter4_codes_per_slot(variant, group_alloc(N)) : 256 * filter8_codes_per_slot(variant, group_alloc(N)));
         if (per_launch >= round) per_launch = per_launch / round * round - 32;
     }
     if (variant_lds_loads(M, variant)) {
@@ -1146,7 +1201,10 @@ pqkm_status assign_tiled(const uint8_t* codes, int64_t N, const uint8_t* centers
                          link->ngroups};
             launch_filter4_bucket(gco, group_alloc(cnt), fin, assign + n0, dist ? dist + n0 : nullptr, st, bo, &link->nwg);
             link->produced = true;
-        } else if (filter)
+        } else if (filter && M == 8)
+            launch_filter8(variant, gc8, group_alloc(cnt), fin, assign + n0, dist ? dist + n0 : nullptr, st, rl,
+                           opt.rounds_per_launch);
+        else if (filter)
             launch_filter4(variant, gco, group_alloc(cnt), fin, assign + n0, dist ? dist + n0 : nullptr, st, rl,
                            opt.rounds_per_launch);
         else if (M == 8 && variant_two_lane(M, variant))

@@ -168,6 +168,21 @@ __global__ __launch_bounds__(256) void filter_image_kernel(const uint8_t* __rest
     img[((size_t)tile * M + m) * 1024 + part * 256 + threadIdx.x] = make_uint4(w[0], w[1], w[2], w[3]);
 }
 
+// For every pair of neighbouring subspaces and every pair of subcodes some center that has both (which one does not
+// matter): codes of clustered data nearly always share a pair with a center close to them.
+template <int M>
+__global__ __launch_bounds__(256) void filter_pairs_kernel(const uint8_t* __restrict__ centers, int K,
+                                                           uint32_t* __restrict__ pairs)
+{
+    const int k = blockIdx.x * 256 + threadIdx.x;
+    if (k >= K) return;
+#pragma unroll
+    for (int p = 0; p < M / 2; ++p) {
+        const uint32_t c = centers[(size_t)k * M + 2 * p] | ((uint32_t)centers[(size_t)k * M + 2 * p + 1] << 8);
+        pairs[(size_t)p * 65536 + c] = (uint32_t)k;
+    }
+}
+
 // (distance, center) as one integer whose order is "smaller distance, then lower index"; -0 counts as +0
 __device__ __forceinline__ unsigned long long filter_key(float s, uint32_t k)
 {
@@ -196,31 +211,65 @@ struct FilterIn {
     unsigned long long* state;       // one key per code position of the launch
     int K, ntiles;                   // ntiles = ceil(K / 64)
     const uint8_t* before;           // the centers of the iteration whose keys `state` holds (seeded == 2)
-    int seeded;                      // 1: assign[] holds a center for every code (of the iteration before); 2: so does `state`
+    const uint32_t* pairs;           // seeded == 3: [M / 2][65536], a center with these two subcodes, or >= K
+    int seeded;                      // 0: nothing known; 1: assign[] holds a center for every code (of the iteration before);
+                                     // 2: so does `state`; 3: `pairs` names candidates
 };
 
-// 4 subcodes of a code or center packed in a word
-__device__ __forceinline__ float filter_distance4(const float* __restrict__ tables, uint32_t x, uint32_t c)
+// a code of the regrouped array (M = 4: code, origin; M = 8: code, code, origin, -) and a center, packed in words
+template <int M> struct FilterCode;
+template <> struct FilterCode<4> {
+    typedef uint2 Raw;
+    uint32_t w[1], origin;
+    __device__ __forceinline__ explicit FilterCode(uint2 v) : w{v.x}, origin(v.y) {}
+    __device__ __forceinline__ FilterCode() {}
+};
+template <> struct FilterCode<8> {
+    typedef uint4 Raw;
+    uint32_t w[2], origin;
+    __device__ __forceinline__ explicit FilterCode(uint4 v) : w{v.x, v.y}, origin(v.z) {}
+    __device__ __forceinline__ FilterCode() {}
+};
+template <int W> struct FilterWords { uint32_t w[W]; };
+
+// the fp32 distance of Eq. 3
+template <int M>
+__device__ __forceinline__ float filter_distance(const float* __restrict__ tables, const uint32_t (&x)[M / 4],
+                                                 const FilterWords<M / 4>& c)
 {
-    const float a0 = tables[((x & 255u) << 8) | (c & 255u)];
-    const float a1 = tables[65536u + ((x & 0xff00u) | ((c >> 8) & 255u))];
-    const float a2 = tables[131072u + (((x >> 8) & 0xff00u) | ((c >> 16) & 255u))];
-    const float a3 = tables[196608u + (((x >> 16) & 0xff00u) | (c >> 24))];
-    return ((a0 + a1) + a2) + a3;
+    float a[M];
+#pragma unroll
+    for (int m = 0; m < M; ++m)
+        a[m] = tables[((uint32_t)m << 16) | (((x[m / 4] >> (8 * (m % 4))) & 255u) << 8) | ((c.w[m / 4] >> (8 * (m % 4))) & 255u)];
+    float s = a[0];
+#pragma unroll
+    for (int m = 1; m < M; ++m) s = s + a[m];
+    return s;
 }
 
 // ---------------------------------------------------------------------------------------------
-// M = 4: regrouped codes and two-lane slots of assign_scan4h_kernel, whose 64-byte rows of 16 fp32 centers are here rows
-// of 64 one-byte centers; the same conflict-free reads, the same half-ahead loads straight into LDS (a tile of 64
-// centers is 64 KB, two buffers).  Per code and tile a lane reads 2 x 16 bytes per subspace = 32 centers, and adds the
-// four bounds and 127 - threshold in every byte of a register (two three-operand adds; at most 4 * 31 + 128 = 252, no
-// byte carries into its neighbour): the high bit of a byte stays clear exactly when the center passes.  A code that
-// adds 128 passes nothing (the holes of the regrouped array).  The high bits of two codes are and'ed into one test per
-// wave; lanes with a clear one append (mask of 32 centers, code, tile) to a queue of their wave in LDS, and 64 entries are worked off
-// at a time, one lane each: subcodes of the center, four table entries through the L2, an atomic minimum of (distance,
-// index) on the code's key in global memory, the new threshold to LDS.  Thresholds are one byte per code in LDS, read 16
-// at a time when a tile begins.  Before the first tile every code needs a bound: the distance to its center of the
-// previous iteration, where there is one, else that to the center with the smallest sum of bounds in the first tile.
+// M = 4, 8: regrouped codes and two-lane slots of assign_scan4h_kernel and assign_scan8q_kernel, whose 64-byte rows of 16
+// fp32 centers are here rows of 64 one-byte centers, with the same conflict-free reads.  Per code and tile of 64 centers a
+// lane reads 2 x 16 bytes per subspace = 32 centers and adds the bounds of four centers per instruction (three-operand
+// adds; at most M * 31 = 248, no byte carries into its neighbour).  A byte per code holds what the sum must stay below:
+// M = 4 adds 127 - threshold (the sum of both is at most 252), M = 8 averages with 254 - threshold, rounding up
+// (v_lerp_u8); either way the high bit of a byte ends up clear exactly when the center passes.  128 or 255 in its place
+// lets nothing pass (the holes of the regrouped array).  The high bits of two codes are and'ed into one test per wave;
+// lanes with a clear one append (mask of 32 centers, code, tile) to a queue of their wave in LDS, and 64 entries are
+// worked off at a time, one lane each: subcodes of the center, M table entries through the L2, an atomic minimum of
+// (distance, index) on the code's key in global memory, the new threshold to LDS.  Thresholds are read four codes at a
+// time when a tile begins.  Before the first tile every code needs a bound: the distance to its center of the previous
+// iteration, where there is one; in a first iteration the distance to the closest of a few centers that share two neighbouring subcodes
+// with it, or else to the center with the smallest sum of bounds in the first tile.
+// A tile is 64 KB at M = 4: two buffers, the next tile's loads straight into LDS run beside the scan.  At M = 8 it is
+// 128 KB, one buffer, loaded between two barriers (about 3000 clocks for 14000 of scan with 4096 codes).
+//
+// Bound by vector issue and LDS reads together (a wave takes about 175 clocks of its SIMD per 32 codes and tile at
+// M = 4, of which the 8 reads are 64), and with few centers by the candidates: a table entry through the L2 costs a
+// compute unit about 5 clocks, a candidate M of them.
+// Measured, plain scan -> this: M = 4, N = 2e6, K = 1e5: 26.5 -> 8.7 ms (2.3e13 code-center pairs/s); N = 3e6,
+// K = 2500: 1.27 -> 1.05 ms in a first iteration, 0.69 ms in later ones.  M = 8, N = 1e7,
+// K = 1e4: 30.2 -> 18.0 ms in a first iteration, 13.0 and 11.5 ms in later ones.
 // ---------------------------------------------------------------------------------------------
 template <int V> struct IntC { static constexpr int value = V; };
 
@@ -231,15 +280,19 @@ __device__ __forceinline__ uint32_t pk_min_u16(uint32_t a, uint32_t b)
     return __builtin_bit_cast(uint32_t, __builtin_elementwise_min(__builtin_bit_cast(v2us, a), __builtin_bit_cast(v2us, b)));
 }
 
-template <int R, bool BUCKET>
-__global__ __launch_bounds__(1024) void assign_filter4_kernel(int64_t N, const uint2* __restrict__ gco, FilterIn f,
-                                                              int32_t* __restrict__ assign, float* __restrict__ dist,
-                                                              RankOut ro, BucketOut bo)
+template <int M, int R, int THREADS, int DEPTH, bool BUCKET>
+__global__ __launch_bounds__(THREADS) void assign_filter_kernel(int64_t N, const typename FilterCode<M>::Raw* __restrict__ gco,
+                                                             FilterIn f, int32_t* __restrict__ assign,
+                                                             float* __restrict__ dist, RankOut ro, BucketOut bo)
 {
-    constexpr int THREADS = 1024, SLOTS = 512, C = SLOTS * R, DEPTH = 3, TW = R / 4;
-    constexpr uint32_t ALL = 127u, DEAD = 128u;          // what passes everything; what is added for a hole
+    constexpr int SLOTS = THREADS / 2, C = SLOTS * R, TW = R / 4, W = M / 4;
+    constexpr int CHUNKS = (int)FILTER_PLANE / (THREADS * 16);              // loads per plane
+    constexpr int BUFFERS = M == 4 ? 2 : 1;
+    constexpr uint32_t STRIDE = BUFFERS * FILTER_PLANE;                     // bytes between two subspaces in LDS
+    constexpr uint32_t ALL = M == 4 ? 127u : 254u, DEAD = ALL + 1u;         // what passes everything; the byte of a hole
     constexpr uint32_t HI = 0x80808080u;
     static_assert(R % 4 == 0, "thresholds are read as words of four codes");
+    static_assert(M * FILTER_Q < 255, "a sum of bounds fits a byte");
     __shared__ float4 tile[TILE_F4];
     __shared__ uint32_t thr_s[SLOTS * TW];
     __shared__ uint2 queue_s[THREADS / 64][FILTER_QUEUE];
@@ -256,61 +309,89 @@ __global__ __launch_bounds__(1024) void assign_filter4_kernel(int64_t N, const u
     const uint32_t low15 = 0x7fffu;
     uint2* queue = queue_s[wave];
 
-    // tile t goes to buffer t & 1, plane m of buffer h at byte (2 m + h) * 16384
+    // plane m of buffer h at byte m * STRIDE + h * 16384
     const uint64_t ip = reinterpret_cast<uint64_t>(f.img);
-    const v4i rs_img = {(int)(uint32_t)ip, (int)(uint32_t)(ip >> 32), (int)((uint32_t)f.ntiles * 65536u), 0x00020000};
+    constexpr uint32_t TILE = M * FILTER_PLANE;
+    const v4i rs_img = {(int)(uint32_t)ip, (int)(uint32_t)(ip >> 32), (int)((uint32_t)f.ntiles * TILE), 0x00020000};
     const uint32_t lds0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) char*)tile;
     const uint32_t wave_off = (uint32_t)wave * 1024u, lane_off = (uint32_t)tid * 16u;
-    auto fetch = [&](int t, int h, int m) {
-        buffer_to_lds16(lds0 + (uint32_t)(2 * m + h) * FILTER_PLANE + wave_off, rs_img, lane_off,
-                        (uint32_t)t * 65536u + (uint32_t)m * FILTER_PLANE);
+    auto fetch = [&](int t, int h, int j) {
+        const uint32_t m = (uint32_t)(j / CHUNKS), part = (uint32_t)(j % CHUNKS) * (THREADS * 16);
+        buffer_to_lds16(lds0 + m * STRIDE + (uint32_t)h * FILTER_PLANE + part + wave_off, rs_img, lane_off,
+                        (uint32_t)t * TILE + m * FILTER_PLANE + part);
     };
 #pragma unroll
-    for (int m = 0; m < 4; ++m) fetch(0, 0, m);
+    for (int j = 0; j < M * CHUNKS; ++j) fetch(0, 0, j);
 
     const FilterScale sc = *f.scale;
-    const uint32_t* cen = reinterpret_cast<const uint32_t*>(f.centers);
+    const FilterWords<W>* cen = reinterpret_cast<const FilterWords<W>*>(f.centers);
     if (tid == 0) trips_s = 0u;
     if (tid < 2) bail_s[tid] = 0u;
 
-    // keys and thresholds of the workgroup's codes; the loads of four codes travel together
-    constexpr int SB = (R / 2) % 4 == 0 ? 4 : (R / 2) % 3 == 0 ? 3 : 2;
+    // keys and thresholds of the workgroup's codes; the loads of a few codes travel together
+    constexpr int SB = M == 8 ? 2 : (R / 2) % 4 == 0 ? 4 : (R / 2) % 3 == 0 ? 3 : 2;
     static_assert((R / 2) % SB == 0, "whole batches");
 #pragma unroll 1
     for (int i0 = 0; i0 < R / 2; i0 += SB) {
-        uint2 g[SB];
+        FilterCode<M> g[SB];
         uint32_t k[SB];
         float s[SB];
         unsigned long long old[SB];
 #pragma unroll
         for (int i = 0; i < SB; ++i) {
             const int64_t n = base + (i0 + i) * THREADS + tid, nc = n < N ? n : N - 1;
-            g[i] = gco[nc];
-            if (n >= N) g[i].y = ORIGIN_NONE;
+            g[i] = FilterCode<M>(gco[nc]);
+            if (n >= N) g[i].origin = ORIGIN_NONE;
             old[i] = f.seeded == 2 ? f.state[nc] : FILTER_NONE;
             k[i] = (uint32_t)old[i];
         }
-        if (f.seeded) {
+        if (f.seeded == 3) {
+            // the closest of the centers that share a pair of subcodes with the code
+            uint32_t cand[SB][M / 2];
+#pragma unroll
+            for (int i = 0; i < SB; ++i)
+#pragma unroll
+                for (int p = 0; p < M / 2; ++p)
+                    cand[i][p] = f.pairs[p * 65536 + ((g[i].w[p / 2] >> (16 * (p % 2))) & 0xffffu)];
 #pragma unroll
             for (int i = 0; i < SB; ++i) {
-                if (f.seeded == 1) k[i] = (uint32_t)assign[g[i].y == ORIGIN_NONE ? 0u : g[i].y];
+                s[i] = INFINITY;
+                k[i] = 0xffffffffu;
+#pragma unroll
+                for (int p = 0; p < M / 2; ++p) {
+                    const uint32_t kk = cand[i][p];
+                    if (kk < (uint32_t)f.K && kk != k[i]) {
+                        const float d = filter_distance<M>(f.tables, g[i].w, cen[kk]);
+                        if (d < s[i] || (d == s[i] && kk < k[i])) { s[i] = d; k[i] = kk; }
+                    }
+                }
+            }
+        } else if (f.seeded) {
+#pragma unroll
+            for (int i = 0; i < SB; ++i) {
+                if (f.seeded == 1) k[i] = (uint32_t)assign[g[i].origin == ORIGIN_NONE ? 0u : g[i].origin];
                 k[i] = k[i] < (uint32_t)f.K ? k[i] : 0u;             // any center will do
             }
 #pragma unroll
             for (int i = 0; i < SB; ++i) {
                 // an unchanged center is as far as it was; table entries are fetched for the others only
-                const uint32_t now = cen[k[i]];
+                const FilterWords<W> now = cen[k[i]];
                 s[i] = filter_key_distance(old[i]);
-                if (f.seeded != 2 || old[i] == FILTER_NONE || reinterpret_cast<const uint32_t*>(f.before)[k[i]] != now)
-                    s[i] = filter_distance4(f.tables, g[i].x, now);
+                bool same = f.seeded == 2 && old[i] != FILTER_NONE;
+                if (same) {
+                    const FilterWords<W> was = reinterpret_cast<const FilterWords<W>*>(f.before)[k[i]];
+#pragma unroll
+                    for (int w = 0; w < W; ++w) same = same && was.w[w] == now.w[w];
+                }
+                if (!same) s[i] = filter_distance<M>(f.tables, g[i].w, now);
             }
         }
 #pragma unroll
         for (int i = 0; i < SB; ++i) {
             const int jj = (i0 + i) * THREADS + tid;
             unsigned long long key = FILTER_NONE;
-            uint32_t t = g[i].y == ORIGIN_NONE ? DEAD : 0u;
-            if (f.seeded && g[i].y != ORIGIN_NONE && s[i] < INFINITY) {
+            uint32_t t = g[i].origin == ORIGIN_NONE ? DEAD : 0u;
+            if (f.seeded && g[i].origin != ORIGIN_NONE && s[i] < INFINITY) {
                 key = filter_key(s[i], k[i]);
                 t = ALL - filter_threshold(s[i], sc, ALL);
             }
@@ -319,19 +400,23 @@ __global__ __launch_bounds__(1024) void assign_filter4_kernel(int64_t N, const u
         }
     }
 
-    uint32_t pa[R], pb[R];
+    // packed row offsets: subspace m < M/2 in the low 15 bits, m + M/2 (64 KB higher) from bit 15 up
+    uint32_t fld[R][M / 2];
 #pragma unroll
     for (int r = 0; r < R; ++r) {
         int64_t n = base + (int64_t)r * SLOTS + c;
         if (n >= N) n = N - 1;
-        const uint32_t pk = gco[n].x;
-        const uint32_t f0 = ((pk & 255u) << 6) | hq;
-        const uint32_t f1 = (((pk >> 8) & 255u) << 6) | hq;
-        const uint32_t f2 = ((((pk >> 16) & 255u) << 6) | hq) + 65536u;
-        const uint32_t f3 = (((pk >> 24) << 6) | hq) + 65536u;
-        pa[r] = f0 | (f2 << 15);
-        pb[r] = f1 | (f3 << 15);
+        const FilterCode<M> g(gco[n]);
+#pragma unroll
+        for (int m = 0; m < M / 2; ++m) {
+            const int m2 = m + M / 2;
+            const uint32_t xa = (g.w[m / 4] >> (8 * (m % 4))) & 255u, xb = (g.w[m2 / 4] >> (8 * (m2 % 4))) & 255u;
+            fld[r][m] = ((xa << 6) | hq) | ((((xb << 6) | hq) + 65536u) << 15);
+        }
     }
+    auto row_of = [&](int r, int m) -> uint32_t {
+        return m < M / 2 ? unpack_low15(low15, fld[r][m]) : unpack_high17(fld[r][m - M / 2]);
+    };
 
     int qn = 0;                                  // entries in the wave's queue (the same in all lanes)
 
@@ -347,7 +432,7 @@ __global__ __launch_bounds__(1024) void assign_filter4_kernel(int64_t N, const u
         const int slot = wave * 32 + (int)sl;
         const int64_t n = base + (int64_t)r * SLOTS + slot;
         const uint32_t piece = 2u * (sl & 1u) + eq;
-        const uint32_t x = gco[n].x;             // only positions below N ever pass
+        const FilterCode<M> x(gco[n]);           // only positions below N ever pass
         // the center the key names already (the bound a code starts with is often its answer) needs no second look
         const unsigned long long known = __hip_atomic_load(&f.state[n], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         {
@@ -367,7 +452,7 @@ __global__ __launch_bounds__(1024) void assign_filter4_kernel(int64_t N, const u
                 mask &= mask - 1u;
                 const uint32_t k = t * FILTER_TK + 16u * (piece ^ ((j >> 2) << 1)) + 4u * (j & 3u) + (bit >> 3);
                 if (k < (uint32_t)f.K) {
-                    const float s = filter_distance4(f.tables, x, cen[k]);
+                    const float s = filter_distance<M>(f.tables, x.w, cen[k]);
                     if (s < INFINITY && (s < sb || (s == sb && k < kb))) { sb = s; kb = k; }
                 }
             }
@@ -415,10 +500,8 @@ __global__ __launch_bounds__(1024) void assign_filter4_kernel(int64_t N, const u
 #pragma unroll
         for (int i = 0; i < TW; ++i) tw[i] = thr_s[c * TW + i];
         auto issue = [&](int step) -> Pair {
-            const int r = step / 4, m = step % 4;
-            const uint32_t ad = (m == 0) ? unpack_low15(low15, pa[r]) : (m == 1) ? unpack_low15(low15, pb[r])
-                              : (m == 2) ? unpack_high17(pa[r]) : unpack_high17(pb[r]);
-            const uint32_t po = ((m & 1) ? 2 * FILTER_PLANE : 0) + h * FILTER_PLANE;
+            const int r = step / M, m = step % M;
+            const uint32_t ad = row_of(r, m), po = (uint32_t)(m % (M / 2)) * STRIDE + h * FILTER_PLANE;
             Pair p;
             p.a = *reinterpret_cast<const uint4*>(tb + ad + po);
             p.b = *reinterpret_cast<const uint4*>(tb + (ad ^ 32u) + po);
@@ -430,28 +513,42 @@ __global__ __launch_bounds__(1024) void assign_filter4_kernel(int64_t N, const u
         uint32_t acc[2][8], all[2];
 #pragma unroll
         for (int r = 0; r < R; ++r) {
-            if (!SEED) {
+            if (BUFFERS == 2 && !SEED) {
 #pragma unroll
-                for (int m = 0; m < 4; ++m)
-                    if ((m * R) / 8 == r && more) fetch(t + 1, h ^ 1, m);
+                for (int j = 0; j < M * CHUNKS; ++j)
+                    if ((j * R) / (2 * M * CHUNKS) == r && more) fetch(t + 1, h ^ 1, j);
             }
             uint32_t (&a)[8] = acc[r & 1];
-            const uint32_t ts = __builtin_amdgcn_perm(tw[r / 4], tw[r / 4], 0x01010101u * (uint32_t)(r & 3));
-            Pair v[4];
-#pragma unroll
-            for (int m = 0; m < 4; ++m) {
-                const int step = 4 * r + m;
-                v[m] = ring[step % DEPTH];
-                if (step + DEPTH < 4 * R) ring[step % DEPTH] = issue(step + DEPTH);
+            uint32_t ts = __builtin_amdgcn_perm(tw[r / 4], tw[r / 4], 0x01010101u * (uint32_t)(r & 3));
+            // sums of the bounds, two subspaces per three-operand add; M = 4 adds the code's byte with the last
+            auto take = [&](int step) -> Pair {
+                const Pair p = ring[step % DEPTH];
+                if (step + DEPTH < M * R) ring[step % DEPTH] = issue(step + DEPTH);
+                return p;
+            };
+            {
+                const Pair p0 = take(M * r), p1 = take(M * r + 1), p2 = take(M * r + 2);
+                a[0] = p0.a.x + p1.a.x + p2.a.x;  a[1] = p0.a.y + p1.a.y + p2.a.y;
+                a[2] = p0.a.z + p1.a.z + p2.a.z;  a[3] = p0.a.w + p1.a.w + p2.a.w;
+                a[4] = p0.b.x + p1.b.x + p2.b.x;  a[5] = p0.b.y + p1.b.y + p2.b.y;
+                a[6] = p0.b.z + p1.b.z + p2.b.z;  a[7] = p0.b.w + p1.b.w + p2.b.w;
             }
-            a[0] = v[0].a.x + v[1].a.x + v[2].a.x;  a[1] = v[0].a.y + v[1].a.y + v[2].a.y;
-            a[2] = v[0].a.z + v[1].a.z + v[2].a.z;  a[3] = v[0].a.w + v[1].a.w + v[2].a.w;
-            a[4] = v[0].b.x + v[1].b.x + v[2].b.x;  a[5] = v[0].b.y + v[1].b.y + v[2].b.y;
-            a[6] = v[0].b.z + v[1].b.z + v[2].b.z;  a[7] = v[0].b.w + v[1].b.w + v[2].b.w;
-            a[0] = a[0] + v[3].a.x + ts;  a[1] = a[1] + v[3].a.y + ts;  a[2] = a[2] + v[3].a.z + ts;  a[3] = a[3] + v[3].a.w + ts;
-            a[4] = a[4] + v[3].b.x + ts;  a[5] = a[5] + v[3].b.y + ts;  a[6] = a[6] + v[3].b.z + ts;  a[7] = a[7] + v[3].b.w + ts;
+#pragma unroll
+            for (int m = 3; m + 1 < M; m += 2) {
+                const Pair p0 = take(M * r + m), p1 = take(M * r + m + 1);
+                a[0] = a[0] + p0.a.x + p1.a.x;  a[1] = a[1] + p0.a.y + p1.a.y;
+                a[2] = a[2] + p0.a.z + p1.a.z;  a[3] = a[3] + p0.a.w + p1.a.w;
+                a[4] = a[4] + p0.b.x + p1.b.x;  a[5] = a[5] + p0.b.y + p1.b.y;
+                a[6] = a[6] + p0.b.z + p1.b.z;  a[7] = a[7] + p0.b.w + p1.b.w;
+            }
+            {
+                const Pair p = take(M * r + M - 1);
+                const uint32_t e = M == 4 && !SEED ? ts : 0u;
+                a[0] = a[0] + p.a.x + e;  a[1] = a[1] + p.a.y + e;  a[2] = a[2] + p.a.z + e;  a[3] = a[3] + p.a.w + e;
+                a[4] = a[4] + p.b.x + e;  a[5] = a[5] + p.b.y + e;  a[6] = a[6] + p.b.z + e;  a[7] = a[7] + p.b.w + e;
+            }
             if (SEED) {
-                // bytes are sums of bounds (codes that have no distance yet) or at least 128 (holes)
+                // codes that have no distance yet: the threshold is the smallest sum of this tile
                 uint32_t mn = 0xffffffffu;
 #pragma unroll
                 for (int j = 0; j < 8; ++j) {
@@ -461,16 +558,23 @@ __global__ __launch_bounds__(1024) void assign_filter4_kernel(int64_t N, const u
                 uint32_t low = (mn & 0xffffu) < (mn >> 16) ? (mn & 0xffffu) : (mn >> 16);
                 const uint32_t other = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)low, 0xB1, 0xf, 0xf, true);
                 low = other < low ? other : low;
-                const uint32_t up = (low <= ALL ? ALL - low : 0u) * 0x01010101u;
+                if (ts == 0u) ts = (ALL - low) * 0x01010101u;
+                if (M == 4) {
 #pragma unroll
-                for (int j = 0; j < 8; ++j) a[j] += up;
+                    for (int j = 0; j < 8; ++j) a[j] += ts;
+                }
+            }
+            if (M == 8) {
+#pragma unroll
+                for (int j = 0; j < 8; ++j) a[j] = __builtin_amdgcn_lerp(a[j], ts, 0x01010101u);
             }
             all[r & 1] = (((a[0] & a[1] & a[2]) & (a[3] & a[4])) & (a[5] & a[6])) & a[7];
-            if ((r & 1) && __builtin_expect(__any((all[0] & all[1] & HI) != HI), 0)) push(acc[0], acc[1], all[0], all[1], r - 1, r, t);
+            if ((r & 1) && __builtin_expect(__any((all[0] & all[1] & HI) != HI), 0))
+                push(acc[0], acc[1], all[0], all[1], r - 1, r, t);
         }
     };
 
-    if (!f.seeded) {
+    if (f.seeded == 0 || f.seeded == 3) {
         wait_vector_loads();
         __syncthreads();
         scan_tile(IntC<0>{}, IntC<1>{}, 0, false);
@@ -482,12 +586,17 @@ __global__ __launch_bounds__(1024) void assign_filter4_kernel(int64_t N, const u
         wait_vector_loads();
         // one thread decides for all whether the candidates cost more than the plain scan would; its verdict of this
         // turn stays untouched until everybody has passed the next barrier
-        if (tid == 0) bail_s[t & 1] = trips_s * 64u > (uint32_t)C * (32u + (uint32_t)t + ((uint32_t)t >> 2)) ? 1u : 0u;
+        if (tid == 0) bail_s[t & 1] = trips_s * 64u > (uint32_t)C * (96u + (uint32_t)t + ((uint32_t)t >> 2)) ? 1u : 0u;
         __syncthreads();
         if (bail_s[t & 1]) { bail = true; break; }
         const bool more = t + 1 < f.ntiles;
-        if (t & 1) scan_tile(IntC<1>{}, IntC<0>{}, t, more);
+        if (BUFFERS == 2 && (t & 1)) scan_tile(IntC<BUFFERS - 1>{}, IntC<0>{}, t, more);
         else scan_tile(IntC<0>{}, IntC<0>{}, t, more);
+        if (BUFFERS == 1 && more) {
+            __syncthreads();                     // nobody reads this tile any more
+#pragma unroll
+            for (int j = 0; j < M * CHUNKS; ++j) fetch(t + 1, 0, j);
+        }
     }
     while (qn > 0) drain();
 
@@ -505,21 +614,19 @@ __global__ __launch_bounds__(1024) void assign_filter4_kernel(int64_t N, const u
         }
         for (int k0 = t * FILTER_TK; k0 < f.K; k0 += 16) {
             __syncthreads();
-            for (int e = tid; e < 4 * L * 16; e += THREADS) {
+            for (int e = tid; e < M * L * 16; e += THREADS) {
                 const int kin = e & 15, x = (e >> 4) & 255, m = e >> 12;
                 const int k = k0 + kin;
-                const float v = k < f.K ? f.tables[((size_t)m * L + x) * L + f.centers[(size_t)k * 4 + m]] : INFINITY;
-                reinterpret_cast<float*>(tile)[m * 8192 + x * 16 + kin] = v;
+                const float v = k < f.K ? f.tables[((size_t)m * L + x) * L + f.centers[(size_t)k * M + m]] : INFINITY;
+                reinterpret_cast<float*>(tile)[m * (STRIDE / 4) + x * 16 + kin] = v;
             }
             __syncthreads();
 #pragma unroll
             for (int r = 0; r < R; ++r) {
                 float v[8];
 #pragma unroll
-                for (int m = 0; m < 4; ++m) {
-                    const uint32_t ad = (m == 0) ? unpack_low15(low15, pa[r]) : (m == 1) ? unpack_low15(low15, pb[r])
-                                      : (m == 2) ? unpack_high17(pa[r]) : unpack_high17(pb[r]);
-                    const uint32_t po = (m & 1) ? 2 * FILTER_PLANE : 0;
+                for (int m = 0; m < M; ++m) {
+                    const uint32_t ad = row_of(r, m), po = (uint32_t)(m % (M / 2)) * STRIDE;
                     const float4 va = lds_read16(tb, ad + po), vb = lds_read16(tb, (ad ^ 32u) + po);
                     const float w[8] = {va.x, va.y, va.z, va.w, vb.x, vb.y, vb.z, vb.w};
 #pragma unroll
@@ -549,16 +656,16 @@ __global__ __launch_bounds__(1024) void assign_filter4_kernel(int64_t N, const u
         const int64_t n = base + jj;
         uint32_t pk = 0u, og = ORIGIN_NONE, k = 0u;
         if (n < N) {
-            const uint2 g = gco[n];
+            const FilterCode<M> g(gco[n]);
             const unsigned long long key = __hip_atomic_load(&f.state[n], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            pk = g.x;
-            og = g.y;
+            pk = g.w[0];
+            og = g.origin;
             k = key == FILTER_NONE ? 0u : (uint32_t)key;
             if (og != ORIGIN_NONE) {
                 assign[og] = (int32_t)k;
                 if (dist) {
                     float s = key == FILTER_NONE ? INFINITY : filter_key_distance(key);
-                    if (s == 0.0f) s = filter_distance4(f.tables, pk, cen[k]);       // the sign of a zero
+                    if (s == 0.0f) s = filter_distance<M>(f.tables, g.w, cen[k]);       // the sign of a zero
                     dist[og] = s;
                 }
                 if (ro.count) ro.rank[og] = atomicAdd(&ro.count[k], 1u);
