@@ -46,24 +46,27 @@ __global__ __launch_bounds__(256) void build_tables_kernel(const float* __restri
 // 3 flops per (vector, codeword, dimension) if every one of them is formed on the vector units.  Here the matrix cores
 // find the codewords that can be the closest, and only where that leaves more than one the fp32 distances decide.
 //
-// v_l = |x|^2/2 + |c_l|^2/2 - x.c_l (half the distance) with x and c split into two bf16 parts each, x = xh + xl + r,
+// v_l = |c_l|^2/2 - x.c_l (half the distance up to |x|^2/2) with x and c split into two bf16 parts each, x = xh + xl + r,
 // |r| <= 2^-18 |x|, three products xh.ch + xh.cl + xl.ch accumulated in fp32.  With s = |x| + max_l |c_l|:
 //   - dropped products and residuals: at most 3 (1 + 2^-8) 2^-18 |x||c| <= 0.76 2^-18 s^2,
-//   - accumulation of 3 Ds products and the two norms: (3 Ds + 8) 2^-23 |x||c|, truncation allowed for, at most
-//     (3 Ds + 8) 2^-25 s^2; norms rounded to fp32: 2^-23 s^2,
-//   - the low 8 bits of v_l hold l: 2^-15 |v_l|,
+//   - accumulation of 3 Ds products and the norm: (3 Ds + 8) 2^-23 |x||c|, truncation allowed for, at most
+//     (3 Ds + 8) 2^-25 s^2; the norm rounded to fp32: 2^-25 s^2,
+//   - the low 4 bits of a kept value hold an index: 2^-19 |v_l| <= 2^-20 s^2,
 //   - the defined fp32 distance is within (Ds + 2) 2^-24 (1 + ..) of the true one, which is at most s^2.
 // The codeword the definition selects therefore has v_l <= v_min + E with twice the sum of the above; E below is
 // rounded up by a quarter and by 1e-30 for flushed denormals.  If the second smallest v exceeds that, the smallest is
-// the answer.  If only the third does, the two are compared by their fp32 distances; else all 256 are.  A vector or
-// codeword that makes E overflow or NaN takes the last way, so non-finite values keep the definition's result.
+// the answer.  Else the fp32 distances decide: of the 32 codewords in the two blocks of 16 that can hold the closest, or, if a
+// third block can, of all 256.  A vector or codeword that makes E overflow or NaN takes the last way, so non-finite values
+// keep the definition's result.
 //
 // One wave takes 32 vectors and one subspace at a time: v_mfma_f32_32x32x16_bf16 with the codewords as rows and the
-// vectors as columns, so that a lane holds 16 codewords of one vector and the three smallest are kept in registers; the
-// two lanes of a vector merge at the end.  The workgroup holds the split codewords of `G` subspaces in LDS (16 KB per
-// subspace and 16 dimensions, 128 KB in all) in the order the instruction reads them.  Bound by the vector units (4
-// instructions per (vector, codeword)) up to 32 dimensions, by the matrix cores above.  Measured, 1e6 vectors of 128
-// dimensions, M = 4: 1.14 ms -> 0.33 ms (0.52 GB of vectors); 5e5 vectors of 96 dimensions, M = 8: 142 ms (any length that was not compiled for) -> 0.23 ms.
+// vectors as columns, so that a lane holds 16 codewords of one vector per instruction.  It takes the minimum of the 16,
+// keeps the three smallest such minima and the 16 values under the smallest (1.9 instructions per value; ranking every
+// value takes 6), and ranks those 16 at the end, when the two lanes of a vector merge.  The workgroup holds the split
+// codewords of `G` subspaces in LDS (16 KB per subspace and 16 dimensions, 128 KB in all) in the order the instruction
+// reads them.  Bound by the vector units and the matrix cores about equally at 32 dimensions, by the latter above.
+// Measured, 1e6 vectors of 128 dimensions (0.52 GB), M = 4: 1.14 ms on the vector units -> 0.26 ms; 5e5 vectors of 96
+// dimensions, M = 8: 142 ms (any length that was not compiled for) -> 0.155 ms.
 // ---------------------------------------------------------------------------------------------
 typedef __bf16 v8bf __attribute__((ext_vector_type(8)));
 typedef float v16f __attribute__((ext_vector_type(16)));
@@ -77,6 +80,19 @@ __device__ __forceinline__ float min_f32(float a, float b)
     float r;
     asm("v_min_f32 %0, %1, %2" : "=v"(r) : "v"(a), "v"(b));
     return r;
+}
+
+// v_minimum3_f32 through the compiler, which keeps the wait states a matrix instruction's result needs (inline assembly on
+// such a result would read it too early)
+__device__ __forceinline__ float minimum3(float a, float b, float c)
+{
+    return __builtin_elementwise_minimum(__builtin_elementwise_minimum(a, b), c);
+}
+
+// v with its low 4 bits replaced
+__device__ __forceinline__ float low_bits(float v, uint32_t name)
+{
+    return __builtin_bit_cast(float, (__builtin_bit_cast(uint32_t, v) & 0xfffffff0u) | name);
 }
 
 // the fp32 distance of the definition
@@ -135,7 +151,7 @@ __global__ __launch_bounds__(THREADS) void encode_mfma_kernel(const float* __res
     __syncthreads();
 
     const int half = lane >> 5;
-    const float kappa = 1.25f * 2.0f * (0.76f * 0x1p-18f + (float)(3 * Ds + 8) * 0x1p-25f + 0x1p-23f + (float)(Ds + 4) * 0x1p-24f);
+    const float kappa = 1.25f * 2.0f * (0.76f * 0x1p-18f + (float)(3 * Ds + 8) * 0x1p-25f + 0x1p-25f + 0x1p-19f + (float)(Ds + 4) * 0x1p-24f);
     const int64_t ntiles = (N + 31) / 32;
     for (int64_t t = (int64_t)w * WAVES + wave; t < ntiles; t += (int64_t)wpg * WAVES) {
         const int64_t n = t * 32 + (lane & 31);
@@ -169,8 +185,10 @@ __global__ __launch_bounds__(THREADS) void encode_mfma_kernel(const float* __res
                 }
             }
             ss = ss + __shfl_xor(ss, 32);
-            const float hx = 0.5f * ss;
-            float m1 = INFINITY, m2 = INFINITY, m3 = INFINITY;
+            float m1 = INFINITY, m2 = INFINITY, m3 = INFINITY;    // smallest minima of 16, the low bits name the block
+            float kept[16];
+#pragma unroll
+            for (int i = 0; i < 16; ++i) kept[i] = INFINITY;
             const float4* hn = reinterpret_cast<const float4*>(hnorm + g * L) + half;
             const float4* fr = frag + (size_t)g * 8 * KS * 2 * 64 + lane;
 #pragma unroll
@@ -179,7 +197,7 @@ __global__ __launch_bounds__(THREADS) void encode_mfma_kernel(const float* __res
 #pragma unroll
                 for (int i = 0; i < 4; ++i) {
                     const float4 h4 = hn[b * 8 + 2 * i];
-                    acc[4 * i] = h4.x + hx; acc[4 * i + 1] = h4.y + hx; acc[4 * i + 2] = h4.z + hx; acc[4 * i + 3] = h4.w + hx;
+                    acc[4 * i] = h4.x; acc[4 * i + 1] = h4.y; acc[4 * i + 2] = h4.z; acc[4 * i + 3] = h4.w;
                 }
 #pragma unroll
                 for (int ks = 0; ks < KS; ++ks) {
@@ -189,44 +207,48 @@ __global__ __launch_bounds__(THREADS) void encode_mfma_kernel(const float* __res
                     acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ch, xl[ks], acc, 0, 0, 0);
                     acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ch, xh[ks], acc, 0, 0, 0);
                 }
+                const float u0 = minimum3(acc[0], acc[1], acc[2]), u1 = minimum3(acc[3], acc[4], acc[5]);
+                const float u2 = minimum3(acc[6], acc[7], acc[8]), u3 = minimum3(acc[9], acc[10], acc[11]);
+                const float u4 = minimum3(acc[12], acc[13], acc[14]);
+                const float e = low_bits(minimum3(minimum3(u0, u1, u2), minimum3(u3, u4, acc[15]), u0), (uint32_t)b);
+                const bool better = e < m1;
+                m3 = __builtin_amdgcn_fmed3f(m2, m3, e);
+                m2 = __builtin_amdgcn_fmed3f(m1, m2, e);
+                m1 = better ? e : m1;
 #pragma unroll
-                for (int i = 0; i < 16; ++i) {
-                    const float a = acc[i];
-                    const float v = __builtin_bit_cast(float, (__builtin_bit_cast(uint32_t, a) & 0xffffff00u) | (uint32_t)(b * 16 + i));
-                    m3 = __builtin_amdgcn_fmed3f(m2, m3, v);
-                    m2 = __builtin_amdgcn_fmed3f(m1, m2, v);
-                    m1 = min_f32(m1, v);
-                }
+                for (int i = 0; i < 16; ++i) kept[i] = better ? acc[i] : kept[i];
             }
-            // bit 7: which lane of the two
-            auto mark = [&](float v) { return __builtin_bit_cast(float, __builtin_bit_cast(uint32_t, v) | ((uint32_t)half << 7)); };
+            // the two smallest of the lane's best block; the low bits name the place in it
+            float w1 = INFINITY, w2 = INFINITY;
+#pragma unroll
+            for (int i = 0; i < 16; ++i) {
+                const float v = low_bits(kept[i], (uint32_t)i);
+                w2 = __builtin_amdgcn_fmed3f(w1, w2, v);
+                w1 = min_f32(w1, v);
+            }
+            // bit 3 of a block's name: which lane of the two
+            auto mark = [&](float v) { return __builtin_bit_cast(float, __builtin_bit_cast(uint32_t, v) | ((uint32_t)half << 3)); };
             m1 = mark(m1); m2 = mark(m2); m3 = mark(m3);
             const float o1 = __shfl_xor(m1, 32), o2 = __shfl_xor(m2, 32), o3 = __shfl_xor(m3, 32);
+            const float p1 = __shfl_xor(w1, 32), p2 = __shfl_xor(w2, 32);
             const float a1 = __builtin_fminf(m1, o1);
             const float a2 = __builtin_fminf(__builtin_fmaxf(m1, o1), __builtin_fminf(m2, o2));
             const float a3 = __builtin_fminf(__builtin_fminf(m3, o3), __builtin_fminf(__builtin_fmaxf(m1, o2), __builtin_fmaxf(m2, o1)));
-            auto codeword_of = [](float v) {
-                const uint32_t u = __builtin_bit_cast(uint32_t, v) & 255u, i = u & 15u;
-                return (int)(((u >> 4) & 7u) * 32u + 8u * (i >> 2) + 4u * (u >> 7) + (i & 3u));
+            const bool mine = ((__builtin_bit_cast(uint32_t, a1) >> 3) & 1u) == (uint32_t)half;
+            const float b1 = mine ? w1 : p1, b2 = mine ? w2 : p2;
+            auto codeword_of = [](uint32_t block, uint32_t i) {      // block: name of a block of 16, i: place in it
+                return (int)((block & 7u) * 32u + 8u * (i >> 2) + 4u * ((block >> 3) & 1u) + (i & 3u));
             };
-            const float s = (__builtin_sqrtf(ss) + __builtin_sqrtf(__builtin_bit_cast(float, cmax[g]))) * 1.0001f;
-            const float E = kappa * s * s + 0x1p-13f * __builtin_fabsf(a1) + 1e-30f;
+            const float s = (__builtin_amdgcn_sqrtf(ss) + __builtin_amdgcn_sqrtf(__builtin_bit_cast(float, cmax[g]))) * 1.0001f;
+            const float E = kappa * s * s + 1e-30f;
             const float lim = a1 + E;
-            const bool sure = a2 > lim, pair = a3 > lim;         // false when anything overflowed or is NaN
-            const bool fin = E < 3e38f;
-            int bl = codeword_of(a1);
+            const bool sure = a2 > lim && b2 > lim;               // false when anything overflowed or is NaN
+            const bool two = a3 > lim && E < 3e38f;
+            int bl = codeword_of(__builtin_bit_cast(uint32_t, a1), __builtin_bit_cast(uint32_t, b1) & 15u);
             const float* cw = codewords + (size_t)(m0 + g) * L * Ds;
-            if (fin && !sure && pair) {
-                // two codewords: each lane of the vector forms one distance
-                const int la = codeword_of(a1), lb = codeword_of(a2);
-                const float dm = encode_distance(xv, cw + (size_t)(half ? lb : la) * Ds, Ds);
-                const float dO = __shfl_xor(dm, 32);
-                const float da = half ? dO : dm, db = half ? dm : dO;
-                bl = (db < da || (db == da && lb < la)) ? lb : la;
-            }
-            uint64_t rest = __ballot(!fin || !(sure || pair)) & 0xffffffffull;
+            uint64_t rest = __ballot(!(sure && E < 3e38f)) & 0xffffffffull;
             while (rest) {
-                // all 256 codewords, the wave together: lane i forms i, i + 64, ...
+                // one vector, the wave together
                 const int v = __builtin_ctzll(rest);
                 rest &= rest - 1;
                 int64_t nv = t * 32 + v;
@@ -234,9 +256,19 @@ __global__ __launch_bounds__(THREADS) void encode_mfma_kernel(const float* __res
                 const float* xr = vectors + ((size_t)nv * M + m0 + g) * Ds;
                 float best = INFINITY;
                 int bi = IDX_NONE;
-                for (int j = 0; j < 4; ++j) {
-                    const float d = encode_distance(xr, cw + (size_t)(lane + 64 * j) * Ds, Ds);
-                    if (d < best) { best = d; bi = lane + 64 * j; }
+                if (__builtin_amdgcn_readlane((int)two, v)) {
+                    const uint32_t n1 = (uint32_t)__builtin_amdgcn_readlane(__builtin_bit_cast(int, a1), v);
+                    const uint32_t n2 = (uint32_t)__builtin_amdgcn_readlane(__builtin_bit_cast(int, a2), v);
+                    if (lane < 32) {
+                        const int l = codeword_of(lane < 16 ? n1 : n2, (uint32_t)lane & 15u);
+                        const float d = encode_distance(xr, cw + (size_t)l * Ds, Ds);
+                        if (d < best) { best = d; bi = l; }
+                    }
+                } else {
+                    for (int j = 0; j < 4; ++j) {
+                        const float d = encode_distance(xr, cw + (size_t)(lane + 64 * j) * Ds, Ds);
+                        if (d < best) { best = d; bi = lane + 64 * j; }
+                    }
                 }
 #pragma unroll
                 for (int off = 32; off; off >>= 1) {
