@@ -191,7 +191,7 @@ Carve carve(int64_t N, int M, int K)
     // keys of the lower-bound scans (8 bytes per code position of a launch): they live only while a scan runs.  Where the
     // histogram of a fused iteration takes the owner path no ranks are handed over, and the keys share the room of the
     // sorted path (the at most 30 padding positions reach into the cluster sizes, which are written after the scan).
-    if (M == 4 || M == 8) {
+    if (tiled_M(M)) {
         if (hp.cheap && N <= GROUP_CHUNK_MAX) {
             c.state_off = c.sidx_off;
         } else {
@@ -394,7 +394,8 @@ inline SwShape sw_shape(int variant, int64_t n)
 
 template <int M>
 pqkm_status launch_scan_sw(int variant, const uint8_t* codes, int64_t N, uint32_t* S, const float4* img, int ntiles16,
-                           int32_t* assign, float* dist, hipStream_t st, RankOut ro = RankOut{}, int rounds_per_launch = 0)
+                           int32_t* assign, float* dist, hipStream_t st, RankOut ro = RankOut{}, int rounds_per_launch = 0,
+                           const uint32_t* only_if = nullptr)
 {
     const SwShape sh = sw_shape(variant, N);
     const bool wide = sh.threads == 1024;
@@ -403,7 +404,7 @@ pqkm_status launch_scan_sw(int variant, const uint8_t* codes, int64_t N, uint32_
     const int64_t nwg = (N + C - 1) / C;
     const int64_t n_alloc = nwg * C;
     hipLaunchKernelGGL((code_skew_kernel<M>), dim3((unsigned)((n_alloc + 255) / 256)), dim3(256), 0, st, codes, N, S,
-                       n_alloc);
+                       n_alloc, only_if);
     // kernel launches of rounds_per_launch rounds of workgroups each, so that the workgroups start in step again
     // (see launch_scan4q_rounds)
     const int64_t per = rounds_per_launch > 0 ? (int64_t)rounds_per_launch * cu_count() : nwg;
@@ -411,13 +412,13 @@ pqkm_status launch_scan_sw(int variant, const uint8_t* codes, int64_t N, uint32_
         const int64_t cnt = nwg - w0 < per ? nwg - w0 : per;
         if (wide)
             hipLaunchKernelGGL((assign_scan_sw_kernel<M, 6, 1024, 2>), dim3((unsigned)cnt), dim3(1024), 0, st, codes, N, S,
-                               n_alloc, img, ntiles16, assign, dist, ro, w0);
+                               n_alloc, img, ntiles16, assign, dist, ro, w0, only_if);
         else if (R == 8)
             hipLaunchKernelGGL((assign_scan_sw_kernel<M, 8, 512, 3>), dim3((unsigned)cnt), dim3(512), 0, st, codes, N, S,
-                               n_alloc, img, ntiles16, assign, dist, ro, w0);
+                               n_alloc, img, ntiles16, assign, dist, ro, w0, only_if);
         else
             hipLaunchKernelGGL((assign_scan_sw_kernel<M, 16, 512, 2>), dim3((unsigned)cnt), dim3(512), 0, st, codes, N, S,
-                               n_alloc, img, ntiles16, assign, dist, ro, w0);
+                               n_alloc, img, ntiles16, assign, dist, ro, w0, only_if);
         ++t_scan_kernels;
     }
     return launched();
@@ -869,7 +870,7 @@ pqkm_status regroup_codes8(const uint8_t* codes, int64_t cnt, uint4* gc8, GroupP
     const int64_t na = group_alloc(cnt);
     if (blocks_of_16)
         hipLaunchKernelGGL(code8_group_clear_kernel, dim3(1024), dim3(256), 0, st, gc8, na);
-    hipLaunchKernelGGL(zero_u32_kernel, dim3(64), dim3(256), 0, st, plan->count, (int64_t)GROUP8_CLASSES);
+    hipLaunchKernelGGL(zero_u32_kernel, dim3(64), dim3(256), 0, st, plan->count, (int64_t)GROUP8_CLASSES, (const uint32_t*)nullptr);
     unsigned g = (unsigned)((cnt + 1023) / 1024 < 4096 ? (cnt + 1023) / 1024 : 4096);
     if (g < 1) g = 1;
     hipLaunchKernelGGL(code8_class_count_kernel, dim3(g), dim3(256), 0, st, codes, cnt, plan);
@@ -1058,6 +1059,48 @@ struct BucketLink {
     bool rank_wanted = false, ranked = false;
 };
 
+// M = 16, 32: is the lower-bound scan tried before the sliding-window scan?  (Ranks of several stretches could not be taken
+// back when a later one gives up, so a fused iteration of more codes than one launch keeps the plain scan: see the caller.)
+constexpr int FILTER_WIDE_PAIRS_MIN_K = 500;
+// Fewest centers, by iteration, as for M = 4.  Measured at N = 1e6 against the sliding-window scan, ms per iteration, M = 32:
+// first 5.1 / 3.8 at K = 2000, 12.4 / 16.4 at 10000; second and third 5.0 / 3.95 and 12.1 / 17.3; later 3.4 / 3.95 and
+// 9.5 / 17.3.  M = 16, K = 3000: 2.9 / 2.9, 2.3 / 3.0, 1.7 / 3.0.
+inline int wide_min_k(int M, int iteration)
+{
+    return M == 32 ? (iteration == 0 ? 5000 : iteration < 3 ? 4000 : 1500) : (iteration == 0 ? 3500 : iteration < 3 ? 1800 : 900);
+}
+inline bool wide_filter(int M, int asked, int variant, int64_t N, int K, const uint8_t* centers, int iteration)
+{
+    if ((M != 16 && M != 32) || !variant_sliding(M, variant)) return false;
+    if (((uintptr_t)centers & 3) != 0 || ((int64_t)K + 63) / 64 * (M * 16384) >= (int64_t)0xfff00000) return false;
+    if (K <= 48) return false;                           // the byte tiles of 64 centers need the room of 16 KB M per 16
+    if (asked == 59) return true;                        // forced
+    return asked == 0 && K >= wide_min_k(M, iteration);
+}
+
+template <int M>
+void launch_filter_wide(const uint8_t* codes, int64_t N, uint32_t* S, FilterWideIn f, int32_t* assign, float* dist,
+                        hipStream_t st, RankOut ro)
+{
+    const int ncu = cu_count();
+    constexpr int64_t C = 1024;                          // more codes per workgroup do not fit the registers
+    const int64_t nwg = (N + C - 1) / C;
+    f.S = S;
+    f.n_alloc = nwg * C;
+    f.codes = codes;
+    hipLaunchKernelGGL((code_rotate_kernel<M>), dim3((unsigned)((f.n_alloc + 255) / 256)), dim3(256), 0, st, codes, N, S, f.n_alloc);
+    // tiles per launch: all of them while there is one round of workgroups
+    const int step = nwg <= ncu ? f.ntiles : (4 << 20) / (M * (int)FILTER_PLANE);
+    for (int t0 = 0; t0 < f.ntiles; t0 += step)
+        for (int64_t w0 = 0; w0 < nwg; w0 += ncu) {      // a round of workgroups per launch: they start in step
+            const unsigned cnt = (unsigned)(nwg - w0 < ncu ? nwg - w0 : ncu);
+            f.t_begin = t0;
+            f.t_end = f.ntiles - t0 < step ? f.ntiles : t0 + step;
+            hipLaunchKernelGGL((assign_filter_wide_kernel<M, 2, 1024>), dim3(cnt), dim3(1024), 0, st, N, f, assign, dist, ro, w0);
+            ++t_scan_kernels;
+        }
+}
+
 template <int M>
 pqkm_status assign_tiled(const uint8_t* codes, int64_t N, const uint8_t* centers, int K, const float* tables,
                          int32_t* assign, float* dist, float* img, const Options& opt, const Carve& c, char* ws,
@@ -1088,6 +1131,14 @@ pqkm_status assign_tiled(const uint8_t* codes, int64_t N, const uint8_t* centers
     const bool plain_before = iteration > 0 && opt.scan_variant == 0 && K < (M == 4 ? filter4_min_k(iteration - 1) : filter8_min_k(iteration - 1));
     const int layout = variant_layout(M, variant);
     const bool sliding = variant_sliding(M, variant);
+    // M = 16, 32: the lower-bound scan of every stretch in front of the sliding-window scan, which runs where it gave up.
+    // Its statistics live in the histograms' room while the assignment runs, its byte tiles and pair tables in that of the
+    // images, which are only built after a scan has given up.
+    const bool wide = sliding && wide_filter(M, opt.scan_variant, variant, N, K, centers, iteration) &&
+                      (!(link && link->rank_wanted) || (N <= GROUP_CHUNK_MAX - 16384 && N <= opt.launch_codes));
+    FilterStat* const wstat = reinterpret_cast<FilterStat*>(ws + c.hist_off);
+    FilterScale* const wscale = reinterpret_cast<FilterScale*>(ws + c.hist_off + 8192);
+    uint32_t* const gave_up = reinterpret_cast<uint32_t*>(ws + c.hist_off + 8448);
     FilterIn fin{};
     if (filter) {
         // (M = 8: behind the byte tiles, which take a quarter of the images' room)
@@ -1117,8 +1168,8 @@ pqkm_status assign_tiled(const uint8_t* codes, int64_t N, const uint8_t* centers
         // tiles of 16 centers, plane-ordered: img[tile][m][x][16]
         ntiles = ((int64_t)K + 15) / 16;
         total = ntiles * (int64_t)16 * M * L;
-        hipLaunchKernelGGL((tile_image_kernel<M, 0, 16>), dim3((unsigned)((total + 255) / 256)), dim3(256), 0, st,
-                           centers, K, tables, img, total);
+        if (!wide) hipLaunchKernelGGL((tile_image_kernel<M, 0, 16>), dim3((unsigned)((total + 255) / 256)), dim3(256), 0, st,
+                           centers, K, tables, img, total, (float*)nullptr, (const uint32_t*)nullptr);
     } else if (layout == 2 && M == 4)
         hipLaunchKernelGGL((tile_image_kernel<4, 2>), dim3((unsigned)((total + 255) / 256)), dim3(256), 0, st,
                            centers, K, tables, img, total, reinterpret_cast<float*>(ws + c.rows_off));
@@ -1174,7 +1225,7 @@ pqkm_status assign_tiled(const uint8_t* codes, int64_t N, const uint8_t* centers
         ro.count = reinterpret_cast<uint32_t*>(ws + c.seg_off);
         ro.rank = reinterpret_cast<uint32_t*>(ws + c.rank_off);
         unsigned zb = (unsigned)((K + 255) / 256 < 1024 ? (K + 255) / 256 : 1024);
-        hipLaunchKernelGGL(zero_u32_kernel, dim3(zb), dim3(256), 0, st, ro.count, (int64_t)K);
+        hipLaunchKernelGGL(zero_u32_kernel, dim3(zb), dim3(256), 0, st, ro.count, (int64_t)K, (const uint32_t*)nullptr);
         link->ranked = true;
     }
     for (int64_t n0 = 0; n0 < N; n0 += per_launch) {
@@ -1191,9 +1242,37 @@ pqkm_status assign_tiled(const uint8_t* codes, int64_t N, const uint8_t* centers
         t_scan_kernels = 0;
         if (sliding) {
             if constexpr (M == 16 || M == 32) {
+                if (wide) {
+                    const bool pairs = iteration == 0 && K >= FILTER_WIDE_PAIRS_MIN_K;
+                    const int nt = (K + FILTER_TK - 1) / FILTER_TK;
+                    uint32_t* pair_tab = reinterpret_cast<uint32_t*>(img) + (size_t)nt * M * (FILTER_PLANE / 4);
+                    // a stretch before this one may have given up and built the plain images in their place
+                    if (n0 == 0) hipLaunchKernelGGL(filter_stats_kernel, dim3(M * FILTER_PARTS), dim3(1024), 0, st, tables, wstat);
+                    hipLaunchKernelGGL((filter_image_kernel<M>), dim3((unsigned)(nt * M * 4)), dim3(256), 0, st, centers, K, tables,
+                                       wstat, reinterpret_cast<uint4*>(img), (uint8_t*)nullptr, wscale, gave_up);
+                    if (pairs) {
+                        hipLaunchKernelGGL(fill_i32_kernel, dim3(256), dim3(256), 0, st, reinterpret_cast<int32_t*>(pair_tab),
+                                           (int64_t)FILTER_WIDE_PAIRS * 65536, (int32_t)-1);
+                        hipLaunchKernelGGL((filter_pairs_kernel<M, FILTER_WIDE_PAIRS>), dim3((unsigned)((K + 255) / 256)), dim3(256),
+                                           0, st, centers, K, pair_tab);
+                    }
+                    launch_filter_wide<M>(codes + n0 * M, cnt, reinterpret_cast<uint32_t*>(ws + c.skew_off),
+                                          FilterWideIn{reinterpret_cast<const uint4*>(img), nullptr, 0, nullptr, centers, tables, wscale,
+                                                       reinterpret_cast<unsigned long long*>(ws + c.state_off),
+                                                       pairs ? pair_tab : nullptr, gave_up, K, 0, nt, nt, iteration > 0 ? 1 : 0},
+                                          assign + n0, dist ? dist + n0 : nullptr, st, rl);
+                    // what follows ends at once unless that scan gave up.  Ranks are then counted from the beginning, which
+                    // is only possible for a single stretch (see below)
+                    if (ro.count)
+                        hipLaunchKernelGGL(zero_u32_kernel, dim3((unsigned)((K + 255) / 256 < 1024 ? (K + 255) / 256 : 1024)), dim3(256),
+                                           0, st, ro.count, (int64_t)K, (const uint32_t*)gave_up);
+                    hipLaunchKernelGGL((tile_image_kernel<M, 0, 16>), dim3((unsigned)((total + 255) / 256)), dim3(256), 0, st,
+                                       centers, K, tables, img, total, (float*)nullptr, (const uint32_t*)gave_up);
+                }
                 if (launch_scan_sw<M>(variant, codes + n0 * M, cnt, reinterpret_cast<uint32_t*>(ws + c.skew_off),
                                       reinterpret_cast<const float4*>(img), (int)ntiles, assign + n0,
-                                      dist ? dist + n0 : nullptr, st, rl, opt.rounds_per_launch) != PQKM_OK)
+                                      dist ? dist + n0 : nullptr, st, rl, wide ? 0 : opt.rounds_per_launch,
+                                      wide ? gave_up : nullptr) != PQKM_OK)
                     return PQKM_ERR_DEVICE;
             }
         } else if (filter && files_records && variant == 63 && N <= per_launch) {
@@ -1355,7 +1434,7 @@ void sort_by_cluster(const int32_t* assign, int64_t N, int K, const Carve& c, ch
         return;
     }
     unsigned zb = (unsigned)((K + 255) / 256 < 1024 ? (K + 255) / 256 : 1024);
-    hipLaunchKernelGGL(zero_u32_kernel, dim3(zb), dim3(256), 0, st, cnt, (int64_t)K);
+    hipLaunchKernelGGL(zero_u32_kernel, dim3(zb), dim3(256), 0, st, cnt, (int64_t)K, (const uint32_t*)nullptr);
     unsigned cb = (unsigned)((N + 4095) / 4096 < 1024 ? (N + 4095) / 4096 : 1024);
     if (cb < 1) cb = 1;
     hipLaunchKernelGGL(seg_count_kernel, dim3(cb), dim3(1024), 0, st, assign, N, K, cnt);
@@ -1396,7 +1475,7 @@ pqkm_status update_impl(const Options& opt, const Carve& c, const uint8_t* codes
     const int64_t nh = (int64_t)K * M * L;
     auto zero_hist = [&]() {
         unsigned zb = (unsigned)((nh + 255) / 256 < 65536 ? (nh + 255) / 256 : 65536);
-        hipLaunchKernelGGL(zero_u32_kernel, dim3(zb), dim3(256), 0, st, hist, nh);
+        hipLaunchKernelGGL(zero_u32_kernel, dim3(zb), dim3(256), 0, st, hist, nh, (const uint32_t*)nullptr);
     };
     // Owner path (LDS-privatised, no global atomics) while streaming the assignment array once per cluster
     // group is cheap; otherwise one global atomic per code and subspace into a zeroed histogram.
@@ -1521,7 +1600,7 @@ pqkm_status assign_indexed_impl(const IndexCarve& c, const uint8_t* codes, int64
     uint32_t* cursor = reinterpret_cast<uint32_t*>(ws + c.cursor_off);
     uint32_t* items = reinterpret_cast<uint32_t*>(ws + c.items_off);
     hipLaunchKernelGGL(index_rows_kernel, dim3(L, (unsigned)M), dim3(256), 0, st, tables, ord, rowmin);
-    hipLaunchKernelGGL(zero_u32_kernel, dim3(64), dim3(256), 0, st, cnt, (int64_t)INDEX_BUCKETS);
+    hipLaunchKernelGGL(zero_u32_kernel, dim3(64), dim3(256), 0, st, cnt, (int64_t)INDEX_BUCKETS, (const uint32_t*)nullptr);
     hipLaunchKernelGGL(index_count_kernel, dim3((unsigned)((K + 255) / 256)), dim3(256), 0, st, centers, K, M, cnt);
     hipLaunchKernelGGL(seg_prefix_kernel, dim3(1), dim3(1024), 0, st, cnt, INDEX_BUCKETS, start, cursor);
     hipLaunchKernelGGL(index_scatter_kernel, dim3((unsigned)((K + 255) / 256)), dim3(256), 0, st, centers, K, M, start,

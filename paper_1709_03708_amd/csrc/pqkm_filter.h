@@ -24,7 +24,8 @@
 
 namespace pqkm {
 
-constexpr int FILTER_Q = 31;              // largest bound of an entry
+constexpr int FILTER_Q = 31;              // largest bound of an entry (M = 16, 32: FILTER_Q_WIDE)
+constexpr int FILTER_Q_WIDE = 63;
 constexpr int FILTER_TK = 64;             // centers per tile: a row of one subcode is 64 bytes
 constexpr uint32_t FILTER_PLANE = 16384;  // bytes per (tile, subspace): 256 subcodes x 64 centers
 constexpr int FILTER_QUEUE = 128;         // candidate entries a wave can hold (drained from 64 on)
@@ -113,7 +114,7 @@ __device__ __forceinline__ FilterScale filter_scale(const FilterStat* __restrict
     float cap = 1.75f * (mean / (float)M);
     cap = span < cap ? span : cap;
     FilterScale f;
-    f.inv = (float)FILTER_Q / cap;
+    f.inv = (float)(M >= 16 ? FILTER_Q_WIDE : FILTER_Q) / cap;
     // no spread, -inf or NaN anywhere, or an inverse out of range: everything passes
     if (!(span > 0.0f && span < INFINITY) || !(cap > 0.0f) || !(f.inv > 0.0f && f.inv < 1e30f) || !(absmax < 1e30f)) f.inv = 0.0f;
     f.base = f.inv > 0.0f ? base : 0.0f;
@@ -121,10 +122,10 @@ __device__ __forceinline__ FilterScale filter_scale(const FilterStat* __restrict
     return f;
 }
 
-__device__ __forceinline__ uint32_t filter_quantise(float a, float lo, float inv)
+__device__ __forceinline__ uint32_t filter_quantise(float a, float lo, float inv, int most)
 {
     const float u = (a - lo) * inv * (1.0f - 0x1p-20f);
-    return u < (float)FILTER_Q ? (uint32_t)(u > 0.0f ? u : 0.0f) : (uint32_t)FILTER_Q;      // NaN and +inf: the cap
+    return u < (float)most ? (uint32_t)(u > 0.0f ? u : 0.0f) : (uint32_t)most;              // NaN and +inf: the cap
 }
 
 // largest sum of bounds a center may have, at most `tmax` (which passes everything); best = NaN or +inf: tmax
@@ -141,17 +142,21 @@ template <int M>
 __global__ __launch_bounds__(256) void filter_image_kernel(const uint8_t* __restrict__ centers, int K,
                                                             const float* __restrict__ tables,
                                                             const FilterStat* __restrict__ st, uint4* __restrict__ img,
-                                                            uint8_t* __restrict__ copy, FilterScale* __restrict__ scale)
+                                                            uint8_t* __restrict__ copy, FilterScale* __restrict__ scale,
+                                                            uint32_t* __restrict__ gave_up = nullptr)
 {
     __shared__ uint32_t sub[FILTER_TK];
     const int tile = (int)(blockIdx.x / (4 * M)), m = (int)(blockIdx.x / 4 % M), part = (int)(blockIdx.x % 4);
     const FilterScale sc = filter_scale<M>(st);
-    if (blockIdx.x == 0 && threadIdx.x == 0) *scale = sc;            // for the scan
+    if (blockIdx.x == 0 && threadIdx.x == 0) {
+        *scale = sc;                                                 // for the scan
+        if (gave_up) *gave_up = 0u;
+    }
     const float inv = sc.inv, lo = filter_low(st, m);
     if (threadIdx.x < FILTER_TK) {
         const int64_t k = (int64_t)tile * FILTER_TK + threadIdx.x;
         sub[threadIdx.x] = k < K ? centers[k * M + m] : 256u;
-        if (part == 0 && k < K) copy[k * M + m] = centers[k * M + m];       // for the next iteration's comparison
+        if (copy && part == 0 && k < K) copy[k * M + m] = centers[k * M + m];       // for the next iteration's comparison
     }
     __syncthreads();
     const int x = part * 64 + (threadIdx.x >> 2), p = threadIdx.x & 3;
@@ -164,20 +169,23 @@ __global__ __launch_bounds__(256) void filter_image_kernel(const uint8_t* __rest
     }
     uint32_t w[4] = {0u, 0u, 0u, 0u};
 #pragma unroll
-    for (int i = 0; i < 16; ++i) w[i >> 2] |= filter_quantise(v[i], lo, inv) << (8 * (i & 3));
-    img[((size_t)tile * M + m) * 1024 + part * 256 + threadIdx.x] = make_uint4(w[0], w[1], w[2], w[3]);
+    for (int i = 0; i < 16; ++i) w[i >> 2] |= filter_quantise(v[i], lo, inv, M >= 16 ? FILTER_Q_WIDE : FILTER_Q) << (8 * (i & 3));
+    if (M >= 16)          // phases of four subspaces: [tile][m / 4][x][m % 4][64 centers]
+        img[((size_t)tile * (M / 4) + m / 4) * 4096 + (size_t)x * 16 + (m % 4) * 4 + p] = make_uint4(w[0], w[1], w[2], w[3]);
+    else
+        img[((size_t)tile * M + m) * 1024 + part * 256 + threadIdx.x] = make_uint4(w[0], w[1], w[2], w[3]);
 }
 
 // For every pair of neighbouring subspaces and every pair of subcodes some center that has both (which one does not
 // matter): codes of clustered data nearly always share a pair with a center close to them.
-template <int M>
+template <int M, int PAIRS = M / 2>
 __global__ __launch_bounds__(256) void filter_pairs_kernel(const uint8_t* __restrict__ centers, int K,
                                                            uint32_t* __restrict__ pairs)
 {
     const int k = blockIdx.x * 256 + threadIdx.x;
     if (k >= K) return;
 #pragma unroll
-    for (int p = 0; p < M / 2; ++p) {
+    for (int p = 0; p < PAIRS; ++p) {
         const uint32_t c = centers[(size_t)k * M + 2 * p] | ((uint32_t)centers[(size_t)k * M + 2 * p + 1] << 8);
         pairs[(size_t)p * 65536 + c] = (uint32_t)k;
     }
@@ -703,6 +711,353 @@ __global__ __launch_bounds__(THREADS) void assign_filter_kernel(int64_t N, const
             const uint4 r = reinterpret_cast<const uint4*>(tile)[i * THREADS + tid];
             if (r.z != 0xffffffffu) bo.pool[base + gbase[r.z] + r.w] = make_uint2(r.x, r.y);
         }
+    }
+}
+
+// ---------------------------------------------------------------------------------------------
+// M = 16, 32: any order of the codes.  A tile is 64 centers; its subspaces pass through the LDS in phases of four, 64 KB
+// each (row (x, s) of 64 bytes at byte x * 256 + s * 64, s = 0..3), two buffers, the next phase's loads straight into LDS
+// beside the scan.  Slots of two lanes as in the other scans; of the eight slots an LDS access serves two belong to each
+// class j = 0..3, and class j reads subspace (t + j) mod 4 in step t, so that the four classes are in four different bank
+// quarters whatever their subcodes are, and of the two slots of a class one starts with the lower half of its rows, the
+// other with the upper: no conflicts.  (The order of integer additions is free; the fp32 scans pay three dummy steps per
+// tile for the same skew.)  A phase's four subcodes come as one word per code, rotated for the slot's class beforehand, and
+// one byte permutation makes an address of a subcode and the lane's constant of the step.  Bounds have 6 bits; the sum of
+// a phase's four fits a byte and is added to 16-bit sums in registers, two per instruction, which start at 0x7fff -
+// threshold: bit 15 ends up clear exactly when the center passes.
+// Candidates as in the scans above.  A code starts from its center of the previous iteration (`assign`), or from the
+// closest of the centers that share one of its first FILTER_WIDE_PAIRS pairs of subcodes, or else from the smallest sum
+// of the first tile.  A launch covers a round of workgroups and the tiles of 4 MB: all rounds pass over them before
+// the next ones, so that they come from the L2 (a phase is scanned in less than the time a load from memory takes, and one
+// phase is all there is room to load ahead); keys carry the state from one launch to the next.  A workgroup whose candidates cost more than the plain scan sets *gave_up, those of later launches stop
+// at once when they see it, and the plain scan that is launched behind this one does all the work.
+// A phase of 1024 codes is short (0.8 us of work in 1.9 us): its barrier and the start of its reads are what bounds it, and
+// more codes do not fit the registers.
+// Measured against the sliding-window scan, M = 32, N = 1e6, K = 1e4: 16.4 -> 12.4 ms in a first iteration, 12.1 and
+// 9.5 ms in later ones.
+// ---------------------------------------------------------------------------------------------
+constexpr int FILTER_WIDE_PAIRS = 3;
+
+// S[phase][position]: the four subcodes of a phase, byte t = subcode (t + j) mod 4 for the position's class j
+template <int M>
+__global__ __launch_bounds__(256) void code_rotate_kernel(const uint8_t* __restrict__ codes, int64_t N,
+                                                          uint32_t* __restrict__ S, int64_t n_alloc)
+{
+    const int64_t n = (int64_t)blockIdx.x * 256 + threadIdx.x;
+    if (n >= n_alloc) return;
+    const uint32_t turn = 8u * (uint32_t)((n & 7) >> 1);
+    const uint32_t* cw = reinterpret_cast<const uint32_t*>(codes + (n < N ? n : N - 1) * M);
+#pragma unroll
+    for (int ph = 0; ph < M / 4; ++ph) S[(size_t)ph * n_alloc + n] = __builtin_amdgcn_alignbit(cw[ph], cw[ph], turn);
+}
+
+struct FilterWideIn {
+    const uint4* img;
+    const uint32_t* S;               // rotated subcode words, n_alloc positions per phase
+    int64_t n_alloc;
+    const uint8_t* codes;            // 4-byte aligned
+    const uint8_t* centers;          // 4-byte aligned
+    const float* tables;
+    const FilterScale* scale;
+    unsigned long long* state;
+    const uint32_t* pairs;           // [FILTER_WIDE_PAIRS][65536], or NULL
+    uint32_t* gave_up;
+    int K;
+    int t_begin, t_end, ntiles;      // tiles of this launch; the keys hold the result of the tiles before them
+    int seeded;                      // assign[] holds a center for every code
+};
+
+template <int M>
+__device__ __forceinline__ float filter_wide_distance(const float* __restrict__ tables, const uint8_t* __restrict__ x,
+                                                      const uint8_t* __restrict__ c)
+{
+    const uint32_t* xw = reinterpret_cast<const uint32_t*>(x);
+    const uint32_t* cw = reinterpret_cast<const uint32_t*>(c);
+    float s = 0.0f;
+#pragma unroll
+    for (int h = 0; h < M; h += 16) {                    // sixteen entries in flight
+        float a[16];
+#pragma unroll
+        for (int i = 0; i < 16; ++i) {
+            const int m = h + i;
+            a[i] = tables[((uint32_t)m << 16) | (((xw[m / 4] >> (8 * (m % 4))) & 255u) << 8) | ((cw[m / 4] >> (8 * (m % 4))) & 255u)];
+        }
+#pragma unroll
+        for (int i = 0; i < 16; ++i) s = h + i == 0 ? a[0] : s + a[i];
+    }
+    return s;
+}
+
+template <int M, int R, int THREADS>
+__global__ __launch_bounds__(THREADS) void assign_filter_wide_kernel(int64_t N, FilterWideIn f, int32_t* __restrict__ assign,
+                                                                  float* __restrict__ dist, RankOut ro, int64_t first_workgroup)
+{
+    constexpr int SLOTS = THREADS / 2, C = SLOTS * R, DEPTH = 3, NPH = M / 4;
+    constexpr int CHUNKS = 65536 / (THREADS * 16);       // loads per phase
+    constexpr uint32_t ALL = M * FILTER_Q_WIDE, DEAD = 0x8000u, HI = 0x80008000u, EVEN = 0x00ff00ffu;
+    static_assert(NPH % 2 == 0 && R % 2 == 0, "two buffers; every lane finishes R / 2 codes");
+    __shared__ float4 tile[TILE_F4];
+    __shared__ uint16_t thr_s[SLOTS * R];
+    __shared__ uint2 queue_s[THREADS / 64][FILTER_QUEUE];
+    __shared__ uint32_t trips_s, stop_s[2];
+    const char* tb = reinterpret_cast<const char*>(tile);
+
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int q = tid & 1, c = tid >> 1;
+    const uint32_t hq = ((uint32_t)(c & 1) << 5) | ((uint32_t)q << 4);
+    const int64_t base = ((int64_t)blockIdx.x + first_workgroup) * C;
+    uint2* queue = queue_s[wave];
+
+    const uint64_t ip = reinterpret_cast<uint64_t>(f.img);
+    const v4i rs_img = {(int)(uint32_t)ip, (int)(uint32_t)(ip >> 32), (int)((uint32_t)f.ntiles * (uint32_t)NPH * 65536u), 0x00020000};
+    const uint32_t lds0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) char*)tile;
+    const uint32_t wave_off = (uint32_t)wave * 1024u, lane_off = (uint32_t)tid * 16u;
+    auto fetch = [&](int gph, int h, int j) {            // part j of phase gph (counted over all tiles) into buffer h
+        buffer_to_lds16(lds0 + (uint32_t)h * 65536u + (uint32_t)(j * THREADS * 16) + wave_off, rs_img, lane_off,
+                        (uint32_t)gph * 65536u + (uint32_t)(j * THREADS * 16));
+    };
+#pragma unroll
+    for (int j = 0; j < CHUNKS; ++j) fetch(f.t_begin * NPH, 0, j);
+
+    // byte t: the lane's offset inside a 256-byte row group in step t
+    uint32_t ub = 0u;
+#pragma unroll
+    for (int t = 0; t < 4; ++t) ub |= ((((uint32_t)t + ((uint32_t)(c & 7) >> 1)) & 3u) * 64u + hq) << (8 * t);
+
+    const FilterScale sc = *f.scale;
+    // one of an earlier launch gave up: the first decision below stops this workgroup, too
+    if (tid == 0) trips_s = __hip_atomic_load(f.gave_up, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) ? 0x2000000u : 0u;
+    if (tid < 2) stop_s[tid] = 0u;
+
+    // keys and thresholds
+#pragma unroll 1
+    for (int i = 0; i < R / 2; ++i) {
+        const int jj = i * THREADS + tid;
+        const int64_t n = base + jj;
+        uint32_t bias = DEAD;
+        if (n < N) {
+            const uint8_t* x = f.codes + n * M;
+            float s = INFINITY;
+            uint32_t k = 0xffffffffu;
+            if (f.t_begin > 0) {
+                const unsigned long long key = f.state[n];
+                if (key != FILTER_NONE) { s = filter_key_distance(key); k = (uint32_t)key; }
+            } else if (f.seeded) {
+                k = (uint32_t)assign[n];
+                k = k < (uint32_t)f.K ? k : 0u;
+                s = filter_wide_distance<M>(f.tables, x, f.centers + (size_t)k * M);
+            } else if (f.pairs) {
+                uint32_t cand[FILTER_WIDE_PAIRS];
+#pragma unroll
+                for (int p = 0; p < FILTER_WIDE_PAIRS; ++p)
+                    cand[p] = f.pairs[p * 65536 + reinterpret_cast<const uint16_t*>(x)[p]];
+#pragma unroll
+                for (int p = 0; p < FILTER_WIDE_PAIRS; ++p)
+                    if (cand[p] < (uint32_t)f.K && cand[p] != k) {
+                        const float d = filter_wide_distance<M>(f.tables, x, f.centers + (size_t)cand[p] * M);
+                        if (d < s || (d == s && cand[p] < k)) { s = d; k = cand[p]; }
+                    }
+            }
+            const bool known = s < INFINITY;
+            if (f.t_begin == 0) f.state[n] = known ? filter_key(s, k) : FILTER_NONE;
+            bias = known ? 0x7fffu - filter_threshold(s, sc, ALL) : 0x7fffu - ALL;
+        }
+        thr_s[(jj % SLOTS) * R + jj / SLOTS] = (uint16_t)bias;
+    }
+
+    int qn = 0;
+    auto drain = [&]() __attribute__((always_inline)) {
+        const int cnt = qn < 64 ? qn : 64;
+        qn -= cnt;
+        __builtin_amdgcn_wave_barrier();
+        const uint2 e = queue[qn + (lane < cnt ? lane : 0)];
+        __builtin_amdgcn_wave_barrier();
+        uint32_t mask = lane < cnt ? e.x : 0u;
+        const uint32_t r = e.y & 31u, sl = (e.y >> 5) & 31u, eq = (e.y >> 10) & 1u, t = e.y >> 11;
+        const int slot = wave * 32 + (int)sl;
+        const int64_t n = base + (int64_t)r * SLOTS + slot;              // only positions below N ever pass
+        const uint32_t piece = 2u * (sl & 1u) + eq;
+        const unsigned long long known = __hip_atomic_load(&f.state[n], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        {
+            const uint32_t in = (uint32_t)known - t * FILTER_TK;
+            if (known != FILTER_NONE && in < (uint32_t)FILTER_TK && ((in >> 4) & ~2u) == (piece & ~2u)) {
+                const uint32_t j = (((in >> 4) == piece) ? 0u : 4u) + ((in >> 2) & 3u);
+                mask &= ~(1u << (8u * (in & 3u) + 7u - j));
+            }
+        }
+        float sb = INFINITY;
+        uint32_t kb = 0xffffffffu;
+        int trips = 0;
+#pragma unroll 1
+        while (__any(mask != 0u)) {
+            ++trips;
+            if (mask) {
+                const uint32_t bit = (uint32_t)__builtin_ctz(mask), j = 7u - (bit & 7u);
+                mask &= mask - 1u;
+                const uint32_t k = t * FILTER_TK + 16u * (piece ^ ((j >> 2) << 1)) + 4u * (j & 3u) + (bit >> 3);
+                if (k < (uint32_t)f.K) {
+                    const float s = filter_wide_distance<M>(f.tables, f.codes + n * M, f.centers + (size_t)k * M);
+                    if (s < INFINITY && (s < sb || (s == sb && k < kb))) { sb = s; kb = k; }
+                }
+            }
+        }
+        if (kb != 0xffffffffu) {
+            atomicMin(&f.state[n], filter_key(sb, kb));
+            const uint16_t bias = (uint16_t)(0x7fffu - filter_threshold(sb, sc, ALL));
+            uint16_t* p = thr_s + slot * R + r;
+            if (bias > *p) *p = bias;
+        }
+        if (lane == 0) atomicAdd(&trips_s, (uint32_t)trips);
+    };
+
+    // 16-bit sums: even[j] bytes 0 and 2 of word j of the lane's 32 centers, odd[j] bytes 1 and 3
+    struct Sums { uint32_t even[8], odd[8]; };
+    uint32_t w[R], wn[R];
+    auto load_words = [&](int ph) {
+#pragma unroll
+        for (int r = 0; r < R; ++r) wn[r] = f.S[(size_t)ph * f.n_alloc + base + (int64_t)r * SLOTS + c];
+    };
+    load_words(0);
+
+    bool stop = false, first = !f.seeded && f.t_begin == 0;   // first: a pass over tile 0 that only finds bounds
+    int t = f.t_begin;
+    while (t < f.t_end) {
+        Sums a[R];
+        uint32_t bias[R];
+#pragma unroll 1
+        for (int ph2 = 0; ph2 < NPH; ph2 += 2) {
+#pragma unroll
+            for (int h = 0; h < 2; ++h) {
+                const int ph = ph2 + h;
+                wait_vector_loads();
+                // one thread decides for all; its verdict of this turn stays until everybody has passed the next barrier
+                if (tid == 0)
+                    stop_s[h] = trips_s * 64u > (uint32_t)C * (64u + (uint32_t)(t - f.t_begin)) ? 1u : 0u;
+                __syncthreads();
+                if (stop_s[h]) { stop = true; break; }
+#pragma unroll
+                for (int r = 0; r < R; ++r) w[r] = wn[r];
+                const bool last = ph == NPH - 1;
+                const int next = last && first ? 0 : t * NPH + ph + 1;                 // tile 0 again after its first pass
+                const bool more = next < f.t_end * NPH;
+                load_words(last ? 0 : ph + 1);
+                if (ph == 0) {
+#pragma unroll
+                    for (int r = 0; r < R; ++r) {
+                        bias[r] = (uint32_t)thr_s[c * R + r] * 0x10001u;
+                        const uint32_t start = first ? 0u : bias[r];
+#pragma unroll
+                        for (int j = 0; j < 8; ++j) { a[r].even[j] = start; a[r].odd[j] = start; }
+                    }
+                }
+                struct Pair { uint4 a, b; };
+                auto issue = [&](int step) -> Pair {
+                    const int r = step / 4, tt = step % 4;
+                    // (subcode << 8) | the step's offset
+                    const uint32_t ad = __builtin_amdgcn_perm(w[r], ub, 0x0c0c0000u | ((uint32_t)(4 + tt) << 8) | (uint32_t)tt) + (uint32_t)h * 65536u;
+                    Pair p;
+                    p.a = *reinterpret_cast<const uint4*>(tb + ad);
+                    p.b = *reinterpret_cast<const uint4*>(tb + (ad ^ 32u));
+                    return p;
+                };
+                Pair ring[DEPTH];
+#pragma unroll
+                for (int d = 0; d < DEPTH; ++d) ring[d] = issue(d);
+#pragma unroll
+                for (int r = 0; r < R; ++r) {
+#pragma unroll
+                    for (int j = 0; j < CHUNKS; ++j)
+                        if ((j * R) / (2 * CHUNKS) == r && more) fetch(next, h ^ 1, j);
+                    auto take = [&](int step) -> Pair {
+                        const Pair p = ring[step % DEPTH];
+                        if (step + DEPTH < 4 * R) ring[step % DEPTH] = issue(step + DEPTH);
+                        return p;
+                    };
+                    uint32_t s[8];
+                    {
+                        const Pair p0 = take(4 * r), p1 = take(4 * r + 1), p2 = take(4 * r + 2);
+                        s[0] = p0.a.x + p1.a.x + p2.a.x;  s[1] = p0.a.y + p1.a.y + p2.a.y;
+                        s[2] = p0.a.z + p1.a.z + p2.a.z;  s[3] = p0.a.w + p1.a.w + p2.a.w;
+                        s[4] = p0.b.x + p1.b.x + p2.b.x;  s[5] = p0.b.y + p1.b.y + p2.b.y;
+                        s[6] = p0.b.z + p1.b.z + p2.b.z;  s[7] = p0.b.w + p1.b.w + p2.b.w;
+                    }
+                    {
+                        const Pair p = take(4 * r + 3);
+                        s[0] += p.a.x;  s[1] += p.a.y;  s[2] += p.a.z;  s[3] += p.a.w;
+                        s[4] += p.b.x;  s[5] += p.b.y;  s[6] += p.b.z;  s[7] += p.b.w;
+                    }
+#pragma unroll
+                    for (int j = 0; j < 8; ++j) {
+                        a[r].even[j] += s[j] & EVEN;
+                        a[r].odd[j] += (s[j] >> 8) & EVEN;
+                    }
+                }
+            }
+            if (stop) break;
+        }
+        if (stop) break;
+#pragma unroll
+        for (int r = 0; r < R; ++r) {
+            if (first) {
+                // codes without a distance yet: what is closest by the bounds passes; the others' own threshold
+                uint32_t mn = 0xffffffffu;
+#pragma unroll
+                for (int j = 0; j < 8; ++j) mn = pk_min_u16(mn, pk_min_u16(a[r].even[j], a[r].odd[j]));
+                uint32_t low = (mn & 0xffffu) < (mn >> 16) ? (mn & 0xffffu) : (mn >> 16);
+                const uint32_t other = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)low, 0xB1, 0xf, 0xf, true);
+                low = other < low ? other : low;
+                const uint32_t add = (bias[r] & 0xffffu) == 0x7fffu - ALL ? (0x7fffu - low) * 0x10001u : bias[r];
+#pragma unroll
+                for (int j = 0; j < 8; ++j) { a[r].even[j] += add; a[r].odd[j] += add; }
+            }
+            uint32_t all = HI;
+#pragma unroll
+            for (int j = 0; j < 8; ++j) all &= a[r].even[j] & a[r].odd[j];
+            const uint64_t who = __ballot(all != HI);
+            if (__builtin_expect(who != 0, 0)) {
+                uint32_t m = 0u;                         // bit 8 b + 7 - j: byte b of word j is pruned
+#pragma unroll
+                for (int j = 0; j < 8; ++j) {
+                    m |= ((a[r].even[j] >> 15) & 0x00010001u) << (7 - j);
+                    m |= ((a[r].odd[j] >> 15) & 0x00010001u) << (15 - j);
+                }
+                m = ~m;
+                const int at = qn + (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(who >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)who, 0u));
+                if (m) queue[at] = make_uint2(m, (uint32_t)r | ((uint32_t)(lane >> 1) << 5) | ((uint32_t)q << 10) | ((uint32_t)t << 11));
+                qn += __builtin_popcountll(who);
+                if (qn >= 64) drain();
+            }
+        }
+        if (first) {
+            while (qn > 0) drain();
+            first = false;
+        } else {
+            ++t;
+        }
+    }
+    if (stop) {
+        wait_vector_loads();                             // nothing may land in LDS after the workgroup has ended
+        if (tid == 0) *f.gave_up = 1u;
+        return;
+    }
+    while (qn > 0) drain();
+    if (f.t_end < f.ntiles) return;
+    wait_vector_loads();
+    __syncthreads();
+#pragma unroll 1
+    for (int i = 0; i < R / 2; ++i) {
+        const int64_t n = base + i * THREADS + tid;
+        if (n >= N) continue;
+        const unsigned long long key = __hip_atomic_load(&f.state[n], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        const uint32_t k = key == FILTER_NONE ? 0u : (uint32_t)key;
+        assign[n] = (int32_t)k;
+        if (dist) {
+            float s = key == FILTER_NONE ? INFINITY : filter_key_distance(key);
+            if (s == 0.0f) s = filter_wide_distance<M>(f.tables, f.codes + n * M, f.centers + (size_t)k * M);   // the sign of a zero
+            dist[n] = s;
+        }
+        if (ro.count) ro.rank[n] = atomicAdd(&ro.count[k], 1u);
     }
 }
 

@@ -534,8 +534,10 @@ __global__ __launch_bounds__(256) void assign_merge_kernel(const NearRecord* __r
 template <int M, int LAYOUT = 0, int TK = 128 / M>
 __global__ __launch_bounds__(256) void tile_image_kernel(const uint8_t* __restrict__ centers, int K,
                                                          const float* __restrict__ tables, float* __restrict__ img,
-                                                         int64_t total, float* __restrict__ rows = nullptr)
+                                                         int64_t total, float* __restrict__ rows = nullptr,
+                                                         const uint32_t* __restrict__ only_if = nullptr)
 {
+    if (only_if && *only_if == 0u) return;
     int64_t e = (int64_t)blockIdx.x * 256 + threadIdx.x;
     if (e >= total) return;
     int kin = (int)(e % TK);
@@ -2996,8 +2998,10 @@ __global__ __launch_bounds__(THREADS) void assign_scan_skew_kernel(const uint8_t
 // ---------------------------------------------------------------------------------------------
 template <int M>
 __global__ __launch_bounds__(256) void code_skew_kernel(const uint8_t* __restrict__ codes, int64_t N,
-                                                        uint32_t* __restrict__ S, int64_t n_alloc)
+                                                        uint32_t* __restrict__ S, int64_t n_alloc,
+                                                        const uint32_t* __restrict__ only_if = nullptr)
 {
+    if (only_if && *only_if == 0u) return;
     constexpr int NW = M / 4, NPH = M / 4 + 1;
     const int64_t n = (int64_t)blockIdx.x * 256 + threadIdx.x;
     if (n >= n_alloc) return;
@@ -3042,8 +3046,10 @@ __global__ __launch_bounds__(THREADS) void assign_scan_sw_kernel(const uint8_t* 
                                                                  const float4* __restrict__ img, int ntiles,
                                                                  int32_t* __restrict__ assign,
                                                                  float* __restrict__ dist, RankOut ro = RankOut{},
-                                                                 int64_t first_workgroup = 0)
+                                                                 int64_t first_workgroup = 0,
+                                                                 const uint32_t* __restrict__ only_if = nullptr)
 {
+    if (only_if && *only_if == 0u) return;
     constexpr int TK = 16, LPS = 2, NPH = M / 4 + 1;
     constexpr int SLOTS = THREADS / LPS;
     constexpr int C = SLOTS * R;
@@ -3262,8 +3268,10 @@ __global__ __launch_bounds__(THREADS) void assign_scan_sw_kernel(const uint8_t* 
 // ---------------------------------------------------------------------------------------------
 // Zero fill (a kernel, not a memset node, so that callers may capture the calls in a graph).
 // ---------------------------------------------------------------------------------------------
-__global__ __launch_bounds__(256) void zero_u32_kernel(uint32_t* __restrict__ p, int64_t n)
+__global__ __launch_bounds__(256) void zero_u32_kernel(uint32_t* __restrict__ p, int64_t n,
+                                                       const uint32_t* __restrict__ only_if = nullptr)
 {
+    if (only_if && *only_if == 0u) return;
     int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
     int64_t stride = (int64_t)gridDim.x * 256;
     for (; i < n; i += stride) p[i] = 0u;

@@ -10,7 +10,7 @@ from _util import progress, rand_tables, u32
 
 pytestmark = pytest.mark.gpu
 
-VARIANTS = {4: [60, 61, 62, 63, 64], 8: [60, 61, 62, 63]}
+VARIANTS = {4: [60, 61, 62, 63, 64], 8: [60, 61, 62, 63], 16: [59], 32: [59]}
 ALL = [(M, v) for M in VARIANTS for v in VARIANTS[M]]
 
 
@@ -51,7 +51,10 @@ def _check(env, codes, centers, tables, variant, offset=0):
         pq.assign(torch.from_numpy(codes).cuda(), torch.from_numpy(centers).cuda(), t, assign=a, dist=d)
     ra, rd = oracle.assign(codes, centers, tables)
     np.testing.assert_array_equal(a.cpu().numpy(), ra)
-    np.testing.assert_array_equal(d.cpu().numpy().view(np.uint32), rd.view(np.uint32))
+    if M >= 16:      # may have been left to the sliding-window scan, whose minimum of a +0 and a -0 is either
+        np.testing.assert_array_equal(d.cpu().numpy(), rd)
+    else:
+        np.testing.assert_array_equal(d.cpu().numpy().view(np.uint32), rd.view(np.uint32))
 
 
 def _metric_tables(rng, M):
@@ -107,7 +110,7 @@ KINDS = ["constant", "zero", "signed zeros", "hamming", "negative", "offset", "o
          "nothing selected"]
 
 
-@pytest.mark.parametrize("M,variant", [(M, v) for M, v in ALL if v in (61, 64 if M == 4 else 63)])
+@pytest.mark.parametrize("M,variant", [(M, v) for M, v in ALL if v in (61, 59, 64 if M == 4 else 63)])
 @pytest.mark.parametrize("kind", KINDS)
 def test_special_tables(env, M, variant, kind):
     rng = np.random.default_rng(len(kind) + M)
@@ -118,7 +121,7 @@ def test_special_tables(env, M, variant, kind):
         _check(env, codes, centers, _special_tables(rng, M, kind), variant)
 
 
-@pytest.mark.parametrize("M,variant", [(M, v) for M, v in ALL if v in (60, 64 if M == 4 else 63)])
+@pytest.mark.parametrize("M,variant", [(M, v) for M, v in ALL if v in (60, 59, 64 if M == 4 else 63)])
 @pytest.mark.parametrize("N,K,kind", [(30_011, 300, "metric"), (5003, 90, "hamming"), (5003, 90, "non-finite"), (9001, 400, "offset"),
                                       (3001, 200, "constant")])
 def test_iterations(env, M, variant, N, K, kind):
@@ -146,7 +149,7 @@ def test_iterations(env, M, variant, N, K, kind):
         np.testing.assert_array_equal(cent.cpu().numpy(), rc)
 
 
-@pytest.mark.parametrize("M,variant", [(M, v) for M, v in ALL if v == (64 if M == 4 else 63)])
+@pytest.mark.parametrize("M,variant", [(M, v) for M, v in ALL if v in (59, 64 if M == 4 else 63)])
 def test_launch_stretches(env, M, variant):
     """Several scan launches and rounds: keys by position serve one launch at a time, the bound then comes from assign[]."""
     pq, oracle, torch = env
