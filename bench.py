@@ -13,10 +13,13 @@ resident in HBM before the timed region.
 
 Prints ONE JSON line.  `value` is code-center SDC evaluations per second over the whole step
 (N*K / time per iteration, update included); `assign_evals_per_s` counts the scan kernel alone.
-`roofline` is for the dominant kernel, the LDS-tiled assignment scan: achieved = N*K*M table
-lookups of 4 bytes per launch / the kernel's average duration (HIP events recorded by the
+`roofline` is for the dominant kernel, the LDS-tiled assignment scan: achieved = the bytes its N*K*M
+look-ups read from LDS per launch / the kernel's average duration (HIP events recorded by the
 library on the stream the kernel runs on), against the LDS gather peak of the chip
-(256 CUs x 2.4 GHz x 256 B/clk); `roofline.assign_step_frac` is the same work over the time of the
+(256 CUs x 2.4 GHz x 256 B/clk).  A look-up of the plain scans reads a 4-byte table entry, one of the
+scans through lower bounds the entry's one-byte bound (`roofline.bytes_per_lookup`; the fp32 distances of
+the few centers that the bounds leave are formed from the tables through the L2 and not counted);
+`roofline.assign_step_frac` is the same work over the time of the
 whole assignment step (tile images and regrouping of the codes included).  `configs` holds the
 same figures for the other configurations (a few steps each).  `cpu_baseline` is the CPU
 oracle timed on the host cores, once on all of them and once on one thread.
@@ -45,7 +48,7 @@ LDS_PEAK_GBS = 256 * 2.4e9 * 256 / 1e9          # 157286 GB/s: 256 CUs x 2.4 GHz
 HBM_PEAK_GBS = 8000.0
 
 
-FP32_VALU_PEAK_TFLOPS = 157.3                    # published fp32 vector peak (fused multiply-adds, packed)
+BF16_MFMA_PEAK_TFLOPS = 2500.0                   # published dense bf16 matrix peak
 
 
 def encoder_bench(args, w, pq, torch, dev) -> int:
@@ -70,14 +73,14 @@ def encoder_bench(args, w, pq, torch, dev) -> int:
     e1.record()
     torch.cuda.synchronize()
     ms = e0.elapsed_time(e1) / steps
-    flops = 3.0 * n * w.D * 256                    # one subtraction and one fused multiply-add per (vector, codeword, dim)
+    flops = 3 * 2.0 * n * w.D * 256                # three bf16 products per (vector, codeword, dim): two-part splits
     tflops = flops / (ms * 1e-3) / 1e12
     print(json.dumps({
         "metric": "PQ encoding (Sec. 2.2), vectors/s", "value": n / (ms * 1e-3), "unit": "vectors/s", "n_gpus": 1,
         "steps": steps, "ms_per_step": ms, "dtype": "f32", "data": "synthetic",
         "config": {"workload": f"encoder, config {args.config} shape: {n} vectors, D={w.D}, M={w.M}, Ds={Ds}, L=256"},
-        "roofline": {"bound": "alu", "kernel": "encode_kernel", "achieved": tflops, "peak": FP32_VALU_PEAK_TFLOPS,
-                     "unit": "TFLOP/s", "frac": tflops / FP32_VALU_PEAK_TFLOPS, "traffic": None},
+        "roofline": {"bound": "mfma", "kernel": "encode_mfma_kernel", "achieved": tflops, "peak": BF16_MFMA_PEAK_TFLOPS,
+                     "unit": "TFLOP/s", "frac": tflops / BF16_MFMA_PEAK_TFLOPS, "traffic": None},
         "hbm_gbs": n * w.D * 4 / (ms * 1e-3) / 1e9}))
     return 0
 
@@ -326,7 +329,7 @@ def measure(args, cfg, steps, warmup, pq, W, torch, dev, t_start=None, budget=0.
     scan_ms = scan_ms_total / max(scan_launches, 1)
     launches_per_step = scan_launches / steps
     lookups_per_launch = evals * M / launches_per_step
-    achieved_gbs = lookups_per_launch * 4 / (scan_ms * 1e-3) / 1e9
+    achieved_gbs = lookups_per_launch * bytes_per_lookup(w) / (scan_ms * 1e-3) / 1e9
     assign_step_ms = step_ms_total / max(assign_steps, 1)
     return {
         "skipped": False, "w": w, "codes": codes, "tables": tables, "centers0": centers0,
@@ -335,8 +338,14 @@ def measure(args, cfg, steps, warmup, pq, W, torch, dev, t_start=None, budget=0.
         "scan_ms": scan_ms, "scan_ms_total": scan_ms_total, "scan_launches": scan_launches,
         "achieved_gbs": achieved_gbs, "lookups_per_launch": lookups_per_launch,
         "assign_step_ms": assign_step_ms,
-        "assign_step_frac": evals * M * 4 / (assign_step_ms * 1e-3) / 1e9 / LDS_PEAK_GBS,
+        "assign_step_frac": evals * M * bytes_per_lookup(w) / (assign_step_ms * 1e-3) / 1e9 / LDS_PEAK_GBS,
     }
+
+
+def bytes_per_lookup(w) -> float:
+    """LDS bytes per (code, center, subspace) of the scan that runs: 1 through lower bounds, which every iteration takes
+    from a few thousand centers on; at configuration 2 (K = 1000, calls of ten iterations) the first three are plain."""
+    return 1.0 if w.K >= 5000 else (3 * 4.0 + (w.iters - 3) * 1.0) / w.iters if w.iters > 3 else 4.0
 
 
 def workload_label(cfg, w) -> str:
@@ -486,7 +495,8 @@ def main() -> int:
         "config": {"workload": workload_label(cfg, w),
                    "N": N, "M": M, "K": K, "iterations_timed": args.steps, "fit_calls": r["fit_calls"],
                    "iterations_per_fit_call": w.iters, "prewarm_s": round(r["prewarm_s"], 3)},
-        "roofline": {"bound": "lds", "kernel": "assign_scan (LDS-tiled linear scan, Eq. 5)",
+        "roofline": {"bound": "lds", "kernel": "assign_filter / assign_scan (LDS-tiled linear scan, Eq. 5)",
+                     "bytes_per_lookup": bytes_per_lookup(w),
                      "achieved": r["achieved_gbs"], "peak": LDS_PEAK_GBS, "unit": "GB/s",
                      "frac": r["achieved_gbs"] / LDS_PEAK_GBS, "traffic": traffic, "traffic_source": traffic_src,
                      "avg_kernel_ms": r["scan_ms"], "launches": r["scan_launches"],
