@@ -870,7 +870,7 @@ pqkm_status regroup_codes8(const uint8_t* codes, int64_t cnt, uint4* gc8, GroupP
     const int64_t na = group_alloc(cnt);
     if (blocks_of_16)
         hipLaunchKernelGGL(code8_group_clear_kernel, dim3(1024), dim3(256), 0, st, gc8, na);
-    hipLaunchKernelGGL(zero_u32_kernel, dim3(64), dim3(256), 0, st, plan->count, (int64_t)GROUP8_CLASSES, (const uint32_t*)nullptr);
+    hipLaunchKernelGGL(zero_u32_kernel, dim3(64), dim3(256), 0, st, plan->count, (int64_t)GROUP8_CLASSES);
     unsigned g = (unsigned)((cnt + 1023) / 1024 < 4096 ? (cnt + 1023) / 1024 : 4096);
     if (g < 1) g = 1;
     hipLaunchKernelGGL(code8_class_count_kernel, dim3(g), dim3(256), 0, st, codes, cnt, plan);
@@ -1059,8 +1059,9 @@ struct BucketLink {
     bool rank_wanted = false, ranked = false;
 };
 
-// M = 16, 32: is the lower-bound scan tried before the sliding-window scan?  (Ranks of several stretches could not be taken
-// back when a later one gives up, so a fused iteration of more codes than one launch keeps the plain scan: see the caller.)
+// M = 16, 32: is the lower-bound scan tried before the sliding-window scan?  (Neither then leaves ranks for the histogram:
+// those of a scan that gave up could not be taken back.  The update's own counting and block-wise scatter take as long as
+// placing the codes by rank.)
 constexpr int FILTER_WIDE_PAIRS_MIN_K = 500;
 // Fewest centers, by iteration, as for M = 4.  Measured at N = 1e6 against the sliding-window scan, ms per iteration, M = 32:
 // first 5.1 / 3.8 at K = 2000, 12.4 / 16.4 at 10000; second and third 5.0 / 3.95 and 12.1 / 17.3; later 3.4 / 3.95 and
@@ -1080,7 +1081,7 @@ inline bool wide_filter(int M, int asked, int variant, int64_t N, int K, const u
 
 template <int M>
 void launch_filter_wide(const uint8_t* codes, int64_t N, uint32_t* S, FilterWideIn f, int32_t* assign, float* dist,
-                        hipStream_t st, RankOut ro)
+                        hipStream_t st)
 {
     const int ncu = cu_count();
     constexpr int64_t C = 1024;                          // more codes per workgroup do not fit the registers
@@ -1096,7 +1097,7 @@ void launch_filter_wide(const uint8_t* codes, int64_t N, uint32_t* S, FilterWide
             const unsigned cnt = (unsigned)(nwg - w0 < ncu ? nwg - w0 : ncu);
             f.t_begin = t0;
             f.t_end = f.ntiles - t0 < step ? f.ntiles : t0 + step;
-            hipLaunchKernelGGL((assign_filter_wide_kernel<M, 2, 1024>), dim3(cnt), dim3(1024), 0, st, N, f, assign, dist, ro, w0);
+            hipLaunchKernelGGL((assign_filter_wide_kernel<M, 2, 1024>), dim3(cnt), dim3(1024), 0, st, N, f, assign, dist, w0);
             ++t_scan_kernels;
         }
 }
@@ -1134,8 +1135,7 @@ pqkm_status assign_tiled(const uint8_t* codes, int64_t N, const uint8_t* centers
     // M = 16, 32: the lower-bound scan of every stretch in front of the sliding-window scan, which runs where it gave up.
     // Its statistics live in the histograms' room while the assignment runs, its byte tiles and pair tables in that of the
     // images, which are only built after a scan has given up.
-    const bool wide = sliding && wide_filter(M, opt.scan_variant, variant, N, K, centers, iteration) &&
-                      (!(link && link->rank_wanted) || (N <= GROUP_CHUNK_MAX - 16384 && N <= opt.launch_codes));
+    const bool wide = sliding && wide_filter(M, opt.scan_variant, variant, N, K, centers, iteration);
     FilterStat* const wstat = reinterpret_cast<FilterStat*>(ws + c.hist_off);
     FilterScale* const wscale = reinterpret_cast<FilterScale*>(ws + c.hist_off + 8192);
     uint32_t* const gave_up = reinterpret_cast<uint32_t*>(ws + c.hist_off + 8448);
@@ -1221,11 +1221,11 @@ pqkm_status assign_tiled(const uint8_t* codes, int64_t N, const uint8_t* centers
     // ranks for the sorted-path histogram: from the scans that finish their codes one per lane (the regrouped scans
     // and the sliding-window scan), unless this iteration already hands records over by cluster group
     RankOut ro{};
-    if (link && link->rank_wanted && (grouped || sliding) && !(M == 4 && link->wanted && (variant == 70 || filter) && N <= per_launch)) {
+    if (link && link->rank_wanted && (grouped || sliding) && !wide && !(M == 4 && link->wanted && (variant == 70 || filter) && N <= per_launch)) {
         ro.count = reinterpret_cast<uint32_t*>(ws + c.seg_off);
         ro.rank = reinterpret_cast<uint32_t*>(ws + c.rank_off);
         unsigned zb = (unsigned)((K + 255) / 256 < 1024 ? (K + 255) / 256 : 1024);
-        hipLaunchKernelGGL(zero_u32_kernel, dim3(zb), dim3(256), 0, st, ro.count, (int64_t)K, (const uint32_t*)nullptr);
+        hipLaunchKernelGGL(zero_u32_kernel, dim3(zb), dim3(256), 0, st, ro.count, (int64_t)K);
         link->ranked = true;
     }
     for (int64_t n0 = 0; n0 < N; n0 += per_launch) {
@@ -1260,12 +1260,8 @@ pqkm_status assign_tiled(const uint8_t* codes, int64_t N, const uint8_t* centers
                                           FilterWideIn{reinterpret_cast<const uint4*>(img), nullptr, 0, nullptr, centers, tables, wscale,
                                                        reinterpret_cast<unsigned long long*>(ws + c.state_off),
                                                        pairs ? pair_tab : nullptr, gave_up, K, 0, nt, nt, iteration > 0 ? 1 : 0},
-                                          assign + n0, dist ? dist + n0 : nullptr, st, rl);
-                    // what follows ends at once unless that scan gave up.  Ranks are then counted from the beginning, which
-                    // is only possible for a single stretch (see below)
-                    if (ro.count)
-                        hipLaunchKernelGGL(zero_u32_kernel, dim3((unsigned)((K + 255) / 256 < 1024 ? (K + 255) / 256 : 1024)), dim3(256),
-                                           0, st, ro.count, (int64_t)K, (const uint32_t*)gave_up);
+                                          assign + n0, dist ? dist + n0 : nullptr, st);
+                    // what follows ends at once unless that scan gave up
                     hipLaunchKernelGGL((tile_image_kernel<M, 0, 16>), dim3((unsigned)((total + 255) / 256)), dim3(256), 0, st,
                                        centers, K, tables, img, total, (float*)nullptr, (const uint32_t*)gave_up);
                 }
@@ -1434,7 +1430,7 @@ void sort_by_cluster(const int32_t* assign, int64_t N, int K, const Carve& c, ch
         return;
     }
     unsigned zb = (unsigned)((K + 255) / 256 < 1024 ? (K + 255) / 256 : 1024);
-    hipLaunchKernelGGL(zero_u32_kernel, dim3(zb), dim3(256), 0, st, cnt, (int64_t)K, (const uint32_t*)nullptr);
+    hipLaunchKernelGGL(zero_u32_kernel, dim3(zb), dim3(256), 0, st, cnt, (int64_t)K);
     unsigned cb = (unsigned)((N + 4095) / 4096 < 1024 ? (N + 4095) / 4096 : 1024);
     if (cb < 1) cb = 1;
     hipLaunchKernelGGL(seg_count_kernel, dim3(cb), dim3(1024), 0, st, assign, N, K, cnt);
@@ -1475,7 +1471,7 @@ pqkm_status update_impl(const Options& opt, const Carve& c, const uint8_t* codes
     const int64_t nh = (int64_t)K * M * L;
     auto zero_hist = [&]() {
         unsigned zb = (unsigned)((nh + 255) / 256 < 65536 ? (nh + 255) / 256 : 65536);
-        hipLaunchKernelGGL(zero_u32_kernel, dim3(zb), dim3(256), 0, st, hist, nh, (const uint32_t*)nullptr);
+        hipLaunchKernelGGL(zero_u32_kernel, dim3(zb), dim3(256), 0, st, hist, nh);
     };
     // Owner path (LDS-privatised, no global atomics) while streaming the assignment array once per cluster
     // group is cheap; otherwise one global atomic per code and subspace into a zeroed histogram.
@@ -1600,7 +1596,7 @@ pqkm_status assign_indexed_impl(const IndexCarve& c, const uint8_t* codes, int64
     uint32_t* cursor = reinterpret_cast<uint32_t*>(ws + c.cursor_off);
     uint32_t* items = reinterpret_cast<uint32_t*>(ws + c.items_off);
     hipLaunchKernelGGL(index_rows_kernel, dim3(L, (unsigned)M), dim3(256), 0, st, tables, ord, rowmin);
-    hipLaunchKernelGGL(zero_u32_kernel, dim3(64), dim3(256), 0, st, cnt, (int64_t)INDEX_BUCKETS, (const uint32_t*)nullptr);
+    hipLaunchKernelGGL(zero_u32_kernel, dim3(64), dim3(256), 0, st, cnt, (int64_t)INDEX_BUCKETS);
     hipLaunchKernelGGL(index_count_kernel, dim3((unsigned)((K + 255) / 256)), dim3(256), 0, st, centers, K, M, cnt);
     hipLaunchKernelGGL(seg_prefix_kernel, dim3(1), dim3(1024), 0, st, cnt, INDEX_BUCKETS, start, cursor);
     hipLaunchKernelGGL(index_scatter_kernel, dim3((unsigned)((K + 255) / 256)), dim3(256), 0, st, centers, K, M, start,

@@ -790,7 +790,7 @@ __device__ __forceinline__ float filter_wide_distance(const float* __restrict__ 
 
 template <int M, int R, int THREADS>
 __global__ __launch_bounds__(THREADS) void assign_filter_wide_kernel(int64_t N, FilterWideIn f, int32_t* __restrict__ assign,
-                                                                  float* __restrict__ dist, RankOut ro, int64_t first_workgroup)
+                                                                  float* __restrict__ dist, int64_t first_workgroup)
 {
     constexpr int SLOTS = THREADS / 2, C = SLOTS * R, DEPTH = 3, NPH = M / 4;
     constexpr int CHUNKS = 65536 / (THREADS * 16);       // loads per phase
@@ -1057,7 +1057,6 @@ __global__ __launch_bounds__(THREADS) void assign_filter_wide_kernel(int64_t N, 
             if (s == 0.0f) s = filter_wide_distance<M>(f.tables, f.codes + n * M, f.centers + (size_t)k * M);   // the sign of a zero
             dist[n] = s;
         }
-        if (ro.count) ro.rank[n] = atomicAdd(&ro.count[k], 1u);
     }
 }
 

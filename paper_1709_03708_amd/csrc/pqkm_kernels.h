@@ -3268,10 +3268,8 @@ __global__ __launch_bounds__(THREADS) void assign_scan_sw_kernel(const uint8_t* 
 // ---------------------------------------------------------------------------------------------
 // Zero fill (a kernel, not a memset node, so that callers may capture the calls in a graph).
 // ---------------------------------------------------------------------------------------------
-__global__ __launch_bounds__(256) void zero_u32_kernel(uint32_t* __restrict__ p, int64_t n,
-                                                       const uint32_t* __restrict__ only_if = nullptr)
+__global__ __launch_bounds__(256) void zero_u32_kernel(uint32_t* __restrict__ p, int64_t n)
 {
-    if (only_if && *only_if == 0u) return;
     int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
     int64_t stride = (int64_t)gridDim.x * 256;
     for (; i < n; i += stride) p[i] = 0u;
