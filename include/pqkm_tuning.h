@@ -29,7 +29,9 @@ extern "C" {
  *                        conflict-free LDS reads when K >= 128 and N exceeds one round of 2048-code
  *                        workgroups, else the subspace-skewed scan in a launch shape chosen by N),
  *                        1..99 = one specific compiled scan and launch shape (for tuning sweeps;
- *                        e.g. 34 = the skewed M = 4 scan without regrouping, 70 = the regrouped one)
+ *                        e.g. 34 = the skewed M = 4 scan without regrouping, 70 = the regrouped one;
+ *                        60 = the scan through lower bounds, M = 4 and 8, 59 the same for M = 16 and 32,
+ *                        65 = the best of the plain M = 4 scans)
  *   "hist_kernel"        0 = choose automatically (default; inside pqkm_fit / pqkm_fit_until with M = 4 this
  *                        includes counting from records the scan files by cluster group), 1 = force one global atomic
  *                        per code and subspace, 2 = force the LDS-privatised histogram over cluster
