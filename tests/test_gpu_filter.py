@@ -171,3 +171,33 @@ def test_launch_stretches(env, M, variant):
     finally:
         pq.set_option("launch_codes_log2", 26)
         pq.set_option("hist_kernel", 0)
+
+
+@pytest.mark.parametrize("M,N,K", [(4, 600_000, 2000), (32, 300_000, 5200)])
+def test_captured_fit(env, M, N, K):
+    """The default scans of these sizes in a captured graph, with eager work and another workspace content between replays."""
+    pq, _, torch = env
+    g = torch.Generator(device="cuda")
+    g.manual_seed(M)
+    T = torch.randint(0, 256, (2 * K, M), generator=g, device="cuda", dtype=torch.uint8)
+    codes = T[torch.randint(0, 2 * K, (N,), generator=g, device="cuda")]
+    fresh = torch.randint(0, 256, (N, M), generator=g, device="cuda", dtype=torch.uint8)
+    codes = torch.where(torch.rand(N, M, generator=g, device="cuda") < 0.2, fresh, codes).contiguous()
+    cent0 = codes[:K].clone()
+    tables = pq.build_tables(torch.randn(M, 256, 8, generator=g, device="cuda"))
+    ws = torch.empty(pq.workspace_bytes(N, M, K), dtype=torch.uint8, device="cuda")
+    eager, a0 = cent0.clone(), torch.full((N,), -1, dtype=torch.int32, device="cuda")
+    pq.fit(codes, tables, eager, 4, assign=a0, workspace=ws)
+    torch.cuda.synchronize()
+    cent, a = cent0.clone(), torch.full((N,), -1, dtype=torch.int32, device="cuda")
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        pq.fit(codes, tables, cent, 4, assign=a, workspace=ws)
+    for rep in range(3):
+        cent.copy_(cent0)
+        a.fill_(-1)
+        ws.fill_(rep + 3)
+        torch.cuda.synchronize()
+        graph.replay()
+        torch.cuda.synchronize()
+        assert torch.equal(cent, eager) and torch.equal(a, a0), f"replay {rep}"
