@@ -62,6 +62,18 @@ pqkm_status pqkm_set_option(const char *name, int32_t value);
 pqkm_status pqkm_profile_read(double *total_ms, int64_t *launches);
 pqkm_status pqkm_profile_read_steps(double *total_ms, int64_t *steps);
 
+/*
+ * pqkm_scan_plan: what the assignment step of iteration `iteration` (from 0) of pqkm_fit runs for N codes against K
+ * centers under the options as they are, for aligned operands: host arithmetic, nothing is launched (without a GPU the
+ * answer is that for 256 compute units).
+ *   out   host, int64[6]: 0 the scan: 0 = one lane per center, 1 = LDS-tiled, 2 = through lower bounds;
+ *         1 its number ("scan_variant"); 2 codes per stretch; 3 lanes per slot that it regroups the codes for (0 = it does
+ *         not); 4 whether it takes over the regrouped copy of the iteration before; 5 where a code's first bound comes
+ *         from (0 = the first tile, 1 = the assignment before, 2 = the key before, 3 = centers that share a pair of subcodes;
+ *         M = 4 and 8 only)
+ */
+pqkm_status pqkm_scan_plan(int64_t N, int32_t M, int32_t K, int32_t iteration, int64_t out[6]);
+
 #ifdef __cplusplus
 }
 #endif

@@ -55,10 +55,11 @@ def load():
         lib.pqkm_encode.argtypes = [vp, i64, i32, i32, vp, vp, vp]
         lib.pqkm_decode.argtypes = [vp, i64, i32, i32, vp, vp, vp]
         lib.pqkm_set_option.argtypes = [ctypes.c_char_p, i32]
+        lib.pqkm_scan_plan.argtypes = [i64, i32, i32, i32, ctypes.POINTER(i64)]
         lib.pqkm_profile_read.argtypes = [ctypes.POINTER(ctypes.c_double), ctypes.POINTER(i64)]
         lib.pqkm_profile_read_steps.argtypes = [ctypes.POINTER(ctypes.c_double), ctypes.POINTER(i64)]
         for n in ("pqkm_build_tables", "pqkm_assign", "pqkm_assign_noalloc", "pqkm_assign_indexed", "pqkm_check", "pqkm_update", "pqkm_fit", "pqkm_fit_until", "pqkm_set_option",
-                  "pqkm_profile_read", "pqkm_profile_read_steps", "pqkm_encode", "pqkm_decode", "pqkm_update_naive"):
+                  "pqkm_scan_plan", "pqkm_profile_read", "pqkm_profile_read_steps", "pqkm_encode", "pqkm_decode", "pqkm_update_naive"):
             getattr(lib, n).restype = ctypes.c_int
         _lib = lib
     return _lib
@@ -331,6 +332,13 @@ def fit_until(codes, tables, centers, max_iters, assign=None, hist=None, counts=
 
 def set_option(name: str, value: int) -> None:
     _check(load().pqkm_set_option(name.encode(), int(value)), f"pqkm_set_option({name})")
+
+
+def scan_plan(N: int, M: int, K: int, iteration: int = 0) -> dict:
+    """What the assignment step of this iteration of a fit runs (host arithmetic, see pqkm_tuning.h)."""
+    out = (ctypes.c_int64 * 6)()
+    _check(load().pqkm_scan_plan(int(N), int(M), int(K), int(iteration), out), "pqkm_scan_plan")
+    return dict(zip(("scan", "variant", "per_launch", "lanes", "reuse", "seeded"), (int(v) for v in out)))
 
 
 def profile_read():

@@ -1102,23 +1102,38 @@ void launch_filter_wide(const uint8_t* codes, int64_t N, uint32_t* S, FilterWide
         }
 }
 
-template <int M>
-pqkm_status assign_tiled(const uint8_t* codes, int64_t N, const uint8_t* centers, int K, const float* tables,
-                         int32_t* assign, float* dist, float* img, const Options& opt, const Carve& c, char* ws,
-                         int iteration, hipStream_t st, BucketLink* link = nullptr)
+// What the iterations of one call (same codes, tables and options) leave in the workspace for the next one.  Successive
+// iterations may run different scans, in stretches of different length, so nothing follows from the iteration's number alone.
+struct Carried {
+    int iteration = 0;        // of the assignment step about to run; > 0: assign[] holds the result of the one before
+    int lanes = 0;            // a regrouped copy of ALL codes, placed for slots of this many lanes (0: there is none)
+    bool stats = false;       // the lower-bound scan's statistics of the tables
+    bool keys = false;        // its keys by position in that copy, and the copy of the centers that they belong to
+};
+
+struct ScanPlan {
+    int variant;
+    bool filter, wide, grouped, sliding;
+    int lanes;                // lanes per slot that the regrouped copy is placed for (grouped)
+    int64_t per_launch;       // codes per stretch
+    bool reuse;               // the regrouped copy is there already
+    int seeded;               // filter: FilterIn::seeded
+    Carried leaves;           // for the next iteration
+};
+
+// Which scan an assignment step runs, in which stretches, and what it can take over from the iteration before: host
+// arithmetic, without a look at the device's memory.
+ScanPlan scan_plan(int M, const Options& opt, int64_t N, int K, const uint8_t* codes, const uint8_t* centers, bool files_records,
+                   const Carve& c, const Carried& had)
 {
-    // iteration > 0: a later iteration of the same call (same codes and tables, assign[] holds the result of the one before)
-    const bool reuse_groups = iteration > 0;
-    constexpr int TK = 128 / M;
-    int64_t ntiles = ((int64_t)K + TK - 1) / TK;
-    int64_t total = ntiles * (int64_t)(TILE_BYTES / 4);
+    ScanPlan p{};
+    const int iteration = had.iteration;
     int variant = effective_variant(M, opt.scan_variant, N, K, codes, centers);
     // No records to file for the histogram: the four-lane scan or the scan with two-lane slots whose tiles are loaded
     // straight into LDS, half a tile ahead, in the shape that the rounds favour
     // Records to file (the fused iteration at owner-path sizes): the same scan in its 4096-code shape, which files
     // them as the four-lane scan does.
-    const bool files_records = M == 4 && link && link->wanted && N <= GROUP_CHUNK_MAX - 16384 && c.bseg_off != c.pool_off;
-    // the lower-bound scan addresses its byte tiles through one 32-bit buffer offset and reads centers as words
+    // The lower-bound scan addresses its byte tiles through one 32-bit buffer offset and reads centers as words.
     const bool filter_ok = (M == 4 || (M == 8 && K > 16)) && ((uintptr_t)centers & 3) == 0 && ((int64_t)K + 63) / 64 * (M * 16384) < (int64_t)0xfff00000;
     if (M == 4 && variant == 70 && opt.scan_variant == 0)
         variant = filter_ok && K >= filter4_min_k(iteration) ? (files_records ? 63 : 60)
@@ -1127,15 +1142,60 @@ pqkm_status assign_tiled(const uint8_t* codes, int64_t N, const uint8_t* centers
         variant = M == 4 ? 85 : 80;
     if (M == 8 && opt.scan_variant == 0 && variant_grouped(8, variant) && filter_ok && K >= filter8_min_k(iteration)) variant = 60;
     if (M == 4 && variant == 65) variant = files_records ? 89 : choose_scan4_large(N);      // the best of the plain scans
-    const bool filter = variant_filter(M, variant);
-    // the iteration before this one ran a plain scan: no statistics and no keys of it
-    const bool plain_before = iteration > 0 && opt.scan_variant == 0 && K < (M == 4 ? filter4_min_k(iteration - 1) : filter8_min_k(iteration - 1));
+    p.variant = variant;
+    p.filter = variant_filter(M, variant);
+    p.grouped = variant_grouped(M, variant);
+    p.sliding = variant_sliding(M, variant);
+    // M = 16, 32: the lower-bound scan of every stretch in front of the sliding-window scan, which runs where it gave up
+    p.wide = p.sliding && wide_filter(M, opt.scan_variant, variant, N, K, centers, iteration);
+    p.lanes = !p.grouped ? 0 : variant_two_lane(M, variant) ? 2 : 4;
+    int64_t per_launch = opt.launch_codes;
+    // a little below the limit: with its padding a launch of exactly 2^26 codes needs one workgroup more than
+    // 64 full rounds of 4096-code workgroups, and that workgroup would run a round of its own
+    if ((p.grouped || p.sliding) && per_launch > GROUP_CHUNK_MAX - 16384) per_launch = GROUP_CHUNK_MAX - 16384;
+    if (p.filter) {
+        const int64_t round = (int64_t)cu_count() *
+                              (M == 4 ? 512 * filter4_codes_per_slot(variant, group_alloc(N)) : 256 * filter8_codes_per_slot(variant, group_alloc(N)));
+        if (per_launch >= round) per_launch = per_launch / round * round - 32;
+    }
+    if (variant_lds_loads(M, variant)) {
+        // whole rounds of these large workgroups per stretch (the regrouped copy pads a stretch by less than 32 codes)
+        const int64_t round = (int64_t)cu_count() * scan4h_codes_per_workgroup(variant);
+        if (per_launch >= round) per_launch = per_launch / round * round - 32;
+    }
+    p.per_launch = per_launch;
+    const bool one = N <= per_launch;
+    p.reuse = p.grouped && one && had.lanes == p.lanes;
+    // A first iteration starts from the centers that share a pair of subcodes with the code, a later one from the center of
+    // the one before: by code position where the keys are there, else through assign[].
+    if (p.filter) p.seeded = iteration == 0 ? (K >= FILTER_PAIRS_MIN_K ? 3 : 0) : had.keys && p.reuse ? 2 : 1;
+    // the keys stay unless the update uses their room (that of the sorted path)
+    const bool keys_survive = c.state_off != c.sidx_off || (owner_histogram(hist_plan(N, M, K), opt.hist_kernel) &&
+                                                            (opt.hist_kernel != 0 || subspace_hist(N, M, K, c).G == 0));
+    p.leaves.iteration = iteration + 1;
+    p.leaves.lanes = one ? p.lanes : 0;
+    p.leaves.stats = p.filter;
+    p.leaves.keys = p.filter && one && keys_survive;
+    return p;
+}
+
+template <int M>
+pqkm_status assign_tiled(const uint8_t* codes, int64_t N, const uint8_t* centers, int K, const float* tables,
+                         int32_t* assign, float* dist, float* img, const Options& opt, const Carve& c, char* ws,
+                         Carried& carried, hipStream_t st, BucketLink* link = nullptr)
+{
+    constexpr int TK = 128 / M;
+    int64_t ntiles = ((int64_t)K + TK - 1) / TK;
+    int64_t total = ntiles * (int64_t)(TILE_BYTES / 4);
+    const int iteration = carried.iteration;
+    const bool files_records = M == 4 && link && link->wanted && N <= GROUP_CHUNK_MAX - 16384 && c.bseg_off != c.pool_off;
+    const ScanPlan plan_of = scan_plan(M, opt, N, K, codes, centers, files_records, c, carried);
+    const int variant = plan_of.variant;
+    const bool filter = plan_of.filter, wide = plan_of.wide, grouped = plan_of.grouped, sliding = plan_of.sliding;
+    const int64_t per_launch = plan_of.per_launch;
     const int layout = variant_layout(M, variant);
-    const bool sliding = variant_sliding(M, variant);
-    // M = 16, 32: the lower-bound scan of every stretch in front of the sliding-window scan, which runs where it gave up.
-    // Its statistics live in the histograms' room while the assignment runs, its byte tiles and pair tables in that of the
-    // images, which are only built after a scan has given up.
-    const bool wide = sliding && wide_filter(M, opt.scan_variant, variant, N, K, centers, iteration);
+    // The statistics of the M = 16, 32 lower-bound scan live in the histograms' room while the assignment runs, its byte tiles
+    // and pair tables in that of the images, which are only built after a scan has given up.
     FilterStat* const wstat = reinterpret_cast<FilterStat*>(ws + c.hist_off);
     FilterScale* const wscale = reinterpret_cast<FilterScale*>(ws + c.hist_off + 8192);
     uint32_t* const gave_up = reinterpret_cast<uint32_t*>(ws + c.hist_off + 8448);
@@ -1152,17 +1212,16 @@ pqkm_status assign_tiled(const uint8_t* codes, int64_t N, const uint8_t* centers
         uint8_t* copies = reinterpret_cast<uint8_t*>(side) + 4352;
         const size_t copy_stride = align256((size_t)K * M);
         uint32_t* pairs = reinterpret_cast<uint32_t*>(copies + 2 * copy_stride);     // at most 1 MB
-        if (iteration == 0 || plain_before)
+        if (!carried.stats)
             hipLaunchKernelGGL(filter_stats_kernel, dim3(M * FILTER_PARTS), dim3(1024), 0, st, tables, stat);
         hipLaunchKernelGGL((filter_image_kernel<M>), dim3((unsigned)(nt * M * 4)), dim3(256), 0, st, centers, K, tables, stat,
                            reinterpret_cast<uint4*>(img), copies + (iteration & 1) * copy_stride, scale);
         fin = FilterIn{reinterpret_cast<const uint4*>(img), tables, centers, scale,
                        reinterpret_cast<unsigned long long*>(ws + c.state_off), K, nt, copies + ((iteration & 1) ^ 1) * copy_stride,
-                       pairs, 0};
-        if (iteration == 0 && K >= FILTER_PAIRS_MIN_K) {
+                       pairs, plan_of.seeded};
+        if (plan_of.seeded == 3) {
             hipLaunchKernelGGL(fill_i32_kernel, dim3(256), dim3(256), 0, st, reinterpret_cast<int32_t*>(pairs), (int64_t)(M / 2) * 65536, (int32_t)-1);
             hipLaunchKernelGGL((filter_pairs_kernel<M>), dim3((unsigned)((K + 255) / 256)), dim3(256), 0, st, centers, K, pairs);
-            fin.seeded = 3;
         }
     } else if (sliding) {
         // tiles of 16 centers, plane-ordered: img[tile][m][x][16]
@@ -1180,27 +1239,6 @@ pqkm_status assign_tiled(const uint8_t* codes, int64_t N, const uint8_t* centers
         hipLaunchKernelGGL((tile_image_kernel<M, 0>), dim3((unsigned)((total + 255) / 256)), dim3(256), 0, st,
                            centers, K, tables, img, total);
     if (launched() != PQKM_OK) return PQKM_ERR_DEVICE;
-    const bool grouped = variant_grouped(M, variant);
-    int64_t per_launch = opt.launch_codes;
-    // a little below the limit: with its padding a launch of exactly 2^26 codes needs one workgroup more than
-    // 64 full rounds of 4096-code workgroups, and that workgroup would run a round of its own
-    if ((grouped || sliding) && per_launch > GROUP_CHUNK_MAX - 16384) per_launch = GROUP_CHUNK_MAX - 16384;
-    if (filter) {
-        const int64_t round = (int64_t)cu_count() *
-                              (M == 4 ? 512 * filter4_codes_per_slot(variant, group_alloc(N)) : 256 * filter8_codes_per_slot(variant, group_alloc(N)));
-        if (per_launch >= round) per_launch = per_launch / round * round - 32;
-    }
-    if (variant_lds_loads(M, variant)) {
-        // whole rounds of these large workgroups per stretch (the regrouped copy pads a stretch by less than 32 codes)
-        const int64_t round = (int64_t)cu_count() * scan4h_codes_per_workgroup(variant);
-        if (per_launch >= round) per_launch = per_launch / round * round - 32;
-    }
-    const bool keys_survive = c.state_off != c.sidx_off || (owner_histogram(hist_plan(N, M, K), opt.hist_kernel) &&
-                                                            (opt.hist_kernel != 0 || subspace_hist(N, M, K, c).G == 0));
-    // a later iteration starts from the center of the one before: by code position where the keys of one launch cover all
-    // codes and nothing has used their room since, else through assign[]
-    if (filter && reuse_groups)
-        fin.seeded = N <= per_launch && !plain_before && keys_survive ? 2 : 1;
     const float4* rows = reinterpret_cast<const float4*>(ws + c.rows_off);
     uint2* gco = reinterpret_cast<uint2*>(ws + c.gco_off);
     GroupPlan* plan = reinterpret_cast<GroupPlan*>(ws + c.plan_off);
@@ -1231,10 +1269,9 @@ pqkm_status assign_tiled(const uint8_t* codes, int64_t N, const uint8_t* centers
     for (int64_t n0 = 0; n0 < N; n0 += per_launch) {
         int64_t cnt = N - n0 < per_launch ? N - n0 : per_launch;
         const RankOut rl{ro.count, ro.count ? ro.rank + n0 : nullptr};
-        // the regrouped copy survives between calls only when one launch covers all codes
-        if (grouped && !(reuse_groups && N <= per_launch)) {
-            const pqkm_status rs = (M == 8) ? regroup_codes8(codes + n0 * M, cnt, gc8, plan8, st, variant_two_lane(M, variant))
-                                            : regroup_codes(codes + n0 * M, cnt, gco, plan, st, variant_two_lane(M, variant));
+        if (grouped && !plan_of.reuse) {
+            const pqkm_status rs = (M == 8) ? regroup_codes8(codes + n0 * M, cnt, gc8, plan8, st, plan_of.lanes == 2)
+                                            : regroup_codes(codes + n0 * M, cnt, gco, plan, st, plan_of.lanes == 2);
             if (rs != PQKM_OK) return PQKM_ERR_DEVICE;
         }
         EventPair ev{};
@@ -1320,6 +1357,7 @@ pqkm_status assign_tiled(const uint8_t* codes, int64_t N, const uint8_t* centers
         }
         if (launched() != PQKM_OK) return PQKM_ERR_DEVICE;
     }
+    carried = plan_of.leaves;
     return PQKM_OK;
 }
 
@@ -1333,6 +1371,13 @@ constexpr int GATHER_ROWS_MIN_K = 160;
 int64_t gather_max_codes(int K)
 {
     return K < GATHER_ROWS_MIN_K ? 16384 : (int64_t)120000 * K / (1550 + (int64_t)K);
+}
+
+// does one of the LDS-tiled scans run?
+bool tiled_scan(const Options& opt, int64_t N, int M, int K, const uint8_t* codes)
+{
+    if (!tiled_M(M) || opt.assign_kernel == 1 || ((uintptr_t)codes & 3) != 0) return false;
+    return opt.assign_kernel != 0 || opt.scan_variant != 0 || N > gather_max_codes(K);
 }
 
 template <int MW, int CN>
@@ -1371,12 +1416,10 @@ pqkm_status launch_gather(const uint8_t* codes, int64_t N, int M, const uint8_t*
 
 pqkm_status assign_core(const Options& opt, const Carve& c, const uint8_t* codes, int64_t N, int M,
                         const uint8_t* centers, int K, const float* tables, int32_t* assign, float* dist, void* ws,
-                        hipStream_t st, int iteration, BucketLink* link)
+                        hipStream_t st, Carried& carried, BucketLink* link)
 {
-    bool tiled = tiled_M(M) && opt.assign_kernel != 1 && ((uintptr_t)codes & 3) == 0;
-    if (opt.assign_kernel == 2 && !tiled) return PQKM_ERR_SHAPE;
-    const bool few = opt.assign_kernel == 0 && opt.scan_variant == 0 && N <= gather_max_codes(K);
-    if (!tiled || few) {
+    if (opt.assign_kernel == 2 && !(tiled_M(M) && ((uintptr_t)codes & 3) == 0)) return PQKM_ERR_SHAPE;
+    if (!tiled_scan(opt, N, M, K, codes)) {
         const bool words = tiled_M(M) && (((uintptr_t)codes | (uintptr_t)centers) & 3) == 0;
         NearRecord* part = tiled_M(M) ? reinterpret_cast<NearRecord*>(static_cast<char*>(ws) + c.img_off) : nullptr;
         const size_t room = tiled_M(M) ? c.img_bytes : 0;
@@ -1389,22 +1432,23 @@ pqkm_status assign_core(const Options& opt, const Carve& c, const uint8_t* codes
     float* img = reinterpret_cast<float*>(static_cast<char*>(ws) + c.img_off);
     char* wsc = static_cast<char*>(ws);
     switch (M) {
-        case 4: return assign_tiled<4>(codes, N, centers, K, tables, assign, dist, img, opt, c, wsc, iteration, st, link);
-        case 8: return assign_tiled<8>(codes, N, centers, K, tables, assign, dist, img, opt, c, wsc, iteration, st, link);
-        case 16: return assign_tiled<16>(codes, N, centers, K, tables, assign, dist, img, opt, c, wsc, iteration, st, link);
-        default: return assign_tiled<32>(codes, N, centers, K, tables, assign, dist, img, opt, c, wsc, iteration, st, link);
+        case 4: return assign_tiled<4>(codes, N, centers, K, tables, assign, dist, img, opt, c, wsc, carried, st, link);
+        case 8: return assign_tiled<8>(codes, N, centers, K, tables, assign, dist, img, opt, c, wsc, carried, st, link);
+        case 16: return assign_tiled<16>(codes, N, centers, K, tables, assign, dist, img, opt, c, wsc, carried, st, link);
+        default: return assign_tiled<32>(codes, N, centers, K, tables, assign, dist, img, opt, c, wsc, carried, st, link);
     }
 }
 
 // one whole assignment step (tile images, regrouping where it is due, scan launches), optionally bracketed by events
 pqkm_status assign_impl(const Options& opt, const Carve& c, const uint8_t* codes, int64_t N, int M,
                         const uint8_t* centers, int K, const float* tables, int32_t* assign, float* dist, void* ws,
-                        hipStream_t st, int iteration = 0, BucketLink* link = nullptr)
+                        hipStream_t st, Carried* carried = nullptr, BucketLink* link = nullptr)
 {
     if (N == 0) return PQKM_OK;
+    Carried none;
     EventPair ev{};
     const bool prof = (opt.profile & 2) && log_begin(g_step_log, st, &ev);
-    const pqkm_status s = assign_core(opt, c, codes, N, M, centers, K, tables, assign, dist, ws, st, iteration, link);
+    const pqkm_status s = assign_core(opt, c, codes, N, M, centers, K, tables, assign, dist, ws, st, carried ? *carried : none, link);
     if (prof) hipEventRecord(ev.b, st);
     return s;
 }
@@ -1851,10 +1895,10 @@ pqkm_status pqkm_fit(const uint8_t* codes, int64_t N, int32_t M, const float* ta
     if (s != PQKM_OK) return s;
     if ((s = check_device()) != PQKM_OK) return s;
     const Options opt = options_snapshot();
+    Carried carried;                        // the codes do not change between iterations: they are regrouped once
     for (int it = 0; it < iters; ++it) {
-        // the codes do not change between iterations: regroup them for the scan once
         BucketLink link = bucket_request(opt, N, M, K);
-        s = assign_impl(opt, c, codes, N, M, centers, K, tables, assign, nullptr, workspace, (hipStream_t)stream, it,
+        s = assign_impl(opt, c, codes, N, M, centers, K, tables, assign, nullptr, workspace, (hipStream_t)stream, &carried,
                         &link);
         if (s != PQKM_OK) return s;
         s = update_impl(opt, c, codes, N, M, assign, K, tables, centers, hist, counts, workspace, (hipStream_t)stream,
@@ -1913,9 +1957,10 @@ pqkm_status pqkm_fit_until(const uint8_t* codes, int64_t N, int32_t M, const flo
         hipLaunchKernelGGL(fill_i32_kernel, dim3(fb), dim3(256), 0, st, prev, N, (int32_t)-1);
     }
     const Options opt = options_snapshot();
+    Carried carried;
     for (int it = 0; it < max_iters; ++it) {
         BucketLink link = bucket_request(opt, N, M, K);
-        s = assign_impl(opt, c, codes, N, M, centers, K, tables, assign, dist, workspace, st, it, &link);
+        s = assign_impl(opt, c, codes, N, M, centers, K, tables, assign, dist, workspace, st, &carried, &link);
         if (s != PQKM_OK) return s;
         hipLaunchKernelGGL(iter_assign_stats_kernel, dim3(STAT_BLOCKS), dim3(256), 0, st, assign, prev, dist, N, pa);
         s = update_impl(opt, c, codes, N, M, assign, K, tables, centers, hist, counts, workspace, st, &link);
@@ -1965,6 +2010,31 @@ pqkm_status pqkm_set_option(const char* name, int32_t value)
     } else {
         return PQKM_ERR_SHAPE;
     }
+    return PQKM_OK;
+}
+
+pqkm_status pqkm_scan_plan(int64_t N, int32_t M, int32_t K, int32_t iteration, int64_t out[6])
+{
+    if (!out) return PQKM_ERR_NULL;
+    if (!shape_ok(N, M, K) || iteration < 0) return PQKM_ERR_SHAPE;
+    const Options opt = options_snapshot();
+    for (int i = 0; i < 6; ++i) out[i] = 0;
+    if (!tiled_scan(opt, N, M, K, nullptr)) return PQKM_OK;
+    const Carve c = carve(N, M, K);
+    const BucketLink link = bucket_request(opt, N, M, K);
+    const bool files_records = M == 4 && link.wanted && N <= GROUP_CHUNK_MAX - 16384 && c.bseg_off != c.pool_off;
+    Carried carried;
+    ScanPlan p{};
+    for (int it = 0; it <= iteration; ++it) {
+        p = scan_plan(M, opt, N, K, nullptr, nullptr, files_records, c, carried);
+        carried = p.leaves;
+    }
+    out[0] = p.filter || p.wide ? 2 : 1;
+    out[1] = p.variant;
+    out[2] = p.per_launch;
+    out[3] = p.lanes;
+    out[4] = p.reuse ? 1 : 0;
+    out[5] = p.seeded;
     return PQKM_OK;
 }
 

@@ -173,6 +173,40 @@ def test_launch_stretches(env, M, variant):
         pq.set_option("hist_kernel", 0)
 
 
+@pytest.mark.parametrize("M,N,K,iters,launch,hist", [
+    (4, 1_834_980, 1000, 3, 21, 3),          # first iteration in two stretches, second in one
+    (4, 1_500_000, 600, 5, 26, 0), (4, 700_000, 1000, 3, 26, 0),
+    (8, 4_200_000, 505, 5, 26, 0),           # placed for four lanes first, read by two later
+    (8, 4_200_000, 600, 5, 26, 0), (8, 4_200_000, 950, 3, 26, 0),
+    (16, 400_000, 1000, 5, 26, 0), (16, 400_000, 2000, 3, 26, 0), (32, 270_000, 1600, 5, 26, 0), (32, 270_000, 4100, 2, 26, 0)])
+def test_plain_iterations_then_lower_bounds(env, M, N, K, iters, launch, hist):
+    """Default fits whose first iterations run a plain scan and whose later ones the lower-bound scan: what an iteration
+    takes over from the one before (regrouped codes, statistics, keys) has to be there."""
+    pq, oracle, torch = env
+    rng = np.random.default_rng(M + K)
+    centers = rng.integers(0, 256, (K, M), dtype=np.uint8)
+    codes = centers[rng.integers(0, K, N)]
+    fresh = rng.random((N, M), dtype=np.float32) < 0.3
+    codes[fresh] = rng.integers(0, 256, int(fresh.sum()), dtype=np.uint8)
+    tables = _metric_tables(rng, M)
+    progress(f"plain, then lower bounds: M={M} N={N} K={K}")
+    try:
+        pq.set_option("launch_codes_log2", launch)
+        pq.set_option("hist_kernel", hist)
+        assert pq.scan_plan(N, M, K, 0)["scan"] == 1 and pq.scan_plan(N, M, K, iters - 1)["scan"] == 2
+        cent = torch.from_numpy(centers).cuda()
+        a = torch.full((N,), -7, dtype=torch.int32, device="cuda")
+        ws = torch.full((pq.workspace_bytes(N, M, K),), 0xA5, dtype=torch.uint8, device="cuda")
+        pq.fit(torch.from_numpy(codes).cuda(), torch.from_numpy(tables).cuda(), cent, iters, assign=a, workspace=ws)
+        torch.cuda.synchronize()
+    finally:
+        pq.set_option("launch_codes_log2", 26)
+        pq.set_option("hist_kernel", 0)
+    rc, ra, _, _ = oracle.fit(codes, tables, centers, iters)
+    np.testing.assert_array_equal(a.cpu().numpy(), ra)
+    np.testing.assert_array_equal(cent.cpu().numpy(), rc)
+
+
 @pytest.mark.parametrize("M,N,K", [(4, 600_000, 2000), (32, 300_000, 5200)])
 def test_captured_fit(env, M, N, K):
     """The default scans of these sizes in a captured graph, with eager work and another workspace content between replays."""
