@@ -56,8 +56,8 @@ __global__ __launch_bounds__(256) void build_tables_kernel(const float* __restri
 // The codeword the definition selects therefore has v_l <= v_min + E with twice the sum of the above; E below is
 // rounded up by a quarter and by 1e-30 for flushed denormals.  If the second smallest v exceeds that, the smallest is
 // the answer.  Else the fp32 distances decide: of the 32 codewords in the two blocks of 16 that can hold the closest, or, if a
-// third block can, of all 256.  A vector or codeword that makes E overflow or NaN takes the last way, so non-finite values
-// keep the definition's result.
+// third block can, of all 256.  A vector or codeword that makes s NaN or larger than 1e19 takes the last way: below that every
+// distance (at most s^2) is finite, above it the defined ones may be +inf, which is never selected.
 //
 // One wave takes 32 vectors and one subspace at a time: v_mfma_f32_32x32x16_bf16 with the codewords as rows and the
 // vectors as columns, so that a lane holds 16 codewords of one vector per instruction.  It takes the minimum of the 16,
@@ -243,10 +243,11 @@ __global__ __launch_bounds__(THREADS) void encode_mfma_kernel(const float* __res
             const float E = kappa * s * s + 1e-30f;
             const float lim = a1 + E;
             const bool sure = a2 > lim && b2 > lim;               // false when anything overflowed or is NaN
-            const bool two = a3 > lim && E < 3e38f;
+            const bool finite = s < 1e19f;
+            const bool two = a3 > lim && finite;
             int bl = codeword_of(__builtin_bit_cast(uint32_t, a1), __builtin_bit_cast(uint32_t, b1) & 15u);
             const float* cw = codewords + (size_t)(m0 + g) * L * Ds;
-            uint64_t rest = __ballot(!(sure && E < 3e38f)) & 0xffffffffull;
+            uint64_t rest = __ballot(!(sure && finite)) & 0xffffffffull;
             while (rest) {
                 // one vector, the wave together
                 const int v = __builtin_ctzll(rest);

@@ -99,3 +99,18 @@ def test_decode_shapes(env, M, Ds, N, offset):
     pq.decode(torch.from_numpy(codes).cuda(), torch.from_numpy(cw).cuda(), vectors=out)
     assert np.array_equal(out.cpu().numpy(), oracle.decode_f32(cw, codes))
     assert bool((buf[offset + N * M * Ds:] == -7.0).all()) and bool((buf[:offset] == -7.0).all())
+
+
+@pytest.mark.parametrize("M,Ds", [(1, 4), (3, 16), (2, 40)])
+def test_encode_distances_that_overflow(env, M, Ds):
+    """Squares that are finite, distances that are not: where every distance is +inf the code is 0, where some are finite it
+    is the closest of those."""
+    oracle = env[1]
+    rng = np.random.default_rng(Ds)
+    with np.errstate(over="ignore"):
+        cw = (-(0.5 + rng.random((M, 256, Ds))) * 1.5e19 / np.sqrt(Ds)).astype(np.float32)
+        cw[-1, 17] = np.float32(1e18)                                     # one codeword within reach of the last subspace
+        vectors = ((0.8 + 0.3 * rng.random((200, M, Ds))) * 1.5e19 / np.sqrt(Ds)).astype(np.float32)
+        vectors[50:100] *= np.float32(0.01)
+        vectors = vectors.reshape(200, M * Ds)
+        assert np.array_equal(_encode(env, vectors, cw), oracle.encode(vectors, cw))
