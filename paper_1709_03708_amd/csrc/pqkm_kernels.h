@@ -49,10 +49,11 @@ __global__ __launch_bounds__(256) void build_tables_kernel(const float* __restri
 // v_l = |c_l|^2/2 - x.c_l (half the distance up to |x|^2/2) with x and c split into two bf16 parts each, x = xh + xl + r,
 // |r| <= 2^-18 |x|, three products xh.ch + xh.cl + xl.ch accumulated in fp32.  With s = |x| + max_l |c_l|:
 //   - dropped products and residuals: at most 3 (1 + 2^-8) 2^-18 |x||c| <= 0.76 2^-18 s^2,
-//   - accumulation of 3 Ds products and the norm: (3 Ds + 8) 2^-23 |x||c|, truncation allowed for, at most
-//     (3 Ds + 8) 2^-25 s^2; the norm rounded to fp32: 2^-25 s^2,
+//   - accumulation of 3 Ds products on top of the norm: every partial sum is at most |c|^2/2 + (1 + 2^-7) |x||c| <=
+//     (1 + 2^-7) s^2/2 (the larger the shorter x is), and an addition loses at most 2^-23 of it, truncation allowed for:
+//     (3 Ds + 8) 2^-24 (1 + 2^-7) s^2; the norm rounded to fp32: 2^-25 s^2,
 //   - the low 4 bits of a kept value hold an index: 2^-19 |v_l| <= 2^-20 s^2,
-//   - the defined fp32 distance is within (Ds + 2) 2^-24 (1 + ..) of the true one, which is at most s^2.
+//   - the defined fp32 distance is within (Ds + 2) 2^-24 (1 + ..) of the true one, which is at most s^2; half of that here.
 // The codeword the definition selects therefore has v_l <= v_min + E with twice the sum of the above; E below is
 // rounded up by a quarter and by 1e-30 for flushed denormals.  If the second smallest v exceeds that, the smallest is
 // the answer.  Else the fp32 distances decide: of the 32 codewords in the two blocks of 16 that can hold the closest, or, if a
@@ -151,7 +152,7 @@ __global__ __launch_bounds__(THREADS) void encode_mfma_kernel(const float* __res
     __syncthreads();
 
     const int half = lane >> 5;
-    const float kappa = 1.25f * 2.0f * (0.76f * 0x1p-18f + (float)(3 * Ds + 8) * 0x1p-25f + 0x1p-25f + 0x1p-19f + (float)(Ds + 4) * 0x1p-24f);
+    const float kappa = 1.25f * 2.0f * (0.76f * 0x1p-18f + (float)(3 * Ds + 8) * 1.01f * 0x1p-24f + 0x1p-25f + 0x1p-20f + (float)(Ds + 4) * 0x1p-25f);
     const int64_t ntiles = (N + 31) / 32;
     for (int64_t t = (int64_t)w * WAVES + wave; t < ntiles; t += (int64_t)wpg * WAVES) {
         const int64_t n = t * 32 + (lane & 31);

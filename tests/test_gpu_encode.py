@@ -114,3 +114,16 @@ def test_encode_distances_that_overflow(env, M, Ds):
         vectors[50:100] *= np.float32(0.01)
         vectors = vectors.reshape(200, M * Ds)
         assert np.array_equal(_encode(env, vectors, cw), oracle.encode(vectors, cw))
+
+
+@pytest.mark.parametrize("Ds", [16, 96, 128])
+def test_encode_codewords_on_a_sphere(env, Ds):
+    """Vectors much shorter than codewords of nearly equal length: the matrix cores' sums start at the codeword's half
+    square and stay as large, and the distances differ by less than their rounding."""
+    oracle = env[1]
+    rng = np.random.default_rng(Ds)
+    cw = rng.standard_normal((2, 256, Ds))
+    cw = (cw / np.linalg.norm(cw, axis=2, keepdims=True)).astype(np.float32)
+    for size in (1e-6, 1e-5, 1e-4, 1e-3):
+        vectors = (size * rng.standard_normal((500, 2 * Ds))).astype(np.float32)
+        assert np.array_equal(_encode(env, vectors, cw), oracle.encode(vectors, cw))
