@@ -46,19 +46,22 @@ __global__ __launch_bounds__(256) void build_tables_kernel(const float* __restri
 // 3 flops per (vector, codeword, dimension) if every one of them is formed on the vector units.  Here the matrix cores
 // find the codewords that can be the closest, and only where that leaves more than one the fp32 distances decide.
 //
-// v_l = |c_l|^2/2 - x.c_l (half the distance up to |x|^2/2) with x and c split into two bf16 parts each, x = xh + xl + r,
-// |r| <= 2^-18 |x|, three products xh.ch + xh.cl + xl.ch accumulated in fp32.  With s = |x| + max_l |c_l|:
-//   - dropped products and residuals: at most 3 (1 + 2^-8) 2^-18 |x||c| <= 0.76 2^-18 s^2,
-//   - accumulation of 3 Ds products on top of the norm: every partial sum is at most |c|^2/2 + (1 + 2^-7) |x||c| <=
-//     (1 + 2^-7) s^2/2 (the larger the shorter x is), and an addition loses at most 2^-23 of it, truncation allowed for:
+// Both sides are centred first, on the mean mu of 16 codewords of the subspace (any value would do): x' = x - mu, c' = c - mu,
+// one fp32 subtraction each, so that a common offset of the data, however large, does not enter the error.
+// v_l = |c'_l|^2/2 - x'.c'_l (half the distance up to |x'|^2/2) with x' and c' split into two bf16 parts each, x' = xh + xl +
+// r, |r| <= 2^-18 |x'|, three products xh.ch + xh.cl + xl.ch accumulated in fp32.  With s = |x'| + max_l |c'_l|:
+//   - dropped products and residuals: at most 3 (1 + 2^-8) 2^-18 |x'||c'| <= 0.76 2^-18 s^2,
+//   - accumulation of 3 Ds products on top of the norm: every partial sum is at most |c'|^2/2 + (1 + 2^-7) |x'||c'| <=
+//     (1 + 2^-7) s^2/2 (the larger the shorter x' is), and an addition loses at most 2^-23 of it, truncation allowed for:
 //     (3 Ds + 8) 2^-24 (1 + 2^-7) s^2; the norm rounded to fp32: 2^-25 s^2,
 //   - the low 4 bits of a kept value hold an index: 2^-19 |v_l| <= 2^-20 s^2,
+//   - the roundings of the two subtractions move the distance by at most 2^-23 s^2, half of that here,
 //   - the defined fp32 distance is within (Ds + 2) 2^-24 (1 + ..) of the true one, which is at most s^2; half of that here.
 // The codeword the definition selects therefore has v_l <= v_min + E with twice the sum of the above; E below is
 // rounded up by a quarter and by 1e-30 for flushed denormals.  If the second smallest v exceeds that, the smallest is
-// the answer.  Else the fp32 distances decide: of the 32 codewords in the two blocks of 16 that can hold the closest, or, if a
-// third block can, of all 256.  A vector or codeword that makes s NaN or larger than 1e19 takes the last way: below that every
-// distance (at most s^2) is finite, above it the defined ones may be +inf, which is never selected.
+// the answer.  Else the vector is open, and the fp32 distances decide: of the 32 codewords in the two blocks of 16 that can
+// hold the closest, or, if a third block can, of all 256.  A vector or codeword that makes s NaN or larger than 1e19 takes the
+// last way: below that every distance (at most s^2) is finite, above it the defined ones may be +inf, which is never selected.
 //
 // One wave takes 32 vectors and one subspace at a time: v_mfma_f32_32x32x16_bf16 with the codewords as rows and the
 // vectors as columns, so that a lane holds 16 codewords of one vector per instruction.  It takes the minimum of the 16,
@@ -66,14 +69,23 @@ __global__ __launch_bounds__(256) void build_tables_kernel(const float* __restri
 // value takes 6), and ranks those 16 at the end, when the two lanes of a vector merge.  The workgroup holds the split
 // codewords of `G` subspaces in LDS (16 KB per subspace and 16 dimensions, 128 KB in all) in the order the instruction
 // reads them.  Bound by the vector units and the matrix cores about equally at 32 dimensions, by the latter above.
+//
+// Open vectors: a wave settles those of two tiles together.  Up to ENC_DENSE of the 64 one by one, the codewords spread over
+// the lanes; more, and each lane forms all 256 distances of its own vector with the codewords as scalar operands, 512 flops
+// per dimension on the vector units as an encoder without matrix cores would, and the matrix cores are then asked only every
+// eighth time.  That is the case for data whose gaps between codewords are small against their spread (two tight clusters far
+// apart: 200000 vectors, M = 4, 32 dimensions: 0.48 ms; one by one it took 3.6 ms).
+//
 // Measured, 1e6 vectors of 128 dimensions (0.52 GB), M = 4: 1.14 ms on the vector units -> 0.26 ms; 5e5 vectors of 96
-// dimensions, M = 8: 142 ms (any length that was not compiled for) -> 0.155 ms.
+// dimensions, M = 8: 142 ms (any length that was not compiled for) -> 0.16 ms.  200000 vectors, M = 4, 32 dimensions with a
+// common offset of 100 times their spread: 0.25 ms on the vector units, 3.6 ms on the matrix cores without centring, 0.08 ms.
 // ---------------------------------------------------------------------------------------------
 typedef __bf16 v8bf __attribute__((ext_vector_type(8)));
 typedef float v16f __attribute__((ext_vector_type(16)));
 
 constexpr int ENC_LDS_F4 = 128 * 1024 / 16;       // split codewords
 constexpr int ENC_MAX_G = 8;                      // subspaces of a workgroup
+constexpr int ENC_DENSE = 12;                     // open vectors of 64 from which on every lane forms all its distances
 
 // one v_min_f32 (fminf would quiet its operands first)
 __device__ __forceinline__ float min_f32(float a, float b)
@@ -96,6 +108,12 @@ __device__ __forceinline__ float low_bits(float v, uint32_t name)
     return __builtin_bit_cast(float, (__builtin_bit_cast(uint32_t, v) & 0xfffffff0u) | name);
 }
 
+// block: name of a block of 16 codewords, i: place in it
+__device__ __forceinline__ int encode_codeword_of(uint32_t block, uint32_t i)
+{
+    return (int)((block & 7u) * 32u + 8u * (i >> 2) + 4u * ((block >> 3) & 1u) + (i & 3u));
+}
+
 // the fp32 distance of the definition
 __device__ __forceinline__ float encode_distance(const float* __restrict__ x, const float* __restrict__ c, int Ds)
 {
@@ -108,8 +126,66 @@ __device__ __forceinline__ float encode_distance(const float* __restrict__ x, co
     return acc;
 }
 
+// The fp32 distances of the definition, one vector per lane against all 256 codewords, which are the same for every lane:
+// the scalar unit fetches them, the vector stays in registers.  Returns the code.
+template <int KS, bool VEC>
+__device__ __forceinline__ int encode_all(const float* __restrict__ xv, const float* __restrict__ cw, int Ds)
+{
+    typedef const __attribute__((address_space(4))) float* ScalarFloats;
+    const ScalarFloats cs = (ScalarFloats)(uintptr_t)cw;
+    float x[KS * 16];
+#pragma unroll
+    for (int d = 0; d < KS * 16; d += 4) {
+        if (VEC) {
+            float4 q = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+            if (d < Ds) q = *reinterpret_cast<const float4*>(xv + d);
+            x[d] = q.x; x[d + 1] = q.y; x[d + 2] = q.z; x[d + 3] = q.w;
+        } else {
+#pragma unroll
+            for (int j = 0; j < 4; ++j) x[d + j] = d + j < Ds ? xv[d + j] : 0.0f;
+        }
+    }
+    // U codewords x STEP dimensions are fetched together: 64 scalar registers
+    constexpr int U = KS == 1 ? 8 : 4, STEP = 64 / U;
+    float best = INFINITY;
+    int bl = 0;
+#pragma unroll 1
+    for (int l = 0; l < L; l += U) {
+        float acc[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) acc[u] = 0.0f;
+        auto add = [&](int d, ScalarFloats c, int j) {
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                const float t = x[d] - c[u * Ds + j];
+                acc[u] = __builtin_fmaf(t, t, acc[u]);
+            }
+        };
+#pragma unroll
+        for (int k = 0; k < KS * 16; k += STEP) {                    // all conditions are the same for all lanes
+            const ScalarFloats c = cs + l * Ds + k;
+            if (k + STEP <= Ds) {
+#pragma unroll
+                for (int j = 0; j < STEP; ++j) add(k + j, c, j);
+            } else {
+#pragma unroll
+                for (int j = 0; j < STEP; j += 4)
+                    if (k + j < Ds) {
+#pragma unroll
+                        for (int i = 0; i < 4; ++i)
+                            if (VEC || k + j + i < Ds) add(k + j + i, c, j + i);
+                    }
+            }
+        }
+#pragma unroll
+        for (int u = 0; u < U; ++u)
+            if (acc[u] < best) { best = acc[u]; bl = l + u; }
+    }
+    return bl;
+}
+
 // Grid: groups of G subspaces x `wpg` workgroups; workgroup w of a group takes the tiles of 32 vectors w * WAVES + wave,
-// + wpg * WAVES, ...  KS = ceil(Ds / 16); VEC: Ds is a multiple of 4 and the vectors are 16-byte aligned.
+// + wpg * WAVES, ..., two at a time.  KS = ceil(Ds / 16); VEC: Ds is a multiple of 4 and the vectors are 16-byte aligned.
 template <int KS, int THREADS, bool VEC>
 __global__ __launch_bounds__(THREADS) void encode_mfma_kernel(const float* __restrict__ vectors, int64_t N, int M, int Ds,
                                                               const float* __restrict__ codewords,
@@ -118,6 +194,7 @@ __global__ __launch_bounds__(THREADS) void encode_mfma_kernel(const float* __res
     constexpr int WAVES = THREADS / 64;
     __shared__ float4 frag[ENC_LDS_F4];
     __shared__ float hnorm[ENC_MAX_G * L];            // |c|^2 / 2
+    __shared__ float4 mid[ENC_MAX_G * 4];             // [g][KS * 16]: what both sides are centred on (8 / KS subspaces at most)
     __shared__ uint32_t cmax[ENC_MAX_G];              // max |c|^2 as bits (non-negative: ordered like integers)
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -126,16 +203,34 @@ __global__ __launch_bounds__(THREADS) void encode_mfma_kernel(const float* __res
     const int ng = (M - m0) < G ? (M - m0) : G;
 
     if (tid < ENC_MAX_G) cmax[tid] = 0u;
+    float* const mu = reinterpret_cast<float*>(mid);
+    if (wave < ng) {
+        // wave g: subspace g
+        constexpr int PER = (KS * 16 + 63) / 64;
+        const float* c = codewords + (size_t)(m0 + wave) * L * Ds;
+#pragma unroll
+        for (int p = 0; p < PER; ++p) {
+            const int d = lane + 64 * p;
+            float v[16], sum = 0.0f;
+#pragma unroll
+            for (int l = 0; l < 16; ++l) v[l] = d < Ds ? c[(size_t)(16 * l + 8) * Ds + d] : 0.0f;
+#pragma unroll
+            for (int l = 0; l < 16; ++l) sum += v[l];
+            sum *= 1.0f / 16.0f;
+            if (d < KS * 16) mu[wave * (KS * 16) + d] = __builtin_fabsf(sum) < INFINITY ? sum : 0.0f;
+        }
+    }
     __syncthreads();
     // fragments: [g][block of 32 codewords][k step][high, low part][lane], the negated codewords
     for (int f = tid; f < ng * 8 * KS * 64; f += THREADS) {
         const int fl = f & 63, ks = (f >> 6) % KS, gb = (f >> 6) / KS;       // gb = g * 8 + block
         const int l = (gb & 7) * 32 + (fl & 31), d0 = ks * 16 + 8 * (fl >> 5);
         const float* c = codewords + ((size_t)(m0 + (gb >> 3)) * L + l) * Ds;
+        const float* mg = mu + (gb >> 3) * (KS * 16);
         v8bf hi, lo;
 #pragma unroll
         for (int j = 0; j < 8; ++j) {
-            const float v = d0 + j < Ds ? -c[d0 + j] : 0.0f;
+            const float v = d0 + j < Ds ? mg[d0 + j] - c[d0 + j] : 0.0f;
             hi[j] = (__bf16)v;
             lo[j] = (__bf16)(v - (float)hi[j]);
         }
@@ -144,125 +239,169 @@ __global__ __launch_bounds__(THREADS) void encode_mfma_kernel(const float* __res
     }
     for (int i = tid; i < ng * L; i += THREADS) {
         const float* c = codewords + ((size_t)m0 * L + i) * Ds;
+        const float* mg = mu + (i >> 8) * (KS * 16);
         double sum = 0.0;
-        for (int d = 0; d < Ds; ++d) sum += (double)c[d] * (double)c[d];
+        for (int d = 0; d < Ds; ++d) {
+            const float v = c[d] - mg[d];
+            sum += (double)v * (double)v;
+        }
         hnorm[i] = (float)(0.5 * sum);
         atomicMax(&cmax[i >> 8], __builtin_bit_cast(uint32_t, (float)sum) & 0x7fffffffu);
     }
     __syncthreads();
 
     const int half = lane >> 5;
-    const float kappa = 1.25f * 2.0f * (0.76f * 0x1p-18f + (float)(3 * Ds + 8) * 1.01f * 0x1p-24f + 0x1p-25f + 0x1p-20f + (float)(Ds + 4) * 0x1p-25f);
-    const int64_t ntiles = (N + 31) / 32;
-    for (int64_t t = (int64_t)w * WAVES + wave; t < ntiles; t += (int64_t)wpg * WAVES) {
-        const int64_t n = t * 32 + (lane & 31);
-        const int64_t nc = n < N ? n : N - 1;
-        const float* row = vectors + ((size_t)nc * M + m0) * Ds;
+    const float kappa = 1.25f * 2.0f * (0.76f * 0x1p-18f + (float)(3 * Ds + 8) * 1.01f * 0x1p-24f + 0x1p-25f + 0x1p-20f + (float)(Ds + 6) * 0x1p-25f);
+    const int64_t ntiles = (N + 31) / 32, stride = (int64_t)wpg * WAVES;
+    // bit g: most vectors of subspace g were left open last time (256 codewords on a line are too close from the start)
+    uint32_t hard = Ds == 1 ? 0xffffffffu : 0u, turn = 0u;
+    for (int64_t t = (int64_t)w * WAVES + wave; t < ntiles; t += 2 * stride) {
+        // the lower half of the wave ends up with the first tile's vectors, the upper with the second's
+        const bool second = t + stride < ntiles;
+        const int64_t n = (half == 0 ? t : t + stride) * 32 + (lane & 31);
+        const bool live = n < N && (half == 0 || second);
+        ++turn;
         for (int g = 0; g < ng; ++g) {
-            // the lane's half of the subvector: dimensions 16 ks + 8 half .. + 7, split
-            const float* xv = row + (size_t)g * Ds;
-            v8bf xh[KS], xl[KS];
-            float ss = 0.0f;
-#pragma unroll
-            for (int ks = 0; ks < KS; ++ks) {
-                const int d0 = ks * 16 + 8 * half;
-                float v[8];
-                if (VEC) {
-#pragma unroll
-                    for (int j = 0; j < 8; j += 4) {
-                        float4 q = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
-                        if (d0 + j < Ds) q = *reinterpret_cast<const float4*>(xv + d0 + j);
-                        v[j] = q.x; v[j + 1] = q.y; v[j + 2] = q.z; v[j + 3] = q.w;
-                    }
-                } else {
-#pragma unroll
-                    for (int j = 0; j < 8; ++j) v[j] = d0 + j < Ds ? xv[d0 + j] : 0.0f;
-                }
-#pragma unroll
-                for (int j = 0; j < 8; ++j) {
-                    ss = __builtin_fmaf(v[j], v[j], ss);
-                    xh[ks][j] = (__bf16)v[j];
-                    xl[ks][j] = (__bf16)(v[j] - (float)xh[ks][j]);
-                }
-            }
-            ss = ss + __shfl_xor(ss, 32);
-            float m1 = INFINITY, m2 = INFINITY, m3 = INFINITY;    // smallest minima of 16, the low bits name the block
-            float kept[16];
-#pragma unroll
-            for (int i = 0; i < 16; ++i) kept[i] = INFINITY;
-            const float4* hn = reinterpret_cast<const float4*>(hnorm + g * L) + half;
-            const float4* fr = frag + (size_t)g * 8 * KS * 2 * 64 + lane;
-#pragma unroll
-            for (int b = 0; b < 8; ++b) {
-                v16f acc;
-#pragma unroll
-                for (int i = 0; i < 4; ++i) {
-                    const float4 h4 = hn[b * 8 + 2 * i];
-                    acc[4 * i] = h4.x; acc[4 * i + 1] = h4.y; acc[4 * i + 2] = h4.z; acc[4 * i + 3] = h4.w;
-                }
+            int bl = 0;
+            uint32_t n1 = 0u, n2 = 0u;                               // the blocks that can hold the closest codeword
+            bool sure = true, two = false;
+            // where the matrix cores leave most vectors open they are asked again only every eighth time
+            const bool skip = ((hard >> g) & 1u) && (turn & 7u);
+            if (skip) sure = false;
+            // the lane's half of the subvector: dimensions 16 ks + 8 half .. + 7
+            auto fetch = [&](int i, float (&v)[KS][8]) __attribute__((always_inline)) {
+                const int64_t nt = (t + i * stride) * 32 + (lane & 31);
+                const float* xv = vectors + ((size_t)(nt < N ? nt : N - 1) * M + m0 + g) * Ds;
 #pragma unroll
                 for (int ks = 0; ks < KS; ++ks) {
-                    const v8bf ch = __builtin_bit_cast(v8bf, fr[((b * KS + ks) * 2) * 64]);
-                    const v8bf cl = __builtin_bit_cast(v8bf, fr[((b * KS + ks) * 2 + 1) * 64]);
-                    acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(cl, xh[ks], acc, 0, 0, 0);
-                    acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ch, xl[ks], acc, 0, 0, 0);
-                    acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ch, xh[ks], acc, 0, 0, 0);
+                    const int d0 = ks * 16 + 8 * half;
+                    if (VEC) {
+#pragma unroll
+                        for (int j = 0; j < 8; j += 4) {
+                            float4 q = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+                            if (d0 + j < Ds) q = *reinterpret_cast<const float4*>(xv + d0 + j);
+                            v[ks][j] = q.x; v[ks][j + 1] = q.y; v[ks][j + 2] = q.z; v[ks][j + 3] = q.w;
+                        }
+                    } else {
+#pragma unroll
+                        for (int j = 0; j < 8; ++j) v[ks][j] = d0 + j < Ds ? xv[d0 + j] : 0.0f;
+                    }
                 }
-                const float u0 = minimum3(acc[0], acc[1], acc[2]), u1 = minimum3(acc[3], acc[4], acc[5]);
-                const float u2 = minimum3(acc[6], acc[7], acc[8]), u3 = minimum3(acc[9], acc[10], acc[11]);
-                const float u4 = minimum3(acc[12], acc[13], acc[14]);
-                const float e = low_bits(minimum3(minimum3(u0, u1, u2), minimum3(u3, u4, acc[15]), u0), (uint32_t)b);
-                const bool better = e < m1;
-                m3 = __builtin_amdgcn_fmed3f(m2, m3, e);
-                m2 = __builtin_amdgcn_fmed3f(m1, m2, e);
-                m1 = better ? e : m1;
-#pragma unroll
-                for (int i = 0; i < 16; ++i) kept[i] = better ? acc[i] : kept[i];
-            }
-            // the two smallest of the lane's best block; the low bits name the place in it
-            float w1 = INFINITY, w2 = INFINITY;
-#pragma unroll
-            for (int i = 0; i < 16; ++i) {
-                const float v = low_bits(kept[i], (uint32_t)i);
-                w2 = __builtin_amdgcn_fmed3f(w1, w2, v);
-                w1 = min_f32(w1, v);
-            }
-            // bit 3 of a block's name: which lane of the two
-            auto mark = [&](float v) { return __builtin_bit_cast(float, __builtin_bit_cast(uint32_t, v) | ((uint32_t)half << 3)); };
-            m1 = mark(m1); m2 = mark(m2); m3 = mark(m3);
-            const float o1 = __shfl_xor(m1, 32), o2 = __shfl_xor(m2, 32), o3 = __shfl_xor(m3, 32);
-            const float p1 = __shfl_xor(w1, 32), p2 = __shfl_xor(w2, 32);
-            const float a1 = __builtin_fminf(m1, o1);
-            const float a2 = __builtin_fminf(__builtin_fmaxf(m1, o1), __builtin_fminf(m2, o2));
-            const float a3 = __builtin_fminf(__builtin_fminf(m3, o3), __builtin_fminf(__builtin_fmaxf(m1, o2), __builtin_fmaxf(m2, o1)));
-            const bool mine = ((__builtin_bit_cast(uint32_t, a1) >> 3) & 1u) == (uint32_t)half;
-            const float b1 = mine ? w1 : p1, b2 = mine ? w2 : p2;
-            auto codeword_of = [](uint32_t block, uint32_t i) {      // block: name of a block of 16, i: place in it
-                return (int)((block & 7u) * 32u + 8u * (i >> 2) + 4u * ((block >> 3) & 1u) + (i & 3u));
             };
-            const float s = (__builtin_amdgcn_sqrtf(ss) + __builtin_amdgcn_sqrtf(__builtin_bit_cast(float, cmax[g]))) * 1.0001f;
-            const float E = kappa * s * s + 1e-30f;
-            const float lim = a1 + E;
-            const bool sure = a2 > lim && b2 > lim;               // false when anything overflowed or is NaN
-            const bool finite = s < 1e19f;
-            const bool two = a3 > lim && finite;
-            int bl = codeword_of(__builtin_bit_cast(uint32_t, a1), __builtin_bit_cast(uint32_t, b1) & 15u);
+            auto rank = [&](int i, float (&v)[KS][8]) __attribute__((always_inline)) {
+                asm volatile("" ::: "memory");        // the split codewords do not fit the registers: read them each time
+                const float4* mg = mid + g * (KS * 4) + 2 * half;
+                v8bf xh[KS], xl[KS];
+                float ss = 0.0f;
+#pragma unroll
+                for (int ks = 0; ks < KS; ++ks) {
+                    const float4 ma = mg[ks * 4], mb = mg[ks * 4 + 1];          // 0 from Ds on
+                    v[ks][0] -= ma.x; v[ks][1] -= ma.y; v[ks][2] -= ma.z; v[ks][3] -= ma.w;
+                    v[ks][4] -= mb.x; v[ks][5] -= mb.y; v[ks][6] -= mb.z; v[ks][7] -= mb.w;
+#pragma unroll
+                    for (int j = 0; j < 8; ++j) {
+                        ss = __builtin_fmaf(v[ks][j], v[ks][j], ss);
+                        xh[ks][j] = (__bf16)v[ks][j];
+                        xl[ks][j] = (__bf16)(v[ks][j] - (float)xh[ks][j]);
+                    }
+                }
+                ss = ss + __shfl_xor(ss, 32);
+                float m1 = INFINITY, m2 = INFINITY, m3 = INFINITY;    // smallest minima of 16, the low bits name the block
+                float kept[16];
+#pragma unroll
+                for (int j = 0; j < 16; ++j) kept[j] = INFINITY;
+                const float4* hn = reinterpret_cast<const float4*>(hnorm + g * L) + half;
+                const float4* fr = frag + (size_t)g * 8 * KS * 2 * 64 + lane;
+#pragma unroll
+                for (int b = 0; b < 8; ++b) {
+                    v16f acc;
+#pragma unroll
+                    for (int j = 0; j < 4; ++j) {
+                        const float4 h4 = hn[b * 8 + 2 * j];
+                        acc[4 * j] = h4.x; acc[4 * j + 1] = h4.y; acc[4 * j + 2] = h4.z; acc[4 * j + 3] = h4.w;
+                    }
+#pragma unroll
+                    for (int ks = 0; ks < KS; ++ks) {
+                        const v8bf ch = __builtin_bit_cast(v8bf, fr[((b * KS + ks) * 2) * 64]);
+                        const v8bf cl = __builtin_bit_cast(v8bf, fr[((b * KS + ks) * 2 + 1) * 64]);
+                        acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(cl, xh[ks], acc, 0, 0, 0);
+                        acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ch, xl[ks], acc, 0, 0, 0);
+                        acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ch, xh[ks], acc, 0, 0, 0);
+                    }
+                    const float u0 = minimum3(acc[0], acc[1], acc[2]), u1 = minimum3(acc[3], acc[4], acc[5]);
+                    const float u2 = minimum3(acc[6], acc[7], acc[8]), u3 = minimum3(acc[9], acc[10], acc[11]);
+                    const float u4 = minimum3(acc[12], acc[13], acc[14]);
+                    const float e = low_bits(minimum3(minimum3(u0, u1, u2), minimum3(u3, u4, acc[15]), u0), (uint32_t)b);
+                    const bool better = e < m1;
+                    m3 = __builtin_amdgcn_fmed3f(m2, m3, e);
+                    m2 = __builtin_amdgcn_fmed3f(m1, m2, e);
+                    m1 = better ? e : m1;
+#pragma unroll
+                    for (int j = 0; j < 16; ++j) kept[j] = better ? acc[j] : kept[j];
+                }
+                // the two smallest of the lane's best block; the low bits name the place in it
+                float w1 = INFINITY, w2 = INFINITY;
+#pragma unroll
+                for (int j = 0; j < 16; ++j) {
+                    const float v = low_bits(kept[j], (uint32_t)j);
+                    w2 = __builtin_amdgcn_fmed3f(w1, w2, v);
+                    w1 = min_f32(w1, v);
+                }
+                // bit 3 of a block's name: which lane of the two
+                auto mark = [&](float v) { return __builtin_bit_cast(float, __builtin_bit_cast(uint32_t, v) | ((uint32_t)half << 3)); };
+                m1 = mark(m1); m2 = mark(m2); m3 = mark(m3);
+                const float o1 = __shfl_xor(m1, 32), o2 = __shfl_xor(m2, 32), o3 = __shfl_xor(m3, 32);
+                const float p1 = __shfl_xor(w1, 32), p2 = __shfl_xor(w2, 32);
+                const float a1 = __builtin_fminf(m1, o1);
+                const float a2 = __builtin_fminf(__builtin_fmaxf(m1, o1), __builtin_fminf(m2, o2));
+                const float a3 = __builtin_fminf(__builtin_fminf(m3, o3), __builtin_fminf(__builtin_fmaxf(m1, o2), __builtin_fmaxf(m2, o1)));
+                const bool mine = ((__builtin_bit_cast(uint32_t, a1) >> 3) & 1u) == (uint32_t)half;
+                const float b1 = mine ? w1 : p1, b2 = mine ? w2 : p2;
+                const float s = (__builtin_amdgcn_sqrtf(ss) + __builtin_amdgcn_sqrtf(__builtin_bit_cast(float, cmax[g]))) * 1.0001f;
+                const float lim = a1 + (kappa * s * s + 1e-30f);
+                const bool finite = s < 1e19f;
+                if (half == i) {
+                    n1 = __builtin_bit_cast(uint32_t, a1);
+                    n2 = __builtin_bit_cast(uint32_t, a2);
+                    sure = a2 > lim && b2 > lim && finite;            // false when anything overflowed or is NaN
+                    two = a3 > lim && finite;
+                    bl = encode_codeword_of(n1, __builtin_bit_cast(uint32_t, b1) & 15u);
+                }
+            };
+            if (!skip) {
+                float v0[KS][8], v1[KS][8];
+                fetch(0, v0);
+                if (KS <= 2 && second) fetch(1, v1);
+                rank(0, v0);
+                if (second) {
+                    if (KS > 2) fetch(1, v1);
+                    rank(1, v1);
+                }
+            }
             const float* cw = codewords + (size_t)(m0 + g) * L * Ds;
-            uint64_t rest = __ballot(!(sure && finite)) & 0xffffffffull;
+            uint64_t rest = __ballot(!sure && live);
+            const int open = __builtin_popcountll(rest);
+            hard = open > 32 ? hard | (1u << g) : hard & ~(1u << g);
+            if (open > ENC_DENSE || skip) {
+                // many: every lane forms all distances of its vector
+                const int64_t nc = live ? n : t * 32;
+                const int l = encode_all<KS, VEC>(vectors + ((size_t)nc * M + m0 + g) * Ds, cw, Ds);
+                bl = sure ? bl : l;
+                rest = 0;
+            }
             while (rest) {
-                // one vector, the wave together
+                // few: one vector at a time, the wave together
                 const int v = __builtin_ctzll(rest);
                 rest &= rest - 1;
-                int64_t nv = t * 32 + v;
-                nv = nv < N ? nv : N - 1;
+                const int64_t nv = (v < 32 ? t : t + stride) * 32 + (v & 31);
                 const float* xr = vectors + ((size_t)nv * M + m0 + g) * Ds;
                 float best = INFINITY;
                 int bi = IDX_NONE;
                 if (__builtin_amdgcn_readlane((int)two, v)) {
-                    const uint32_t n1 = (uint32_t)__builtin_amdgcn_readlane(__builtin_bit_cast(int, a1), v);
-                    const uint32_t n2 = (uint32_t)__builtin_amdgcn_readlane(__builtin_bit_cast(int, a2), v);
+                    const uint32_t v1 = (uint32_t)__builtin_amdgcn_readlane((int)n1, v);
+                    const uint32_t v2 = (uint32_t)__builtin_amdgcn_readlane((int)n2, v);
                     if (lane < 32) {
-                        const int l = codeword_of(lane < 16 ? n1 : n2, (uint32_t)lane & 15u);
+                        const int l = encode_codeword_of(lane < 16 ? v1 : v2, (uint32_t)lane & 15u);
                         const float d = encode_distance(xr, cw + (size_t)l * Ds, Ds);
                         if (d < best) { best = d; bi = l; }
                     }
@@ -278,9 +417,9 @@ __global__ __launch_bounds__(THREADS) void encode_mfma_kernel(const float* __res
                     const int oi = __shfl_xor(bi, off);
                     if (ob < best || (ob == best && oi < bi)) { best = ob; bi = oi; }
                 }
-                if ((lane & 31) == v) bl = bi == IDX_NONE ? 0 : bi;
+                if (lane == v) bl = bi == IDX_NONE ? 0 : bi;
             }
-            if (half == 0 && n < N) codes[n * M + m0 + g] = (uint8_t)bl;
+            if (live) codes[n * M + m0 + g] = (uint8_t)bl;
         }
     }
 }

@@ -127,3 +127,49 @@ def test_encode_codewords_on_a_sphere(env, Ds):
     for size in (1e-6, 1e-5, 1e-4, 1e-3):
         vectors = (size * rng.standard_normal((500, 2 * Ds))).astype(np.float32)
         assert np.array_equal(_encode(env, vectors, cw), oracle.encode(vectors, cw))
+
+
+@pytest.mark.parametrize("M,Ds,N", [(3, 1, 4000), (2, 4, 70_000), (5, 7, 6000), (2, 16, 40_000), (1, 33, 9000), (2, 64, 20_000), (1, 100, 3000)])
+@pytest.mark.parametrize("kind", ["offset", "two clusters", "few of them open"])
+def test_encode_open_vectors(env, M, Ds, N, kind):
+    """Data whose gaps are small against their size or their spread, with the tiles of 32 in every state: all open, some, none;
+    enough of them that a wave goes on after tiles it had to settle on the vector units."""
+    oracle = env[1]
+    rng = np.random.default_rng(Ds + N)
+    cw = rng.standard_normal((M, 256, Ds))
+    vectors = rng.standard_normal((N, M, Ds))
+    if kind == "offset":
+        cw, vectors = cw + 1000.0, vectors + 1000.0
+    elif kind == "two clusters":
+        cw += 300.0 * (rng.random((M, 256, 1)) < 0.5)
+        vectors += 300.0 * (rng.random((N, M, 1)) < 0.5)
+    else:
+        cw[:, ::2] = cw[:, 1::2]                                       # every codeword twice
+        cw[:, 64:128] *= 1e3
+        vectors[rng.random(N) < 0.1] *= 1e3
+    cw, vectors = cw.astype(np.float32), vectors.astype(np.float32).reshape(N, M * Ds)
+    assert np.array_equal(_encode(env, vectors, cw), oracle.encode(vectors, cw))
+    assert np.array_equal(_encode(env, vectors[: N // 3], cw, 1), oracle.encode(vectors[: N // 3], cw))
+
+
+def test_encode_time_does_not_depend_on_a_common_offset(env):
+    """The share of open vectors, and with it the time, is that of the centred data."""
+    pq, _, torch = env
+    g = torch.Generator(device="cuda")
+    g.manual_seed(1)
+    v = torch.randn(300_000, 128, generator=g, device="cuda")
+    cw = torch.randn(4, 256, 32, generator=g, device="cuda")
+
+    def best_us(shift):
+        a, b = v + shift, cw + shift
+        times = []
+        for _ in range(5):
+            s, e = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            s.record()
+            pq.encode(a, b)
+            e.record()
+            torch.cuda.synchronize()
+            times.append(s.elapsed_time(e) * 1e3)
+        return min(times)
+
+    assert best_us(100.0) < 3.0 * best_us(0.0)                         # 13 times before the data were centred
