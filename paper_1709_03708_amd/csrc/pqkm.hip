@@ -1361,16 +1361,28 @@ pqkm_status assign_tiled(const uint8_t* codes, int64_t N, const uint8_t* centers
     return PQKM_OK;
 }
 
-// Scan with one lane per center: from this many centers on the table rows of a block's codes are copied to LDS first
-// (measured, M = 4, per code: 0.64 ns without and 1.05 ns with the copies at K = 100, 4.4 and 1.5 ns at K = 1000)
-constexpr int GATHER_ROWS_MIN_K = 160;
+// Scan with one lane per center: from this many centers on the table rows of a block's codes are copied to LDS first.
+// Several codes per block (aligned operands, M = 4, 8, 16, 32), M = 4, per code: 0.64 ns without and 1.05 ns with the copies at
+// K = 100, 4.4 and 1.5 ns at K = 1000.  One code per block, N = 4e5, ms without / with: M = 1, K = 2000: 0.76 / 2.07, M = 6:
+// 1.22 / 2.17 at K = 500 and 4.7 / 3.8 at K = 2000, M = 24: 1.99 / 4.33 at K = 200 and 9.2 / 6.8 at K = 1000.
+inline int gather_rows_min_k(int M, bool words) { return words ? 160 : 250 + 6000 / M; }
+
+// With few centers most of its lanes have none, and one lane per code (assign_generic_kernel) is faster: that takes about
+// 0.27 us per look-up of a code while the codes do not fill the chip and 3.9 ps each beyond, the scan above 0.75 ns and 0.03 ns
+// M per code.  Measured, one lane per code / per center, us: M = 2, K = 16: 11 / 19 at N = 2e4, 44 / 333 at 4e5; M = 6, N = 4e5:
+// 138 / 445 at K = 16, 599 / 471 at 64; M = 24, N = 4e5: 169 / 950 at K = 4, 800 / 1330 at 16, 3700 / 1450 at 64.
+bool lane_per_code(int64_t N, int M, int K)
+{
+    const double fill = 0.0033 * (double)N;
+    return (double)K * M < (fill < 215.0 ? fill : 215.0) * (1.0 + M / 22.0);
+}
 
 // Most codes for which it is faster than the tiled scans (M = 4, 8, 16, 32), whose time does not depend on N below one
 // round of their smallest workgroups: at M = 4 10 us + 74 ns K against 10 us + N (0.96 ns + 0.00062 ns K), equal at
 // 47000 codes for K = 1000 and 100000 for K = 8000, later for larger M; without rows equal at about 18000 codes.
 int64_t gather_max_codes(int K)
 {
-    return K < GATHER_ROWS_MIN_K ? 16384 : (int64_t)120000 * K / (1550 + (int64_t)K);
+    return K < 160 ? 16384 : (int64_t)120000 * K / (1550 + (int64_t)K);
 }
 
 // does one of the LDS-tiled scans run?
@@ -1401,7 +1413,7 @@ pqkm_status launch_gather(const uint8_t* codes, int64_t N, int M, const uint8_t*
         float* dn = dist ? dist + n0 : nullptr;
         NearRecord* pn = splits > 1 ? part : nullptr;
         const dim3 grid((unsigned)blocks, (unsigned)splits);
-        if (K >= GATHER_ROWS_MIN_K)
+        if (K >= gather_rows_min_k(M, MW > 0))
             hipLaunchKernelGGL((assign_gather_kernel<MW, CN, true>), grid, dim3(256), 0, st, codes + n0 * M, cnt, M, centers, K,
                                tables, assign + n0, dn, pn, per);
         else
@@ -1427,6 +1439,11 @@ pqkm_status assign_core(const Options& opt, const Carve& c, const uint8_t* codes
         if (words && M == 8) return launch_gather<2, 4>(codes, N, M, centers, K, tables, assign, dist, part, room, st);
         if (words && M == 16) return launch_gather<4, 2>(codes, N, M, centers, K, tables, assign, dist, part, room, st);
         if (words && M == 32) return launch_gather<8, 1>(codes, N, M, centers, K, tables, assign, dist, part, room, st);
+        if (lane_per_code(N, M, K)) {
+            hipLaunchKernelGGL(assign_generic_kernel, dim3((unsigned)((N + 255) / 256)), dim3(256), 0, st, codes, N, M, centers, K,
+                               tables, assign, dist);
+            return launched();
+        }
         return launch_gather<0, 1>(codes, N, M, centers, K, tables, assign, dist, part, room, st);
     }
     float* img = reinterpret_cast<float*>(static_cast<char*>(ws) + c.img_off);

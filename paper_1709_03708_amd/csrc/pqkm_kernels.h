@@ -640,6 +640,30 @@ __global__ __launch_bounds__(256) void assign_gather_kernel(const uint8_t* __res
     }
 }
 
+// One lane per code, centers in ascending order, table entries through the caches: few centers, any M.
+__global__ __launch_bounds__(256) void assign_generic_kernel(const uint8_t* __restrict__ codes, int64_t N, int M,
+                                                             const uint8_t* __restrict__ centers, int K,
+                                                             const float* __restrict__ tables,
+                                                             int32_t* __restrict__ assign, float* __restrict__ dist)
+{
+    const int64_t n = (int64_t)blockIdx.x * 256 + threadIdx.x;
+    if (n >= N) return;
+    const uint8_t* x = codes + n * M;
+    float best = INFINITY;
+    int bk = 0;
+    for (int k = 0; k < K; ++k) {
+        const uint8_t* mu = centers + (size_t)k * M;
+        float s = tables[(size_t)x[0] * L + mu[0]];
+        for (int m = 1; m < M; ++m) s = s + tables[((size_t)m * L + x[m]) * L + mu[m]];
+        if (s < best) {
+            best = s;
+            bk = k;
+        }
+    }
+    assign[n] = bk;
+    if (dist) dist[n] = best;
+}
+
 // one wave per code: the records of its `splits` blocks
 __global__ __launch_bounds__(256) void assign_merge_kernel(const NearRecord* __restrict__ part, int64_t N, int splits,
                                                            int32_t* __restrict__ assign, float* __restrict__ dist)
