@@ -1379,17 +1379,21 @@ bool lane_per_code(int64_t N, int M, int K)
 
 // Most codes for which it is faster than the tiled scans (M = 4, 8, 16, 32), whose time does not depend on N below one
 // round of their smallest workgroups: at M = 4 10 us + 74 ns K against 10 us + N (0.96 ns + 0.00062 ns K), equal at
-// 47000 codes for K = 1000 and 100000 for K = 8000, later for larger M; without rows equal at about 18000 codes.
-int64_t gather_max_codes(int K)
+// 47000 codes for K = 1000 and 100000 for K = 8000, later for larger M.  Without rows 7 us + 0.6 ns N against 7 us + 2.8 us for
+// every 32 centers at M = 4, 4.7 us at M = 8 and 7 us at M = 16 (N = 16384, K = 16: 16.5 / 10.4, 15.9 / 11.9, 20.6 / 15.6 us;
+// M = 4, K = 100, N = 1e4: 12 / 18).
+int64_t gather_max_codes(int M, int K)
 {
-    return K < 160 ? 16384 : (int64_t)120000 * K / (1550 + (int64_t)K);
+    if (K >= 160) return (int64_t)120000 * K / (1550 + (int64_t)K);
+    const int64_t most = (int64_t)(M == 4 ? 4700 : M == 8 ? 7800 : 11600) * ((K + 31) / 32);
+    return M == 32 || most > 16384 ? 16384 : most;
 }
 
 // does one of the LDS-tiled scans run?
 bool tiled_scan(const Options& opt, int64_t N, int M, int K, const uint8_t* codes)
 {
     if (!tiled_M(M) || opt.assign_kernel == 1 || ((uintptr_t)codes & 3) != 0) return false;
-    return opt.assign_kernel != 0 || opt.scan_variant != 0 || N > gather_max_codes(K);
+    return opt.assign_kernel != 0 || opt.scan_variant != 0 || N > gather_max_codes(M, K);
 }
 
 template <int MW, int CN>

@@ -94,3 +94,9 @@ def test_copy_is_placed_for_the_scan_that_reads_it(pq, M, N, K):
     plans = _walk(pq, N, M, K, 6)
     assert plans[0]["scan"] == 1 and plans[-1]["scan"] == 2
     assert plans[-1]["lanes"] == 2 and plans[-1]["reuse"] and plans[-1]["seeded"] == 2
+
+
+@pytest.mark.parametrize("M,K,most", [(4, 16, 4700), (4, 64, 9400), (4, 100, 16384), (8, 16, 7800), (8, 100, 16384), (16, 3, 11600), (32, 1, 16384)])
+def test_few_codes_take_no_more_than_a_round_of_tiles(pq, M, K, most):
+    """One lane per center only up to the codes for which it is the faster one: with few centers the tiled scans are cheap."""
+    assert pq.scan_plan(most, M, K)["scan"] == 0 and pq.scan_plan(most + 1, M, K)["scan"] == 1
