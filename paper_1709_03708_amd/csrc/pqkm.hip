@@ -1040,13 +1040,21 @@ struct SubspaceHist { int G, S; };
 SubspaceHist subspace_hist(int64_t N, int M, int K, const Carve& c)
 {
     SubspaceHist p{0, 1};
-    // below 65536 codes the owner path's more, smaller workgroups are faster (1e4 codes, K = 100: 11 us against 13 us)
-    if (N < 65536 || N > (int64_t)0xffffffff || (int64_t)K * L > SUBSPACE_HIST_WORDS) return p;
+    // Every workgroup reads a word of every code of its slice, whatever M is, and leaves K G KB for the vote to add; the owner
+    // path reads a byte per code and group, but a heavy cluster is the work of one of its workgroups.  Clusters of even size, whole
+    // update, owner / this, us: M = 4, K = 100: 42 / 54 at N = 5e5, 54 / 57 at 1e6, 104 / 87 at 3e6; M = 8, K = 100: 60 / 72 at
+    // 1e6, 120 / 90 at 3e6; M = 16, K = 100: 72 / 110 at 1e6, 150 / 145 at 3e6; M = 32, K = 100: 96 / 285 at 1e6, 208 / 412 at
+    // 3e6; M = 4, K = 10: 82 / 113 at 3e6; M = 16, K = 10: 68 / 63 at 1e6.  Uneven clusters (a power law): M = 4, K = 100, 1e6:
+    // 150 / 58, M = 8, 3e6: 666 / 91.  Taken where it does not cost even clusters more than a few per cent.
+    if (N > (int64_t)0xffffffff || (int64_t)K * L > SUBSPACE_HIST_WORDS) return p;
+    if (!(K >= 32 && M >= 4 && M <= 16 && N >= (int64_t)300000 * M) && !(K < 32 && M >= 16 && N >= 1000000)) return p;
     p.G = 1;
     while (p.G < 4 && p.G * 2 <= M && (int64_t)K * L * p.G * 2 <= SUBSPACE_HIST_WORDS) p.G *= 2;
     const int64_t room = (int64_t)(c.seg_off - c.sidx_off) / (int64_t)align256(c.hist_bytes);
     const int64_t groups = (M + p.G - 1) / p.G;
     while (p.S < 16 && p.S * 2 <= room && groups * p.S * 2 <= cu_count() && N / (p.S * 2) >= 2048) p.S *= 2;
+    // with fewer slices (no room for their arrays) the chip is half idle: M = 4, K = 128, N = 1e6: 70 us with 8
+    if (K >= 32 && p.S < 16) p.G = 0;
     return p;
 }
 

@@ -34,7 +34,10 @@ def _assignment(rng, kind, N, K):
 @pytest.mark.parametrize("M,N,K,hist_kernel", [
     (4, 90_001, 1, 0), (4, 70_003, 100, 0), (4, 70_001, 128, 0), (4, 9001, 129, 0), (8, 70_000, 31, 0), (3, 70_007, 60, 0),
     (16, 66_001, 128, 0), (32, 65_536, 17, 0), (6, 66_000, 33, 0), (8, 60_001, 500, 3), (8, 200_003, 3000, 3), (4, 30_000, 9000, 3),
-    (32, 30_001, 300, 3), (5, 40_000, 700, 3), (4, 20_000, 33_000, 3)])
+    (32, 30_001, 300, 3), (5, 40_000, 700, 3), (4, 20_000, 33_000, 3),
+    # counted by subspace: all clusters of one or several subspaces in a workgroup
+    (4, 1_200_001, 33, 0), (4, 1_200_003, 100, 0), (4, 1_200_007, 128, 0), (6, 1_800_001, 61, 0), (8, 2_400_000, 100, 0),
+    (16, 1_000_009, 17, 0), (32, 1_000_001, 31, 0)])
 @pytest.mark.parametrize("kind", ["even", "one", "heavy", "tail"])
 def test_update(env, M, N, K, hist_kernel, kind):
     pq, oracle, torch = env
@@ -55,12 +58,12 @@ def test_update(env, M, N, K, hist_kernel, kind):
     np.testing.assert_array_equal(d.cpu().numpy(), rcen)
 
 
-@pytest.mark.parametrize("K,hist_kernel", [(100, 0), (2000, 3)])
-def test_dropped_assignments(env, K, hist_kernel):
+@pytest.mark.parametrize("N,K,hist_kernel", [(70_001, 100, 0), (1_200_001, 100, 0), (70_001, 2000, 3)])
+def test_dropped_assignments(env, N, K, hist_kernel):
     """Values outside [0, K) are ignored."""
     pq, oracle, torch = env
     rng = np.random.default_rng(K)
-    N, M = 70_001, 4
+    M = 4
     codes = rng.integers(0, 256, (N, M), dtype=np.uint8)
     a = rng.integers(-3, K + 3, N).astype(np.int32)
     a[:5] = [-2**31, 2**31 - 1, K, -1, K + 1]
