@@ -1614,12 +1614,15 @@ pqkm_status update_impl(const Options& opt, const Carve& c, const uint8_t* codes
         const int64_t ng = ((int64_t)K + KT - 1) / KT;
         const int64_t twice = 2 * ((N + ng - 1) / ng);
         const uint32_t most = (uint32_t)(twice > 8192 ? (twice < 0x40000000 ? twice : 0x40000000) : 8192);
-        int64_t shares = (N + most - 1) / most;
-        if (shares > 32) shares = 32;
-        if (shares > 1)
-            hipLaunchKernelGGL(seg_zero_kernel, dim3((unsigned)ng), dim3(256), 0, st, start, M, K, KT, most, hist);
-        hipLaunchKernelGGL(seg_hist_kernel, dim3((unsigned)ng, (unsigned)shares), dim3(1024), 0, st, codes, M, start, sidx, K, KT,
-                           shares > 1 ? most : 0xffffffffu, hist);
+        // further shares: at most half as many as groups, listed in the room of the cluster sizes, which are not needed any more
+        const int64_t further = ng > 1 ? N / most : 0;
+        const size_t seg_stride = align256(((size_t)K + 1) * sizeof(uint32_t));
+        uint2* items = reinterpret_cast<uint2*>(static_cast<char*>(ws) + c.seg_off);
+        uint32_t* listed = reinterpret_cast<uint32_t*>(static_cast<char*>(ws) + c.seg_off + 2 * seg_stride) + K;
+        if (further > 0)
+            hipLaunchKernelGGL(seg_zero_kernel, dim3((unsigned)ng), dim3(256), 0, st, start, M, K, KT, most, hist, listed, items);
+        hipLaunchKernelGGL(seg_hist_kernel, dim3((unsigned)(ng + further)), dim3(1024), 0, st, codes, M, start, sidx, K, KT,
+                           further > 0 ? most : 0xffffffffu, (int)ng, listed, items, hist);
     } else {
         zero_hist();
         const int64_t per = (int64_t)1 << 30;

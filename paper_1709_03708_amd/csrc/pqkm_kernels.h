@@ -3526,7 +3526,10 @@ __global__ __launch_bounds__(1024) void seg_prefix_kernel(const uint32_t* __rest
         if (tid == 1023) carry = e + v;
         __syncthreads();
     }
-    if (tid == 0) start[K] = carry;
+    if (tid == 0) {
+        start[K] = carry;
+        cursor[K] = 0u;                  // counts the shares that seg_zero_kernel lists
+    }
 }
 
 __global__ __launch_bounds__(256) void seg_scatter_kernel(const int32_t* __restrict__ assign, int64_t N, int K,
@@ -3583,22 +3586,31 @@ __global__ __launch_bounds__(256) void seg_place_kernel(const int32_t* __restric
     }
 }
 
-// Workgroup (b, p) owns clusters b*KT .. b*KT+KT-1; LDS holds KT*M*256 counters (at most HIST_LDS_WORDS).  Clusters are of
-// uneven size, and one workgroup with ten times the average of codes would be what the step takes: a group of more than
-// `most` codes is shared by up to gridDim.y workgroups, which add their counters to the result that seg_zero_kernel
-// cleared; any other group has one, which stores them.  Measured, 2e6 codes of a mixture, M = 8, K = 5000: 450 us -> 114 us.
-__device__ __forceinline__ uint32_t seg_shares(uint32_t codes, uint32_t most, uint32_t at_most)
+// A workgroup owns the clusters b*KT .. b*KT+KT-1 of a group b; LDS holds KT*M*256 counters (at most HIST_LDS_WORDS).  Clusters
+// are of uneven size, and one workgroup with ten times the average of codes would be what the step takes: a group of more than
+// `most` codes is shared by several workgroups, which add their counters to the result that seg_zero_kernel cleared; any other
+// group has one, which stores them.  The first workgroups of the grid take the first share of every group, the others what
+// seg_zero_kernel lists (a grid of groups x shares would be nearly all empty workgroups of 128 KB of LDS: 60 to 80 us at
+// K = 30000).  Measured, 2e6 codes of a mixture, M = 8, K = 5000: 450 us -> 114 us.
+__device__ __forceinline__ uint32_t seg_shares(uint32_t codes, uint32_t most)
 {
-    const uint32_t p = (codes + most - 1) / most;
-    return p < 1u ? 1u : p < at_most ? p : at_most;
+    return codes <= most ? 1u : (codes - 1) / most + 1u;
 }
 
+// clears the histograms of the groups that are shared and lists their further shares: (group, share) in `items`, at most
+// (number of codes) / most
 __global__ __launch_bounds__(256) void seg_zero_kernel(const uint32_t* __restrict__ start, int M, int K, int KT, uint32_t most,
-                                                       uint32_t* __restrict__ hist)
+                                                       uint32_t* __restrict__ hist, uint32_t* __restrict__ count,
+                                                       uint2* __restrict__ items)
 {
+    __shared__ uint32_t at;
     const int k0 = blockIdx.x * KT;
     const int nk = K - k0 < KT ? K - k0 : KT;
-    if (start[k0 + nk] - start[k0] <= most) return;
+    const uint32_t shares = seg_shares(start[k0 + nk] - start[k0], most);
+    if (shares == 1u) return;
+    if (threadIdx.x == 0) at = atomicAdd(count, shares - 1u);
+    __syncthreads();
+    for (uint32_t i = threadIdx.x; i < shares - 1u; i += 256) items[at + i] = make_uint2(blockIdx.x, i + 1u);
     uint32_t* out = hist + (size_t)k0 * M * L;
     for (int i = threadIdx.x; i < nk * M * L; i += 256) out[i] = 0u;
 }
@@ -3606,22 +3618,29 @@ __global__ __launch_bounds__(256) void seg_zero_kernel(const uint32_t* __restric
 __global__ __launch_bounds__(1024) void seg_hist_kernel(const uint8_t* __restrict__ codes, int M,
                                                         const uint32_t* __restrict__ start,
                                                         const uint32_t* __restrict__ sidx, int K, int KT, uint32_t most,
-                                                        uint32_t* __restrict__ hist)
+                                                        int groups, const uint32_t* __restrict__ count,
+                                                        const uint2* __restrict__ items, uint32_t* __restrict__ hist)
 {
     __shared__ uint32_t lh[32768];
     __shared__ uint32_t st[130];
     const int tid = threadIdx.x;
-    const int k0 = blockIdx.x * KT;
+    uint32_t group = blockIdx.x, part = 0u;
+    if ((int)blockIdx.x >= groups) {
+        const uint32_t e = blockIdx.x - (uint32_t)groups;
+        if (e >= *count) return;
+        group = items[e].x;
+        part = items[e].y;
+    }
+    const int k0 = (int)group * KT;
     const int nk = K - k0 < KT ? K - k0 : KT;
     const int words = nk * M * L;
     const uint32_t first = start[k0], last = start[k0 + nk];
-    const uint32_t shares = seg_shares(last - first, most, gridDim.y);
-    if (blockIdx.y >= shares) return;
+    const uint32_t shares = seg_shares(last - first, most);
     for (int i = tid; i < words; i += 1024) lh[i] = 0u;
     for (int i = tid; i <= nk; i += 1024) st[i] = start[k0 + i];
     __syncthreads();
     const uint32_t share = (last - first + shares - 1) / shares;
-    const uint32_t p0 = first + blockIdx.y * share;
+    const uint32_t p0 = first + part * share;
     const uint32_t p1 = last - p0 < share ? last : p0 + share;
     const bool wordwise = (M & 3) == 0 && ((uintptr_t)codes & 3) == 0;
     constexpr int PER = 4;                        // positions per thread whose loads travel together

@@ -35,6 +35,8 @@ def _assignment(rng, kind, N, K):
     (4, 90_001, 1, 0), (4, 70_003, 100, 0), (4, 70_001, 128, 0), (4, 9001, 129, 0), (8, 70_000, 31, 0), (3, 70_007, 60, 0),
     (16, 66_001, 128, 0), (32, 65_536, 17, 0), (6, 66_000, 33, 0), (8, 60_001, 500, 3), (8, 200_003, 3000, 3), (4, 30_000, 9000, 3),
     (32, 30_001, 300, 3), (5, 40_000, 700, 3), (4, 20_000, 33_000, 3),
+    # shares of heavy groups, few and many of them, and as many groups as codes would fill
+    (4, 400_000, 33, 3), (4, 300_000, 9000, 3), (32, 150_000, 2000, 3), (64, 40_000, 130, 3), (4, 500_000, 30_000, 0),
     # counted by subspace: all clusters of one or several subspaces in a workgroup
     (4, 1_200_001, 33, 0), (4, 1_200_003, 100, 0), (4, 1_200_007, 128, 0), (6, 1_800_001, 61, 0), (8, 2_400_000, 100, 0),
     (16, 1_000_009, 17, 0), (32, 1_000_001, 31, 0)])
