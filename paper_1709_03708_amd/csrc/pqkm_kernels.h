@@ -496,7 +496,7 @@ __global__ __launch_bounds__(256) void decode_kernel(const uint8_t* __restrict__
     }
 }
 
-// the same one element per thread, for outputs or codewords that are not 16-byte aligned
+// the same one element per thread: outputs or codewords that are not 16-byte aligned, small outputs of odd lengths
 __global__ __launch_bounds__(256) void decode_element_kernel(const uint8_t* __restrict__ codes, int64_t total, int M, int Ds,
                                                              const float* __restrict__ codewords, float* __restrict__ out)
 {

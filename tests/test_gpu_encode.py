@@ -173,3 +173,15 @@ def test_encode_time_does_not_depend_on_a_common_offset(env):
         return min(times)
 
     assert best_us(100.0) < 3.0 * best_us(0.0)                         # 13 times before the data were centred
+
+
+@pytest.mark.parametrize("M,Ds,N", [(3, 7, 199_728), (3, 7, 199_729), (5, 6, 139_811), (16, 3, 100_001), (32, 9, 14_600), (1, 1, 4_194_307),
+                                    (2, 1001, 2200)])
+def test_decode_odd_lengths(env, M, Ds, N):
+    """Both sides of the sizes from which a thread writes four elements of an odd length, and ragged ends of those."""
+    pq, oracle, torch = env
+    rng = np.random.default_rng(N)
+    cw = rng.standard_normal((M, 256, Ds)).astype(np.float32)
+    codes = rng.integers(0, 256, (N, M), dtype=np.uint8)
+    got = pq.decode(torch.from_numpy(codes).cuda(), torch.from_numpy(cw).cuda()).cpu().numpy()
+    assert np.array_equal(got, cw[np.arange(M), codes].reshape(N, M * Ds))
