@@ -93,8 +93,11 @@ inline bool tiled_M(int M) { return M == 4 || M == 8 || M == 16 || M == 32; }
 struct Carve {
     size_t img_off, img_bytes, hist_off, hist_bytes, counts_off, counts_bytes, parts_off, parts_bytes, gid_off,
         gid_bytes, gco_off, plan_off, rows_off, gc8_off, plan8_off, sidx_off, seg_off, pool_off, bseg_off, skew_off,
-        rank_off, tabt_off, rowoff_off, state_off, total;
+        rank_off, tabt_off, rowoff_off, state_off, side_off, total;
 };
+
+// room of the M = 8 lower-bound scan for what lasts from one iteration to the next (FilterSide)
+inline size_t filter_side_bytes(int M, int K) { return 4096 + 512 + 2 * align256((size_t)K * M); }
 
 // The regrouped copy of the codes (M = 4 scan) covers one scan launch of at most this many codes.
 constexpr int64_t GROUP_CHUNK_MAX = (int64_t)1 << 26;
@@ -220,6 +223,13 @@ Carve carve(int64_t N, int M, int K)
     if (M == 16 || M == 32) {
         const int64_t na = sw_alloc(N < GROUP_CHUNK_MAX ? N : GROUP_CHUNK_MAX);
         off += align256((size_t)na * (size_t)(M / 4 + 1) * sizeof(uint32_t));
+    }
+    // the side room of the M = 8 lower-bound scan, unless a problem that pqkm_assign_noalloc can hold would not fit any more (it
+    // then runs the plain scans)
+    c.side_off = 0;
+    if (M == 8 && !(off <= PQKM_NOALLOC_SCRATCH_BYTES && off + filter_side_bytes(M, K) > PQKM_NOALLOC_SCRATCH_BYTES)) {
+        c.side_off = off;
+        off += filter_side_bytes(M, K);
     }
     c.total = off;
     return c;
@@ -645,8 +655,13 @@ int choose_scan4_large(int64_t n)
 // through the L2 each: several in the first iteration, less from the bound that the center of the iteration before gives,
 // less still once most centers no longer change.  Measured against the plain scans, ms per iteration, N = 1e6: first
 // 0.28 / 0.24 at K = 1000, 0.337 / 0.313 at 1500; second and third 0.181 / 0.180 at K = 700, 0.202 / 0.220 at 1000;
-// later 0.132 / 0.172 at K = 700.  N = 3e6, K = 2500: 1.02 / 1.27, 0.84 / 1.26, 0.69 / 1.26.
-inline int filter4_min_k(int iteration) { return iteration == 0 ? 1800 : iteration < 3 ? 900 : 500; }
+// later 0.132 / 0.172 at K = 700.  N = 3e6, K = 2500: 1.02 / 1.27, 0.84 / 1.26, 0.69 / 1.26.  Where one round of workgroups covers
+// the codes there is none to warn the next ones off tables that the bounds do not separate (K = 2500, distances of one dimension:
+// 2.1 times the plain scan, 1.0 over several rounds), so a first iteration needs more to gain: 0.95 at K = 2500, 0.8 at 5000.
+inline int filter4_min_k(int iteration, int64_t N)
+{
+    return iteration == 0 ? (N > (int64_t)cu_count() * 8192 ? 2500 : 4000) : iteration < 3 ? 900 : 500;
+}
 int filter4_codes_per_slot(int variant, int64_t n_alloc)
 {
     switch (variant) {
@@ -681,6 +696,7 @@ void launch_filter_rounds(const typename FilterCode<M>::Raw* gco, int64_t n_allo
     for (int64_t w0 = 0; w0 < nwg; w0 += per) {
         const int64_t cnt = nwg - w0 < per ? nwg - w0 : per;
         f.state = state + w0 * C;
+        f.launched = (int)w0;
         hipLaunchKernelGGL((assign_filter_kernel<M, R, THREADS, DEPTH, false>), dim3((unsigned)cnt), dim3(THREADS), 0, st, n_alloc - w0 * C,
                            gco + w0 * C, f, assign, dist, ro, BucketOut{});
         ++t_scan_kernels;
@@ -732,6 +748,39 @@ void launch_filter8(int variant, const uint4* gc8, int64_t n_alloc, const Filter
         case 16: launch_filter_rounds<8, 16, 512, 4>(gc8, n_alloc, f, assign, dist, st, ro, rounds_per_launch); break;
         default: launch_filter_rounds<8, 24, 512, 4>(gc8, n_alloc, f, assign, dist, st, ro, rounds_per_launch); break;
     }
+}
+
+// The plain scan of what a lower-bound scan left (it ends at once if that is nothing), in the shape that the rounds favour were
+// it everything: the LDS-direct scan at M = 4, the two-lane scan at M = 8.  Not counted as a scan kernel.
+void launch_left4(const uint2* gco, int64_t n_alloc, const float4* img, const float4* rows, int ntiles, int nhalves,
+                  const FilterIn& f, int32_t* assign, float* dist, hipStream_t st, RankOut ro, const BucketOut* bo)
+{
+    const int64_t ncu = cu_count();
+    auto wgs = [&](int R) { return (n_alloc + 512 * R - 1) / (512 * R); };
+    auto cost = [&](int R) { return (double)((wgs(R) + ncu - 1) / ncu) * (2.45 * 512 * R + 1064.0); };     // choose_scan4_large
+    if (bo)
+        hipLaunchKernelGGL((assign_scan4h_kernel<8, 1024, 3, true, true>), dim3((unsigned)wgs(8)), dim3(1024), 0, st, n_alloc, gco,
+                           img, rows, ntiles, nhalves, assign, dist, RankOut{}, *bo, f.state);
+    else if (cost(8) < cost(16))
+        hipLaunchKernelGGL((assign_scan4h_kernel<8, 1024, 3, false, true>), dim3((unsigned)wgs(8)), dim3(1024), 0, st, n_alloc, gco,
+                           img, rows, ntiles, nhalves, assign, dist, ro, BucketOut{}, f.state);
+    else
+        hipLaunchKernelGGL((assign_scan4h_kernel<16, 1024, 3, false, true>), dim3((unsigned)wgs(16)), dim3(1024), 0, st, n_alloc, gco,
+                           img, rows, ntiles, nhalves, assign, dist, ro, BucketOut{}, f.state);
+}
+
+void launch_left8(const uint4* gc8, int64_t n_alloc, const float4* img, int ntiles, const FilterIn& f, int32_t* assign, float* dist,
+                  hipStream_t st, RankOut ro)
+{
+    const int64_t ncu = cu_count();
+    auto wgs = [&](int R) { return (n_alloc + 256 * R - 1) / (256 * R); };
+    auto cost = [&](int R) { return ((wgs(R) + ncu - 1) / ncu) * (2 * R + 13); };                          // scan8q_codes_per_slot
+    if (cost(16) < cost(24))
+        hipLaunchKernelGGL((assign_scan8q_kernel<16, 512, 3, true>), dim3((unsigned)wgs(16)), dim3(512), 0, st, n_alloc, gc8, img,
+                           ntiles, assign, dist, ro, f.state);
+    else
+        hipLaunchKernelGGL((assign_scan8q_kernel<24, 512, 2, true>), dim3((unsigned)wgs(24)), dim3(512), 0, st, n_alloc, gc8, img,
+                           ntiles, assign, dist, ro, f.state);
 }
 
 // the 4096-code shape, filing (code, center) records by cluster group for the histogram: all workgroups in one launch
@@ -1096,6 +1145,7 @@ void launch_filter_wide(const uint8_t* codes, int64_t N, uint32_t* S, FilterWide
     const int64_t nwg = (N + C - 1) / C;
     f.S = S;
     f.n_alloc = nwg * C;
+    f.spent = S + (size_t)(M / 4) * f.n_alloc;           // the room has a word per code more than the rotated words take
     f.codes = codes;
     hipLaunchKernelGGL((code_rotate_kernel<M>), dim3((unsigned)((f.n_alloc + 255) / 256)), dim3(256), 0, st, codes, N, S, f.n_alloc);
     // tiles per launch: all of them while there is one round of workgroups
@@ -1142,9 +1192,9 @@ ScanPlan scan_plan(int M, const Options& opt, int64_t N, int K, const uint8_t* c
     // Records to file (the fused iteration at owner-path sizes): the same scan in its 4096-code shape, which files
     // them as the four-lane scan does.
     // The lower-bound scan addresses its byte tiles through one 32-bit buffer offset and reads centers as words.
-    const bool filter_ok = (M == 4 || (M == 8 && K > 16)) && ((uintptr_t)centers & 3) == 0 && ((int64_t)K + 63) / 64 * (M * 16384) < (int64_t)0xfff00000;
+    const bool filter_ok = (M == 4 || (M == 8 && K > 16 && c.side_off > 0)) && ((uintptr_t)centers & 3) == 0 && ((int64_t)K + 63) / 64 * (M * 16384) < (int64_t)0xfff00000;
     if (M == 4 && variant == 70 && opt.scan_variant == 0)
-        variant = filter_ok && K >= filter4_min_k(iteration) ? (files_records ? 63 : 60)
+        variant = filter_ok && K >= filter4_min_k(iteration, N) ? (files_records ? 63 : 60)
                   : files_records ? 89 : choose_scan4_large(N);
     else if (variant_filter(M, variant) && !filter_ok)
         variant = M == 4 ? 85 : 80;
@@ -1207,30 +1257,24 @@ pqkm_status assign_tiled(const uint8_t* codes, int64_t N, const uint8_t* centers
     FilterStat* const wstat = reinterpret_cast<FilterStat*>(ws + c.hist_off);
     FilterScale* const wscale = reinterpret_cast<FilterScale*>(ws + c.hist_off + 8192);
     uint32_t* const gave_up = reinterpret_cast<uint32_t*>(ws + c.hist_off + 8448);
+    // M = 4, 8: byte tiles in the room of the images, which are built there only for codes that the scan left; the pair tables in
+    // that of the row-ordered images (M = 4) or behind the byte tiles, which take a quarter of the images' room (M = 8: at most
+    // 1 MB).  What lasts until the next iteration has a room of its own: statistics, the scale, two copies of the centers (this
+    // iteration's and the one before).
+    char* const side = M == 4 ? ws + c.tabt_off : ws + c.side_off;
+    const int nt64 = (K + FILTER_TK - 1) / FILTER_TK;
     FilterIn fin{};
+    uint32_t* pairs = nullptr;
+    uint8_t* this_copy = nullptr;
     if (filter) {
-        // (M = 8: behind the byte tiles, which take a quarter of the images' room)
-        char* const side = M == 4 ? ws + c.rows_off : ws + c.img_off + align256((size_t)((K + FILTER_TK - 1) / FILTER_TK) * M * FILTER_PLANE);
-        FilterStat* stat = reinterpret_cast<FilterStat*>(side);
-        const int nt = (K + FILTER_TK - 1) / FILTER_TK;
-        // statistics, the scale, then two copies of the centers (this iteration's, the one before) in the room of the
-        // row-ordered images
         static_assert(M * FILTER_PARTS * sizeof(FilterStat) <= 4096, "statistics");
-        FilterScale* scale = reinterpret_cast<FilterScale*>(side + 4096);
-        uint8_t* copies = reinterpret_cast<uint8_t*>(side) + 4352;
+        uint8_t* copies = M == 4 ? reinterpret_cast<uint8_t*>(ws + c.rowoff_off) : reinterpret_cast<uint8_t*>(side + 4096 + 512);
         const size_t copy_stride = align256((size_t)K * M);
-        uint32_t* pairs = reinterpret_cast<uint32_t*>(copies + 2 * copy_stride);     // at most 1 MB
-        if (!carried.stats)
-            hipLaunchKernelGGL(filter_stats_kernel, dim3(M * FILTER_PARTS), dim3(1024), 0, st, tables, stat);
-        hipLaunchKernelGGL((filter_image_kernel<M>), dim3((unsigned)(nt * M * 4)), dim3(256), 0, st, centers, K, tables, stat,
-                           reinterpret_cast<uint4*>(img), copies + (iteration & 1) * copy_stride, scale);
-        fin = FilterIn{reinterpret_cast<const uint4*>(img), tables, centers, scale,
-                       reinterpret_cast<unsigned long long*>(ws + c.state_off), K, nt, copies + ((iteration & 1) ^ 1) * copy_stride,
-                       pairs, plan_of.seeded};
-        if (plan_of.seeded == 3) {
-            hipLaunchKernelGGL(fill_i32_kernel, dim3(256), dim3(256), 0, st, reinterpret_cast<int32_t*>(pairs), (int64_t)(M / 2) * 65536, (int32_t)-1);
-            hipLaunchKernelGGL((filter_pairs_kernel<M>), dim3((unsigned)((K + 255) / 256)), dim3(256), 0, st, centers, K, pairs);
-        }
+        this_copy = copies + (iteration & 1) * copy_stride;
+        pairs = reinterpret_cast<uint32_t*>(M == 4 ? ws + c.rows_off : ws + c.img_off + align256((size_t)nt64 * M * FILTER_PLANE));
+        fin = FilterIn{reinterpret_cast<const uint4*>(img), tables, centers, reinterpret_cast<FilterScale*>(side + 4096),
+                       reinterpret_cast<unsigned long long*>(ws + c.state_off), K, nt64, copies + ((iteration & 1) ^ 1) * copy_stride,
+                       pairs, plan_of.seeded, reinterpret_cast<uint32_t*>(side + 4096 + 256), 0};
     } else if (sliding) {
         // tiles of 16 centers, plane-ordered: img[tile][m][x][16]
         ntiles = ((int64_t)K + 15) / 16;
@@ -1274,9 +1318,23 @@ pqkm_status assign_tiled(const uint8_t* codes, int64_t N, const uint8_t* centers
         hipLaunchKernelGGL(zero_u32_kernel, dim3(zb), dim3(256), 0, st, ro.count, (int64_t)K);
         link->ranked = true;
     }
+    // images that are built only for codes that a lower-bound scan left
+    const unsigned left_blocks = (unsigned)((total + 255) / 256 < 8192 ? (total + 255) / 256 : 8192);
     for (int64_t n0 = 0; n0 < N; n0 += per_launch) {
         int64_t cnt = N - n0 < per_launch ? N - n0 : per_launch;
         const RankOut rl{ro.count, ro.count ? ro.rank + n0 : nullptr};
+        if (filter) {
+            // for every stretch anew: the plain scan of the one before may have needed the room
+            FilterStat* stat = reinterpret_cast<FilterStat*>(side);
+            if (n0 == 0 && !carried.stats)
+                hipLaunchKernelGGL(filter_stats_kernel, dim3(M * FILTER_PARTS), dim3(1024), 0, st, tables, stat);
+            hipLaunchKernelGGL((filter_image_kernel<M>), dim3((unsigned)(nt64 * M * 4)), dim3(256), 0, st, centers, K, tables, stat,
+                               reinterpret_cast<uint4*>(img), this_copy, reinterpret_cast<FilterScale*>(side + 4096), fin.gave_up);
+            if (plan_of.seeded == 3) {
+                hipLaunchKernelGGL(fill_i32_kernel, dim3(256), dim3(256), 0, st, reinterpret_cast<int32_t*>(pairs), (int64_t)(M / 2) * 65536, (int32_t)-1);
+                hipLaunchKernelGGL((filter_pairs_kernel<M>), dim3((unsigned)((K + 255) / 256)), dim3(256), 0, st, centers, K, pairs);
+            }
+        }
         if (grouped && !plan_of.reuse) {
             const pqkm_status rs = (M == 8) ? regroup_codes8(codes + n0 * M, cnt, gc8, plan8, st, plan_of.lanes == 2)
                                             : regroup_codes(codes + n0 * M, cnt, gco, plan, st, plan_of.lanes == 2);
@@ -1304,10 +1362,10 @@ pqkm_status assign_tiled(const uint8_t* codes, int64_t N, const uint8_t* centers
                     launch_filter_wide<M>(codes + n0 * M, cnt, reinterpret_cast<uint32_t*>(ws + c.skew_off),
                                           FilterWideIn{reinterpret_cast<const uint4*>(img), nullptr, 0, nullptr, centers, tables, wscale,
                                                        reinterpret_cast<unsigned long long*>(ws + c.state_off),
-                                                       pairs ? pair_tab : nullptr, gave_up, K, 0, nt, nt, iteration > 0 ? 1 : 0},
+                                                       pairs ? pair_tab : nullptr, gave_up, nullptr, K, 0, nt, nt, iteration > 0 ? 1 : 0},
                                           assign + n0, dist ? dist + n0 : nullptr, st);
                     // what follows ends at once unless that scan gave up
-                    hipLaunchKernelGGL((tile_image_kernel<M, 0, 16>), dim3((unsigned)((total + 255) / 256)), dim3(256), 0, st,
+                    hipLaunchKernelGGL((tile_image_kernel<M, 0, 16>), dim3(left_blocks), dim3(256), 0, st,
                                        centers, K, tables, img, total, (float*)nullptr, (const uint32_t*)gave_up);
                 }
                 if (launch_scan_sw<M>(variant, codes + n0 * M, cnt, reinterpret_cast<uint32_t*>(ws + c.skew_off),
@@ -1316,18 +1374,34 @@ pqkm_status assign_tiled(const uint8_t* codes, int64_t N, const uint8_t* centers
                                       wide ? gave_up : nullptr) != PQKM_OK)
                     return PQKM_ERR_DEVICE;
             }
-        } else if (filter && files_records && variant == 63 && N <= per_launch) {
-            BucketOut bo{reinterpret_cast<uint2*>(ws + c.pool_off), reinterpret_cast<uint2*>(ws + c.bseg_off), link->KT,
-                         link->ngroups};
-            launch_filter4_bucket(gco, group_alloc(cnt), fin, assign + n0, dist ? dist + n0 : nullptr, st, bo, &link->nwg);
-            link->produced = true;
-        } else if (filter && M == 8)
-            launch_filter8(variant, gc8, group_alloc(cnt), fin, assign + n0, dist ? dist + n0 : nullptr, st, rl,
-                           opt.rounds_per_launch);
-        else if (filter)
-            launch_filter4(variant, gco, group_alloc(cnt), fin, assign + n0, dist ? dist + n0 : nullptr, st, rl,
-                           opt.rounds_per_launch);
-        else if (M == 8 && variant_two_lane(M, variant))
+        } else if (filter && M == 8) {
+            if constexpr (M == 8) {
+                launch_filter8(variant, gc8, group_alloc(cnt), fin, assign + n0, dist ? dist + n0 : nullptr, st, rl,
+                               opt.rounds_per_launch);
+                hipLaunchKernelGGL((tile_image_kernel<8, 0>), dim3(left_blocks), dim3(256), 0, st, centers, K, tables, img, total,
+                                   (float*)nullptr, (const uint32_t*)fin.gave_up);
+                launch_left8(gc8, group_alloc(cnt), reinterpret_cast<const float4*>(img), (int)ntiles, fin, assign + n0,
+                             dist ? dist + n0 : nullptr, st, rl);
+            }
+        } else if (filter) {
+            if constexpr (M == 4) {
+                const bool bucket = files_records && variant == 63 && N <= per_launch;
+                BucketOut bo{};
+                if (bucket) {
+                    bo = BucketOut{reinterpret_cast<uint2*>(ws + c.pool_off), reinterpret_cast<uint2*>(ws + c.bseg_off), link->KT,
+                                   link->ngroups};
+                    launch_filter4_bucket(gco, group_alloc(cnt), fin, assign + n0, dist ? dist + n0 : nullptr, st, bo, &link->nwg);
+                    link->produced = true;
+                } else {
+                    launch_filter4(variant, gco, group_alloc(cnt), fin, assign + n0, dist ? dist + n0 : nullptr, st, rl,
+                                   opt.rounds_per_launch);
+                }
+                hipLaunchKernelGGL((tile_image_kernel<4, 2>), dim3(left_blocks), dim3(256), 0, st, centers, K, tables, img, total,
+                                   reinterpret_cast<float*>(ws + c.rows_off), (const uint32_t*)fin.gave_up);
+                launch_left4(gco, group_alloc(cnt), reinterpret_cast<const float4*>(img), rows, (int)ntiles, (K + 15) / 16, fin,
+                             assign + n0, dist ? dist + n0 : nullptr, st, rl, bucket ? &bo : nullptr);
+            }
+        } else if (M == 8 && variant_two_lane(M, variant))
             launch_scan_grouped8_q(variant, gc8, group_alloc(cnt), reinterpret_cast<const float4*>(img), (int)ntiles,
                                    assign + n0, dist ? dist + n0 : nullptr, st, rl, opt.rounds_per_launch);
         else if (variant == 89 && files_records && N <= per_launch) {

@@ -17,8 +17,9 @@
 // capped, which only loosens the bound (between 1.5 and 2 the fewest centers pass on codes of clustered data).
 //
 // Where the bound selects too little (ties everywhere, tables without spread) forming the fp32 distances one by one
-// would be slower than the plain scan.  A workgroup counts the candidates it has formed, and when they exceed what the
-// plain scan would have cost it finishes its codes that way: fp32 tiles built in LDS from the tables.
+// would be slower than the plain scan.  A workgroup counts the candidates it has formed and gives up when what is left would
+// cost it more than the plain scan of everything (filter_budget); its codes are then left to the plain scan that is launched
+// behind this one and ends at once where nothing was left to it.
 #pragma once
 #include "pqkm_kernels.h"
 
@@ -29,6 +30,28 @@ constexpr int FILTER_Q_WIDE = 63;
 constexpr int FILTER_TK = 64;             // centers per tile: a row of one subcode is 64 bytes
 constexpr uint32_t FILTER_PLANE = 16384;  // bytes per (tile, subspace): 256 subcodes x 64 centers
 constexpr int FILTER_QUEUE = 128;         // candidate entries a wave can hold (drained from 64 on)
+
+// Clocks of a compute unit per code: the plain scan of 64 centers, this one's, and a candidate (M table entries through the
+// L2 at 5 clocks each), from the times beside the kernels below.  first, later: candidates per code that a first and a later
+// iteration may take before their rate counts.  Codes start from a bound that the first tiles improve: where the scan gains,
+// clustered codes and Gaussian codewords take 2 to 5 candidates in the first four tiles at M = 4, 3 to 7 at M = 8, 3 to 9 at
+// M = 16 and 6 to 12 at M = 32, and then 0.1 per tile and less; with distances that are small integers it is one per tile.
+template <int M> struct FilterCost;
+template <> struct FilterCost<4> { static constexpr float plain = 5.5f, scan = 1.7f, candidate = 20.0f, first = 6.0f, later = 2.0f; };
+template <> struct FilterCost<8> { static constexpr float plain = 12.0f, scan = 4.5f, candidate = 40.0f, first = 10.0f, later = 6.0f; };
+template <> struct FilterCost<16> { static constexpr float plain = 39.0f, scan = 22.0f, candidate = 80.0f, first = 10.0f, later = 7.0f; };
+template <> struct FilterCost<32> { static constexpr float plain = 64.0f, scan = 37.0f, candidate = 160.0f, first = 12.0f, later = 8.0f; };
+
+// Candidates per code that are worth going on with after t of T tiles.  Giving up costs the plain scan of all T tiles; going on,
+// the T - t that are left at the rate r of candidates per tile seen so far, (scan + r candidate) (T - t).  The two are equal at
+// r = (plain T / (T - t) - scan) / candidate.  On top of that what is free: `first` or `later`, or 0.25 (M = 16, 32: 0.3) of the plain scan.
+template <int M>
+__device__ __forceinline__ float filter_budget(int t, int T, bool later)
+{
+    typedef FilterCost<M> Cost;
+    const float rate = (Cost::plain * (float)T / (float)(T - t) - Cost::scan) * (1.0f / Cost::candidate);
+    return __builtin_fmaxf(later ? Cost::later : Cost::first, (M >= 16 ? 0.3f : 0.25f) * Cost::plain / Cost::candidate * (float)T) + (float)t * rate;
+}
 
 // statistics of the tables, FILTER_PARTS blocks per subspace; st[m * FILTER_PARTS + part]
 constexpr int FILTER_PARTS = 8;
@@ -204,12 +227,7 @@ __device__ __forceinline__ float filter_key_distance(unsigned long long key)
     const uint32_t o = (uint32_t)(key >> 32);
     return __builtin_bit_cast(float, o ^ ((o >> 31) ? 0x80000000u : 0xffffffffu));
 }
-__device__ __forceinline__ float filter_next_up(float v)          // the next float above a finite v or -inf
-{
-    const int32_t b = __builtin_bit_cast(int32_t, v + 0.0f);
-    return v == 0.0f ? 0x1p-149f : __builtin_bit_cast(float, b < 0 ? b - 1 : b + 1);
-}
-constexpr unsigned long long FILTER_NONE = ~0ull;        // no center selected yet
+constexpr unsigned long long FILTER_NONE = ~0ull;        // no center selected yet (GAVE_UP: left to the plain scan)
 
 struct FilterIn {
     const uint4* img;                // byte tiles
@@ -222,6 +240,8 @@ struct FilterIn {
     const uint32_t* pairs;           // seeded == 3: [M / 2][65536], a center with these two subcodes, or >= K
     int seeded;                      // 0: nothing known; 1: assign[] holds a center for every code (of the iteration before);
                                      // 2: so does `state`; 3: `pairs` names candidates
+    uint32_t* gave_up;               // workgroups of this stretch of codes that gave up
+    int launched;                    // workgroups of it in earlier launches: if most of those gave up, so do these
 };
 
 // a code of the regrouped array (M = 4: code, origin; M = 8: code, code, origin, -) and a center, packed in words
@@ -304,7 +324,7 @@ __global__ __launch_bounds__(THREADS) void assign_filter_kernel(int64_t N, const
     __shared__ float4 tile[TILE_F4];
     __shared__ uint32_t thr_s[SLOTS * TW];
     __shared__ uint2 queue_s[THREADS / 64][FILTER_QUEUE];
-    __shared__ uint32_t trips_s, bail_s[2];
+    __shared__ uint32_t spent_s, quit_s, bail_s[2];
     __shared__ uint32_t gcnt[BUCKET ? 256 : 1], gbase[BUCKET ? 256 : 1];
     const char* tb = reinterpret_cast<const char*>(tile);
     uint8_t* thr_b = reinterpret_cast<uint8_t*>(thr_s);
@@ -333,8 +353,25 @@ __global__ __launch_bounds__(THREADS) void assign_filter_kernel(int64_t N, const
 
     const FilterScale sc = *f.scale;
     const FilterWords<W>* cen = reinterpret_cast<const FilterWords<W>*>(f.centers);
-    if (tid == 0) trips_s = 0u;
+    static_assert(C % GAVE_UP_STEP == 0, "the plain scan looks at one key per step");
+    auto give_up = [&]() {
+        wait_vector_loads();                     // nothing may land in LDS after the workgroup has ended
+        for (int i = tid; i < C; i += THREADS)
+            if (base + i < N) f.state[base + i] = GAVE_UP;
+        if (tid == 0) atomicAdd(f.gave_up, 1u);
+    };
+    if (tid == 0) {
+        spent_s = 0u;
+        // tables that the bounds say nothing about
+        const uint32_t left = __hip_atomic_load(f.gave_up, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        quit_s = !(sc.inv > 0.0f) || (f.launched > 0 && 2u * left > (uint32_t)f.launched) ? 1u : 0u;
+    }
     if (tid < 2) bail_s[tid] = 0u;
+    __syncthreads();
+    if (quit_s) {
+        give_up();
+        return;
+    }
 
     // keys and thresholds of the workgroup's codes; the loads of a few codes travel together
     constexpr int SB = M == 8 ? 2 : (R / 2) % 4 == 0 ? 4 : (R / 2) % 3 == 0 ? 3 : 2;
@@ -377,7 +414,7 @@ __global__ __launch_bounds__(THREADS) void assign_filter_kernel(int64_t N, const
         } else if (f.seeded) {
 #pragma unroll
             for (int i = 0; i < SB; ++i) {
-                if (f.seeded == 1) k[i] = (uint32_t)assign[g[i].origin == ORIGIN_NONE ? 0u : g[i].origin];
+                if (f.seeded == 1 || old[i] == GAVE_UP) k[i] = (uint32_t)assign[g[i].origin == ORIGIN_NONE ? 0u : g[i].origin];
                 k[i] = k[i] < (uint32_t)f.K ? k[i] : 0u;             // any center will do
             }
 #pragma unroll
@@ -385,7 +422,7 @@ __global__ __launch_bounds__(THREADS) void assign_filter_kernel(int64_t N, const
                 // an unchanged center is as far as it was; table entries are fetched for the others only
                 const FilterWords<W> now = cen[k[i]];
                 s[i] = filter_key_distance(old[i]);
-                bool same = f.seeded == 2 && old[i] != FILTER_NONE;
+                bool same = f.seeded == 2 && old[i] != FILTER_NONE && old[i] != GAVE_UP;
                 if (same) {
                     const FilterWords<W> was = reinterpret_cast<const FilterWords<W>*>(f.before)[k[i]];
 #pragma unroll
@@ -427,9 +464,17 @@ __global__ __launch_bounds__(THREADS) void assign_filter_kernel(int64_t N, const
     };
 
     int qn = 0;                                  // entries in the wave's queue (the same in all lanes)
+    // candidates that the workgroup may have formed up to the tile at hand
+    const bool later = f.seeded == 1 || f.seeded == 2;
+    float allowed = filter_budget<M>(0, f.ntiles, later) * (float)C;
 
     // up to 64 entries, one lane each
     auto drain = [&]() __attribute__((always_inline)) {
+        if ((float)__builtin_amdgcn_readfirstlane(spent_s) > allowed) {
+            quit_s = 1u;
+            qn = 0;
+            return;
+        }
         const int cnt = qn < 64 ? qn : 64;
         qn -= cnt;
         __builtin_amdgcn_wave_barrier();
@@ -452,9 +497,11 @@ __global__ __launch_bounds__(THREADS) void assign_filter_kernel(int64_t N, const
         }
         float sb = INFINITY;
         uint32_t kb = 0xffffffffu;
-        int trips = 0;
-        while (__any(mask != 0u)) {
-            ++trips;
+        uint32_t formed = 0u;
+        while (true) {
+            const uint64_t who = __ballot(mask != 0u);
+            if (!who) break;
+            formed += (uint32_t)__builtin_popcountll(who);
             if (mask) {
                 const uint32_t bit = (uint32_t)__builtin_ctz(mask), j = 7u - (bit & 7u);
                 mask &= mask - 1u;
@@ -471,7 +518,7 @@ __global__ __launch_bounds__(THREADS) void assign_filter_kernel(int64_t N, const
             uint8_t* p = thr_b + slot * R + r;
             if (nt > *p) *p = (uint8_t)nt;
         }
-        if (lane == 0) atomicAdd(&trips_s, (uint32_t)trips);
+        if (lane == 0) atomicAdd(&spent_s, formed);
     };
     // The lanes with a clear high bit in what they hold of code r0 (a0; n0 is the and of its registers) or r1 append
     // their 32 centers: bit 8 b + 7 - j for byte b of register j.  A lane with both appends twice.
@@ -592,12 +639,13 @@ __global__ __launch_bounds__(THREADS) void assign_filter_kernel(int64_t N, const
     bool bail = false;
     for (; t < f.ntiles; ++t) {
         wait_vector_loads();
-        // one thread decides for all whether the candidates cost more than the plain scan would; its verdict of this
-        // turn stays untouched until everybody has passed the next barrier
-        if (tid == 0) bail_s[t & 1] = trips_s * 64u > (uint32_t)C * (96u + (uint32_t)t + ((uint32_t)t >> 2)) ? 1u : 0u;
+        // one thread says for all whether a wave has run out of its budget; its verdict of this turn stays untouched until
+        // everybody has passed the next barrier
+        if (tid == 0) bail_s[t & 1] = quit_s;
         __syncthreads();
         if (bail_s[t & 1]) { bail = true; break; }
         const bool more = t + 1 < f.ntiles;
+        allowed = filter_budget<M>(t, f.ntiles, later) * (float)C;
         if (BUFFERS == 2 && (t & 1)) scan_tile(IntC<BUFFERS - 1>{}, IntC<0>{}, t, more);
         else scan_tile(IntC<0>{}, IntC<0>{}, t, more);
         if (BUFFERS == 1 && more) {
@@ -606,58 +654,17 @@ __global__ __launch_bounds__(THREADS) void assign_filter_kernel(int64_t N, const
             for (int j = 0; j < M * CHUNKS; ++j) fetch(t + 1, 0, j);
         }
     }
-    while (qn > 0) drain();
-
-    if (bail) {
-        // The plain scan of what is left: 16 centers at a time as fp32 rows in the first buffer's planes.  All loads
-        // into LDS have been waited for above.
-        float best[R];
-        __syncthreads();
-#pragma unroll
-        for (int r = 0; r < R; ++r) {
-            const int64_t n = base + (int64_t)r * SLOTS + c;
-            const unsigned long long key = n < N ? __hip_atomic_load(&f.state[n], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : FILTER_NONE;
-            // the next float up, so that an equal distance at a lower index (the bound may come from a later center) still counts
-            best[r] = key == FILTER_NONE ? INFINITY : filter_next_up(filter_key_distance(key));
-        }
-        for (int k0 = t * FILTER_TK; k0 < f.K; k0 += 16) {
-            __syncthreads();
-            for (int e = tid; e < M * L * 16; e += THREADS) {
-                const int kin = e & 15, x = (e >> 4) & 255, m = e >> 12;
-                const int k = k0 + kin;
-                const float v = k < f.K ? f.tables[((size_t)m * L + x) * L + f.centers[(size_t)k * M + m]] : INFINITY;
-                reinterpret_cast<float*>(tile)[m * (STRIDE / 4) + x * 16 + kin] = v;
-            }
-            __syncthreads();
-#pragma unroll
-            for (int r = 0; r < R; ++r) {
-                float v[8];
-#pragma unroll
-                for (int m = 0; m < M; ++m) {
-                    const uint32_t ad = row_of(r, m), po = (uint32_t)(m % (M / 2)) * STRIDE;
-                    const float4 va = lds_read16(tb, ad + po), vb = lds_read16(tb, (ad ^ 32u) + po);
-                    const float w[8] = {va.x, va.y, va.z, va.w, vb.x, vb.y, vb.z, vb.w};
-#pragma unroll
-                    for (int j = 0; j < 8; ++j) v[j] = m == 0 ? w[j] : v[j] + w[j];
-                }
-                // lane's pieces of four centers: first read, second read
-                const uint32_t p0 = hq >> 4;
-                int kk = -1;
-#pragma unroll
-                for (int j = 0; j < 8; ++j) {
-                    const int k = k0 + 4 * (int)(j < 4 ? p0 : (p0 ^ 2u)) + (j & 3);
-                    if (v[j] < best[r] || (kk >= 0 && v[j] == best[r] && k < kk)) { best[r] = v[j]; kk = k; }
-                }
-                const int64_t n = base + (int64_t)r * SLOTS + c;
-                if (kk >= 0 && n < N) atomicMin(&f.state[n], filter_key(best[r], (uint32_t)kk));
-            }
-        }
-    }
+    if (!bail)
+        while (qn > 0) drain();
 
     // results: lane l finishes the codes l, l + THREADS, ...
     if (BUCKET && tid < 256) gcnt[tid] = 0u;
     wait_vector_loads();
     __syncthreads();
+    if (quit_s) {
+        give_up();
+        return;
+    }
 #pragma unroll 4
     for (int i = 0; i < R / 2; ++i) {
         const int jj = i * THREADS + tid;
@@ -729,8 +736,9 @@ __global__ __launch_bounds__(THREADS) void assign_filter_kernel(int64_t N, const
 // closest of the centers that share one of its first FILTER_WIDE_PAIRS pairs of subcodes, or else from the smallest sum
 // of the first tile.  A launch covers a round of workgroups and the tiles of 4 MB: all rounds pass over them before
 // the next ones, so that they come from the L2 (a phase is scanned in less than the time a load from memory takes, and one
-// phase is all there is room to load ahead); keys carry the state from one launch to the next.  A workgroup whose candidates cost more than the plain scan sets *gave_up, those of later launches stop
-// at once when they see it, and the plain scan that is launched behind this one does all the work.
+// phase is all there is room to load ahead); keys and the count of candidates carry over from one launch to the next.  A
+// workgroup that has used up its budget sets *gave_up, those of later launches stop at once when they see it, and the plain
+// scan that is launched behind this one does all the work.
 // A phase of 1024 codes is short (0.8 us of work in 1.9 us): its barrier and the start of its reads are what bounds it, and
 // more codes do not fit the registers.
 // Measured against the sliding-window scan, M = 32, N = 1e6, K = 1e4: 16.4 -> 12.4 ms in a first iteration, 12.1 and
@@ -762,6 +770,7 @@ struct FilterWideIn {
     unsigned long long* state;
     const uint32_t* pairs;           // [FILTER_WIDE_PAIRS][65536], or NULL
     uint32_t* gave_up;
+    uint32_t* spent;                 // per workgroup: candidates formed in the launches before
     int K;
     int t_begin, t_end, ntiles;      // tiles of this launch; the keys hold the result of the tiles before them
     int seeded;                      // assign[] holds a center for every code
@@ -799,7 +808,7 @@ __global__ __launch_bounds__(THREADS) void assign_filter_wide_kernel(int64_t N, 
     __shared__ float4 tile[TILE_F4];
     __shared__ uint16_t thr_s[SLOTS * R];
     __shared__ uint2 queue_s[THREADS / 64][FILTER_QUEUE];
-    __shared__ uint32_t trips_s, stop_s[2];
+    __shared__ uint32_t spent_s, quit_s, stop_s[2];
     const char* tb = reinterpret_cast<const char*>(tile);
 
     const int tid = threadIdx.x, lane = tid & 63;
@@ -826,9 +835,19 @@ __global__ __launch_bounds__(THREADS) void assign_filter_wide_kernel(int64_t N, 
     for (int t = 0; t < 4; ++t) ub |= ((((uint32_t)t + ((uint32_t)(c & 7) >> 1)) & 3u) * 64u + hq) << (8 * t);
 
     const FilterScale sc = *f.scale;
-    // one of an earlier launch gave up: the first decision below stops this workgroup, too
-    if (tid == 0) trips_s = __hip_atomic_load(f.gave_up, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) ? 0x2000000u : 0u;
+    const int64_t workgroup = (int64_t)blockIdx.x + first_workgroup;
+    if (tid == 0) {
+        spent_s = f.t_begin > 0 ? f.spent[workgroup] : 0u;
+        // one gave up already, or tables that the bounds say nothing about
+        quit_s = __hip_atomic_load(f.gave_up, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) || !(sc.inv > 0.0f) ? 1u : 0u;
+    }
     if (tid < 2) stop_s[tid] = 0u;
+    __syncthreads();
+    if (quit_s) {
+        wait_vector_loads();                             // nothing may land in LDS after the workgroup has ended
+        if (tid == 0) *f.gave_up = 1u;
+        return;
+    }
 
     // keys and thresholds
 #pragma unroll 1
@@ -867,7 +886,14 @@ __global__ __launch_bounds__(THREADS) void assign_filter_wide_kernel(int64_t N, 
     }
 
     int qn = 0;
+    // candidates that the workgroup may have formed up to the tile at hand
+    float allowed = filter_budget<M>(f.t_begin, f.ntiles, f.seeded != 0) * (float)C;
     auto drain = [&]() __attribute__((always_inline)) {
+        if ((float)__builtin_amdgcn_readfirstlane(spent_s) > allowed) {
+            quit_s = 1u;
+            qn = 0;
+            return;
+        }
         const int cnt = qn < 64 ? qn : 64;
         qn -= cnt;
         __builtin_amdgcn_wave_barrier();
@@ -888,10 +914,12 @@ __global__ __launch_bounds__(THREADS) void assign_filter_wide_kernel(int64_t N, 
         }
         float sb = INFINITY;
         uint32_t kb = 0xffffffffu;
-        int trips = 0;
+        uint32_t formed = 0u;
 #pragma unroll 1
-        while (__any(mask != 0u)) {
-            ++trips;
+        while (true) {
+            const uint64_t who = __ballot(mask != 0u);
+            if (!who) break;
+            formed += (uint32_t)__builtin_popcountll(who);
             if (mask) {
                 const uint32_t bit = (uint32_t)__builtin_ctz(mask), j = 7u - (bit & 7u);
                 mask &= mask - 1u;
@@ -908,7 +936,7 @@ __global__ __launch_bounds__(THREADS) void assign_filter_wide_kernel(int64_t N, 
             uint16_t* p = thr_s + slot * R + r;
             if (bias > *p) *p = bias;
         }
-        if (lane == 0) atomicAdd(&trips_s, (uint32_t)trips);
+        if (lane == 0) atomicAdd(&spent_s, formed);
     };
 
     // 16-bit sums: even[j] bytes 0 and 2 of word j of the lane's 32 centers, odd[j] bytes 1 and 3
@@ -932,8 +960,7 @@ __global__ __launch_bounds__(THREADS) void assign_filter_wide_kernel(int64_t N, 
                 const int ph = ph2 + h;
                 wait_vector_loads();
                 // one thread decides for all; its verdict of this turn stays until everybody has passed the next barrier
-                if (tid == 0)
-                    stop_s[h] = trips_s * 64u > (uint32_t)C * (64u + (uint32_t)(t - f.t_begin)) ? 1u : 0u;
+                if (tid == 0) stop_s[h] = quit_s;
                 __syncthreads();
                 if (stop_s[h]) { stop = true; break; }
 #pragma unroll
@@ -1034,17 +1061,21 @@ __global__ __launch_bounds__(THREADS) void assign_filter_wide_kernel(int64_t N, 
             first = false;
         } else {
             ++t;
+            if (t < f.ntiles) allowed = filter_budget<M>(t, f.ntiles, f.seeded != 0) * (float)C;
         }
     }
-    if (stop) {
-        wait_vector_loads();                             // nothing may land in LDS after the workgroup has ended
+    if (!stop)
+        while (qn > 0) drain();
+    wait_vector_loads();                                 // nothing may land in LDS after the workgroup has ended
+    __syncthreads();
+    if (quit_s) {
         if (tid == 0) *f.gave_up = 1u;
         return;
     }
-    while (qn > 0) drain();
-    if (f.t_end < f.ntiles) return;
-    wait_vector_loads();
-    __syncthreads();
+    if (f.t_end < f.ntiles) {
+        if (tid == 0) f.spent[workgroup] = spent_s;
+        return;
+    }
 #pragma unroll 1
     for (int i = 0; i < R / 2; ++i) {
         const int64_t n = base + i * THREADS + tid;

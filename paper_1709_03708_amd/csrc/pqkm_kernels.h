@@ -703,30 +703,30 @@ __global__ __launch_bounds__(256) void tile_image_kernel(const uint8_t* __restri
                                                          const uint32_t* __restrict__ only_if = nullptr)
 {
     if (only_if && *only_if == 0u) return;
-    int64_t e = (int64_t)blockIdx.x * 256 + threadIdx.x;
-    if (e >= total) return;
-    int kin = (int)(e % TK);
-    int x, m;
-    if (LAYOUT == 2) {
-        const int h = (int)((e / (16 * L)) % 2);
-        kin = (int)(e % 16) + 16 * h;
-        x = (int)((e / 16) % L);
-        m = (int)((e / (32 * L)) % M);
-    } else if (LAYOUT == 1) {
-        m = (int)((e / TK) % M);
-        x = (int)((e / (TK * M)) % L);
-    } else {
-        x = (int)((e / TK) % L);
-        m = (int)((e / (TK * L)) % M);
+    for (int64_t e = (int64_t)blockIdx.x * 256 + threadIdx.x; e < total; e += (int64_t)gridDim.x * 256) {
+        int kin = (int)(e % TK);
+        int x, m;
+        if (LAYOUT == 2) {
+            const int h = (int)((e / (16 * L)) % 2);
+            kin = (int)(e % 16) + 16 * h;
+            x = (int)((e / 16) % L);
+            m = (int)((e / (32 * L)) % M);
+        } else if (LAYOUT == 1) {
+            m = (int)((e / TK) % M);
+            x = (int)((e / (TK * M)) % L);
+        } else {
+            x = (int)((e / TK) % L);
+            m = (int)((e / (TK * L)) % M);
+        }
+        int64_t tile = e / ((int64_t)TK * M * L);
+        int64_t k = tile * TK + kin;
+        float v = INFINITY;
+        if (k < K) v = tables[((size_t)m * L + x) * L + centers[k * M + m]];
+        img[e] = v;
+        // second copy in the plain order [tile][m][x][k] (LAYOUT 2 only): one 128-byte line per (tile, m, x), read by
+        // the epilogue of the half-plane scan
+        if (LAYOUT == 2 && rows) rows[((tile * M + m) * L + x) * TK + kin] = v;
     }
-    int64_t tile = e / ((int64_t)TK * M * L);
-    int64_t k = tile * TK + kin;
-    float v = INFINITY;
-    if (k < K) v = tables[((size_t)m * L + x) * L + centers[k * M + m]];
-    img[e] = v;
-    // second copy in the plain order [tile][m][x][k] (LAYOUT 2 only): one 128-byte line per (tile, m, x), read by
-    // the epilogue of the half-plane scan
-    if (LAYOUT == 2 && rows) rows[((tile * M + m) * L + x) * TK + kin] = v;
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -2108,19 +2108,41 @@ __device__ __forceinline__ void buffer_to_lds16(uint32_t lds_addr, v4i rsrc, uin
                  : "s"(lds_addr), "v"(voffset), "s"(rsrc), "s"(soffset)
                  : "memory", "m0");
 }
+// A code whose key holds this was left by a scan through lower bounds that gave up (pqkm_filter.h); it gives up for whole
+// workgroups of a multiple of GAVE_UP_STEP codes.
+constexpr unsigned long long GAVE_UP = ~1ull;
+constexpr int GAVE_UP_STEP = 2048;
+
+// does any of the workgroup's codes base .. base + C - 1 need the plain scan?  (base is a multiple of GAVE_UP_STEP)
+template <int C>
+__device__ __forceinline__ bool any_gave_up(const unsigned long long* __restrict__ keys, int64_t base, int64_t N)
+{
+    static_assert(C % GAVE_UP_STEP == 0, "whole steps");
+    bool any = false;
+#pragma unroll
+    for (int i = 0; i < C; i += GAVE_UP_STEP)
+        if (base + i < N) any = any || keys[base + i] == GAVE_UP;
+    return any;
+}
+
 __device__ __forceinline__ void wait_vector_loads() { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); }
 
-template <int R, int THREADS, int DEPTH, bool BUCKET = false>
+// LEFT: only the codes whose key says GAVE_UP are finished.
+template <int R, int THREADS, int DEPTH, bool BUCKET = false, bool LEFT = false>
 __global__ __launch_bounds__(THREADS) void assign_scan4h_kernel(int64_t N, const uint2* __restrict__ gco,
                                                             const float4* __restrict__ img,
                                                             const float4* __restrict__ rows, int ntiles, int nhalves,
                                                             int32_t* __restrict__ assign, float* __restrict__ dist,
-                                                            RankOut ro, BucketOut bo = BucketOut{})
+                                                            RankOut ro, BucketOut bo = BucketOut{},
+                                                            const unsigned long long* __restrict__ keys = nullptr)
 {
     constexpr int LPS = 2, TK = 32;
     constexpr int SLOTS = THREADS / LPS;
     constexpr int C = SLOTS * R;
     constexpr uint32_t HPLANE = 16384;      // bytes per (m, h) plane: 256 subcodes x 16 centers
+    if constexpr (LEFT) {
+        if (!any_gave_up<C>(keys, (int64_t)blockIdx.x * C, N)) return;
+    }
     static_assert(R % 2 == 0, "the epilogue gives every lane R / 2 codes");
     static_assert(C * 8 <= TILE_BYTES, "one 8-byte record per code must fit the tile buffer");
     static_assert(!BUCKET || C * 24 <= TILE_BYTES, "BUCKET: 16 more bytes per code behind the records");
@@ -2276,9 +2298,10 @@ __global__ __launch_bounds__(THREADS) void assign_scan4h_kernel(int64_t N, const
         const uint32_t h = (uint32_t)(um & 1);
         const uint2 g = gco[n];
         const uint32_t pk = g.x;
-        const uint32_t og = live ? g.y : ORIGIN_NONE;
+        const uint32_t og = live && (!LEFT || keys[n] == GAVE_UP) ? g.y : ORIGIN_NONE;
         const uint32_t hs = (uint32_t)(jj & 1);      // which half of the row the code's slot read first
         int bi = IDX_NONE;
+        float exact = sm;                            // LEFT: the selected center's own sum (a zero with its sign)
         while (__any(cand != 0u)) {                  // one trip unless the two lane positions tie exactly
             const uint32_t qe = cand ? (uint32_t)__builtin_ctz(cand) : 0u;
             // lane position qe of a slot with first half hs owns the pieces 2 hs + qe (first read) and 2 (1 - hs) + qe
@@ -2299,15 +2322,19 @@ __global__ __launch_bounds__(THREADS) void assign_scan4h_kernel(int64_t N, const
                 const int kt = tm * TK + 16 * (int)h;
                 const int kA = kt + (int)pA * 4, kB = kt + (int)pB * 4;
                 int k = IDX_NONE;
+                float vk = sm;
                 auto take = [&](const v4f& v, int k0) {
                     int kk = IDX_NONE;
-                    if (v.w == sm) kk = k0 + 3;
-                    if (v.z == sm) kk = k0 + 2;
-                    if (v.y == sm) kk = k0 + 1;
-                    if (v.x == sm) kk = k0;
+                    float vv = sm;
+                    if (v.w == sm) { kk = k0 + 3; vv = v.w; }
+                    if (v.z == sm) { kk = k0 + 2; vv = v.z; }
+                    if (v.y == sm) { kk = k0 + 1; vv = v.y; }
+                    if (v.x == sm) { kk = k0; vv = v.x; }
+                    vk = kk < k ? vv : vk;
                     k = kk < k ? kk : k;
                 };
                 take(sA, kA); take(sB, kB);
+                if (LEFT && k < bi) exact = vk;
                 bi = k < bi ? k : bi;
                 cand &= cand - 1u;
             }
@@ -2315,7 +2342,7 @@ __global__ __launch_bounds__(THREADS) void assign_scan4h_kernel(int64_t N, const
         if (og != ORIGIN_NONE) {
             const int kw = (bi == IDX_NONE) ? 0 : bi;
             assign[og] = kw;
-            if (dist) dist[og] = sm;
+            if (dist) dist[og] = LEFT ? exact : sm;
             if (ro.count) ro.rank[og] = atomicAdd(&ro.count[kw], 1u);
         }
         if (BUCKET) {
@@ -2801,17 +2828,21 @@ __global__ __launch_bounds__(256) void code8_group_clear_kernel(uint4* __restric
 // then (address ^ 32) the piece of the other half; even slots start with the lower half, odd slots with the upper;
 // a workgroup of 512 threads holds 256 R codes per tile fill instead of 128 R.
 // ---------------------------------------------------------------------------------------------
-template <int R, int THREADS, int DEPTH>
+template <int R, int THREADS, int DEPTH, bool LEFT = false>
 __global__ __launch_bounds__(THREADS) void assign_scan8q_kernel(int64_t N, const uint4* __restrict__ gc8,
                                                                 const float4* __restrict__ img, int ntiles,
                                                                 int32_t* __restrict__ assign,
-                                                                float* __restrict__ dist, RankOut ro)
+                                                                float* __restrict__ dist, RankOut ro,
+                                                                const unsigned long long* __restrict__ keys = nullptr)
 {
     constexpr int LPS = 2, TK = 16, M = 8;
     constexpr int SLOTS = THREADS / LPS;
     constexpr int C = SLOTS * R;
     constexpr int NF = TILE_F4 / THREADS;
     constexpr uint32_t PLANE = 16384;       // bytes per subspace plane: 256 subcodes x 16 centers
+    if constexpr (LEFT) {                   // as in assign_scan4h_kernel
+        if (!any_gave_up<C>(keys, (int64_t)blockIdx.x * C, N)) return;
+    }
     static_assert(TILE_F4 % THREADS == 0, "tile must divide evenly over the workgroup");
     static_assert(R * THREADS * 8 <= TILE_BYTES, "the per-lane records must fit the tile buffer");
     static_assert(R % 2 == 0, "the epilogue gives every lane R / 2 codes");
@@ -2932,9 +2963,10 @@ __global__ __launch_bounds__(THREADS) void assign_scan8q_kernel(int64_t N, const
         uint32_t cand = (uint32_t)(c0 == tm) | ((uint32_t)(c1 == tm) << 1);
         if (tm == TNONE || !live) cand = 0u;
         const uint4 g = gc8[n];
-        const uint32_t og = live ? g.z : ORIGIN_NONE;
+        const uint32_t og = live && (!LEFT || keys[n] == GAVE_UP) ? g.z : ORIGIN_NONE;
         const uint32_t hs = (uint32_t)((jj % SLOTS) & 1);
         int bi = IDX_NONE;
+        float exact = sm;                            // LEFT: the selected center's own sum (a zero with its sign)
         while (__any(cand != 0u)) {
             const uint32_t qe = cand ? (uint32_t)__builtin_ctz(cand) : 0u;
             const uint32_t pA = 2u * hs + qe, pB = 2u * (1u - hs) + qe;
@@ -2952,15 +2984,19 @@ __global__ __launch_bounds__(THREADS) void assign_scan8q_kernel(int64_t N, const
             if (cand) {
                 const int kA = tm * TK + (int)pA * 4, kB = tm * TK + (int)pB * 4;
                 int k = IDX_NONE;
+                float vk = sm;
                 auto take = [&](const v4f& v, int k0) {
                     int kk = IDX_NONE;
-                    if (v.w == sm) kk = k0 + 3;
-                    if (v.z == sm) kk = k0 + 2;
-                    if (v.y == sm) kk = k0 + 1;
-                    if (v.x == sm) kk = k0;
+                    float vv = sm;
+                    if (v.w == sm) { kk = k0 + 3; vv = v.w; }
+                    if (v.z == sm) { kk = k0 + 2; vv = v.z; }
+                    if (v.y == sm) { kk = k0 + 1; vv = v.y; }
+                    if (v.x == sm) { kk = k0; vv = v.x; }
+                    vk = kk < k ? vv : vk;
                     k = kk < k ? kk : k;
                 };
                 take(sA, kA); take(sB, kB);
+                if (LEFT && k < bi) exact = vk;
                 bi = k < bi ? k : bi;
                 cand &= cand - 1u;
             }
@@ -2968,7 +3004,7 @@ __global__ __launch_bounds__(THREADS) void assign_scan8q_kernel(int64_t N, const
         if (og != ORIGIN_NONE) {
             const int kw = (bi == IDX_NONE) ? 0 : bi;
             assign[og] = kw;
-            if (dist) dist[og] = sm;
+            if (dist) dist[og] = LEFT ? exact : sm;
             if (ro.count) ro.rank[og] = atomicAdd(&ro.count[kw], 1u);
         }
     }

@@ -207,6 +207,96 @@ def test_plain_iterations_then_lower_bounds(env, M, N, K, iters, launch, hist):
     np.testing.assert_array_equal(cent.cpu().numpy(), rc)
 
 
+@pytest.mark.parametrize("M,variant", [(M, v) for M, v in ALL if v in (60, 59, 64 if M == 4 else 63)])
+@pytest.mark.parametrize("hist_kernel", [0, 3])
+def test_some_workgroups_give_up(env, M, variant, hist_kernel):
+    """Stretches of codes that share no subcode with any center, between others that are close to one: the former tie with
+    every center and are left to the plain scan, the latter are not, and both hand over to the histograms."""
+    pq, oracle, torch = env
+    rng = np.random.default_rng(M + hist_kernel)
+    N, K = 60_013, 1100
+    centers = rng.integers(0, 128, (K, M), dtype=np.uint8)
+    codes = np.where(rng.random((N, M)) < 0.3, rng.integers(0, 128, (N, M)), centers[rng.integers(0, K, N)]).astype(np.uint8)
+    codes[20_000:45_000] = 128 + (codes[20_000:45_000] & 3)
+    tables = _metric_tables(rng, M)
+    tables[:, 128:] = 50.0
+    tables[:, :, 128:] = 50.0
+    d = dict(codes=torch.from_numpy(codes).cuda(), tables=torch.from_numpy(tables).cuda())
+    try:
+        pq.set_option("hist_kernel", hist_kernel)
+        for iters in (1, 4):
+            hist = torch.empty((K, M, 256), dtype=torch.int32, device="cuda")
+            cent = torch.from_numpy(centers).cuda()
+            with _Variant(pq, variant):
+                _, a = pq.fit(d["codes"], d["tables"], cent, iters, hist=hist)
+            rc, ra, rh, _ = oracle.fit(codes, tables, centers, iters)
+            np.testing.assert_array_equal(a.cpu().numpy(), ra)
+            np.testing.assert_array_equal(u32(hist), rh)
+            np.testing.assert_array_equal(cent.cpu().numpy(), rc)
+    finally:
+        pq.set_option("hist_kernel", 0)
+
+
+@pytest.mark.parametrize("M,N,K,late", [(32, 270_000, 1700, False), (32, 270_000, 1700, True), (16, 395_000, 2300, True), (16, 395_000, 2300, False)])
+def test_wide_scan_in_several_launches(env, M, N, K, late):
+    """More than one round of workgroups, so that the tiles come in several launches: keys and counts of candidates carry over.
+    late: the centers of the last tiles are all at the same distance from many codes, so that workgroups give up in a launch
+    after others have carried their keys over or have written results."""
+    pq, oracle, torch = env
+    rng = np.random.default_rng(M + late)
+    centers = rng.integers(0, 128, (K, M), dtype=np.uint8)
+    codes = centers[rng.integers(0, K // 2, N)]
+    fresh = rng.random((N, M), dtype=np.float32) < 0.5
+    codes[fresh] = rng.integers(0, 128, int(fresh.sum()), dtype=np.uint8)
+    tables = _metric_tables(rng, M)
+    if late:
+        tables[:, :, 200] = tables[:, :, :128].min(axis=2) * np.float32(0.5)      # near every code in every subspace
+        centers[K // 2 + 64:] = 200
+    a = torch.full((N,), -7, dtype=torch.int32, device="cuda")
+    d = torch.full((N,), float("nan"), dtype=torch.float32, device="cuda")
+    progress(f"wide scan, several launches: M={M} N={N} K={K} late={late}")
+    with _Variant(pq, 59):
+        pq.assign(torch.from_numpy(codes).cuda(), torch.from_numpy(centers).cuda(), torch.from_numpy(tables).cuda(), assign=a, dist=d)
+    ra, rd = oracle.assign(codes, centers, tables)
+    np.testing.assert_array_equal(a.cpu().numpy(), ra)
+    np.testing.assert_array_equal(d.cpu().numpy(), rd)
+
+
+@pytest.mark.parametrize("M,N,K,plain", [(4, 1_000_000, 4000, 65), (4, 3_000_000, 10_000, 65), (8, 4_300_000, 2000, 80), (16, 500_000, 4000, 50),
+                                         (32, 300_000, 10_000, 50)])
+@pytest.mark.parametrize("kind", ["constant", "hamming"])
+def test_giving_up_costs_little(env, M, N, K, plain, kind):
+    """Tables that the bounds say nothing or too little about: the time stays near that of the plain scan (it was up to ten
+    times that)."""
+    pq, _, torch = env
+    g = torch.Generator(device="cuda")
+    g.manual_seed(M)
+    codes = torch.randint(0, 256, (N, M), generator=g, device="cuda", dtype=torch.uint8)
+    centers = torch.randint(0, 256, (K, M), generator=g, device="cuda", dtype=torch.uint8)
+    tables = torch.ones(M, 256, 256, device="cuda")
+    if kind == "hamming":
+        tables[:, torch.arange(256), torch.arange(256)] = 0.0
+    ws = torch.empty(pq.workspace_bytes(N, M, K), dtype=torch.uint8, device="cuda")
+    out = {}
+    for variant in (0, plain):
+        a = torch.empty(N, dtype=torch.int32, device="cuda")
+        times = []
+        pq.set_option("scan_variant", variant)
+        try:
+            for _ in range(4):
+                s, e = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+                s.record()
+                pq.assign(codes, centers, tables, assign=a, want_dist=False, workspace=ws)
+                e.record()
+                torch.cuda.synchronize()
+                times.append(s.elapsed_time(e))
+        finally:
+            pq.set_option("scan_variant", 0)
+        out[variant] = (min(times), a)
+    assert torch.equal(out[0][1], out[plain][1])
+    assert out[0][0] < 2.2 * out[plain][0]                   # measured 1.0 to 1.7
+
+
 @pytest.mark.parametrize("M,N,K", [(4, 600_000, 2000), (32, 300_000, 5200)])
 def test_captured_fit(env, M, N, K):
     """The default scans of these sizes in a captured graph, with eager work and another workspace content between replays."""
