@@ -1499,6 +1499,7 @@ pqkm_status launch_gather(const uint8_t* codes, int64_t N, int M, const uint8_t*
         float* dn = dist ? dist + n0 : nullptr;
         NearRecord* pn = splits > 1 ? part : nullptr;
         const dim3 grid((unsigned)blocks, (unsigned)splits);
+        ++t_scan_kernels;
         if (K >= gather_rows_min_k(M, MW > 0))
             hipLaunchKernelGGL((assign_gather_kernel<MW, CN, true>), grid, dim3(256), 0, st, codes + n0 * M, cnt, M, centers, K,
                                tables, assign + n0, dn, pn, per);
@@ -1512,25 +1513,41 @@ pqkm_status launch_gather(const uint8_t* codes, int64_t N, int M, const uint8_t*
     return launched();
 }
 
+// one lane per center, or per code where there are few centers
+pqkm_status assign_untiled(const Carve& c, const uint8_t* codes, int64_t N, int M, const uint8_t* centers, int K,
+                           const float* tables, int32_t* assign, float* dist, void* ws, hipStream_t st)
+{
+    const bool words = tiled_M(M) && (((uintptr_t)codes | (uintptr_t)centers) & 3) == 0;
+    NearRecord* part = tiled_M(M) ? reinterpret_cast<NearRecord*>(static_cast<char*>(ws) + c.img_off) : nullptr;
+    const size_t room = tiled_M(M) ? c.img_bytes : 0;
+    if (words && M == 4) return launch_gather<1, 8>(codes, N, M, centers, K, tables, assign, dist, part, room, st);
+    if (words && M == 8) return launch_gather<2, 4>(codes, N, M, centers, K, tables, assign, dist, part, room, st);
+    if (words && M == 16) return launch_gather<4, 2>(codes, N, M, centers, K, tables, assign, dist, part, room, st);
+    if (words && M == 32) return launch_gather<8, 1>(codes, N, M, centers, K, tables, assign, dist, part, room, st);
+    if (lane_per_code(N, M, K)) {
+        hipLaunchKernelGGL(assign_generic_kernel, dim3((unsigned)((N + 255) / 256)), dim3(256), 0, st, codes, N, M, centers, K,
+                           tables, assign, dist);
+        return launched();
+    }
+    return launch_gather<0, 1>(codes, N, M, centers, K, tables, assign, dist, part, room, st);
+}
+
 pqkm_status assign_core(const Options& opt, const Carve& c, const uint8_t* codes, int64_t N, int M,
                         const uint8_t* centers, int K, const float* tables, int32_t* assign, float* dist, void* ws,
                         hipStream_t st, Carried& carried, BucketLink* link)
 {
     if (opt.assign_kernel == 2 && !(tiled_M(M) && ((uintptr_t)codes & 3) == 0)) return PQKM_ERR_SHAPE;
     if (!tiled_scan(opt, N, M, K, codes)) {
-        const bool words = tiled_M(M) && (((uintptr_t)codes | (uintptr_t)centers) & 3) == 0;
-        NearRecord* part = tiled_M(M) ? reinterpret_cast<NearRecord*>(static_cast<char*>(ws) + c.img_off) : nullptr;
-        const size_t room = tiled_M(M) ? c.img_bytes : 0;
-        if (words && M == 4) return launch_gather<1, 8>(codes, N, M, centers, K, tables, assign, dist, part, room, st);
-        if (words && M == 8) return launch_gather<2, 4>(codes, N, M, centers, K, tables, assign, dist, part, room, st);
-        if (words && M == 16) return launch_gather<4, 2>(codes, N, M, centers, K, tables, assign, dist, part, room, st);
-        if (words && M == 32) return launch_gather<8, 1>(codes, N, M, centers, K, tables, assign, dist, part, room, st);
-        if (lane_per_code(N, M, K)) {
-            hipLaunchKernelGGL(assign_generic_kernel, dim3((unsigned)((N + 255) / 256)), dim3(256), 0, st, codes, N, M, centers, K,
-                               tables, assign, dist);
-            return launched();
+        EventPair ev{};
+        const bool prof = (opt.profile & 1) && log_begin(g_scan_log, st, &ev);
+        t_scan_kernels = 0;
+        const pqkm_status s = assign_untiled(c, codes, N, M, centers, K, tables, assign, dist, ws, st);
+        if (prof) {
+            hipEventRecord(ev.b, st);
+            std::lock_guard<std::mutex> lk(g_mu);
+            g_scan_log.kernels += t_scan_kernels > 0 ? t_scan_kernels : 1;
         }
-        return launch_gather<0, 1>(codes, N, M, centers, K, tables, assign, dist, part, room, st);
+        return s;
     }
     float* img = reinterpret_cast<float*>(static_cast<char*>(ws) + c.img_off);
     char* wsc = static_cast<char*>(ws);

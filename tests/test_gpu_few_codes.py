@@ -110,3 +110,20 @@ def test_few_centers_take_no_block_per_code(env, M, K):
         return min(times)
 
     assert best_us() < 200.0                                                     # 30 to 70 us against 310 to 940
+
+
+@pytest.mark.parametrize("M,N,K", [(4, 10_000, 100), (4, 48, 1000), (6, 100_000, 3), (6, 5000, 2000), (4, 100_000, 100)])
+def test_scan_event_log_has_every_scan(env, M, N, K):
+    """Bit 0 of "profile" brackets the scan of any call, whichever it is."""
+    pq, _, torch = env
+    codes = torch.zeros(N, M, dtype=torch.uint8, device="cuda")
+    tables = torch.rand(M, 256, 256, device="cuda")
+    pq.profile_read()
+    pq.set_option("profile", 1)
+    try:
+        for _ in range(3):
+            pq.assign(codes, torch.zeros(K, M, dtype=torch.uint8, device="cuda"), tables)
+    finally:
+        pq.set_option("profile", 0)
+    ms, launches = pq.profile_read()
+    assert launches == 3 and ms > 0.0
