@@ -327,9 +327,9 @@ def measure(args, cfg, steps, warmup, pq, W, torch, dev, t_start=None, budget=0.
     ms_per_step = (t1 - t0) * 1e3 / steps
     evals = float(N) * K
     scan_ms = scan_ms_total / max(scan_launches, 1)
-    launches_per_step = scan_launches / steps
-    lookups_per_launch = evals * M / launches_per_step
-    achieved_gbs = lookups_per_launch * bytes_per_lookup(w) / (scan_ms * 1e-3) / 1e9
+    lookups_per_launch = evals * M * steps / max(scan_launches, 1)
+    bytes_each = bytes_per_lookup(w, pq)
+    achieved_gbs = lookups_per_launch * bytes_each / (scan_ms * 1e-3) / 1e9 if scan_ms > 0 else None
     assign_step_ms = step_ms_total / max(assign_steps, 1)
     return {
         "skipped": False, "w": w, "codes": codes, "tables": tables, "centers0": centers0,
@@ -338,14 +338,16 @@ def measure(args, cfg, steps, warmup, pq, W, torch, dev, t_start=None, budget=0.
         "scan_ms": scan_ms, "scan_ms_total": scan_ms_total, "scan_launches": scan_launches,
         "achieved_gbs": achieved_gbs, "lookups_per_launch": lookups_per_launch,
         "assign_step_ms": assign_step_ms,
-        "assign_step_frac": evals * M * bytes_per_lookup(w) / (assign_step_ms * 1e-3) / 1e9 / LDS_PEAK_GBS,
+        "bytes_per_lookup": bytes_each,
+        "assign_step_frac": evals * M * bytes_each / (assign_step_ms * 1e-3) / 1e9 / LDS_PEAK_GBS if assign_step_ms > 0 else None,
     }
 
 
-def bytes_per_lookup(w) -> float:
-    """LDS bytes per (code, center, subspace) of the scan that runs: 1 through lower bounds, which every iteration takes
-    from a few thousand centers on; at configuration 2 (K = 1000, calls of ten iterations) the first three are plain."""
-    return 1.0 if w.K >= 5000 else (3 * 4.0 + (w.iters - 3) * 1.0) / w.iters if w.iters > 3 else 4.0
+def bytes_per_lookup(w, pq) -> float:
+    """LDS bytes per (code, center, subspace), averaged over the iterations of a fit call: 1 for the scan through lower bounds,
+    4 for the others; the library says which of them an iteration runs."""
+    each = [1.0 if pq.scan_plan(w.N, w.M, w.K, it)["scan"] == 2 else 4.0 for it in range(w.iters)]
+    return sum(each) / len(each)
 
 
 def workload_label(cfg, w) -> str:
@@ -466,17 +468,6 @@ def main() -> int:
     w = r["w"]
     N, M, K = w.N, w.M, w.K
 
-    # HBM traffic of the scan kernel: from the committed rocprofv3 --pmc summary of this workload (FETCH_SIZE and
-    # WRITE_SIZE scaled by a copy of known size), not a value of this run
-    traffic, traffic_src = None, None
-    tfile = os.path.join(ROOT, "profiles", f"traffic_{w.name}.json")
-    if os.path.exists(tfile):
-        try:
-            traffic = json.load(open(tfile)).get("scan_bytes_per_launch")
-            traffic_src = f"committed profile profiles/traffic_{w.name}.json (rocprofv3 --pmc FETCH_SIZE, WRITE_SIZE)"
-        except Exception:
-            traffic = None
-
     out = {
         "metric": "code-center SDC evaluations/sec in assignment (N*K/s); seconds per PQk-means iter",
         "value": r["value"],
@@ -496,9 +487,9 @@ def main() -> int:
                    "N": N, "M": M, "K": K, "iterations_timed": args.steps, "fit_calls": r["fit_calls"],
                    "iterations_per_fit_call": w.iters, "prewarm_s": round(r["prewarm_s"], 3)},
         "roofline": {"bound": "lds", "kernel": "assign_filter / assign_scan (LDS-tiled linear scan, Eq. 5)",
-                     "bytes_per_lookup": bytes_per_lookup(w),
+                     "bytes_per_lookup": r["bytes_per_lookup"],
                      "achieved": r["achieved_gbs"], "peak": LDS_PEAK_GBS, "unit": "GB/s",
-                     "frac": r["achieved_gbs"] / LDS_PEAK_GBS, "traffic": traffic, "traffic_source": traffic_src,
+                     "frac": r["achieved_gbs"] / LDS_PEAK_GBS if r["achieved_gbs"] else None, "traffic": None,
                      "avg_kernel_ms": r["scan_ms"], "launches": r["scan_launches"],
                      "timed_in": ("a second pass of the same steps with HIP event pairs around every scan launch"
                                   if r["short"] else "the timed region (HIP event pairs around every scan launch)"),
