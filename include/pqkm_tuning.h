@@ -22,8 +22,9 @@ extern "C" {
 /*
  * pqkm_set_option: integer knobs, by name (host string).  Unknown
  * name or out-of-range value -> PQKM_ERR_SHAPE.  Names:
- *   "assign_kernel"      0 = choose automatically (default), 1 = force the generic
- *                        scan with one lane per center, which needs no tile images,
+ *   "assign_kernel"      0 = choose automatically (default), 1 = force the scans
+ *                        that need no tile images (one lane per center; one per code where neither M nor the
+ *                        alignment has a tiled scan and the centers are few),
  *                        2 = force the LDS-tiled scan (M in {4, 8, 16, 32} only)
  *   "scan_variant"       0 = default scan of the LDS-tiled assignment (for M = 4: codes regrouped for
  *                        conflict-free LDS reads when K >= 128 and N exceeds one round of 2048-code
