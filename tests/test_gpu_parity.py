@@ -759,15 +759,17 @@ def test_fit_files_codes_by_cluster_group(env, N, K, kind):
     progress(f"fused fit N={N} K={K} {kind}: bit-exact, {int((rcnt == 0).sum())} empty clusters")
 
 
-@pytest.mark.parametrize("M,N,K", [(4, 600_007, 20_000), (8, 4_300_003, 10_000), (32, 300_007, 3_000), (16, 420_001, 5_000),
-                                   (4, 70_001, 20_000), (4, 2_400_003, 20_000)])
-def test_fit_hands_ranks_to_the_sorted_histogram(env, M, N, K):
-    """pqkm_fit at sizes where the histogram sorts the code indices by cluster (more than 255 cluster groups): the
-    regrouped scans (4- and 8-byte codes) and the sliding-window scan (16, 32 bytes) count the clusters in their
-    epilogue and leave every code's rank, so the update needs no counting pass and no atomics in its scatter.  The
-    fifth case takes a scan without that hand-over through the same call, the last one the scan that loads its half
-    tiles straight into LDS, in the shape chosen for a few rounds of workgroups.  Two iterations against the oracle's loop:
-    centers, assignments, histograms, counts."""
+@pytest.mark.parametrize("M,N,K,variant", [(4, 600_007, 20_000, 0), (8, 4_300_003, 10_000, 0), (32, 300_007, 3_000, 0),
+                                           (16, 420_001, 5_000, 0), (4, 70_001, 20_000, 0), (4, 2_400_003, 20_000, 0),
+                                           (4, 600_007, 20_000, 65), (4, 600_007, 20_000, 70), (4, 2_400_003, 9_000, 85),
+                                           (8, 700_003, 6_000, 70), (8, 700_003, 6_000, 80), (16, 420_001, 5_000, 50)])
+def test_fit_hands_ranks_to_the_sorted_histogram(env, M, N, K, variant):
+    """pqkm_fit at sizes where the histogram sorts the code indices by cluster (more than 255 cluster groups): the scans
+    of regrouped codes (4 and 8 bytes), the one through lower bounds (the default here) and the plain ones named by
+    `variant`, and the sliding-window scan (16, 32 bytes) count the clusters in their epilogue and leave every code's
+    rank, so the update needs no counting pass and no atomics in its scatter.  The lower-bound scan of 16- and 32-byte
+    codes (the default at M = 16 here) and the skewed scan (N = 70001) leave none, and the update counts by itself.  Two
+    iterations against the oracle's loop: centers, assignments, histograms, counts."""
     pq, oracle, W, torch = env["pq"], env["oracle"], env["W"], env["torch"]
     w = workload(2 if M == 4 else 3, N=N, K=K, M=M, D=16 * M)
     codes = W.codes_numpy(w)
@@ -776,9 +778,13 @@ def test_fit_hands_ranks_to_the_sorted_histogram(env, M, N, K):
     hist = torch.empty((K, M, 256), dtype=torch.int32, device=env["dev"])
     counts = torch.empty((K,), dtype=torch.int32, device=env["dev"])
     d_cent = _dev(env, cent0)
-    progress(f"fit with rank hand-over M={M} N={N} K={K}: GPU")
-    _, fa = pq.fit(_dev(env, codes), _dev(env, tables), d_cent, 2, hist=hist, counts=counts)
-    _sync(env)
+    progress(f"fit with rank hand-over M={M} N={N} K={K} variant={variant}: GPU")
+    try:
+        pq.set_option("scan_variant", variant)
+        _, fa = pq.fit(_dev(env, codes), _dev(env, tables), d_cent, 2, hist=hist, counts=counts)
+        _sync(env)
+    finally:
+        pq.set_option("scan_variant", 0)
     progress(f"fit with rank hand-over M={M} N={N} K={K}: oracle")
     rc, ra, rh, rcnt = oracle.fit(codes, tables, cent0, 2)
     np.testing.assert_array_equal(fa.cpu().numpy(), ra)
