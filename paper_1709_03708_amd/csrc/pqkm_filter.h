@@ -31,26 +31,28 @@ constexpr int FILTER_TK = 64;             // centers per tile: a row of one subc
 constexpr uint32_t FILTER_PLANE = 16384;  // bytes per (tile, subspace): 256 subcodes x 64 centers
 constexpr int FILTER_QUEUE = 128;         // candidate entries a wave can hold (drained from 64 on)
 
-// Clocks of a compute unit per code: the plain scan of 64 centers, this one's, and a candidate (M table entries through the
-// L2 at 5 clocks each), from the times beside the kernels below.  first, later: candidates per code that a first and a later
-// iteration may take before their rate counts.  Codes start from a bound that the first tiles improve: where the scan gains,
-// clustered codes and Gaussian codewords take 2 to 5 candidates in the first four tiles at M = 4, 3 to 7 at M = 8, 3 to 9 at
-// M = 16 and 6 to 12 at M = 32, and then 0.1 per tile and less; with distances that are small integers it is one per tile.
+// Clocks of a compute unit per code: the plain scan of 64 centers, this one's, and a candidate, from the times beside the
+// kernels below.  A candidate is M table entries through the L2 at 5 clocks each; at M = 4 its entry's code, key and center
+// count as well (27 clocks at N = 1e6, K = 20000).  first, later, share: candidates per code that a first and a later
+// iteration may take before their rate counts, at least that share of the plain scan.  Codes start from a bound that the
+// first tiles improve: where the scan gains, clustered codes and Gaussian codewords take 2 to 5 candidates in the first
+// four tiles at M = 4, 3 to 7 at M = 8, 3 to 9 at M = 16 and 6 to 12 at M = 32, and then 0.1 per tile and less; with
+// distances that are small integers it is up to one per tile throughout.
 template <int M> struct FilterCost;
-template <> struct FilterCost<4> { static constexpr float plain = 5.5f, scan = 1.7f, candidate = 20.0f, first = 6.0f, later = 2.0f; };
-template <> struct FilterCost<8> { static constexpr float plain = 12.0f, scan = 4.5f, candidate = 40.0f, first = 10.0f, later = 6.0f; };
-template <> struct FilterCost<16> { static constexpr float plain = 39.0f, scan = 22.0f, candidate = 80.0f, first = 10.0f, later = 7.0f; };
-template <> struct FilterCost<32> { static constexpr float plain = 64.0f, scan = 37.0f, candidate = 160.0f, first = 12.0f, later = 8.0f; };
+template <> struct FilterCost<4> { static constexpr float plain = 5.5f, scan = 1.7f, candidate = 30.0f, first = 6.0f, later = 2.0f, share = 0.375f; };
+template <> struct FilterCost<8> { static constexpr float plain = 12.0f, scan = 4.5f, candidate = 40.0f, first = 10.0f, later = 6.0f, share = 0.25f; };
+template <> struct FilterCost<16> { static constexpr float plain = 39.0f, scan = 22.0f, candidate = 80.0f, first = 10.0f, later = 7.0f, share = 0.3f; };
+template <> struct FilterCost<32> { static constexpr float plain = 64.0f, scan = 37.0f, candidate = 160.0f, first = 12.0f, later = 8.0f, share = 0.3f; };
 
 // Candidates per code that are worth going on with after t of T tiles.  Giving up costs the plain scan of all T tiles; going on,
 // the T - t that are left at the rate r of candidates per tile seen so far, (scan + r candidate) (T - t).  The two are equal at
-// r = (plain T / (T - t) - scan) / candidate.  On top of that what is free: `first` or `later`, or 0.25 (M = 16, 32: 0.3) of the plain scan.
+// r = (plain T / (T - t) - scan) / candidate.  On top of that what is free.
 template <int M>
 __device__ __forceinline__ float filter_budget(int t, int T, bool later)
 {
     typedef FilterCost<M> Cost;
     const float rate = (Cost::plain * (float)T / (float)(T - t) - Cost::scan) * (1.0f / Cost::candidate);
-    return __builtin_fmaxf(later ? Cost::later : Cost::first, (M >= 16 ? 0.3f : 0.25f) * Cost::plain / Cost::candidate * (float)T) + (float)t * rate;
+    return __builtin_fmaxf(later ? Cost::later : Cost::first, Cost::share * Cost::plain / Cost::candidate * (float)T) + (float)t * rate;
 }
 
 // statistics of the tables, FILTER_PARTS blocks per subspace; st[m * FILTER_PARTS + part]
