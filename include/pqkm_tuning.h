@@ -32,7 +32,8 @@ extern "C" {
  *                        1..99 = one specific compiled scan and launch shape (for tuning sweeps;
  *                        e.g. 34 = the skewed M = 4 scan without regrouping, 70 = the regrouped one;
  *                        60 = the scan through lower bounds, M = 4 and 8, 59 the same for M = 16 and 32,
- *                        65 = the best of the plain M = 4 scans)
+ *                        65 = the best of the plain M = 4 scans, 20 = the scan on the matrix cores whatever the sizes,
+ *                        in front of the default ones)
  *   "hist_kernel"        0 = choose automatically (default; inside pqkm_fit / pqkm_fit_until with M = 4 this
  *                        includes counting from records the scan files by cluster group), 1 = force one global atomic
  *                        per code and subspace, 2 = force the LDS-privatised histogram over cluster
@@ -67,6 +68,7 @@ pqkm_status pqkm_profile_read_steps(double *total_ms, int64_t *steps);
  * pqkm_scan_plan: what the assignment step of iteration `iteration` (from 0) of pqkm_fit runs for N codes against K
  * centers under the options as they are, for aligned operands: host arithmetic, nothing is launched (without a GPU the
  * answer is that for 256 compute units).
+ * Where the scan on the matrix cores is tried first the answer is what it leaves the codes to.
  *   out   host, int64[6]: 0 the scan: 0 = one lane per center, 1 = LDS-tiled, 2 = through lower bounds;
  *         1 its number ("scan_variant"); 2 codes per stretch; 3 lanes per slot that it regroups the codes for (0 = it does
  *         not); 4 whether it takes over the regrouped copy of the iteration before; 5 where a code's first bound comes

@@ -9,6 +9,7 @@ ROOT = os.path.dirname(HERE)
 LIB = os.path.join(HERE, "libpqkm.so")
 SOURCES = [os.path.join(HERE, "csrc", "pqkm.hip")]
 DEPS = SOURCES + [os.path.join(HERE, "csrc", "pqkm_kernels.h"), os.path.join(HERE, "csrc", "pqkm_filter.h"),
+                  os.path.join(HERE, "csrc", "pqkm_dot.h"),
                   os.path.join(ROOT, "include", "pqkm.h"),
                   os.path.join(ROOT, "include", "pqkm_tuning.h")]
 MICROBENCH_LIB = os.path.join(HERE, "libpqkm_microbench.so")          # measurement code, loaded by bench.py only

@@ -12,6 +12,7 @@
 
 #include "pqkm_kernels.h"
 #include "pqkm_filter.h"
+#include "pqkm_dot.h"
 
 // Scratch of pqkm_assign_noalloc: one array per GPU, held from the moment the library is loaded on it until the
 // process ends.  In host code this name is only a handle for hipGetSymbolAddress, never an address to pass on.
@@ -93,7 +94,7 @@ inline bool tiled_M(int M) { return M == 4 || M == 8 || M == 16 || M == 32; }
 struct Carve {
     size_t img_off, img_bytes, hist_off, hist_bytes, counts_off, counts_bytes, parts_off, parts_bytes, gid_off,
         gid_bytes, gco_off, plan_off, rows_off, gc8_off, plan8_off, sidx_off, seg_off, pool_off, bseg_off, skew_off,
-        rank_off, tabt_off, rowoff_off, state_off, side_off, total;
+        rank_off, tabt_off, rowoff_off, state_off, side_off, dot_off, total;
 };
 
 // room of the M = 8 lower-bound scan for what lasts from one iteration to the next (FilterSide)
@@ -130,6 +131,24 @@ HistPlan hist_plan(int64_t N, int M, int K)
 bool owner_histogram(const HistPlan& hp, int force)
 {
     return hp.KT >= 1 && hp.groups <= 255 && force != 1 && force != 3 && (force == 2 || hp.cheap);
+}
+
+// The scan on the matrix cores, inside the images' room: fragments of the centers, halves of the points, what rounding took of
+// each, the points, statistics.
+struct DotCarve { size_t img_off, emb_off, lost_off, u_off, stat_off, check_off, total; };
+
+DotCarve dot_carve(int M, int K)
+{
+    DotCarve c{};
+    size_t off = 0;
+    c.img_off = off;    off += align256((((size_t)K + DOT_TILE - 1) / DOT_TILE) * DOT_CHUNK);     // 256 dimensions: a chunk per tile
+    c.emb_off = off;    off += (size_t)L * 256 * 2;
+    c.lost_off = off;   off += (size_t)M * L * sizeof(float);
+    c.u_off = off;      off += (size_t)L * 256 * sizeof(float);
+    c.stat_off = off;   off += align256((size_t)M * sizeof(DotStat));
+    c.check_off = off;  off += align256((size_t)M * DOT_PARTS * sizeof(DotCheck));
+    c.total = off;
+    return c;
 }
 
 Carve carve(int64_t N, int M, int K)
@@ -231,6 +250,13 @@ Carve carve(int64_t N, int M, int K)
         c.side_off = off;
         off += filter_side_bytes(M, K);
     }
+    // state of the scan on the matrix cores (DotState), under the same condition; its other arrays share the images' room
+    c.dot_off = 0;
+    if (tiled_M(M) && !(off <= PQKM_NOALLOC_SCRATCH_BYTES && off + 256 > PQKM_NOALLOC_SCRATCH_BYTES) &&
+        dot_carve(M, K).total <= c.img_bytes) {
+        c.dot_off = off;
+        off += 256;
+    }
     c.total = off;
     return c;
 }
@@ -309,12 +335,12 @@ void launch_scan(const uint8_t* codes, int64_t N, const float4* img, int ntiles,
 
 template <int R, int THREADS>
 void launch_scan4s(const uint8_t* codes, int64_t N, const float4* img, int ntiles, int32_t* assign, float* dist,
-                   hipStream_t st)
+                   hipStream_t st, const uint32_t* only_if)
 {
     constexpr int C = (THREADS / 4) * R;
     int64_t nwg = (N + C - 1) / C;
     hipLaunchKernelGGL((assign_scan4s_kernel<R, THREADS>), dim3((unsigned)nwg), dim3(THREADS), 0, st, codes, N, img,
-                       ntiles, assign, dist);
+                       ntiles, assign, dist, only_if);
 }
 
 template <int R, int THREADS, int DEPTH, bool BUCKET = false>
@@ -330,12 +356,12 @@ void launch_scan4p(const uint8_t* codes, int64_t N, const uint2* gco, const floa
 
 template <int M, int R, int THREADS, int DEPTH = 1>
 void launch_scan_skew(const uint8_t* codes, int64_t N, const float4* img, int ntiles, int32_t* assign, float* dist,
-                      hipStream_t st)
+                      hipStream_t st, const uint32_t* only_if)
 {
     constexpr int C = (THREADS / (128 / M / 4)) * R;
     int64_t nwg = (N + C - 1) / C;
     hipLaunchKernelGGL((assign_scan_skew_kernel<M, R, THREADS, DEPTH>), dim3((unsigned)nwg), dim3(THREADS), 0, st, codes,
-                       N, img, ntiles, assign, dist);
+                       N, img, ntiles, assign, dist, only_if);
 }
 
 // tile image layout a scan shape reads: 0 = [m][x][k], 1 = [x][m][k] (subspace-skewed scans), 2 = half planes
@@ -375,7 +401,7 @@ void launch_scan8p(const uint8_t* codes, int64_t N, const uint4* gc8, const floa
 
 template <int M>
 void launch_scan_M(int variant, const uint8_t* codes, int64_t N, const float4* img, const float4* rows, int ntiles,
-                   int32_t* assign, float* dist, hipStream_t st);
+                   int32_t* assign, float* dist, hipStream_t st, const uint32_t* only_if);
 
 // Sliding-window scan of the wide codes (variants 50..59): the subcode words of this launch, then the scan.
 // Shapes: 512 threads with 16 or 8 codes per lane-slot (4096 or 2048 codes per workgroup, variants 51 and 52) and
@@ -404,8 +430,7 @@ inline SwShape sw_shape(int variant, int64_t n)
 
 template <int M>
 pqkm_status launch_scan_sw(int variant, const uint8_t* codes, int64_t N, uint32_t* S, const float4* img, int ntiles16,
-                           int32_t* assign, float* dist, hipStream_t st, RankOut ro = RankOut{}, int rounds_per_launch = 0,
-                           const uint32_t* only_if = nullptr)
+                           int32_t* assign, float* dist, hipStream_t st, RankOut ro, int rounds_per_launch, const uint32_t* only_if)
 {
     const SwShape sh = sw_shape(variant, N);
     const bool wide = sh.threads == 1024;
@@ -948,68 +973,68 @@ pqkm_status regroup_codes(const uint8_t* codes, int64_t cnt, uint2* gco, GroupPl
 
 template <>
 void launch_scan_M<4>(int variant, const uint8_t* codes, int64_t N, const float4* img, const float4* rows,
-                      int ntiles, int32_t* assign, float* dist, hipStream_t st)
+                      int ntiles, int32_t* assign, float* dist, hipStream_t st, const uint32_t* only_if)
 {
     switch (variant) {
         case 1: launch_scan<4, 16, 512, false>(codes, N, img, ntiles, assign, dist, st); break;
         case 3: launch_scan<4, 16, 512, true>(codes, N, img, ntiles, assign, dist, st); break;
         case 5: launch_scan<4, 8, 1024, false>(codes, N, img, ntiles, assign, dist, st); break;
-        case 32: launch_scan4s<16, 768>(codes, N, img, ntiles, assign, dist, st); break;
-        case 34: launch_scan4s<16, 1024>(codes, N, img, ntiles, assign, dist, st); break;
-        case 36: launch_scan4s<16, 512>(codes, N, img, ntiles, assign, dist, st); break;
-        case 37: launch_scan4s<8, 1024>(codes, N, img, ntiles, assign, dist, st); break;
-        case 33: launch_scan4s<4, 512>(codes, N, img, ntiles, assign, dist, st); break;
-        case 35: launch_scan4s<8, 512>(codes, N, img, ntiles, assign, dist, st); break;
+        case 32: launch_scan4s<16, 768>(codes, N, img, ntiles, assign, dist, st, only_if); break;
+        case 34: launch_scan4s<16, 1024>(codes, N, img, ntiles, assign, dist, st, only_if); break;
+        case 36: launch_scan4s<16, 512>(codes, N, img, ntiles, assign, dist, st, only_if); break;
+        case 37: launch_scan4s<8, 1024>(codes, N, img, ntiles, assign, dist, st, only_if); break;
+        case 33: launch_scan4s<4, 512>(codes, N, img, ntiles, assign, dist, st, only_if); break;
+        case 35: launch_scan4s<8, 512>(codes, N, img, ntiles, assign, dist, st, only_if); break;
         case 41: launch_scan4p<16, 1024, 1>(codes, N, nullptr, img, rows, ntiles, assign, dist, st); break;
         case 44: launch_scan4p<24, 512, 4>(codes, N, nullptr, img, rows, ntiles, assign, dist, st); break;
         case 46: launch_scan4p<28, 512, 3>(codes, N, nullptr, img, rows, ntiles, assign, dist, st); break;
         case 48: launch_scan4p<32, 512, 3>(codes, N, nullptr, img, rows, ntiles, assign, dist, st); break;
-        default: launch_scan4s<16, 1024>(codes, N, img, ntiles, assign, dist, st); break;
+        default: launch_scan4s<16, 1024>(codes, N, img, ntiles, assign, dist, st, only_if); break;
     }
 }
 template <>
 void launch_scan_M<8>(int variant, const uint8_t* codes, int64_t N, const float4* img, const float4* rows,
-                      int ntiles, int32_t* assign, float* dist, hipStream_t st)
+                      int ntiles, int32_t* assign, float* dist, hipStream_t st, const uint32_t* only_if)
 {
     switch (variant) {
         case 1: launch_scan<8, 8, 512, false>(codes, N, img, ntiles, assign, dist, st); break;
-        case 2: launch_scan_skew<8, 6, 1024>(codes, N, img, ntiles, assign, dist, st); break;
-        case 3: launch_scan_skew<8, 12, 1024>(codes, N, img, ntiles, assign, dist, st); break;
-        case 4: launch_scan_skew<8, 16, 512>(codes, N, img, ntiles, assign, dist, st); break;
-        case 5: launch_scan_skew<8, 24, 512>(codes, N, img, ntiles, assign, dist, st); break;
-        case 6: launch_scan_skew<8, 2, 1024>(codes, N, img, ntiles, assign, dist, st); break;
-        case 7: launch_scan_skew<8, 4, 1024>(codes, N, img, ntiles, assign, dist, st); break;
+        case 2: launch_scan_skew<8, 6, 1024>(codes, N, img, ntiles, assign, dist, st, only_if); break;
+        case 3: launch_scan_skew<8, 12, 1024>(codes, N, img, ntiles, assign, dist, st, only_if); break;
+        case 4: launch_scan_skew<8, 16, 512>(codes, N, img, ntiles, assign, dist, st, only_if); break;
+        case 5: launch_scan_skew<8, 24, 512>(codes, N, img, ntiles, assign, dist, st, only_if); break;
+        case 6: launch_scan_skew<8, 2, 1024>(codes, N, img, ntiles, assign, dist, st, only_if); break;
+        case 7: launch_scan_skew<8, 4, 1024>(codes, N, img, ntiles, assign, dist, st, only_if); break;
         case 40: launch_scan8p<24, 512, 4>(codes, N, nullptr, img, ntiles, assign, dist, st); break;
         case 41: launch_scan8p<12, 1024, 2>(codes, N, nullptr, img, ntiles, assign, dist, st); break;
-        default: launch_scan_skew<8, 8, 1024>(codes, N, img, ntiles, assign, dist, st); break;
+        default: launch_scan_skew<8, 8, 1024>(codes, N, img, ntiles, assign, dist, st, only_if); break;
     }
 }
 template <>
 void launch_scan_M<16>(int variant, const uint8_t* codes, int64_t N, const float4* img, const float4* rows,
-                       int ntiles, int32_t* assign, float* dist, hipStream_t st)
+                       int ntiles, int32_t* assign, float* dist, hipStream_t st, const uint32_t* only_if)
 {
     switch (variant) {
         case 1: launch_scan<16, 4, 512, false>(codes, N, img, ntiles, assign, dist, st); break;
-        case 2: launch_scan_skew<16, 3, 1024>(codes, N, img, ntiles, assign, dist, st); break;
-        case 3: launch_scan_skew<16, 6, 1024>(codes, N, img, ntiles, assign, dist, st); break;
-        case 4: launch_scan_skew<16, 10, 512>(codes, N, img, ntiles, assign, dist, st); break;
-        case 6: launch_scan_skew<16, 2, 1024>(codes, N, img, ntiles, assign, dist, st); break;
-        case 7: launch_scan_skew<16, 1, 1024>(codes, N, img, ntiles, assign, dist, st); break;
-        default: launch_scan_skew<16, 4, 1024>(codes, N, img, ntiles, assign, dist, st); break;
+        case 2: launch_scan_skew<16, 3, 1024>(codes, N, img, ntiles, assign, dist, st, only_if); break;
+        case 3: launch_scan_skew<16, 6, 1024>(codes, N, img, ntiles, assign, dist, st, only_if); break;
+        case 4: launch_scan_skew<16, 10, 512>(codes, N, img, ntiles, assign, dist, st, only_if); break;
+        case 6: launch_scan_skew<16, 2, 1024>(codes, N, img, ntiles, assign, dist, st, only_if); break;
+        case 7: launch_scan_skew<16, 1, 1024>(codes, N, img, ntiles, assign, dist, st, only_if); break;
+        default: launch_scan_skew<16, 4, 1024>(codes, N, img, ntiles, assign, dist, st, only_if); break;
     }
 }
 template <>
 void launch_scan_M<32>(int variant, const uint8_t* codes, int64_t N, const float4* img, const float4* rows,
-                       int ntiles, int32_t* assign, float* dist, hipStream_t st)
+                       int ntiles, int32_t* assign, float* dist, hipStream_t st, const uint32_t* only_if)
 {
     switch (variant) {
         case 1: launch_scan<32, 2, 512, false>(codes, N, img, ntiles, assign, dist, st); break;
-        case 2: launch_scan_skew<32, 1, 1024>(codes, N, img, ntiles, assign, dist, st); break;
-        case 3: launch_scan_skew<32, 4, 1024>(codes, N, img, ntiles, assign, dist, st); break;
-        case 4: launch_scan_skew<32, 6, 512>(codes, N, img, ntiles, assign, dist, st); break;
-        case 5: launch_scan_skew<32, 8, 512>(codes, N, img, ntiles, assign, dist, st); break;
-        case 6: launch_scan_skew<32, 1, 512>(codes, N, img, ntiles, assign, dist, st); break;
-        default: launch_scan_skew<32, 2, 1024>(codes, N, img, ntiles, assign, dist, st); break;
+        case 2: launch_scan_skew<32, 1, 1024>(codes, N, img, ntiles, assign, dist, st, only_if); break;
+        case 3: launch_scan_skew<32, 4, 1024>(codes, N, img, ntiles, assign, dist, st, only_if); break;
+        case 4: launch_scan_skew<32, 6, 512>(codes, N, img, ntiles, assign, dist, st, only_if); break;
+        case 5: launch_scan_skew<32, 8, 512>(codes, N, img, ntiles, assign, dist, st, only_if); break;
+        case 6: launch_scan_skew<32, 1, 512>(codes, N, img, ntiles, assign, dist, st, only_if); break;
+        default: launch_scan_skew<32, 2, 1024>(codes, N, img, ntiles, assign, dist, st, only_if); break;
     }
 }
 
@@ -1147,7 +1172,7 @@ void launch_filter_wide(const uint8_t* codes, int64_t N, uint32_t* S, FilterWide
     f.n_alloc = nwg * C;
     f.spent = S + (size_t)(M / 4) * f.n_alloc;           // the room has a word per code more than the rotated words take
     f.codes = codes;
-    hipLaunchKernelGGL((code_rotate_kernel<M>), dim3((unsigned)((f.n_alloc + 255) / 256)), dim3(256), 0, st, codes, N, S, f.n_alloc);
+    hipLaunchKernelGGL((code_rotate_kernel<M>), dim3((unsigned)((f.n_alloc + 255) / 256)), dim3(256), 0, st, codes, N, S, f.n_alloc, f.only_if);
     // tiles per launch: all of them while there is one round of workgroups
     const int step = nwg <= ncu ? f.ntiles : (4 << 20) / (M * (int)FILTER_PLANE);
     for (int t0 = 0; t0 < f.ntiles; t0 += step)
@@ -1167,11 +1192,63 @@ struct Carried {
     int lanes = 0;            // a regrouped copy of ALL codes, placed for slots of this many lanes (0: there is none)
     bool stats = false;       // the lower-bound scan's statistics of the tables
     bool keys = false;        // its keys by position in that copy, and the copy of the centers that they belong to
+    bool dot = false;         // the points of the scan on the matrix cores, or that it is not for these tables
 };
+
+// Is the scan on the matrix cores tried first?  It takes about 6e12 center-code pairs per second at 128 dimensions (half of that
+// at 256) whatever M is, behind 25 to 35 us for the points, once per call, and the fragments of the centers; tables it is not for
+// cost 10 to 25 us.  Plain scans / this, us, 128 dimensions: M = 8: 87 / 97 at N = 3e5, K = 300; 148 / 77 at 1e5, 1000; 569 / 318 at
+// 1e6, 1000; M = 16: 101 / 36 at 3e4, 300; 47 / 47 at 1e4, 1000; M = 32: 83 / 47 at 1e4, 1000; 227 / 38 at 3e4, 300.  The sizes at
+// which M = 8 regroups its codes for the lower-bound scan are left to that (up to 8.7e12 pairs per second), and all of M = 4 to
+// its scans (64 / 88 at 1e5, 700).  256 dimensions, M = 8: 145 / 120 at 1e5, 1000; 563 / 588 at 1e6, 1000, so only up to 400000 codes.
+inline bool dot_scan_wanted(int M, const Options& opt, int64_t N, int K, const uint8_t* centers, const Carve& c)
+{
+    if (c.dot_off == 0 || ((uintptr_t)centers & 3) != 0 || (int64_t)K > ((int64_t)1 << 22)) return false;
+    if (opt.scan_variant == 20) return true;             // forced
+    const double pairs = (double)N * K;
+    return opt.scan_variant == 0 && ((M == 8 && pairs >= 9e7 && K >= 500) || (M == 16 && pairs >= 9e6 && N >= 25000) || (M == 32 && pairs >= 9e6));
+}
+
+template <int M>
+void launch_dot(const uint8_t* codes, int64_t N, const uint8_t* centers, int K, const float* tables, int32_t* assign, float* dist,
+                const Carve& c, char* ws, const Carried& carried, const Options& opt, hipStream_t st)
+{
+    const DotCarve d = dot_carve(M, K);
+    char* room = ws + c.img_off;
+    DotState* state = reinterpret_cast<DotState*>(ws + c.dot_off);
+    DotStat* stat = reinterpret_cast<DotStat*>(room + d.stat_off);
+    DotCheck* check = reinterpret_cast<DotCheck*>(room + d.check_off);
+    _Float16* emb = reinterpret_cast<_Float16*>(room + d.emb_off);
+    float* lost = reinterpret_cast<float*>(room + d.lost_off);
+    float* points = reinterpret_cast<float*>(room + d.u_off);
+    if (!carried.dot) {
+        hipLaunchKernelGGL((dot_embed_kernel<M>), dim3(M), dim3(256), 0, st, tables, points, stat);
+        hipLaunchKernelGGL((dot_check_kernel<M>), dim3(M * DOT_PARTS), dim3(256), 0, st, tables, points, stat, check, emb, lost, state);
+    }
+    hipLaunchKernelGGL((dot_centers_kernel<M>), dim3((unsigned)((K + DOT_TILE - 1) / DOT_TILE)), dim3(256), 0, st, centers, K, stat,
+                       check, emb, lost, state, room + d.img_off, carried.iteration, !carried.dot, M == 8 && N > 400000 ? 128 : 256);
+    EventPair ev{};
+    const bool prof = (opt.profile & 1) && log_begin(g_scan_log, st, &ev);
+    const DotIn in{codes, centers, tables, stat, emb, lost, room + d.img_off, state, N, K, carried.iteration};
+    const int64_t ncu = cu_count();
+    // one or two columns of codes per wave, by the time of the rounds: about 20 tiles' worth for what a round costs beside its tiles
+    auto cost = [&](int64_t ct) { return (double)(((N + 256 * ct - 1) / (256 * ct) + ncu - 1) / ncu) * ((double)K / DOT_TILE * (double)ct + 20.0); };
+    const int ct = cost(2) <= cost(1) ? 2 : 1;
+    const int64_t blocks = (N + 256 * ct - 1) / (256 * ct);
+    const dim3 grid((unsigned)(blocks < ncu ? blocks : ncu));
+    if (ct == 2) hipLaunchKernelGGL((assign_dot_kernel<M, 2>), grid, dim3(512), 0, st, in, assign, dist);
+    else hipLaunchKernelGGL((assign_dot_kernel<M, 1>), grid, dim3(512), 0, st, in, assign, dist);
+    if (prof) {
+        hipEventRecord(ev.b, st);
+        std::lock_guard<std::mutex> lk(g_mu);
+        ++g_scan_log.kernels;
+    }
+}
 
 struct ScanPlan {
     int variant;
     bool filter, wide, grouped, sliding;
+    bool dot;                 // the scan on the matrix cores is tried first; all of the above is for what it leaves
     int lanes;                // lanes per slot that the regrouped copy is placed for (grouped)
     int64_t per_launch;       // codes per stretch
     bool reuse;               // the regrouped copy is there already
@@ -1186,26 +1263,28 @@ ScanPlan scan_plan(int M, const Options& opt, int64_t N, int K, const uint8_t* c
 {
     ScanPlan p{};
     const int iteration = had.iteration;
-    int variant = effective_variant(M, opt.scan_variant, N, K, codes, centers);
+    const int asked = opt.scan_variant == 20 ? 0 : opt.scan_variant;      // 20: the scan on the matrix cores in front of the default ones
+    int variant = effective_variant(M, asked, N, K, codes, centers);
     // No records to file for the histogram: the four-lane scan or the scan with two-lane slots whose tiles are loaded
     // straight into LDS, half a tile ahead, in the shape that the rounds favour
     // Records to file (the fused iteration at owner-path sizes): the same scan in its 4096-code shape, which files
     // them as the four-lane scan does.
     // The lower-bound scan addresses its byte tiles through one 32-bit buffer offset and reads centers as words.
     const bool filter_ok = (M == 4 || (M == 8 && K > 16 && c.side_off > 0)) && ((uintptr_t)centers & 3) == 0 && ((int64_t)K + 63) / 64 * (M * 16384) < (int64_t)0xfff00000;
-    if (M == 4 && variant == 70 && opt.scan_variant == 0)
+    if (M == 4 && variant == 70 && asked == 0)
         variant = filter_ok && K >= filter4_min_k(iteration, N) ? (files_records ? 63 : 60)
                   : files_records ? 89 : choose_scan4_large(N);
     else if (variant_filter(M, variant) && !filter_ok)
         variant = M == 4 ? 85 : 80;
-    if (M == 8 && opt.scan_variant == 0 && variant_grouped(8, variant) && filter_ok && K >= filter8_min_k(iteration)) variant = 60;
+    if (M == 8 && asked == 0 && variant_grouped(8, variant) && filter_ok && K >= filter8_min_k(iteration)) variant = 60;
     if (M == 4 && variant == 65) variant = files_records ? 89 : choose_scan4_large(N);      // the best of the plain scans
     p.variant = variant;
     p.filter = variant_filter(M, variant);
     p.grouped = variant_grouped(M, variant);
     p.sliding = variant_sliding(M, variant);
     // M = 16, 32: the lower-bound scan of every stretch in front of the sliding-window scan, which runs where it gave up
-    p.wide = p.sliding && wide_filter(M, opt.scan_variant, variant, N, K, centers, iteration);
+    p.wide = p.sliding && wide_filter(M, asked, variant, N, K, centers, iteration);
+    p.dot = dot_scan_wanted(M, opt, N, K, centers, c) && !p.grouped;
     p.lanes = !p.grouped ? 0 : variant_two_lane(M, variant) ? 2 : 4;
     int64_t per_launch = opt.launch_codes;
     // a little below the limit: with its padding a launch of exactly 2^26 codes needs one workgroup more than
@@ -1234,6 +1313,7 @@ ScanPlan scan_plan(int M, const Options& opt, int64_t N, int K, const uint8_t* c
     p.leaves.lanes = one ? p.lanes : 0;
     p.leaves.stats = p.filter;
     p.leaves.keys = p.filter && one && keys_survive;
+    p.leaves.dot = p.dot;
     return p;
 }
 
@@ -1252,6 +1332,18 @@ pqkm_status assign_tiled(const uint8_t* codes, int64_t N, const uint8_t* centers
     const bool filter = plan_of.filter, wide = plan_of.wide, grouped = plan_of.grouped, sliding = plan_of.sliding;
     const int64_t per_launch = plan_of.per_launch;
     const int layout = variant_layout(M, variant);
+    // not NULL: a word that says whether the scans below have anything to do
+    const uint32_t* left = nullptr;
+    if (plan_of.dot) {
+        launch_dot<M>(codes, N, centers, K, tables, assign, dist, c, ws, carried, opt, st);
+        if (launched() != PQKM_OK) return PQKM_ERR_DEVICE;
+        left = &reinterpret_cast<const DotState*>(ws + c.dot_off)->left;
+    }
+    // images that may not be needed are built by few blocks
+    auto blocks_of = [&](int64_t elements) {
+        const int64_t b = (elements + 255) / 256;
+        return (unsigned)(left && b > 2048 ? 2048 : b);
+    };
     // The statistics of the M = 16, 32 lower-bound scan live in the histograms' room while the assignment runs, its byte tiles
     // and pair tables in that of the images, which are only built after a scan has given up.
     FilterStat* const wstat = reinterpret_cast<FilterStat*>(ws + c.hist_off);
@@ -1279,17 +1371,17 @@ pqkm_status assign_tiled(const uint8_t* codes, int64_t N, const uint8_t* centers
         // tiles of 16 centers, plane-ordered: img[tile][m][x][16]
         ntiles = ((int64_t)K + 15) / 16;
         total = ntiles * (int64_t)16 * M * L;
-        if (!wide) hipLaunchKernelGGL((tile_image_kernel<M, 0, 16>), dim3((unsigned)((total + 255) / 256)), dim3(256), 0, st,
-                           centers, K, tables, img, total, (float*)nullptr, (const uint32_t*)nullptr);
+        if (!wide) hipLaunchKernelGGL((tile_image_kernel<M, 0, 16>), dim3(blocks_of(total)), dim3(256), 0, st,
+                           centers, K, tables, img, total, (float*)nullptr, left);
     } else if (layout == 2 && M == 4)
         hipLaunchKernelGGL((tile_image_kernel<4, 2>), dim3((unsigned)((total + 255) / 256)), dim3(256), 0, st,
                            centers, K, tables, img, total, reinterpret_cast<float*>(ws + c.rows_off));
     else if (layout == 1)
-        hipLaunchKernelGGL((tile_image_kernel<M, 1>), dim3((unsigned)((total + 255) / 256)), dim3(256), 0, st,
-                           centers, K, tables, img, total);
+        hipLaunchKernelGGL((tile_image_kernel<M, 1>), dim3(blocks_of(total)), dim3(256), 0, st,
+                           centers, K, tables, img, total, (float*)nullptr, left);
     else
-        hipLaunchKernelGGL((tile_image_kernel<M, 0>), dim3((unsigned)((total + 255) / 256)), dim3(256), 0, st,
-                           centers, K, tables, img, total);
+        hipLaunchKernelGGL((tile_image_kernel<M, 0>), dim3(blocks_of(total)), dim3(256), 0, st,
+                           centers, K, tables, img, total, (float*)nullptr, left);
     if (launched() != PQKM_OK) return PQKM_ERR_DEVICE;
     const float4* rows = reinterpret_cast<const float4*>(ws + c.rows_off);
     uint2* gco = reinterpret_cast<uint2*>(ws + c.gco_off);
@@ -1311,7 +1403,7 @@ pqkm_status assign_tiled(const uint8_t* codes, int64_t N, const uint8_t* centers
     // ranks for the sorted-path histogram: from the scans that finish their codes one per lane (the regrouped scans
     // and the sliding-window scan), unless this iteration already hands records over by cluster group
     RankOut ro{};
-    if (link && link->rank_wanted && (grouped || sliding) && !wide && !(M == 4 && link->wanted && (variant == 70 || filter) && N <= per_launch)) {
+    if (link && link->rank_wanted && (grouped || sliding) && !wide && !left && !(M == 4 && link->wanted && (variant == 70 || filter) && N <= per_launch)) {
         ro.count = reinterpret_cast<uint32_t*>(ws + c.seg_off);
         ro.rank = reinterpret_cast<uint32_t*>(ws + c.rank_off);
         unsigned zb = (unsigned)((K + 255) / 256 < 1024 ? (K + 255) / 256 : 1024);
@@ -1350,19 +1442,20 @@ pqkm_status assign_tiled(const uint8_t* codes, int64_t N, const uint8_t* centers
                     const int nt = (K + FILTER_TK - 1) / FILTER_TK;
                     uint32_t* pair_tab = reinterpret_cast<uint32_t*>(img) + (size_t)nt * M * (FILTER_PLANE / 4);
                     // a stretch before this one may have given up and built the plain images in their place
-                    if (n0 == 0) hipLaunchKernelGGL(filter_stats_kernel, dim3(M * FILTER_PARTS), dim3(1024), 0, st, tables, wstat);
+                    if (n0 == 0) hipLaunchKernelGGL(filter_stats_kernel, dim3(M * FILTER_PARTS), dim3(1024), 0, st, tables, wstat, left);
                     hipLaunchKernelGGL((filter_image_kernel<M>), dim3((unsigned)(nt * M * 4)), dim3(256), 0, st, centers, K, tables,
-                                       wstat, reinterpret_cast<uint4*>(img), (uint8_t*)nullptr, wscale, gave_up);
+                                       wstat, reinterpret_cast<uint4*>(img), (uint8_t*)nullptr, wscale, gave_up, left);
                     if (pairs) {
                         hipLaunchKernelGGL(fill_i32_kernel, dim3(256), dim3(256), 0, st, reinterpret_cast<int32_t*>(pair_tab),
-                                           (int64_t)FILTER_WIDE_PAIRS * 65536, (int32_t)-1);
+                                           (int64_t)FILTER_WIDE_PAIRS * 65536, (int32_t)-1, left);
                         hipLaunchKernelGGL((filter_pairs_kernel<M, FILTER_WIDE_PAIRS>), dim3((unsigned)((K + 255) / 256)), dim3(256),
-                                           0, st, centers, K, pair_tab);
+                                           0, st, centers, K, pair_tab, left);
                     }
                     launch_filter_wide<M>(codes + n0 * M, cnt, reinterpret_cast<uint32_t*>(ws + c.skew_off),
                                           FilterWideIn{reinterpret_cast<const uint4*>(img), nullptr, 0, nullptr, centers, tables, wscale,
                                                        reinterpret_cast<unsigned long long*>(ws + c.state_off),
-                                                       pairs ? pair_tab : nullptr, gave_up, nullptr, K, 0, nt, nt, iteration > 0 ? 1 : 0},
+                                                       pairs ? pair_tab : nullptr, gave_up, nullptr, K, 0, nt, nt, iteration > 0 ? 1 : 0,
+                                                       left},
                                           assign + n0, dist ? dist + n0 : nullptr, st);
                     // what follows ends at once unless that scan gave up
                     hipLaunchKernelGGL((tile_image_kernel<M, 0, 16>), dim3(left_blocks), dim3(256), 0, st,
@@ -1371,7 +1464,7 @@ pqkm_status assign_tiled(const uint8_t* codes, int64_t N, const uint8_t* centers
                 if (launch_scan_sw<M>(variant, codes + n0 * M, cnt, reinterpret_cast<uint32_t*>(ws + c.skew_off),
                                       reinterpret_cast<const float4*>(img), (int)ntiles, assign + n0,
                                       dist ? dist + n0 : nullptr, st, rl, wide ? 0 : opt.rounds_per_launch,
-                                      wide ? gave_up : nullptr) != PQKM_OK)
+                                      wide ? gave_up : left) != PQKM_OK)
                     return PQKM_ERR_DEVICE;
             }
         } else if (filter && M == 8) {
@@ -1431,7 +1524,7 @@ pqkm_status assign_tiled(const uint8_t* codes, int64_t N, const uint8_t* centers
                                 (int)ntiles, assign + n0, dist ? dist + n0 : nullptr, st, nullptr, nullptr, rl);
         else
             launch_scan_M<M>(variant, codes + n0 * M, cnt, reinterpret_cast<const float4*>(img), rows, (int)ntiles,
-                             assign + n0, dist ? dist + n0 : nullptr, st);
+                             assign + n0, dist ? dist + n0 : nullptr, st, left);
         if (prof) {
             hipEventRecord(ev.b, st);
             std::lock_guard<std::mutex> lk(g_mu);

@@ -59,8 +59,10 @@ __device__ __forceinline__ float filter_budget(int t, int T, bool later)
 constexpr int FILTER_PARTS = 8;
 struct FilterStat { float lo, hi, mean, absmax; };       // finite entries; lo = -inf if there is a -inf entry
 
-__global__ __launch_bounds__(1024) void filter_stats_kernel(const float* __restrict__ tables, FilterStat* __restrict__ st)
+__global__ __launch_bounds__(1024) void filter_stats_kernel(const float* __restrict__ tables, FilterStat* __restrict__ st,
+                                                            const uint32_t* __restrict__ only_if = nullptr)
 {
+    if (only_if && *only_if == 0u) return;
     __shared__ float lo_s[16], hi_s[16], sum_s[16];
     constexpr int PART = L * L / FILTER_PARTS;
     const float* part = tables + (size_t)blockIdx.x * PART;
@@ -168,9 +170,14 @@ __global__ __launch_bounds__(256) void filter_image_kernel(const uint8_t* __rest
                                                             const float* __restrict__ tables,
                                                             const FilterStat* __restrict__ st, uint4* __restrict__ img,
                                                             uint8_t* __restrict__ copy, FilterScale* __restrict__ scale,
-                                                            uint32_t* __restrict__ gave_up = nullptr)
+                                                            uint32_t* __restrict__ gave_up = nullptr,
+                                                            const uint32_t* __restrict__ only_if = nullptr)
 {
     __shared__ uint32_t sub[FILTER_TK];
+    if (only_if && *only_if == 0u) {
+        if (gave_up && blockIdx.x == 0 && threadIdx.x == 0) *gave_up = 0u;       // for what is launched behind
+        return;
+    }
     const int tile = (int)(blockIdx.x / (4 * M)), m = (int)(blockIdx.x / 4 % M), part = (int)(blockIdx.x % 4);
     const FilterScale sc = filter_scale<M>(st);
     if (blockIdx.x == 0 && threadIdx.x == 0) {
@@ -205,10 +212,11 @@ __global__ __launch_bounds__(256) void filter_image_kernel(const uint8_t* __rest
 // matter): codes of clustered data nearly always share a pair with a center close to them.
 template <int M, int PAIRS = M / 2>
 __global__ __launch_bounds__(256) void filter_pairs_kernel(const uint8_t* __restrict__ centers, int K,
-                                                           uint32_t* __restrict__ pairs)
+                                                           uint32_t* __restrict__ pairs,
+                                                           const uint32_t* __restrict__ only_if = nullptr)
 {
     const int k = blockIdx.x * 256 + threadIdx.x;
-    if (k >= K) return;
+    if (k >= K || (only_if && *only_if == 0u)) return;
 #pragma unroll
     for (int p = 0; p < PAIRS; ++p) {
         const uint32_t c = centers[(size_t)k * M + 2 * p] | ((uint32_t)centers[(size_t)k * M + 2 * p + 1] << 8);
@@ -751,10 +759,11 @@ constexpr int FILTER_WIDE_PAIRS = 3;
 // S[phase][position]: the four subcodes of a phase, byte t = subcode (t + j) mod 4 for the position's class j
 template <int M>
 __global__ __launch_bounds__(256) void code_rotate_kernel(const uint8_t* __restrict__ codes, int64_t N,
-                                                          uint32_t* __restrict__ S, int64_t n_alloc)
+                                                          uint32_t* __restrict__ S, int64_t n_alloc,
+                                                          const uint32_t* __restrict__ only_if = nullptr)
 {
     const int64_t n = (int64_t)blockIdx.x * 256 + threadIdx.x;
-    if (n >= n_alloc) return;
+    if (n >= n_alloc || (only_if && *only_if == 0u)) return;
     const uint32_t turn = 8u * (uint32_t)((n & 7) >> 1);
     const uint32_t* cw = reinterpret_cast<const uint32_t*>(codes + (n < N ? n : N - 1) * M);
 #pragma unroll
@@ -776,6 +785,7 @@ struct FilterWideIn {
     int K;
     int t_begin, t_end, ntiles;      // tiles of this launch; the keys hold the result of the tiles before them
     int seeded;                      // assign[] holds a center for every code
+    const uint32_t* only_if;         // the scan runs unless this names a word that is 0
 };
 
 template <int M>
@@ -803,6 +813,7 @@ template <int M, int R, int THREADS>
 __global__ __launch_bounds__(THREADS) void assign_filter_wide_kernel(int64_t N, FilterWideIn f, int32_t* __restrict__ assign,
                                                                   float* __restrict__ dist, int64_t first_workgroup)
 {
+    if (f.only_if && *f.only_if == 0u) return;
     constexpr int SLOTS = THREADS / 2, C = SLOTS * R, DEPTH = 3, NPH = M / 4;
     constexpr int CHUNKS = 65536 / (THREADS * 16);       // loads per phase
     constexpr uint32_t ALL = M * FILTER_Q_WIDE, DEAD = 0x8000u, HI = 0x80008000u, EVEN = 0x00ff00ffu;

@@ -954,8 +954,10 @@ template <int R, int THREADS>
 __global__ __launch_bounds__(THREADS) void assign_scan4s_kernel(const uint8_t* __restrict__ codes, int64_t N,
                                                                 const float4* __restrict__ img, int ntiles,
                                                                 int32_t* __restrict__ assign,
-                                                                float* __restrict__ dist)
+                                                                float* __restrict__ dist,
+                                                                const uint32_t* __restrict__ only_if = nullptr)
 {
+    if (only_if && *only_if == 0u) return;
     constexpr int LPS = 4, TK = 32;
     constexpr int SLOTS = THREADS / LPS;
     constexpr int C = SLOTS * R;
@@ -3029,8 +3031,10 @@ template <int M, int R, int THREADS, int DEPTH = 1>
 __global__ __launch_bounds__(THREADS) void assign_scan_skew_kernel(const uint8_t* __restrict__ codes, int64_t N,
                                                                    const float4* __restrict__ img, int ntiles,
                                                                    int32_t* __restrict__ assign,
-                                                                   float* __restrict__ dist)
+                                                                   float* __restrict__ dist,
+                                                                   const uint32_t* __restrict__ only_if = nullptr)
 {
+    if (only_if && *only_if == 0u) return;
     constexpr int TK = 128 / M, LPS = TK / 4, SL = 16 / LPS, STEPS = M + SL - 1;
     constexpr int RQ = LPS;                   // row size in 16-byte units
     constexpr int NFW = (STEPS + 1) / 2;      // registers of packed offsets per code
@@ -4416,8 +4420,10 @@ __global__ __launch_bounds__(1024) void iter_stats_final_kernel(const StatPartia
     }
 }
 
-__global__ __launch_bounds__(256) void fill_i32_kernel(int32_t* __restrict__ p, int64_t n, int32_t v)
+__global__ __launch_bounds__(256) void fill_i32_kernel(int32_t* __restrict__ p, int64_t n, int32_t v,
+                                                       const uint32_t* __restrict__ only_if = nullptr)
 {
+    if (only_if && *only_if == 0u) return;
     int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
     int64_t stride = (int64_t)gridDim.x * 256;
     for (; i < n; i += stride) p[i] = v;
