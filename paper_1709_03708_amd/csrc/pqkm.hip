@@ -127,6 +127,15 @@ HistPlan hist_plan(int64_t N, int M, int K)
     return p;
 }
 
+// Where the owner path is possible but the sorted one faster (nothing forced, no records from the scan, not by subspace): every
+// cluster group streams a byte per code, and tight clusters meet on few counters.  Whole update, owner / sorted, us, codes of a
+// mixture: M = 8: 113 / 100 at N = 1e6, K = 2000, 178 / 117 at 1e6, 4000, 357 / 180 at 3e6, 2000; M = 16: 179 / 149 at 1e6, 2000,
+// 304 / 254 at 3e6, 1000; but M = 8: 153 / 350 at 3e6, 300.  Clusters at random: 130 / 130, 170 / 169, 211 / 216, 207 / 209, 242 / 280.
+inline bool sorted_histogram_pays(const HistPlan& hp, int64_t N)
+{
+    return hp.groups > 100 && (double)hp.groups * (double)N > 2.2e8 && N <= (int64_t)0xffffffff;
+}
+
 // does the histogram take the LDS-privatised owner path for this problem (and the call's options)?
 bool owner_histogram(const HistPlan& hp, int force)
 {
@@ -1308,7 +1317,9 @@ ScanPlan scan_plan(int M, const Options& opt, int64_t N, int K, const uint8_t* c
     if (p.filter) p.seeded = iteration == 0 ? (K >= FILTER_PAIRS_MIN_K ? 3 : 0) : had.keys && p.reuse ? 2 : 1;
     // the keys stay unless the update uses their room (that of the sorted path)
     const bool keys_survive = c.state_off != c.sidx_off || (owner_histogram(hist_plan(N, M, K), opt.hist_kernel) &&
-                                                            (opt.hist_kernel != 0 || subspace_hist(N, M, K, c).G == 0));
+                                                            (opt.hist_kernel != 0 ||
+                                                             (subspace_hist(N, M, K, c).G == 0 &&
+                                                              (files_records || !sorted_histogram_pays(hist_plan(N, M, K), N)))));
     p.leaves.iteration = iteration + 1;
     p.leaves.lanes = one ? p.lanes : 0;
     p.leaves.stats = p.filter;
@@ -1411,7 +1422,7 @@ pqkm_status assign_tiled(const uint8_t* codes, int64_t N, const uint8_t* centers
         link->ranked = true;
     }
     // images that are built only for codes that a lower-bound scan left
-    const unsigned left_blocks = (unsigned)((total + 255) / 256 < 8192 ? (total + 255) / 256 : 8192);
+    const unsigned left_blocks = (unsigned)((total + 255) / 256 < 1024 ? (total + 255) / 256 : 1024);
     for (int64_t n0 = 0; n0 < N; n0 += per_launch) {
         int64_t cnt = N - n0 < per_launch ? N - n0 : per_launch;
         const RankOut rl{ro.count, ro.count ? ro.rank + n0 : nullptr};
@@ -1734,11 +1745,12 @@ pqkm_status update_impl(const Options& opt, const Carve& c, const uint8_t* codes
     // group is cheap; otherwise one global atomic per code and subspace into a zeroed histogram.
     const HistPlan hp = hist_plan(N, M, K);
     const int force = opt.hist_kernel;
-    const bool owner = owner_histogram(hp, force);
+    const bool possible = owner_histogram(hp, force);
     int S = 1;
     size_t part_stride = 0;
     uint32_t* parts = hist;
-    const bool linked = owner && link && link->produced && link->KT == hp.KT && link->ngroups == (int)hp.groups;
+    const bool linked = possible && link && link->produced && link->KT == hp.KT && link->ngroups == (int)hp.groups;
+    const bool owner = possible && (linked || force != 0 || subspace_hist(N, M, K, c).G > 0 || !sorted_histogram_pays(hp, N));
     if (linked && M == 4 && hp.KT <= VOTE_REC_KT && link->nwg <= VOTE_REC_SEGS) {
         // the scan of this iteration filed (code, center) records by cluster group, and a vote workgroup can take
         // one group (and one subspace): it counts its histograms itself -- no histogram pass at all
@@ -1788,11 +1800,15 @@ pqkm_status update_impl(const Options& opt, const Carve& c, const uint8_t* codes
         else
             hipLaunchKernelGGL((histogram_owner_kernel<HIST_LDS_WORDS>), dim3((unsigned)(hp.groups * S)), dim3(1024),
                                0, st, codes, N, M, assign, gid, K, hp.KT, S, parts, part_stride);
-    } else if (force != 1 && N <= (int64_t)0xffffffff && N > 0 && M <= 128) {
+    } else if (force != 1 && N <= (int64_t)0xffffffff && N > 0 && M <= 64) {
         // sorted path: counting sort of the code indices by cluster, then LDS histograms per stretch of clusters
         uint32_t *start, *sidx;
         sort_by_cluster(assign, N, K, c, static_cast<char*>(ws), &start, &sidx, st, link && link->ranked);
-        int KT = (HIST_LDS_WORDS / L) / M;
+        // 64 KB of counters per workgroup, two workgroups per compute unit: half the grain of a round.  At M = 32 that is two
+        // clusters, and with few codes in each the workgroups' own cost shows (N = 1e5, K = 2000: 130 us against 126 with 128 KB; N =
+        // 1e6, K = 1000: 215 against 230)
+        const int hist_words = M < 32 || N >= (int64_t)200 * K ? SEG_HIST_WORDS : HIST_LDS_WORDS;
+        int KT = (hist_words / L) / M;
         if (KT > 128) KT = 128;
         // groups of more than twice the average of codes are shared by several workgroups
         const int64_t ng = ((int64_t)K + KT - 1) / KT;
@@ -1805,8 +1821,12 @@ pqkm_status update_impl(const Options& opt, const Carve& c, const uint8_t* codes
         uint32_t* listed = reinterpret_cast<uint32_t*>(static_cast<char*>(ws) + c.seg_off + 2 * seg_stride) + K;
         if (further > 0)
             hipLaunchKernelGGL(seg_zero_kernel, dim3((unsigned)ng), dim3(256), 0, st, start, M, K, KT, most, hist, listed, items);
-        hipLaunchKernelGGL(seg_hist_kernel, dim3((unsigned)(ng + further)), dim3(1024), 0, st, codes, M, start, sidx, K, KT,
-                           further > 0 ? most : 0xffffffffu, (int)ng, listed, items, hist);
+        if (hist_words == SEG_HIST_WORDS)
+            hipLaunchKernelGGL((seg_hist_kernel<SEG_HIST_WORDS>), dim3((unsigned)(ng + further)), dim3(1024), 0, st, codes, M, start, sidx, K, KT,
+                               further > 0 ? most : 0xffffffffu, (int)ng, listed, items, hist);
+        else
+            hipLaunchKernelGGL((seg_hist_kernel<HIST_LDS_WORDS>), dim3((unsigned)(ng + further)), dim3(1024), 0, st, codes, M, start, sidx, K, KT,
+                               further > 0 ? most : 0xffffffffu, (int)ng, listed, items, hist);
     } else {
         zero_hist();
         const int64_t per = (int64_t)1 << 30;

@@ -3631,7 +3631,32 @@ __global__ __launch_bounds__(256) void seg_place_kernel(const int32_t* __restric
 // `most` codes is shared by several workgroups, which add their counters to the result that seg_zero_kernel cleared; any other
 // group has one, which stores them.  The first workgroups of the grid take the first share of every group, the others what
 // seg_zero_kernel lists (a grid of groups x shares would be nearly all empty workgroups of 128 KB of LDS: 60 to 80 us at
-// K = 30000).  Measured, 2e6 codes of a mixture, M = 8, K = 5000: 450 us -> 114 us.
+// K = 30000).  Bound by the LDS atomics and by the rounds of workgroups: 64 KB of counters each, two workgroups per compute unit.
+// Measured, 2e6 codes of a mixture, M = 8, K = 5000: 98 us with 128 KB and the subspaces in the same order in all lanes, now 52 us.
+// The counters of a code whose words are read one by one (M a multiple of 4), starting with another subspace in each lane: lanes of
+// one cluster often hold the same subcode, and 64 of them adding to one LDS word are served one after the other.  Lane l takes the
+// words from (l / 4) mod (M / 4) on and the bytes of a word from l mod 4 on, so that at most 64 / M meet.  (The owner path, whose
+// lanes hold codes of a few clusters in any order, gains nothing from it.)
+struct HistTurn {
+    uint32_t off[4];          // of the byte that comes b-th
+    uint32_t bits;
+    int words, first;
+    __device__ __forceinline__ HistTurn(int M, int lane) : bits(8u * (uint32_t)(lane & 3)), words(M / 4), first((lane >> 2) % (M / 4))
+    {
+#pragma unroll
+        for (int b = 0; b < 4; ++b) off[b] = (uint32_t)((b + lane) & 3) * L;
+    }
+    __device__ __forceinline__ int word(int w) const { return w + first < words ? w + first : w + first - words; }
+    __device__ __forceinline__ void count(uint32_t* h, int ww, uint32_t v) const
+    {
+        const uint32_t r = __builtin_amdgcn_alignbit(v, v, bits);
+        uint32_t* hw = h + 4 * ww * L;
+        atomicAdd(&hw[off[0] + (r & 255u)], 1u);
+        atomicAdd(&hw[off[1] + ((r >> 8) & 255u)], 1u);
+        atomicAdd(&hw[off[2] + ((r >> 16) & 255u)], 1u);
+        atomicAdd(&hw[off[3] + (r >> 24)], 1u);
+    }
+};
 __device__ __forceinline__ uint32_t seg_shares(uint32_t codes, uint32_t most)
 {
     return codes <= most ? 1u : (codes - 1) / most + 1u;
@@ -3655,13 +3680,14 @@ __global__ __launch_bounds__(256) void seg_zero_kernel(const uint32_t* __restric
     for (int i = threadIdx.x; i < nk * M * L; i += 256) out[i] = 0u;
 }
 
+template <int LDS_WORDS>
 __global__ __launch_bounds__(1024) void seg_hist_kernel(const uint8_t* __restrict__ codes, int M,
                                                         const uint32_t* __restrict__ start,
                                                         const uint32_t* __restrict__ sidx, int K, int KT, uint32_t most,
                                                         int groups, const uint32_t* __restrict__ count,
                                                         const uint2* __restrict__ items, uint32_t* __restrict__ hist)
 {
-    __shared__ uint32_t lh[32768];
+    __shared__ uint32_t lh[LDS_WORDS];
     __shared__ uint32_t st[130];
     const int tid = threadIdx.x;
     uint32_t group = blockIdx.x, part = 0u;
@@ -3683,33 +3709,49 @@ __global__ __launch_bounds__(1024) void seg_hist_kernel(const uint8_t* __restric
     const uint32_t p0 = first + part * share;
     const uint32_t p1 = last - p0 < share ? last : p0 + share;
     const bool wordwise = (M & 3) == 0 && ((uintptr_t)codes & 3) == 0;
-    constexpr int PER = 4;                        // positions per thread whose loads travel together
-    for (uint64_t pb = (uint64_t)p0 + tid; pb < p1; pb += 1024 * PER) {
-        uint32_t n[PER];
+    // the cluster of position p: the last kk with st[kk] <= p
+    auto cluster_of = [&](uint64_t p) {
+        int kk = 0;
+        for (int step = 64; step >= 1; step >>= 1)
+            if (kk + step < nk && st[kk + step] <= p) kk += step;
+        return kk;
+    };
+    if (wordwise) {
+        const HistTurn turn(M, tid & 63);
+        constexpr int PER = 4;                    // positions per thread whose loads travel together, two words each
+        for (uint64_t pb = (uint64_t)p0 + tid; pb < p1; pb += 1024 * PER) {
+            const uint32_t* x[PER];
+            uint32_t* h[PER];
+            uint32_t n[PER];
 #pragma unroll
-        for (int i = 0; i < PER; ++i) n[i] = pb + i * 1024 < p1 ? sidx[pb + i * 1024] : 0xffffffffu;
+            for (int i = 0; i < PER; ++i) n[i] = sidx[pb + i * 1024 < p1 ? pb + i * 1024 : pb];
 #pragma unroll
-        for (int i = 0; i < PER; ++i) {
-            const uint64_t p = pb + i * 1024;
-            if (p >= p1) break;
-            // the cluster of position p: the last kk with st[kk] <= p
-            int kk = 0;
-            for (int step = 64; step >= 1; step >>= 1)
-                if (kk + step < nk && st[kk + step] <= p) kk += step;
-            const uint8_t* x = codes + (size_t)n[i] * M;
-            uint32_t* h = lh + kk * M * L;
-            if (wordwise) {
-                const uint32_t* xw = reinterpret_cast<const uint32_t*>(x);
-                for (int w = 0; w < M / 4; ++w) {
-                    const uint32_t v = xw[w];
-                    atomicAdd(&h[(4 * w + 0) * L + (v & 255u)], 1u);
-                    atomicAdd(&h[(4 * w + 1) * L + ((v >> 8) & 255u)], 1u);
-                    atomicAdd(&h[(4 * w + 2) * L + ((v >> 16) & 255u)], 1u);
-                    atomicAdd(&h[(4 * w + 3) * L + (v >> 24)], 1u);
-                }
-            } else {
-                for (int m = 0; m < M; ++m) atomicAdd(&h[m * L + x[m]], 1u);
+            for (int i = 0; i < PER; ++i) {
+                x[i] = reinterpret_cast<const uint32_t*>(codes + (size_t)n[i] * M);
+                h[i] = lh + cluster_of(pb + i * 1024 < p1 ? pb + i * 1024 : pb) * M * L;
             }
+            for (int w = 0; w < turn.words; w += 2) {
+                const bool two = w + 1 < turn.words;
+                const int wa = turn.word(w), wb = turn.word(two ? w + 1 : w);
+                uint32_t va[PER], vb[PER];
+#pragma unroll
+                for (int i = 0; i < PER; ++i) va[i] = x[i][wa];
+                if (two)
+#pragma unroll
+                    for (int i = 0; i < PER; ++i) vb[i] = x[i][wb];
+#pragma unroll
+                for (int i = 0; i < PER; ++i)
+                    if (pb + i * 1024 < p1) {
+                        turn.count(h[i], wa, va[i]);
+                        if (two) turn.count(h[i], wb, vb[i]);
+                    }
+            }
+        }
+    } else {
+        for (uint64_t p = (uint64_t)p0 + tid; p < p1; p += 1024) {
+            const uint8_t* x = codes + (size_t)sidx[p] * M;
+            uint32_t* h = lh + cluster_of(p) * M * L;
+            for (int m = 0; m < M; ++m) atomicAdd(&h[m * L + x[m]], 1u);
         }
     }
     __syncthreads();
@@ -3840,6 +3882,7 @@ __global__ __launch_bounds__(256) void naive_update_kernel(const uint8_t* __rest
 constexpr int HIST_LDS_WORDS = 32768;   // 128 KB of private histograms (large instantiation)
 constexpr int HIST_LDS_WORDS_SMALL = 4096;   // 16 KB (small instantiation: several workgroups per CU)
 constexpr int HIST_QCAP = 4096;         // queue entries (16 KB)
+constexpr int SEG_HIST_WORDS = 16384;   // 64 KB: the histogram over indices sorted by cluster
 
 // One code into the private histograms of its cluster (LDS atomics).  Kept out of line: it is called
 // from many places of the scan loop, most of them cold.
