@@ -1165,7 +1165,7 @@ inline bool wide_filter(int M, int asked, int variant, int64_t N, int K, const u
 {
     if ((M != 16 && M != 32) || !variant_sliding(M, variant)) return false;
     if (((uintptr_t)centers & 3) != 0 || ((int64_t)K + 63) / 64 * (M * 16384) >= (int64_t)0xfff00000) return false;
-    if (K <= 48) return false;                           // the byte tiles of 64 centers need the room of 16 KB M per 16
+    if (K <= 80) return false;                           // the byte tables in the histograms' room; byte tiles of 64 centers in that of 16 KB M per 16
     if (asked == 59) return true;                        // forced
     return asked == 0 && K >= wide_min_k(M, iteration);
 }
@@ -1360,6 +1360,7 @@ pqkm_status assign_tiled(const uint8_t* codes, int64_t N, const uint8_t* centers
     FilterStat* const wstat = reinterpret_cast<FilterStat*>(ws + c.hist_off);
     FilterScale* const wscale = reinterpret_cast<FilterScale*>(ws + c.hist_off + 8192);
     uint32_t* const gave_up = reinterpret_cast<uint32_t*>(ws + c.hist_off + 8448);
+    uint32_t* const wbytes = reinterpret_cast<uint32_t*>(ws + c.hist_off + 16384);
     // M = 4, 8: byte tiles in the room of the images, which are built there only for codes that the scan left; the pair tables in
     // that of the row-ordered images (M = 4) or behind the byte tiles, which take a quarter of the images' room (M = 8: at most
     // 1 MB).  What lasts until the next iteration has a room of its own: statistics, the scale, two copies of the centers (this
@@ -1431,8 +1432,9 @@ pqkm_status assign_tiled(const uint8_t* codes, int64_t N, const uint8_t* centers
             FilterStat* stat = reinterpret_cast<FilterStat*>(side);
             if (n0 == 0 && !carried.stats)
                 hipLaunchKernelGGL(filter_stats_kernel, dim3(M * FILTER_PARTS), dim3(1024), 0, st, tables, stat);
-            hipLaunchKernelGGL((filter_image_kernel<M>), dim3((unsigned)(nt64 * M * 4)), dim3(256), 0, st, centers, K, tables, stat,
-                               reinterpret_cast<uint4*>(img), this_copy, reinterpret_cast<FilterScale*>(side + 4096), fin.gave_up);
+            if constexpr (M < 16)
+                hipLaunchKernelGGL((filter_image_kernel<M>), dim3((unsigned)(nt64 * M * 4)), dim3(256), 0, st, centers, K, tables, stat,
+                                   reinterpret_cast<uint4*>(img), this_copy, reinterpret_cast<FilterScale*>(side + 4096), fin.gave_up);
             if (plan_of.seeded == 3) {
                 hipLaunchKernelGGL(fill_i32_kernel, dim3(256), dim3(256), 0, st, reinterpret_cast<int32_t*>(pairs), (int64_t)(M / 2) * 65536, (int32_t)-1);
                 hipLaunchKernelGGL((filter_pairs_kernel<M>), dim3((unsigned)((K + 255) / 256)), dim3(256), 0, st, centers, K, pairs);
@@ -1454,8 +1456,9 @@ pqkm_status assign_tiled(const uint8_t* codes, int64_t N, const uint8_t* centers
                     uint32_t* pair_tab = reinterpret_cast<uint32_t*>(img) + (size_t)nt * M * (FILTER_PLANE / 4);
                     // a stretch before this one may have given up and built the plain images in their place
                     if (n0 == 0) hipLaunchKernelGGL(filter_stats_kernel, dim3(M * FILTER_PARTS), dim3(1024), 0, st, tables, wstat, left);
-                    hipLaunchKernelGGL((filter_image_kernel<M>), dim3((unsigned)(nt * M * 4)), dim3(256), 0, st, centers, K, tables,
-                                       wstat, reinterpret_cast<uint4*>(img), (uint8_t*)nullptr, wscale, gave_up, left);
+                    hipLaunchKernelGGL((filter_bytes_kernel<M>), dim3(M * 16), dim3(256), 0, st, tables, wstat, wbytes, wscale, gave_up, left);
+                    hipLaunchKernelGGL((filter_wide_image_kernel<M>), dim3((unsigned)(nt * M * 4)), dim3(256), 0, st, centers, K,
+                                       reinterpret_cast<const uint4*>(wbytes), reinterpret_cast<uint4*>(img), left);
                     if (pairs) {
                         hipLaunchKernelGGL(fill_i32_kernel, dim3(256), dim3(256), 0, st, reinterpret_cast<int32_t*>(pair_tab),
                                            (int64_t)FILTER_WIDE_PAIRS * 65536, (int32_t)-1, left);

@@ -170,19 +170,15 @@ __global__ __launch_bounds__(256) void filter_image_kernel(const uint8_t* __rest
                                                             const float* __restrict__ tables,
                                                             const FilterStat* __restrict__ st, uint4* __restrict__ img,
                                                             uint8_t* __restrict__ copy, FilterScale* __restrict__ scale,
-                                                            uint32_t* __restrict__ gave_up = nullptr,
-                                                            const uint32_t* __restrict__ only_if = nullptr)
+                                                            uint32_t* __restrict__ gave_up)
 {
+    static_assert(M < 16, "M = 16, 32: filter_wide_image_kernel");
     __shared__ uint32_t sub[FILTER_TK];
-    if (only_if && *only_if == 0u) {
-        if (gave_up && blockIdx.x == 0 && threadIdx.x == 0) *gave_up = 0u;       // for what is launched behind
-        return;
-    }
     const int tile = (int)(blockIdx.x / (4 * M)), m = (int)(blockIdx.x / 4 % M), part = (int)(blockIdx.x % 4);
     const FilterScale sc = filter_scale<M>(st);
     if (blockIdx.x == 0 && threadIdx.x == 0) {
         *scale = sc;                                                 // for the scan
-        if (gave_up) *gave_up = 0u;
+        *gave_up = 0u;
     }
     const float inv = sc.inv, lo = filter_low(st, m);
     if (threadIdx.x < FILTER_TK) {
@@ -201,11 +197,62 @@ __global__ __launch_bounds__(256) void filter_image_kernel(const uint8_t* __rest
     }
     uint32_t w[4] = {0u, 0u, 0u, 0u};
 #pragma unroll
-    for (int i = 0; i < 16; ++i) w[i >> 2] |= filter_quantise(v[i], lo, inv, M >= 16 ? FILTER_Q_WIDE : FILTER_Q) << (8 * (i & 3));
-    if (M >= 16)          // phases of four subspaces: [tile][m / 4][x][m % 4][64 centers]
-        img[((size_t)tile * (M / 4) + m / 4) * 4096 + (size_t)x * 16 + (m % 4) * 4 + p] = make_uint4(w[0], w[1], w[2], w[3]);
-    else
-        img[((size_t)tile * M + m) * 1024 + part * 256 + threadIdx.x] = make_uint4(w[0], w[1], w[2], w[3]);
+    for (int i = 0; i < 16; ++i) w[i >> 2] |= filter_quantise(v[i], lo, inv, FILTER_Q) << (8 * (i & 3));
+    img[((size_t)tile * M + m) * 1024 + part * 256 + threadIdx.x] = make_uint4(w[0], w[1], w[2], w[3]);
+}
+
+// M = 16, 32: the tables as bytes first, [m][x][256], so that the images read a quarter of what they read of the tables (K = 10000,
+// M = 32: 1.3 GB through the L2 for images of 82 MB, 201 us; with the bytes and their rows in LDS see below).
+template <int M>
+__global__ __launch_bounds__(256) void filter_bytes_kernel(const float* __restrict__ tables, const FilterStat* __restrict__ st,
+                                                            uint32_t* __restrict__ bytes, FilterScale* __restrict__ scale,
+                                                            uint32_t* __restrict__ gave_up, const uint32_t* __restrict__ only_if)
+{
+    if (blockIdx.x == 0 && threadIdx.x == 0) *gave_up = 0u;                     // also where the scan has nothing to do
+    if (only_if && *only_if == 0u) return;
+    const FilterScale sc = filter_scale<M>(st);
+    if (blockIdx.x == 0 && threadIdx.x == 0) *scale = sc;                        // for the scan
+    const int m = (int)blockIdx.x / 16;
+    const float lo = filter_low(st, m);
+    const size_t first = (size_t)blockIdx.x * 4096;                              // 16 rows
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        const size_t at = first + i * 1024 + threadIdx.x * 4;
+        uint32_t w = 0u;
+#pragma unroll
+        for (int j = 0; j < 4; ++j) w |= filter_quantise(tables[at + j], lo, sc.inv, FILTER_Q_WIDE) << (8 * j);
+        bytes[at / 4] = w;
+    }
+}
+
+// img[tile][m / 4][x][m % 4][64 centers], the phases of four subspaces: block (tile, m, quarter of the subcodes) with its 64 rows of bytes in
+// LDS, 16 bytes per thread.  Centers past K take the cap; the scan drops them by their index.
+template <int M>
+__global__ __launch_bounds__(256) void filter_wide_image_kernel(const uint8_t* __restrict__ centers, int K,
+                                                                 const uint4* __restrict__ bytes, uint4* __restrict__ img,
+                                                                 const uint32_t* __restrict__ only_if)
+{
+    __shared__ uint4 rows[64 * 16];
+    __shared__ uint32_t sub[FILTER_TK];
+    if (only_if && *only_if == 0u) return;
+    const int tile = (int)(blockIdx.x / (4 * M)), m = (int)(blockIdx.x / 4 % M), part = (int)(blockIdx.x % 4);
+    const uint4* from = bytes + ((size_t)m * L + part * 64) * 16;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) rows[i * 256 + threadIdx.x] = from[i * 256 + threadIdx.x];
+    if (threadIdx.x < FILTER_TK) {
+        const int64_t k = (int64_t)tile * FILTER_TK + threadIdx.x;
+        sub[threadIdx.x] = k < K ? centers[k * M + m] : 256u;
+    }
+    __syncthreads();
+    const int xr = threadIdx.x >> 2, p = threadIdx.x & 3;
+    const uint8_t* row = reinterpret_cast<const uint8_t*>(rows) + xr * 256;
+    uint32_t w[4] = {0u, 0u, 0u, 0u};
+#pragma unroll
+    for (int i = 0; i < 16; ++i) {
+        const uint32_t c = sub[p * 16 + i];
+        w[i >> 2] |= (c < 256u ? (uint32_t)row[c] : (uint32_t)FILTER_Q_WIDE) << (8 * (i & 3));
+    }
+    img[((size_t)tile * (M / 4) + m / 4) * 4096 + (size_t)(part * 64 + xr) * 16 + (m % 4) * 4 + p] = make_uint4(w[0], w[1], w[2], w[3]);
 }
 
 // For every pair of neighbouring subspaces and every pair of subcodes some center that has both (which one does not
@@ -813,7 +860,6 @@ template <int M, int R, int THREADS>
 __global__ __launch_bounds__(THREADS) void assign_filter_wide_kernel(int64_t N, FilterWideIn f, int32_t* __restrict__ assign,
                                                                   float* __restrict__ dist, int64_t first_workgroup)
 {
-    if (f.only_if && *f.only_if == 0u) return;
     constexpr int SLOTS = THREADS / 2, C = SLOTS * R, DEPTH = 3, NPH = M / 4;
     constexpr int CHUNKS = 65536 / (THREADS * 16);       // loads per phase
     constexpr uint32_t ALL = M * FILTER_Q_WIDE, DEAD = 0x8000u, HI = 0x80008000u, EVEN = 0x00ff00ffu;
@@ -853,12 +899,13 @@ __global__ __launch_bounds__(THREADS) void assign_filter_wide_kernel(int64_t N, 
         spent_s = f.t_begin > 0 ? f.spent[workgroup] : 0u;
         // one gave up already, or tables that the bounds say nothing about
         quit_s = __hip_atomic_load(f.gave_up, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) || !(sc.inv > 0.0f) ? 1u : 0u;
+        if (f.only_if && *f.only_if == 0u) quit_s = 2u;      // nothing to do (asked here, beside the other loads: 0.5 us per launch)
     }
     if (tid < 2) stop_s[tid] = 0u;
     __syncthreads();
     if (quit_s) {
         wait_vector_loads();                             // nothing may land in LDS after the workgroup has ended
-        if (tid == 0) *f.gave_up = 1u;
+        if (tid == 0 && quit_s == 1u) *f.gave_up = 1u;
         return;
     }
 
