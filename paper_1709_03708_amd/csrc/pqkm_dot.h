@@ -420,7 +420,7 @@ __device__ __forceinline__ float dot_distance(const float* __restrict__ tables, 
 // power limit (32 with zeros as operands).  Two columns per wave, so that a fragment read from LDS serves two instructions;
 // reads run four steps ahead (two in flight: 1.2 times the time).  With few centers a block's own cost shows: codes, gather and
 // two barriers with the distances between, 10 to 13 us per 512 codes, so the next block's codes are loaded ahead.
-// Measured, plain or lower-bound scan -> this with all its launches, us: M = 16, N = 250007, K = 999, with distances: 355 -> 128;
+// Measured, plain or lower-bound scan -> this with all its launches, us: M = 16, N = 250007, K = 999, with distances: 355 -> 115;
 // M = 8, N = 1e6, K = 1000: 569 -> 318; M = 16, N = 3e5, K = 3000: 1282 -> 300; M = 32, N = 1e5, K = 3000: 1986 -> 158.  The kernel
 // itself at M = 8, N = 5e5, K = 5000: 560 us, 4.5e12 pairs per second, of which the matrix instructions alone take 440.
 // ---------------------------------------------------------------------------------------------

@@ -35,9 +35,16 @@ def _problem(rng, N, M, K, Ds, spread=1.0):
     return cw, np.ascontiguousarray(codes), np.ascontiguousarray(centers)
 
 
-def _check(env, codes, centers, tables, offset=0, dist=True):
+def _check(env, codes, centers, tables, offset=0, dist=True, shift=0):
+    """offset: floats by which the tables are moved off their alignment, shift: bytes likewise for codes and centers"""
     pq, oracle, torch = env
     N = codes.shape[0]
+
+    def moved(v):
+        buf = torch.zeros(v.size + shift, dtype=torch.uint8, device="cuda")
+        buf[shift:] = torch.from_numpy(v.reshape(-1)).cuda()
+        return buf[shift:].view(v.shape)
+
     buf = torch.empty(tables.size + offset, dtype=torch.float32, device="cuda")
     t = buf[offset:].view(tables.shape)
     t.copy_(torch.from_numpy(tables))
@@ -45,7 +52,7 @@ def _check(env, codes, centers, tables, offset=0, dist=True):
     d = torch.full((N,), float("nan"), dtype=torch.float32, device="cuda") if dist else None
     pq.set_option("scan_variant", FORCED)
     try:
-        pq.assign(torch.from_numpy(codes).cuda(), torch.from_numpy(centers).cuda(), t, assign=a, dist=d, want_dist=dist)
+        pq.assign(moved(codes), moved(centers), t, assign=a, dist=d, want_dist=dist)
     finally:
         pq.set_option("scan_variant", 0)
     ra, rd = oracle.assign(codes, centers, tables)
@@ -66,6 +73,16 @@ def test_sizes(env, M, N, dK, dims):
     rng = np.random.default_rng(1000 * M + N + dims)
     cw, codes, centers = _problem(rng, N, M, MIN_K[M] + dK, dims // M)
     _check(env, codes, centers, oracle.build_tables(cw), offset=N % 3, dist=N != 511)
+
+
+@pytest.mark.parametrize("M", [4, 8, 16, 32])
+@pytest.mark.parametrize("shift", [4, 8, 12, 1])
+def test_operands_off_their_alignment(env, M, shift):
+    """Codes and centers are read as words (shift 1: left to the scans that read bytes)."""
+    pq, oracle, _ = env
+    rng = np.random.default_rng(M + shift)
+    cw, codes, centers = _problem(rng, 1501, M, 133, 128 // M)
+    _check(env, codes, centers, oracle.build_tables(cw), shift=shift)
 
 
 @pytest.mark.parametrize("M", [8, 32])
