@@ -468,6 +468,7 @@ __device__ __forceinline__ void dot_scan(const DotIn& f, int32_t* __restrict__ a
     const float nc = __builtin_sqrtf(__builtin_bit_cast(float, f.state->nc2[f.iteration & 1])) * 1.0001f;
     // fp32 distances that may be formed per code: what the plain scan costs, at 5 clocks per entry
     const float free_evals = 0.7f * FilterCost<M>::plain * (float)f.K * (1.0f / 64.0f) / (5.0f * (float)M) + (dist ? 1.0f : 0.0f);
+    const float most = 2.0f * free_evals * (float)C + 1024.0f;   // in one block
     float spent = 0.0f, done_codes = 0.0f;
     int gb = 0;                                                  // buffer of the next chunk
     // the codes of a block, one block ahead: C M bytes in pieces of 1 KB, zeros past the end
@@ -637,7 +638,7 @@ __device__ __forceinline__ void dot_scan(const DotIn& f, int32_t* __restrict__ a
                  __builtin_amdgcn_mbcnt_hi((uint32_t)(who >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)who, 0u));
             if (!mine) return;
             if (at < (uint32_t)DOT_LIST) list_s[at] = (uint32_t)c | (k << 9);
-            else form(c, k);                                     // no room
+            else if ((float)at < most) form(c, k);               // no room; from `most` on the codes are left anyway
         };
         const int c0 = wave * (32 * CT);
 #pragma unroll
@@ -695,7 +696,7 @@ __device__ __forceinline__ void dot_scan(const DotIn& f, int32_t* __restrict__ a
         const uint32_t listed = misc[2], overs = misc[3];
         // far more than the plain scan of these codes would cost: the same verdict in all threads
         const float cost = (float)listed + (float)overs * (float)f.K;
-        if (overs > (uint32_t)DOT_OVER || cost > 4.0f * free_evals * (float)C) {
+        if (overs > (uint32_t)DOT_OVER || cost > most) {
             if (tid == 0) f.state->left = 1u;
             break;
         }
