@@ -56,10 +56,11 @@ def load():
         lib.pqkm_decode.argtypes = [vp, i64, i32, i32, vp, vp, vp]
         lib.pqkm_set_option.argtypes = [ctypes.c_char_p, i32]
         lib.pqkm_scan_plan.argtypes = [i64, i32, i32, i32, ctypes.POINTER(i64)]
+        lib.pqkm_dot_scan.argtypes = [i64, i32, i32, vp, ctypes.POINTER(i32)]
         lib.pqkm_profile_read.argtypes = [ctypes.POINTER(ctypes.c_double), ctypes.POINTER(i64)]
         lib.pqkm_profile_read_steps.argtypes = [ctypes.POINTER(ctypes.c_double), ctypes.POINTER(i64)]
         for n in ("pqkm_build_tables", "pqkm_assign", "pqkm_assign_noalloc", "pqkm_assign_indexed", "pqkm_check", "pqkm_update", "pqkm_fit", "pqkm_fit_until", "pqkm_set_option",
-                  "pqkm_scan_plan", "pqkm_profile_read", "pqkm_profile_read_steps", "pqkm_encode", "pqkm_decode", "pqkm_update_naive"):
+                  "pqkm_scan_plan", "pqkm_dot_scan", "pqkm_profile_read", "pqkm_profile_read_steps", "pqkm_encode", "pqkm_decode", "pqkm_update_naive"):
             getattr(lib, n).restype = ctypes.c_int
         _lib = lib
     return _lib
@@ -339,6 +340,14 @@ def scan_plan(N: int, M: int, K: int, iteration: int = 0) -> dict:
     out = (ctypes.c_int64 * 6)()
     _check(load().pqkm_scan_plan(int(N), int(M), int(K), int(iteration), out), "pqkm_scan_plan")
     return dict(zip(("scan", "variant", "per_launch", "lanes", "reuse", "seeded"), (int(v) for v in out)))
+
+
+def dot_scan(N: int, M: int, K: int, workspace=None) -> dict:
+    """Whether the scan on the matrix cores is tried first, and, with the workspace of a call for these sizes, whether that call
+    was left to the scans behind it (None: not asked, or not tried)."""
+    out = (ctypes.c_int32 * 2)()
+    _check(load().pqkm_dot_scan(int(N), int(M), int(K), workspace.data_ptr() if workspace is not None else None, out), "pqkm_dot_scan")
+    return dict(tried=bool(out[0]), left=None if out[1] < 0 else bool(out[1]))
 
 
 def profile_read():

@@ -2299,6 +2299,27 @@ pqkm_status pqkm_scan_plan(int64_t N, int32_t M, int32_t K, int32_t iteration, i
     return PQKM_OK;
 }
 
+pqkm_status pqkm_dot_scan(int64_t N, int32_t M, int32_t K, const void* workspace, int32_t out[2])
+{
+    if (!out) return PQKM_ERR_NULL;
+    if (!shape_ok(N, M, K)) return PQKM_ERR_SHAPE;
+    const Options opt = options_snapshot();
+    out[0] = 0;
+    out[1] = -1;
+    if (!tiled_scan(opt, N, M, K, nullptr)) return PQKM_OK;
+    const Carve c = carve(N, M, K);
+    const BucketLink link = bucket_request(opt, N, M, K);
+    const bool files_records = M == 4 && link.wanted && N <= GROUP_CHUNK_MAX - 16384 && c.bseg_off != c.pool_off;
+    out[0] = scan_plan(M, opt, N, K, nullptr, nullptr, files_records, c, Carried{}).dot ? 1 : 0;
+    if (!workspace || !out[0]) return PQKM_OK;
+    uint32_t left = 0;
+    if (hipDeviceSynchronize() != hipSuccess ||
+        hipMemcpy(&left, static_cast<const char*>(workspace) + c.dot_off + offsetof(DotState, left), sizeof(left), hipMemcpyDeviceToHost) != hipSuccess)
+        return PQKM_ERR_DEVICE;
+    out[1] = left ? 1 : 0;
+    return PQKM_OK;
+}
+
 pqkm_status pqkm_profile_read(double* total_ms, int64_t* launches)
 {
     return log_read(g_scan_log, total_ms, launches);

@@ -35,10 +35,11 @@ def _problem(rng, N, M, K, Ds, spread=1.0):
     return cw, np.ascontiguousarray(codes), np.ascontiguousarray(centers)
 
 
-def _check(env, codes, centers, tables, offset=0, dist=True, shift=0):
-    """offset: floats by which the tables are moved off their alignment, shift: bytes likewise for codes and centers"""
+def _check(env, codes, centers, tables, offset=0, dist=True, shift=0, left=None, variant=FORCED):
+    """offset: floats by which the tables are moved off their alignment, shift: bytes likewise for codes and centers; left: whether
+    the scan on the matrix cores, which has to be tried, hands the codes to the scans behind it"""
     pq, oracle, torch = env
-    N = codes.shape[0]
+    (N, M), K = codes.shape, centers.shape[0]
 
     def moved(v):
         buf = torch.zeros(v.size + shift, dtype=torch.uint8, device="cuda")
@@ -50,15 +51,22 @@ def _check(env, codes, centers, tables, offset=0, dist=True, shift=0):
     t.copy_(torch.from_numpy(tables))
     a = torch.full((N,), -7, dtype=torch.int32, device="cuda")
     d = torch.full((N,), float("nan"), dtype=torch.float32, device="cuda") if dist else None
-    pq.set_option("scan_variant", FORCED)
+    ws = torch.full((pq.workspace_bytes(N, M, K),), 0xA5, dtype=torch.uint8, device="cuda")
+    pq.set_option("scan_variant", variant)
     try:
-        pq.assign(moved(codes), moved(centers), t, assign=a, dist=d, want_dist=dist)
+        pq.assign(moved(codes), moved(centers), t, assign=a, dist=d, want_dist=dist, workspace=ws)
+        if left is not None:
+            assert pq.dot_scan(N, M, K, ws) == dict(tried=True, left=left)
     finally:
         pq.set_option("scan_variant", 0)
     ra, rd = oracle.assign(codes, centers, tables)
     np.testing.assert_array_equal(a.cpu().numpy(), ra)
     if dist:
         np.testing.assert_array_equal(d.cpu().numpy(), rd)
+
+
+# M = 4 keeps its own scans
+LEFT_TO_OTHERS = {4: None, 8: False, 16: False, 32: False}
 
 
 # fewest centers whose images leave room for the scan: 125, 58, 28, 14
@@ -72,7 +80,7 @@ def test_sizes(env, M, N, dK, dims):
     pq, oracle, _ = env
     rng = np.random.default_rng(1000 * M + N + dims)
     cw, codes, centers = _problem(rng, N, M, MIN_K[M] + dK, dims // M)
-    _check(env, codes, centers, oracle.build_tables(cw), offset=N % 3, dist=N != 511)
+    _check(env, codes, centers, oracle.build_tables(cw), offset=N % 3, dist=N != 511, left=LEFT_TO_OTHERS[M])
 
 
 @pytest.mark.parametrize("M", [4, 8, 16, 32])
@@ -91,7 +99,7 @@ def test_many_centers_and_blocks(env, M):
     pq, oracle, _ = env
     rng = np.random.default_rng(M)
     cw, codes, centers = _problem(rng, 300_001, M, 333, 128 // M)
-    _check(env, codes, centers, oracle.build_tables(cw), dist=False)
+    _check(env, codes, centers, oracle.build_tables(cw), dist=False, left=False)
 
 
 @pytest.mark.parametrize("M", [4, 8, 16, 32])
@@ -128,7 +136,8 @@ def test_tables(env, M, kind):
         t = t - np.float32(3.0)                    # a constant that all distances share, but not on the diagonal of any points
     elif kind == "wide":
         t = oracle.build_tables(rng.standard_normal((M, 256, 300 // M + 1)).astype(np.float32))
-    _check(env, codes, centers, t, dist=kind != "integer")
+    kept = kind in ("lattice", "huge", "tiny")
+    _check(env, codes, centers, t, dist=kind != "integer", left=None if M == 4 or kind == "hamming" else not kept)
 
 
 @pytest.mark.parametrize("M", [8, 16])
@@ -138,7 +147,7 @@ def test_near_ties_are_decided_by_the_sum_of_the_definition(env, M):
     rng = np.random.default_rng(3 * M)
     cw, codes, centers = _problem(rng, 4001, M, 700, 128 // M)
     cw = np.round(cw * 2.0).astype(np.float32) * np.float32(0.1)
-    _check(env, codes, centers, oracle.build_tables(cw))
+    _check(env, codes, centers, oracle.build_tables(cw), left=False)
     one = np.repeat(centers[:1], 64, axis=0)       # one center, 64 times
     _check(env, codes, np.ascontiguousarray(one), oracle.build_tables(cw))
 
@@ -153,9 +162,11 @@ def test_fit(env, M, N, K):
     c = torch.from_numpy(centers).cuda()
     h = torch.empty((K, M, 256), dtype=torch.int32, device="cuda")
     n = torch.empty(K, dtype=torch.int32, device="cuda")
+    ws = torch.full((pq.workspace_bytes(N, M, K),), 0xA5, dtype=torch.uint8, device="cuda")
     pq.set_option("scan_variant", FORCED)
     try:
-        _, a = pq.fit(torch.from_numpy(codes).cuda(), torch.from_numpy(t).cuda(), c, 4, hist=h, counts=n)
+        _, a = pq.fit(torch.from_numpy(codes).cuda(), torch.from_numpy(t).cuda(), c, 4, hist=h, counts=n, workspace=ws)
+        assert pq.dot_scan(N, M, K, ws) == dict(tried=True, left=False)
     finally:
         pq.set_option("scan_variant", 0)
     want = centers
@@ -166,6 +177,50 @@ def test_fit(env, M, N, K):
     np.testing.assert_array_equal(c.cpu().numpy(), want)
     np.testing.assert_array_equal(u32(h), rh)
     np.testing.assert_array_equal(u32(n), rn)
+
+
+def _alike(rng, N, M, K, same):
+    """Codewords of the last subspace that are all one point, and centers in groups of `same` that differ there only: every code is
+    as far from all of a group, though no center repeats another.  The tables are those of points all the same."""
+    cw = rng.standard_normal((M, 256, 128 // M)).astype(np.float32)
+    cw[M - 1] = cw[M - 1, :1]
+    centers = np.repeat(rng.integers(0, 256, ((K + same - 1) // same, M), dtype=np.uint8), same, axis=0)[:K]
+    centers[:, M - 1] = np.arange(K) % same
+    codes = centers[rng.integers(0, K, N)]
+    codes = np.where(rng.random((N, M)) < 0.2, rng.integers(0, 256, (N, M), dtype=np.uint8), codes)
+    return cw, np.ascontiguousarray(codes), np.ascontiguousarray(centers)
+
+
+@pytest.mark.parametrize("M,N,K,kind", [
+    (8, 30_001, 600, "wide"), (16, 30_001, 600, "wide"), (32, 30_001, 400, "wide"),      # more dimensions: left before the first scan
+    (8, 30_001, 600, "ties"), (32, 30_001, 600, "ties"),                                 # too many centers alike in every block
+    (8, 300_001, 1000, "some ties")])                                                    # 5 per code: only all blocks together are too much
+def test_fit_that_is_left(env, M, N, K, kind):
+    """The scans behind build their images over the points, and the iterations that follow start from them."""
+    pq, oracle, torch = env
+    rng = np.random.default_rng(M + N)
+    if kind == "wide":
+        cw, codes, centers = _problem(rng, N, M, K, 320 // M)
+    else:
+        cw, codes, centers = _alike(rng, N, M, K, 5 if kind == "some ties" else 200)
+    t = oracle.build_tables(cw)
+    iters = 1 if kind == "some ties" else 4
+    c = torch.from_numpy(centers).cuda()
+    h = torch.empty((K, M, 256), dtype=torch.int32, device="cuda")
+    ws = torch.full((pq.workspace_bytes(N, M, K),), 0xA5, dtype=torch.uint8, device="cuda")
+    pq.set_option("scan_variant", FORCED)
+    try:
+        _, a = pq.fit(torch.from_numpy(codes).cuda(), torch.from_numpy(t).cuda(), c, iters, hist=h, workspace=ws)
+        assert pq.dot_scan(N, M, K, ws) == dict(tried=True, left=True)
+    finally:
+        pq.set_option("scan_variant", 0)
+    want = centers
+    for _ in range(iters):
+        ra, _ = oracle.assign(codes, want, t)
+        want, rh, _ = oracle.update(codes, ra, t, want)
+    np.testing.assert_array_equal(a.cpu().numpy(), ra)
+    np.testing.assert_array_equal(c.cpu().numpy(), want)
+    np.testing.assert_array_equal(u32(h), rh)
 
 
 def test_captured(env):
@@ -196,3 +251,4 @@ def test_captured(env):
         torch.cuda.synchronize()
         np.testing.assert_array_equal(a.cpu().numpy(), ra)
         np.testing.assert_array_equal(d.cpu().numpy(), rd)
+        assert pq.dot_scan(N, M, K, ws) == dict(tried=True, left=False)
