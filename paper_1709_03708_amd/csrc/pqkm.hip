@@ -128,9 +128,11 @@ HistPlan hist_plan(int64_t N, int M, int K)
 }
 
 // Where the owner path is possible but the sorted one faster (nothing forced, no records from the scan, not by subspace): every
-// cluster group streams a byte per code, and tight clusters meet on few counters.  Whole update, owner / sorted, us, codes of a
-// mixture: M = 8: 113 / 100 at N = 1e6, K = 2000, 178 / 117 at 1e6, 4000, 357 / 180 at 3e6, 2000; M = 16: 179 / 149 at 1e6, 2000,
-// 304 / 254 at 3e6, 1000; but M = 8: 153 / 350 at 3e6, 300.  Clusters at random: 130 / 130, 170 / 169, 211 / 216, 207 / 209, 242 / 280.
+// cluster group streams a byte per code, tight clusters meet on few counters, and a heavy cluster is one workgroup's work.  Whole
+// update, owner / sorted, us.  Codes without a pattern, clusters of even size: M = 2: 150 / 157 at N = 2e6, K = 8000 (the only M at
+// which any was slower, up to 9 %); M = 4: 230 / 192 at 2e6, 5000; M = 8: 179 / 176 at 1e6, 4000, 214 / 202 at 3e6, 2000; M = 16: 241 /
+// 198 at 3e6, 1000; M = 24: 251 / 245 at 1e6, 1200; M = 48: 250 / 204 at 1e6, 500.  Uneven clusters: 640 / 165, 598 / 171, 788 / 181,
+// 1187 / 210, 2052 / 214, 1975 / 240, 3254 / 227.  Tight ones: M = 4: 355 / 164; M = 8: 415 / 159; M = 16: 1076 / 222.
 inline bool sorted_histogram_pays(const HistPlan& hp, int64_t N)
 {
     return hp.groups > 100 && (double)hp.groups * (double)N > 2.2e8 && N <= (int64_t)0xffffffff;
@@ -1824,9 +1826,9 @@ pqkm_status update_impl(const Options& opt, const Carve& c, const uint8_t* codes
         // sorted path: counting sort of the code indices by cluster, then LDS histograms per stretch of clusters
         uint32_t *start, *sidx;
         sort_by_cluster(assign, N, K, c, static_cast<char*>(ws), &start, &sidx, st, link && link->ranked);
-        // 64 KB of counters per workgroup, two workgroups per compute unit: half the grain of a round.  At M = 32 that is two
-        // clusters, and with few codes in each the workgroups' own cost shows (N = 1e5, K = 2000: 130 us against 126 with 128 KB; N =
-        // 1e6, K = 1000: 215 against 230)
+        // 64 KB of counters per workgroup, two workgroups per compute unit: half the grain of a round (128 KB: 1.04 to 1.16 times the
+        // update at M = 4, 6, 8, 16).  From M = 32 on that is one or two clusters, and with few codes in each the workgroups' own cost
+        // shows: M = 48, N = 3e5, K = 1500: 301 us against 282 with 128 KB where they are even, 277 against 307 where they are tight.
         const int hist_words = M < 32 || N >= (int64_t)200 * K ? SEG_HIST_WORDS : HIST_LDS_WORDS;
         int KT = (hist_words / L) / M;
         if (KT > 128) KT = 128;

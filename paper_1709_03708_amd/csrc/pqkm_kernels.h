@@ -9,6 +9,7 @@
 #pragma once
 #include <hip/hip_runtime.h>
 #include <stdint.h>
+#include <type_traits>
 
 namespace pqkm {
 
@@ -3633,28 +3634,53 @@ __global__ __launch_bounds__(256) void seg_place_kernel(const int32_t* __restric
 // seg_zero_kernel lists (a grid of groups x shares would be nearly all empty workgroups of 128 KB of LDS: 60 to 80 us at
 // K = 30000).  Bound by the LDS atomics and by the rounds of workgroups: 64 KB of counters each, two workgroups per compute unit.
 // Measured, 2e6 codes of a mixture, M = 8, K = 5000: 98 us with 128 KB and the subspaces in the same order in all lanes, now 52 us.
-// The counters of a code whose words are read one by one (M a multiple of 4), starting with another subspace in each lane: lanes of
-// one cluster often hold the same subcode, and 64 of them adding to one LDS word are served one after the other.  Lane l takes the
-// words from (l / 4) mod (M / 4) on and the bytes of a word from l mod 4 on, so that at most 64 / M meet.  (The owner path, whose
-// lanes hold codes of a few clusters in any order, gains nothing from it.)
+// The counters of a code that is read as words (M a multiple of 4), starting with another subspace in each lane: lanes of one
+// cluster often hold the same subcode, and 64 of them adding to one LDS word are served one after the other.  Lane l takes the
+// bytes of a word from l mod 4 on, the words of a chunk of CW from (l / 4) mod CW on and the chunks of a code from l / (4 CW) on, so
+// that 64 / M of them meet where M is a power of two.  Chunks are read whole and turned in registers: words read one by one where a
+// code has four or more cost codes of no pattern 1.05 to 1.3 times the update (they are loads per code, not bytes).  (The owner path,
+// whose lanes hold codes of a few clusters in any order, gains nothing from turning.)
+template <int CW>
 struct HistTurn {
-    uint32_t off[4];          // of the byte that comes b-th
+    typedef uint32_t Chunk __attribute__((ext_vector_type(CW), aligned(4)));
+    uint32_t off[4], woff[CW];        // of the byte that comes b-th, of the word that comes q-th
     uint32_t bits;
-    int words, first;
-    __device__ __forceinline__ HistTurn(int M, int lane) : bits(8u * (uint32_t)(lane & 3)), words(M / 4), first((lane >> 2) % (M / 4))
+    int chunks, first;
+    bool one, two;                    // turned by an odd number of words, by two or three
+    __device__ __forceinline__ HistTurn(int M, int lane)
+        : bits(8u * (uint32_t)(lane & 3)), chunks(M / (4 * CW)), first((lane / (4 * CW)) % (M / (4 * CW))), one(CW > 1 && ((lane >> 2) & 1)),
+          two(CW > 2 && ((lane >> 2) & 2))
     {
 #pragma unroll
         for (int b = 0; b < 4; ++b) off[b] = (uint32_t)((b + lane) & 3) * L;
+#pragma unroll
+        for (int q = 0; q < CW; ++q) woff[q] = (uint32_t)((q + (lane >> 2)) & (CW - 1)) * 4u * L;
     }
-    __device__ __forceinline__ int word(int w) const { return w + first < words ? w + first : w + first - words; }
-    __device__ __forceinline__ void count(uint32_t* h, int ww, uint32_t v) const
+    __device__ __forceinline__ int chunk(int c) const { return c + first < chunks ? c + first : c + first - chunks; }
+    __device__ __forceinline__ void count(uint32_t* h, int c, const Chunk& read) const
     {
-        const uint32_t r = __builtin_amdgcn_alignbit(v, v, bits);
-        uint32_t* hw = h + 4 * ww * L;
-        atomicAdd(&hw[off[0] + (r & 255u)], 1u);
-        atomicAdd(&hw[off[1] + ((r >> 8) & 255u)], 1u);
-        atomicAdd(&hw[off[2] + ((r >> 16) & 255u)], 1u);
-        atomicAdd(&hw[off[3] + (r >> 24)], 1u);
+        uint32_t v[CW];
+#pragma unroll
+        for (int q = 0; q < CW; ++q) v[q] = read[q];
+        if constexpr (CW == 4) {
+            const uint32_t v0 = v[0], v1 = v[1];
+            v[0] = two ? v[2] : v[0]; v[1] = two ? v[3] : v[1]; v[2] = two ? v0 : v[2]; v[3] = two ? v1 : v[3];
+        }
+        if constexpr (CW > 1) {
+            const uint32_t v0 = v[0];
+#pragma unroll
+            for (int q = 0; q < CW; ++q) v[q] = one ? (q + 1 < CW ? v[q + 1] : v0) : v[q];
+        }
+        uint32_t* hc = h + c * (4 * CW * L);
+#pragma unroll
+        for (int q = 0; q < CW; ++q) {
+            const uint32_t r = __builtin_amdgcn_alignbit(v[q], v[q], bits);
+            uint32_t* hw = hc + woff[q];
+            atomicAdd(&hw[off[0] + (r & 255u)], 1u);
+            atomicAdd(&hw[off[1] + ((r >> 8) & 255u)], 1u);
+            atomicAdd(&hw[off[2] + ((r >> 16) & 255u)], 1u);
+            atomicAdd(&hw[off[3] + (r >> 24)], 1u);
+        }
     }
 };
 __device__ __forceinline__ uint32_t seg_shares(uint32_t codes, uint32_t most)
@@ -3716,42 +3742,67 @@ __global__ __launch_bounds__(1024) void seg_hist_kernel(const uint8_t* __restric
             if (kk + step < nk && st[kk + step] <= p) kk += step;
         return kk;
     };
+    // four positions of the sorted indices per thread whose loads travel together
+    constexpr int PER = 4;
+    auto positions = [&](uint64_t pb, uint32_t (&n)[PER]) {
+#pragma unroll
+        for (int i = 0; i < PER; ++i) n[i] = sidx[pb + i * 1024 < p1 ? pb + i * 1024 : pb];
+    };
     if (wordwise) {
-        const HistTurn turn(M, tid & 63);
-        constexpr int PER = 4;                    // positions per thread whose loads travel together, two words each
-        for (uint64_t pb = (uint64_t)p0 + tid; pb < p1; pb += 1024 * PER) {
-            const uint32_t* x[PER];
-            uint32_t* h[PER];
-            uint32_t n[PER];
+        // chunks of CW words, S of them of C codes in flight
+        auto count_chunks = [&](auto chunk_words, auto codes_at_once) {
+            constexpr int CW = decltype(chunk_words)::value, C = decltype(codes_at_once)::value, S = PER / C;
+            typedef typename HistTurn<CW>::Chunk Chunk;
+            const HistTurn<CW> turn(M, tid & 63);
+            for (uint64_t pb = (uint64_t)p0 + tid; pb < p1; pb += 1024 * PER) {
+                uint32_t n[PER];
+                positions(pb, n);
 #pragma unroll
-            for (int i = 0; i < PER; ++i) n[i] = sidx[pb + i * 1024 < p1 ? pb + i * 1024 : pb];
+                for (int g = 0; g < PER; g += C) {
+                    for (int c = 0; c < turn.chunks; c += S) {
+                        Chunk v[S][C];
 #pragma unroll
-            for (int i = 0; i < PER; ++i) {
-                x[i] = reinterpret_cast<const uint32_t*>(codes + (size_t)n[i] * M);
-                h[i] = lh + cluster_of(pb + i * 1024 < p1 ? pb + i * 1024 : pb) * M * L;
-            }
-            for (int w = 0; w < turn.words; w += 2) {
-                const bool two = w + 1 < turn.words;
-                const int wa = turn.word(w), wb = turn.word(two ? w + 1 : w);
-                uint32_t va[PER], vb[PER];
+                        for (int q = 0; q < S; ++q)
+                            if (c + q < turn.chunks)
 #pragma unroll
-                for (int i = 0; i < PER; ++i) va[i] = x[i][wa];
-                if (two)
+                                for (int i = 0; i < C; ++i)
+                                    v[q][i] = *reinterpret_cast<const Chunk*>(codes + (size_t)n[g + i] * M + turn.chunk(c + q) * (4 * CW));
 #pragma unroll
-                    for (int i = 0; i < PER; ++i) vb[i] = x[i][wb];
+                        for (int i = 0; i < C; ++i) {
+                            const uint64_t p = pb + (g + i) * 1024;
+                            if (p >= p1) break;
+                            uint32_t* h = lh + cluster_of(p) * M * L;
 #pragma unroll
-                for (int i = 0; i < PER; ++i)
-                    if (pb + i * 1024 < p1) {
-                        turn.count(h[i], wa, va[i]);
-                        if (two) turn.count(h[i], wb, vb[i]);
+                            for (int q = 0; q < S; ++q)
+                                if (c + q < turn.chunks) turn.count(h, turn.chunk(c + q), v[q][i]);
+                        }
                     }
+                }
             }
+        };
+        const int nw = M / 4;
+        if (nw % 4 == 0) {
+            if (nw == 4) count_chunks(std::integral_constant<int, 4>{}, std::integral_constant<int, 4>{});
+            else if (nw == 8) count_chunks(std::integral_constant<int, 4>{}, std::integral_constant<int, 2>{});
+            else count_chunks(std::integral_constant<int, 4>{}, std::integral_constant<int, 1>{});
+        } else if (nw % 2 == 0) {
+            if (nw == 2) count_chunks(std::integral_constant<int, 2>{}, std::integral_constant<int, 4>{});
+            else count_chunks(std::integral_constant<int, 2>{}, std::integral_constant<int, 2>{});
+        } else {
+            if (nw == 1) count_chunks(std::integral_constant<int, 1>{}, std::integral_constant<int, 4>{});
+            else count_chunks(std::integral_constant<int, 1>{}, std::integral_constant<int, 1>{});
         }
     } else {
-        for (uint64_t p = (uint64_t)p0 + tid; p < p1; p += 1024) {
-            const uint8_t* x = codes + (size_t)sidx[p] * M;
-            uint32_t* h = lh + cluster_of(p) * M * L;
-            for (int m = 0; m < M; ++m) atomicAdd(&h[m * L + x[m]], 1u);
+        for (uint64_t pb = (uint64_t)p0 + tid; pb < p1; pb += 1024 * PER) {
+            uint32_t n[PER];
+            positions(pb, n);
+#pragma unroll
+            for (int i = 0; i < PER; ++i) {
+                if (pb + i * 1024 >= p1) break;
+                const uint8_t* x = codes + (size_t)n[i] * M;
+                uint32_t* h = lh + cluster_of(pb + i * 1024) * M * L;
+                for (int m = 0; m < M; ++m) atomicAdd(&h[m * L + x[m]], 1u);
+            }
         }
     }
     __syncthreads();

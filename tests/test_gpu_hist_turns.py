@@ -12,8 +12,11 @@ pytestmark = pytest.mark.gpu
 
 @pytest.mark.parametrize("kernel", [0, 2, 3])
 @pytest.mark.parametrize("N,M,K", [(1, 4, 1), (63, 12, 3), (1025, 20, 7), (5000, 16, 300), (4097, 32, 65), (3000, 64, 5),
-                                   (2049, 28, 129), (70_001, 8, 700)])
-def test_update(kernel, N, M, K):
+                                   (2049, 28, 129), (70_001, 8, 700), (40_003, 24, 50), (9001, 40, 33), (5003, 48, 90), (30_001, 6, 40),
+                                   (20_011, 16, 1), (66_003, 64, 70)])
+@pytest.mark.parametrize("shift", [0, 1, 4])
+def test_update(kernel, N, M, K, shift):
+    """shift: bytes by which the codes are moved off their alignment (1: read byte by byte)"""
     import torch
 
     import oracle
@@ -27,9 +30,12 @@ def test_update(kernel, N, M, K):
     t = rng.random((M, 256, 256), dtype=np.float32)
     centers = rng.integers(0, 256, (K, M), dtype=np.uint8)
     c = torch.from_numpy(centers.copy()).cuda()
+    buf = torch.zeros(codes.size + shift, dtype=torch.uint8, device="cuda")
+    x = buf[shift:].view(codes.shape)
+    x.copy_(torch.from_numpy(codes))
     pq.set_option("hist_kernel", kernel)
     try:
-        _, h, n = pq.update(torch.from_numpy(codes).cuda(), torch.from_numpy(a).cuda(), torch.from_numpy(t).cuda(), c)
+        _, h, n = pq.update(x, torch.from_numpy(a).cuda(), torch.from_numpy(t).cuda(), c)
     finally:
         pq.set_option("hist_kernel", 0)
     valid = (a >= 0) & (a < K)
