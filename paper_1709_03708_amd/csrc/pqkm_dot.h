@@ -56,6 +56,9 @@ __device__ __forceinline__ int dot_dims(const DotStat* __restrict__ st)
     return most <= 128 / M ? 128 : most <= 256 / M ? 256 : 0;
 }
 
+// the larger of two, NaN if either is
+__device__ __forceinline__ float dot_worse(float a, float b) { return b <= a || a != a ? a : b; }
+
 // the largest of a wave's values, in lane 63
 __device__ __forceinline__ uint32_t dot_wave_max(uint32_t v)
 {
@@ -196,13 +199,12 @@ __global__ __launch_bounds__(256) void dot_check_kernel(const float* __restrict_
         const float a = tables[((size_t)m * L + part * ROWS + i) * L + j];
         // the roundings of q itself: R + 2 of them, each at most 2^-24 of it
         const float e = __builtin_fabsf(a - q) + q * ((float)(R + 8) * 0x1p-23f);
-        e0 = e <= e0 ? e0 : e;                                   // keeps a NaN
+        e0 = dot_worse(e0, e);
         sum += a;
     }
 #pragma unroll
     for (int off = 32; off; off >>= 1) {
-        const float o = __shfl_xor(e0, off);
-        e0 = o <= e0 ? e0 : o;
+        e0 = dot_worse(e0, __shfl_xor(e0, off));
         sum += __shfl_xor(sum, off);
     }
     if ((j & 63) == 0) { red_s[0][j >> 6] = e0; red_s[1][j >> 6] = sum; }
@@ -220,7 +222,7 @@ __global__ __launch_bounds__(256) void dot_check_kernel(const float* __restrict_
     __syncthreads();
     if (j == 0) {
         for (int w = 1; w < 4; ++w) {
-            e0 = red_s[0][w] <= e0 ? e0 : red_s[0][w];
+            e0 = dot_worse(e0, red_s[0][w]);
             sum += red_s[1][w];
         }
         check[blockIdx.x] = DotCheck{e0, sum};
@@ -252,7 +254,7 @@ __global__ __launch_bounds__(256) void dot_centers_kernel(const uint8_t* __restr
 #pragma unroll
                 for (int p = 0; p < DOT_PARTS; ++p) {
                     const DotCheck c = check[t * DOT_PARTS + p];
-                    e0 = c.e0 <= e0 ? e0 : c.e0;
+                    e0 = dot_worse(e0, c.e0);
                     sum += c.sum;
                 }
                 e0_s[t] = e0;
@@ -263,7 +265,8 @@ __global__ __launch_bounds__(256) void dot_centers_kernel(const uint8_t* __restr
                 float e0 = 0.0f, sum = 0.0f;
                 if (usable)
                     for (int m = 0; m < M; ++m) { e0 += e0_s[m]; sum += sum_s[m]; }
-                state->left = usable && e0 <= DOT_E0_MAX * (sum * (1.0f / 65536.0f)) ? 0u : 1u;
+                // an infinite entry makes e0 and perhaps the sum infinite, a NaN both NaN
+                state->left = usable && e0 < INFINITY && sum < INFINITY && e0 <= DOT_E0_MAX * (sum * (1.0f / 65536.0f)) ? 0u : 1u;
                 state->e0 = e0;
             }
         }

@@ -140,6 +140,20 @@ def test_tables(env, M, kind):
     _check(env, codes, centers, t, dist=kind != "integer", left=None if M == 4 or kind == "hamming" else not kept)
 
 
+@pytest.mark.parametrize("M", [8, 16, 32])
+@pytest.mark.parametrize("value", [np.inf, -np.inf, np.nan])
+def test_one_entry_that_is_not_finite(env, M, value):
+    """Off the first row and the diagonal, and so few codes and centers that giving all their distances exceeds none of the scan's own
+    limits: it is the check of the tables that leaves them."""
+    pq, oracle, _ = env
+    rng = np.random.default_rng(M)
+    cw, codes, centers = _problem(rng, 3, M, 66, 128 // M)
+    for at in ((0, 7, 9), (M - 1, 250, 3), (M // 2, 255, 254)):
+        t = oracle.build_tables(cw)
+        t[at] = value
+        _check(env, codes, centers, t, left=True)
+
+
 @pytest.mark.parametrize("M", [8, 16])
 def test_near_ties_are_decided_by_the_sum_of_the_definition(env, M):
     """Codewords on few values: thousands of centers at distances that differ in the last bits or not at all."""
