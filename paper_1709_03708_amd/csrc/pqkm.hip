@@ -90,6 +90,7 @@ pqkm_status log_read(EventLog& log, double* total_ms, int64_t* count)
 
 inline size_t align256(size_t x) { return (x + 255) & ~(size_t)255; }
 inline bool tiled_M(int M) { return M == 4 || M == 8 || M == 16 || M == 32; }
+inline bool dot_M(int M) { return M == 8 || M == 16 || M == 32; }      // has the scan on the matrix cores
 
 struct Carve {
     size_t img_off, img_bytes, hist_off, hist_bytes, counts_off, counts_bytes, parts_off, parts_bytes, gid_off,
@@ -263,7 +264,7 @@ Carve carve(int64_t N, int M, int K)
     }
     // state of the scan on the matrix cores (DotState), under the same condition; its other arrays share the images' room
     c.dot_off = 0;
-    if (tiled_M(M) && !(off <= PQKM_NOALLOC_SCRATCH_BYTES && off + 256 > PQKM_NOALLOC_SCRATCH_BYTES) &&
+    if (dot_M(M) && !(off <= PQKM_NOALLOC_SCRATCH_BYTES && off + 256 > PQKM_NOALLOC_SCRATCH_BYTES) &&
         dot_carve(M, K).total <= c.img_bytes) {
         c.dot_off = off;
         off += 256;
@@ -346,12 +347,12 @@ void launch_scan(const uint8_t* codes, int64_t N, const float4* img, int ntiles,
 
 template <int R, int THREADS>
 void launch_scan4s(const uint8_t* codes, int64_t N, const float4* img, int ntiles, int32_t* assign, float* dist,
-                   hipStream_t st, const uint32_t* only_if)
+                   hipStream_t st)
 {
     constexpr int C = (THREADS / 4) * R;
     int64_t nwg = (N + C - 1) / C;
     hipLaunchKernelGGL((assign_scan4s_kernel<R, THREADS>), dim3((unsigned)nwg), dim3(THREADS), 0, st, codes, N, img,
-                       ntiles, assign, dist, only_if);
+                       ntiles, assign, dist);
 }
 
 template <int R, int THREADS, int DEPTH, bool BUCKET = false>
@@ -984,23 +985,23 @@ pqkm_status regroup_codes(const uint8_t* codes, int64_t cnt, uint2* gco, GroupPl
 
 template <>
 void launch_scan_M<4>(int variant, const uint8_t* codes, int64_t N, const float4* img, const float4* rows,
-                      int ntiles, int32_t* assign, float* dist, hipStream_t st, const uint32_t* only_if)
+                      int ntiles, int32_t* assign, float* dist, hipStream_t st, const uint32_t*)
 {
     switch (variant) {
         case 1: launch_scan<4, 16, 512, false>(codes, N, img, ntiles, assign, dist, st); break;
         case 3: launch_scan<4, 16, 512, true>(codes, N, img, ntiles, assign, dist, st); break;
         case 5: launch_scan<4, 8, 1024, false>(codes, N, img, ntiles, assign, dist, st); break;
-        case 32: launch_scan4s<16, 768>(codes, N, img, ntiles, assign, dist, st, only_if); break;
-        case 34: launch_scan4s<16, 1024>(codes, N, img, ntiles, assign, dist, st, only_if); break;
-        case 36: launch_scan4s<16, 512>(codes, N, img, ntiles, assign, dist, st, only_if); break;
-        case 37: launch_scan4s<8, 1024>(codes, N, img, ntiles, assign, dist, st, only_if); break;
-        case 33: launch_scan4s<4, 512>(codes, N, img, ntiles, assign, dist, st, only_if); break;
-        case 35: launch_scan4s<8, 512>(codes, N, img, ntiles, assign, dist, st, only_if); break;
+        case 32: launch_scan4s<16, 768>(codes, N, img, ntiles, assign, dist, st); break;
+        case 34: launch_scan4s<16, 1024>(codes, N, img, ntiles, assign, dist, st); break;
+        case 36: launch_scan4s<16, 512>(codes, N, img, ntiles, assign, dist, st); break;
+        case 37: launch_scan4s<8, 1024>(codes, N, img, ntiles, assign, dist, st); break;
+        case 33: launch_scan4s<4, 512>(codes, N, img, ntiles, assign, dist, st); break;
+        case 35: launch_scan4s<8, 512>(codes, N, img, ntiles, assign, dist, st); break;
         case 41: launch_scan4p<16, 1024, 1>(codes, N, nullptr, img, rows, ntiles, assign, dist, st); break;
         case 44: launch_scan4p<24, 512, 4>(codes, N, nullptr, img, rows, ntiles, assign, dist, st); break;
         case 46: launch_scan4p<28, 512, 3>(codes, N, nullptr, img, rows, ntiles, assign, dist, st); break;
         case 48: launch_scan4p<32, 512, 3>(codes, N, nullptr, img, rows, ntiles, assign, dist, st); break;
-        default: launch_scan4s<16, 1024>(codes, N, img, ntiles, assign, dist, st, only_if); break;
+        default: launch_scan4s<16, 1024>(codes, N, img, ntiles, assign, dist, st); break;
     }
 }
 template <>
@@ -1347,10 +1348,12 @@ pqkm_status assign_tiled(const uint8_t* codes, int64_t N, const uint8_t* centers
     const int layout = variant_layout(M, variant);
     // not NULL: a word that says whether the scans below have anything to do
     const uint32_t* left = nullptr;
-    if (plan_of.dot) {
-        launch_dot<M>(codes, N, centers, K, tables, assign, dist, c, ws, carried, opt, st);
-        if (launched() != PQKM_OK) return PQKM_ERR_DEVICE;
-        left = &reinterpret_cast<const DotState*>(ws + c.dot_off)->left;
+    if constexpr (M != 4) {
+        if (plan_of.dot) {
+            launch_dot<M>(codes, N, centers, K, tables, assign, dist, c, ws, carried, opt, st);
+            if (launched() != PQKM_OK) return PQKM_ERR_DEVICE;
+            left = &reinterpret_cast<const DotState*>(ws + c.dot_off)->left;
+        }
     }
     // images that may not be needed are built by few blocks
     auto blocks_of = [&](int64_t elements) {

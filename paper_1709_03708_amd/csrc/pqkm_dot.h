@@ -208,7 +208,7 @@ __global__ __launch_bounds__(256) void dot_check_kernel(const float* __restrict_
         sum += __shfl_xor(sum, off);
     }
     if ((j & 63) == 0) { red_s[0][j >> 6] = e0; red_s[1][j >> 6] = sum; }
-    // the halves: r = 4, 8, .. 64 neighbouring lanes to a row
+    // the halves: r = 4, 8, 16 or 32 neighbouring lanes to a row
     const int r = dims / M;
     for (int at = j; at < ROWS * r; at += 256) {                 // ROWS r is a multiple of 64: whole waves
         const int i = at / r, k = at % r;

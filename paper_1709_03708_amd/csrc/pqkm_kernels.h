@@ -955,10 +955,8 @@ template <int R, int THREADS>
 __global__ __launch_bounds__(THREADS) void assign_scan4s_kernel(const uint8_t* __restrict__ codes, int64_t N,
                                                                 const float4* __restrict__ img, int ntiles,
                                                                 int32_t* __restrict__ assign,
-                                                                float* __restrict__ dist,
-                                                                const uint32_t* __restrict__ only_if = nullptr)
+                                                                float* __restrict__ dist)
 {
-    if (only_if && *only_if == 0u) return;
     constexpr int LPS = 4, TK = 32;
     constexpr int SLOTS = THREADS / LPS;
     constexpr int C = SLOTS * R;

@@ -100,3 +100,14 @@ def test_copy_is_placed_for_the_scan_that_reads_it(pq, M, N, K):
 def test_few_codes_take_no_more_than_a_round_of_tiles(pq, M, K, most):
     """One lane per center only up to the codes for which it is the faster one: with few centers the tiled scans are cheap."""
     assert pq.scan_plan(most, M, K)["scan"] == 0 and pq.scan_plan(most + 1, M, K)["scan"] == 1
+
+
+def test_matrix_core_scan_where_it_is_built(pq):
+    """M = 4 has no scan on the matrix cores, and one that regroups its codes is not preceded by it."""
+    _options(pq, variant=20)
+    assert not pq.dot_scan(100_000, 4, 1000)["tried"]
+    for M, K in ((8, 48), (16, 16)):                  # the images leave no room for it
+        assert not pq.dot_scan(100_000, M, K)["tried"] and pq.dot_scan(100_000, M, K + 1)["tried"]
+    assert pq.dot_scan(100_000, 32, 1)["tried"]
+    assert not pq.dot_scan(5_000_000, 8, 1000)["tried"] and pq.scan_plan(5_000_000, 8, 1000)["lanes"]
+    _options(pq)
