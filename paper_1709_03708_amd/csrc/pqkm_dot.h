@@ -485,6 +485,9 @@ __device__ __forceinline__ void dot_scan(const DotIn& f, int32_t* __restrict__ a
     fetch_codes(blockIdx.x);
     fetch(0, 0);
 
+    // seen by the workgroups of other XCDs while this kernel runs, not only behind its end
+    auto leave = [&]() { __hip_atomic_store(&f.state->left, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); };
+
     for (int64_t blk = blockIdx.x; blk < nblocks; blk += gridDim.x) {
         const int64_t base = blk * C + wave * (32 * CT);
         // has another workgroup given up?  One thread asks for all
@@ -700,7 +703,7 @@ __device__ __forceinline__ void dot_scan(const DotIn& f, int32_t* __restrict__ a
         // far more than the plain scan of these codes would cost: the same verdict in all threads
         const float cost = (float)listed + (float)overs * (float)f.K;
         if (overs > (uint32_t)DOT_OVER || cost > most) {
-            if (tid == 0) f.state->left = 1u;
+            if (tid == 0) leave();
             break;
         }
         for (uint32_t i = (uint32_t)tid; i < (listed < (uint32_t)DOT_LIST ? listed : (uint32_t)DOT_LIST); i += 512u) {
@@ -718,7 +721,10 @@ __device__ __forceinline__ void dot_scan(const DotIn& f, int32_t* __restrict__ a
         if (spent > free_evals * done_codes) {
             if (tid == 0) {
                 const unsigned long long all = atomicAdd(&f.state->formed[f.iteration & 1], (unsigned long long)spent);
-                if ((float)all + spent > 0.5f * free_evals * (float)f.N) f.state->left = given_up = 1u;
+                if ((float)all + spent > 0.5f * free_evals * (float)f.N) {
+                    leave();
+                    given_up = 1u;
+                }
             }
             spent = done_codes = 0.0f;
         }
