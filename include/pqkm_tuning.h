@@ -34,7 +34,7 @@ extern "C" {
  *                        60 = the scan through lower bounds, M = 4 and 8, 59 the same for M = 16 and 32,
  *                        65 = the best of the plain M = 4 scans, 20 = the scan on the matrix cores, M = 8, 16 and 32, in front of
  *                        the default ones, unless these regroup the codes or the images leave it no room: M = 8 with
- *                        fewer than 49 centers, M = 16 with fewer than 17)
+ *                        fewer than 17 centers)
  *   "hist_kernel"        0 = choose automatically (default; inside pqkm_fit / pqkm_fit_until with M = 4 this
  *                        includes counting from records the scan files by cluster group), 1 = force one global atomic
  *                        per code and subspace, 2 = force the LDS-privatised histogram over cluster

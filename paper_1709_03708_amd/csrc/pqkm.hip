@@ -145,18 +145,17 @@ bool owner_histogram(const HistPlan& hp, int force)
     return hp.KT >= 1 && hp.groups <= 255 && force != 1 && force != 3 && (force == 2 || hp.cheap);
 }
 
-// The scan on the matrix cores, inside the images' room: fragments of the centers, halves of the points, what rounding took of
-// each, the points, statistics.
-struct DotCarve { size_t img_off, emb_off, lost_off, u_off, stat_off, check_off, total; };
+// The scan on the matrix cores, inside the images' room: fragments of the centers, halves of the points (all columns, and the
+// first half of them), what rounding took of each, statistics.
+struct DotCarve { size_t img_off, emb_off, lost_off, stat_off, check_off, total; };
 
 DotCarve dot_carve(int M, int K)
 {
     DotCarve c{};
     size_t off = 0;
     c.img_off = off;    off += align256((((size_t)K + DOT_TILE - 1) / DOT_TILE) * DOT_CHUNK);     // 256 dimensions: a chunk per tile
-    c.emb_off = off;    off += (size_t)L * 256 * 2;
+    c.emb_off = off;    off += (size_t)L * (256 + 128) * 2;
     c.lost_off = off;   off += (size_t)M * L * sizeof(float);
-    c.u_off = off;      off += (size_t)L * 256 * sizeof(float);
     c.stat_off = off;   off += align256((size_t)M * sizeof(DotStat));
     c.check_off = off;  off += align256((size_t)M * DOT_PARTS * sizeof(DotCheck));
     c.total = off;
@@ -1207,23 +1206,33 @@ struct Carried {
     bool dot = false;         // the points of the scan on the matrix cores, or that it is not for these tables
 };
 
-// Is the scan on the matrix cores tried first?  It takes about 6e12 center-code pairs per second at 128 dimensions (half of that
-// at 256) whatever M is, behind 25 to 35 us for the points, once per call, and the fragments of the centers; tables it is not for
-// cost 10 to 25 us.  Plain scans / this, us, 128 dimensions: M = 8: 87 / 97 at N = 3e5, K = 300; 148 / 77 at 1e5, 1000; 569 / 318 at
-// 1e6, 1000; M = 16: 101 / 36 at 3e4, 300; 47 / 47 at 1e4, 1000; M = 32: 83 / 47 at 1e4, 1000; 227 / 38 at 3e4, 300.  The sizes at
-// which M = 8 regroups its codes for the lower-bound scan are left to that (up to 8.7e12 pairs per second), and all of M = 4 to
-// its scans (64 / 88 at 1e5, 700).  256 dimensions, M = 8: 145 / 120 at 1e5, 1000; 563 / 588 at 1e6, 1000, so only up to 400000 codes.
-inline bool dot_scan_wanted(int M, const Options& opt, int64_t N, int K, const uint8_t* centers, const Carve& c)
+// Is the scan on the matrix cores tried first, and for how many dimensions?  Whole calls take up to 4e12 center-code pairs per
+// second at 128 dimensions (M = 8, N = 1e6, K = 4000) and half of that at 256, behind 10 to 27 us for the points, once per call, and 8 for the centers' fragments, and
+// a block of codes costs 10 to 13 us beside its centers; tables it is not for cost 10 us (M = 8: 14).  Plain scans / this, us, whole
+// calls with distances, both measured where this is taken and where it is not.
+// M = 8, 128 dimensions: 150 / 69 at N = 1e5, K = 1000; 93 / 74 at 2e5, 450; 84 / 81 at 3e5, 300; 574 / 342 at 1e6, 1000; 215 / 208 at 2e6,
+// 100.  256 dimensions: 148 / 113 at 1e5, 1000; 190 / 153 at 1.8e5, 1000; 541 / 483 at 4e5, 2000; but 103 / 123 at 2e5, 500; 184 /
+// 186 at 2.6e5, 1000; 562 / 582 at 1e6, 1000.
+// M = 16, 128 dimensions: 66 / 37 at 6e4, 200; 127 / 39 at 25100, 400; 187 / 159 at 1e6, 100; but 57 / 58 at 2e5, 100; 139 / 142 at 1e6,
+// 64; 117 / 132 at 1e6, 40.  256 dimensions: 131 / 103 at 2e5, 300; 383 / 322 at 1e6, 300; but 91 / 94 at 2e5, 200; 182 / 229 at 1e6, 100.
+// M = 32, 128 dimensions: 90 / 60 at 1e5, 100; 385 / 268 at 1e6, 100; 83 / 84 at 2e5, 64.  256: 91 / 72, 376 / 346; 85 / 103.
+// Below gather_max_codes the scan with one lane per center runs and this is not asked for (M = 32, K = 1000: up to 47058 codes); the
+// sizes at which M = 8 regroups its codes are left to the lower-bound scan (up to 8.7e12 pairs per second in later iterations, 2e12 in
+// a first one), and all of M = 4 to its scans.
+int dot_scan_dims(int M, const Options& opt, int64_t N, int K, const uint8_t* centers, const Carve& c)
 {
-    if (c.dot_off == 0 || ((uintptr_t)centers & 3) != 0 || (int64_t)K > ((int64_t)1 << 22)) return false;
-    if (opt.scan_variant == 20) return true;             // forced
+    if (c.dot_off == 0 || ((uintptr_t)centers & 3) != 0 || (int64_t)K > ((int64_t)1 << 22)) return 0;
+    if (opt.scan_variant == 20) return 256;              // forced
+    if (opt.scan_variant != 0) return 0;
     const double pairs = (double)N * K;
-    return opt.scan_variant == 0 && ((M == 8 && pairs >= 9e7 && K >= 500) || (M == 16 && pairs >= 9e6 && N >= 25000) || (M == 32 && pairs >= 9e6));
+    if (M == 8) return pairs < 9e7 || K < 500 ? 0 : K >= 650 && N <= (K >= 2000 ? 400000 : 200000) ? 256 : 128;
+    if (M == 16) return pairs < 9e6 || N < 25000 || K < (pairs < 5e7 ? 200 : 100) ? 0 : K >= 300 ? 256 : 128;
+    return pairs < 9e6 || K < 100 ? 0 : 256;
 }
 
 template <int M>
 void launch_dot(const uint8_t* codes, int64_t N, const uint8_t* centers, int K, const float* tables, int32_t* assign, float* dist,
-                const Carve& c, char* ws, const Carried& carried, const Options& opt, hipStream_t st)
+                const Carve& c, char* ws, const Carried& carried, const Options& opt, int most_dims, hipStream_t st)
 {
     const DotCarve d = dot_carve(M, K);
     char* room = ws + c.img_off;
@@ -1232,13 +1241,10 @@ void launch_dot(const uint8_t* codes, int64_t N, const uint8_t* centers, int K, 
     DotCheck* check = reinterpret_cast<DotCheck*>(room + d.check_off);
     _Float16* emb = reinterpret_cast<_Float16*>(room + d.emb_off);
     float* lost = reinterpret_cast<float*>(room + d.lost_off);
-    float* points = reinterpret_cast<float*>(room + d.u_off);
-    if (!carried.dot) {
-        hipLaunchKernelGGL((dot_embed_kernel<M>), dim3(M), dim3(256), 0, st, tables, points, stat);
-        hipLaunchKernelGGL((dot_check_kernel<M>), dim3(M * DOT_PARTS), dim3(256), 0, st, tables, points, stat, check, emb, lost, state);
-    }
+    if (!carried.dot)
+        hipLaunchKernelGGL((dot_points_kernel<M>), dim3(M * DOT_PARTS), dim3(256), 0, st, tables, stat, check, emb, lost, state);
     hipLaunchKernelGGL((dot_centers_kernel<M>), dim3((unsigned)((K + DOT_TILE - 1) / DOT_TILE)), dim3(256), 0, st, centers, K, stat,
-                       check, emb, lost, state, room + d.img_off, carried.iteration, !carried.dot, M == 8 && N > 400000 ? 128 : 256);
+                       check, emb, lost, state, room + d.img_off, carried.iteration, !carried.dot, most_dims);
     EventPair ev{};
     const bool prof = (opt.profile & 1) && log_begin(g_scan_log, st, &ev);
     const DotIn in{codes, centers, tables, stat, emb, lost, room + d.img_off, state, N, K, carried.iteration};
@@ -1260,7 +1266,7 @@ void launch_dot(const uint8_t* codes, int64_t N, const uint8_t* centers, int K, 
 struct ScanPlan {
     int variant;
     bool filter, wide, grouped, sliding;
-    bool dot;                 // the scan on the matrix cores is tried first; all of the above is for what it leaves
+    int dot;                  // dimensions up to which the scan on the matrix cores is tried first; the above is for what it leaves
     int lanes;                // lanes per slot that the regrouped copy is placed for (grouped)
     int64_t per_launch;       // codes per stretch
     bool reuse;               // the regrouped copy is there already
@@ -1296,7 +1302,7 @@ ScanPlan scan_plan(int M, const Options& opt, int64_t N, int K, const uint8_t* c
     p.sliding = variant_sliding(M, variant);
     // M = 16, 32: the lower-bound scan of every stretch in front of the sliding-window scan, which runs where it gave up
     p.wide = p.sliding && wide_filter(M, asked, variant, N, K, centers, iteration);
-    p.dot = dot_scan_wanted(M, opt, N, K, centers, c) && !p.grouped;
+    p.dot = p.grouped ? 0 : dot_scan_dims(M, opt, N, K, centers, c);
     p.lanes = !p.grouped ? 0 : variant_two_lane(M, variant) ? 2 : 4;
     int64_t per_launch = opt.launch_codes;
     // a little below the limit: with its padding a launch of exactly 2^26 codes needs one workgroup more than
@@ -1327,7 +1333,7 @@ ScanPlan scan_plan(int M, const Options& opt, int64_t N, int K, const uint8_t* c
     p.leaves.lanes = one ? p.lanes : 0;
     p.leaves.stats = p.filter;
     p.leaves.keys = p.filter && one && keys_survive;
-    p.leaves.dot = p.dot;
+    p.leaves.dot = p.dot > 0;
     return p;
 }
 
@@ -1350,7 +1356,7 @@ pqkm_status assign_tiled(const uint8_t* codes, int64_t N, const uint8_t* centers
     const uint32_t* left = nullptr;
     if constexpr (M != 4) {
         if (plan_of.dot) {
-            launch_dot<M>(codes, N, centers, K, tables, assign, dist, c, ws, carried, opt, st);
+            launch_dot<M>(codes, N, centers, K, tables, assign, dist, c, ws, carried, opt, plan_of.dot, st);
             if (launched() != PQKM_OK) return PQKM_ERR_DEVICE;
             left = &reinterpret_cast<const DotState*>(ws + c.dot_off)->left;
         }

@@ -5,9 +5,8 @@
 // product per code and center, d(x, c) = |u_x|^2 + |u_c|^2 - 2 u_x.u_c, whose cost does not depend on M.
 //
 // Nothing is assumed about the tables.  A call first looks for such points: per subspace a pivoted Cholesky factorisation
-// of the Gram matrix (A[0][i] + A[0][j] - A[i][j]) / 2, at most 256 / M columns, moved to the points' mean (dot_embed_kernel).
-// Every entry of the tables is then compared with the points (dot_check_kernel): `e0` bounds what an entry sum of Eq. 3 can
-// differ by.  Tables that no such points describe (more dimensions, not symmetric, infinities, NaN) set `left`, and the
+// of the Gram matrix (A[0][i] + A[0][j] - A[i][j]) / 2, at most 256 / M columns, moved to the points' mean.  Every entry of the
+// tables is then compared with the points (both in dot_points_kernel): `e0` bounds what an entry sum of Eq. 3 can differ by.  Tables that no such points describe (more dimensions, not symmetric, infinities, NaN) set `left`, and the
 // scans that are launched behind do the work as if this one did not exist; they end at once where it is 0.
 //
 // The bound.  With u' the points rounded to half precision (times a power of two, all below in those units), d_x = |u_x - u'_x|,
@@ -44,7 +43,7 @@ struct DotState {
     uint32_t dc2[2], nc2[2];                      // per parity of the iteration: max |u_c - u'_c|^2, max |u'_c|^2, as bits
     unsigned long long formed[2];                 // likewise: fp32 distances formed
 };
-struct DotStat { int rank; float most; };         // per subspace: columns found (more than 256 / M: not enough), max |u|
+struct DotStat { int rank; };                     // per subspace: columns found (more than 256 / M: not enough)
 struct DotCheck { float e0, sum; };               // per part of a subspace: largest difference, sum of the entries
 
 // 128 or 256 dimensions in all (128 / M or 256 / M per subspace), 0: too many
@@ -72,51 +71,160 @@ __device__ __forceinline__ uint32_t dot_wave_max(uint32_t v)
     return v;
 }
 
-// One block per subspace, thread i owns row i of the factor, whose columns are in LDS.  U[m][i][256 / M].  Serial in the columns:
-// two barriers and a row of the tables each, 1.1 us.  (Reading the whole table first, so that the rows come from the near L2, took
-// longer than it saved: 22 us instead of 18 at M = 8 with 16 columns.)
+// Block (m, part): the points of subspace m, which every block of the subspace finds for itself (a launch and a trip through memory
+// less), then rows 16 part .. 16 part + 15 of its table against all 256 of them, the halves of those 16 and what rounding took.
+//
+// The factorisation is serial in its columns, and a column of all 256 points costs two barriers and a row of the tables, 0.9 us.  So
+// one wave first factorises the Gram matrix of 64 of the points, a row of it per lane and the factor in registers: where they
+// need too many columns, so do all points, and the block is done; else their pivots serve all points, whose rows then come in one go
+// (forward substitution), and only columns that the 64 do not span are found one by one.
+// emb[m][x][256 / M] halves and, behind them, the same with the first half of the columns; lost[m][x] = |u - u'|^2.
+// Measured, us, against a factorisation of all 256 points by one block per subspace and a launch for the comparison: M = 8 with 16
+// columns 29 -> 17 (and a launch), with 32 42 -> 27; M = 16 15 -> 12; M = 32 11 -> 10.  Whole calls whose tables have more than 256
+// dimensions pay 35, 22 and 15 -> 14, 10 and 10 us at M = 8, 16 and 32.
+constexpr int DOT_SAMPLE = 64;
+
 template <int M>
-__global__ __launch_bounds__(256) void dot_embed_kernel(const float* __restrict__ tables, float* __restrict__ U,
-                                                        DotStat* __restrict__ st)
+__global__ __launch_bounds__(256) void dot_points_kernel(const float* __restrict__ tables, DotStat* __restrict__ st,
+                                                         DotCheck* __restrict__ check, _Float16* __restrict__ emb,
+                                                         float* __restrict__ lost, DotState* __restrict__ state)
 {
-    constexpr int R = 256 / M;
+    static_assert(M >= 8, "the columns of a lane are registers");
+    constexpr int R = 256 / M, S = DOT_SAMPLE, ROWS = L / DOT_PARTS;
     __shared__ float col[R][L];
-    __shared__ float a0_s[L], pd_s, part_s[4];
-    __shared__ uint32_t red[4];
-    const int i = threadIdx.x, wave = i >> 6;
-    const float* A = tables + (size_t)blockIdx.x * (L * L);
-    const float a0 = A[i];
-    float d = a0 - 0.5f * A[i * (L + 1)];
+    __shared__ float gram_s[S][S];
+    __shared__ __attribute__((aligned(16))) float low_s[R][R], row_s[ROWS][R];       // the pivots' rows of the factor; rows to compare
+    __shared__ float a0_s[L], d_s[L], inv_s[R], pd_s, red_s[2][4];
+    __shared__ int piv_s[R], rank_s;
+    __shared__ uint32_t red[2][4];
+    const int m = (int)blockIdx.x / DOT_PARTS, part = (int)blockIdx.x % DOT_PARTS;
+    const int i = threadIdx.x, lane = i & 63, wave = __builtin_amdgcn_readfirstlane(i >> 6);
+    auto sample = [](int t) { return (t & 15) | ((t >> 4) << 6); };    // 64 points: four stretches of 16, a cache line of a row each
+    const float* A = tables + (size_t)m * (L * L);
+    float sam[S / 4], head[M];
+#pragma unroll
+    for (int j = 0; j < S / 4; ++j) sam[j] = A[sample(wave * (S / 4) + j) * L + sample(lane)];
+#pragma unroll
+    for (int q = 0; q < M; ++q) head[q] = tables[(size_t)q * (L * L) + i];
+    const float a0 = A[i], diag = A[i * (L + 1)], down = A[i * L];
+    float d = a0 - 0.5f * diag, top = 0.0f;
     a0_s[i] = a0;
-    float stop = 0.0f;
-    int rank = 0;
+    d_s[i] = d;
     // distances that could not be any points': not zero on the diagonal, not symmetric in the first row and column
-    const bool odd = __builtin_fabsf(A[i * (L + 1)]) + __builtin_fabsf(a0 - A[i * L]) > 1e-3f * __builtin_fabsf(a0) && i > 0;
-    if (__syncthreads_or(odd)) {
-        if (i == 0) st[blockIdx.x] = DotStat{R + 1, 0.0f};
+    const bool odd = __builtin_fabsf(diag) + __builtin_fabsf(a0 - down) > 1e-3f * __builtin_fabsf(a0) && i > 0;
+    // the largest |u|^2 of the subspace, which says where a column is nothing but rounding, and of all subspaces (negative and NaN
+    // count as 0)
+#pragma unroll
+    for (int q = 0; q < M; ++q) top = head[q] > top ? head[q] : top;
+    uint32_t v = dot_wave_max(d > 0.0f ? __builtin_bit_cast(uint32_t, d) : 0u);
+    uint32_t vt = dot_wave_max(__builtin_bit_cast(uint32_t, top));
+    if (lane == 63) {
+        red[0][wave] = v;
+        red[1][wave] = vt;
+    }
+    const bool none = __syncthreads_or(odd);
+    v = red[0][0];
+    vt = red[1][0];
+#pragma unroll
+    for (int w = 1; w < 4; ++w) {
+        v = red[0][w] > v ? red[0][w] : v;
+        vt = red[1][w] > vt ? red[1][w] : vt;
+    }
+    const float stop = __builtin_bit_cast(float, v) * 0x1p-17f;
+    // points are at most 2 sqrt(top) from their mean: a power of two that brings that below 128
+    const int ex = (int)(vt >> 23) - 127;
+    const float scale = ex > -107 && ex < 109 ? __builtin_bit_cast(float, (uint32_t)(127 + 6 - ((ex + 2) >> 1)) << 23) : 0.0f;
+    if (blockIdx.x == 0 && i == 0) {
+        state->scale = scale;                                    // 0: nothing to go on with
+        state->dc2[0] = state->nc2[0] = 0u;
+        state->formed[0] = 0ull;
+    }
+    if (none || scale == 0.0f) {
+        if (part == 0 && i == 0) st[m] = DotStat{R + 1};
         return;
     }
-#pragma unroll 1
-    for (int k = 0; k <= R; ++k) {
-        // the largest of what is left, with its row in the low bits; negative and NaN count as 0
-        uint32_t v = d > 0.0f ? (__builtin_bit_cast(uint32_t, d) & ~255u) | (uint32_t)i : (uint32_t)i;
-        v = dot_wave_max(v);
-        if ((i & 63) == 63) red[wave] = v;
-        __syncthreads();
-        v = red[0];
 #pragma unroll
-        for (int w = 1; w < 4; ++w) v = red[w] > v ? red[w] : v;
-        const int p = (int)(v & 255u);
-        const float ap = A[p * L + i];
+    for (int j = 0; j < S / 4; ++j) {
+        const int row = wave * (S / 4) + j;
+        gram_s[row][lane] = 0.5f * (a0_s[sample(row)] + a0_s[sample(lane)] - sam[j]);
+    }
+    __syncthreads();
+    if (wave == 0) {
+        float f[R], ds = d_s[sample(lane)];
+        int rank = 0, mine = -1;
+#pragma unroll
+        for (int k = 0; k < R; ++k) f[k] = 0.0f;
+#pragma unroll
+        for (int k = 0; k <= R; ++k) {
+            const uint32_t w = dot_wave_max(ds > 0.0f ? (__builtin_bit_cast(uint32_t, ds) & ~63u) | (uint32_t)lane : (uint32_t)lane);
+            const int p = __builtin_amdgcn_readlane((int)w, 63) & 63;
+            const float pd = __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, ds), p));
+            if (!(pd > stop) || !(pd < INFINITY)) break;
+            if (k == R) {
+                if (pd > 8.0f * stop) rank = R + 1;
+                break;
+            }
+            float g[2] = {0.0f, 0.0f};
+            const float whole = gram_s[p][lane];
+#pragma unroll
+            for (int j = 0; j < k; ++j)
+                g[j & 1] = __builtin_fmaf(f[j], __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, f[j]), p)), g[j & 1]);
+            const float inv = __builtin_amdgcn_rsqf(pd);
+            f[k] = (whole - (g[0] + g[1])) * inv;
+            ds = lane == p ? 0.0f : __builtin_fmaf(-f[k], f[k], ds);
+            mine = lane == p ? k : mine;
+            if (lane == 0) {
+                piv_s[k] = sample(p);
+                inv_s[k] = inv;
+            }
+            rank = k + 1;
+        }
+        if (mine >= 0)
+#pragma unroll
+            for (int k = 0; k < R; ++k) low_s[mine][k] = f[k];
+        if (lane == 0) rank_s = rank;
+    }
+    __syncthreads();
+    int rank = __builtin_amdgcn_readfirstlane(rank_s);
+    if (rank > R) {
+        if (part == 0 && i == 0) st[m] = DotStat{R + 1};
+        return;
+    }
+    float u[R];
+#pragma unroll
+    for (int k = 0; k < R; ++k) u[k] = k < rank ? A[piv_s[k] * L + i] : 0.0f;
+#pragma unroll
+    for (int k = 0; k < R; ++k)
+        if (k < rank) {
+            float g[2] = {0.0f, 0.0f};
+#pragma unroll
+            for (int j = 0; j < k; ++j) g[j & 1] = __builtin_fmaf(u[j], low_s[k][j], g[j & 1]);
+            const int x = piv_s[k];
+            u[k] = (0.5f * (a0 + a0_s[x] - u[k]) - (g[0] + g[1])) * inv_s[k];
+            col[k][i] = u[k];
+            d = i == x ? 0.0f : __builtin_fmaf(-u[k], u[k], d);
+        }
+    __syncthreads();
+#pragma unroll 1
+    for (int k = rank; k <= R; ++k) {
+        // the largest of what is left, with its row in the low bits; negative and NaN count as 0
+        uint32_t w = d > 0.0f ? (__builtin_bit_cast(uint32_t, d) & ~255u) | (uint32_t)i : (uint32_t)i;
+        w = dot_wave_max(w);
+        if (lane == 63) red[0][wave] = w;
+        __syncthreads();
+        w = red[0][0];
+#pragma unroll
+        for (int q = 1; q < 4; ++q) w = red[0][q] > w ? red[0][q] : w;
+        const int p = (int)(w & 255u);
         if (i == p) pd_s = d;
         __syncthreads();
         const float pd = pd_s;
-        if (k == 0) stop = pd * 0x1p-17f;
         if (!(pd > stop) || !(pd < INFINITY)) break;
         if (k == R) {
             if (pd > 8.0f * stop) rank = R + 1;
             break;
         }
+        const float ap = A[p * L + i];
         float g = 0.0f;
 #pragma unroll 8
         for (int j = 0; j < k; ++j) g = __builtin_fmaf(col[j][i], col[j][p], g);
@@ -125,102 +233,62 @@ __global__ __launch_bounds__(256) void dot_embed_kernel(const float* __restrict_
         d = i == p ? 0.0f : __builtin_fmaf(-g, g, d);
         rank = k + 1;
     }
+    if (part == 0 && i == 0) st[m] = DotStat{rank};
+    if (rank > R) return;
+    float a[ROWS];
+#pragma unroll
+    for (int r = 0; r < ROWS; ++r) a[r] = A[(part * ROWS + r) * L + i];
     __syncthreads();
     // moved to the mean of the 256 points: shorter vectors, smaller roundings
-    const int have = rank < R ? rank : R;
-    for (int k = wave; k < have; k += 4) {
+    for (int k = wave; k < rank; k += 4) {
         float s = 0.0f;
 #pragma unroll
-        for (int q = 0; q < 4; ++q) s += col[k][(i & 63) + 64 * q];
+        for (int q = 0; q < 4; ++q) s += col[k][lane + 64 * q];
 #pragma unroll
         for (int off = 32; off; off >>= 1) s += __shfl_xor(s, off);
         s *= 1.0f / 256.0f;
 #pragma unroll
-        for (int q = 0; q < 4; ++q) col[k][(i & 63) + 64 * q] -= s;
+        for (int q = 0; q < 4; ++q) col[k][lane + 64 * q] -= s;
     }
     __syncthreads();
-    float most = 0.0f;
-    float* row = U + ((size_t)blockIdx.x * L + i) * R;
-    for (int k = 0; k < R; ++k) {
-        const float v = k < have ? col[k][i] : 0.0f;
-        row[k] = v;
-        most = __builtin_fmaxf(most, __builtin_fabsf(v));
-    }
 #pragma unroll
-    for (int off = 32; off; off >>= 1) most = __builtin_fmaxf(most, __shfl_xor(most, off));
-    if ((i & 63) == 0) part_s[wave] = most;
-    __syncthreads();
-    if (i == 0)
-        st[blockIdx.x] = DotStat{rank, __builtin_fmaxf(__builtin_fmaxf(part_s[0], part_s[1]), __builtin_fmaxf(part_s[2], part_s[3]))};
-}
-
-// Block (m, part): rows 16 part .. 16 part + 15 of subspace m against all 256 points; their halves and what rounding took.
-// emb[m][x][dims / M] halves, lost[m][x] = |u - u'|^2.
-template <int M>
-__global__ __launch_bounds__(256) void dot_check_kernel(const float* __restrict__ tables, const float* __restrict__ U,
-                                                        const DotStat* __restrict__ st, DotCheck* __restrict__ check,
-                                                        _Float16* __restrict__ emb, float* __restrict__ lost,
-                                                        DotState* __restrict__ state)
-{
-    constexpr int R = 256 / M, ROWS = L / DOT_PARTS;
-    __shared__ float row_s[ROWS][R];
-    __shared__ float red_s[2][4];
-    const int m = (int)blockIdx.x / DOT_PARTS, part = (int)blockIdx.x % DOT_PARTS, j = threadIdx.x;
-    float most = 0.0f;
-    for (int i = 0; i < M; ++i) most = __builtin_fmaxf(most, st[i].most);
-    // the largest coordinate between 64 and 128
-    const uint32_t ex = (__builtin_bit_cast(uint32_t, most) >> 23) & 255u;
-    const float scale = ex > 72u && ex < 184u ? __builtin_bit_cast(float, (127u + 6u + 127u - ex) << 23) : 0.0f;
-    const int dims = dot_dims<M>(st);
-    if (blockIdx.x == 0 && j == 0) {
-        state->scale = dims > 0 ? scale : 0.0f;                  // 0: nothing to go on with
-        state->dc2[0] = state->nc2[0] = 0u;
-        state->formed[0] = 0ull;
-    }
-    if (dims == 0 || scale == 0.0f) return;
-    const float* rows = U + ((size_t)m * L + part * ROWS) * R;
-    for (int t = j; t < ROWS * R; t += 256) row_s[t / R][t % R] = rows[t];
-    float u[R];
-#pragma unroll
-    for (int k = 0; k < R; k += 4) {
-        const float4 v = *reinterpret_cast<const float4*>(U + ((size_t)m * L + j) * R + k);
-        u[k] = v.x; u[k + 1] = v.y; u[k + 2] = v.z; u[k + 3] = v.w;
-    }
+    for (int k = 0; k < R; ++k) u[k] = k < rank ? col[k][i] : 0.0f;
+    for (int t = i; t < ROWS * R; t += 256) row_s[t / R][t % R] = t % R < rank ? col[t % R][part * ROWS + t / R] : 0.0f;
     __syncthreads();
     float e0 = 0.0f, sum = 0.0f;
-#pragma unroll 4
-    for (int i = 0; i < ROWS; ++i) {
+#pragma unroll
+    for (int r = 0; r < ROWS; ++r) {
         float q = 0.0f;
 #pragma unroll
         for (int k = 0; k < R; ++k) {
-            const float t = u[k] - row_s[i][k];
+            const float t = u[k] - row_s[r][k];
             q = __builtin_fmaf(t, t, q);
         }
-        const float a = tables[((size_t)m * L + part * ROWS + i) * L + j];
         // the roundings of q itself: R + 2 of them, each at most 2^-24 of it
-        const float e = __builtin_fabsf(a - q) + q * ((float)(R + 8) * 0x1p-23f);
-        e0 = dot_worse(e0, e);
-        sum += a;
+        e0 = dot_worse(e0, __builtin_fabsf(a[r] - q) + q * ((float)(R + 8) * 0x1p-23f));
+        sum += a[r];
     }
 #pragma unroll
     for (int off = 32; off; off >>= 1) {
         e0 = dot_worse(e0, __shfl_xor(e0, off));
         sum += __shfl_xor(sum, off);
     }
-    if ((j & 63) == 0) { red_s[0][j >> 6] = e0; red_s[1][j >> 6] = sum; }
-    // the halves: r = 4, 8, 16 or 32 neighbouring lanes to a row
-    const int r = dims / M;
-    for (int at = j; at < ROWS * r; at += 256) {                 // ROWS r is a multiple of 64: whole waves
-        const int i = at / r, k = at % r;
-        const float v = row_s[i][k] * scale;
-        const _Float16 h = (_Float16)v;
-        float took = (v - (float)h) * (v - (float)h);
-        for (int off = 1; off < r; off <<= 1) took += __shfl_xor(took, off);
-        emb[((size_t)m * L + part * ROWS + i) * r + k] = h;
-        if (k == 0) lost[m * L + part * ROWS + i] = took * (1.0f + 0x1p-16f);
+    if (lane == 0) { red_s[0][wave] = e0; red_s[1][wave] = sum; }
+    // the halves: R = 8, 16 or 32 neighbouring lanes to a row
+    for (int at = i; at < ROWS * R; at += 256) {                 // ROWS R is a multiple of 64: whole waves
+        const int r = at / R, k = at % R;
+        const size_t x = (size_t)m * L + part * ROWS + r;
+        const float w = row_s[r][k] * scale;
+        const _Float16 h = (_Float16)w;
+        float took = (w - (float)h) * (w - (float)h);
+#pragma unroll
+        for (int off = 1; off < R; off <<= 1) took += __shfl_xor(took, off);
+        emb[x * R + k] = h;
+        if (k < R / 2) emb[(size_t)L * 256 + x * (R / 2) + k] = h;
+        if (k == 0) lost[x] = took * (1.0f + 0x1p-16f);
     }
     __syncthreads();
-    if (j == 0) {
+    if (i == 0) {
         for (int w = 1; w < 4; ++w) {
             e0 = dot_worse(e0, red_s[0][w]);
             sum += red_s[1][w];
@@ -308,6 +376,7 @@ __global__ __launch_bounds__(256) void dot_centers_kernel(const uint8_t* __restr
         }
     }
     const int r = dims / M, steps = dims / 16;
+    if (dims == 128) emb += (size_t)L * 256;                     // the halves of the first columns only
     const int per = 256 / dims;                                  // tiles per chunk
     char* chunk = img + (size_t)(tile / per) * DOT_CHUNK;
     for (int f = t; f < steps * 64; f += 256) {
@@ -444,7 +513,7 @@ __device__ __forceinline__ void dot_scan(const DotIn& f, int32_t* __restrict__ a
         return v4i{(int)(uint32_t)a, (int)(uint32_t)(a >> 32), (int)bytes, 0x00020000};
     };
     const v4i rs_img = rsrc_of(f.img, (uint32_t)nchunks * DOT_CHUNK);
-    const v4i rs_emb = rsrc_of(f.emb, (uint32_t)HALVES * 65536u);
+    const v4i rs_emb = rsrc_of(f.emb + (DIMS == 128 ? L * 256 : 0), (uint32_t)HALVES * 65536u);
     auto lds_of = [&](const void* p) { return (uint32_t)(uintptr_t)(__attribute__((address_space(3))) const char*)p; };
     const uint32_t buf0 = lds_of(buf), tab0 = lds_of(tab), lane16 = (uint32_t)lane * 16u;
     auto fetch = [&](int chunk, int b) {

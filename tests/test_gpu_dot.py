@@ -69,7 +69,7 @@ def _check(env, codes, centers, tables, offset=0, dist=True, shift=0, left=None,
 LEFT_TO_OTHERS = {4: None, 8: False, 16: False, 32: False}
 
 
-# with these the images leave room for the scan (from 49, 17 and 1 center on)
+# with these the images leave room for the scan (M = 8: from 17 centers on)
 MIN_K = {4: 128, 8: 64, 16: 32, 32: 33}
 
 

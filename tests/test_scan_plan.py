@@ -106,8 +106,21 @@ def test_matrix_core_scan_where_it_is_built(pq):
     """M = 4 has no scan on the matrix cores, and one that regroups its codes is not preceded by it."""
     _options(pq, variant=20)
     assert not pq.dot_scan(100_000, 4, 1000)["tried"]
-    for M, K in ((8, 48), (16, 16)):                  # the images leave no room for it
-        assert not pq.dot_scan(100_000, M, K)["tried"] and pq.dot_scan(100_000, M, K + 1)["tried"]
-    assert pq.dot_scan(100_000, 32, 1)["tried"]
+    assert not pq.dot_scan(100_000, 8, 16)["tried"] and pq.dot_scan(100_000, 8, 17)["tried"]      # the images leave no room for it
+    assert pq.dot_scan(100_000, 16, 1)["tried"] and pq.dot_scan(100_000, 32, 1)["tried"]
     assert not pq.dot_scan(5_000_000, 8, 1000)["tried"] and pq.scan_plan(5_000_000, 8, 1000)["lanes"]
     _options(pq)
+
+
+@pytest.mark.parametrize("M,N,K", [(8, 200_000, 500), (16, 45_001, 200), (16, 500_000, 100), (32, 90_001, 100), (16, 25_000, 360)])
+def test_matrix_core_scan_by_size(pq, M, N, K):
+    """Edges of the rule: one code or center less and the plain scans run alone."""
+    assert pq.dot_scan(N, M, K)["tried"] and pq.scan_plan(N, M, K)["scan"] == 1
+    assert not pq.dot_scan(N, M, K - 1)["tried"]
+    assert not pq.dot_scan(N // 2, M, K)["tried"]
+
+
+def test_one_lane_per_center_comes_before_the_matrix_core_scan(pq):
+    for M, N, K in ((32, 47_058, 1000), (16, 86_486, 4000), (8, 86_486, 4000)):
+        assert not pq.dot_scan(N, M, K)["tried"] and pq.scan_plan(N, M, K)["scan"] == 0
+        assert pq.dot_scan(N + 1, M, K)["tried"]
