@@ -43,7 +43,7 @@ struct DotState {
     uint32_t dc2[2], nc2[2];                      // per parity of the iteration: max |u_c - u'_c|^2, max |u'_c|^2, as bits
     unsigned long long formed[2];                 // likewise: fp32 distances formed
 };
-struct DotStat { int rank; };                     // per subspace: columns found (more than 256 / M: not enough)
+struct DotStat { int rank; float spread; };       // per subspace: columns found (more than 256 / M: not enough), see DOT_COARSE
 struct DotCheck { float e0, sum; };               // per part of a subspace: largest difference, sum of the entries
 
 // 128 or 256 dimensions in all (128 / M or 256 / M per subspace), 0: too many
@@ -82,7 +82,15 @@ __device__ __forceinline__ uint32_t dot_wave_max(uint32_t v)
 // Measured, us, against a factorisation of all 256 points by one block per subspace and a launch for the comparison: M = 8 with 16
 // columns 29 -> 17 (and a launch), with 32 42 -> 27; M = 16 15 -> 12; M = 32 11 -> 10.  Whole calls whose tables have more than 256
 // dimensions pay 35, 22 and 15 -> 14, 10 and 10 us at M = 8, 16 and 32.
+//
+// Tables of few values (Hamming distances and the like) are those of points, but so many centers are equally far that the fp32
+// distances cost more than the plain scans; they are left (dot_centers_kernel).  Few: in every subspace multiples of the smallest
+// positive entry among the 64, and the sum of Eq. 3 spreads by less than DOT_COARSE multiples.
+// Hamming distances of 8 bits (a sum spreads by 4 to 8), whole call, plain scan / without this / with it, us: M = 8: 156 / 250 / 179
+// at N = 1e5, K = 1000; 557 / 712 / 581 at 1e6, 1000; M = 16: 392 / 567 / 409 at 250007, 999; M = 32: 1084 / 330 to 1380 / 1100 at
+// 3e5, 1000.
 constexpr int DOT_SAMPLE = 64;
+constexpr float DOT_COARSE = 9.0f;
 
 template <int M>
 __global__ __launch_bounds__(256) void dot_points_kernel(const float* __restrict__ tables, DotStat* __restrict__ st,
@@ -96,7 +104,7 @@ __global__ __launch_bounds__(256) void dot_points_kernel(const float* __restrict
     __shared__ __attribute__((aligned(16))) float low_s[R][R], row_s[ROWS][R];       // the pivots' rows of the factor; rows to compare
     __shared__ float a0_s[L], d_s[L], inv_s[R], pd_s, red_s[2][4];
     __shared__ int piv_s[R], rank_s;
-    __shared__ uint32_t red[2][4];
+    __shared__ uint32_t red[3][4];
     const int m = (int)blockIdx.x / DOT_PARTS, part = (int)blockIdx.x % DOT_PARTS;
     const int i = threadIdx.x, lane = i & 63, wave = __builtin_amdgcn_readfirstlane(i >> 6);
     auto sample = [](int t) { return (t & 15) | ((t >> 4) << 6); };    // 64 points: four stretches of 16, a cache line of a row each
@@ -118,17 +126,27 @@ __global__ __launch_bounds__(256) void dot_points_kernel(const float* __restrict
     for (int q = 0; q < M; ++q) top = head[q] > top ? head[q] : top;
     uint32_t v = dot_wave_max(d > 0.0f ? __builtin_bit_cast(uint32_t, d) : 0u);
     uint32_t vt = dot_wave_max(__builtin_bit_cast(uint32_t, top));
+    uint32_t least = 0x7f800000u;                                // smallest positive entry
+#pragma unroll
+    for (int j = 0; j < S / 4; ++j) {
+        const uint32_t b = sam[j] > 0.0f ? __builtin_bit_cast(uint32_t, sam[j]) : 0x7f800000u;
+        least = b < least ? b : least;
+    }
+    least = ~dot_wave_max(~least);
     if (lane == 63) {
         red[0][wave] = v;
         red[1][wave] = vt;
+        red[2][wave] = least;
     }
     const bool none = __syncthreads_or(odd);
     v = red[0][0];
     vt = red[1][0];
+    least = red[2][0];
 #pragma unroll
     for (int w = 1; w < 4; ++w) {
         v = red[0][w] > v ? red[0][w] : v;
         vt = red[1][w] > vt ? red[1][w] : vt;
+        least = red[2][w] < least ? red[2][w] : least;
     }
     const float stop = __builtin_bit_cast(float, v) * 0x1p-17f;
     // points are at most 2 sqrt(top) from their mean: a power of two that brings that below 128
@@ -140,7 +158,7 @@ __global__ __launch_bounds__(256) void dot_points_kernel(const float* __restrict
         state->formed[0] = 0ull;
     }
     if (none || scale == 0.0f) {
-        if (part == 0 && i == 0) st[m] = DotStat{R + 1};
+        if (part == 0 && i == 0) st[m] = DotStat{R + 1, INFINITY};
         return;
     }
 #pragma unroll
@@ -148,7 +166,29 @@ __global__ __launch_bounds__(256) void dot_points_kernel(const float* __restrict
         const int row = wave * (S / 4) + j;
         gram_s[row][lane] = 0.5f * (a0_s[sample(row)] + a0_s[sample(lane)] - sam[j]);
     }
-    __syncthreads();
+    const float unit = 1.0f / __builtin_bit_cast(float, least);
+    float first = 0.0f, second = 0.0f;
+    bool fine = false;
+#pragma unroll
+    for (int j = 0; j < S / 4; ++j) {
+        const float x = sam[j] * unit;
+        fine = fine || !(__builtin_fabsf(x - __builtin_rintf(x)) < 1e-3f);
+        first += x;
+        second += x * x;
+    }
+    if (!__any(fine)) {
+#pragma unroll
+        for (int off = 32; off; off >>= 1) {
+            first += __shfl_xor(first, off);
+            second += __shfl_xor(second, off);
+        }
+        if (lane == 0) { red_s[0][wave] = first; red_s[1][wave] = second; }
+    }
+    float spread = INFINITY;                                     // variance of the entries, in multiples of the smallest
+    if (!__syncthreads_or(fine)) {
+        const float mean = (red_s[0][0] + red_s[0][1] + red_s[0][2] + red_s[0][3]) * (1.0f / (S * S));
+        spread = (red_s[1][0] + red_s[1][1] + red_s[1][2] + red_s[1][3]) * (1.0f / (S * S)) - mean * mean;
+    }
     if (wave == 0) {
         float f[R], ds = d_s[sample(lane)];
         int rank = 0, mine = -1;
@@ -187,7 +227,7 @@ __global__ __launch_bounds__(256) void dot_points_kernel(const float* __restrict
     __syncthreads();
     int rank = __builtin_amdgcn_readfirstlane(rank_s);
     if (rank > R) {
-        if (part == 0 && i == 0) st[m] = DotStat{R + 1};
+        if (part == 0 && i == 0) st[m] = DotStat{R + 1, INFINITY};
         return;
     }
     float u[R];
@@ -233,7 +273,7 @@ __global__ __launch_bounds__(256) void dot_points_kernel(const float* __restrict
         d = i == p ? 0.0f : __builtin_fmaf(-g, g, d);
         rank = k + 1;
     }
-    if (part == 0 && i == 0) st[m] = DotStat{rank};
+    if (part == 0 && i == 0) st[m] = DotStat{rank, spread};
     if (rank > R) return;
     float a[ROWS];
 #pragma unroll
@@ -330,11 +370,12 @@ __global__ __launch_bounds__(256) void dot_centers_kernel(const uint8_t* __restr
             }
             __syncthreads();
             if (t == 0) {
-                float e0 = 0.0f, sum = 0.0f;
+                float e0 = 0.0f, sum = 0.0f, spread = 0.0f;
                 if (usable)
-                    for (int m = 0; m < M; ++m) { e0 += e0_s[m]; sum += sum_s[m]; }
+                    for (int m = 0; m < M; ++m) { e0 += e0_s[m]; sum += sum_s[m]; spread += st[m].spread; }
                 // an infinite entry makes e0 and perhaps the sum infinite, a NaN both NaN
-                state->left = usable && e0 < INFINITY && sum < INFINITY && e0 <= DOT_E0_MAX * (sum * (1.0f / 65536.0f)) ? 0u : 1u;
+                state->left = usable && e0 < INFINITY && sum < INFINITY && e0 <= DOT_E0_MAX * (sum * (1.0f / 65536.0f)) &&
+                              !(spread < DOT_COARSE * DOT_COARSE) ? 0u : 1u;
                 state->e0 = e0;
             }
         }

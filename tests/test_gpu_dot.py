@@ -137,7 +137,24 @@ def test_tables(env, M, kind):
     elif kind == "wide":
         t = oracle.build_tables(rng.standard_normal((M, 256, 300 // M + 1)).astype(np.float32))
     kept = kind in ("lattice", "huge", "tiny")
-    _check(env, codes, centers, t, dist=kind != "integer", left=None if M == 4 or kind == "hamming" else not kept)
+    _check(env, codes, centers, t, dist=kind != "integer", left=None if M == 4 else not kept)
+
+
+@pytest.mark.parametrize("M", [8, 16, 32])
+@pytest.mark.parametrize("levels,left", [(2, True), (9, False)])
+def test_tables_of_few_values(env, M, levels, left):
+    """Codewords on a grid: left where the distances take few values in all subspaces, not where one subspace takes many."""
+    pq, oracle, _ = env
+    rng = np.random.default_rng(M + levels)
+    cw, codes, centers = _problem(rng, 2001, M, 150, 128 // M)
+    cw[:] = np.float32(0.3) * rng.integers(0, levels, cw.shape)
+    if left:
+        cw[:, :, 2:] = 0.0
+        _check(env, codes, centers, oracle.build_tables(cw), left=True)
+        cw[0] = rng.standard_normal(cw[0].shape)
+        _check(env, codes, centers, oracle.build_tables(cw))
+    else:
+        _check(env, codes, centers, oracle.build_tables(cw), left=False)
 
 
 @pytest.mark.parametrize("M", [8, 16, 32])
