@@ -1167,7 +1167,7 @@ inline bool wide_filter(int M, int asked, int variant, int64_t N, int K, const u
 {
     if ((M != 16 && M != 32) || !variant_sliding(M, variant)) return false;
     if (((uintptr_t)centers & 3) != 0 || ((int64_t)K + 63) / 64 * (M * 16384) >= (int64_t)0xfff00000) return false;
-    if (K <= 80) return false;                           // the byte tables in the histograms' room; byte tiles of 64 centers in that of 16 KB M per 16
+    if (K <= 64) return false;                           // the byte tables take 16 KB + 64 KB M of the histograms' room, M KB per center
     if (asked == 59) return true;                        // forced
     return asked == 0 && K >= wide_min_k(M, iteration);
 }

@@ -48,6 +48,8 @@ def _check(env, codes, centers, tables, variant, offset=0):
     a = torch.full((N,), -7, dtype=torch.int32, device="cuda")
     d = torch.full((N,), float("nan"), dtype=torch.float32, device="cuda")
     with _Variant(pq, variant):
+        # M = 16, 32: the byte tables need room for 65 centers
+        assert pq.scan_plan(N, M, centers.shape[0])["scan"] == (2 if centers.shape[0] > {4: 0, 8: 16, 16: 64, 32: 64}[M] else 1)
         pq.assign(torch.from_numpy(codes).cuda(), torch.from_numpy(centers).cuda(), t, assign=a, dist=d)
     ra, rd = oracle.assign(codes, centers, tables)
     np.testing.assert_array_equal(a.cpu().numpy(), ra)
@@ -57,13 +59,15 @@ def _check(env, codes, centers, tables, variant, offset=0):
         np.testing.assert_array_equal(d.cpu().numpy().view(np.uint32), rd.view(np.uint32))
 
 
-def _metric_tables(rng, M):
-    cw = rng.standard_normal((M, 256, 6)).astype(np.float32)
+def _metric_tables(rng, M, dims=6):
+    """dims: per subspace; M = 16 and 32: more than 256 in all are left by the scan on the matrix cores"""
+    cw = rng.standard_normal((M, 256, dims)).astype(np.float32)
     return np.ascontiguousarray(((cw[:, :, None] - cw[:, None]) ** 2).sum(3, dtype=np.float32))
 
 
 @pytest.mark.parametrize("M,variant", ALL)
-@pytest.mark.parametrize("N,K", [(1, 1), (7, 64), (33, 63), (2047, 65), (2048, 128), (4097, 129), (20011, 640), (8191, 2000)])
+@pytest.mark.parametrize("N,K", [(1, 1), (7, 64), (33, 63), (2047, 65), (2048, 128), (4097, 129), (2049, 66), (1025, 127), (4097, 191), (1024, 192),
+                                 (20011, 640), (8191, 2000)])
 def test_edges(env, M, variant, N, K):
     rng = np.random.default_rng(N + K + M)
     centers = rng.integers(0, 256, (K, M), dtype=np.uint8)
@@ -173,13 +177,14 @@ def test_launch_stretches(env, M, variant):
         pq.set_option("hist_kernel", 0)
 
 
-@pytest.mark.parametrize("M,N,K,iters,launch,hist", [
-    (4, 1_834_980, 1000, 3, 21, 3),          # first iteration in two stretches, second in one
-    (4, 1_500_000, 600, 5, 26, 0), (4, 700_000, 1000, 3, 26, 0),
-    (8, 4_200_000, 505, 5, 26, 0),           # placed for four lanes first, read by two later
-    (8, 4_200_000, 600, 5, 26, 0), (8, 4_200_000, 950, 3, 26, 0),
-    (16, 400_000, 1000, 5, 26, 0), (16, 400_000, 2000, 3, 26, 0), (32, 270_000, 1600, 5, 26, 0), (32, 270_000, 4100, 2, 26, 0)])
-def test_plain_iterations_then_lower_bounds(env, M, N, K, iters, launch, hist):
+@pytest.mark.parametrize("M,N,K,iters,launch,hist,dims", [
+    (4, 1_834_980, 1000, 3, 21, 3, 6),       # first iteration in two stretches, second in one
+    (4, 1_500_000, 600, 5, 26, 0, 6), (4, 700_000, 1000, 3, 26, 0, 6),
+    (8, 4_200_000, 505, 5, 26, 0, 6),        # placed for four lanes first, read by two later
+    (8, 4_200_000, 600, 5, 26, 0, 6), (8, 4_200_000, 950, 3, 26, 0, 6),
+    (16, 400_000, 1000, 5, 26, 0, 18), (16, 400_000, 2000, 3, 26, 0, 18), (32, 270_000, 1600, 5, 26, 0, 10), (32, 270_000, 4100, 2, 26, 0, 10),
+    (16, 400_000, 1000, 5, 26, 0, 6), (32, 270_000, 1600, 5, 26, 0, 6)])       # the scan on the matrix cores, in front of all of them
+def test_plain_iterations_then_lower_bounds(env, M, N, K, iters, launch, hist, dims):
     """Default fits whose first iterations run a plain scan and whose later ones the lower-bound scan: what an iteration
     takes over from the one before (regrouped codes, statistics, keys) has to be there."""
     pq, oracle, torch = env
@@ -188,8 +193,8 @@ def test_plain_iterations_then_lower_bounds(env, M, N, K, iters, launch, hist):
     codes = centers[rng.integers(0, K, N)]
     fresh = rng.random((N, M), dtype=np.float32) < 0.3
     codes[fresh] = rng.integers(0, 256, int(fresh.sum()), dtype=np.uint8)
-    tables = _metric_tables(rng, M)
-    progress(f"plain, then lower bounds: M={M} N={N} K={K}")
+    tables = _metric_tables(rng, M, dims)
+    progress(f"plain, then lower bounds: M={M} N={N} K={K} {dims} dimensions per subspace")
     try:
         pq.set_option("launch_codes_log2", launch)
         pq.set_option("hist_kernel", hist)
@@ -199,6 +204,7 @@ def test_plain_iterations_then_lower_bounds(env, M, N, K, iters, launch, hist):
         ws = torch.full((pq.workspace_bytes(N, M, K),), 0xA5, dtype=torch.uint8, device="cuda")
         pq.fit(torch.from_numpy(codes).cuda(), torch.from_numpy(tables).cuda(), cent, iters, assign=a, workspace=ws)
         torch.cuda.synchronize()
+        assert pq.dot_scan(N, M, K, ws) == (dict(tried=True, left=dims * M > 256) if M >= 16 else dict(tried=False, left=None))
     finally:
         pq.set_option("launch_codes_log2", 26)
         pq.set_option("hist_kernel", 0)
@@ -297,9 +303,9 @@ def test_giving_up_costs_little(env, M, N, K, plain, kind):
     assert out[0][0] < 2.2 * out[plain][0]                   # measured 1.0 to 1.7
 
 
-@pytest.mark.parametrize("M,N,K", [(4, 600_000, 2000), (32, 300_000, 5200)])
-def test_captured_fit(env, M, N, K):
-    """The default scans of these sizes in a captured graph, with eager work and another workspace content between replays."""
+@pytest.mark.parametrize("M,N,K,dims", [(4, 600_000, 2000, 8), (32, 300_000, 5200, 8), (32, 300_000, 5200, 12), (16, 400_000, 4000, 20)])
+def test_captured_fit(env, M, N, K, dims):
+    """dims: per subspace; more than 256 in all are left by the scan on the matrix cores.  The default scans of these sizes in a captured graph, with eager work and another workspace content between replays."""
     pq, _, torch = env
     g = torch.Generator(device="cuda")
     g.manual_seed(M)
@@ -308,7 +314,7 @@ def test_captured_fit(env, M, N, K):
     fresh = torch.randint(0, 256, (N, M), generator=g, device="cuda", dtype=torch.uint8)
     codes = torch.where(torch.rand(N, M, generator=g, device="cuda") < 0.2, fresh, codes).contiguous()
     cent0 = codes[:K].clone()
-    tables = pq.build_tables(torch.randn(M, 256, 8, generator=g, device="cuda"))
+    tables = pq.build_tables(torch.randn(M, 256, dims, generator=g, device="cuda"))
     ws = torch.empty(pq.workspace_bytes(N, M, K), dtype=torch.uint8, device="cuda")
     eager, a0 = cent0.clone(), torch.full((N,), -1, dtype=torch.int32, device="cuda")
     pq.fit(codes, tables, eager, 4, assign=a0, workspace=ws)
@@ -325,3 +331,4 @@ def test_captured_fit(env, M, N, K):
         graph.replay()
         torch.cuda.synchronize()
         assert torch.equal(cent, eager) and torch.equal(a, a0), f"replay {rep}"
+        assert pq.dot_scan(N, M, K, ws) == (dict(tried=True, left=dims * M > 256) if M >= 16 else dict(tried=False, left=None))
