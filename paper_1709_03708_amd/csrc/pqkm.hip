@@ -1143,6 +1143,20 @@ SubspaceHist subspace_hist(int64_t N, int M, int K, const Carve& c)
     return p;
 }
 
+// How the update counts its histograms: from the records of the fused iteration (`linked`), per cluster group, per group of
+// subspaces, from the indices sorted by cluster, or by global atomics.
+enum HistPath { HIST_RECORDS, HIST_OWNER, HIST_SUBSPACE, HIST_SORTED, HIST_ATOMIC };
+HistPath hist_path(int64_t N, int M, int K, const Carve& c, int force, bool linked)
+{
+    const HistPlan hp = hist_plan(N, M, K);
+    if (owner_histogram(hp, force)) {
+        if (linked) return HIST_RECORDS;
+        if (force == 0 && subspace_hist(N, M, K, c).G > 0) return HIST_SUBSPACE;
+        if (force != 0 || !sorted_histogram_pays(hp, N)) return HIST_OWNER;
+    }
+    return force != 1 && N <= (int64_t)0xffffffff && N > 0 ? HIST_SORTED : HIST_ATOMIC;
+}
+
 // The fused iteration's hand-over from the scan to the histogram: filled in by the caller (wanted, KT, ngroups),
 // completed by the assignment (produced, nwg) when the scan that ran could file its codes by cluster group.
 struct BucketLink {
@@ -1324,11 +1338,10 @@ ScanPlan scan_plan(int M, const Options& opt, int64_t N, int K, const uint8_t* c
     // A first iteration starts from the centers that share a pair of subcodes with the code, a later one from the center of
     // the one before: by code position where the keys are there, else through assign[].
     if (p.filter) p.seeded = iteration == 0 ? (K >= FILTER_PAIRS_MIN_K ? 3 : 0) : had.keys && p.reuse ? 2 : 1;
-    // the keys stay unless the update uses their room (that of the sorted path)
-    const bool keys_survive = c.state_off != c.sidx_off || (owner_histogram(hist_plan(N, M, K), opt.hist_kernel) &&
-                                                            (opt.hist_kernel != 0 ||
-                                                             (subspace_hist(N, M, K, c).G == 0 &&
-                                                              (files_records || !sorted_histogram_pays(hist_plan(N, M, K), N)))));
+    // the keys stay unless the update uses their room (that of the sorted path, and of the arrays of HIST_SUBSPACE); of the scans with
+    // keys only M = 4's 63 files records
+    const HistPath path = hist_path(N, M, K, c, opt.hist_kernel, files_records && variant == 63 && one);
+    const bool keys_survive = c.state_off != c.sidx_off || path == HIST_RECORDS || path == HIST_OWNER;
     p.leaves.iteration = iteration + 1;
     p.leaves.lanes = one ? p.lanes : 0;
     p.leaves.stats = p.filter;
@@ -1734,8 +1747,9 @@ BucketLink bucket_request(const Options& opt, int64_t N, int M, int K)
     if (N < 1) return l;
     const HistPlan hp = hist_plan(N, M, K);
     const int force = opt.hist_kernel;
-    // sorted-path sizes: the scan counts the clusters and leaves every code's rank
-    if (force == 0 && !owner_histogram(hp, force) && N <= (int64_t)0xffffffff && M <= 128) l.rank_wanted = true;
+    // Sorted-path sizes: the scan counts the clusters and leaves every code's rank.  Not where the owner path is possible and the sorted
+    // one only faster: there the keys of the lower-bound scans lie in the ranks' room.
+    if (force == 0 && !owner_histogram(hp, force) && N <= (int64_t)0xffffffff) l.rank_wanted = true;
     if (M != 4) return l;
     if (force != 0 || !owner_histogram(hp, force)) return l;     // a forced histogram kernel is used as named
     l.wanted = true;
@@ -1770,12 +1784,11 @@ pqkm_status update_impl(const Options& opt, const Carve& c, const uint8_t* codes
     // group is cheap; otherwise one global atomic per code and subspace into a zeroed histogram.
     const HistPlan hp = hist_plan(N, M, K);
     const int force = opt.hist_kernel;
-    const bool possible = owner_histogram(hp, force);
     int S = 1;
     size_t part_stride = 0;
     uint32_t* parts = hist;
-    const bool linked = possible && link && link->produced && link->KT == hp.KT && link->ngroups == (int)hp.groups;
-    const bool owner = possible && (linked || force != 0 || subspace_hist(N, M, K, c).G > 0 || !sorted_histogram_pays(hp, N));
+    const HistPath path = hist_path(N, M, K, c, force, link && link->produced && link->KT == hp.KT && link->ngroups == (int)hp.groups);
+    const bool linked = path == HIST_RECORDS;
     if (linked && M == 4 && hp.KT <= VOTE_REC_KT && link->nwg <= VOTE_REC_SEGS) {
         // the scan of this iteration filed (code, center) records by cluster group, and a vote workgroup can take
         // one group (and one subspace): it counts its histograms itself -- no histogram pass at all
@@ -1806,7 +1819,7 @@ pqkm_status update_impl(const Options& opt, const Carve& c, const uint8_t* codes
         else
             hipLaunchKernelGGL((histogram_bucket_kernel<HIST_LDS_WORDS>), dim3((unsigned)(hp.groups * S)), dim3(1024),
                                0, st, pool, bseg, link->nwg, K, hp.KT, S, parts, part_stride);
-    } else if (owner && force == 0 && subspace_hist(N, M, K, c).G > 0) {
+    } else if (path == HIST_SUBSPACE) {
         const SubspaceHist sh = subspace_hist(N, M, K, c);
         S = sh.S;
         if (S > 1) {
@@ -1815,7 +1828,7 @@ pqkm_status update_impl(const Options& opt, const Carve& c, const uint8_t* codes
         }
         hipLaunchKernelGGL(histogram_subspace_kernel, dim3((unsigned)((M + sh.G - 1) / sh.G * S)), dim3(1024), 0, st, codes, N, M,
                            assign, K, sh.G, S, parts, part_stride);
-    } else if (owner) {
+    } else if (path == HIST_OWNER) {
         S = hp.S;
         if (S > 1) {
             parts = reinterpret_cast<uint32_t*>(static_cast<char*>(ws) + c.parts_off);
@@ -1831,7 +1844,7 @@ pqkm_status update_impl(const Options& opt, const Carve& c, const uint8_t* codes
         else
             hipLaunchKernelGGL((histogram_owner_kernel<HIST_LDS_WORDS>), dim3((unsigned)(hp.groups * S)), dim3(1024),
                                0, st, codes, N, M, assign, gid, K, hp.KT, S, parts, part_stride);
-    } else if (force != 1 && N <= (int64_t)0xffffffff && N > 0 && M <= 64) {
+    } else if (path == HIST_SORTED) {
         // sorted path: counting sort of the code indices by cluster, then LDS histograms per stretch of clusters
         uint32_t *start, *sidx;
         sort_by_cluster(assign, N, K, c, static_cast<char*>(ws), &start, &sidx, st, link && link->ranked);

@@ -243,6 +243,29 @@ def test_some_workgroups_give_up(env, M, variant, hist_kernel):
         pq.set_option("hist_kernel", 0)
 
 
+@pytest.mark.parametrize("variant", [60, 63, 64])
+def test_large_update_sorts_into_the_room_of_the_keys(env, variant):
+    """M = 4 without records: the update of this size sorts the indices there, so the next iteration may not start from keys."""
+    pq, _, torch = env
+    g = torch.Generator(device="cuda")
+    g.manual_seed(variant)
+    N, M, K = 3_000_000, 4, 5000
+    T = torch.randint(0, 256, (K, M), generator=g, device="cuda", dtype=torch.uint8)
+    x = T[torch.randint(0, K, (N,), generator=g, device="cuda")]
+    x = torch.where(torch.rand(N, M, generator=g, device="cuda") < 0.3,
+                    torch.randint(0, 256, (N, M), generator=g, device="cuda", dtype=torch.uint8), x).contiguous()
+    t = pq.build_tables(torch.randn(M, 256, 8, generator=g, device="cuda"))
+    out = []
+    for v in (variant, 65):                                           # 65: plain scans
+        c = x[:K].clone()
+        with _Variant(pq, v):
+            if v == variant:
+                assert pq.scan_plan(N, M, K, 2)["seeded"] == (2 if v == 63 else 1)
+            _, a = pq.fit(x, t, c, 3)
+        out.append((a, c))
+    assert torch.equal(out[0][0], out[1][0]) and torch.equal(out[0][1], out[1][1])
+
+
 @pytest.mark.parametrize("M,N,K,late", [(32, 270_000, 1700, False), (32, 270_000, 1700, True), (16, 395_000, 2300, True), (16, 395_000, 2300, False)])
 def test_wide_scan_in_several_launches(env, M, N, K, late):
     """More than one round of workgroups, so that the tiles come in several launches: keys and counts of candidates carry over.

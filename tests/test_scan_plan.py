@@ -124,3 +124,13 @@ def test_one_lane_per_center_comes_before_the_matrix_core_scan(pq):
     for M, N, K in ((32, 47_058, 1000), (16, 86_486, 4000), (8, 86_486, 4000)):
         assert not pq.dot_scan(N, M, K)["tried"] and pq.scan_plan(N, M, K)["scan"] == 0
         assert pq.dot_scan(N + 1, M, K)["tried"]
+
+
+@pytest.mark.parametrize("variant,seeded", [(0, 2), (60, 1), (61, 1), (62, 1), (63, 2), (64, 1)])
+def test_keys_share_their_room_with_the_sorted_indices(pq, variant, seeded):
+    """Of the M = 4 scans through lower bounds only 63 files records; behind the others a large update sorts the indices into the
+    room of the keys, and the next iteration starts from assign[]."""
+    _options(pq, variant=variant)
+    assert pq.scan_plan(3_000_000, 4, 5000, 2)["seeded"] == seeded
+    _options(pq, variant=variant, hist=2)
+    assert pq.scan_plan(3_000_000, 4, 5000, 2)["seeded"] == 2
