@@ -79,7 +79,7 @@ pqkm_status pqkm_profile_read_steps(double *total_ms, int64_t *steps);
 pqkm_status pqkm_scan_plan(int64_t N, int32_t M, int32_t K, int32_t iteration, int64_t out[6]);
 
 /*
- * pqkm_dot_scan: the scan on the matrix cores, for aligned operands and the options as they are.
+ * pqkm_dot_scan: the scan on the matrix cores, for aligned operands, a call that asks for no distances, and the options as they are.
  *   workspace   that of a pqkm_assign or pqkm_fit call for these N, M, K, or NULL; with it the call waits for the device
  *   out         host, int32[2]: 0 whether the scan is tried first; 1 with a workspace, and where it is tried: whether the last
  *               assignment step there was left to the scans behind it, which pqkm_scan_plan names (1) or not (0), else -1

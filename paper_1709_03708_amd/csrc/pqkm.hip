@@ -1221,27 +1221,39 @@ struct Carried {
 };
 
 // Is the scan on the matrix cores tried first, and for how many dimensions?  Whole calls take up to 4e12 center-code pairs per
-// second at 128 dimensions (M = 8, N = 1e6, K = 4000) and half of that at 256, behind 10 to 27 us for the points, once per call, and 8 for the centers' fragments, and
-// a block of codes costs 10 to 13 us beside its centers; tables it is not for cost 10 us (M = 8: 14).  Plain scans / this, us, whole
-// calls with distances, both measured where this is taken and where it is not.
-// M = 8, 128 dimensions: 150 / 69 at N = 1e5, K = 1000; 93 / 74 at 2e5, 450; 84 / 81 at 3e5, 300; 574 / 342 at 1e6, 1000; 215 / 208 at 2e6,
-// 100.  256 dimensions: 148 / 113 at 1e5, 1000; 190 / 153 at 1.8e5, 1000; 541 / 483 at 4e5, 2000; but 103 / 123 at 2e5, 500; 184 /
-// 186 at 2.6e5, 1000; 562 / 582 at 1e6, 1000.
-// M = 16, 128 dimensions: 66 / 37 at 6e4, 200; 127 / 39 at 25100, 400; 187 / 159 at 1e6, 100; but 57 / 58 at 2e5, 100; 139 / 142 at 1e6,
-// 64; 117 / 132 at 1e6, 40.  256 dimensions: 131 / 103 at 2e5, 300; 383 / 322 at 1e6, 300; but 91 / 94 at 2e5, 200; 182 / 229 at 1e6, 100.
-// M = 32, 128 dimensions: 90 / 60 at 1e5, 100; 385 / 268 at 1e6, 100; 83 / 84 at 2e5, 64.  256: 91 / 72, 376 / 346; 85 / 103.
+// second at 128 dimensions (M = 8, N = 1e6, K = 4000) and half of that at 256, behind 10 to 27 us for the points, once per call, and
+// 8 for the centers' fragments, and a block of codes costs 10 to 13 us beside its centers; tables it is not for cost 10 us (M = 8: 14,
+// 20 where they take few values).  The distances, where they are asked for, are M table entries per code from the L2 (0.13 us per
+// 1000 codes at M = 16).  Whole calls, plain scans / this, us, where this is taken and where it is not.
+// M = 8, with distances, 128 dimensions: 150 / 69 at N = 1e5, K = 1000; 106 / 76 at 2e5, 500; 574 / 342 at 1e6, 1000; but 84 / 81 at 3e5,
+// 300; 215 / 208 at 2e6, 100.  256 dimensions: 148 / 113 at 1e5, 1000; 190 / 153 at 1.8e5, 1000; 541 / 483 at 4e5, 2000; but 103 /
+// 123 at 2e5, 500; 184 / 186 at 2.6e5, 1000; 305 / 320 at 5e5, 1000; 562 / 582 at 1e6, 1000: by the rounds of both.
+// M = 16, with distances, 128: 51 / 44 at 1e5, 130; 127 / 39 at 25100, 400; 187 / 159 at 1e6, 100; but 57 / 58 at 2e5, 100; 139 / 142
+// at 1e6, 64.  256: 66 / 46 at 6e4, 200; 131 / 103 at 2e5, 300; but 91 / 94 at 2e5, 200.  Without, 128: 41 / 39 at 1.5e5, 64; 103 /
+// 83 at 1e6, 20; but 42 / 45 at 3e5, 32.  256: 99 / 88 at 3.5e5, 103; 51 / 50 at 1e5, 130; but 137 / 145 at 1e6, 64.
+// M = 32, with, 128: 90 / 60 at 1e5, 100; 150 / 119 at 3e5, 80; but 83 / 84 at 2e5, 64.  256: 91 / 72 at 1e5, 100; 376 / 346 at 1e6, 100;
+// but 305 / 324 at 1e6, 80.  Without, 128: 100 / 65 at 5e5, 20; 70 / 49 at 2.5e5, 40.  256: 78 / 55 at 1.2e5, 80; but 72 / 78 at 2.5e5, 40.
 // Below gather_max_codes the scan with one lane per center runs and this is not asked for (M = 32, K = 1000: up to 47058 codes); the
 // sizes at which M = 8 regroups its codes are left to the lower-bound scan (up to 8.7e12 pairs per second in later iterations, 2e12 in
 // a first one), and all of M = 4 to its scans.
-int dot_scan_dims(int M, const Options& opt, int64_t N, int K, const uint8_t* centers, const Carve& c)
+int dot_scan_dims(int M, const Options& opt, int64_t N, int K, bool dist, const uint8_t* centers, const Carve& c)
 {
     if (c.dot_off == 0 || ((uintptr_t)centers & 3) != 0 || (int64_t)K > ((int64_t)1 << 22)) return 0;
     if (opt.scan_variant == 20) return 256;              // forced
     if (opt.scan_variant != 0) return 0;
     const double pairs = (double)N * K;
-    if (M == 8) return pairs < 9e7 || K < 500 ? 0 : K >= 650 && N <= (K >= 2000 ? 400000 : 200000) ? 256 : 128;
-    if (M == 16) return pairs < 9e6 || N < 25000 || K < (pairs < 5e7 ? 200 : 100) ? 0 : K >= 300 ? 256 : 128;
-    return pairs < 9e6 || K < 100 ? 0 : 256;
+    if (M == 8) {
+        if (pairs < 9e7 || K < 500) return 0;
+        // 256 dimensions, us: 45 and rounds of 256 codes per compute unit, against the rounds of the skewed scan (effective_variant)
+        const int64_t ncu = cu_count();
+        const double rounds = (double)((N + 256 * ncu - 1) / (256 * ncu)) * (13.0 + 0.0205 * K);
+        const double plain = 0.001 * K * (N <= ncu * 512 ? 139.0 : N <= ncu * 1024 ? 172.0 : N <= ncu * 1536 ? 220.0 : 263.0 * (double)((N + 2048 * ncu - 1) / (2048 * ncu)));
+        return 45.0 + rounds < 0.95 * (12.0 + plain) ? 256 : 128;
+    }
+    if (pairs < 9e6 || (M == 16 && N < 25000)) return 0;
+    if (M == 16 && dist) return K < (pairs < 5e7 ? 120 : 100) ? 0 : K >= (N < 150000 ? 200 : 300) ? 256 : 128;
+    if (M == 16) return K < (pairs < 2e7 ? 64 : 17) ? 0 : K >= 100 ? 256 : 128;
+    return K < (dist ? 80 : 16) ? 0 : K >= (dist ? 100 : 80) ? 256 : 128;
 }
 
 template <int M>
@@ -1256,9 +1268,9 @@ void launch_dot(const uint8_t* codes, int64_t N, const uint8_t* centers, int K, 
     _Float16* emb = reinterpret_cast<_Float16*>(room + d.emb_off);
     float* lost = reinterpret_cast<float*>(room + d.lost_off);
     if (!carried.dot)
-        hipLaunchKernelGGL((dot_points_kernel<M>), dim3(M * DOT_PARTS), dim3(256), 0, st, tables, stat, check, emb, lost, state);
+        hipLaunchKernelGGL((dot_points_kernel<M>), dim3(M * DOT_PARTS), dim3(256), 0, st, tables, stat, check, emb, lost, state, most_dims);
     hipLaunchKernelGGL((dot_centers_kernel<M>), dim3((unsigned)((K + DOT_TILE - 1) / DOT_TILE)), dim3(256), 0, st, centers, K, stat,
-                       check, emb, lost, state, room + d.img_off, carried.iteration, !carried.dot, most_dims);
+                       check, emb, lost, state, room + d.img_off, carried.iteration, !carried.dot);
     EventPair ev{};
     const bool prof = (opt.profile & 1) && log_begin(g_scan_log, st, &ev);
     const DotIn in{codes, centers, tables, stat, emb, lost, room + d.img_off, state, N, K, carried.iteration};
@@ -1291,7 +1303,7 @@ struct ScanPlan {
 // Which scan an assignment step runs, in which stretches, and what it can take over from the iteration before: host
 // arithmetic, without a look at the device's memory.
 ScanPlan scan_plan(int M, const Options& opt, int64_t N, int K, const uint8_t* codes, const uint8_t* centers, bool files_records,
-                   const Carve& c, const Carried& had)
+                   bool dist, const Carve& c, const Carried& had)
 {
     ScanPlan p{};
     const int iteration = had.iteration;
@@ -1316,7 +1328,7 @@ ScanPlan scan_plan(int M, const Options& opt, int64_t N, int K, const uint8_t* c
     p.sliding = variant_sliding(M, variant);
     // M = 16, 32: the lower-bound scan of every stretch in front of the sliding-window scan, which runs where it gave up
     p.wide = p.sliding && wide_filter(M, asked, variant, N, K, centers, iteration);
-    p.dot = p.grouped ? 0 : dot_scan_dims(M, opt, N, K, centers, c);
+    p.dot = p.grouped ? 0 : dot_scan_dims(M, opt, N, K, dist, centers, c);
     p.lanes = !p.grouped ? 0 : variant_two_lane(M, variant) ? 2 : 4;
     int64_t per_launch = opt.launch_codes;
     // a little below the limit: with its padding a launch of exactly 2^26 codes needs one workgroup more than
@@ -1360,7 +1372,7 @@ pqkm_status assign_tiled(const uint8_t* codes, int64_t N, const uint8_t* centers
     int64_t total = ntiles * (int64_t)(TILE_BYTES / 4);
     const int iteration = carried.iteration;
     const bool files_records = M == 4 && link && link->wanted && N <= GROUP_CHUNK_MAX - 16384 && c.bseg_off != c.pool_off;
-    const ScanPlan plan_of = scan_plan(M, opt, N, K, codes, centers, files_records, c, carried);
+    const ScanPlan plan_of = scan_plan(M, opt, N, K, codes, centers, files_records, dist != nullptr, c, carried);
     const int variant = plan_of.variant;
     const bool filter = plan_of.filter, wide = plan_of.wide, grouped = plan_of.grouped, sliding = plan_of.sliding;
     const int64_t per_launch = plan_of.per_launch;
@@ -2312,7 +2324,7 @@ pqkm_status pqkm_scan_plan(int64_t N, int32_t M, int32_t K, int32_t iteration, i
     Carried carried;
     ScanPlan p{};
     for (int it = 0; it <= iteration; ++it) {
-        p = scan_plan(M, opt, N, K, nullptr, nullptr, files_records, c, carried);
+        p = scan_plan(M, opt, N, K, nullptr, nullptr, files_records, false, c, carried);
         carried = p.leaves;
     }
     out[0] = p.filter || p.wide ? 2 : 1;
@@ -2335,7 +2347,7 @@ pqkm_status pqkm_dot_scan(int64_t N, int32_t M, int32_t K, const void* workspace
     const Carve c = carve(N, M, K);
     const BucketLink link = bucket_request(opt, N, M, K);
     const bool files_records = M == 4 && link.wanted && N <= GROUP_CHUNK_MAX - 16384 && c.bseg_off != c.pool_off;
-    out[0] = scan_plan(M, opt, N, K, nullptr, nullptr, files_records, c, Carried{}).dot ? 1 : 0;
+    out[0] = scan_plan(M, opt, N, K, nullptr, nullptr, files_records, false, c, Carried{}).dot ? 1 : 0;
     if (!workspace || !out[0]) return PQKM_OK;
     uint32_t left = 0;
     if (hipDeviceSynchronize() != hipSuccess ||

@@ -43,7 +43,7 @@ struct DotState {
     uint32_t dc2[2], nc2[2];                      // per parity of the iteration: max |u_c - u'_c|^2, max |u'_c|^2, as bits
     unsigned long long formed[2];                 // likewise: fp32 distances formed
 };
-struct DotStat { int rank; float spread; };       // per subspace: columns found (more than 256 / M: not enough), see DOT_COARSE
+struct DotStat { int rank; float spread; };       // per subspace: columns found (more than 256 / M: too many), see DOT_COARSE
 struct DotCheck { float e0, sum; };               // per part of a subspace: largest difference, sum of the entries
 
 // 128 or 256 dimensions in all (128 / M or 256 / M per subspace), 0: too many
@@ -77,7 +77,7 @@ __device__ __forceinline__ uint32_t dot_wave_max(uint32_t v)
 // The factorisation is serial in its columns, and a column of all 256 points costs two barriers and a row of the tables, 0.9 us.  So
 // one wave first factorises the Gram matrix of 64 of the points, a row of it per lane and the factor in registers: where they
 // need too many columns, so do all points, and the block is done; else their pivots serve all points, whose rows then come in one go
-// (forward substitution), and only columns that the 64 do not span are found one by one.
+// (forward substitution), and only columns that the 64 do not span are found one by one.  No more than most_dims / M columns.
 // emb[m][x][256 / M] halves and, behind them, the same with the first half of the columns; lost[m][x] = |u - u'|^2.
 // Measured, us, against a factorisation of all 256 points by one block per subspace and a launch for the comparison: M = 8 with 16
 // columns 29 -> 17 (and a launch), with 32 42 -> 27; M = 16 15 -> 12; M = 32 11 -> 10.  Whole calls whose tables have more than 256
@@ -86,16 +86,16 @@ __device__ __forceinline__ uint32_t dot_wave_max(uint32_t v)
 // Tables of few values (Hamming distances and the like) are those of points, but so many centers are equally far that the fp32
 // distances cost more than the plain scans; they are left (dot_centers_kernel).  Few: in every subspace multiples of the smallest
 // positive entry among the 64, and the sum of Eq. 3 spreads by less than DOT_COARSE multiples.
-// Hamming distances of 8 bits (a sum spreads by 4 to 8), whole call, plain scan / without this / with it, us: M = 8: 156 / 250 / 179
-// at N = 1e5, K = 1000; 557 / 712 / 581 at 1e6, 1000; M = 16: 392 / 567 / 409 at 250007, 999; M = 32: 1084 / 330 to 1380 / 1100 at
-// 3e5, 1000.
+// Hamming distances of 8 bits, whole call, plain scan / without this / with it, us: M = 8 (a sum spreads by 4): 156 / 250 / 177 at N =
+// 1e5, K = 1000; 557 / 712 / 582 at 1e6, 1000; M = 16 (5.7): 392 / 567 / 405 at 250007, 999.  M = 32 (8) is tried: 1072 / 337 where
+// codes are close to centers, 1091 / 1250 where they are not, at 3e5, 1000.
 constexpr int DOT_SAMPLE = 64;
-constexpr float DOT_COARSE = 9.0f;
+constexpr float DOT_COARSE = 6.0f;
 
 template <int M>
 __global__ __launch_bounds__(256) void dot_points_kernel(const float* __restrict__ tables, DotStat* __restrict__ st,
                                                          DotCheck* __restrict__ check, _Float16* __restrict__ emb,
-                                                         float* __restrict__ lost, DotState* __restrict__ state)
+                                                         float* __restrict__ lost, DotState* __restrict__ state, int most_dims)
 {
     static_assert(M >= 8, "the columns of a lane are registers");
     constexpr int R = 256 / M, S = DOT_SAMPLE, ROWS = L / DOT_PARTS;
@@ -200,7 +200,7 @@ __global__ __launch_bounds__(256) void dot_points_kernel(const float* __restrict
             const int p = __builtin_amdgcn_readlane((int)w, 63) & 63;
             const float pd = __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, ds), p));
             if (!(pd > stop) || !(pd < INFINITY)) break;
-            if (k == R) {
+            if (k == R || (k == R / 2 && most_dims == 128)) {    // no more columns
                 if (pd > 8.0f * stop) rank = R + 1;
                 break;
             }
@@ -245,8 +245,9 @@ __global__ __launch_bounds__(256) void dot_points_kernel(const float* __restrict
             d = i == x ? 0.0f : __builtin_fmaf(-u[k], u[k], d);
         }
     __syncthreads();
+    const int columns = most_dims / M;
 #pragma unroll 1
-    for (int k = rank; k <= R; ++k) {
+    for (int k = rank; k <= columns; ++k) {
         // the largest of what is left, with its row in the low bits; negative and NaN count as 0
         uint32_t w = d > 0.0f ? (__builtin_bit_cast(uint32_t, d) & ~255u) | (uint32_t)i : (uint32_t)i;
         w = dot_wave_max(w);
@@ -260,7 +261,7 @@ __global__ __launch_bounds__(256) void dot_points_kernel(const float* __restrict
         __syncthreads();
         const float pd = pd_s;
         if (!(pd > stop) || !(pd < INFINITY)) break;
-        if (k == R) {
+        if (k == columns) {
             if (pd > 8.0f * stop) rank = R + 1;
             break;
         }
@@ -347,14 +348,14 @@ __global__ __launch_bounds__(256) void dot_centers_kernel(const uint8_t* __restr
                                                           const DotStat* __restrict__ st, const DotCheck* __restrict__ check,
                                                           const _Float16* __restrict__ emb, const float* __restrict__ lost,
                                                           DotState* __restrict__ state, char* __restrict__ img, int iteration,
-                                                          bool decide, int most_dims)
+                                                          bool decide)
 {
     __shared__ float sq_s[32][DOT_TILE], lost_s[8][DOT_TILE];
     __shared__ float e0_s[M], sum_s[M];
     __shared__ uint32_t word_s[DOT_TILE], dup_s[DOT_TILE];
     const int tile = (int)blockIdx.x, t = threadIdx.x;
     const int dims = dot_dims<M>(st);
-    const bool usable = dims > 0 && dims <= most_dims && state->scale > 0.0f;
+    const bool usable = dims > 0 && state->scale > 0.0f;
     if (decide) {
         if (blockIdx.x == 0) {
             if (t < M && usable) {

@@ -112,12 +112,12 @@ def test_matrix_core_scan_where_it_is_built(pq):
     _options(pq)
 
 
-@pytest.mark.parametrize("M,N,K", [(8, 200_000, 500), (16, 45_001, 200), (16, 500_000, 100), (32, 90_001, 100), (16, 25_000, 360)])
+@pytest.mark.parametrize("M,N,K", [(8, 180_000, 500), (16, 140_626, 64), (16, 1_176_471, 17), (32, 562_501, 16), (16, 25_000, 360)])
 def test_matrix_core_scan_by_size(pq, M, N, K):
     """Edges of the rule: one code or center less and the plain scans run alone."""
     assert pq.dot_scan(N, M, K)["tried"] and pq.scan_plan(N, M, K)["scan"] == 1
     assert not pq.dot_scan(N, M, K - 1)["tried"]
-    assert not pq.dot_scan(N // 2, M, K)["tried"]
+    assert not pq.dot_scan(N - 2, M, K)["tried"]
 
 
 def test_one_lane_per_center_comes_before_the_matrix_core_scan(pq):
