@@ -1223,8 +1223,8 @@ struct Carried {
 // Is the scan on the matrix cores tried first, and for how many dimensions?  Whole calls take up to 4e12 center-code pairs per
 // second at 128 dimensions (M = 8, N = 1e6, K = 4000) and half of that at 256, behind 10 to 27 us for the points, once per call, and
 // 8 for the centers' fragments, and a block of codes costs 10 to 13 us beside its centers; tables it is not for cost 10 us (M = 8: 14,
-// 20 where they take few values).  The distances, where they are asked for, are M table entries per code from the L2 (0.13 us per
-// 1000 codes at M = 16).  Whole calls, plain scans / this, us, where this is taken and where it is not.
+// 20 where they take few values).  The distances, where they are asked for, are M table entries per code from the L2 (18 us at M =
+// 16, N = 250007).  Whole calls, plain scans / this, us, where this is taken and where it is not.
 // M = 8, with distances, 128 dimensions: 150 / 69 at N = 1e5, K = 1000; 106 / 76 at 2e5, 500; 574 / 342 at 1e6, 1000; but 84 / 81 at 3e5,
 // 300; 215 / 208 at 2e6, 100.  256 dimensions: 148 / 113 at 1e5, 1000; 190 / 153 at 1.8e5, 1000; 541 / 483 at 4e5, 2000; but 103 /
 // 123 at 2e5, 500; 184 / 186 at 2.6e5, 1000; 305 / 320 at 5e5, 1000; 562 / 582 at 1e6, 1000: by the rounds of both.

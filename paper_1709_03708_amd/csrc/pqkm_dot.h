@@ -6,8 +6,9 @@
 //
 // Nothing is assumed about the tables.  A call first looks for such points: per subspace a pivoted Cholesky factorisation
 // of the Gram matrix (A[0][i] + A[0][j] - A[i][j]) / 2, at most 256 / M columns, moved to the points' mean.  Every entry of the
-// tables is then compared with the points (both in dot_points_kernel): `e0` bounds what an entry sum of Eq. 3 can differ by.  Tables that no such points describe (more dimensions, not symmetric, infinities, NaN) set `left`, and the
-// scans that are launched behind do the work as if this one did not exist; they end at once where it is 0.
+// tables is then compared with the points (both in dot_points_kernel): `e0` bounds what an entry sum of Eq. 3 can differ by.
+// Tables that no such points describe (more dimensions, not symmetric, infinities, NaN) set `left`, and the scans that are launched
+// behind do the work as if this one did not exist; they end at once where it is 0.
 //
 // The bound.  With u' the points rounded to half precision (times a power of two, all below in those units), d_x = |u_x - u'_x|,
 // d_c likewise (the largest of the centers), delta = d_x + d_c, v_c = |u'_c|^2 - 2 u'_x.u'_c from the matrix cores,
@@ -530,13 +531,15 @@ __device__ __forceinline__ float dot_distance(const float* __restrict__ tables, 
 // list together; where there is a fourth block it forms all K.  A workgroup whose codes need so many that the plain scans are cheaper (ties
 // everywhere) sets `left` and ends, and so do the others when they next look.
 //
-// Bound by the matrix cores: 8 instructions per 32 codes x 32 centers x 128 dimensions, 50 to 55 clocks each where the chip is at its
-// power limit (32 with zeros as operands).  Two columns per wave, so that a fragment read from LDS serves two instructions;
-// reads run four steps ahead (two in flight: 1.2 times the time).  With few centers a block's own cost shows: codes, gather and
-// two barriers with the distances between, 10 to 13 us per 512 codes, so the next block's codes are loaded ahead.
-// Measured, plain or lower-bound scan -> this with all its launches, us: M = 16, N = 250007, K = 999, with distances: 355 -> 115;
-// M = 8, N = 1e6, K = 1000: 569 -> 318; M = 16, N = 3e5, K = 3000: 1282 -> 300; M = 32, N = 1e5, K = 3000: 1986 -> 158.  The kernel
-// itself at M = 8, N = 5e5, K = 5000: 560 us, 4.5e12 pairs per second, of which the matrix instructions alone take 440.
+// Per tile and 32 codes 8 matrix instructions (128 dimensions) of 32 clocks and about 40 vector instructions of 4.  Two waves per
+// SIMD, whose two kinds of instruction overlap little: at M = 8, N = 5e5, K = 5000 the matrix cores are busy 46 per cent of the
+// time and the vector units 28, at 2.0 GHz (the clock falls from 2.4 under this load); LDS reads 18.  Two columns per wave, so that
+// a fragment read from LDS serves two instructions; reads run four steps ahead (two in flight: 1.2 times the time).  With few centers
+// a block's own cost shows: codes, gather and two barriers with the distances between, 10 to 13 us per 512 codes, so the next block's
+// codes are loaded ahead.
+// Measured, plain or lower-bound scan -> this with all its launches, us, with distances: M = 16, N = 250007, K = 999: 355 -> 118;
+// M = 8, N = 1e6, K = 1000: 574 -> 342; M = 16, N = 4e5, K = 5000: 1752 -> 680; M = 32, N = 3e5, K = 6000: 6850 -> 719.  The kernel
+// itself at M = 8, N = 5e5, K = 5000, without distances: 670 to 730 us, 3.4 to 3.7e12 pairs per second.
 // ---------------------------------------------------------------------------------------------
 template <int M, int DIMS, int CT>
 __device__ __forceinline__ void dot_scan(const DotIn& f, int32_t* __restrict__ assign, float* __restrict__ dist, float4* tab,

@@ -796,8 +796,8 @@ __global__ __launch_bounds__(THREADS) void assign_filter_kernel(int64_t N, const
 // phase is all there is room to load ahead); keys and the count of candidates carry over from one launch to the next.  A
 // workgroup that has used up its budget sets *gave_up, those of later launches stop at once when they see it, and the plain
 // scan that is launched behind this one does all the work.
-// A phase of 1024 codes is short (0.8 us of work in 1.9 us): its barrier and the start of its reads are what bounds it, and
-// more codes do not fit the registers.
+// A phase of 1024 codes is short (0.8 us of work in 1.9 us): either its fill (64 KB per compute unit in that time are 8.8 TB/s out
+// of the L2) or its barrier and the start of its reads bound it, and more codes do not fit the registers.
 // Measured against the sliding-window scan, M = 32, N = 1e6, K = 1e4: 16.4 -> 12.4 ms in a first iteration, 12.1 and
 // 9.5 ms in later ones.
 // ---------------------------------------------------------------------------------------------

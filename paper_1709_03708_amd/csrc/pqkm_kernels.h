@@ -3631,7 +3631,8 @@ __global__ __launch_bounds__(256) void seg_place_kernel(const int32_t* __restric
 // group has one, which stores them.  The first workgroups of the grid take the first share of every group, the others what
 // seg_zero_kernel lists (a grid of groups x shares would be nearly all empty workgroups of 128 KB of LDS: 60 to 80 us at
 // K = 30000).  Bound by the LDS atomics and by the rounds of workgroups: 64 KB of counters each, two workgroups per compute unit.
-// Measured, 2e6 codes of a mixture, M = 8, K = 5000: 98 us with 128 KB and the subspaces in the same order in all lanes, now 52 us.
+// Measured, 2e6 codes of a mixture, M = 8, K = 5000: 98 us with 128 KB and the subspaces in the same order in all lanes, 52 with 64 KB and
+// words turned by lane one by one, now 40.
 // The counters of a code that is read as words (M a multiple of 4), starting with another subspace in each lane: lanes of one
 // cluster often hold the same subcode, and 64 of them adding to one LDS word are served one after the other.  Lane l takes the
 // bytes of a word from l mod 4 on, the words of a chunk of CW from (l / 4) mod CW on and the chunks of a code from l / (4 CW) on, so
