@@ -169,7 +169,7 @@ __global__ __launch_bounds__(256) void dot_points_kernel(const float* __restrict
     }
     const float unit = 1.0f / __builtin_bit_cast(float, least);
     float first = 0.0f, second = 0.0f;
-    bool fine = false;
+    bool fine = least == 0x7f800000u;                            // nothing positive among them: says nothing
 #pragma unroll
     for (int j = 0; j < S / 4; ++j) {
         const float x = sam[j] * unit;

@@ -141,6 +141,35 @@ def test_tables(env, M, kind):
 
 
 @pytest.mark.parametrize("M", [8, 16, 32])
+@pytest.mark.parametrize("kind", ["sample spans half", "sample is one point", "too many outside the sample", "repeated", "scales",
+                                  "one subspace", "ranks"])
+def test_points(env, M, kind):
+    """Codewords 0..15, 64..79, 128..143, 192..207 are factorised first; what they do not span is found afterwards."""
+    pq, oracle, _ = env
+    rng = np.random.default_rng(M + len(kind))
+    r = 256 // M
+    first = np.arange(256) % 64 < 16
+    cw, codes, centers = _problem(rng, 2003, M, 140, r + 1 if kind.startswith("too many") else r)
+    if kind == "sample spans half":
+        cw[:, first, r // 2:] = 0.0
+    elif kind == "sample is one point":
+        cw[:, first] = cw[:, :1]
+    elif kind == "too many outside the sample":
+        cw[:, first, r // 2:] = 0.0
+    elif kind == "repeated":
+        cw[:, 40:] = cw[:, :216] + 0.0
+        cw[:, 200:] = cw[:, 3:4]
+    elif kind == "scales":
+        cw *= (np.float32(2.0) ** (np.arange(M) % 5 - 2).astype(np.float32))[:, None, None]
+    elif kind == "one subspace":
+        cw[1:] = 0.0
+    elif kind == "ranks":
+        for m in range(M):
+            cw[m, :, 1 + m % r:] = 0.0
+    _check(env, codes, centers, oracle.build_tables(cw), left=None if kind == "one subspace" else kind.startswith("too many"))
+
+
+@pytest.mark.parametrize("M", [8, 16, 32])
 @pytest.mark.parametrize("levels,left", [(2, True), (9, False)])
 def test_tables_of_few_values(env, M, levels, left):
     """Codewords on a grid: left where the distances take few values in all subspaces, not where one subspace takes many."""
