@@ -1228,11 +1228,13 @@ struct Carried {
 // M = 8, with distances, 128 dimensions: 150 / 69 at N = 1e5, K = 1000; 106 / 76 at 2e5, 500; 574 / 342 at 1e6, 1000; but 84 / 81 at 3e5,
 // 300; 215 / 208 at 2e6, 100.  256 dimensions: 148 / 113 at 1e5, 1000; 190 / 153 at 1.8e5, 1000; 541 / 483 at 4e5, 2000; but 103 /
 // 123 at 2e5, 500; 184 / 186 at 2.6e5, 1000; 305 / 320 at 5e5, 1000; 562 / 582 at 1e6, 1000: by the rounds of both.
-// M = 16, with distances, 128: 51 / 44 at 1e5, 130; 127 / 39 at 25100, 400; 187 / 159 at 1e6, 100; but 57 / 58 at 2e5, 100; 139 / 142
-// at 1e6, 64.  256: 66 / 46 at 6e4, 200; 131 / 103 at 2e5, 300; but 91 / 94 at 2e5, 200.  Without, 128: 41 / 39 at 1.5e5, 64; 103 /
-// 83 at 1e6, 20; but 42 / 45 at 3e5, 32.  256: 99 / 88 at 3.5e5, 103; 51 / 50 at 1e5, 130; but 137 / 145 at 1e6, 64.
-// M = 32, with, 128: 90 / 60 at 1e5, 100; 150 / 119 at 3e5, 80; but 83 / 84 at 2e5, 64.  256: 91 / 72 at 1e5, 100; 376 / 346 at 1e6, 100;
-// but 305 / 324 at 1e6, 80.  Without, 128: 100 / 65 at 5e5, 20; 70 / 49 at 2.5e5, 40.  256: 78 / 55 at 1.2e5, 80; but 72 / 78 at 2.5e5, 40.
+// M = 16, with distances, 128: 51 / 44 at 1e5, 130; 127 / 39 at 25100, 400; 187 / 159 at 1e6, 100; 205 / 177 at 1.2e6, 72; but 57 / 58
+// at 2e5, 100; 139 / 142 at 1e6, 64.  256: 66 / 46 at 6e4, 200; 131 / 103 at 2e5, 300; but 91 / 94 at 2e5, 200.  Without distances, 128:
+// 41 / 39 at 1.5e5, 64; 103 / 83 at 1e6, 20; 74 / 66 at 6e5, 25; but 42 / 45 at 3e5, 32.  256: 99 / 88 at 3.5e5, 103; 51 / 50 at 1e5,
+// 130; 169 / 160 at 1e6, 90; but 137 / 145 at 1e6, 64.
+// M = 32, with, 128: 90 / 60 at 1e5, 100; 150 / 119 at 3e5, 80; 265 / 244 at 1e6, 64; but 83 / 84 at 2e5, 64.  256: 91 / 72 at 1e5, 100; 75
+// / 69 at 1e5, 80; 376 / 346 at 1e6, 100; but 305 / 324 at 1e6, 80.  Without, 128: 100 / 65 at 5e5, 20; 70 / 49 at 2.5e5, 40.  256: 78 / 55 at 1.2e5, 80; 224 /
+// 165 at 1e6, 40; 96 / 73 at 3e5, 31; 199 / 152 at 6.7e5, 54 (but 269 / 441 at 1e6, 64, left, where no code lies near a center).
 // Below gather_max_codes the scan with one lane per center runs and this is not asked for (M = 32, K = 1000: up to 47058 codes); the
 // sizes at which M = 8 regroups its codes are left to the lower-bound scan (up to 8.7e12 pairs per second in later iterations, 2e12 in
 // a first one), and all of M = 4 to its scans.
@@ -1251,9 +1253,10 @@ int dot_scan_dims(int M, const Options& opt, int64_t N, int K, bool dist, const 
         return 45.0 + rounds < 0.95 * (12.0 + plain) ? 256 : 128;
     }
     if (pairs < 9e6 || (M == 16 && N < 25000)) return 0;
-    if (M == 16 && dist) return K < (pairs < 5e7 ? 120 : 100) ? 0 : K >= (N < 150000 ? 200 : 300) ? 256 : 128;
-    if (M == 16) return K < (pairs < 2e7 ? 64 : 17) ? 0 : K >= 100 ? 256 : 128;
-    return K < (dist ? 80 : 16) ? 0 : K >= (dist ? 100 : 80) ? 256 : 128;
+    if (M == 16 && dist) return K < (pairs < 5e7 ? 110 : 70) ? 0 : K >= (N < 150000 ? 180 : 300) ? 256 : 128;
+    if (M == 16) return K < (pairs < 1.3e7 ? 64 : 17) ? 0 : K >= 80 ? 256 : 128;
+    if (dist) return K < (pairs < 1.6e7 ? 80 : 64) ? 0 : K >= (N < 400000 ? 80 : 100) ? 256 : 128;
+    return K < 16 ? 0 : 256;
 }
 
 template <int M>

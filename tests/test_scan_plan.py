@@ -112,7 +112,7 @@ def test_matrix_core_scan_where_it_is_built(pq):
     _options(pq)
 
 
-@pytest.mark.parametrize("M,N,K", [(8, 180_000, 500), (16, 140_626, 64), (16, 1_176_471, 17), (32, 562_501, 16), (16, 25_000, 360)])
+@pytest.mark.parametrize("M,N,K", [(8, 180_000, 500), (16, 140_626, 64), (16, 764_706, 17), (32, 562_501, 16), (16, 25_000, 360)])
 def test_matrix_core_scan_by_size(pq, M, N, K):
     """Edges of the rule: one code or center less and the plain scans run alone."""
     assert pq.dot_scan(N, M, K)["tried"] and pq.scan_plan(N, M, K)["scan"] == 1
