@@ -1785,6 +1785,25 @@ inline bool vote_counts_codes(int64_t N, int M, int K)
     return N >= 1 && N <= 40000 && blocks <= (N <= 20000 ? 512 : 256);
 }
 
+// Few clusters: rows straight from the L2 (vote_few_kernel), while they are fewer than 550000 in all (a cluster has at most 256 non-zero bins
+// per subspace, and no more than it has members).  vote_kernel / this, us: M = 4: 13.1 / 6.9 at N = 1e4, K = 100, 23.4 / 13.5 at 1.28e6, 100,
+// 21.0 / 17.8 at 2e5, 300, but 16.8 / 20.7 at 2e5, 1000; M = 8: 23.5 / 21.8 at 1e6, 256, 21.0 / 16.6 at 4e4, 1000, but 21.2 / 24.1 at 2e5,
+// 300; M = 16: 19.6 / 15.8 at 4e4, 100; M = 32: 45 / 32 at 1e4, 1000, 25.5 / 26.2 at 4e4, 100.
+inline bool vote_few(int64_t N, int M, int K)
+{
+    const int64_t rows = (int64_t)K * M * L < N * M ? (int64_t)K * M * L : N * M;
+    return N >= 1 && rows <= 550000 && K <= 65536;
+}
+
+// Few codes as well: each of its workgroups counts its cluster from all codes, while one round of them covers all.  Whole update, us, where
+// vote_kernel counts or a histogram is formed first / so: M = 4: 16.3 / 10.4 at N = 1e4, K = 100, 17.9 / 11.6 at 2e4, 256, 27.3 / 22.5 at
+// 4e4, 100, but 31.8 / 35.0 at 8e4, 100; M = 8: 27.5 / 22.9 at 4e4, 100; M = 6, byte by byte: 16.6 / 13.6 at 1e4, 100, but 20.8 / 21.4 at 2e4, 100.
+inline bool vote_few_counts_codes(int64_t N, int M, int K, const uint8_t* codes)
+{
+    const bool words = (M & 3) == 0 && ((uintptr_t)codes & 3) == 0;
+    return N >= 1 && N <= (words ? 40000 : 12000) && (int64_t)K * ((M + 3) / 4) <= cu_count();
+}
+
 pqkm_status update_impl(const Options& opt, const Carve& c, const uint8_t* codes, int64_t N, int M,
                         const int32_t* assign, int K, const float* tables, uint8_t* centers, uint32_t* hist,
                         uint32_t* counts, void* ws, hipStream_t st, const BucketLink* link = nullptr)
@@ -1812,6 +1831,11 @@ pqkm_status update_impl(const Options& opt, const Carve& c, const uint8_t* codes
         const uint2* bseg = reinterpret_cast<const uint2*>(static_cast<char*>(ws) + c.bseg_off);
         hipLaunchKernelGGL((vote_kernel<VOTE_RECORDS>), dim3((unsigned)(hp.groups * M)), dim3(VOTE_THREADS), 0, st, hist, hist, 1,
                            (size_t)0, counts, K, M, hp.KT, tables, centers, VoteRecords{pool, bseg, link->nwg, nullptr, nullptr, 0});
+        return launched();
+    }
+    if (!linked && force == 0 && vote_few_counts_codes(N, M, K, codes)) {
+        hipLaunchKernelGGL((vote_few_kernel<VOTE_CODES>), dim3((unsigned)((int64_t)K * ((M + 3) / 4))), dim3(VOTE_FEW_THREADS), 0, st, hist, hist, 1,
+                           (size_t)0, counts, K, M, tables, centers, VoteRecords{nullptr, nullptr, 0, codes, assign, N});
         return launched();
     }
     if (!linked && force == 0 && vote_counts_codes(N, M, K)) {
@@ -1895,6 +1919,11 @@ pqkm_status update_impl(const Options& opt, const Carve& c, const uint8_t* codes
             hipLaunchKernelGGL(histogram_atomic_kernel, dim3((unsigned)((cnt + 255) / 256)), dim3(256), 0, st,
                                codes + n0 * M, cnt, M, assign + n0, K, hist);
         }
+    }
+    if (vote_few(N, M, K)) {
+        hipLaunchKernelGGL((vote_few_kernel<VOTE_PARTS>), dim3((unsigned)((int64_t)K * ((M + 3) / 4))), dim3(256), 0, st, hist, parts, S, part_stride,
+                           counts, K, M, tables, centers, VoteRecords{});
+        return launched();
     }
     // vote: one workgroup per (subspace, CW clusters); about a thousand workgroups, at least one cluster per wave
     int64_t cw = ((int64_t)K * M + 1023) / 1024;

@@ -4329,6 +4329,145 @@ __global__ __launch_bounds__(VOTE_THREADS) void vote_kernel(uint32_t* __restrict
 }
 
 // ---------------------------------------------------------------------------------------------
+// Eq. 8 for few clusters: a workgroup serves one cluster and four subspaces, a wave one subspace with four candidates per lane.
+// vote_kernel's workgroups are few then, and each fetches 256 KB of table for the rows of sixteen histograms; here the row of
+// every non-zero bin comes straight from the L2, up to 32 rows in flight per wave, and rows that no bin asks for stay there.
+// A row costs its wave about eight vector instructions (the bin's row and count from their lane, an address, four fmaf).
+// Bound by the L2's latency with one wave per SIMD (33 ns per row) and by its bandwidth with many (K = 1000, M = 4, 117 bins: 479 MB at 29
+// TB/s).  Measured, M = 4, K = 100, vote_kernel -> this: 74 bins 13.1 -> 6.9 us, 256 bins 23.4 -> 13.5; with its own counting, 1e4 codes:
+// 16.3 -> 10.4.  One candidate per lane and four waves per subspace: 10.3 instead of 6.9 (issue bound); 16 rows without 16 ahead: 8.2.
+// VOTE_CODES: VOTE_FEW_THREADS threads count the cluster's bins first, of which four waves go on.
+// ---------------------------------------------------------------------------------------------
+constexpr int VOTE_FEW_ROWS = 16;        // rows asked for together, and as many ahead of them
+constexpr int VOTE_FEW_THREADS = 512;    // 1024 would leave 128 registers, too few for the rows
+
+template <VoteFrom FROM>
+__global__ __launch_bounds__(FROM == VOTE_CODES ? VOTE_FEW_THREADS : 256) void vote_few_kernel(
+    uint32_t* __restrict__ hist, const uint32_t* __restrict__ parts, int S, size_t part_stride, uint32_t* __restrict__ counts,
+    int K, int M, const float* __restrict__ tables, uint8_t* __restrict__ centers, VoteRecords vr)
+{
+    static_assert(FROM != VOTE_RECORDS, "from partial histograms or from all codes");
+    __shared__ uint32_t bins[FROM == VOTE_CODES ? 4 * L : 1];
+    __shared__ uint2 list[4 * L];            // per wave the non-zero bins in ascending order: byte offset of the row, count as a float
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int quads = (M + 3) / 4;
+    const int k = (int)blockIdx.x / quads, m0 = (int)blockIdx.x % quads * 4;
+    uint32_t h[4];                           // bins chunk * 64 + lane
+    if (FROM == VOTE_CODES) {
+        for (int i = tid; i < 4 * L; i += VOTE_FEW_THREADS) bins[i] = 0u;
+        __syncthreads();
+        constexpr int PER = 20;                                              // codes per thread whose loads travel together
+        const bool words = (M & 3) == 0 && ((uintptr_t)vr.codes & 3) == 0;
+        const int width = M - m0 < 4 ? M - m0 : 4;
+        for (int64_t nb = tid; nb < vr.N; nb += VOTE_FEW_THREADS * PER) {
+            int32_t kk[PER];
+#pragma unroll
+            for (int u = 0; u < PER; ++u) kk[u] = nb + u * VOTE_FEW_THREADS < vr.N ? vr.assign[nb + u * VOTE_FEW_THREADS] : -1;
+            __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+            for (int u = 0; u < PER; ++u) {
+                if (kk[u] != k) continue;
+                const uint8_t* x = vr.codes + (nb + u * VOTE_FEW_THREADS) * M + m0;
+                if (words) {
+                    const uint32_t w = *reinterpret_cast<const uint32_t*>(x);
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) atomicAdd(&bins[i * L + ((w >> (8 * i)) & 255u)], 1u);
+                } else {
+                    for (int i = 0; i < width; ++i) atomicAdd(&bins[i * L + x[i]], 1u);
+                }
+            }
+        }
+        __syncthreads();
+    }
+    const int m = m0 + wave;
+    if (wave >= 4 || m >= M) return;
+    const size_t pair = (size_t)k * M + m;
+    if (FROM == VOTE_CODES) {
+#pragma unroll
+        for (int ch = 0; ch < 4; ++ch) h[ch] = bins[wave * L + ch * 64 + lane];
+    } else {
+        const size_t at = pair * L + lane;
+        if (S <= 1) {
+#pragma unroll
+            for (int ch = 0; ch < 4; ++ch) h[ch] = hist[at + ch * 64];
+        } else {
+#pragma unroll
+            for (int ch = 0; ch < 4; ++ch) h[ch] = 0u;
+            for (int u0 = 0; u0 < S; u0 += 8) {
+                uint32_t t[8][4];
+#pragma unroll
+                for (int u = 0; u < 8; ++u)
+#pragma unroll
+                    for (int ch = 0; ch < 4; ++ch) t[u][ch] = parts[(size_t)(u0 + u < S ? u0 + u : S - 1) * part_stride + at + ch * 64];
+#pragma unroll
+                for (int u = 0; u < 8; ++u)
+#pragma unroll
+                    for (int ch = 0; ch < 4; ++ch) h[ch] += u0 + u < S ? t[u][ch] : 0u;
+            }
+        }
+    }
+    uint2* mine = list + wave * L;
+    uint32_t n = 0u;
+#pragma unroll
+    for (int ch = 0; ch < 4; ++ch) {
+        if (FROM == VOTE_CODES || S > 1) hist[pair * L + ch * 64 + lane] = h[ch];
+        const uint64_t set = __ballot(h[ch] != 0u);
+        if (h[ch] != 0u)
+            mine[n + __builtin_amdgcn_mbcnt_hi((uint32_t)(set >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)set, 0u))] =
+                make_uint2((uint32_t)(ch * 64 + lane) * (L * 4), __builtin_bit_cast(uint32_t, (float)h[ch]));
+        n += (uint32_t)__popcll(set);
+    }
+    uint32_t cnt = h[0] + h[1] + h[2] + h[3];
+#pragma unroll
+    for (int d = 32; d >= 1; d >>= 1) cnt += __shfl_xor(cnt, d);
+    if (m == 0 && lane == 0) counts[k] = cnt;
+    if (cnt == 0u) return;                                                   // an empty cluster keeps its code
+    __builtin_amdgcn_wave_barrier();
+    n = __builtin_amdgcn_readfirstlane(n);
+    const float* table = tables + (size_t)m * L * L;
+    float4 acc = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+    for (uint32_t i0 = 0; i0 < n; i0 += 64) {
+        const uint2 e = mine[i0 + lane < n ? i0 + lane : n - 1];             // past the end: the last row again
+        const int left = (int)(n - i0) < 64 ? (int)(n - i0) : 64;
+        float4 r[2][VOTE_FEW_ROWS];
+        auto fetch = [&](float4 (&to)[VOTE_FEW_ROWS], int j0) {
+#pragma unroll
+            for (int u = 0; u < VOTE_FEW_ROWS; ++u)
+                to[u] = *reinterpret_cast<const float4*>(reinterpret_cast<const char*>(table) +
+                                                         (uint32_t)__builtin_amdgcn_readlane((int)e.x, j0 + u) + (uint32_t)lane * 16u);
+        };
+        fetch(r[0], 0);
+#pragma unroll
+        for (int b = 0; b < 64 / VOTE_FEW_ROWS; ++b) {
+            const int j0 = b * VOTE_FEW_ROWS;
+            if (j0 >= left) break;
+            if (j0 + VOTE_FEW_ROWS < left) fetch(r[(b + 1) & 1], j0 + VOTE_FEW_ROWS);
+            __builtin_amdgcn_sched_barrier(0);                               // the next rows are asked for before these are waited for
+#pragma unroll
+            for (int u = 0; u < VOTE_FEW_ROWS; ++u) {
+                const float c = __builtin_bit_cast(float, __builtin_amdgcn_readlane((int)e.y, j0 + u));
+                if (j0 + u < left) {
+                    const float4 row = r[b & 1][u];
+                    acc.x = fmaf(c, row.x, acc.x); acc.y = fmaf(c, row.y, acc.y);
+                    acc.z = fmaf(c, row.z, acc.z); acc.w = fmaf(c, row.w, acc.w);
+                }
+            }
+        }
+    }
+    // as in vote_kernel: from +inf, strict "<" over ascending candidates
+    float b = INFINITY;
+    int bi = IDX_NONE;
+    if (acc.x < b) { b = acc.x; bi = lane * 4; }
+    if (acc.y < b) { b = acc.y; bi = lane * 4 + 1; }
+    if (acc.z < b) { b = acc.z; bi = lane * 4 + 2; }
+    if (acc.w < b) { b = acc.w; bi = lane * 4 + 3; }
+#pragma unroll
+    for (int d = 32; d >= 1; d >>= 1) near_merge(b, bi, __shfl_xor(b, d), __shfl_xor(bi, d));
+    if (lane == 0) centers[pair] = (uint8_t)(bi == IDX_NONE ? 0 : bi);
+}
+
+// ---------------------------------------------------------------------------------------------
 // Exact index over the centers (Sec. 3.1, the table-based FindNN of Alg. 1).
 //
 // The paper's table is a hash table over the center codes that is probed with candidate codes in
