@@ -69,7 +69,7 @@ pqkm_status pqkm_profile_read_steps(double *total_ms, int64_t *steps);
  * pqkm_scan_plan: what the assignment step of iteration `iteration` (from 0) of pqkm_fit runs for N codes against K
  * centers under the options as they are, for aligned operands: host arithmetic, nothing is launched (without a GPU the
  * answer is that for 256 compute units).
- * Where the scan on the matrix cores is tried first (pqkm_dot_scan) the answer is what it leaves the codes to.
+ * Where the scan on the matrix cores is tried first the answer is what it leaves the codes to.
  *   out   host, int64[6]: 0 the scan: 0 = one lane per center, 1 = LDS-tiled, 2 = through lower bounds;
  *         1 its number ("scan_variant"); 2 codes per stretch; 3 lanes per slot that it regroups the codes for (0 = it does
  *         not); 4 whether it takes over the regrouped copy of the iteration before; 5 where a code's first bound comes
@@ -79,7 +79,9 @@ pqkm_status pqkm_profile_read_steps(double *total_ms, int64_t *steps);
 pqkm_status pqkm_scan_plan(int64_t N, int32_t M, int32_t K, int32_t iteration, int64_t out[6]);
 
 /*
- * pqkm_dot_scan: the scan on the matrix cores, for aligned operands, a call that asks for no distances, and the options as they are.
+ * pqkm_dot_scan: the scan on the matrix cores in front of an LDS-tiled scan or one through lower bounds, for aligned operands, a call that
+ * asks for no distances, and the options as they are.  Where pqkm_scan_plan names one lane per center, whether that is preceded by it is not
+ * reported here (the event log counts two scan kernels then).
  *   workspace   that of a pqkm_assign or pqkm_fit call for these N, M, K, or NULL; with it the call waits for the device
  *   out         host, int32[2]: 0 whether the scan is tried first; 1 with a workspace, and where it is tried: whether the last
  *               assignment step there was left to the scans behind it, which pqkm_scan_plan names (1) or not (0), else -1

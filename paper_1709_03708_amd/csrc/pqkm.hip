@@ -1235,7 +1235,7 @@ struct Carried {
 // M = 32, with, 128: 90 / 60 at 1e5, 100; 150 / 119 at 3e5, 80; 265 / 244 at 1e6, 64; but 83 / 84 at 2e5, 64.  256: 91 / 72 at 1e5, 100; 75
 // / 69 at 1e5, 80; 376 / 346 at 1e6, 100; but 305 / 324 at 1e6, 80.  Without, 128: 100 / 65 at 5e5, 20; 70 / 49 at 2.5e5, 40.  256: 78 / 55 at 1.2e5, 80; 224 /
 // 165 at 1e6, 40; 96 / 73 at 3e5, 31; 199 / 152 at 6.7e5, 54 (but 269 / 441 at 1e6, 64, left, where no code lies near a center).
-// Below gather_max_codes the scan with one lane per center runs and this is not asked for (M = 32, K = 1000: up to 47058 codes); the
+// This is for sizes with an LDS-tiled scan behind it; below gather_max_codes dot_before_rows decides.  The
 // sizes at which M = 8 regroups its codes are left to the lower-bound scan (up to 8.7e12 pairs per second in later iterations, 2e12 in
 // a first one), and all of M = 4 to its scans.
 int dot_scan_dims(int M, const Options& opt, int64_t N, int K, bool dist, const uint8_t* centers, const Carve& c)
@@ -1594,7 +1594,7 @@ pqkm_status assign_tiled(const uint8_t* codes, int64_t N, const uint8_t* centers
 // Several codes per block (aligned operands, M = 4, 8, 16, 32), M = 4, per code: 0.64 ns without and 1.05 ns with the copies at
 // K = 100, 4.4 and 1.5 ns at K = 1000.  One code per block, N = 4e5, ms without / with: M = 1, K = 2000: 0.76 / 2.07, M = 6:
 // 1.22 / 2.17 at K = 500 and 4.7 / 3.8 at K = 2000, M = 24: 1.99 / 4.33 at K = 200 and 9.2 / 6.8 at K = 1000.
-inline int gather_rows_min_k(int M, bool words) { return words ? 160 : 250 + 6000 / M; }
+inline int gather_rows_min_k(int M, bool words) { return words ? (M < 16 ? 1 : M == 16 ? 64 : 160) : 250 + 6000 / M; }
 
 // With few centers most of its lanes have none, and one lane per code (assign_generic_kernel) is faster: that takes about
 // 0.27 us per look-up of a code while the codes do not fill the chip and 3.9 ps each beyond, the scan above 0.75 ns and 0.03 ns
@@ -1606,16 +1606,52 @@ bool lane_per_code(int64_t N, int M, int K)
     return (double)K * M < (fill < 215.0 ? fill : 215.0) * (1.0 + M / 22.0);
 }
 
-// Most codes for which it is faster than the tiled scans (M = 4, 8, 16, 32), whose time does not depend on N below one
-// round of their smallest workgroups: at M = 4 10 us + 74 ns K against 10 us + N (0.96 ns + 0.00062 ns K), equal at
-// 47000 codes for K = 1000 and 100000 for K = 8000, later for larger M.  Without rows 7 us + 0.6 ns N against 7 us + 2.8 us for
-// every 32 centers at M = 4, 4.7 us at M = 8 and 7 us at M = 16 (N = 16384, K = 16: 16.5 / 10.4, 15.9 / 11.9, 20.6 / 15.6 us;
-// M = 4, K = 100, N = 1e4: 12 / 18).
+// us of the scan with one lane per center and its rows in LDS (many codes): measured at K = 160, 300, 1000 and 4000, ns per code: M = 4:
+// 0.40, 0.44, 0.85, 2.8; M = 8: 0.68, 0.79, 1.6, 5.6; M = 16: 1.35, 1.6, 3.3, 10.8; M = 32: 3.35, 3.9, 5.9, 21.
+double rows_us(int64_t N, int M, int K)
+{
+    const double base = M == 4 ? 0.26 : M == 8 ? 0.43 : M == 16 ? 1.0 : 2.4, pass = M == 4 ? 0.164 : M == 8 ? 0.33 : M == 16 ? 0.61 : 1.15;
+    return 3.6 + 0.001 * (double)N * (base + pass * ((double)K / 256.0));
+}
+
+// Most codes for which it is faster than the tiled scans (M = 4, 8, 16, 32), whose time does not depend on N below one round of their
+// smallest workgroups: a fixed part and about 2.45 us (M = 4) per tile of 128 / M centers.  Where the scan on the matrix cores takes
+// over from the tiled ones (dot_scan_dims) that is the limit.  With distances, tiled / one lane per center, us, on either side: M = 4, K = 1000:
+// 87 / 64 at N = 7e4, 90 / 98 at 1.1e5; K = 300: 32.6 / 22.5 at 4e4, 33 / 36 at 7e4; M = 8, K = 300: 50 / 37 at 4e4, 51 / 59 at 7e4; M = 16, K =
+// 160: 55 / 33 at 2e4, 55 / 60 at 4e4; M = 32, K = 160: 136 / 73 at 2e4, 134 / 138 at 4e4.  Fewer than 160 centers, without the rows: 7 us +
+// 0.6 ns N against 7 us + 2.8 us for every 32 centers at M = 4, 4.7 us at M = 8 and 7 us at M = 16 (with rows it is faster beyond that).
 int64_t gather_max_codes(int M, int K)
 {
-    if (K >= 160) return (int64_t)120000 * K / (1550 + (int64_t)K);
+    if (K >= 160) {
+        const int64_t tiles = ((int64_t)K * M + 127) / 128;
+        const double tiled = M == 4 ? 8.0 + 2.45 * (double)tiles : M == 8 ? 9.5 + 2.12 * (double)tiles : M == 16 ? 11.8 + 2.13 * (double)tiles : 19.5 + 2.63 * (double)tiles;
+        int64_t most = (int64_t)((tiled - 3.6) / (rows_us(1000000, M, K) - 3.6) * 1e6);
+        const int64_t dot_from = M == 8 ? 90000000 / K : M == 16 && 9000000 / K < 25000 ? 25000 : 9000000 / K;
+        if (M > 4 && (M > 8 || K >= 500) && most >= dot_from) most = dot_from - 1;
+        if (most > 512 * (int64_t)cu_count()) most = 512 * (int64_t)cu_count();
+        const int64_t least = (int64_t)120000 * K / (1550 + (int64_t)K);
+        return most > least ? most : least;
+    }
     const int64_t most = (int64_t)(M == 4 ? 4700 : M == 8 ? 7800 : 11600) * ((K + 31) / 32);
     return M == 32 || most > 16384 ? 16384 : most;
+}
+
+// Is the scan on the matrix cores tried before the one with one lane per center, and for how many dimensions?  While its blocks of 256
+// codes fill the chip no more than once it takes a time that hardly depends on N, more by half at 256 dimensions; tables it is not for
+// cost 10 us (M = 8: 14) and are left to the scan behind, as those of 256 dimensions are where only 128 pay.  One lane per
+// center alone, then this with tables of 128 / 256 dimensions / it is not for, us, with distances: M = 8, K = 1000: 57 (51 / 69 / 67) at N =
+// 3.3e4, 78 (60 / 76 / 86) at 4.6e4; K = 4000: 142 (91 / 147 / 148) at 2.5e4, 251 (122 / 151 / 261) at 4.6e4; M = 16, K = 300: 45 (40 / 56 / 53) at
+// 2.5e4; K = 1000: 63 (49 / 71 / 73) at 1.8e4, 152 (65 / 75 / 159) at 4.6e4; K = 4000: 201 (92 / 138 / 208) at 1.8e4; M = 32, K = 160: 90 (53 / 59 /
+// 99) at 2.5e4; K = 1000: 78 (61 / 77 / 86) at 1.2e4, 279 (69 / 95 / 290) at 4.6e4.
+int dot_before_rows(int M, const Options& opt, int64_t N, int K, const uint8_t* codes, const uint8_t* centers, const Carve& c)
+{
+    if (M < 8 || !tiled_M(M) || K < 160 || K > (1 << 22) || opt.assign_kernel == 1 || c.dot_off == 0 ||
+        (((uintptr_t)codes | (uintptr_t)centers) & 3) != 0)
+        return 0;
+    const int64_t round = 256 * (int64_t)cu_count(), rounds = (N + round - 1) / round;
+    const double few = M == 8 ? 35.0 : M == 16 ? 32.0 : 45.0, many = M == 8 ? 49.0 : M == 16 ? 37.0 : 51.0, rows = rows_us(N, M, K);
+    auto dot = [&](double fixed, double center) { return fixed + center * K * (double)rounds + 10.0 * (double)(rounds - 1); };
+    return rows > 1.25 * dot(many, 0.025) ? 256 : rows > 1.2 * dot(few, 0.015) ? 128 : 0;
 }
 
 // does one of the LDS-tiled scans run?
@@ -1627,16 +1663,28 @@ bool tiled_scan(const Options& opt, int64_t N, int M, int K, const uint8_t* code
 
 template <int MW, int CN>
 pqkm_status launch_gather(const uint8_t* codes, int64_t N, int M, const uint8_t* centers, int K, const float* tables,
-                          int32_t* assign, float* dist, NearRecord* part, size_t room, hipStream_t st)
+                          int32_t* assign, float* dist, NearRecord* part, size_t room, const uint32_t* only_if, hipStream_t st)
 {
     const int64_t per_launch = (int64_t)CN << 23;                  // 2^31 threads
+    const bool rows = K >= gather_rows_min_k(M, MW > 0);
     for (int64_t n0 = 0; n0 < N; n0 += per_launch) {
         const int64_t cnt = N - n0 < per_launch ? N - n0 : per_launch;
         const int64_t blocks = (cnt + CN - 1) / CN;
-        // about eight blocks per compute unit, as long as each keeps 256 centers and the records fit their room
-        int64_t splits = 8 * (int64_t)cu_count() / blocks;
-        if (splits > ((int64_t)K + 255) / 256) splits = ((int64_t)K + 255) / 256;
+        const int64_t passes = ((int64_t)K + 255) / 256;           // of a block over its centers
+        int64_t splits;
+        if (MW > 0 && rows) {
+            // A pass takes 60 ns + 10 ns M, the second launch and the records 2.5 us: M = 4, one code per block, us: 48 codes, K = 4096:
+            // 4.6 in one, 5.6 in sixteen parts; 4 codes, K = 50000: 22 and 6.2; M = 32, 48 codes: 5.4 and 6.4 at K = 1000, 9.8 and 7.7 at 4096.
+            splits = (double)passes * (0.06 + 0.01 * M) > 3.0 ? 2 * (int64_t)cu_count() / blocks : 1;
+            if (splits > passes / 4) splits = passes / 4;
+        } else {
+            // about eight blocks per compute unit, as long as each keeps 256 centers
+            splits = 8 * (int64_t)cu_count() / blocks;
+            if (splits > passes) splits = passes;
+        }
+        // the records fit their room
         if (splits > (int64_t)(room / sizeof(NearRecord)) / cnt) splits = (int64_t)(room / sizeof(NearRecord)) / cnt;
+        if (only_if) splits = 1;                                   // the room of the records is in use
         int per = K;
         if (splits > 1) {
             per = (int)((((int64_t)K + splits - 1) / splits + 255) / 256 * 256);
@@ -1647,12 +1695,21 @@ pqkm_status launch_gather(const uint8_t* codes, int64_t N, int M, const uint8_t*
         NearRecord* pn = splits > 1 ? part : nullptr;
         const dim3 grid((unsigned)blocks, (unsigned)splits);
         ++t_scan_kernels;
-        if (K >= gather_rows_min_k(M, MW > 0))
-            hipLaunchKernelGGL((assign_gather_kernel<MW, CN, true>), grid, dim3(256), 0, st, codes + n0 * M, cnt, M, centers, K,
-                               tables, assign + n0, dn, pn, per);
-        else
-            hipLaunchKernelGGL((assign_gather_kernel<MW, CN, false>), grid, dim3(256), 0, st, codes + n0 * M, cnt, M, centers, K,
-                               tables, assign + n0, dn, pn, per);
+        if constexpr (MW > 0) {
+            if (rows)
+                hipLaunchKernelGGL((assign_rows_kernel<MW, CN, 256>), grid, dim3(256), 0, st, codes + n0 * M, cnt, centers, K, tables,
+                                   assign + n0, dn, pn, per, only_if);
+            else
+                hipLaunchKernelGGL((assign_gather_kernel<MW, CN, false>), grid, dim3(256), 0, st, codes + n0 * M, cnt, M, centers, K,
+                                   tables, assign + n0, dn, pn, per);
+        } else {
+            if (rows)
+                hipLaunchKernelGGL((assign_gather_kernel<0, 1, true>), grid, dim3(256), 0, st, codes + n0 * M, cnt, M, centers, K,
+                                   tables, assign + n0, dn, pn, per);
+            else
+                hipLaunchKernelGGL((assign_gather_kernel<0, 1, false>), grid, dim3(256), 0, st, codes + n0 * M, cnt, M, centers, K,
+                                   tables, assign + n0, dn, pn, per);
+        }
         if (splits > 1)
             hipLaunchKernelGGL(assign_merge_kernel, dim3((unsigned)((cnt + 3) / 4)), dim3(256), 0, st, pn, cnt, (int)splits,
                                assign + n0, dn);
@@ -1662,21 +1719,27 @@ pqkm_status launch_gather(const uint8_t* codes, int64_t N, int M, const uint8_t*
 
 // one lane per center, or per code where there are few centers
 pqkm_status assign_untiled(const Carve& c, const uint8_t* codes, int64_t N, int M, const uint8_t* centers, int K,
-                           const float* tables, int32_t* assign, float* dist, void* ws, hipStream_t st)
+                           const float* tables, int32_t* assign, float* dist, void* ws, const uint32_t* only_if, hipStream_t st)
 {
     const bool words = tiled_M(M) && (((uintptr_t)codes | (uintptr_t)centers) & 3) == 0;
     NearRecord* part = tiled_M(M) ? reinterpret_cast<NearRecord*>(static_cast<char*>(ws) + c.img_off) : nullptr;
     const size_t room = tiled_M(M) ? c.img_bytes : 0;
-    if (words && M == 4) return launch_gather<1, 8>(codes, N, M, centers, K, tables, assign, dist, part, room, st);
-    if (words && M == 8) return launch_gather<2, 4>(codes, N, M, centers, K, tables, assign, dist, part, room, st);
-    if (words && M == 16) return launch_gather<4, 2>(codes, N, M, centers, K, tables, assign, dist, part, room, st);
-    if (words && M == 32) return launch_gather<8, 1>(codes, N, M, centers, K, tables, assign, dist, part, room, st);
+    // Codes per block: one while that fills the chip no more than four times, then what shares the centers' words best.  us, M = 4: N = 500,
+    // K = 1000: 3.6 / 3.9 / 4.4 / 6.2 with 1, 2, 4, 8; N = 1e4: 15.3 / 13.0 / 12.0 / 14.2; M = 8: 4.0 / 4.3 / 5.3 and 21.9 / 19.8 / 19.4 (K =
+    // 100: 12.6 / 9.9 / 11.1) with 1, 2, 4; M = 16: 5.2 / 5.4 and 36.3 / 35.3 (K = 100: 17.1 / 19.2) with 1, 2.
+    const bool few = N <= 4 * (int64_t)cu_count();
+    if (words && M == 4 && few) return launch_gather<1, 1>(codes, N, M, centers, K, tables, assign, dist, part, room, only_if, st);
+    if (words && M == 4) return launch_gather<1, 4>(codes, N, M, centers, K, tables, assign, dist, part, room, only_if, st);
+    if (words && M == 8 && few) return launch_gather<2, 1>(codes, N, M, centers, K, tables, assign, dist, part, room, only_if, st);
+    if (words && M == 8) return launch_gather<2, 2>(codes, N, M, centers, K, tables, assign, dist, part, room, only_if, st);
+    if (words && M == 16) return launch_gather<4, 1>(codes, N, M, centers, K, tables, assign, dist, part, room, only_if, st);
+    if (words && M == 32) return launch_gather<8, 1>(codes, N, M, centers, K, tables, assign, dist, part, room, only_if, st);
     if (lane_per_code(N, M, K)) {
         hipLaunchKernelGGL(assign_generic_kernel, dim3((unsigned)((N + 255) / 256)), dim3(256), 0, st, codes, N, M, centers, K,
                            tables, assign, dist);
         return launched();
     }
-    return launch_gather<0, 1>(codes, N, M, centers, K, tables, assign, dist, part, room, st);
+    return launch_gather<0, 1>(codes, N, M, centers, K, tables, assign, dist, part, room, only_if, st);
 }
 
 pqkm_status assign_core(const Options& opt, const Carve& c, const uint8_t* codes, int64_t N, int M,
@@ -1685,10 +1748,23 @@ pqkm_status assign_core(const Options& opt, const Carve& c, const uint8_t* codes
 {
     if (opt.assign_kernel == 2 && !(tiled_M(M) && ((uintptr_t)codes & 3) == 0)) return PQKM_ERR_SHAPE;
     if (!tiled_scan(opt, N, M, K, codes)) {
+        // tables that the scan on the matrix cores is not for are left to the one with one lane per center
+        const int dims = dot_before_rows(M, opt, N, K, codes, centers, c);
+        const uint32_t* left = nullptr;
+        if (dims) {
+            char* wsc = static_cast<char*>(ws);
+            if (M == 8) launch_dot<8>(codes, N, centers, K, tables, assign, dist, c, wsc, carried, opt, dims, st);
+            else if (M == 16) launch_dot<16>(codes, N, centers, K, tables, assign, dist, c, wsc, carried, opt, dims, st);
+            else launch_dot<32>(codes, N, centers, K, tables, assign, dist, c, wsc, carried, opt, dims, st);
+            if (launched() != PQKM_OK) return PQKM_ERR_DEVICE;
+            left = &reinterpret_cast<const DotState*>(wsc + c.dot_off)->left;
+            ++carried.iteration;
+            carried.dot = true;
+        }
         EventPair ev{};
         const bool prof = (opt.profile & 1) && log_begin(g_scan_log, st, &ev);
         t_scan_kernels = 0;
-        const pqkm_status s = assign_untiled(c, codes, N, M, centers, K, tables, assign, dist, ws, st);
+        const pqkm_status s = assign_untiled(c, codes, N, M, centers, K, tables, assign, dist, ws, left, st);
         if (prof) {
             hipEventRecord(ev.b, st);
             std::lock_guard<std::mutex> lk(g_mu);

@@ -18,6 +18,20 @@ constexpr int TILE_BYTES = 128 * 1024;    // LDS image of one center tile
 constexpr int TILE_F4 = TILE_BYTES / 16;  // the same in float4 units
 constexpr int IDX_NONE = 0x7fffffff;      // "no center improved yet"
 
+typedef int v4i __attribute__((ext_vector_type(4)));
+
+// 16 bytes per lane from a buffer straight into LDS: lane l of the wave writes LDS bytes lds_addr + 16 l .. + 15
+// (lds_addr is the same for the whole wave) with the 16 bytes at buffer offset voffset + soffset.  Counted like
+// any other vector memory load (s_waitcnt vmcnt).
+__device__ __forceinline__ void buffer_to_lds16(uint32_t lds_addr, v4i rsrc, uint32_t voffset, uint32_t soffset)
+{
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, %3 offen lds"
+                 :
+                 : "s"(lds_addr), "v"(voffset), "s"(rsrc), "s"(soffset)
+                 : "memory", "m0");
+}
+__device__ __forceinline__ void wait_vector_loads() { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); }
+
 // ---------------------------------------------------------------------------------------------
 // Sec. 2.2: A^m[i][j] = || c^m_i - c^m_j ||^2, fp64 accumulation in ascending dimension, direct
 // difference form, one rounding to fp32.  Grid (256, M), block 256: block (i, m), thread j.
@@ -510,24 +524,149 @@ __global__ __launch_bounds__(256) void decode_element_kernel(const uint8_t* __re
 }
 
 // ---------------------------------------------------------------------------------------------
-// Assignment one lane per center (any M, any alignment; Eq. 5 as written): a block takes CN codes, copies their CN * M
-// table rows of 1 KB into LDS and walks over the centers, one lane per center, whose subcodes are the offsets of the
-// look-ups in every row: one four-byte LDS read and one add per look-up.  Needs no tile images and no regrouping, and
-// a handful of codes fills the chip: the fastest of the scans for few codes (bound by the bank conflicts of random
-// four-byte reads, the tiled scans by the tiles that too few workgroups walk one after the other), and for subspace counts
-// without a tiled scan the only one.  A lane sees its centers in ascending order and keeps the first minimum; lanes merge by
-// (distance, index).  With few blocks the centers are split over gridDim.y blocks, which leave (distance, index) records
-// for assign_merge_kernel.  MW = M / 4 with codes and centers read as words, or 0: any M, byte by byte.  With few centers
-// the copies of whole rows would cost more than the look-ups (ROWS false): those then go through the caches, a wave's 64
-// into the 8 lines of one row.
-// Measured, skewed tiled scan -> this, M = 4: 48 codes, K = 1000: 87 -> 13 us; 1e4 codes: 88 -> 23 us; 1e4 codes,
-// K = 8000: 610 -> 70 us; 1e4 codes, K = 100: 18 -> 12 us (17 us with rows).  M = 32, 1e4 codes, K = 1000: 676 -> 84 us.
+// Assignment one lane per center (any M, any alignment; Eq. 5 as written): a block takes CN codes and walks over the centers, one
+// lane per center, whose subcodes are the offsets of the look-ups in the codes' table rows.  Needs no tile images and no regrouping,
+// and a handful of codes fills the chip: the fastest of the scans for few codes, and for subspace counts without a tiled scan the
+// only one.  A lane sees its centers in ascending order and keeps the first minimum; lanes merge by (distance, index).  Where the blocks
+// of the codes leave the chip idle the centers are split over gridDim.y blocks, which leave (distance, index) records for
+// assign_merge_kernel.
+//
+// assign_rows_kernel (M = 4, 8, 16, 32, codes and centers read as words): the CN * M rows of 1 KB come straight into LDS, a wave's 64 x 16
+// bytes per row, all of them and the first centers' words asked for at once: a block waits for memory twice, for its codes and
+// for the rows.  With few codes that is all it does (48 codes, K = 1000, M = 4: 3.4 us); with many it is bound by the bank conflicts of
+// random four-byte reads (M = 4, K = 4000: 1.4e12 pairs per second).
+// assign_gather_kernel: any M and alignment byte by byte (MW = 0, with the rows in LDS or through the caches), and rows through the caches
+// where few centers would not pay for whole rows at M = 16 and 32 (MW = M / 4): a wave's 64 look-ups into the 8 lines of one row.
+// Measured, rows copied through registers one by one, and split and merged -> this, M = 4: 48 codes, K = 1000: 10.6 -> 3.4 us; 1e4 codes, K =
+// 100: 12.0 -> 7.0, K = 1000: 21.4 -> 12.0, K = 8000: 66 -> 59; M = 8, 500 codes, K = 4096: 18.8 -> 6.1; M = 32, 1e4 codes, K = 1000: 79 -> 65.
 // ---------------------------------------------------------------------------------------------
 struct NearRecord { float dist; int32_t index; };
 
 __device__ __forceinline__ void near_merge(float& s, int& k, float os, int ok)
 {
     if (os < s || (os == s && ok < k)) { s = os; k = ok; }
+}
+
+// Lanes of a wave hold (distance, index) of CN codes each; afterwards lane i (64 / CN) holds the merged pair of code i.  Halves of the
+// codes are exchanged for halves of the lanes, so that CN = 8 takes 20 shuffles and not 96.
+template <int CN>
+__device__ __forceinline__ void near_merge_wave(float (&best)[CN], int (&bk)[CN])
+{
+    const int lane = threadIdx.x & 63;
+    int held = CN;
+#pragma unroll
+    for (int off = 32; off; off >>= 1) {
+        if (held > 1) {
+            held /= 2;
+            const bool up = (lane & off) != 0;
+#pragma unroll
+            for (int i = 0; i < CN / 2; ++i) {
+                if (i >= held) break;
+                const float give = up ? best[i] : best[i + held];
+                const int give_k = up ? bk[i] : bk[i + held];
+                best[i] = up ? best[i + held] : best[i];
+                bk[i] = up ? bk[i + held] : bk[i];
+                near_merge(best[i], bk[i], __shfl_xor(give, off), __shfl_xor(give_k, off));
+            }
+        } else {
+            near_merge(best[0], bk[0], __shfl_xor(best[0], off), __shfl_xor(bk[0], off));
+        }
+    }
+}
+
+template <int MW, int CN, int THREADS>
+__global__ __launch_bounds__(THREADS) void assign_rows_kernel(const uint8_t* __restrict__ codes, int64_t N,
+                                                              const uint8_t* __restrict__ centers, int K,
+                                                              const float* __restrict__ tables,
+                                                              int32_t* __restrict__ assign, float* __restrict__ dist,
+                                                              NearRecord* __restrict__ part, int per, const uint32_t* __restrict__ only_if)
+{
+    constexpr int M = 4 * MW, ROWS = CN * M, WAVES = THREADS / 64, MINE = (ROWS + WAVES - 1) / WAVES;
+    __shared__ float row_s[ROWS * L];                                // row i * M + m: subspace m for the subcode of code i
+    __shared__ NearRecord rec[WAVES][CN];
+    if (only_if && *only_if == 0u) return;                           // the scan in front of it did the work
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int64_t n0 = (int64_t)blockIdx.x * CN;
+    const int k_begin = (int)blockIdx.y * per;
+    const int k_end = K - k_begin < per ? K : k_begin + per;
+    const uint32_t* cen = reinterpret_cast<const uint32_t*>(centers);
+    const uint32_t* cod = reinterpret_cast<const uint32_t*>(codes);
+    uint32_t x[MINE];
+#pragma unroll
+    for (int j = 0; j < MINE; ++j) {
+        const int r = wave + j * WAVES, i = r / M, m = r % M;
+        const int64_t n = n0 + i < N ? n0 + i : N - 1;
+        x[j] = r < ROWS ? (cod[n * MW + m / 4] >> (8 * (m % 4))) & 255u : 0u;
+    }
+    // the first centers travel beside the rows
+    uint32_t c[MW];
+    {
+        const int64_t k = (int64_t)k_begin + tid < k_end ? k_begin + tid : k_end - 1;
+#pragma unroll
+        for (int w = 0; w < MW; ++w) c[w] = cen[k * MW + w];
+    }
+    if (((uintptr_t)tables & 15) == 0) {
+        const uint64_t tp = reinterpret_cast<uint64_t>(tables);
+        const v4i rs = {(int)(uint32_t)tp, (int)(uint32_t)(tp >> 32), M * L * L * 4, 0x00020000};
+        const uint32_t lds0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) char*)row_s;
+#pragma unroll
+        for (int j = 0; j < MINE; ++j) {
+            const int r = wave + j * WAVES, m = r % M;
+            const uint32_t row = __builtin_amdgcn_readfirstlane((uint32_t)m * L + x[j]);
+            if (r < ROWS) buffer_to_lds16(lds0 + (uint32_t)r * (L * 4), rs, (uint32_t)lane * 16u, row * (L * 4));
+        }
+        wait_vector_loads();
+    } else {
+#pragma unroll
+        for (int j = 0; j < MINE; ++j) {
+            const int r = wave + j * WAVES, m = r % M;
+            if (r >= ROWS) break;
+            const float* from = tables + ((size_t)m * L + x[j]) * L;
+#pragma unroll
+            for (int e = 0; e < 4; ++e) row_s[r * L + e * 64 + lane] = from[e * 64 + lane];
+        }
+    }
+    __syncthreads();
+    float best[CN];
+    int bk[CN];
+#pragma unroll
+    for (int i = 0; i < CN; ++i) { best[i] = INFINITY; bk[i] = IDX_NONE; }
+    for (int64_t k = (int64_t)k_begin + tid; k < k_end; k += THREADS) {
+        const float* at[M];
+#pragma unroll
+        for (int m = 0; m < M; ++m) at[m] = row_s + ((c[m / 4] >> (8 * (m % 4))) & 255u);
+        const int64_t next = k + THREADS < k_end ? k + THREADS : k;
+#pragma unroll
+        for (int w = 0; w < MW; ++w) c[w] = cen[next * MW + w];
+        float s[CN];
+#pragma unroll
+        for (int m = 0; m < M; ++m)
+#pragma unroll
+            for (int i = 0; i < CN; ++i) {
+                const float a = at[m][(i * M + m) * L];
+                s[i] = m == 0 ? a : s[i] + a;
+            }
+#pragma unroll
+        for (int i = 0; i < CN; ++i)
+            if (s[i] < best[i]) { best[i] = s[i]; bk[i] = (int)k; }
+    }
+    near_merge_wave<CN>(best, bk);
+    if (lane % (64 / CN) == 0) rec[wave][lane / (64 / CN)] = NearRecord{best[0], bk[0]};
+    __syncthreads();
+    if (tid < CN && n0 + tid < N) {
+        float s = rec[0][tid].dist;
+        int k = rec[0][tid].index;
+#pragma unroll
+        for (int w = 1; w < WAVES; ++w) near_merge(s, k, rec[w][tid].dist, rec[w][tid].index);
+        const int64_t n = n0 + tid;
+        if (part) {
+            part[n * gridDim.y + blockIdx.y] = NearRecord{s, k};
+        } else {
+            assign[n] = k == IDX_NONE ? 0 : k;
+            if (dist) dist[n] = s;
+        }
+    }
 }
 
 template <int MW, int CN, bool ROWS>
@@ -2097,18 +2236,6 @@ __global__ __launch_bounds__(THREADS) void assign_scan4q_kernel(int64_t N, const
 // and xor.  Per code and lane: two registers of packed row offsets, the running minimum, the HALF tile
 // (2 tile + h) in which it last improved.
 // ---------------------------------------------------------------------------------------------
-typedef int v4i __attribute__((ext_vector_type(4)));
-
-// 16 bytes per lane from a buffer straight into LDS: lane l of the wave writes LDS bytes lds_addr + 16 l .. + 15
-// (lds_addr is the same for the whole wave) with the 16 bytes at buffer offset voffset + soffset.  Counted like
-// any other vector memory load (s_waitcnt vmcnt).
-__device__ __forceinline__ void buffer_to_lds16(uint32_t lds_addr, v4i rsrc, uint32_t voffset, uint32_t soffset)
-{
-    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, %3 offen lds"
-                 :
-                 : "s"(lds_addr), "v"(voffset), "s"(rsrc), "s"(soffset)
-                 : "memory", "m0");
-}
 // A code whose key holds this was left by a scan through lower bounds that gave up (pqkm_filter.h); it gives up for whole
 // workgroups of a multiple of GAVE_UP_STEP codes.
 constexpr unsigned long long GAVE_UP = ~1ull;
@@ -2125,8 +2252,6 @@ __device__ __forceinline__ bool any_gave_up(const unsigned long long* __restrict
         if (base + i < N) any = any || keys[base + i] == GAVE_UP;
     return any;
 }
-
-__device__ __forceinline__ void wait_vector_loads() { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); }
 
 // LEFT: only the codes whose key says GAVE_UP are finished.
 template <int R, int THREADS, int DEPTH, bool BUCKET = false, bool LEFT = false>

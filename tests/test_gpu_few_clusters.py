@@ -1,5 +1,5 @@
-"""The update with few clusters (one wave per cluster and subspace) against the oracle: edges of its launches and rules, uneven and
-empty clusters, tables that are not finite."""
+"""The update with few clusters (one wave per cluster and subspace), and the scan on the matrix cores in front of the one with one lane
+per center, against the oracle: edges of their launches and rules, uneven and empty clusters, tables that are not finite or no distances."""
 from __future__ import annotations
 
 import numpy as np
@@ -72,3 +72,65 @@ def test_update_with_ties_and_non_finite_tables(env, N, K):
     bad[1] = np.nan                                                              # no candidate can be taken
     bad[2, :, 7:] = np.inf
     _check_update(env, codes, assign, bad, K)
+
+
+def _points(rng, M, dims):
+    p = rng.standard_normal((M, 256, dims))
+    return ((p[:, :, None, :] - p[:, None, :, :]) ** 2).sum(3).astype(np.float32)
+
+
+# sizes on either side of the rule (128 and 256 dimensions in all), tables it is for and not for; the log has a scan more where it is tried
+@pytest.mark.parametrize("M,N,K,tried", [(8, 36_001, 1000, True), (8, 20_000, 1000, False), (16, 24_000, 300, True), (16, 9000, 300, False),
+                                         (16, 30_011, 1000, True), (32, 19_999, 300, True), (32, 5000, 160, False), (32, 11_003, 1500, True)])
+@pytest.mark.parametrize("dims", [128, 256, 0])
+def test_matrix_cores_before_one_lane_per_center(env, M, N, K, tried, dims):
+    pq, oracle, torch = env
+    rng = np.random.default_rng(N + K + dims)
+    tables = _points(rng, M, dims // M) if dims else rand_tables(rng, M)
+    codes = rng.integers(0, 256, (N, M), dtype=np.uint8)
+    centers = codes[rng.permutation(N)[:K]].copy()
+    assert pq.scan_plan(N, M, K)["scan"] == 0
+    d = [torch.from_numpy(v).cuda() for v in (codes, centers, tables)]
+    pq.profile_read()
+    pq.set_option("profile", 1)
+    try:
+        a, dist = pq.assign(*d)
+    finally:
+        pq.set_option("profile", 0)
+    assert pq.profile_read()[1] == (2 if tried else 1)
+    ra, rd = oracle.assign(codes, centers, tables)
+    np.testing.assert_array_equal(a.cpu().numpy(), ra)
+    np.testing.assert_array_equal(dist.cpu().numpy().view(np.uint32), rd.view(np.uint32))
+
+
+@pytest.mark.parametrize("M", [8, 16])
+@pytest.mark.parametrize("suited", [True, False])
+def test_fit_with_both(env, M, suited):
+    """Several iterations: the points are found once, the centers' fragments each time."""
+    pq, oracle, torch = env
+    rng = np.random.default_rng(M)
+    N, K = 36_000, 1000
+    tables = _points(rng, M, 128 // M) if suited else rand_tables(rng, M)
+    codes = rng.integers(0, 256, (N, M), dtype=np.uint8)
+    centers = codes[:K].copy()
+    c = torch.from_numpy(centers.copy()).cuda()
+    _, a = pq.fit(torch.from_numpy(codes).cuda(), torch.from_numpy(tables).cuda(), c, 3)
+    for _ in range(3):
+        ra, _ = oracle.assign(codes, centers, tables)
+        centers, _, _ = oracle.update(codes, ra, tables, centers)
+    np.testing.assert_array_equal(a.cpu().numpy(), ra)
+    np.testing.assert_array_equal(c.cpu().numpy(), centers)
+
+
+@pytest.mark.parametrize("M,N,K", [(4, 2, 9000), (4, 1024, 513), (4, 1025, 513), (8, 3, 20_000), (8, 1025, 300), (32, 7, 3000), (16, 40, 64), (16, 40, 63)])
+def test_rows_of_one_and_several_codes(env, M, N, K):
+    """Codes per block, and centers split over blocks."""
+    pq, oracle, torch = env
+    rng = np.random.default_rng(N + K)
+    codes = rng.integers(0, 20, (N, M), dtype=np.uint8)
+    centers = rng.integers(0, 20, (K, M), dtype=np.uint8)
+    tables = rand_tables(rng, M)
+    a, dist = pq.assign(*[torch.from_numpy(v).cuda() for v in (codes, centers, tables)])
+    ra, rd = oracle.assign(codes, centers, tables)
+    np.testing.assert_array_equal(a.cpu().numpy(), ra)
+    np.testing.assert_array_equal(dist.cpu().numpy().view(np.uint32), rd.view(np.uint32))
