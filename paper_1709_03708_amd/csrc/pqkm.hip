@@ -668,7 +668,7 @@ void launch_scan4h_bucket(const uint2* gco, int64_t n_alloc, const float4* img, 
 // M = 4, many codes: the four-lane scan (variant 70) or one of the shapes of the LDS-direct scan (85..87, 89), by the time
 // the rounds of workgroups take.  Clocks per tile and workgroup of C codes, from the measured times: four lanes per
 // code 2.30 C + 2065 (the fill of 128 KB between two barriers), LDS-direct 2.45 C + 1064 (two halves).
-int choose_scan4_large(int64_t n)
+int choose_scan4_large(int64_t n, double* clocks = nullptr)
 {
     const int ncu = cu_count();
     const int64_t na = group_alloc(n);
@@ -676,13 +676,17 @@ int choose_scan4_large(int64_t n)
     const int64_t c4p = 128 * (int64_t)scan4p_codes_per_slot(na);
     double best_cost = (double)rounds(c4p) * (2.30 * (double)c4p + 2065.0);
     int best = 70;
-    if (n >= ((int64_t)1 << 23)) return 85;            // stretches are cut to whole rounds of the largest shape
+    if (n >= ((int64_t)1 << 23)) {                     // stretches are cut to whole rounds of the largest shape
+        if (clocks) *clocks = (double)rounds(8192) * (2.45 * 8192.0 + 1064.0);
+        return 85;
+    }
     static const int cand[] = {85, 87, 86, 89};
     for (int v : cand) {
         const int64_t C = scan4h_codes_per_workgroup(v);
         const double cost = (double)rounds(C) * (2.45 * (double)C + 1064.0);
         if (cost < best_cost) { best_cost = cost; best = v; }
     }
+    if (clocks) *clocks = best_cost;
     return best;
 }
 
@@ -994,6 +998,8 @@ void launch_scan_M<4>(int variant, const uint8_t* codes, int64_t N, const float4
         case 34: launch_scan4s<16, 1024>(codes, N, img, ntiles, assign, dist, st); break;
         case 36: launch_scan4s<16, 512>(codes, N, img, ntiles, assign, dist, st); break;
         case 37: launch_scan4s<8, 1024>(codes, N, img, ntiles, assign, dist, st); break;
+        case 38: launch_scan4s<10, 1024>(codes, N, img, ntiles, assign, dist, st); break;
+        case 39: launch_scan4s<12, 1024>(codes, N, img, ntiles, assign, dist, st); break;
         case 33: launch_scan4s<4, 512>(codes, N, img, ntiles, assign, dist, st); break;
         case 35: launch_scan4s<8, 512>(codes, N, img, ntiles, assign, dist, st); break;
         case 41: launch_scan4p<16, 1024, 1>(codes, N, nullptr, img, rows, ntiles, assign, dist, st); break;
@@ -1051,7 +1057,23 @@ void launch_scan_M<32>(int variant, const uint8_t* codes, int64_t N, const float
 
 // Which scan runs: for M = 4 with the default variant, the regrouped half-plane scan when there is enough work
 // to pay for regrouping (a pass over the codes) and the subspace-skewed scan otherwise.
-inline int effective_variant(int M, int variant, int64_t N, int K, const uint8_t* codes, const uint8_t* centers)
+// M = 4, skewed scan of 2048 (37), 2560 (38), 3072 (39) or 4096 (34) codes per workgroup by the time of its rounds, from measured ones, us: one
+// round 21 / 24.5 / 27.5 / 35 at K = 32, 45 / 50 / 56 / 76 at K = 200, 140 / 162 / 186 / 260 at K = 1000 (the last one spills registers).
+struct SkewChoice { int variant; double us; };
+SkewChoice choose_scan4s(int64_t N, int K)
+{
+    static const struct { int variant, codes; double round, tile; } shapes[] = {
+        {37, 2048, 9.7, 3.85}, {38, 2560, 12.0, 4.43}, {39, 3072, 14.5, 5.1}, {34, 4096, 20.0, 7.25}};
+    const int64_t ncu = cu_count();
+    SkewChoice best{37, 1e300};
+    for (const auto& s : shapes) {
+        const double us = 8.0 + (double)(((N + s.codes - 1) / s.codes + ncu - 1) / ncu) * (s.round + s.tile * (double)((K + 31) / 32));
+        if (us < best.us) best = SkewChoice{s.variant, us};
+    }
+    return best;
+}
+
+inline int effective_variant(int M, int variant, int64_t N, int K, const uint8_t* codes, const uint8_t* centers, bool alone)
 {
     // the regrouped scans address the tile images through one 32-bit buffer offset: below 4 GB of images only
     const int TK = 128 / M;
@@ -1073,7 +1095,10 @@ inline int effective_variant(int M, int variant, int64_t N, int K, const uint8_t
             // skewed scan: while one round of workgroups covers the codes, the smallest shape that does so (measured
             // per round at K = 1000: 139, 172, 220, 263 us for 512, 1024, 1536, 2048 codes per workgroup)
             const int64_t ncu = cu_count();
-            return N <= ncu * 512 ? 6 : N <= ncu * 1024 ? 7 : N <= ncu * 1536 ? 2 : 0;
+            if (N <= ncu * 1536) return N <= ncu * 512 ? 6 : N <= ncu * 1024 ? 7 : 2;
+            // then whichever of the two large ones takes less for its rounds: N = 524289, K = 100: 98 / 83 us, K = 400: 231 / 195
+            auto rounds = [&](int64_t C) { return (double)((N + C * ncu - 1) / (C * ncu)); };
+            return rounds(1536) * 0.84 < rounds(2048) ? 2 : 0;
         }
         return variant;
     }
@@ -1090,14 +1115,21 @@ inline int effective_variant(int M, int variant, int64_t N, int K, const uint8_t
     // time grows with its codes (measured per round at K = 1000: 82, 107, 133, 254 us for 512, 1024, 2048, 4096),
     // so while one round of workgroups covers all codes the smallest shape that does so wins, also over the
     // regrouped scan (117 us and up per round plus the regrouping).  Beyond one round of 2048-code workgroups the
-    // regrouped scan is faster; with few centers (it needs K >= 128) the two largest skewed shapes remain.
+    // regrouped scan is faster where a fit uses the regrouped codes several times and K >= 128; else the skewed shape with the
+    // fewest microseconds, and for one assignment by itself the faster of the two.
     const int64_t ncu = cu_count();
     if (N <= ncu * 512) return 33;
     if (N <= ncu * 1024) return 35;
     if (N <= ncu * 2048) return 37;
-    if (K < 128 || !img32) {
-        const int64_t t34 = (((N + 4095) / 4096 + ncu - 1) / ncu) * 79, t37 = (((N + 2047) / 2048 + ncu - 1) / ncu) * 42;
-        return t37 < t34 ? 37 : 34;
+    const SkewChoice best = choose_scan4s(N, K);
+    if (K < 128 || !img32) return best.variant;
+    // regrouping and the rest 25 us and 40 ps per code, and the rounds of choose_scan4_large.  One assignment, regrouped / skewed, us: K = 200:
+    // 87 / 51 at N = 655360, 146 / 109 at 1.57e6, 165 / 148 at 2e6; K = 500: 142 / 104 at 786432, 201 / 172 at 1.28e6, but 256 / 275 at 2e6; K =
+    // 1000: 193 / 165 at 655360, 305 / 262 at 1048576, but 356 / 365 at 1.57e6.
+    if (alone && K < filter4_min_k(0, N)) {
+        double clocks;
+        choose_scan4_large(N, &clocks);
+        if (best.us < 0.97 * (25.0 + 4e-5 * (double)N + clocks * (double)((K + 31) / 32) / 2200.0)) return best.variant;
     }
     return 70;                            // regrouped half-plane scan, codes per lane-slot chosen per launch
 }
@@ -1217,6 +1249,7 @@ struct Carried {
     int lanes = 0;            // a regrouped copy of ALL codes, placed for slots of this many lanes (0: there is none)
     bool stats = false;       // the lower-bound scan's statistics of the tables
     bool keys = false;        // its keys by position in that copy, and the copy of the centers that they belong to
+    bool alone = false;       // one assignment by itself, not an iteration of a fit
     bool dot = false;         // the points of the scan on the matrix cores, or that it is not for these tables
 };
 
@@ -1311,7 +1344,7 @@ ScanPlan scan_plan(int M, const Options& opt, int64_t N, int K, const uint8_t* c
     ScanPlan p{};
     const int iteration = had.iteration;
     const int asked = opt.scan_variant == 20 ? 0 : opt.scan_variant;      // 20: the scan on the matrix cores in front of the default ones
-    int variant = effective_variant(M, asked, N, K, codes, centers);
+    int variant = effective_variant(M, asked, N, K, codes, centers, had.alone);
     // No records to file for the histogram: the four-lane scan or the scan with two-lane slots whose tiles are loaded
     // straight into LDS, half a tile ahead, in the shape that the rounds favour
     // Records to file (the fused iteration at owner-path sizes): the same scan in its 4096-code shape, which files
@@ -1789,6 +1822,7 @@ pqkm_status assign_impl(const Options& opt, const Carve& c, const uint8_t* codes
 {
     if (N == 0) return PQKM_OK;
     Carried none;
+    none.alone = true;
     EventPair ev{};
     const bool prof = (opt.profile & 2) && log_begin(g_step_log, st, &ev);
     const pqkm_status s = assign_core(opt, c, codes, N, M, centers, K, tables, assign, dist, ws, st, carried ? *carried : none, link);
