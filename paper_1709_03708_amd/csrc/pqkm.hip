@@ -2088,10 +2088,10 @@ pqkm_status assign_indexed_impl(const IndexCarve& c, const uint8_t* codes, int64
 
 // Encoder: a workgroup holds the split codewords of G subspaces, as many as fit 128 KB of LDS, so that it reads whole
 // stretches of the vectors; with few vectors one subspace per workgroup, so that more workgroups share the work.
-template <int KS, int THREADS>
+template <int DP, int THREADS>
 void launch_encode(const float* vectors, int64_t N, int M, int Ds, const float* codewords, uint8_t* codes, hipStream_t st)
 {
-    constexpr int WAVES = THREADS / 64;
+    constexpr int WAVES = THREADS / 64, KS = DP <= 16 ? 1 : DP / 16;
     int G = 8 / KS;
     if (G > M) G = M;
     const int64_t tiles = (N + 31) / 32;
@@ -2103,10 +2103,10 @@ void launch_encode(const float* vectors, int64_t N, int M, int Ds, const float* 
     if (wpg > most) wpg = most;
     const dim3 grid((unsigned)(groups(G) * wpg));
     if (Ds % 4 == 0 && ((uintptr_t)vectors & 15) == 0)
-        hipLaunchKernelGGL((encode_mfma_kernel<KS, THREADS, true>), grid, dim3(THREADS), 0, st, vectors, N, M, Ds, codewords,
+        hipLaunchKernelGGL((encode_mfma_kernel<DP, THREADS, true>), grid, dim3(THREADS), 0, st, vectors, N, M, Ds, codewords,
                            codes, G, (int)wpg);
     else
-        hipLaunchKernelGGL((encode_mfma_kernel<KS, THREADS, false>), grid, dim3(THREADS), 0, st, vectors, N, M, Ds,
+        hipLaunchKernelGGL((encode_mfma_kernel<DP, THREADS, false>), grid, dim3(THREADS), 0, st, vectors, N, M, Ds,
                            codewords, codes, G, (int)wpg);
 }
 
@@ -2153,11 +2153,12 @@ pqkm_status pqkm_encode(const float* vectors, int64_t N, int32_t M, int32_t Ds, 
     if (s != PQKM_OK) return s;
     if (N == 0) return PQKM_OK;
     hipStream_t st = (hipStream_t)stream;
-    const int ks = (Ds + 15) / 16;
-    if (ks == 1) launch_encode<1, 1024>(vectors, N, M, Ds, codewords, codes, st);
-    else if (ks == 2) launch_encode<2, 1024>(vectors, N, M, Ds, codewords, codes, st);
-    else if (ks <= 4) launch_encode<4, 512>(vectors, N, M, Ds, codewords, codes, st);
-    else if (ks <= 8) launch_encode<8, 512>(vectors, N, M, Ds, codewords, codes, st);
+    if (Ds <= 4) launch_encode<4, 1024>(vectors, N, M, Ds, codewords, codes, st);
+    else if (Ds <= 8) launch_encode<8, 1024>(vectors, N, M, Ds, codewords, codes, st);
+    else if (Ds <= 16) launch_encode<16, 1024>(vectors, N, M, Ds, codewords, codes, st);
+    else if (Ds <= 32) launch_encode<32, 1024>(vectors, N, M, Ds, codewords, codes, st);
+    else if (Ds <= 64) launch_encode<64, 512>(vectors, N, M, Ds, codewords, codes, st);
+    else if (Ds <= 128) launch_encode<128, 512>(vectors, N, M, Ds, codewords, codes, st);
     else
         hipLaunchKernelGGL(encode_generic_kernel, dim3((unsigned)((N + 255) / 256), (unsigned)M), dim3(256), 0, st, vectors,
                            N, M, Ds, codewords, codes);

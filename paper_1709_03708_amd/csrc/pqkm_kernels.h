@@ -79,11 +79,13 @@ __global__ __launch_bounds__(256) void build_tables_kernel(const float* __restri
 // last way: below that every distance (at most s^2) is finite, above it the defined ones may be +inf, which is never selected.
 //
 // One wave takes 32 vectors and one subspace at a time: v_mfma_f32_32x32x16_bf16 with the codewords as rows and the
-// vectors as columns, so that a lane holds 16 codewords of one vector per instruction.  It takes the minimum of the 16,
-// keeps the three smallest such minima and the 16 values under the smallest (1.9 instructions per value; ranking every
-// value takes 6), and ranks those 16 at the end, when the two lanes of a vector merge.  The workgroup holds the split
+// vectors as columns, so that a lane holds 16 codewords of one vector per instruction.  It keeps the three smallest minima
+// over the 16 of a block, and for each of the 16 places the minimum over the blocks, whose two smallest it ranks at the end
+// (1.3 instructions per value; keeping the 16 values under the smallest minimum took 1.9, ranking every value takes 6).
+// The two lanes of a vector merge once per two tiles.  The workgroup holds the split
 // codewords of `G` subspaces in LDS (16 KB per subspace and 16 dimensions, 128 KB in all) in the order the instruction
-// reads them.  Bound by the vector units and the matrix cores about equally at 32 dimensions, by the latter above.
+// reads them.  Bound by the vector units (min3 issues every 4.2 clocks) and the matrix cores, whose times add up more than
+// they overlap: at 32 dimensions two thirds of the products left out take 0.08 of 0.24 ms.
 //
 // Open vectors: a wave settles those of two tiles together.  Up to ENC_DENSE of the 64 one by one, the codewords spread over
 // the lanes; more, and each lane forms all 256 distances of its own vector with the codewords as scalar operands, 512 flops
@@ -91,8 +93,12 @@ __global__ __launch_bounds__(256) void build_tables_kernel(const float* __restri
 // eighth time.  That is the case for data whose gaps between codewords are small against their spread (two tight clusters far
 // apart: 200000 vectors, M = 4, 32 dimensions: 0.48 ms; one by one it took 3.6 ms).
 //
-// Measured, 1e6 vectors of 128 dimensions (0.52 GB), M = 4: 1.14 ms on the vector units -> 0.26 ms; 5e5 vectors of 96
-// dimensions, M = 8: 142 ms (any length that was not compiled for) -> 0.16 ms.  200000 vectors, M = 4, 32 dimensions with a
+// Measured, 1e6 vectors of 128 dimensions (0.52 GB), M = 4: 1.14 ms on the vector units -> 0.26 ms -> 0.246 with the minima by
+// place; 5e5 vectors of 96 dimensions, M = 8: 142 ms (any length that was not compiled for) -> 0.16 ms -> 0.146.  Short
+// subvectors with the products side by side as well: 5e5 of 128 dimensions, M = 16 (8 each): 0.288 -> 0.234 ms; 3e5, M = 32
+// (4 each): 0.340 -> 0.219; 29000 of 4096, M = 32 (128 each): 0.345 -> 0.270.  Tried and taken out: two tiles per
+// read of the split codewords with 8 and 12 waves per compute unit (0.27 ms), a tile loaded ahead (spills: 0.39 ms), and the open
+// vectors settled eight at a time from a queue (1 to 5 % at 4 and 8 dimensions, 20 % slower from 64 on).  200000 vectors, M = 4, 32 dimensions with a
 // common offset of 100 times their spread: 0.25 ms on the vector units, 3.6 ms on the matrix cores without centring, 0.08 ms.
 // ---------------------------------------------------------------------------------------------
 typedef __bf16 v8bf __attribute__((ext_vector_type(8)));
@@ -123,6 +129,16 @@ __device__ __forceinline__ float low_bits(float v, uint32_t name)
     return __builtin_bit_cast(float, (__builtin_bit_cast(uint32_t, v) & 0xfffffff0u) | name);
 }
 
+// v[0] of the upper half of the wave against v[1] of the lower half: of two tiles whose vectors lie on lanes l and l + 32, the
+// lower half then holds both parts of the first tile's vectors, the upper of the second's
+__device__ __forceinline__ void trade_halves(float (&v)[2])
+{
+    const auto r = __builtin_amdgcn_permlane32_swap(__builtin_bit_cast(uint32_t, v[0]), __builtin_bit_cast(uint32_t, v[1]), false, false);
+    const uint32_t lower = r[0], upper = r[1];        // (a bit_cast of an element of a vector takes element 0, whichever is named)
+    v[0] = __builtin_bit_cast(float, lower);
+    v[1] = __builtin_bit_cast(float, upper);
+}
+
 // block: name of a block of 16 codewords, i: place in it
 __device__ __forceinline__ int encode_codeword_of(uint32_t block, uint32_t i)
 {
@@ -133,8 +149,19 @@ __device__ __forceinline__ int encode_codeword_of(uint32_t block, uint32_t i)
 __device__ __forceinline__ float encode_distance(const float* __restrict__ x, const float* __restrict__ c, int Ds)
 {
     float acc = 0.0f;
+    int d = 0;
+    for (; d + 16 <= Ds; d += 16) {                   // the loads of sixteen dimensions are in flight together
+        float a[16], b[16];
+#pragma unroll
+        for (int j = 0; j < 16; ++j) { a[j] = x[d + j]; b[j] = c[d + j]; }
+#pragma unroll
+        for (int j = 0; j < 16; ++j) {
+            const float t = a[j] - b[j];
+            acc = __builtin_fmaf(t, t, acc);
+        }
+    }
 #pragma unroll 4
-    for (int d = 0; d < Ds; ++d) {
+    for (; d < Ds; ++d) {
         const float t = x[d] - c[d];
         acc = __builtin_fmaf(t, t, acc);
     }
@@ -200,16 +227,29 @@ __device__ __forceinline__ int encode_all(const float* __restrict__ xv, const fl
 }
 
 // Grid: groups of G subspaces x `wpg` workgroups; workgroup w of a group takes the tiles of 32 vectors w * WAVES + wave,
-// + wpg * WAVES, ..., two at a time.  KS = ceil(Ds / 16); VEC: Ds is a multiple of 4 and the vectors are 16-byte aligned.
-template <int KS, int THREADS, bool VEC>
+// + wpg * WAVES, ..., two at a time.  DP: Ds rounded up to 4, 8, 16, 32, 64 or 128; VEC: Ds is a multiple of 4 and the vectors
+// are 16-byte aligned.
+//
+// From 16 dimensions on a matrix instruction takes 16 dimensions of one of the three products.  Up to 8 (DP = 4 and 8) the
+// products lie side by side in its 16 places and the rest hold |c'|^2/2 in three bf16 parts against ones:
+//   DP = 4: lower lanes xh xl | ch ch, upper lanes xh 1 1 1 0 | cl n1 n2 n3 0,
+//   DP = 8: lower lanes xh | ch, upper xl | ch, and then lower xh | cl, upper 1 1 1 0 .. | n1 n2 n3 0 ..,
+// one or two instructions per 32 codewords instead of three, and no LDS reads of the norms.  The bound above holds: no partial
+// sum is larger in this order, there are 3 Ds + 3 operands, and the three parts leave 2^-28 s^2 of the norm (the quarter covers it).
+template <int DP, int THREADS, bool VEC>
 __global__ __launch_bounds__(THREADS) void encode_mfma_kernel(const float* __restrict__ vectors, int64_t N, int M, int Ds,
                                                               const float* __restrict__ codewords,
                                                               uint8_t* __restrict__ codes, int G, int wpg)
 {
     constexpr int WAVES = THREADS / 64;
+    constexpr bool PACKED = DP <= 8;
+    constexpr int KS = PACKED ? 1 : DP / 16;          // steps of 16 dimensions
+    constexpr int XD = PACKED ? DP : 8 * KS;          // dimensions of a vector that one of its two lanes reads
+    constexpr int NF = PACKED ? DP / 4 : 2 * KS;      // fragments of 32 codewords
+    constexpr int STEP = KS <= 2 ? 2 : 1;             // blocks of 32 codewords whose values are held together
     __shared__ float4 frag[ENC_LDS_F4];
     __shared__ float hnorm[ENC_MAX_G * L];            // |c|^2 / 2
-    __shared__ float4 mid[ENC_MAX_G * 4];             // [g][KS * 16]: what both sides are centred on (8 / KS subspaces at most)
+    __shared__ float4 mid[ENC_MAX_G * 4];             // [g][DP]: what both sides are centred on (8 / KS subspaces at most)
     __shared__ uint32_t cmax[ENC_MAX_G];              // max |c|^2 as bits (non-negative: ordered like integers)
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -221,7 +261,7 @@ __global__ __launch_bounds__(THREADS) void encode_mfma_kernel(const float* __res
     float* const mu = reinterpret_cast<float*>(mid);
     if (wave < ng) {
         // wave g: subspace g
-        constexpr int PER = (KS * 16 + 63) / 64;
+        constexpr int PER = (DP + 63) / 64;
         const float* c = codewords + (size_t)(m0 + wave) * L * Ds;
 #pragma unroll
         for (int p = 0; p < PER; ++p) {
@@ -232,16 +272,39 @@ __global__ __launch_bounds__(THREADS) void encode_mfma_kernel(const float* __res
 #pragma unroll
             for (int l = 0; l < 16; ++l) sum += v[l];
             sum *= 1.0f / 16.0f;
-            if (d < KS * 16) mu[wave * (KS * 16) + d] = __builtin_fabsf(sum) < INFINITY ? sum : 0.0f;
+            if (d < DP) mu[wave * DP + d] = __builtin_fabsf(sum) < INFINITY ? sum : 0.0f;
         }
     }
     __syncthreads();
-    // fragments: [g][block of 32 codewords][k step][high, low part][lane], the negated codewords
-    for (int f = tid; f < ng * 8 * KS * 64; f += THREADS) {
+    for (int i = tid; i < ng * L; i += THREADS) {
+        const float* c = codewords + ((size_t)m0 * L + i) * Ds;
+        const float* mg = mu + (i >> 8) * DP;
+        double sum = 0.0;
+        int d = 0;
+        for (; d + 4 <= Ds; d += 4) {
+            float q[4];
+#pragma unroll
+            for (int j = 0; j < 4; ++j) q[j] = c[d + j];
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                const float v = q[j] - mg[d + j];
+                sum += (double)v * (double)v;
+            }
+        }
+        for (; d < Ds; ++d) {
+            const float v = c[d] - mg[d];
+            sum += (double)v * (double)v;
+        }
+        hnorm[i] = (float)(0.5 * sum);
+        atomicMax(&cmax[i >> 8], __builtin_bit_cast(uint32_t, (float)sum) & 0x7fffffffu);
+    }
+    if (PACKED) __syncthreads();
+    // fragments of the negated codewords: [g][block of 32 codewords][k step][high, low part][lane], or as above
+    for (int f = tid; f < ng * 8 * (PACKED ? 1 : KS) * 64; f += THREADS) {
         const int fl = f & 63, ks = (f >> 6) % KS, gb = (f >> 6) / KS;       // gb = g * 8 + block
-        const int l = (gb & 7) * 32 + (fl & 31), d0 = ks * 16 + 8 * (fl >> 5);
+        const int l = (gb & 7) * 32 + (fl & 31), d0 = PACKED ? 0 : ks * 16 + 8 * (fl >> 5);
         const float* c = codewords + ((size_t)(m0 + (gb >> 3)) * L + l) * Ds;
-        const float* mg = mu + (gb >> 3) * (KS * 16);
+        const float* mg = mu + (gb >> 3) * DP;
         v8bf hi, lo;
 #pragma unroll
         for (int j = 0; j < 8; ++j) {
@@ -249,19 +312,34 @@ __global__ __launch_bounds__(THREADS) void encode_mfma_kernel(const float* __res
             hi[j] = (__bf16)v;
             lo[j] = (__bf16)(v - (float)hi[j]);
         }
-        frag[((size_t)(gb * KS + ks) * 2) * 64 + fl] = __builtin_bit_cast(float4, hi);
-        frag[((size_t)(gb * KS + ks) * 2 + 1) * 64 + fl] = __builtin_bit_cast(float4, lo);
-    }
-    for (int i = tid; i < ng * L; i += THREADS) {
-        const float* c = codewords + ((size_t)m0 * L + i) * Ds;
-        const float* mg = mu + (i >> 8) * (KS * 16);
-        double sum = 0.0;
-        for (int d = 0; d < Ds; ++d) {
-            const float v = c[d] - mg[d];
-            sum += (double)v * (double)v;
+        if constexpr (PACKED) {
+            const float h = hnorm[(gb >> 3) * L + l];
+            __bf16 n[3];
+            float left = h;
+#pragma unroll
+            for (int p = 0; p < 3; ++p) {
+                n[p] = (__bf16)left;
+                left -= (float)n[p];
+            }
+            const bool upper = fl >> 5;
+            v8bf a = hi, b = lo;
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                const __bf16 tail = j < 3 ? n[j < 3 ? j : 0] : (__bf16)0.0f;
+                if (DP == 4) {
+                    a[j] = upper ? lo[j] : hi[j];
+                    a[j + 4] = upper ? tail : hi[j];
+                } else if (upper) {
+                    b[j] = tail;
+                    b[j + 4] = (__bf16)0.0f;
+                }
+            }
+            frag[(size_t)gb * NF * 64 + fl] = __builtin_bit_cast(float4, a);
+            if (DP == 8) frag[((size_t)gb * NF + NF - 1) * 64 + fl] = __builtin_bit_cast(float4, b);
+        } else {
+            frag[((size_t)gb * NF + 2 * ks) * 64 + fl] = __builtin_bit_cast(float4, hi);
+            frag[((size_t)gb * NF + 2 * ks + 1) * 64 + fl] = __builtin_bit_cast(float4, lo);
         }
-        hnorm[i] = (float)(0.5 * sum);
-        atomicMax(&cmax[i >> 8], __builtin_bit_cast(uint32_t, (float)sum) & 0x7fffffffu);
     }
     __syncthreads();
 
@@ -270,6 +348,23 @@ __global__ __launch_bounds__(THREADS) void encode_mfma_kernel(const float* __res
     const int64_t ntiles = (N + 31) / 32, stride = (int64_t)wpg * WAVES;
     // bit g: most vectors of subspace g were left open last time (256 codewords on a line are too close from the start)
     uint32_t hard = Ds == 1 ? 0xffffffffu : 0u, turn = 0u;
+    // the lane's part of a subvector: all of it up to 8 dimensions, else dimensions 16 ks + 8 half .. + 7
+    auto fetch = [&](int64_t tile, int g, float (&v)[XD]) __attribute__((always_inline)) {
+        const int64_t nt = tile * 32 + (lane & 31);
+        const float* xv = vectors + ((size_t)(nt < N ? nt : N - 1) * M + m0 + g) * Ds;
+#pragma unroll
+        for (int e = 0; e < XD; e += 4) {
+            const int d = PACKED ? e : (e >> 3) * 16 + 8 * half + (e & 7);
+            if (VEC) {
+                float4 q = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+                if (PACKED || d < Ds) q = *reinterpret_cast<const float4*>(xv + d);        // Ds is DP up to 8
+                v[e] = q.x; v[e + 1] = q.y; v[e + 2] = q.z; v[e + 3] = q.w;
+            } else {
+#pragma unroll
+                for (int j = 0; j < 4; ++j) v[e + j] = d + j < Ds ? xv[d + j] : 0.0f;
+            }
+        }
+    };
     for (int64_t t = (int64_t)w * WAVES + wave; t < ntiles; t += 2 * stride) {
         // the lower half of the wave ends up with the first tile's vectors, the upper with the second's
         const bool second = t + stride < ntiles;
@@ -282,116 +377,142 @@ __global__ __launch_bounds__(THREADS) void encode_mfma_kernel(const float* __res
             bool sure = true, two = false;
             // where the matrix cores leave most vectors open they are asked again only every eighth time
             const bool skip = ((hard >> g) & 1u) && (turn & 7u);
-            if (skip) sure = false;
-            // the lane's half of the subvector: dimensions 16 ks + 8 half .. + 7
-            auto fetch = [&](int i, float (&v)[KS][8]) __attribute__((always_inline)) {
-                const int64_t nt = (t + i * stride) * 32 + (lane & 31);
-                const float* xv = vectors + ((size_t)(nt < N ? nt : N - 1) * M + m0 + g) * Ds;
+            // of tile i: the three smallest minima of 16 codewords, whose low bits name the block; the two smallest minima
+            // over the blocks of the 16 places in a block, whose low bits name the place; |x'|^2
+            float m1[2], m2[2], m3[2], w1[2], w2[2], ss[2];
+            auto rank = [&](int i, float (&v)[XD]) __attribute__((always_inline)) {
+                asm volatile("" ::: "memory");        // the split codewords do not fit the registers: read them each time
+                const float4* mg = mid + g * (DP / 4) + (PACKED ? 0 : 2 * half);
+                float sum = 0.0f;
+                v8bf xh[KS], xl[KS];
 #pragma unroll
                 for (int ks = 0; ks < KS; ++ks) {
-                    const int d0 = ks * 16 + 8 * half;
-                    if (VEC) {
 #pragma unroll
-                        for (int j = 0; j < 8; j += 4) {
-                            float4 q = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
-                            if (d0 + j < Ds) q = *reinterpret_cast<const float4*>(xv + d0 + j);
-                            v[ks][j] = q.x; v[ks][j + 1] = q.y; v[ks][j + 2] = q.z; v[ks][j + 3] = q.w;
+                    for (int j = 0; j < 8; ++j) xh[ks][j] = xl[ks][j] = (__bf16)0.0f;
+#pragma unroll
+                    for (int j = 0; j < (XD < 8 ? XD : 8); j += 4) {
+                        const float4 m4 = mg[ks * 4 + j / 4];                   // 0 from Ds on
+                        const float mj[4] = {m4.x, m4.y, m4.z, m4.w};
+#pragma unroll
+                        for (int q = 0; q < 4; ++q) {
+                            const float c = v[ks * 8 + j + q] - mj[q];
+                            sum = __builtin_fmaf(c, c, sum);
+                            xh[ks][j + q] = (__bf16)c;
+                            xl[ks][j + q] = (__bf16)(c - (float)xh[ks][j + q]);
                         }
+                    }
+                }
+                if constexpr (PACKED) {
+                    // both lanes of a vector hold all of it
+                    typedef uint32_t v4u __attribute__((ext_vector_type(4)));
+                    const v4u h = __builtin_bit_cast(v4u, xh[0]), o = __builtin_bit_cast(v4u, xl[0]);
+                    v4u a, b;
+                    if (DP == 4) {
+                        a[0] = h[0]; a[1] = h[1];
+                        a[2] = half ? 0x3f803f80u : o[0]; a[3] = half ? 0x00003f80u : o[1];
+                        b = a;
                     } else {
 #pragma unroll
-                        for (int j = 0; j < 8; ++j) v[ks][j] = d0 + j < Ds ? xv[d0 + j] : 0.0f;
+                        for (int j = 0; j < 4; ++j) {
+                            a[j] = half ? o[j] : h[j];
+                            b[j] = half ? (j == 0 ? 0x3f803f80u : j == 1 ? 0x00003f80u : 0u) : h[j];
+                        }
                     }
+                    xh[0] = __builtin_bit_cast(v8bf, a);
+                    xl[0] = __builtin_bit_cast(v8bf, b);
                 }
-            };
-            auto rank = [&](int i, float (&v)[KS][8]) __attribute__((always_inline)) {
-                asm volatile("" ::: "memory");        // the split codewords do not fit the registers: read them each time
-                const float4* mg = mid + g * (KS * 4) + 2 * half;
-                v8bf xh[KS], xl[KS];
-                float ss = 0.0f;
+                float s1 = INFINITY, s2 = INFINITY, s3 = INFINITY, place[16];
 #pragma unroll
-                for (int ks = 0; ks < KS; ++ks) {
-                    const float4 ma = mg[ks * 4], mb = mg[ks * 4 + 1];          // 0 from Ds on
-                    v[ks][0] -= ma.x; v[ks][1] -= ma.y; v[ks][2] -= ma.z; v[ks][3] -= ma.w;
-                    v[ks][4] -= mb.x; v[ks][5] -= mb.y; v[ks][6] -= mb.z; v[ks][7] -= mb.w;
-#pragma unroll
-                    for (int j = 0; j < 8; ++j) {
-                        ss = __builtin_fmaf(v[ks][j], v[ks][j], ss);
-                        xh[ks][j] = (__bf16)v[ks][j];
-                        xl[ks][j] = (__bf16)(v[ks][j] - (float)xh[ks][j]);
-                    }
-                }
-                ss = ss + __shfl_xor(ss, 32);
-                float m1 = INFINITY, m2 = INFINITY, m3 = INFINITY;    // smallest minima of 16, the low bits name the block
-                float kept[16];
-#pragma unroll
-                for (int j = 0; j < 16; ++j) kept[j] = INFINITY;
+                for (int j = 0; j < 16; ++j) place[j] = INFINITY;
                 const float4* hn = reinterpret_cast<const float4*>(hnorm + g * L) + half;
-                const float4* fr = frag + (size_t)g * 8 * KS * 2 * 64 + lane;
+                const float4* fr = frag + (size_t)g * 8 * NF * 64 + lane;
 #pragma unroll
-                for (int b = 0; b < 8; ++b) {
-                    v16f acc;
+                for (int b0 = 0; b0 < 8; b0 += STEP) {
+                    v16f acc[STEP];
 #pragma unroll
-                    for (int j = 0; j < 4; ++j) {
-                        const float4 h4 = hn[b * 8 + 2 * j];
-                        acc[4 * j] = h4.x; acc[4 * j + 1] = h4.y; acc[4 * j + 2] = h4.z; acc[4 * j + 3] = h4.w;
+                    for (int q = 0; q < STEP; ++q) {
+                        const int b = b0 + q;
+                        if constexpr (PACKED) {
+#pragma unroll
+                            for (int j = 0; j < 16; ++j) acc[q][j] = 0.0f;
+                            acc[q] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(v8bf, fr[b * NF * 64]), xh[0], acc[q], 0, 0, 0);
+                            if (DP == 8)
+                                acc[q] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(v8bf, fr[(b * NF + NF - 1) * 64]), xl[0], acc[q], 0, 0, 0);
+                        } else {
+#pragma unroll
+                            for (int j = 0; j < 4; ++j) {
+                                const float4 h4 = hn[b * 8 + 2 * j];
+                                acc[q][4 * j] = h4.x; acc[q][4 * j + 1] = h4.y; acc[q][4 * j + 2] = h4.z; acc[q][4 * j + 3] = h4.w;
+                            }
+#pragma unroll
+                            for (int ks = 0; ks < KS; ++ks) {
+                                const v8bf ch = __builtin_bit_cast(v8bf, fr[(b * NF + 2 * ks) * 64]);
+                                const v8bf cl = __builtin_bit_cast(v8bf, fr[(b * NF + 2 * ks + 1) * 64]);
+                                acc[q] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(cl, xh[ks], acc[q], 0, 0, 0);
+                                acc[q] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ch, xl[ks], acc[q], 0, 0, 0);
+                                acc[q] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ch, xh[ks], acc[q], 0, 0, 0);
+                            }
+                        }
                     }
 #pragma unroll
-                    for (int ks = 0; ks < KS; ++ks) {
-                        const v8bf ch = __builtin_bit_cast(v8bf, fr[((b * KS + ks) * 2) * 64]);
-                        const v8bf cl = __builtin_bit_cast(v8bf, fr[((b * KS + ks) * 2 + 1) * 64]);
-                        acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(cl, xh[ks], acc, 0, 0, 0);
-                        acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ch, xl[ks], acc, 0, 0, 0);
-                        acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ch, xh[ks], acc, 0, 0, 0);
+                    for (int q = 0; q < STEP; ++q) {
+                        const v16f& r = acc[q];
+                        const float u0 = minimum3(r[0], r[1], r[2]), u1 = minimum3(r[3], r[4], r[5]);
+                        const float u2 = minimum3(r[6], r[7], r[8]), u3 = minimum3(r[9], r[10], r[11]);
+                        const float u4 = minimum3(r[12], r[13], r[14]);
+                        const float e = low_bits(minimum3(minimum3(u0, u1, u2), minimum3(u3, u4, r[15]), u0), (uint32_t)(b0 + q));
+                        s3 = __builtin_amdgcn_fmed3f(s2, s3, e);
+                        s2 = __builtin_amdgcn_fmed3f(s1, s2, e);
+                        s1 = __builtin_elementwise_minimum(s1, e);
                     }
-                    const float u0 = minimum3(acc[0], acc[1], acc[2]), u1 = minimum3(acc[3], acc[4], acc[5]);
-                    const float u2 = minimum3(acc[6], acc[7], acc[8]), u3 = minimum3(acc[9], acc[10], acc[11]);
-                    const float u4 = minimum3(acc[12], acc[13], acc[14]);
-                    const float e = low_bits(minimum3(minimum3(u0, u1, u2), minimum3(u3, u4, acc[15]), u0), (uint32_t)b);
-                    const bool better = e < m1;
-                    m3 = __builtin_amdgcn_fmed3f(m2, m3, e);
-                    m2 = __builtin_amdgcn_fmed3f(m1, m2, e);
-                    m1 = better ? e : m1;
 #pragma unroll
-                    for (int j = 0; j < 16; ++j) kept[j] = better ? acc[j] : kept[j];
+                    for (int j = 0; j < 16; ++j) place[j] = minimum3(place[j], acc[0][j], acc[STEP - 1][j]);
                 }
-                // the two smallest of the lane's best block; the low bits name the place in it
-                float w1 = INFINITY, w2 = INFINITY;
+                float p1 = INFINITY, p2 = INFINITY;
 #pragma unroll
                 for (int j = 0; j < 16; ++j) {
-                    const float v = low_bits(kept[j], (uint32_t)j);
-                    w2 = __builtin_amdgcn_fmed3f(w1, w2, v);
-                    w1 = min_f32(w1, v);
+                    const float p = low_bits(place[j], (uint32_t)j);
+                    p2 = __builtin_amdgcn_fmed3f(p1, p2, p);
+                    p1 = __builtin_elementwise_minimum(p1, p);
                 }
-                // bit 3 of a block's name: which lane of the two
-                auto mark = [&](float v) { return __builtin_bit_cast(float, __builtin_bit_cast(uint32_t, v) | ((uint32_t)half << 3)); };
-                m1 = mark(m1); m2 = mark(m2); m3 = mark(m3);
-                const float o1 = __shfl_xor(m1, 32), o2 = __shfl_xor(m2, 32), o3 = __shfl_xor(m3, 32);
-                const float p1 = __shfl_xor(w1, 32), p2 = __shfl_xor(w2, 32);
-                const float a1 = __builtin_fminf(m1, o1);
-                const float a2 = __builtin_fminf(__builtin_fmaxf(m1, o1), __builtin_fminf(m2, o2));
-                const float a3 = __builtin_fminf(__builtin_fminf(m3, o3), __builtin_fminf(__builtin_fmaxf(m1, o2), __builtin_fmaxf(m2, o1)));
-                const bool mine = ((__builtin_bit_cast(uint32_t, a1) >> 3) & 1u) == (uint32_t)half;
-                const float b1 = mine ? w1 : p1, b2 = mine ? w2 : p2;
-                const float s = (__builtin_amdgcn_sqrtf(ss) + __builtin_amdgcn_sqrtf(__builtin_bit_cast(float, cmax[g]))) * 1.0001f;
+                // the results are formed here: moved to their use behind the branches below, they would keep 128 values alive
+                asm volatile("" : "+v"(s1), "+v"(s2), "+v"(s3), "+v"(p1), "+v"(p2), "+v"(sum));
+                m1[i] = s1; m2[i] = s2; m3[i] = s3; w1[i] = p1; w2[i] = p2; ss[i] = sum;
+            };
+            if (skip) {
+                sure = false;
+            } else {
+                float v[XD];
+                fetch(t, g, v);
+                rank(0, v);
+                if (second) {
+                    fetch(t + stride, g, v);
+                    rank(1, v);
+                } else {
+                    m1[1] = m2[1] = m3[1] = w1[1] = w2[1] = ss[1] = 0.0f;
+                }
+                // [0]: what the lower half of the wave held of the lane's vector, [1]: the upper
+                trade_halves(m1); trade_halves(m2); trade_halves(m3); trade_halves(w1); trade_halves(w2); trade_halves(ss);
+                // bit 3 of a block's name: which half
+                auto mark = [](float x) { return __builtin_bit_cast(float, __builtin_bit_cast(uint32_t, x) | 8u); };
+                m1[1] = mark(m1[1]); m2[1] = mark(m2[1]); m3[1] = mark(m3[1]);
+                const float a1 = __builtin_fminf(m1[0], m1[1]);
+                const float a2 = __builtin_fminf(__builtin_fmaxf(m1[0], m1[1]), __builtin_fminf(m2[0], m2[1]));
+                const float a3 = __builtin_fminf(__builtin_fminf(m3[0], m3[1]),
+                                                 __builtin_fminf(__builtin_fmaxf(m1[0], m2[1]), __builtin_fmaxf(m2[0], m1[1])));
+                n1 = __builtin_bit_cast(uint32_t, a1);
+                n2 = __builtin_bit_cast(uint32_t, a2);
+                const bool upper = (n1 >> 3) & 1u;
+                const float b1 = upper ? w1[1] : w1[0], b2 = upper ? w2[1] : w2[0];
+                const float xx = PACKED ? ss[0] : ss[0] + ss[1];
+                const float s = (__builtin_amdgcn_sqrtf(xx) + __builtin_amdgcn_sqrtf(__builtin_bit_cast(float, cmax[g]))) * 1.0001f;
                 const float lim = a1 + (kappa * s * s + 1e-30f);
                 const bool finite = s < 1e19f;
-                if (half == i) {
-                    n1 = __builtin_bit_cast(uint32_t, a1);
-                    n2 = __builtin_bit_cast(uint32_t, a2);
-                    sure = a2 > lim && b2 > lim && finite;            // false when anything overflowed or is NaN
-                    two = a3 > lim && finite;
-                    bl = encode_codeword_of(n1, __builtin_bit_cast(uint32_t, b1) & 15u);
-                }
-            };
-            if (!skip) {
-                float v0[KS][8], v1[KS][8];
-                fetch(0, v0);
-                if (KS <= 2 && second) fetch(1, v1);
-                rank(0, v0);
-                if (second) {
-                    if (KS > 2) fetch(1, v1);
-                    rank(1, v1);
-                }
+                // One block and one place can hold a value up to the limit: it is the smallest, and the only one.  (A place
+                // of another block is above the limit with its block.)  false when anything overflowed or is NaN.
+                sure = a2 > lim && b2 > lim && finite;
+                two = a3 > lim && finite;
+                bl = encode_codeword_of(n1, __builtin_bit_cast(uint32_t, b1) & 15u);
             }
             const float* cw = codewords + (size_t)(m0 + g) * L * Ds;
             uint64_t rest = __ballot(!sure && live);
@@ -413,10 +534,10 @@ __global__ __launch_bounds__(THREADS) void encode_mfma_kernel(const float* __res
                 float best = INFINITY;
                 int bi = IDX_NONE;
                 if (__builtin_amdgcn_readlane((int)two, v)) {
-                    const uint32_t v1 = (uint32_t)__builtin_amdgcn_readlane((int)n1, v);
-                    const uint32_t v2 = (uint32_t)__builtin_amdgcn_readlane((int)n2, v);
+                    const uint32_t c1 = (uint32_t)__builtin_amdgcn_readlane((int)n1, v);
+                    const uint32_t c2 = (uint32_t)__builtin_amdgcn_readlane((int)n2, v);
                     if (lane < 32) {
-                        const int l = encode_codeword_of(lane < 16 ? v1 : v2, (uint32_t)lane & 15u);
+                        const int l = encode_codeword_of(lane < 16 ? c1 : c2, (uint32_t)lane & 15u);
                         const float d = encode_distance(xr, cw + (size_t)l * Ds, Ds);
                         if (d < best) { best = d; bi = l; }
                     }
