@@ -1830,11 +1830,28 @@ pqkm_status assign_impl(const Options& opt, const Carve& c, const uint8_t* codes
     return s;
 }
 
-// counting sort of the code indices by cluster into the workspace: start[0..K] and sidx[0..#valid)
-void sort_by_cluster(const int32_t* assign, int64_t N, int K, const Carve& c, char* ws, uint32_t** start_out,
-                     uint32_t** sidx_out, hipStream_t st, bool ranked = false)
+template <int PER>
+void launch_seg_scatter(const int32_t* assign, int64_t N, int K, const SegKey& sk, const uint32_t* start, uint32_t* cursor, uint32_t* sidx,
+                        const SegZero& z, hipStream_t st)
 {
+    const unsigned blocks = (unsigned)((N + 1024 * PER - 1) / (1024 * PER));
+    if (K <= 8192)
+        hipLaunchKernelGGL((seg_scatter_block_kernel<PER, 8192>), dim3(blocks + (unsigned)z.groups), dim3(1024), 0, st, assign, N, K,
+                           sk, start, cursor, sidx, blocks, z);
+    else
+        hipLaunchKernelGGL((seg_scatter_block_kernel<PER, SEG_BLOCK_MAX_K>), dim3(blocks + (unsigned)z.groups), dim3(1024), 0, st,
+                           assign, N, K, sk, start, cursor, sidx, blocks, z);
+}
+
+// counting sort of the code indices by cluster, or by group of KT clusters, into the workspace: start[0..K] and sidx[0..#valid); and
+// seg_zero for every group
+void sort_by_cluster(const int32_t* assign, int64_t N, int K, const Carve& c, char* ws, uint32_t** start_out,
+                     uint32_t** sidx_out, hipStream_t st, bool ranked = false, const SegZero& z = SegZero{}, int KT = 1, int bits = 32)
+{
+    // sorted by group of KT clusters, K is the number of groups from here on
+    const SegKey sk{(uint32_t)K, (uint32_t)KT, KT > 1 ? (uint32_t)(((uint64_t)1 << 32) / (uint32_t)KT) + 1u : 0u, bits};
     const size_t seg_stride = align256(((size_t)K + 1) * sizeof(uint32_t));
+    K = (K + KT - 1) / KT;
     uint32_t* sidx = reinterpret_cast<uint32_t*>(ws + c.sidx_off);
     uint32_t* cnt = reinterpret_cast<uint32_t*>(ws + c.seg_off);
     uint32_t* start = reinterpret_cast<uint32_t*>(ws + c.seg_off + seg_stride);
@@ -1846,21 +1863,29 @@ void sort_by_cluster(const int32_t* assign, int64_t N, int K, const Carve& c, ch
         const uint32_t* rank = reinterpret_cast<const uint32_t*>(ws + c.rank_off);
         hipLaunchKernelGGL(seg_prefix_kernel, dim3(1), dim3(1024), 0, st, cnt, K, start, cursor);
         hipLaunchKernelGGL(seg_place_kernel, dim3(sb), dim3(256), 0, st, assign, rank, N, K, start, sidx);
+        if (z.groups > 0) hipLaunchKernelGGL(seg_zero_kernel, dim3((unsigned)z.groups), dim3(256), 0, st, z, start);
         *start_out = start;
         *sidx_out = sidx;
         return;
     }
     unsigned zb = (unsigned)((K + 255) / 256 < 1024 ? (K + 255) / 256 : 1024);
     hipLaunchKernelGGL(zero_u32_kernel, dim3(zb), dim3(256), 0, st, cnt, (int64_t)K);
-    unsigned cb = (unsigned)((N + 4095) / 4096 < 1024 ? (N + 4095) / 4096 : 1024);
+    // 8192 codes or more per workgroup: every one adds its K sizes to the sums
+    unsigned cb = (unsigned)((N + 8191) / 8192 < 512 ? (N + 8191) / 8192 : 512);
     if (cb < 1) cb = 1;
-    hipLaunchKernelGGL(seg_count_kernel, dim3(cb), dim3(1024), 0, st, assign, N, K, cnt);
+    hipLaunchKernelGGL(seg_count_kernel, dim3(cb), dim3(1024), 0, st, assign, N, K, sk, cnt);
     hipLaunchKernelGGL(seg_prefix_kernel, dim3(1), dim3(1024), 0, st, cnt, K, start, cursor);
-    if (K <= SEG_BLOCK_MAX_K)
-        hipLaunchKernelGGL(seg_scatter_block_kernel, dim3((unsigned)((N + SEG_BLOCK - 1) / SEG_BLOCK)), dim3(1024), 0, st, assign,
-                           N, K, start, cursor, sidx);
-    else
-        hipLaunchKernelGGL(seg_scatter_kernel, dim3(sb), dim3(256), 0, st, assign, N, K, start, cursor, sidx);
+    if (K <= SEG_BLOCK_MAX_K) {
+        // about one block per compute unit: fewer leave some idle, more pay for K more sizes each
+        const int64_t per = (N + 1023) / 1024 / cu_count();
+        if (per < 2) launch_seg_scatter<2>(assign, N, K, sk, start, cursor, sidx, z, st);
+        else if (per < 4) launch_seg_scatter<4>(assign, N, K, sk, start, cursor, sidx, z, st);
+        else if (per < 8) launch_seg_scatter<8>(assign, N, K, sk, start, cursor, sidx, z, st);
+        else launch_seg_scatter<16>(assign, N, K, sk, start, cursor, sidx, z, st);
+    } else {
+        hipLaunchKernelGGL(seg_scatter_kernel, dim3(sb), dim3(256), 0, st, assign, N, sk, start, cursor, sidx);
+        if (z.groups > 0) hipLaunchKernelGGL(seg_zero_kernel, dim3((unsigned)z.groups), dim3(256), 0, st, z, start);
+    }
     *start_out = start;
     *sidx_out = sidx;
 }
@@ -1997,7 +2022,6 @@ pqkm_status update_impl(const Options& opt, const Carve& c, const uint8_t* codes
     } else if (path == HIST_SORTED) {
         // sorted path: counting sort of the code indices by cluster, then LDS histograms per stretch of clusters
         uint32_t *start, *sidx;
-        sort_by_cluster(assign, N, K, c, static_cast<char*>(ws), &start, &sidx, st, link && link->ranked);
         // 64 KB of counters per workgroup, two workgroups per compute unit: half the grain of a round (128 KB: 1.04 to 1.16 times the
         // update at M = 4, 6, 8, 16).  From M = 32 on that is one or two clusters, and with few codes in each the workgroups' own cost
         // shows: M = 48, N = 3e5, K = 1500: 301 us against 282 with 128 KB where they are even, 277 against 307 where they are tight.
@@ -2012,14 +2036,22 @@ pqkm_status update_impl(const Options& opt, const Carve& c, const uint8_t* codes
         const int64_t further = ng > 1 ? N / most : 0;
         const size_t seg_stride = align256(((size_t)K + 1) * sizeof(uint32_t));
         uint2* items = reinterpret_cast<uint2*>(static_cast<char*>(ws) + c.seg_off);
-        uint32_t* listed = reinterpret_cast<uint32_t*>(static_cast<char*>(ws) + c.seg_off + 2 * seg_stride) + K;
-        if (further > 0)
-            hipLaunchKernelGGL(seg_zero_kernel, dim3((unsigned)ng), dim3(256), 0, st, start, M, K, KT, most, hist, listed, items);
+        uint32_t* cursor = reinterpret_cast<uint32_t*>(static_cast<char*>(ws) + c.seg_off + 2 * seg_stride);
+        // Sorted by group only, where the scan has not left ranks and a place in the group fits beside the index: as many
+        // counters as groups in the sort, longer stretches of a block's codes in its stores, no search for the cluster.
+        const bool ranked = link && link->ranked;
+        int bits = 32;
+        while ((KT - 1) >> (32 - bits)) --bits;
+        if (ranked || KT == 1 || N > ((int64_t)1 << bits) || K > (1 << 24)) bits = 32;
+        uint32_t* const listed = cursor + (bits < 32 ? ng : K);        // behind the keys' cursors
+        sort_by_cluster(assign, N, K, c, static_cast<char*>(ws), &start, &sidx, st, ranked,
+                        further > 0 ? SegZero{(int)ng, M, K, KT, bits < 32 ? 1 : KT, most, hist, listed, items} : SegZero{},
+                        bits < 32 ? KT : 1, bits);
         if (hist_words == SEG_HIST_WORDS)
-            hipLaunchKernelGGL((seg_hist_kernel<SEG_HIST_WORDS>), dim3((unsigned)(ng + further)), dim3(1024), 0, st, codes, M, start, sidx, K, KT,
+            hipLaunchKernelGGL((seg_hist_kernel<SEG_HIST_WORDS>), dim3((unsigned)(ng + further)), dim3(1024), 0, st, codes, M, bits, start, sidx, K, KT,
                                further > 0 ? most : 0xffffffffu, (int)ng, listed, items, hist);
         else
-            hipLaunchKernelGGL((seg_hist_kernel<HIST_LDS_WORDS>), dim3((unsigned)(ng + further)), dim3(1024), 0, st, codes, M, start, sidx, K, KT,
+            hipLaunchKernelGGL((seg_hist_kernel<HIST_LDS_WORDS>), dim3((unsigned)(ng + further)), dim3(1024), 0, st, codes, M, bits, start, sidx, K, KT,
                                further > 0 ? most : 0xffffffffu, (int)ng, listed, items, hist);
     } else {
         zero_hist();

@@ -3766,7 +3766,21 @@ __global__ __launch_bounds__(256) void histogram_atomic_kernel(const uint8_t* __
 // ---------------------------------------------------------------------------------------------
 constexpr int SEG_COUNT_LDS_K = 16384;      // cluster sizes are counted in LDS up to this many clusters
 
-__global__ __launch_bounds__(1024) void seg_count_kernel(const int32_t* __restrict__ assign, int64_t N, int K,
+// What the codes are sorted by: their cluster (KT = 1), or its group of KT clusters, where the index keeps the place in the group
+// in the bits from `bits` on.  inv = 2^32 / KT + 1: exact for fewer than 2^32 / KT clusters.
+struct SegKey {
+    uint32_t K, KT, inv;
+    int bits;
+    __device__ __forceinline__ bool valid(int k) const { return (uint32_t)k < K; }
+    __device__ __forceinline__ uint32_t key(int k) const { return KT == 1u ? (uint32_t)k : __umulhi((uint32_t)k, inv); }
+    __device__ __forceinline__ uint32_t index(int k, int64_t n) const
+    {
+        return KT == 1u ? (uint32_t)n : (uint32_t)n | ((uint32_t)k - key(k) * KT) << bits;
+    }
+};
+
+// sizes of K keys
+__global__ __launch_bounds__(1024) void seg_count_kernel(const int32_t* __restrict__ assign, int64_t N, int K, SegKey sk,
                                                          uint32_t* __restrict__ cnt)
 {
     __shared__ uint32_t h[SEG_COUNT_LDS_K];
@@ -3775,9 +3789,14 @@ __global__ __launch_bounds__(1024) void seg_count_kernel(const int32_t* __restri
         for (int k = threadIdx.x; k < K; k += 1024) h[k] = 0u;
         __syncthreads();
     }
-    for (int64_t i = (int64_t)blockIdx.x * 1024 + threadIdx.x; i < N; i += (int64_t)gridDim.x * 1024) {
-        const int k = assign[i];
-        if ((unsigned)k < (unsigned)K) atomicAdd(lds ? &h[k] : &cnt[k], 1u);
+    constexpr int PER = 8;                               // codes per thread whose loads travel together
+    for (int64_t i = (int64_t)blockIdx.x * (1024 * PER) + threadIdx.x; i < N; i += (int64_t)gridDim.x * (1024 * PER)) {
+        int k[PER];
+#pragma unroll
+        for (int u = 0; u < PER; ++u) k[u] = i + u * 1024 < N ? assign[i + u * 1024] : -1;
+#pragma unroll
+        for (int u = 0; u < PER; ++u)
+            if (sk.valid(k[u])) atomicAdd(lds ? &h[sk.key(k[u])] : &cnt[sk.key(k[u])], 1u);
     }
     if (lds) {
         __syncthreads();
@@ -3786,78 +3805,142 @@ __global__ __launch_bounds__(1024) void seg_count_kernel(const int32_t* __restri
     }
 }
 
-// one workgroup: start[0..K] = exclusive prefix of cnt, cursor[0..K) = 0
+// one workgroup: start[0..K] = exclusive prefix of cnt, cursor[0..K) = 0.  The sizes of four rounds are loaded together.
 __global__ __launch_bounds__(1024) void seg_prefix_kernel(const uint32_t* __restrict__ cnt, int K,
                                                           uint32_t* __restrict__ start, uint32_t* __restrict__ cursor)
 {
-    __shared__ uint32_t wsum[16];
-    __shared__ uint32_t carry;
-    const int tid = threadIdx.x;
-    if (tid == 0) carry = 0u;
-    __syncthreads();
-    for (int k0 = 0; k0 < K; k0 += 1024) {
-        const int k = k0 + tid;
-        const uint32_t v = k < K ? cnt[k] : 0u;
-        const uint32_t inc = wave_inclusive_scan(v);
-        if ((tid & 63) == 63) wsum[tid >> 6] = inc;
-        __syncthreads();
-        uint32_t e = carry + inc - v;
-        for (int w = 0; w < (tid >> 6); ++w) e += wsum[w];
-        if (k < K) {
-            start[k] = e;
-            cursor[k] = 0u;
+    constexpr int PER = 4;
+    __shared__ uint32_t wsum[2][PER][16];
+    const int tid = threadIdx.x, wave = tid >> 6;
+    uint32_t carry = 0u;
+    int turn = 0;
+    for (int k0 = 0; k0 < K; k0 += 1024 * PER, turn ^= 1) {
+        uint32_t v[PER], inc[PER];
+#pragma unroll
+        for (int i = 0; i < PER; ++i) v[i] = k0 + i * 1024 + tid < K ? cnt[k0 + i * 1024 + tid] : 0u;
+#pragma unroll
+        for (int i = 0; i < PER; ++i) {
+            inc[i] = wave_inclusive_scan(v[i]);
+            if ((tid & 63) == 63) wsum[turn][i][wave] = inc[i];
         }
-        __syncthreads();
-        if (tid == 1023) carry = e + v;
-        __syncthreads();
+        __syncthreads();                             // (the other half of wsum is written next: one barrier per round)
+#pragma unroll
+        for (int i = 0; i < PER; ++i) {
+            uint32_t e = carry + inc[i] - v[i];
+#pragma unroll
+            for (int w = 0; w < 16; ++w) {
+                e += w < wave ? wsum[turn][i][w] : 0u;
+                carry += wsum[turn][i][w];
+            }
+            const int k = k0 + i * 1024 + tid;
+            if (k < K) {
+                start[k] = e;
+                cursor[k] = 0u;
+            }
+        }
     }
     if (tid == 0) {
         start[K] = carry;
-        cursor[K] = 0u;                  // counts the shares that seg_zero_kernel lists
+        cursor[K] = 0u;                  // counts the shares that seg_zero lists
     }
 }
 
-__global__ __launch_bounds__(256) void seg_scatter_kernel(const int32_t* __restrict__ assign, int64_t N, int K,
+__global__ __launch_bounds__(256) void seg_scatter_kernel(const int32_t* __restrict__ assign, int64_t N, SegKey sk,
                                                           const uint32_t* __restrict__ start,
                                                           uint32_t* __restrict__ cursor, uint32_t* __restrict__ sidx)
 {
     for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < N; i += (int64_t)gridDim.x * 256) {
         const int k = assign[i];
-        if ((unsigned)k < (unsigned)K) sidx[start[k] + atomicAdd(&cursor[k], 1u)] = (uint32_t)i;
+        if (sk.valid(k)) sidx[start[sk.key(k)] + atomicAdd(&cursor[sk.key(k)], 1u)] = sk.index(k, i);
     }
 }
 
-// The same with one global atomic per (block, cluster) instead of one per code, which clusters of uneven size slow down by
-// their contention: a block ranks its SEG_BLOCK codes inside their clusters in LDS, reserves their places, and writes.
-// Measured, 2e6 codes of a mixture, K = 5000: 615 us -> 22 us.
-constexpr int SEG_BLOCK_PER = 16, SEG_BLOCK = 1024 * SEG_BLOCK_PER;
+__device__ __forceinline__ uint32_t seg_shares(uint32_t codes, uint32_t most)
+{
+    return codes <= most ? 1u : (codes - 1) / most + 1u;
+}
+
+// what the histogram of the sorted codes needs cleared and listed (groups = 0: nothing)
+struct SegZero {
+    int groups, M, K, KT, step;       // `start` holds a group every `step` entries: KT, or 1 where the groups are the keys
+    uint32_t most;
+    uint32_t* hist;
+    uint32_t* count;
+    uint2* items;
+};
+
+// One workgroup, group b: clears its histograms if it is shared and lists its further shares, (group, share) in `items`, at most
+// (number of codes) / most in all.
+__device__ __forceinline__ void seg_zero(const SegZero& z, int b, const uint32_t* __restrict__ start, uint32_t* at)
+{
+    const int k0 = b * z.KT;
+    const int nk = z.K - k0 < z.KT ? z.K - k0 : z.KT;
+    const uint32_t* s = start + (size_t)b * z.step;
+    const uint32_t shares = seg_shares(s[z.step == 1 ? 1 : nk] - s[0], z.most);
+    if (shares == 1u) return;
+    if (threadIdx.x == 0) *at = atomicAdd(z.count, shares - 1u);
+    __syncthreads();
+    for (uint32_t i = threadIdx.x; i < shares - 1u; i += blockDim.x) z.items[*at + i] = make_uint2((uint32_t)b, i + 1u);
+    uint32_t* out = z.hist + (size_t)k0 * z.M * L;
+    for (int i = threadIdx.x; i < nk * z.M * L; i += blockDim.x) out[i] = 0u;
+}
+
+__global__ __launch_bounds__(256) void seg_zero_kernel(SegZero z, const uint32_t* __restrict__ start)
+{
+    __shared__ uint32_t at;
+    seg_zero(z, blockIdx.x, start, &at);
+}
+
+// The scatter with one global atomic per (block, cluster) instead of one per code, which clusters of uneven size slow down by
+// their contention: a block ranks its 1024 PER codes inside their clusters in LDS, reserves their places, and writes.  The
+// launcher takes the PER that gives every compute unit a block.  The workgroups behind the first `blocks` do seg_zero's work
+// meanwhile.  Measured, 2e6 codes of a mixture, K = 5000: 615 us -> 22 us with blocks of 16384 and seg_zero in a launch of its own
+// (5 us) -> 17 us for both with blocks of 8192 and the 625 groups of eight clusters in the place of the clusters.
 constexpr int SEG_BLOCK_MAX_K = 32768;
 
-__global__ __launch_bounds__(1024) void seg_scatter_block_kernel(const int32_t* __restrict__ assign, int64_t N, int K,
+template <int PER, int LDS_K>
+__global__ __launch_bounds__(1024) void seg_scatter_block_kernel(const int32_t* __restrict__ assign, int64_t N, int K, SegKey sk,
                                                                  const uint32_t* __restrict__ start,
-                                                                 uint32_t* __restrict__ cursor, uint32_t* __restrict__ sidx)
+                                                                 uint32_t* __restrict__ cursor, uint32_t* __restrict__ sidx,
+                                                                 unsigned blocks, SegZero z)
 {
-    __shared__ uint32_t h[SEG_BLOCK_MAX_K];
-    const int64_t n0 = (int64_t)blockIdx.x * SEG_BLOCK + threadIdx.x;
-    int k[SEG_BLOCK_PER];
-    uint32_t r[SEG_BLOCK_PER];
+    __shared__ uint32_t h[LDS_K];
+    if (blockIdx.x >= blocks) {
+        seg_zero(z, (int)(blockIdx.x - blocks), start, h);
+        return;
+    }
+    const int64_t n0 = (int64_t)blockIdx.x * (1024 * PER) + threadIdx.x;
+    int k[PER];
+    uint32_t r[PER];
 #pragma unroll
-    for (int i = 0; i < SEG_BLOCK_PER; ++i) {
+    for (int i = 0; i < PER; ++i) {
         const int64_t n = n0 + i * 1024;
         k[i] = n < N ? assign[n] : -1;
     }
     for (int i = threadIdx.x; i < K; i += 1024) h[i] = 0u;
     __syncthreads();
 #pragma unroll
-    for (int i = 0; i < SEG_BLOCK_PER; ++i)
-        if ((unsigned)k[i] < (unsigned)K) r[i] = atomicAdd(&h[k[i]], 1u);
+    for (int i = 0; i < PER; ++i)
+        if (sk.valid(k[i])) r[i] = atomicAdd(&h[sk.key(k[i])], 1u);
     __syncthreads();
-    for (int i = threadIdx.x; i < K; i += 1024)
-        if (h[i]) h[i] = start[i] + atomicAdd(&cursor[i], h[i]);
+    constexpr int R = 4;                             // reservations of a thread that travel together
+    for (int i0 = threadIdx.x; i0 < K; i0 += 1024 * R) {
+        uint32_t c[R], at[R];
+#pragma unroll
+        for (int j = 0; j < R; ++j) c[j] = i0 + 1024 * j < K ? h[i0 + 1024 * j] : 0u;
+#pragma unroll
+        for (int j = 0; j < R; ++j) at[j] = c[j] ? start[i0 + 1024 * j] : 0u;
+#pragma unroll
+        for (int j = 0; j < R; ++j)
+            if (c[j]) c[j] = atomicAdd(&cursor[i0 + 1024 * j], c[j]);
+#pragma unroll
+        for (int j = 0; j < R; ++j)
+            if (i0 + 1024 * j < K) h[i0 + 1024 * j] = at[j] + c[j];
+    }
     __syncthreads();
 #pragma unroll
-    for (int i = 0; i < SEG_BLOCK_PER; ++i)
-        if ((unsigned)k[i] < (unsigned)K) sidx[h[k[i]] + r[i]] = (uint32_t)(n0 + i * 1024);
+    for (int i = 0; i < PER; ++i)
+        if (sk.valid(k[i])) sidx[h[sk.key(k[i])] + r[i]] = sk.index(k[i], n0 + i * 1024);
 }
 
 // the scatter when the scan has left every code's rank inside its cluster: no atomics, one pass
@@ -3878,7 +3961,7 @@ __global__ __launch_bounds__(256) void seg_place_kernel(const int32_t* __restric
 // seg_zero_kernel lists (a grid of groups x shares would be nearly all empty workgroups of 128 KB of LDS: 60 to 80 us at
 // K = 30000).  Bound by the LDS atomics and by the rounds of workgroups: 64 KB of counters each, two workgroups per compute unit.
 // Measured, 2e6 codes of a mixture, M = 8, K = 5000: 98 us with 128 KB and the subspaces in the same order in all lanes, 52 with 64 KB and
-// words turned by lane one by one, now 40.
+// words turned by lane one by one, 40 with the search for the cluster, now 37; the whole update 142 -> 118.
 // The counters of a code that is read as words (M a multiple of 4), starting with another subspace in each lane: lanes of one
 // cluster often hold the same subcode, and 64 of them adding to one LDS word are served one after the other.  Lane l takes the
 // bytes of a word from l mod 4 on, the words of a chunk of CW from (l / 4) mod CW on and the chunks of a code from l / (4 CW) on, so
@@ -3928,31 +4011,9 @@ struct HistTurn {
         }
     }
 };
-__device__ __forceinline__ uint32_t seg_shares(uint32_t codes, uint32_t most)
-{
-    return codes <= most ? 1u : (codes - 1) / most + 1u;
-}
-
-// clears the histograms of the groups that are shared and lists their further shares: (group, share) in `items`, at most
-// (number of codes) / most
-__global__ __launch_bounds__(256) void seg_zero_kernel(const uint32_t* __restrict__ start, int M, int K, int KT, uint32_t most,
-                                                       uint32_t* __restrict__ hist, uint32_t* __restrict__ count,
-                                                       uint2* __restrict__ items)
-{
-    __shared__ uint32_t at;
-    const int k0 = blockIdx.x * KT;
-    const int nk = K - k0 < KT ? K - k0 : KT;
-    const uint32_t shares = seg_shares(start[k0 + nk] - start[k0], most);
-    if (shares == 1u) return;
-    if (threadIdx.x == 0) at = atomicAdd(count, shares - 1u);
-    __syncthreads();
-    for (uint32_t i = threadIdx.x; i < shares - 1u; i += 256) items[at + i] = make_uint2(blockIdx.x, i + 1u);
-    uint32_t* out = hist + (size_t)k0 * M * L;
-    for (int i = threadIdx.x; i < nk * M * L; i += 256) out[i] = 0u;
-}
-
+// bits < 32: the codes are sorted by group only, and an index holds the place in the group from there on.
 template <int LDS_WORDS>
-__global__ __launch_bounds__(1024) void seg_hist_kernel(const uint8_t* __restrict__ codes, int M,
+__global__ __launch_bounds__(1024) void seg_hist_kernel(const uint8_t* __restrict__ codes, int M, int bits,
                                                         const uint32_t* __restrict__ start,
                                                         const uint32_t* __restrict__ sidx, int K, int KT, uint32_t most,
                                                         int groups, const uint32_t* __restrict__ count,
@@ -3971,27 +4032,33 @@ __global__ __launch_bounds__(1024) void seg_hist_kernel(const uint8_t* __restric
     const int k0 = (int)group * KT;
     const int nk = K - k0 < KT ? K - k0 : KT;
     const int words = nk * M * L;
-    const uint32_t first = start[k0], last = start[k0 + nk];
+    const bool grouped = bits < 32;
+    const uint32_t first = start[grouped ? group : (uint32_t)k0], last = start[grouped ? group + 1u : (uint32_t)(k0 + nk)];
     const uint32_t shares = seg_shares(last - first, most);
-    for (int i = tid; i < words; i += 1024) lh[i] = 0u;
-    for (int i = tid; i <= nk; i += 1024) st[i] = start[k0 + i];
-    __syncthreads();
     const uint32_t share = (last - first + shares - 1) / shares;
     const uint32_t p0 = first + part * share;
     const uint32_t p1 = last - p0 < share ? last : p0 + share;
-    const bool wordwise = (M & 3) == 0 && ((uintptr_t)codes & 3) == 0;
-    // the cluster of position p: the last kk with st[kk] <= p
-    auto cluster_of = [&](uint64_t p) {
-        int kk = 0;
-        for (int step = 64; step >= 1; step >>= 1)
-            if (kk + step < nk && st[kk + step] <= p) kk += step;
-        return kk;
-    };
-    // four positions of the sorted indices per thread whose loads travel together
+    // four positions of the sorted indices per thread whose loads travel together; the first are under way while LDS is cleared
     constexpr int PER = 4;
     auto positions = [&](uint64_t pb, uint32_t (&n)[PER]) {
 #pragma unroll
         for (int i = 0; i < PER; ++i) n[i] = sidx[pb + i * 1024 < p1 ? pb + i * 1024 : pb];
+    };
+    uint32_t n[PER] = {0u, 0u, 0u, 0u};
+    if ((uint64_t)p0 + tid < p1) positions((uint64_t)p0 + tid, n);
+    if (!grouped)
+        for (int i = tid; i <= nk; i += 1024) st[i] = start[k0 + i];
+    for (int i = tid; i < words; i += 1024) lh[i] = 0u;
+    __syncthreads();
+    const bool wordwise = (M & 3) == 0 && ((uintptr_t)codes & 3) == 0;
+    const uint32_t mask = grouped ? (1u << bits) - 1u : 0xffffffffu;
+    // the cluster of index n at position p: the last kk with st[kk] <= p where the codes are sorted by cluster
+    auto cluster_of = [&](uint64_t p, uint32_t n) {
+        if (grouped) return (int)(n >> bits);
+        int kk = 0;
+        for (int step = 64; step >= 1; step >>= 1)
+            if (kk + step < nk && st[kk + step] <= p) kk += step;
+        return kk;
     };
     if (wordwise) {
         // chunks of CW words, S of them of C codes in flight
@@ -4000,8 +4067,7 @@ __global__ __launch_bounds__(1024) void seg_hist_kernel(const uint8_t* __restric
             typedef typename HistTurn<CW>::Chunk Chunk;
             const HistTurn<CW> turn(M, tid & 63);
             for (uint64_t pb = (uint64_t)p0 + tid; pb < p1; pb += 1024 * PER) {
-                uint32_t n[PER];
-                positions(pb, n);
+                if (pb >= (uint64_t)p0 + 1024 * PER) positions(pb, n);
 #pragma unroll
                 for (int g = 0; g < PER; g += C) {
                     for (int c = 0; c < turn.chunks; c += S) {
@@ -4011,12 +4077,12 @@ __global__ __launch_bounds__(1024) void seg_hist_kernel(const uint8_t* __restric
                             if (c + q < turn.chunks)
 #pragma unroll
                                 for (int i = 0; i < C; ++i)
-                                    v[q][i] = *reinterpret_cast<const Chunk*>(codes + (size_t)n[g + i] * M + turn.chunk(c + q) * (4 * CW));
+                                    v[q][i] = *reinterpret_cast<const Chunk*>(codes + (size_t)(n[g + i] & mask) * M + turn.chunk(c + q) * (4 * CW));
 #pragma unroll
                         for (int i = 0; i < C; ++i) {
                             const uint64_t p = pb + (g + i) * 1024;
                             if (p >= p1) break;
-                            uint32_t* h = lh + cluster_of(p) * M * L;
+                            uint32_t* h = lh + cluster_of(p, n[g + i]) * M * L;
 #pragma unroll
                             for (int q = 0; q < S; ++q)
                                 if (c + q < turn.chunks) turn.count(h, turn.chunk(c + q), v[q][i]);
@@ -4039,13 +4105,12 @@ __global__ __launch_bounds__(1024) void seg_hist_kernel(const uint8_t* __restric
         }
     } else {
         for (uint64_t pb = (uint64_t)p0 + tid; pb < p1; pb += 1024 * PER) {
-            uint32_t n[PER];
-            positions(pb, n);
+            if (pb >= (uint64_t)p0 + 1024 * PER) positions(pb, n);
 #pragma unroll
             for (int i = 0; i < PER; ++i) {
                 if (pb + i * 1024 >= p1) break;
-                const uint8_t* x = codes + (size_t)n[i] * M;
-                uint32_t* h = lh + cluster_of(pb + i * 1024) * M * L;
+                const uint8_t* x = codes + (size_t)(n[i] & mask) * M;
+                uint32_t* h = lh + cluster_of(pb + i * 1024, n[i]) * M * L;
                 for (int m = 0; m < M; ++m) atomicAdd(&h[m * L + x[m]], 1u);
             }
         }
