@@ -134,10 +134,21 @@ HistPlan hist_plan(int64_t N, int M, int K)
 // which any was slower, up to 9 %); M = 4: 230 / 192 at 2e6, 5000; M = 8: 179 / 176 at 1e6, 4000, 214 / 202 at 3e6, 2000; M = 16: 241 /
 // 198 at 3e6, 1000; M = 24: 251 / 245 at 1e6, 1200; M = 48: 250 / 204 at 1e6, 500.  Uneven clusters: 640 / 165, 598 / 171, 788 / 181,
 // 1187 / 210, 2052 / 214, 1975 / 240, 3254 / 227.  Tight ones: M = 4: 355 / 164; M = 8: 415 / 159; M = 16: 1076 / 222.
-inline bool sorted_histogram_pays(const HistPlan& hp, int64_t N)
+// Sorted by group, which came later, the line lies lower, from 1e5 codes and 8000 histograms of a subspace on (4800 from M = 16 on).  Even
+// clusters, owner / sorted: M = 4: 113 / 96 at 1e6, 3000, 104 / 102 at 2e6, 2000, but 79 / 88 at 1e6, 1200; M = 8: 66 / 63 at 3e5, 1000, 88 / 87
+// at 1e6, 1000, but 134 / 139 at 3e6, 600; M = 12: 70 / 76 at 3e5, 500; M = 16: 61 / 63 at 1e5, 300, 96 / 94 at 1e6, 300, 152 / 136 at 1e6,
+// 1000, but 51 / 67 at 6e5, 100; M = 32: 119 / 101 at 3e5, 300, 116 / 108 at 1e6, 150; byte by byte M = 6: 99 / 119 at 1e6, 800.  Uneven
+// ones at the same sizes: 174 / 95, 290 / 111 (157 / 87); 107 / 75, 221 / 94 (573 / 165); (118 / 87); 77 / 65, 346 / 104, 599 / 138 (184 /
+// 81); 221 / 107, 563 / 128; (272 / 144).  Not in the fits whose lower-bound scans keep their keys in the sorted indices' room (`keys`).
+inline bool sorted_histogram_pays(const HistPlan& hp, int64_t N, int M, int K, bool keys)
 {
-    return hp.groups > 100 && (double)hp.groups * (double)N > 2.2e8 && N <= (int64_t)0xffffffff;
+    if (N > (int64_t)0xffffffff) return false;
+    if (!keys && N >= 100000 && (M & 3) == 0 && (int64_t)K * M >= (M < 16 ? 8000 : 4800)) return true;
+    return hp.groups > 100 && (double)hp.groups * (double)N > 2.2e8;
 }
+
+// are a fit's lower-bound scans of the kind that keeps keys by position of a code?
+inline bool scans_keep_keys(int M) { return M == 4 || M == 8; }
 
 // does the histogram take the LDS-privatised owner path for this problem (and the call's options)?
 bool owner_histogram(const HistPlan& hp, int force)
@@ -1178,13 +1189,13 @@ SubspaceHist subspace_hist(int64_t N, int M, int K, const Carve& c)
 // How the update counts its histograms: from the records of the fused iteration (`linked`), per cluster group, per group of
 // subspaces, from the indices sorted by cluster, or by global atomics.
 enum HistPath { HIST_RECORDS, HIST_OWNER, HIST_SUBSPACE, HIST_SORTED, HIST_ATOMIC };
-HistPath hist_path(int64_t N, int M, int K, const Carve& c, int force, bool linked)
+HistPath hist_path(int64_t N, int M, int K, const Carve& c, int force, bool linked, bool keys)
 {
     const HistPlan hp = hist_plan(N, M, K);
     if (owner_histogram(hp, force)) {
         if (linked) return HIST_RECORDS;
         if (force == 0 && subspace_hist(N, M, K, c).G > 0) return HIST_SUBSPACE;
-        if (force != 0 || !sorted_histogram_pays(hp, N)) return HIST_OWNER;
+        if (force != 0 || !sorted_histogram_pays(hp, N, M, K, keys)) return HIST_OWNER;
     }
     return force != 1 && N <= (int64_t)0xffffffff && N > 0 ? HIST_SORTED : HIST_ATOMIC;
 }
@@ -1388,7 +1399,7 @@ ScanPlan scan_plan(int M, const Options& opt, int64_t N, int K, const uint8_t* c
     if (p.filter) p.seeded = iteration == 0 ? (K >= FILTER_PAIRS_MIN_K ? 3 : 0) : had.keys && p.reuse ? 2 : 1;
     // the keys stay unless the update uses their room (that of the sorted path, and of the arrays of HIST_SUBSPACE); of the scans with
     // keys only M = 4's 63 files records
-    const HistPath path = hist_path(N, M, K, c, opt.hist_kernel, files_records && variant == 63 && one);
+    const HistPath path = hist_path(N, M, K, c, opt.hist_kernel, files_records && variant == 63 && one, scans_keep_keys(M));
     const bool keys_survive = c.state_off != c.sidx_off || path == HIST_RECORDS || path == HIST_OWNER;
     p.leaves.iteration = iteration + 1;
     p.leaves.lanes = one ? p.lanes : 0;
@@ -1957,7 +1968,8 @@ pqkm_status update_impl(const Options& opt, const Carve& c, const uint8_t* codes
     int S = 1;
     size_t part_stride = 0;
     uint32_t* parts = hist;
-    const HistPath path = hist_path(N, M, K, c, force, link && link->produced && link->KT == hp.KT && link->ngroups == (int)hp.groups);
+    const HistPath path = hist_path(N, M, K, c, force, link && link->produced && link->KT == hp.KT && link->ngroups == (int)hp.groups,
+                                    link && scans_keep_keys(M));
     const bool linked = path == HIST_RECORDS;
     if (linked && M == 4 && hp.KT <= VOTE_REC_KT && link->nwg <= VOTE_REC_SEGS) {
         // the scan of this iteration filed (code, center) records by cluster group, and a vote workgroup can take
