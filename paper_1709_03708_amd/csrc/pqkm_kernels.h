@@ -276,7 +276,7 @@ __global__ __launch_bounds__(THREADS) void encode_mfma_kernel(const float* __res
         }
     }
     __syncthreads();
-    for (int i = tid; i < ng * L; i += THREADS) {
+    for (int i = tid; !PACKED && i < ng * L; i += THREADS) {
         const float* c = codewords + ((size_t)m0 * L + i) * Ds;
         const float* mg = mu + (i >> 8) * DP;
         double sum = 0.0;
@@ -298,7 +298,6 @@ __global__ __launch_bounds__(THREADS) void encode_mfma_kernel(const float* __res
         hnorm[i] = (float)(0.5 * sum);
         atomicMax(&cmax[i >> 8], __builtin_bit_cast(uint32_t, (float)sum) & 0x7fffffffu);
     }
-    if (PACKED) __syncthreads();
     // fragments of the negated codewords: [g][block of 32 codewords][k step][high, low part][lane], or as above
     for (int f = tid; f < ng * 8 * (PACKED ? 1 : KS) * 64; f += THREADS) {
         const int fl = f & 63, ks = (f >> 6) % KS, gb = (f >> 6) / KS;       // gb = g * 8 + block
@@ -306,16 +305,18 @@ __global__ __launch_bounds__(THREADS) void encode_mfma_kernel(const float* __res
         const float* c = codewords + ((size_t)(m0 + (gb >> 3)) * L + l) * Ds;
         const float* mg = mu + (gb >> 3) * DP;
         v8bf hi, lo;
+        double sum = 0.0;
 #pragma unroll
         for (int j = 0; j < 8; ++j) {
             const float v = d0 + j < Ds ? mg[d0 + j] - c[d0 + j] : 0.0f;
+            if (PACKED) sum += (double)v * (double)v;
             hi[j] = (__bf16)v;
             lo[j] = (__bf16)(v - (float)hi[j]);
         }
         if constexpr (PACKED) {
-            const float h = hnorm[(gb >> 3) * L + l];
+            if (fl < 32) atomicMax(&cmax[gb >> 3], __builtin_bit_cast(uint32_t, (float)sum) & 0x7fffffffu);
             __bf16 n[3];
-            float left = h;
+            float left = (float)(0.5 * sum);
 #pragma unroll
             for (int p = 0; p < 3; ++p) {
                 n[p] = (__bf16)left;
