@@ -1163,11 +1163,12 @@ inline bool variant_lds_loads(int M, int variant) { return M == 4 && variant >= 
 inline bool variant_sliding(int M, int variant) { return (M == 16 || M == 32) && variant >= 50 && variant <= 59; }
 
 // Histogram with all clusters of G subspaces in a workgroup's LDS (G = 0: not taken): about one workgroup per compute unit,
-// slices of at least 2048 codes, at most the 16 partial arrays the vote adds, in the room of the sorted path.
-struct SubspaceHist { int G, S; };
+// slices of at least 2048 codes, at most 64, whose partial arrays fit the room of the sorted path: of 16-bit counters (halves) where
+// that leaves no more codes per slice than they count.
+struct SubspaceHist { int G, S; bool halves; };
 SubspaceHist subspace_hist(int64_t N, int M, int K, const Carve& c)
 {
-    SubspaceHist p{0, 1};
+    SubspaceHist p{0, 1, false};
     // Every workgroup reads a word of every code of its slice, whatever M is, and leaves K G KB for the vote to add; the owner
     // path reads a byte per code and group, but a heavy cluster is the work of one of its workgroups.  Clusters of even size, whole
     // update, owner / this, us: M = 4, K = 100: 42 / 54 at N = 5e5, 54 / 57 at 1e6, 104 / 87 at 3e6; M = 8, K = 100: 60 / 72 at
@@ -1178,9 +1179,17 @@ SubspaceHist subspace_hist(int64_t N, int M, int K, const Carve& c)
     if (!(K >= 32 && M >= 4 && M <= 16 && N >= (int64_t)300000 * M) && !(K < 32 && M >= 16 && N >= 1000000)) return p;
     p.G = 1;
     while (p.G < 4 && p.G * 2 <= M && (int64_t)K * L * p.G * 2 <= SUBSPACE_HIST_WORDS) p.G *= 2;
-    const int64_t room = (int64_t)(c.seg_off - c.sidx_off) / (int64_t)align256(c.hist_bytes);
     const int64_t groups = (M + p.G - 1) / p.G;
-    while (p.S < 16 && p.S * 2 <= room && groups * p.S * 2 <= cu_count() && N / (p.S * 2) >= 2048) p.S *= 2;
+    auto slices = [&](size_t part_bytes) {
+        const int64_t room = (int64_t)(c.seg_off - c.sidx_off) / (int64_t)align256(part_bytes);
+        const int64_t most[] = {room, cu_count() / groups, N / 2048, 64};
+        int64_t S = most[0];
+        for (int64_t x : most) S = x < S ? x : S;
+        return (int)(S < 1 ? 1 : S);
+    };
+    p.S = slices((size_t)K * M * L * sizeof(uint16_t));
+    p.halves = p.S > 1 && ((N + p.S - 1) / p.S + 1023) / 1024 * 1024 <= SUBSPACE_HALF_CODES;
+    if (!p.halves) p.S = slices((size_t)K * M * L * sizeof(uint32_t));
     // with fewer slices (no room for their arrays) the chip is half idle: M = 4, K = 128, N = 1e6: 70 us with 8
     if (K >= 32 && p.S < 16) p.G = 0;
     return p;
@@ -1966,6 +1975,7 @@ pqkm_status update_impl(const Options& opt, const Carve& c, const uint8_t* codes
     const HistPlan hp = hist_plan(N, M, K);
     const int force = opt.hist_kernel;
     int S = 1;
+    bool halves = false;
     size_t part_stride = 0;
     uint32_t* parts = hist;
     const HistPath path = hist_path(N, M, K, c, force, link && link->produced && link->KT == hp.KT && link->ngroups == (int)hp.groups,
@@ -1982,7 +1992,7 @@ pqkm_status update_impl(const Options& opt, const Carve& c, const uint8_t* codes
     }
     if (!linked && force == 0 && vote_few_counts_codes(N, M, K, codes)) {
         hipLaunchKernelGGL((vote_few_kernel<VOTE_CODES>), dim3((unsigned)((int64_t)K * ((M + 3) / 4))), dim3(VOTE_FEW_THREADS), 0, st, hist, hist, 1,
-                           (size_t)0, counts, K, M, tables, centers, VoteRecords{nullptr, nullptr, 0, codes, assign, N});
+                           (size_t)0, false, counts, K, M, tables, centers, VoteRecords{nullptr, nullptr, 0, codes, assign, N});
         return launched();
     }
     if (!linked && force == 0 && vote_counts_codes(N, M, K)) {
@@ -2011,10 +2021,14 @@ pqkm_status update_impl(const Options& opt, const Carve& c, const uint8_t* codes
         S = sh.S;
         if (S > 1) {
             parts = reinterpret_cast<uint32_t*>(static_cast<char*>(ws) + c.sidx_off);
-            part_stride = align256(c.hist_bytes) / sizeof(uint32_t);
+            part_stride = align256((size_t)nh * (sh.halves ? sizeof(uint16_t) : sizeof(uint32_t))) / sizeof(uint32_t);
         }
-        hipLaunchKernelGGL(histogram_subspace_kernel, dim3((unsigned)((M + sh.G - 1) / sh.G * S)), dim3(1024), 0, st, codes, N, M,
-                           assign, K, sh.G, S, parts, part_stride);
+        halves = sh.halves;
+        const dim3 grid((unsigned)((M + sh.G - 1) / sh.G * S));
+        if (halves)
+            hipLaunchKernelGGL((histogram_subspace_kernel<true>), grid, dim3(1024), 0, st, codes, N, M, assign, K, sh.G, S, parts, part_stride);
+        else
+            hipLaunchKernelGGL((histogram_subspace_kernel<false>), grid, dim3(1024), 0, st, codes, N, M, assign, K, sh.G, S, parts, part_stride);
     } else if (path == HIST_OWNER) {
         S = hp.S;
         if (S > 1) {
@@ -2074,9 +2088,10 @@ pqkm_status update_impl(const Options& opt, const Carve& c, const uint8_t* codes
                                codes + n0 * M, cnt, M, assign + n0, K, hist);
         }
     }
+    // (HIST_SUBSPACE is always of few clusters: at most 128 KB of counters per subspace and 16 subspaces, or 31 clusters)
     if (vote_few(N, M, K)) {
         hipLaunchKernelGGL((vote_few_kernel<VOTE_PARTS>), dim3((unsigned)((int64_t)K * ((M + 3) / 4))), dim3(256), 0, st, hist, parts, S, part_stride,
-                           counts, K, M, tables, centers, VoteRecords{});
+                           halves, counts, K, M, tables, centers, VoteRecords{});
         return launched();
     }
     // vote: one workgroup per (subspace, CW clusters); about a thousand workgroups, at least one cluster per wave

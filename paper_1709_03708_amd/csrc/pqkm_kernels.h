@@ -4129,11 +4129,16 @@ __global__ __launch_bounds__(1024) void seg_hist_kernel(const uint8_t* __restric
 // Eq. 7, few centers: the histograms of `G` subspaces of ALL clusters fit a workgroup's LDS (K * G KB <= 128 KB), so
 // workgroup (g, s) takes subspaces g*G .. g*G+G-1 and slice s of the codes, reads assignment and subcodes of each code
 // once and counts.  No pass that names cluster groups, no search for members, and heavy clusters are spread over the
-// slices.  Slices of S > 1 leave partial arrays that the vote adds.  Measured, 1.28e6 codes, M = 4, K = 100: 84 us (the
-// owner path below with its group bytes) -> 31 us.
+// slices.  Slices of S > 1 leave partial arrays that the vote adds: 16-bit counters where a slice has at most SUBSPACE_HALF_CODES
+// codes (HALF; a word holds bins i and i + 128), so that twice as many slices fit the room for them and the vote reads.  Bound by
+// the LDS atomics and loads of a slice: 16 slices of four subspaces kept a quarter of the compute units busy.  Measured, 1.28e6
+// codes, M = 4, K = 100: 84 us (the owner path below with its group bytes) -> 30 with 16 slices -> 17 with 49, and
+// the vote that adds them 13 -> 15.
 // ---------------------------------------------------------------------------------------------
 constexpr int SUBSPACE_HIST_WORDS = 32768;
+constexpr int SUBSPACE_HALF_CODES = 64512;      // whole rounds of 1024 below 65536
 
+template <bool HALF>
 __global__ __launch_bounds__(1024) void histogram_subspace_kernel(const uint8_t* __restrict__ codes, int64_t N, int M,
                                                                   const int32_t* __restrict__ assign, int K, int G, int S,
                                                                   uint32_t* __restrict__ parts, size_t part_stride)
@@ -4175,9 +4180,18 @@ __global__ __launch_bounds__(1024) void histogram_subspace_kernel(const uint8_t*
     }
     __syncthreads();
     uint32_t* out = parts + (size_t)s * part_stride;
-    for (int i = tid; i < K * nm * L; i += 1024) {
-        const int k = i / (nm * L), e = i % (nm * L);
-        out[((size_t)k * M + m0) * L + e] = h[k * G * L + e];
+    if constexpr (HALF) {
+        for (int i = tid; i < K * nm * (L / 2); i += 1024) {
+            const int row = i / (L / 2), e = i % (L / 2);
+            const int k = row / nm, m = row % nm;
+            const uint32_t* hr = h + (k * G + m) * L + e;
+            out[((size_t)k * M + m0 + m) * (L / 2) + e] = hr[0] | hr[L / 2] << 16;
+        }
+    } else {
+        for (int i = tid; i < K * nm * L; i += 1024) {
+            const int k = i / (nm * L), e = i % (nm * L);
+            out[((size_t)k * M + m0) * L + e] = h[k * G * L + e];
+        }
     }
 }
 
@@ -4655,8 +4669,8 @@ constexpr int VOTE_FEW_THREADS = 512;    // 1024 would leave 128 registers, too 
 
 template <VoteFrom FROM>
 __global__ __launch_bounds__(FROM == VOTE_CODES ? VOTE_FEW_THREADS : 256) void vote_few_kernel(
-    uint32_t* __restrict__ hist, const uint32_t* __restrict__ parts, int S, size_t part_stride, uint32_t* __restrict__ counts,
-    int K, int M, const float* __restrict__ tables, uint8_t* __restrict__ centers, VoteRecords vr)
+    uint32_t* __restrict__ hist, const uint32_t* __restrict__ parts, int S, size_t part_stride, bool halves,
+    uint32_t* __restrict__ counts, int K, int M, const float* __restrict__ tables, uint8_t* __restrict__ centers, VoteRecords vr)
 {
     static_assert(FROM != VOTE_RECORDS, "from partial histograms or from all codes");
     __shared__ uint32_t bins[FROM == VOTE_CODES ? 4 * L : 1];
@@ -4706,7 +4720,24 @@ __global__ __launch_bounds__(FROM == VOTE_CODES ? VOTE_FEW_THREADS : 256) void v
         } else {
 #pragma unroll
             for (int ch = 0; ch < 4; ++ch) h[ch] = 0u;
-            for (int u0 = 0; u0 < S; u0 += 8) {
+            if (halves) {
+                // words of bins i and i + 128
+                const size_t word = pair * (L / 2) + lane;
+                for (int u0 = 0; u0 < S; u0 += 16) {
+                    uint32_t t[16][2];
+#pragma unroll
+                    for (int u = 0; u < 16; ++u)
+#pragma unroll
+                        for (int ch = 0; ch < 2; ++ch) t[u][ch] = parts[(size_t)(u0 + u < S ? u0 + u : S - 1) * part_stride + word + ch * 64];
+#pragma unroll
+                    for (int u = 0; u < 16; ++u)
+#pragma unroll
+                        for (int ch = 0; ch < 2; ++ch) {
+                            h[ch] += u0 + u < S ? t[u][ch] & 0xffffu : 0u;
+                            h[ch + 2] += u0 + u < S ? t[u][ch] >> 16 : 0u;
+                        }
+                }
+            } else for (int u0 = 0; u0 < S; u0 += 8) {
                 uint32_t t[8][4];
 #pragma unroll
                 for (int u = 0; u < 8; ++u)
