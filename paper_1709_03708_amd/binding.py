@@ -74,24 +74,33 @@ def workspace_bytes(N: int, M: int, K: int) -> int:
     return int(load().pqkm_workspace_bytes(int(N), int(M), int(K)))
 
 
+# A call of a few codes takes as long as this marshalling: the kernel of 48 codes and 1000 centers 3.4 us, the call 9.3 us with a
+# c_void_p made per pointer (argtypes convert plain integers and None by themselves), a Stream object per call, an import of
+# torch per operand and shapes copied to compare them, 6.4 without.
+_tensor = None
+
+
 def _ptr(t):
-    return ctypes.c_void_p(t.data_ptr()) if t is not None else ctypes.c_void_p(0)
+    return t.data_ptr() if t is not None else None
 
 
 def _stream():
     import torch
 
-    return ctypes.c_void_p(torch.cuda.current_stream().cuda_stream)
+    return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device())
 
 
 def _need(t, dtype, shape, name):
-    import torch
-
+    global _tensor
     if t is None:
         return
-    if not isinstance(t, torch.Tensor) or not t.is_cuda or not t.is_contiguous():
+    if _tensor is None:
+        import torch
+
+        _tensor = torch.Tensor
+    if not isinstance(t, _tensor) or not t.is_cuda or not t.is_contiguous():
         raise TypeError(f"{name}: expected a contiguous CUDA tensor")
-    if t.dtype != dtype or tuple(t.shape) != tuple(shape):
+    if t.dtype != dtype or t.shape != shape:
         raise TypeError(f"{name}: expected {dtype} {tuple(shape)}, got {t.dtype} {tuple(t.shape)}")
 
 
