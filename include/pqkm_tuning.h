@@ -80,13 +80,25 @@ pqkm_status pqkm_scan_plan(int64_t N, int32_t M, int32_t K, int32_t iteration, i
 
 /*
  * pqkm_dot_scan: the scan on the matrix cores in front of an LDS-tiled scan or one through lower bounds, for aligned operands, a call that
- * asks for no distances, and the options as they are.  Where pqkm_scan_plan names one lane per center, whether that is preceded by it is not
- * reported here (the event log counts two scan kernels then).
+ * asks for no distances, and the options as they are.  Where pqkm_scan_plan names one lane per center, pqkm_call_plan says whether that is
+ * preceded by it.
  *   workspace   that of a pqkm_assign or pqkm_fit call for these N, M, K, or NULL; with it the call waits for the device
  *   out         host, int32[2]: 0 whether the scan is tried first; 1 with a workspace, and where it is tried: whether the last
  *               assignment step there was left to the scans behind it, which pqkm_scan_plan names (1) or not (0), else -1
  */
 pqkm_status pqkm_dot_scan(int64_t N, int32_t M, int32_t K, const void *workspace, int32_t out[2]);
+
+/*
+ * pqkm_call_plan: what one pqkm_assign and one pqkm_update call by themselves run under the options as they are: host arithmetic, as
+ * pqkm_scan_plan.
+ *   flags  1: codes, 2: centers that are not 4-byte aligned; 4: distances are asked for
+ *   out    host, int64[8]: 0 the scan as pqkm_scan_plan names it; 1 its number, or for one lane per center whether the table rows go
+ *          through the caches (0) or LDS (1), or a lane takes a code (2); 2 dimensions up to which the scan on the matrix cores is tried first
+ *          (0 = it is not); 3 codes per block and 4 parts of the centers (one lane per center); 5 how the update counts: 1 = per group
+ *          of clusters, 2 = per group of subspaces, 3 = from indices sorted by cluster, 4 = global atomics, or in the vote, 5 = a workgroup
+ *          per cluster, 6 = per sixteen clusters; 6 its slices of the codes; 7 whether the vote takes a workgroup per cluster
+ */
+pqkm_status pqkm_call_plan(int64_t N, int32_t M, int32_t K, int32_t flags, int64_t out[8]);
 
 #ifdef __cplusplus
 }

@@ -56,11 +56,12 @@ def load():
         lib.pqkm_decode.argtypes = [vp, i64, i32, i32, vp, vp, vp]
         lib.pqkm_set_option.argtypes = [ctypes.c_char_p, i32]
         lib.pqkm_scan_plan.argtypes = [i64, i32, i32, i32, ctypes.POINTER(i64)]
+        lib.pqkm_call_plan.argtypes = [i64, i32, i32, i32, ctypes.POINTER(i64)]
         lib.pqkm_dot_scan.argtypes = [i64, i32, i32, vp, ctypes.POINTER(i32)]
         lib.pqkm_profile_read.argtypes = [ctypes.POINTER(ctypes.c_double), ctypes.POINTER(i64)]
         lib.pqkm_profile_read_steps.argtypes = [ctypes.POINTER(ctypes.c_double), ctypes.POINTER(i64)]
         for n in ("pqkm_build_tables", "pqkm_assign", "pqkm_assign_noalloc", "pqkm_assign_indexed", "pqkm_check", "pqkm_update", "pqkm_fit", "pqkm_fit_until", "pqkm_set_option",
-                  "pqkm_scan_plan", "pqkm_dot_scan", "pqkm_profile_read", "pqkm_profile_read_steps", "pqkm_encode", "pqkm_decode", "pqkm_update_naive"):
+                  "pqkm_scan_plan", "pqkm_call_plan", "pqkm_dot_scan", "pqkm_profile_read", "pqkm_profile_read_steps", "pqkm_encode", "pqkm_decode", "pqkm_update_naive"):
             getattr(lib, n).restype = ctypes.c_int
         _lib = lib
     return _lib
@@ -349,6 +350,19 @@ def scan_plan(N: int, M: int, K: int, iteration: int = 0) -> dict:
     out = (ctypes.c_int64 * 6)()
     _check(load().pqkm_scan_plan(int(N), int(M), int(K), int(iteration), out), "pqkm_scan_plan")
     return dict(zip(("scan", "variant", "per_launch", "lanes", "reuse", "seeded"), (int(v) for v in out)))
+
+
+_SCANS = ("one_lane_per_center", "tiled", "lower_bounds")
+_COUNTS = (None, "cluster_groups", "subspaces", "sorted", "atomics", "vote_per_cluster", "vote")
+
+
+def call_plan(N: int, M: int, K: int, codes_aligned: bool = True, centers_aligned: bool = True, dist: bool = False) -> dict:
+    """What one assign() and one update() call by themselves run (host arithmetic, see pqkm_tuning.h)."""
+    out = (ctypes.c_int64 * 8)()
+    flags = (0 if codes_aligned else 1) | (0 if centers_aligned else 2) | (4 if dist else 0)
+    _check(load().pqkm_call_plan(int(N), int(M), int(K), flags, out), "pqkm_call_plan")
+    plan = dict(zip(("scan", "variant", "dot", "codes", "parts", "count", "slices", "vote_per_cluster"), (int(v) for v in out)))
+    return dict(plan, scan=_SCANS[plan["scan"]], count=_COUNTS[plan["count"]], vote_per_cluster=bool(plan["vote_per_cluster"]))
 
 
 def dot_scan(N: int, M: int, K: int, workspace=None) -> dict:

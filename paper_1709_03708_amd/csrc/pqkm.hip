@@ -1714,30 +1714,60 @@ bool tiled_scan(const Options& opt, int64_t N, int M, int K, const uint8_t* code
     return opt.assign_kernel != 0 || opt.scan_variant != 0 || N > gather_max_codes(M, K);
 }
 
+// What the scan with one lane per center does with N codes (one lane per code where `per_code`).
+struct GatherPlan {
+    bool words;               // codes and centers are read as words
+    bool rows;                // the rows of a block's codes are copied to LDS
+    bool per_code;
+    int codes;                // per block
+    int64_t parts;            // that the centers are split into
+};
+
+// room: for the records of the parts; `whole`: it is in use, so that the centers stay in one part
+GatherPlan gather_plan(int64_t N, int M, int K, bool aligned, size_t room, bool whole)
+{
+    GatherPlan p{};
+    p.words = tiled_M(M) && aligned;
+    p.rows = K >= gather_rows_min_k(M, p.words);
+    p.codes = 1;
+    p.parts = 1;
+    if (!p.words && lane_per_code(N, M, K)) {
+        p.per_code = true;
+        return p;
+    }
+    // Codes per block: one while that fills the chip no more than four times, then what shares the centers' words best.  us, M = 4: N = 500,
+    // K = 1000: 3.6 / 3.9 / 4.4 / 6.2 with 1, 2, 4, 8; N = 1e4: 15.3 / 13.0 / 12.0 / 14.2; M = 8: 4.0 / 4.3 / 5.3 and 21.9 / 19.8 / 19.4 (K =
+    // 100: 12.6 / 9.9 / 11.1) with 1, 2, 4; M = 16: 5.2 / 5.4 and 36.3 / 35.3 (K = 100: 17.1 / 19.2) with 1, 2.
+    if (p.words && N > 4 * (int64_t)cu_count()) p.codes = M == 4 ? 4 : M == 8 ? 2 : 1;
+    const int64_t blocks = (N + p.codes - 1) / p.codes;
+    const int64_t passes = ((int64_t)K + 255) / 256;               // of a block over its centers
+    if (whole || blocks < 1) return p;
+    if (p.words && p.rows) {
+        // A pass takes 60 ns + 10 ns M, the second launch and the records 2.5 us: M = 4, one code per block, us: 48 codes, K = 4096:
+        // 4.6 in one, 5.6 in sixteen parts; 4 codes, K = 50000: 22 and 6.2; M = 32, 48 codes: 5.4 and 6.4 at K = 1000, 9.8 and 7.7 at 4096.
+        p.parts = (double)passes * (0.06 + 0.01 * M) > 3.0 ? 2 * (int64_t)cu_count() / blocks : 1;
+        if (p.parts > passes / 4) p.parts = passes / 4;
+    } else {
+        // about eight blocks per compute unit, as long as each keeps 256 centers
+        p.parts = 8 * (int64_t)cu_count() / blocks;
+        if (p.parts > passes) p.parts = passes;
+    }
+    // the records fit their room
+    if (p.parts > (int64_t)(room / sizeof(NearRecord)) / N) p.parts = (int64_t)(room / sizeof(NearRecord)) / N;
+    if (p.parts < 1) p.parts = 1;
+    return p;
+}
+
 template <int MW, int CN>
-pqkm_status launch_gather(const uint8_t* codes, int64_t N, int M, const uint8_t* centers, int K, const float* tables,
-                          int32_t* assign, float* dist, NearRecord* part, size_t room, const uint32_t* only_if, hipStream_t st)
+pqkm_status launch_gather(const GatherPlan& plan, const uint8_t* codes, int64_t N, int M, const uint8_t* centers, int K, const float* tables,
+                          int32_t* assign, float* dist, NearRecord* part, const uint32_t* only_if, hipStream_t st)
 {
     const int64_t per_launch = (int64_t)CN << 23;                  // 2^31 threads
-    const bool rows = K >= gather_rows_min_k(M, MW > 0);
+    const bool rows = plan.rows;
     for (int64_t n0 = 0; n0 < N; n0 += per_launch) {
         const int64_t cnt = N - n0 < per_launch ? N - n0 : per_launch;
         const int64_t blocks = (cnt + CN - 1) / CN;
-        const int64_t passes = ((int64_t)K + 255) / 256;           // of a block over its centers
-        int64_t splits;
-        if (MW > 0 && rows) {
-            // A pass takes 60 ns + 10 ns M, the second launch and the records 2.5 us: M = 4, one code per block, us: 48 codes, K = 4096:
-            // 4.6 in one, 5.6 in sixteen parts; 4 codes, K = 50000: 22 and 6.2; M = 32, 48 codes: 5.4 and 6.4 at K = 1000, 9.8 and 7.7 at 4096.
-            splits = (double)passes * (0.06 + 0.01 * M) > 3.0 ? 2 * (int64_t)cu_count() / blocks : 1;
-            if (splits > passes / 4) splits = passes / 4;
-        } else {
-            // about eight blocks per compute unit, as long as each keeps 256 centers
-            splits = 8 * (int64_t)cu_count() / blocks;
-            if (splits > passes) splits = passes;
-        }
-        // the records fit their room
-        if (splits > (int64_t)(room / sizeof(NearRecord)) / cnt) splits = (int64_t)(room / sizeof(NearRecord)) / cnt;
-        if (only_if) splits = 1;                                   // the room of the records is in use
+        int64_t splits = plan.parts;
         int per = K;
         if (splits > 1) {
             per = (int)((((int64_t)K + splits - 1) / splits + 255) / 256 * 256);
@@ -1774,25 +1804,20 @@ pqkm_status launch_gather(const uint8_t* codes, int64_t N, int M, const uint8_t*
 pqkm_status assign_untiled(const Carve& c, const uint8_t* codes, int64_t N, int M, const uint8_t* centers, int K,
                            const float* tables, int32_t* assign, float* dist, void* ws, const uint32_t* only_if, hipStream_t st)
 {
-    const bool words = tiled_M(M) && (((uintptr_t)codes | (uintptr_t)centers) & 3) == 0;
     NearRecord* part = tiled_M(M) ? reinterpret_cast<NearRecord*>(static_cast<char*>(ws) + c.img_off) : nullptr;
-    const size_t room = tiled_M(M) ? c.img_bytes : 0;
-    // Codes per block: one while that fills the chip no more than four times, then what shares the centers' words best.  us, M = 4: N = 500,
-    // K = 1000: 3.6 / 3.9 / 4.4 / 6.2 with 1, 2, 4, 8; N = 1e4: 15.3 / 13.0 / 12.0 / 14.2; M = 8: 4.0 / 4.3 / 5.3 and 21.9 / 19.8 / 19.4 (K =
-    // 100: 12.6 / 9.9 / 11.1) with 1, 2, 4; M = 16: 5.2 / 5.4 and 36.3 / 35.3 (K = 100: 17.1 / 19.2) with 1, 2.
-    const bool few = N <= 4 * (int64_t)cu_count();
-    if (words && M == 4 && few) return launch_gather<1, 1>(codes, N, M, centers, K, tables, assign, dist, part, room, only_if, st);
-    if (words && M == 4) return launch_gather<1, 4>(codes, N, M, centers, K, tables, assign, dist, part, room, only_if, st);
-    if (words && M == 8 && few) return launch_gather<2, 1>(codes, N, M, centers, K, tables, assign, dist, part, room, only_if, st);
-    if (words && M == 8) return launch_gather<2, 2>(codes, N, M, centers, K, tables, assign, dist, part, room, only_if, st);
-    if (words && M == 16) return launch_gather<4, 1>(codes, N, M, centers, K, tables, assign, dist, part, room, only_if, st);
-    if (words && M == 32) return launch_gather<8, 1>(codes, N, M, centers, K, tables, assign, dist, part, room, only_if, st);
-    if (lane_per_code(N, M, K)) {
+    const GatherPlan p = gather_plan(N, M, K, (((uintptr_t)codes | (uintptr_t)centers) & 3) == 0, tiled_M(M) ? c.img_bytes : 0, only_if != nullptr);
+    if (p.per_code) {
         hipLaunchKernelGGL(assign_generic_kernel, dim3((unsigned)((N + 255) / 256)), dim3(256), 0, st, codes, N, M, centers, K,
                            tables, assign, dist);
         return launched();
     }
-    return launch_gather<0, 1>(codes, N, M, centers, K, tables, assign, dist, part, room, only_if, st);
+    if (p.words && M == 4 && p.codes == 1) return launch_gather<1, 1>(p, codes, N, M, centers, K, tables, assign, dist, part, only_if, st);
+    if (p.words && M == 4) return launch_gather<1, 4>(p, codes, N, M, centers, K, tables, assign, dist, part, only_if, st);
+    if (p.words && M == 8 && p.codes == 1) return launch_gather<2, 1>(p, codes, N, M, centers, K, tables, assign, dist, part, only_if, st);
+    if (p.words && M == 8) return launch_gather<2, 2>(p, codes, N, M, centers, K, tables, assign, dist, part, only_if, st);
+    if (p.words && M == 16) return launch_gather<4, 1>(p, codes, N, M, centers, K, tables, assign, dist, part, only_if, st);
+    if (p.words && M == 32) return launch_gather<8, 1>(p, codes, N, M, centers, K, tables, assign, dist, part, only_if, st);
+    return launch_gather<0, 1>(p, codes, N, M, centers, K, tables, assign, dist, part, only_if, st);
 }
 
 pqkm_status assign_core(const Options& opt, const Carve& c, const uint8_t* codes, int64_t N, int M,
@@ -1959,6 +1984,16 @@ inline bool vote_few_counts_codes(int64_t N, int M, int K, const uint8_t* codes)
     return N >= 1 && N <= (words ? 40000 : 12000) && (int64_t)K * ((M + 3) / 4) <= cu_count();
 }
 
+// How an update counts its histograms: as hist_path says, or the vote counts them itself, a workgroup per cluster and four subspaces or
+// per sixteen clusters and one (not where the scan has left records).
+enum UpdateRoute { UPDATE_PASS, UPDATE_IN_VOTE_FEW, UPDATE_IN_VOTE };
+UpdateRoute update_route(HistPath path, int force, int64_t N, int M, int K, const uint8_t* codes)
+{
+    if (path == HIST_RECORDS || force != 0) return UPDATE_PASS;
+    if (vote_few_counts_codes(N, M, K, codes)) return UPDATE_IN_VOTE_FEW;
+    return vote_counts_codes(N, M, K) ? UPDATE_IN_VOTE : UPDATE_PASS;
+}
+
 pqkm_status update_impl(const Options& opt, const Carve& c, const uint8_t* codes, int64_t N, int M,
                         const int32_t* assign, int K, const float* tables, uint8_t* centers, uint32_t* hist,
                         uint32_t* counts, void* ws, hipStream_t st, const BucketLink* link = nullptr)
@@ -1990,12 +2025,13 @@ pqkm_status update_impl(const Options& opt, const Carve& c, const uint8_t* codes
                            (size_t)0, counts, K, M, hp.KT, tables, centers, VoteRecords{pool, bseg, link->nwg, nullptr, nullptr, 0});
         return launched();
     }
-    if (!linked && force == 0 && vote_few_counts_codes(N, M, K, codes)) {
+    const UpdateRoute route = update_route(path, force, N, M, K, codes);
+    if (route == UPDATE_IN_VOTE_FEW) {
         hipLaunchKernelGGL((vote_few_kernel<VOTE_CODES>), dim3((unsigned)((int64_t)K * ((M + 3) / 4))), dim3(VOTE_FEW_THREADS), 0, st, hist, hist, 1,
                            (size_t)0, false, counts, K, M, tables, centers, VoteRecords{nullptr, nullptr, 0, codes, assign, N});
         return launched();
     }
-    if (!linked && force == 0 && vote_counts_codes(N, M, K)) {
+    if (route == UPDATE_IN_VOTE) {
         hipLaunchKernelGGL((vote_kernel<VOTE_CODES>), dim3((unsigned)(((K + VOTE_REC_KT - 1) / VOTE_REC_KT) * M)), dim3(VOTE_THREADS), 0, st,
                            hist, hist, 1, (size_t)0, counts, K, M, VOTE_REC_KT, tables, centers,
                            VoteRecords{nullptr, nullptr, 0, codes, assign, N});
@@ -2535,6 +2571,37 @@ pqkm_status pqkm_scan_plan(int64_t N, int32_t M, int32_t K, int32_t iteration, i
     out[3] = p.lanes;
     out[4] = p.reuse ? 1 : 0;
     out[5] = p.seeded;
+    return PQKM_OK;
+}
+
+pqkm_status pqkm_call_plan(int64_t N, int32_t M, int32_t K, int32_t flags, int64_t out[8])
+{
+    if (!out) return PQKM_ERR_NULL;
+    if (!shape_ok(N, M, K) || flags < 0 || flags > 7) return PQKM_ERR_SHAPE;
+    const Options opt = options_snapshot();
+    const Carve c = carve(N, M, K);
+    const uint8_t* codes = reinterpret_cast<const uint8_t*>((uintptr_t)(flags & 1));          // an address that is looked at only
+    const uint8_t* centers = reinterpret_cast<const uint8_t*>((uintptr_t)(flags >> 1 & 1));
+    for (int i = 0; i < 8; ++i) out[i] = 0;
+    if (tiled_scan(opt, N, M, K, codes)) {
+        Carried none;
+        none.alone = true;
+        const ScanPlan p = scan_plan(M, opt, N, K, codes, centers, false, (flags & 4) != 0, c, none);
+        out[0] = p.filter || p.wide ? 2 : 1;
+        out[1] = p.variant;
+        out[2] = p.dot;
+    } else {
+        out[2] = dot_before_rows(M, opt, N, K, codes, centers, c);
+        const GatherPlan p = gather_plan(N, M, K, (((uintptr_t)codes | (uintptr_t)centers) & 3) == 0, tiled_M(M) ? c.img_bytes : 0, out[2] != 0);
+        out[1] = p.per_code ? 2 : p.rows ? 1 : 0;
+        out[3] = p.codes;
+        out[4] = p.parts;
+    }
+    const HistPath path = hist_path(N, M, K, c, opt.hist_kernel, false, false);
+    const UpdateRoute route = update_route(path, opt.hist_kernel, N, M, K, codes);
+    out[5] = route == UPDATE_IN_VOTE_FEW ? 5 : route == UPDATE_IN_VOTE ? 6 : (int64_t)path;
+    out[6] = route != UPDATE_PASS ? 1 : path == HIST_SUBSPACE ? subspace_hist(N, M, K, c).S : path == HIST_OWNER ? hist_plan(N, M, K).S : 1;
+    out[7] = route == UPDATE_IN_VOTE_FEW || (route == UPDATE_PASS && vote_few(N, M, K)) ? 1 : 0;
     return PQKM_OK;
 }
 

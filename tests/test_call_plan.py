@@ -1,0 +1,53 @@
+"""What one assignment and one update by themselves run, by size, alignment and options (host arithmetic, no GPU: the answers are
+those for 256 compute units)."""
+from __future__ import annotations
+
+import os
+
+import pytest
+
+
+@pytest.fixture(scope="module")
+def pq():
+    import torch
+
+    import paper_1709_03708_amd as pq
+
+    if not os.path.exists(pq.lib_path()):
+        from paper_1709_03708_amd import build
+
+        build.build()
+    if torch.cuda.is_available() and torch.cuda.get_device_properties(0).multi_processor_count != 256:
+        pytest.skip("the rules count compute units")
+    return pq
+
+
+def test_arguments(pq):
+    import ctypes
+
+    out = (ctypes.c_int64 * 8)()
+    call = pq.load().pqkm_call_plan
+    assert call(10, 4, 10, 0, None) == 1
+    for bad in ((-1, 4, 10, 0), (10, 65, 10, 0), (10, 4, 0, 0), (10, 4, 10, 8), (10, 4, 10, -1)):
+        assert call(*bad, out) == 2
+    assert call(0, 4, 10, 7, out) == 0
+
+
+@pytest.mark.parametrize("N,K,variant", [(655_360, 64, 38), (786_000, 40, 39), (1_000_000, 32, 37), (786_433, 100, 34), (600_001, 300, 38)])
+def test_skewed_shapes(pq, N, K, variant):
+    """M = 4, few centers: the shape whose rounds take least; beyond 127 centers only for one assignment by itself."""
+    p = pq.call_plan(N, 4, K)
+    assert p["scan"] == "tiled" and p["variant"] == variant
+    if K < 128:
+        assert pq.scan_plan(N, 4, K)["variant"] == variant
+    else:
+        assert pq.scan_plan(N, 4, K)["variant"] != variant
+
+
+@pytest.mark.parametrize("M,N,K,dims", [(8, 36_001, 1000, 128), (8, 20_000, 1000, 0), (16, 24_000, 300, 128), (16, 9000, 300, 0),
+                                        (16, 30_011, 1000, 256), (32, 11_003, 1500, 128), (32, 5000, 160, 0), (4, 46_000, 1000, 0)])
+def test_matrix_cores_before_one_lane_per_center(pq, M, N, K, dims):
+    """pqkm_dot_scan answers for the scans behind the tiled sizes only."""
+    p = pq.call_plan(N, M, K)
+    assert p["scan"] == "one_lane_per_center" and p["dot"] == dims
+    assert not pq.dot_scan(N, M, K)["tried"]

@@ -52,9 +52,13 @@ def test_edges(env, variant, C, K):
     _check(env, codes, centers, bad, variant)
 
 
-# the default: 2560 codes, 3072, 2048, one assignment with more than 128 centers, and M = 8 in rounds of 1536
-@pytest.mark.parametrize("M,N,K", [(4, 655_360, 64), (4, 786_000, 40), (4, 786_433, 100), (4, 600_001, 300), (8, 530_001, 60)])
-def test_default(env, M, N, K):
+# the default: 2560 codes, 3072, 4096, 2048, one assignment with more than 128 centers, and M = 8 in rounds of 1536
+@pytest.mark.parametrize("M,N,K,variant", [(4, 655_360, 64, 38), (4, 786_000, 40, 39), (4, 786_433, 100, 34), (4, 1_000_000, 32, 37),
+                                           (4, 600_001, 300, 38), (8, 530_001, 60, 2)])
+def test_default(env, M, N, K, variant):
+    pq, _, torch = env
+    if torch.cuda.get_device_properties(0).multi_processor_count == 256:
+        assert pq.call_plan(N, M, K)["variant"] == variant
     rng = np.random.default_rng(N)
     codes = rng.integers(0, 256, (N, M), dtype=np.uint8)
     _check(env, codes, codes[:K].copy(), rand_tables(rng, M), 0)
