@@ -1673,8 +1673,12 @@ double rows_us(int64_t N, int M, int K)
 // 87 / 64 at N = 7e4, 90 / 98 at 1.1e5; K = 300: 32.6 / 22.5 at 4e4, 33 / 36 at 7e4; M = 8, K = 300: 50 / 37 at 4e4, 51 / 59 at 7e4; M = 16, K =
 // 160: 55 / 33 at 2e4, 55 / 60 at 4e4; M = 32, K = 160: 136 / 73 at 2e4, 134 / 138 at 4e4.  Fewer than 160 centers, without the rows: 7 us +
 // 0.6 ns N against 7 us + 2.8 us for every 32 centers at M = 4, 4.7 us at M = 8 and 7 us at M = 16 (with rows it is faster beyond that).
-int64_t gather_max_codes(int M, int K)
+// Centers that are not aligned are read byte by byte, one code per block, several times as slowly, and the line stays lower.  Tiled / so, us:
+// M = 4, K = 1000: 88 / 431 at 9e4, K = 300: 32 / 88 at 4.6e4; M = 8, K = 1000: 145 / 562 at 7e4; M = 32, K = 300: 223 / 365 at 2.5e4.
+int64_t gather_max_codes(int M, int K, bool aligned)
 {
+    const int64_t least = (int64_t)120000 * K / (1550 + (int64_t)K);
+    if (K >= 160 && !aligned) return least;
     if (K >= 160) {
         const int64_t tiles = ((int64_t)K * M + 127) / 128;
         const double tiled = M == 4 ? 8.0 + 2.45 * (double)tiles : M == 8 ? 9.5 + 2.12 * (double)tiles : M == 16 ? 11.8 + 2.13 * (double)tiles : 19.5 + 2.63 * (double)tiles;
@@ -1682,7 +1686,6 @@ int64_t gather_max_codes(int M, int K)
         const int64_t dot_from = M == 8 ? 90000000 / K : M == 16 && 9000000 / K < 25000 ? 25000 : 9000000 / K;
         if (M > 4 && (M > 8 || K >= 500) && most >= dot_from) most = dot_from - 1;
         if (most > 512 * (int64_t)cu_count()) most = 512 * (int64_t)cu_count();
-        const int64_t least = (int64_t)120000 * K / (1550 + (int64_t)K);
         return most > least ? most : least;
     }
     const int64_t most = (int64_t)(M == 4 ? 4700 : M == 8 ? 7800 : 11600) * ((K + 31) / 32);
@@ -1708,10 +1711,10 @@ int dot_before_rows(int M, const Options& opt, int64_t N, int K, const uint8_t* 
 }
 
 // does one of the LDS-tiled scans run?
-bool tiled_scan(const Options& opt, int64_t N, int M, int K, const uint8_t* codes)
+bool tiled_scan(const Options& opt, int64_t N, int M, int K, const uint8_t* codes, const uint8_t* centers)
 {
     if (!tiled_M(M) || opt.assign_kernel == 1 || ((uintptr_t)codes & 3) != 0) return false;
-    return opt.assign_kernel != 0 || opt.scan_variant != 0 || N > gather_max_codes(M, K);
+    return opt.assign_kernel != 0 || opt.scan_variant != 0 || N > gather_max_codes(M, K, ((uintptr_t)centers & 3) == 0);
 }
 
 // What the scan with one lane per center does with N codes (one lane per code where `per_code`).
@@ -1825,7 +1828,7 @@ pqkm_status assign_core(const Options& opt, const Carve& c, const uint8_t* codes
                         hipStream_t st, Carried& carried, BucketLink* link)
 {
     if (opt.assign_kernel == 2 && !(tiled_M(M) && ((uintptr_t)codes & 3) == 0)) return PQKM_ERR_SHAPE;
-    if (!tiled_scan(opt, N, M, K, codes)) {
+    if (!tiled_scan(opt, N, M, K, codes, centers)) {
         // tables that the scan on the matrix cores is not for are left to the one with one lane per center
         const int dims = dot_before_rows(M, opt, N, K, codes, centers, c);
         const uint32_t* left = nullptr;
@@ -2555,7 +2558,7 @@ pqkm_status pqkm_scan_plan(int64_t N, int32_t M, int32_t K, int32_t iteration, i
     if (!shape_ok(N, M, K) || iteration < 0) return PQKM_ERR_SHAPE;
     const Options opt = options_snapshot();
     for (int i = 0; i < 6; ++i) out[i] = 0;
-    if (!tiled_scan(opt, N, M, K, nullptr)) return PQKM_OK;
+    if (!tiled_scan(opt, N, M, K, nullptr, nullptr)) return PQKM_OK;
     const Carve c = carve(N, M, K);
     const BucketLink link = bucket_request(opt, N, M, K);
     const bool files_records = M == 4 && link.wanted && N <= GROUP_CHUNK_MAX - 16384 && c.bseg_off != c.pool_off;
@@ -2583,7 +2586,7 @@ pqkm_status pqkm_call_plan(int64_t N, int32_t M, int32_t K, int32_t flags, int64
     const uint8_t* codes = reinterpret_cast<const uint8_t*>((uintptr_t)(flags & 1));          // an address that is looked at only
     const uint8_t* centers = reinterpret_cast<const uint8_t*>((uintptr_t)(flags >> 1 & 1));
     for (int i = 0; i < 8; ++i) out[i] = 0;
-    if (tiled_scan(opt, N, M, K, codes)) {
+    if (tiled_scan(opt, N, M, K, codes, centers)) {
         Carried none;
         none.alone = true;
         const ScanPlan p = scan_plan(M, opt, N, K, codes, centers, false, (flags & 4) != 0, c, none);
@@ -2612,7 +2615,7 @@ pqkm_status pqkm_dot_scan(int64_t N, int32_t M, int32_t K, const void* workspace
     const Options opt = options_snapshot();
     out[0] = 0;
     out[1] = -1;
-    if (!tiled_scan(opt, N, M, K, nullptr)) return PQKM_OK;
+    if (!tiled_scan(opt, N, M, K, nullptr, nullptr)) return PQKM_OK;
     const Carve c = carve(N, M, K);
     const BucketLink link = bucket_request(opt, N, M, K);
     const bool files_records = M == 4 && link.wanted && N <= GROUP_CHUNK_MAX - 16384 && c.bseg_off != c.pool_off;

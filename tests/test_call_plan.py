@@ -51,3 +51,13 @@ def test_matrix_cores_before_one_lane_per_center(pq, M, N, K, dims):
     p = pq.call_plan(N, M, K)
     assert p["scan"] == "one_lane_per_center" and p["dot"] == dims
     assert not pq.dot_scan(N, M, K)["tried"]
+
+
+@pytest.mark.parametrize("M,K,least", [(4, 300, 19_459), (4, 1000, 47_058), (8, 1000, 47_058), (8, 4000, 86_486), (16, 300, 19_459), (32, 300, 19_459)])
+def test_centers_off_their_alignment(pq, M, K, least):
+    """They are read byte by byte, which is slower than the tiled scans from fewer codes on."""
+    assert pq.call_plan(least, M, K, centers_aligned=False)["scan"] == "one_lane_per_center"
+    p = pq.call_plan(least + 1, M, K, centers_aligned=False)
+    assert p["scan"] == "tiled" and p["dot"] == 0
+    if M == 4:
+        assert pq.call_plan(least + 1, M, K)["scan"] == "one_lane_per_center"

@@ -1,0 +1,46 @@
+"""Calls at the edges of the rules that choose their scan or their count, against the oracle."""
+from __future__ import annotations
+
+import numpy as np
+import pytest
+
+from _util import rand_tables
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def env():
+    import torch
+
+    import oracle
+    import paper_1709_03708_amd as pq
+
+    assert torch.cuda.is_available()
+    return pq, oracle, torch
+
+
+def _off(torch, a, by):
+    """a on the device, `by` bytes off its alignment"""
+    buf = torch.empty(a.nbytes + by, dtype=torch.uint8, device="cuda")
+    buf[by:].copy_(torch.from_numpy(a.view(np.uint8).reshape(-1)))
+    return buf[by:].view(*a.shape)
+
+
+def _check_assign(env, codes, centers, tables, centers_on=None):
+    pq, oracle, torch = env
+    x, t = torch.from_numpy(codes).cuda(), torch.from_numpy(tables).cuda()
+    c = torch.from_numpy(centers).cuda() if centers_on is None else centers_on
+    a, d = pq.assign(x, c, t)
+    with np.errstate(all="ignore"):
+        ra, rd = oracle.assign(codes, centers, tables)
+    np.testing.assert_array_equal(a.cpu().numpy(), ra)
+    np.testing.assert_array_equal(d.cpu().numpy().view(np.uint32), rd.view(np.uint32))
+
+
+@pytest.mark.parametrize("M,N,K", [(4, 19_459, 300), (4, 19_460, 300), (8, 19_460, 300), (16, 19_460, 300), (32, 19_460, 300)])
+def test_centers_off_their_alignment(env, M, N, K):
+    rng = np.random.default_rng(N + M)
+    codes = rng.integers(0, 256, (N, M), dtype=np.uint8)
+    centers = codes[rng.permutation(N)[:K]].copy()
+    _check_assign(env, codes, centers, rand_tables(rng, M), _off(env[2], centers, 1 + M % 3))
