@@ -1644,10 +1644,11 @@ pqkm_status assign_tiled(const uint8_t* codes, int64_t N, const uint8_t* centers
 }
 
 // Scan with one lane per center: from this many centers on the table rows of a block's codes are copied to LDS first.
-// Several codes per block (aligned operands, M = 4, 8, 16, 32), M = 4, per code: 0.64 ns without and 1.05 ns with the copies at
-// K = 100, 4.4 and 1.5 ns at K = 1000.  One code per block, N = 4e5, ms without / with: M = 1, K = 2000: 0.76 / 2.07, M = 6:
-// 1.22 / 2.17 at K = 500 and 4.7 / 3.8 at K = 2000, M = 24: 1.99 / 4.33 at K = 200 and 9.2 / 6.8 at K = 1000.
-inline int gather_rows_min_k(int M, bool words) { return words ? (M < 16 ? 1 : M == 16 ? 64 : 160) : 250 + 6000 / M; }
+// Aligned operands, straight into LDS, us through the caches / so: M = 4, K = 1: 12.4 / 8.9 at N = 16384, K = 100: 12.9 / 9.1; M = 8, K = 16:
+// 4.8 / 4.5 at N = 2000 and 9.6 / 9.6 at 1e4; M = 16, N = 1e4: 13.5 / 16.2 at K = 64, 15.0 / 16.5 at K = 80, 17.8 / 17.0 at K = 100; M = 32, N =
+// 2000: 10.5 / 9.7 at K = 130.  Byte by byte, one code per block, N = 4e5, ms: M = 1, K = 2000: 0.76 / 2.07, M = 6: 1.22 / 2.17 at K =
+// 500 and 4.7 / 3.8 at K = 2000, M = 24: 1.99 / 4.33 at K = 200 and 9.2 / 6.8 at K = 1000.
+inline int gather_rows_min_k(int M, bool words) { return words ? (M < 16 ? 1 : M == 16 ? 96 : 160) : 250 + 6000 / M; }
 
 // With few centers most of its lanes have none, and one lane per code (assign_generic_kernel) is faster: that takes about
 // 0.27 us per look-up of a code while the codes do not fill the chip and 3.9 ps each beyond, the scan above 0.75 ns and 0.03 ns
@@ -1738,25 +1739,39 @@ GatherPlan gather_plan(int64_t N, int M, int K, bool aligned, size_t room, bool 
         p.per_code = true;
         return p;
     }
-    // Codes per block: one while that fills the chip no more than four times, then what shares the centers' words best.  us, M = 4: N = 500,
-    // K = 1000: 3.6 / 3.9 / 4.4 / 6.2 with 1, 2, 4, 8; N = 1e4: 15.3 / 13.0 / 12.0 / 14.2; M = 8: 4.0 / 4.3 / 5.3 and 21.9 / 19.8 / 19.4 (K =
-    // 100: 12.6 / 9.9 / 11.1) with 1, 2, 4; M = 16: 5.2 / 5.4 and 36.3 / 35.3 (K = 100: 17.1 / 19.2) with 1, 2.
-    if (p.words && N > 4 * (int64_t)cu_count()) p.codes = M == 4 ? 4 : M == 8 ? 2 : 1;
-    const int64_t blocks = (N + p.codes - 1) / p.codes;
     const int64_t passes = ((int64_t)K + 255) / 256;               // of a block over its centers
-    if (whole || blocks < 1) return p;
+    const int64_t ncu = cu_count(), most = N > 0 ? (int64_t)(room / sizeof(NearRecord)) / N : 0;      // whose records fit their room
     if (p.words && p.rows) {
-        // A pass takes 60 ns + 10 ns M, the second launch and the records 2.5 us: M = 4, one code per block, us: 48 codes, K = 4096:
-        // 4.6 in one, 5.6 in sixteen parts; 4 codes, K = 50000: 22 and 6.2; M = 32, 48 codes: 5.4 and 6.4 at K = 1000, 9.8 and 7.7 at 4096.
-        p.parts = (double)passes * (0.06 + 0.01 * M) > 3.0 ? 2 * (int64_t)cu_count() / blocks : 1;
-        if (p.parts > passes / 4) p.parts = passes / 4;
-    } else {
-        // about eight blocks per compute unit, as long as each keeps 256 centers
-        p.parts = 8 * (int64_t)cu_count() / blocks;
-        if (p.parts > passes) p.parts = passes;
+        // Codes per block and parts of the centers by the time they take: a compute unit has k blocks, and a block's pass takes 10 ns M per
+        // code of it where they share the unit, and 20 ns more by itself; beside its passes a block costs 50 ns + 4.5 ns M per code,
+        // and parts a second launch.  What matters is how evenly the blocks fill the units.  us, codes x parts: M = 4, N = 257, K = 300000:
+        // 122 (1 x 1) / 60 (1 x 16); N = 1025: 393 (4 x 1) / 213 (2 x 12); N = 2100, K = 50000: 103 (4 x 1) / 77 (2 x 6); N = 500, K =
+        // 1000: 4.2 (1 x 1) / 4.3 (2 x 1) / 4.9 (4 x 1), N = 8000: 12.6 / 10.6 / 10.0; M = 8, N = 257, K = 300000: 196 / 110 (1 x 24);
+        // M = 16, N = 257, K = 50000: 69 / 42 (2 x 16), N = 8000, K = 1000: 30.1 (1 x 1) / 28.6 (2 x 1) / 33.5 (4 x 1); M = 32, N =
+        // 257, K = 50000: 134 / 79 (1 x 24).  Two codes of M = 16 leave room for fewer blocks, which few passes show: K = 300, N = 1e4: 19.4 / 21.7.
+        double best = 1e300;
+        const int widest = N < 2 || M == 32 || (M == 16 && passes <= 2) ? 1 : M == 4 ? 4 : 2;
+        for (int codes = 1; codes <= widest; codes *= 2) {
+            const int64_t blocks = (N + codes - 1) / codes;
+            const double code = 0.0104 * M * codes, pass = code + (codes == 1 ? 0.005 : 0.0), lone = code + 0.02 < 0.09 ? 0.09 : code + 0.02;
+            const double beside = 0.05 + 0.0045 * M * codes;
+            const int64_t parts_of[] = {1, 2, 3, 4, 6, 8, 12, 16, 24, 32, 64, 128, passes};
+            for (int64_t parts : parts_of) {
+                if (parts > 1 && (whole || (double)passes * lone < 2.8)) break;
+                if (parts > 1 && (parts > passes || parts > most || parts > 128)) continue;
+                const double mine = (double)((passes + parts - 1) / parts), k = (double)((blocks * parts + ncu - 1) / ncu);
+                const double one = mine * lone + beside, all = k * (mine * pass + beside);
+                const double us = (one > all ? one : all) + (parts > 1 ? 2.8 + 0.0006 * (double)N : 0.0);
+                if (us < best) { best = us; p.codes = codes; p.parts = parts; }
+            }
+        }
+        return p;
     }
-    // the records fit their room
-    if (p.parts > (int64_t)(room / sizeof(NearRecord)) / N) p.parts = (int64_t)(room / sizeof(NearRecord)) / N;
+    // about eight blocks per compute unit, as long as each keeps 256 centers
+    if (whole || N < 1) return p;
+    p.parts = 8 * ncu / N;
+    if (p.parts > passes) p.parts = passes;
+    if (p.parts > most) p.parts = most;
     if (p.parts < 1) p.parts = 1;
     return p;
 }
@@ -1815,9 +1830,11 @@ pqkm_status assign_untiled(const Carve& c, const uint8_t* codes, int64_t N, int 
         return launched();
     }
     if (p.words && M == 4 && p.codes == 1) return launch_gather<1, 1>(p, codes, N, M, centers, K, tables, assign, dist, part, only_if, st);
+    if (p.words && M == 4 && p.codes == 2) return launch_gather<1, 2>(p, codes, N, M, centers, K, tables, assign, dist, part, only_if, st);
     if (p.words && M == 4) return launch_gather<1, 4>(p, codes, N, M, centers, K, tables, assign, dist, part, only_if, st);
     if (p.words && M == 8 && p.codes == 1) return launch_gather<2, 1>(p, codes, N, M, centers, K, tables, assign, dist, part, only_if, st);
     if (p.words && M == 8) return launch_gather<2, 2>(p, codes, N, M, centers, K, tables, assign, dist, part, only_if, st);
+    if (p.words && M == 16 && p.codes == 2) return launch_gather<4, 2>(p, codes, N, M, centers, K, tables, assign, dist, part, only_if, st);
     if (p.words && M == 16) return launch_gather<4, 1>(p, codes, N, M, centers, K, tables, assign, dist, part, only_if, st);
     if (p.words && M == 32) return launch_gather<8, 1>(p, codes, N, M, centers, K, tables, assign, dist, part, only_if, st);
     return launch_gather<0, 1>(p, codes, N, M, centers, K, tables, assign, dist, part, only_if, st);

@@ -61,3 +61,27 @@ def test_centers_off_their_alignment(pq, M, K, least):
     assert p["scan"] == "tiled" and p["dot"] == 0
     if M == 4:
         assert pq.call_plan(least + 1, M, K)["scan"] == "one_lane_per_center"
+
+
+@pytest.mark.parametrize("M,N,K,codes", [(4, 1, 2500, 1), (4, 257, 300_000, 0), (4, 1025, 300_000, 0), (4, 2100, 50_000, 0), (8, 257, 300_000, 0), (8, 2100, 50_000, 0),
+                                         (16, 257, 50_000, 0), (16, 8000, 1000, 2), (16, 8000, 300, 1), (32, 257, 50_000, 1), (32, 1025, 50_000, 1),
+                                         (4, 8000, 1000, 4)])
+def test_blocks_of_one_lane_per_center(pq, M, N, K, codes):
+    """Blocks fill the compute units evenly: a code more than one block per unit takes may not double the time."""
+    p = pq.call_plan(N, M, K)
+    assert p["scan"] == "one_lane_per_center" and p["variant"] == 1
+    assert p["codes"] == codes or not codes
+    passes, blocks = -(-K // 256), -(-N // p["codes"]) * p["parts"]
+    if passes * M > 700:
+        assert -(-passes // p["parts"]) * -(-blocks // 256) * p["codes"] < 1.35 * passes * N / 256          # the busiest unit's passes over a code
+    else:
+        assert p["parts"] == 1
+    for n, k in ((N, K), (N + 1, K), (2 * N, K), (N, 2 * K)):
+        q = pq.call_plan(n, M, k)
+        if q["scan"] == "one_lane_per_center":
+            assert q["parts"] == 1 or q["parts"] * n * 8 <= (k + 128 // M - 1) // (128 // M) * 131072      # their records fit the images' room
+    assert pq.call_plan(N, M, 95)["variant"] == (1 if M < 16 else 0)
+
+
+def test_rows_of_sixteen_subspaces(pq):
+    assert pq.call_plan(2000, 16, 95)["variant"] == 0 and pq.call_plan(2000, 16, 96)["variant"] == 1

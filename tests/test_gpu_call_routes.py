@@ -44,3 +44,18 @@ def test_centers_off_their_alignment(env, M, N, K):
     codes = rng.integers(0, 256, (N, M), dtype=np.uint8)
     centers = codes[rng.permutation(N)[:K]].copy()
     _check_assign(env, codes, centers, rand_tables(rng, M), _off(env[2], centers, 1 + M % 3))
+
+
+# one lane per center: two codes per block (M = 4, 16), parts of the centers, a ragged last code and part, rows in LDS or not
+@pytest.mark.parametrize("M,N,K", [(4, 300, 1000), (4, 2101, 1000), (4, 1025, 20_001), (4, 257, 60_003), (8, 257, 30_000), (16, 2101, 513), (16, 1501, 2500),
+                                   (16, 1025, 9001), (32, 257, 9000), (32, 3, 5000), (16, 300, 95), (16, 300, 96)])
+@pytest.mark.parametrize("ties", [False, True])
+def test_rows_and_parts(env, M, N, K, ties):
+    rng = np.random.default_rng(N + K)
+    top = 8 if ties else 256
+    codes, centers = rng.integers(0, top, (N, M), dtype=np.uint8), rng.integers(0, top, (K, M), dtype=np.uint8)
+    tables = rand_tables(rng, M, integer=ties)
+    if ties:
+        tables[0, 3] = np.inf
+        tables[M - 1, 5] = np.nan                                                # codes without any distance
+    _check_assign(env, codes, centers, tables)
