@@ -1314,7 +1314,7 @@ int dot_scan_dims(int M, const Options& opt, int64_t N, int K, bool dist, const 
 
 template <int M>
 void launch_dot(const uint8_t* codes, int64_t N, const uint8_t* centers, int K, const float* tables, int32_t* assign, float* dist,
-                const Carve& c, char* ws, const Carried& carried, const Options& opt, int most_dims, hipStream_t st)
+                const Carve& c, char* ws, const Carried& carried, const Options& opt, int most_dims, bool marks, hipStream_t st)
 {
     const DotCarve d = dot_carve(M, K);
     char* room = ws + c.img_off;
@@ -1329,7 +1329,7 @@ void launch_dot(const uint8_t* codes, int64_t N, const uint8_t* centers, int K, 
                        check, emb, lost, state, room + d.img_off, carried.iteration, !carried.dot);
     EventPair ev{};
     const bool prof = (opt.profile & 1) && log_begin(g_scan_log, st, &ev);
-    const DotIn in{codes, centers, tables, stat, emb, lost, room + d.img_off, state, N, K, carried.iteration};
+    const DotIn in{codes, centers, tables, stat, emb, lost, room + d.img_off, state, N, K, carried.iteration, marks};
     const int64_t ncu = cu_count();
     // one or two columns of codes per wave, by the time of the rounds: about 20 tiles' worth for what a round costs beside its tiles
     auto cost = [&](int64_t ct) { return (double)(((N + 256 * ct - 1) / (256 * ct) + ncu - 1) / ncu) * ((double)K / DOT_TILE * (double)ct + 20.0); };
@@ -1437,7 +1437,7 @@ pqkm_status assign_tiled(const uint8_t* codes, int64_t N, const uint8_t* centers
     const uint32_t* left = nullptr;
     if constexpr (M != 4) {
         if (plan_of.dot) {
-            launch_dot<M>(codes, N, centers, K, tables, assign, dist, c, ws, carried, opt, plan_of.dot, st);
+            launch_dot<M>(codes, N, centers, K, tables, assign, dist, c, ws, carried, opt, plan_of.dot, false, st);
             if (launched() != PQKM_OK) return PQKM_ERR_DEVICE;
             left = &reinterpret_cast<const DotState*>(ws + c.dot_off)->left;
         }
@@ -1778,7 +1778,7 @@ GatherPlan gather_plan(int64_t N, int M, int K, bool aligned, size_t room, bool 
 
 template <int MW, int CN>
 pqkm_status launch_gather(const GatherPlan& plan, const uint8_t* codes, int64_t N, int M, const uint8_t* centers, int K, const float* tables,
-                          int32_t* assign, float* dist, NearRecord* part, const uint32_t* only_if, hipStream_t st)
+                          int32_t* assign, float* dist, NearRecord* part, const DotState* front, hipStream_t st)
 {
     const int64_t per_launch = (int64_t)CN << 23;                  // 2^31 threads
     const bool rows = plan.rows;
@@ -1799,7 +1799,7 @@ pqkm_status launch_gather(const GatherPlan& plan, const uint8_t* codes, int64_t 
         if constexpr (MW > 0) {
             if (rows)
                 hipLaunchKernelGGL((assign_rows_kernel<MW, CN, 256>), grid, dim3(256), 0, st, codes + n0 * M, cnt, centers, K, tables,
-                                   assign + n0, dn, pn, per, only_if);
+                                   assign + n0, dn, pn, per, front ? &front->left : nullptr, front ? &front->some : nullptr);
             else
                 hipLaunchKernelGGL((assign_gather_kernel<MW, CN, false>), grid, dim3(256), 0, st, codes + n0 * M, cnt, M, centers, K,
                                    tables, assign + n0, dn, pn, per);
@@ -1818,26 +1818,26 @@ pqkm_status launch_gather(const GatherPlan& plan, const uint8_t* codes, int64_t 
     return launched();
 }
 
-// one lane per center, or per code where there are few centers
+// one lane per center, or per code where there are few centers; `front`: state of the scan on the matrix cores that was tried first
 pqkm_status assign_untiled(const Carve& c, const uint8_t* codes, int64_t N, int M, const uint8_t* centers, int K,
-                           const float* tables, int32_t* assign, float* dist, void* ws, const uint32_t* only_if, hipStream_t st)
+                           const float* tables, int32_t* assign, float* dist, void* ws, const DotState* front, hipStream_t st)
 {
     NearRecord* part = tiled_M(M) ? reinterpret_cast<NearRecord*>(static_cast<char*>(ws) + c.img_off) : nullptr;
-    const GatherPlan p = gather_plan(N, M, K, (((uintptr_t)codes | (uintptr_t)centers) & 3) == 0, tiled_M(M) ? c.img_bytes : 0, only_if != nullptr);
+    const GatherPlan p = gather_plan(N, M, K, (((uintptr_t)codes | (uintptr_t)centers) & 3) == 0, tiled_M(M) ? c.img_bytes : 0, front != nullptr);
     if (p.per_code) {
         hipLaunchKernelGGL(assign_generic_kernel, dim3((unsigned)((N + 255) / 256)), dim3(256), 0, st, codes, N, M, centers, K,
                            tables, assign, dist);
         return launched();
     }
-    if (p.words && M == 4 && p.codes == 1) return launch_gather<1, 1>(p, codes, N, M, centers, K, tables, assign, dist, part, only_if, st);
-    if (p.words && M == 4 && p.codes == 2) return launch_gather<1, 2>(p, codes, N, M, centers, K, tables, assign, dist, part, only_if, st);
-    if (p.words && M == 4) return launch_gather<1, 4>(p, codes, N, M, centers, K, tables, assign, dist, part, only_if, st);
-    if (p.words && M == 8 && p.codes == 1) return launch_gather<2, 1>(p, codes, N, M, centers, K, tables, assign, dist, part, only_if, st);
-    if (p.words && M == 8) return launch_gather<2, 2>(p, codes, N, M, centers, K, tables, assign, dist, part, only_if, st);
-    if (p.words && M == 16 && p.codes == 2) return launch_gather<4, 2>(p, codes, N, M, centers, K, tables, assign, dist, part, only_if, st);
-    if (p.words && M == 16) return launch_gather<4, 1>(p, codes, N, M, centers, K, tables, assign, dist, part, only_if, st);
-    if (p.words && M == 32) return launch_gather<8, 1>(p, codes, N, M, centers, K, tables, assign, dist, part, only_if, st);
-    return launch_gather<0, 1>(p, codes, N, M, centers, K, tables, assign, dist, part, only_if, st);
+    if (p.words && M == 4 && p.codes == 1) return launch_gather<1, 1>(p, codes, N, M, centers, K, tables, assign, dist, part, front, st);
+    if (p.words && M == 4 && p.codes == 2) return launch_gather<1, 2>(p, codes, N, M, centers, K, tables, assign, dist, part, front, st);
+    if (p.words && M == 4) return launch_gather<1, 4>(p, codes, N, M, centers, K, tables, assign, dist, part, front, st);
+    if (p.words && M == 8 && p.codes == 1) return launch_gather<2, 1>(p, codes, N, M, centers, K, tables, assign, dist, part, front, st);
+    if (p.words && M == 8) return launch_gather<2, 2>(p, codes, N, M, centers, K, tables, assign, dist, part, front, st);
+    if (p.words && M == 16 && p.codes == 2) return launch_gather<4, 2>(p, codes, N, M, centers, K, tables, assign, dist, part, front, st);
+    if (p.words && M == 16) return launch_gather<4, 1>(p, codes, N, M, centers, K, tables, assign, dist, part, front, st);
+    if (p.words && M == 32) return launch_gather<8, 1>(p, codes, N, M, centers, K, tables, assign, dist, part, front, st);
+    return launch_gather<0, 1>(p, codes, N, M, centers, K, tables, assign, dist, part, front, st);
 }
 
 pqkm_status assign_core(const Options& opt, const Carve& c, const uint8_t* codes, int64_t N, int M,
@@ -1848,21 +1848,21 @@ pqkm_status assign_core(const Options& opt, const Carve& c, const uint8_t* codes
     if (!tiled_scan(opt, N, M, K, codes, centers)) {
         // tables that the scan on the matrix cores is not for are left to the one with one lane per center
         const int dims = dot_before_rows(M, opt, N, K, codes, centers, c);
-        const uint32_t* left = nullptr;
+        const DotState* state = nullptr;
         if (dims) {
             char* wsc = static_cast<char*>(ws);
-            if (M == 8) launch_dot<8>(codes, N, centers, K, tables, assign, dist, c, wsc, carried, opt, dims, st);
-            else if (M == 16) launch_dot<16>(codes, N, centers, K, tables, assign, dist, c, wsc, carried, opt, dims, st);
-            else launch_dot<32>(codes, N, centers, K, tables, assign, dist, c, wsc, carried, opt, dims, st);
+            if (M == 8) launch_dot<8>(codes, N, centers, K, tables, assign, dist, c, wsc, carried, opt, dims, true, st);
+            else if (M == 16) launch_dot<16>(codes, N, centers, K, tables, assign, dist, c, wsc, carried, opt, dims, true, st);
+            else launch_dot<32>(codes, N, centers, K, tables, assign, dist, c, wsc, carried, opt, dims, true, st);
             if (launched() != PQKM_OK) return PQKM_ERR_DEVICE;
-            left = &reinterpret_cast<const DotState*>(wsc + c.dot_off)->left;
+            state = reinterpret_cast<const DotState*>(wsc + c.dot_off);
             ++carried.iteration;
             carried.dot = true;
         }
         EventPair ev{};
         const bool prof = (opt.profile & 1) && log_begin(g_scan_log, st, &ev);
         t_scan_kernels = 0;
-        const pqkm_status s = assign_untiled(c, codes, N, M, centers, K, tables, assign, dist, ws, left, st);
+        const pqkm_status s = assign_untiled(c, codes, N, M, centers, K, tables, assign, dist, ws, state, st);
         if (prof) {
             hipEventRecord(ev.b, st);
             std::lock_guard<std::mutex> lk(g_mu);

@@ -43,6 +43,7 @@ struct DotState {
     float scale;                                  // power of two: units of the rounded points
     uint32_t dc2[2], nc2[2];                      // per parity of the iteration: max |u_c - u'_c|^2, max |u'_c|^2, as bits
     unsigned long long formed[2];                 // likewise: fp32 distances formed
+    uint32_t some;                                // not zero: the codes whose assignment is -1 are left (DotIn::marks)
 };
 struct DotStat { int rank; float spread; };       // per subspace: columns found (more than 256 / M: too many), see DOT_COARSE
 struct DotCheck { float e0, sum; };               // per part of a subspace: largest difference, sum of the entries
@@ -389,6 +390,7 @@ __global__ __launch_bounds__(256) void dot_centers_kernel(const uint8_t* __restr
     if (blockIdx.x == 0 && t == 0) {
         state->dc2[(iteration & 1) ^ 1] = state->nc2[(iteration & 1) ^ 1] = 0u;
         state->formed[(iteration & 1) ^ 1] = 0ull;
+        state->some = 0u;
     }
     // which centers repeat one of a lower index, by their first four subcodes and then the rest
     if (t < DOT_TILE) {
@@ -496,6 +498,7 @@ struct DotIn {
     DotState* state;
     int64_t N;
     int K, iteration;
+    bool marks;                                   // the scan behind looks for single codes that are left
 };
 
 // the fp32 distance of Eq. 3
@@ -530,7 +533,10 @@ __device__ __forceinline__ float dot_distance(const float* __restrict__ tables, 
 // the two lanes of a code know the limit, and all but a few codes have one center within.
 // The others list the centers of their block within it and all 16 of a second and a third one, and the workgroup works off the
 // list together; where there is a fourth block it forms all K.  A workgroup whose codes need so many that the plain scans are cheaper (ties
-// everywhere) sets `left` and ends, and so do the others when they next look.
+// everywhere) sets `left` and ends, and so do the others when they next look.  Where the scan behind can take single codes (one lane
+// per center) it marks its block's instead and goes on, until half of all codes are marked: with few codes a workgroup has one
+// block, and knows at its end.  M = 16, 256 dimensions, N = 33000, K = 6000, one such block of 129: 525 us by the scan behind alone, 810 with all
+// codes left to it, 290 with the block's.
 //
 // Per tile and 32 codes 8 matrix instructions (128 dimensions) of 32 clocks and about 40 vector instructions of 4.  Two waves per
 // SIMD, whose two kinds of instruction overlap little: at M = 8, N = 5e5, K = 5000 the matrix cores are busy 46 per cent of the
@@ -817,21 +823,26 @@ __device__ __forceinline__ void dot_scan(const DotIn& f, int32_t* __restrict__ a
         const uint32_t listed = misc[2], overs = misc[3];
         // far more than the plain scan of these codes would cost: the same verdict in all threads
         const float cost = (float)listed + (float)overs * (float)f.K;
-        if (overs > (uint32_t)DOT_OVER || cost > most) {
+        const bool beyond = overs > (uint32_t)DOT_OVER || cost > most;
+        if (beyond && !f.marks) {
             if (tid == 0) leave();
             break;
         }
-        for (uint32_t i = (uint32_t)tid; i < (listed < (uint32_t)DOT_LIST ? listed : (uint32_t)DOT_LIST); i += 512u) {
-            const uint32_t e = list_s[i];
-            form((int)(e & 511u), e >> 9);
-        }
-        for (uint32_t i = 0; i < overs; ++i) {
-            const int c = (int)over_s[i];
+        if (beyond) {
+            if (tid == 0) __hip_atomic_store(&f.state->some, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        } else {
+            for (uint32_t i = (uint32_t)tid; i < (listed < (uint32_t)DOT_LIST ? listed : (uint32_t)DOT_LIST); i += 512u) {
+                const uint32_t e = list_s[i];
+                form((int)(e & 511u), e >> 9);
+            }
+            for (uint32_t i = 0; i < overs; ++i) {
+                const int c = (int)over_s[i];
 #pragma unroll 4
-            for (int k = tid; k < f.K; k += 512) form(c, (uint32_t)k);
+                for (int k = tid; k < f.K; k += 512) form(c, (uint32_t)k);
+            }
         }
         // more than this workgroup's share of what the plain scan would cost: told to the others, and half of the whole is enough
-        spent += cost;
+        spent += beyond ? 1.01f * free_evals * (float)C : cost;
         done_codes += (float)C;
         if (spent > free_evals * done_codes) {
             if (tid == 0) {
@@ -850,8 +861,8 @@ __device__ __forceinline__ void dot_scan(const DotIn& f, int32_t* __restrict__ a
             if (n < f.N) {
                 const unsigned long long key = keys[lane];
                 const uint32_t k = key == FILTER_NONE ? 0u : (uint32_t)key;
-                assign[n] = (int32_t)k;
-                if (dist) {
+                assign[n] = beyond ? -1 : (int32_t)k;
+                if (dist && !beyond) {
                     float s = key == FILTER_NONE ? INFINITY : filter_key_distance(key);
                     if (s == 0.0f) s = dot_distance<M>(f.tables, f.codes + n * M, f.centers + (size_t)k * M);     // the sign of a zero
                     dist[n] = s;

@@ -701,15 +701,22 @@ __global__ __launch_bounds__(THREADS) void assign_rows_kernel(const uint8_t* __r
                                                               const uint8_t* __restrict__ centers, int K,
                                                               const float* __restrict__ tables,
                                                               int32_t* __restrict__ assign, float* __restrict__ dist,
-                                                              NearRecord* __restrict__ part, int per, const uint32_t* __restrict__ only_if)
+                                                              NearRecord* __restrict__ part, int per, const uint32_t* __restrict__ only_if,
+                                                              const uint32_t* __restrict__ some)
 {
     constexpr int M = 4 * MW, ROWS = CN * M, WAVES = THREADS / 64, MINE = (ROWS + WAVES - 1) / WAVES;
     __shared__ float row_s[ROWS * L];                                // row i * M + m: subspace m for the subcode of code i
     __shared__ NearRecord rec[WAVES][CN];
-    if (only_if && *only_if == 0u) return;                           // the scan in front of it did the work
+    const int64_t n0 = (int64_t)blockIdx.x * CN;
+    if (only_if && *only_if == 0u) {                                 // the scan in front of it did the work, but for the codes it marked
+        if (*some == 0u) return;
+        bool any = false;
+#pragma unroll
+        for (int i = 0; i < CN; ++i) any = any || (n0 + i < N && assign[n0 + i] < 0);
+        if (!any) return;
+    }
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int64_t n0 = (int64_t)blockIdx.x * CN;
     const int k_begin = (int)blockIdx.y * per;
     const int k_end = K - k_begin < per ? K : k_begin + per;
     const uint32_t* cen = reinterpret_cast<const uint32_t*>(centers);

@@ -59,3 +59,41 @@ def test_rows_and_parts(env, M, N, K, ties):
         tables[0, 3] = np.inf
         tables[M - 1, 5] = np.nan                                                # codes without any distance
     _check_assign(env, codes, centers, tables)
+
+
+@pytest.mark.parametrize("M,N,K", [(8, 36_001, 1000), (16, 30_011, 1000), (32, 11_003, 1500)])
+@pytest.mark.parametrize("blocks", [1, 3, 1000])
+def test_single_codes_left_by_the_matrix_cores(env, M, N, K, blocks):
+    """Stretches of codes that are as far from 200 centers, no two of them equal: few of them are left to one lane per center, and no
+    others; all of them, and everything is.  The scan's state is the end of the workspace: word 0 is for everything, word 12 for some."""
+    pq, oracle, torch = env
+    rng = np.random.default_rng(M + blocks)
+    cw = rng.standard_normal((M, 256, 128 // M)).astype(np.float32)
+    cw[M - 1, :200] = cw[M - 1, 0]
+    tables = oracle.build_tables(cw)
+    centers = rng.integers(0, 256, (K, M), dtype=np.uint8)
+    order = rng.permutation(K)
+    alike, others = order[:200], order[200:]
+    centers[alike] = centers[alike[0]]
+    centers[alike, M - 1] = np.arange(200)
+    codes = rng.integers(0, 256, (N, M), dtype=np.uint8)
+    near = rng.random((N, M)) < 0.8
+    codes[near] = centers[others[rng.integers(0, K - 200, N)]][near]
+    for b in range(min(blocks, N // 2048)):
+        codes[b * 2048 + 100: b * 2048 + 500 if blocks < 1000 else N] = centers[alike[7]]
+    ws = torch.full((pq.workspace_bytes(N, M, K),), 0xA5, dtype=torch.uint8, device="cuda")
+    assert pq.call_plan(N, M, K, dist=True)["dot"]
+    a, d = pq.assign(*[torch.from_numpy(v).cuda() for v in (codes, centers, tables)], workspace=ws)
+    state = ws[-256:].view(torch.int32).cpu().numpy()
+    ra, rd = oracle.assign(codes, centers, tables)
+    np.testing.assert_array_equal(a.cpu().numpy(), ra)
+    np.testing.assert_array_equal(d.cpu().numpy().view(np.uint32), rd.view(np.uint32))
+    assert (state[0] == 0 and state[12] == 1) if blocks < 1000 else state[0] == 1
+    c = torch.from_numpy(centers).cuda()
+    _, a = pq.fit(torch.from_numpy(codes).cuda(), torch.from_numpy(tables).cuda(), c, 2)
+    want = centers
+    for _ in range(2):
+        ra, _ = oracle.assign(codes, want, tables)
+        want, _, _ = oracle.update(codes, ra, tables, want)
+    np.testing.assert_array_equal(a.cpu().numpy(), ra)
+    np.testing.assert_array_equal(c.cpu().numpy(), want)
