@@ -1699,7 +1699,8 @@ int64_t gather_max_codes(int M, int K, bool aligned)
 // center alone, then this with tables of 128 / 256 dimensions / it is not for, us, with distances: M = 8, K = 1000: 57 (51 / 69 / 67) at N =
 // 3.3e4, 78 (60 / 76 / 86) at 4.6e4; K = 4000: 142 (91 / 147 / 148) at 2.5e4, 251 (122 / 151 / 261) at 4.6e4; M = 16, K = 300: 45 (40 / 56 / 53) at
 // 2.5e4; K = 1000: 63 (49 / 71 / 73) at 1.8e4, 152 (65 / 75 / 159) at 4.6e4; K = 4000: 201 (92 / 138 / 208) at 1.8e4; M = 32, K = 160: 90 (53 / 59 /
-// 99) at 2.5e4; K = 1000: 78 (61 / 77 / 86) at 1.2e4, 279 (69 / 95 / 290) at 4.6e4.
+// 99) at 2.5e4; K = 1000: 78 (61 / 77 / 86) at 1.2e4, 279 (69 / 95 / 290) at 4.6e4.  More centers than codes lie close together, and a scan that then leaves them
+// all was for nothing (M = 16, N = 8000, K = 50000 of 500 components: 1060 and 1590): it has to promise more.
 int dot_before_rows(int M, const Options& opt, int64_t N, int K, const uint8_t* codes, const uint8_t* centers, const Carve& c)
 {
     if (M < 8 || !tiled_M(M) || K < 160 || K > (1 << 22) || opt.assign_kernel == 1 || c.dot_off == 0 ||
@@ -1708,7 +1709,7 @@ int dot_before_rows(int M, const Options& opt, int64_t N, int K, const uint8_t* 
     const int64_t round = 256 * (int64_t)cu_count(), rounds = (N + round - 1) / round;
     const double few = M == 8 ? 35.0 : M == 16 ? 32.0 : 45.0, many = M == 8 ? 49.0 : M == 16 ? 37.0 : 51.0, rows = rows_us(N, M, K);
     auto dot = [&](double fixed, double center) { return fixed + center * K * (double)rounds + 10.0 * (double)(rounds - 1); };
-    return rows > 1.25 * dot(many, 0.025) ? 256 : rows > 1.2 * dot(few, 0.015) ? 128 : 0;
+    return rows > (K > N ? 1.6 : 1.25) * dot(many, 0.025) ? 256 : rows > (K > N ? 1.5 : 1.2) * dot(few, 0.015) ? 128 : 0;
 }
 
 // does one of the LDS-tiled scans run?

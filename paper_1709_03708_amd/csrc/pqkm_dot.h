@@ -535,8 +535,8 @@ __device__ __forceinline__ float dot_distance(const float* __restrict__ tables, 
 // list together; where there is a fourth block it forms all K.  A workgroup whose codes need so many that the plain scans are cheaper (ties
 // everywhere) sets `left` and ends, and so do the others when they next look.  Where the scan behind can take single codes (one lane
 // per center) it marks its block's instead and goes on, until half of all codes are marked: with few codes a workgroup has one
-// block, and knows at its end.  M = 16, 256 dimensions, N = 33000, K = 6000, one such block of 129: 525 us by the scan behind alone, 810 with all
-// codes left to it, 290 with the block's.
+// block, and knows at its end.  M = 16, 256 dimensions, N = 33000, K = 6000, one such block of 129: 525 us by the scan behind alone, 800 with all
+// codes left to it, 310 with the block's, 285 where there is none.
 //
 // Per tile and 32 codes 8 matrix instructions (128 dimensions) of 32 clocks and about 40 vector instructions of 4.  Two waves per
 // SIMD, whose two kinds of instruction overlap little: at M = 8, N = 5e5, K = 5000 the matrix cores are busy 46 per cent of the

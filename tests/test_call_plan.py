@@ -53,6 +53,11 @@ def test_matrix_cores_before_one_lane_per_center(pq, M, N, K, dims):
     assert not pq.dot_scan(N, M, K)["tried"]
 
 
+def test_matrix_cores_with_more_centers_than_codes(pq):
+    """They lie close together: not for a small gain."""
+    assert pq.call_plan(8000, 16, 50_000)["dot"] == 0 and pq.call_plan(8000, 32, 20_000)["dot"] > 0
+
+
 @pytest.mark.parametrize("M,K,least", [(4, 300, 19_459), (4, 1000, 47_058), (8, 1000, 47_058), (8, 4000, 86_486), (16, 300, 19_459), (32, 300, 19_459)])
 def test_centers_off_their_alignment(pq, M, K, least):
     """They are read byte by byte, which is slower than the tiled scans from fewer codes on."""
