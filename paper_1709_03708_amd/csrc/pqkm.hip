@@ -1996,13 +1996,20 @@ inline bool vote_few(int64_t N, int M, int K)
     return N >= 1 && rows <= 550000 && K <= 65536;
 }
 
-// Few codes as well: each of its workgroups counts its cluster from all codes, while one round of them covers all.  Whole update, us, where
-// vote_kernel counts or a histogram is formed first / so: M = 4: 16.3 / 10.4 at N = 1e4, K = 100, 17.9 / 11.6 at 2e4, 256, 27.3 / 22.5 at
-// 4e4, 100, but 31.8 / 35.0 at 8e4, 100; M = 8: 27.5 / 22.9 at 4e4, 100; M = 6, byte by byte: 16.6 / 13.6 at 1e4, 100, but 20.8 / 21.4 at 2e4, 100.
-inline bool vote_few_counts_codes(int64_t N, int M, int K, const uint8_t* codes)
+// Few codes as well: each of its workgroups counts its cluster from all codes, as few subspaces as one round of them allows.  Whole update, us,
+// where vote_kernel counts or a histogram is formed first / so: M = 4: 17 / 10 at N = 1e4, K = 100, 27.3 / 18.2 at 2e4, 32, 18.0 / 13.2 at 2e4, 256,
+// 31.0 / 24.3 at 4e4, 64, 24.7 / 20.3 at 4e4, 256, but 31.8 / 35.0 at 8e4, 100; M = 8: 20.9 / 16.5 at 2e4, 128, 31.1 / 27.2 at 4e4, 64; M = 16: 34.3 /
+// 29.1 at 4e4, 64.  A workgroup with a large share of the codes takes longer: 23.4 / 22.8 at 3e4, 8, but 25.2 / 26.6 at 4e4, 8 and 37.8 / 46.2 at
+// M = 64.  Byte by byte, four subspaces are too many: M = 6: 20.4 / 16.5 at 12000, 64, but 17.0 / 17.9 at 12000, 128.  All codes in one cluster:
+// M = 4: 19.6 / 18.3 at 2e4, 64, 19.8 / 21.4 at 2e4, 256, 23.1 / 26.0 at 4e4, 64; all of them alike: 26 / 17 at 2e4, 64 (70 in one copy of the bins).
+// Returns the subspaces per workgroup, 0: not.
+inline int vote_few_counts_codes(int64_t N, int M, int K, const uint8_t* codes)
 {
     const bool words = (M & 3) == 0 && ((uintptr_t)codes & 3) == 0;
-    return N >= 1 && N <= (words ? 40000 : 12000) && (int64_t)K * ((M + 3) / 4) <= cu_count();
+    if (N < 1 || N > (!words ? 12000 : K < 16 ? 28000 : 40000)) return 0;
+    for (int G = 1; G <= (words || N < 1500 ? 4 : 2); G *= 2)
+        if ((int64_t)K * ((M + G - 1) / G) <= cu_count()) return G;
+    return 0;
 }
 
 // How an update counts its histograms: as hist_path says, or the vote counts them itself, a workgroup per cluster and four subspaces or
@@ -2048,8 +2055,15 @@ pqkm_status update_impl(const Options& opt, const Carve& c, const uint8_t* codes
     }
     const UpdateRoute route = update_route(path, force, N, M, K, codes);
     if (route == UPDATE_IN_VOTE_FEW) {
-        hipLaunchKernelGGL((vote_few_kernel<VOTE_CODES>), dim3((unsigned)((int64_t)K * ((M + 3) / 4))), dim3(VOTE_FEW_THREADS), 0, st, hist, hist, 1,
-                           (size_t)0, false, counts, K, M, tables, centers, VoteRecords{nullptr, nullptr, 0, codes, assign, N});
+        const int G = vote_few_counts_codes(N, M, K, codes);
+        const dim3 grid((unsigned)((int64_t)K * ((M + G - 1) / G)));
+        const VoteRecords all{nullptr, nullptr, 0, codes, assign, N};
+        if (G == 1)
+            hipLaunchKernelGGL((vote_few_kernel<VOTE_CODES, 1>), grid, dim3(VOTE_FEW_THREADS), 0, st, hist, hist, 1, (size_t)0, false, counts, K, M, tables, centers, all);
+        else if (G == 2)
+            hipLaunchKernelGGL((vote_few_kernel<VOTE_CODES, 2>), grid, dim3(VOTE_FEW_THREADS), 0, st, hist, hist, 1, (size_t)0, false, counts, K, M, tables, centers, all);
+        else
+            hipLaunchKernelGGL((vote_few_kernel<VOTE_CODES, 4>), grid, dim3(VOTE_FEW_THREADS), 0, st, hist, hist, 1, (size_t)0, false, counts, K, M, tables, centers, all);
         return launched();
     }
     if (route == UPDATE_IN_VOTE) {

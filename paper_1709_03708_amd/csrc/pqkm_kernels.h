@@ -4662,59 +4662,86 @@ __global__ __launch_bounds__(VOTE_THREADS) void vote_kernel(uint32_t* __restrict
 }
 
 // ---------------------------------------------------------------------------------------------
-// Eq. 8 for few clusters: a workgroup serves one cluster and four subspaces, a wave one subspace with four candidates per lane.
+// Eq. 8 for few clusters: a workgroup serves one cluster and four (G) subspaces, a wave one subspace with four candidates per lane.
 // vote_kernel's workgroups are few then, and each fetches 256 KB of table for the rows of sixteen histograms; here the row of
 // every non-zero bin comes straight from the L2, up to 32 rows in flight per wave, and rows that no bin asks for stay there.
 // A row costs its wave about eight vector instructions (the bin's row and count from their lane, an address, four fmaf).
 // Bound by the L2's latency with one wave per SIMD (33 ns per row) and by its bandwidth with many (K = 1000, M = 4, 117 bins: 479 MB at 29
 // TB/s).  Measured, M = 4, K = 100, vote_kernel -> this: 74 bins 13.1 -> 6.9 us, 256 bins 23.4 -> 13.5; with its own counting, 1e4 codes:
 // 16.3 -> 10.4.  One candidate per lane and four waves per subspace: 10.3 instead of 6.9 (issue bound); 16 rows without 16 ahead: 8.2.
-// VOTE_CODES: VOTE_FEW_THREADS threads count the cluster's bins first, of which four waves go on.
+// VOTE_CODES: VOTE_FEW_THREADS threads count the bins of G subspaces of the cluster first, of which G waves go on.  A heavy cluster costs its
+// workgroup the LDS atomics of its members, so that G is as small as one round of workgroups allows.  Members often hold the same
+// subcodes, and lanes that add to one LDS word are served one after the other (40000 codes alike: 137 us): every lane starts with
+// another of the subspaces, and there are VOTE_FEW_COPIES / G copies of the bins.
 // ---------------------------------------------------------------------------------------------
 constexpr int VOTE_FEW_ROWS = 16;        // rows asked for together, and as many ahead of them
 constexpr int VOTE_FEW_THREADS = 512;    // 1024 would leave 128 registers, too few for the rows
+constexpr int VOTE_FEW_COPIES = 32;      // times G bins
+constexpr int VOTE_FEW_PAD = 8;          // words: the same bin of two copies lies in different banks
 
-template <VoteFrom FROM>
+template <VoteFrom FROM, int G = 4>
 __global__ __launch_bounds__(FROM == VOTE_CODES ? VOTE_FEW_THREADS : 256) void vote_few_kernel(
     uint32_t* __restrict__ hist, const uint32_t* __restrict__ parts, int S, size_t part_stride, bool halves,
     uint32_t* __restrict__ counts, int K, int M, const float* __restrict__ tables, uint8_t* __restrict__ centers, VoteRecords vr)
 {
     static_assert(FROM != VOTE_RECORDS, "from partial histograms or from all codes");
-    __shared__ uint32_t bins[FROM == VOTE_CODES ? 4 * L : 1];
-    __shared__ uint2 list[4 * L];            // per wave the non-zero bins in ascending order: byte offset of the row, count as a float
+    static_assert(G == 4 || FROM == VOTE_CODES, "partial histograms: four subspaces");
+    constexpr int COPIES = VOTE_FEW_COPIES / G, COPY = G * L + VOTE_FEW_PAD;
+    __shared__ uint32_t bins[FROM == VOTE_CODES ? COPIES * COPY : 1];
+    __shared__ uint2 list[G * L];            // per wave the non-zero bins in ascending order: byte offset of the row, count as a float
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int quads = (M + 3) / 4;
-    const int k = (int)blockIdx.x / quads, m0 = (int)blockIdx.x % quads * 4;
+    const int quads = (M + G - 1) / G;
+    const int k = (int)blockIdx.x / quads, m0 = (int)blockIdx.x % quads * G;
     uint32_t h[4];                           // bins chunk * 64 + lane
     if (FROM == VOTE_CODES) {
-        for (int i = tid; i < 4 * L; i += VOTE_FEW_THREADS) bins[i] = 0u;
-        __syncthreads();
         constexpr int PER = 20;                                              // codes per thread whose loads travel together
         const bool words = (M & 3) == 0 && ((uintptr_t)vr.codes & 3) == 0;
-        const int width = M - m0 < 4 ? M - m0 : 4;
-        for (int64_t nb = tid; nb < vr.N; nb += VOTE_FEW_THREADS * PER) {
-            int32_t kk[PER];
+        const int width = M - m0 < G ? M - m0 : G;
+        int32_t kk[PER];
+        auto ask = [&](int64_t nb) {
 #pragma unroll
             for (int u = 0; u < PER; ++u) kk[u] = nb + u * VOTE_FEW_THREADS < vr.N ? vr.assign[nb + u * VOTE_FEW_THREADS] : -1;
-            __builtin_amdgcn_sched_barrier(0);
+        };
+        if (tid < vr.N) ask(tid);
+        for (int i = tid; i < COPIES * COPY; i += VOTE_FEW_THREADS) bins[i] = 0u;
+        __syncthreads();
+        uint32_t* const mine = bins + (lane / G & (COPIES - 1)) * COPY;
+        for (int64_t nb = tid; nb < vr.N; nb += VOTE_FEW_THREADS * PER) {
+            if (nb >= VOTE_FEW_THREADS * PER) ask(nb);
+            uint32_t w[PER];
+#pragma unroll
+            for (int u = 0; u < PER; ++u) {
+                w[u] = 0u;
+                if (kk[u] != k) continue;
+                const uint8_t* x = vr.codes + (nb + u * VOTE_FEW_THREADS) * M + m0;
+                if (words) w[u] = *reinterpret_cast<const uint32_t*>(x - (m0 & 3)) >> (8 * (m0 & 3));
+                else if (G == 1) w[u] = x[0];
+                else
+                    for (int i = 0; i < width; ++i) w[u] |= (uint32_t)x[i] << (8 * i);
+            }
+            __builtin_amdgcn_sched_barrier(0);                               // all members' subcodes are asked for before the first is waited for
 #pragma unroll
             for (int u = 0; u < PER; ++u) {
                 if (kk[u] != k) continue;
-                const uint8_t* x = vr.codes + (nb + u * VOTE_FEW_THREADS) * M + m0;
-                if (words) {
-                    const uint32_t w = *reinterpret_cast<const uint32_t*>(x);
 #pragma unroll
-                    for (int i = 0; i < 4; ++i) atomicAdd(&bins[i * L + ((w >> (8 * i)) & 255u)], 1u);
-                } else {
-                    for (int i = 0; i < width; ++i) atomicAdd(&bins[i * L + x[i]], 1u);
+                for (int i = 0; i < G; ++i) {
+                    const int j = (i + lane) & (G - 1);
+                    if (j < width) atomicAdd(&mine[j * L + ((w[u] >> (8 * j)) & 255u)], 1u);
                 }
             }
         }
         __syncthreads();
+        for (int i = tid; i < G * L; i += VOTE_FEW_THREADS) {
+            uint32_t sum = bins[i];
+#pragma unroll
+            for (int c = 1; c < COPIES; ++c) sum += bins[c * COPY + i];
+            bins[i] = sum;
+        }
+        __syncthreads();
     }
     const int m = m0 + wave;
-    if (wave >= 4 || m >= M) return;
+    if (wave >= G || m >= M) return;
     const size_t pair = (size_t)k * M + m;
     if (FROM == VOTE_CODES) {
 #pragma unroll

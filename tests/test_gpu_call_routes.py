@@ -97,3 +97,26 @@ def test_single_codes_left_by_the_matrix_cores(env, M, N, K, blocks):
         want, _, _ = oracle.update(codes, ra, tables, want)
     np.testing.assert_array_equal(a.cpu().numpy(), ra)
     np.testing.assert_array_equal(c.cpu().numpy(), want)
+
+
+# the vote counts: one, two and four subspaces per workgroup, read as words and byte by byte, and what lies beyond its limits
+@pytest.mark.parametrize("M,N,K", [(4, 40_000, 64), (4, 30_001, 65), (4, 10_241, 129), (4, 10_240, 256), (8, 511, 32), (8, 20_481, 64), (3, 12_000, 85), (3, 12_000, 86),
+                                   (6, 12_000, 43), (6, 1499, 128), (1, 9, 1), (4, 28_001, 8), (64, 10_241, 16)])
+@pytest.mark.parametrize("codes_are", ["spread", "alike", "two", "one word"])
+def test_vote_counts_heavy_clusters(env, M, N, K, codes_are):
+    pq, oracle, torch = env
+    rng = np.random.default_rng(N + K)
+    codes = rng.integers(0, 256, (N, M), dtype=np.uint8)
+    assign = rng.integers(-1, K + 1, N).astype(np.int32)                         # some outside: not counted
+    if codes_are != "spread":
+        assign[N // 5:] = K - 1
+        codes[:] = codes[0] if codes_are == "alike" else codes[rng.integers(0, 2, N)] if codes_are == "two" else codes[:, :1]
+    centers = rng.integers(0, 256, (K, M), dtype=np.uint8)
+    tables = rand_tables(rng, M)
+    c = torch.from_numpy(centers.copy()).cuda()
+    _, h, n = pq.update(torch.from_numpy(codes).cuda(), torch.from_numpy(assign).cuda(), torch.from_numpy(tables).cuda(), c)
+    inside = (assign >= 0) & (assign < K)
+    rc, rh, rn = oracle.update(codes[inside], assign[inside], tables, centers)
+    np.testing.assert_array_equal(h.cpu().numpy().view(np.uint32), rh)
+    np.testing.assert_array_equal(n.cpu().numpy().view(np.uint32), rn)
+    np.testing.assert_array_equal(c.cpu().numpy(), rc)
