@@ -1987,13 +1987,20 @@ inline bool vote_counts_codes(int64_t N, int M, int K)
 }
 
 // Few clusters: rows straight from the L2 (vote_few_kernel), while they are fewer than 550000 in all (a cluster has at most 256 non-zero bins
-// per subspace, and no more than it has members).  vote_kernel / this, us: M = 4: 13.1 / 6.9 at N = 1e4, K = 100, 23.4 / 13.5 at 1.28e6, 100,
-// 21.0 / 17.8 at 2e5, 300, but 16.8 / 20.7 at 2e5, 1000; M = 8: 23.5 / 21.8 at 1e6, 256, 21.0 / 16.6 at 4e4, 1000, but 21.2 / 24.1 at 2e5,
-// 300; M = 16: 19.6 / 15.8 at 4e4, 100; M = 32: 45 / 32 at 1e4, 1000, 25.5 / 26.2 at 4e4, 100.
+// per subspace, and no more than it has members; a workgroup's waves beyond M are idle but there).  vote_kernel / this, us: M = 4: 13.1 / 6.9 at N =
+// 1e4, K = 100, 23.4 / 13.5 at 1.28e6, 100, 21.0 / 17.8 at 2e5, 300, but 16.8 / 20.7 at 2e5, 1000; M = 8: 23.5 / 21.8 at 1e6, 256, but 21.2 / 24.1
+// at 2e5, 300; M = 16: 19.6 / 15.8 at 4e4, 100; M = 32: 45 / 32 at 1e4, 1000.  Whole update: M = 6: 45 / 49 at 3e5, 300.
+// Many rows with few bins each: where vote_kernel's workgroups of sixteen clusters are one round that is nearly full, it is the better one
+// (M = 4, K = 1000: 33.7 / 35.9 at 1e5, 31 / 31 at 5e4; M = 8, K = 500: 33.4 / 35.7 at 5e4), and beyond some 10000 workgroups of this one
+// their own cost shows: M = 8, K = 5000: 73 / 68 at 1e4, K = 10000: 108 / 110 at 2e4; M = 16, K = 3000: 73 / 79 at 1e4; M = 24, K = 1500: 79 / 69
+// and K = 2000: 77 / 80 at 5000; M = 32, K = 1000: 61 / 56, K = 3000: 116 / 129 at 1e4; M = 64, K = 1000: 101 / 93, K = 1500: 125 / 127 at 5000; M = 6, K = 3000: 44 / 41, K = 4000: 45 / 48 at 1e4.
 inline bool vote_few(int64_t N, int M, int K)
 {
-    const int64_t rows = (int64_t)K * M * L < N * M ? (int64_t)K * M * L : N * M;
-    return N >= 1 && rows <= 550000 && K <= 65536;
+    const int64_t quads = (M + 3) / 4, waves = M <= 4 ? M : 4 * quads;
+    const int64_t rows = (int64_t)K * waves * L < N * waves ? (int64_t)K * waves * L : N * waves;
+    const int64_t kept = (int64_t)K * M / 16;                      // workgroups of vote_kernel
+    if (kept > cu_count() * 2 / 3 && kept <= cu_count() && rows > 190000) return false;
+    return N >= 1 && rows <= 550000 && (int64_t)K * quads <= (M <= 4 ? 10000 : M % 4 ? 6000 : M <= 8 ? 10000 : M < 40 ? 9000 : 250 * M);
 }
 
 // Few codes as well: each of its workgroups counts its cluster from all codes, as few subspaces as one round of them allows.  Whole update, us,
@@ -2159,8 +2166,8 @@ pqkm_status update_impl(const Options& opt, const Carve& c, const uint8_t* codes
                                codes + n0 * M, cnt, M, assign + n0, K, hist);
         }
     }
-    // (HIST_SUBSPACE is always of few clusters: at most 128 KB of counters per subspace and 16 subspaces, or 31 clusters)
-    if (vote_few(N, M, K)) {
+    // vote_kernel adds at most 16 partial arrays, of 32-bit counters
+    if (path == HIST_SUBSPACE || vote_few(N, M, K)) {
         hipLaunchKernelGGL((vote_few_kernel<VOTE_PARTS>), dim3((unsigned)((int64_t)K * ((M + 3) / 4))), dim3(256), 0, st, hist, parts, S, part_stride,
                            halves, counts, K, M, tables, centers, VoteRecords{});
         return launched();
@@ -2636,7 +2643,7 @@ pqkm_status pqkm_call_plan(int64_t N, int32_t M, int32_t K, int32_t flags, int64
     const UpdateRoute route = update_route(path, opt.hist_kernel, N, M, K, codes);
     out[5] = route == UPDATE_IN_VOTE_FEW ? 5 : route == UPDATE_IN_VOTE ? 6 : (int64_t)path;
     out[6] = route != UPDATE_PASS ? 1 : path == HIST_SUBSPACE ? subspace_hist(N, M, K, c).S : path == HIST_OWNER ? hist_plan(N, M, K).S : 1;
-    out[7] = route == UPDATE_IN_VOTE_FEW || (route == UPDATE_PASS && vote_few(N, M, K)) ? 1 : 0;
+    out[7] = route == UPDATE_IN_VOTE_FEW || (route == UPDATE_PASS && (path == HIST_SUBSPACE || vote_few(N, M, K))) ? 1 : 0;
     return PQKM_OK;
 }
 

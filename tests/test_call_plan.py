@@ -98,3 +98,27 @@ def test_rows_of_sixteen_subspaces(pq):
 def test_vote_that_counts_a_cluster_per_workgroup(pq, M, N, K, aligned, few):
     """Not where a workgroup has too large a share of the codes, or reads four subspaces of them byte by byte."""
     assert (pq.call_plan(N, M, K, codes_aligned=aligned)["count"] == "vote_per_cluster") == few
+
+
+@pytest.mark.parametrize("M,N,K,few", [(4, 47_500, 1000, True), (4, 100_000, 1000, False), (8, 50_000, 500, False), (8, 50_000, 300, True), (6, 300_000, 300, False),
+                                       (6, 300_000, 200, True), (6, 60_000, 3000, True), (6, 10_000, 3001, False), (4, 100_000, 10_000, True), (8, 20_000, 5000, True),
+                                       (8, 20_000, 5001, False), (16, 20_000, 2250, True), (16, 20_000, 2251, False), (32, 10_000, 5000, False), (64, 5000, 1000, True),
+                                       (64, 5000, 1001, False), (2, 200_000, 1000, True), (3, 500_000, 700, True)])
+def test_vote_with_a_workgroup_per_cluster(pq, M, N, K, few):
+    assert pq.call_plan(N, M, K)["vote_per_cluster"] == few
+
+
+def test_partial_histograms_of_subspaces_have_a_vote_that_adds_them(pq):
+    """Up to 64 arrays of 16-bit counters: only the vote with a workgroup per cluster reads them."""
+    import random
+
+    rng = random.Random(1)
+    seen = 0
+    for _ in range(20_000):
+        M, K, N = rng.randint(1, 64), int(2 ** rng.uniform(0, 7.1)), int(2 ** rng.uniform(17, 25))
+        p = pq.call_plan(N, M, K)
+        if p["count"] == "subspaces":
+            seen += 1
+            assert p["vote_per_cluster"], (M, N, K)
+        assert p["slices"] <= (64 if p["vote_per_cluster"] else 16)
+    assert seen > 1000
