@@ -88,7 +88,8 @@ def _ptr(t):
 def _stream():
     import torch
 
-    return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device())
+    raw = getattr(torch._C, "_cuda_getCurrentRawStream", None)        # not public: a torch without it pays for a Stream object
+    return raw(torch.cuda.current_device()) if raw is not None else torch.cuda.current_stream().cuda_stream
 
 
 def _need(t, dtype, shape, name):
