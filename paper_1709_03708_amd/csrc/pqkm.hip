@@ -1782,7 +1782,6 @@ pqkm_status launch_gather(const GatherPlan& plan, const uint8_t* codes, int64_t 
                           int32_t* assign, float* dist, NearRecord* part, const DotState* front, hipStream_t st)
 {
     const int64_t per_launch = (int64_t)CN << 23;                  // 2^31 threads
-    const bool rows = plan.rows;
     for (int64_t n0 = 0; n0 < N; n0 += per_launch) {
         const int64_t cnt = N - n0 < per_launch ? N - n0 : per_launch;
         const int64_t blocks = (cnt + CN - 1) / CN;
@@ -1797,20 +1796,23 @@ pqkm_status launch_gather(const GatherPlan& plan, const uint8_t* codes, int64_t 
         NearRecord* pn = splits > 1 ? part : nullptr;
         const dim3 grid((unsigned)blocks, (unsigned)splits);
         ++t_scan_kernels;
-        if constexpr (MW > 0) {
-            if (rows)
-                hipLaunchKernelGGL((assign_rows_kernel<MW, CN, 256>), grid, dim3(256), 0, st, codes + n0 * M, cnt, centers, K, tables,
-                                   assign + n0, dn, pn, per, front ? &front->left : nullptr, front ? &front->some : nullptr);
+        auto launch_rows = [&]() {
+            if constexpr (MW > 0)
+                hipLaunchKernelGGL((assign_rows_kernel<MW, CN>), grid, dim3(256), 0, st, codes + n0 * M, cnt, centers, K, tables, assign + n0,
+                                   dn, pn, per, front ? &front->left : nullptr, front ? &front->some : nullptr);
             else
-                hipLaunchKernelGGL((assign_gather_kernel<MW, CN, false>), grid, dim3(256), 0, st, codes + n0 * M, cnt, M, centers, K,
-                                   tables, assign + n0, dn, pn, per);
+                hipLaunchKernelGGL((assign_gather_kernel<0, true>), grid, dim3(256), 0, st, codes + n0 * M, M, centers, K, tables, assign + n0,
+                                   dn, pn, per);
+        };
+        // through the caches: byte by byte, or few centers from sixteen subspaces on (gather_rows_min_k), one code per block
+        if constexpr (CN == 1 && (MW == 0 || MW >= 4)) {
+            if (plan.rows)
+                launch_rows();
+            else
+                hipLaunchKernelGGL((assign_gather_kernel<MW, false>), grid, dim3(256), 0, st, codes + n0 * M, M, centers, K, tables, assign + n0,
+                                   dn, pn, per);
         } else {
-            if (rows)
-                hipLaunchKernelGGL((assign_gather_kernel<0, 1, true>), grid, dim3(256), 0, st, codes + n0 * M, cnt, M, centers, K,
-                                   tables, assign + n0, dn, pn, per);
-            else
-                hipLaunchKernelGGL((assign_gather_kernel<0, 1, false>), grid, dim3(256), 0, st, codes + n0 * M, cnt, M, centers, K,
-                                   tables, assign + n0, dn, pn, per);
+            launch_rows();
         }
         if (splits > 1)
             hipLaunchKernelGGL(assign_merge_kernel, dim3((unsigned)((cnt + 3) / 4)), dim3(256), 0, st, pn, cnt, (int)splits,

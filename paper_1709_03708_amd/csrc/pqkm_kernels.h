@@ -657,8 +657,9 @@ __global__ __launch_bounds__(256) void decode_element_kernel(const uint8_t* __re
 // bytes per row, all of them and the first centers' words asked for at once: a block waits for memory twice, for its codes and
 // for the rows.  With few codes that is all it does (48 codes, K = 1000, M = 4: 3.4 us); with many it is bound by the bank conflicts of
 // random four-byte reads (M = 4, K = 4000: 1.4e12 pairs per second).
-// assign_gather_kernel: any M and alignment byte by byte (MW = 0, with the rows in LDS or through the caches), and rows through the caches
-// where few centers would not pay for whole rows at M = 16 and 32 (MW = M / 4): a wave's 64 look-ups into the 8 lines of one row.
+// assign_gather_kernel, one code per block: any M and alignment byte by byte (MW = 0, with the rows in LDS or through the caches), and rows
+// through the caches where few centers would not pay for whole rows at M = 16 and 32 (MW = M / 4): a wave's 64 look-ups into the 8 lines
+// of one row.
 // Measured, rows copied through registers one by one, and split and merged -> this, M = 4: 48 codes, K = 1000: 10.6 -> 3.4 us; 1e4 codes, K =
 // 100: 12.0 -> 7.0, K = 1000: 21.4 -> 12.0, K = 8000: 66 -> 59; M = 8, 500 codes, K = 4096: 18.8 -> 6.1; M = 32, 1e4 codes, K = 1000: 79 -> 65.
 // ---------------------------------------------------------------------------------------------
@@ -670,7 +671,7 @@ __device__ __forceinline__ void near_merge(float& s, int& k, float os, int ok)
 }
 
 // Lanes of a wave hold (distance, index) of CN codes each; afterwards lane i (64 / CN) holds the merged pair of code i.  Halves of the
-// codes are exchanged for halves of the lanes, so that CN = 8 takes 20 shuffles and not 96.
+// codes are exchanged for halves of the lanes, so that CN = 4 takes 14 shuffles and not 48.
 template <int CN>
 __device__ __forceinline__ void near_merge_wave(float (&best)[CN], int (&bk)[CN])
 {
@@ -696,15 +697,15 @@ __device__ __forceinline__ void near_merge_wave(float (&best)[CN], int (&bk)[CN]
     }
 }
 
-template <int MW, int CN, int THREADS>
-__global__ __launch_bounds__(THREADS) void assign_rows_kernel(const uint8_t* __restrict__ codes, int64_t N,
-                                                              const uint8_t* __restrict__ centers, int K,
-                                                              const float* __restrict__ tables,
-                                                              int32_t* __restrict__ assign, float* __restrict__ dist,
-                                                              NearRecord* __restrict__ part, int per, const uint32_t* __restrict__ only_if,
-                                                              const uint32_t* __restrict__ some)
+template <int MW, int CN>
+__global__ __launch_bounds__(256) void assign_rows_kernel(const uint8_t* __restrict__ codes, int64_t N,
+                                                          const uint8_t* __restrict__ centers, int K,
+                                                          const float* __restrict__ tables,
+                                                          int32_t* __restrict__ assign, float* __restrict__ dist,
+                                                          NearRecord* __restrict__ part, int per, const uint32_t* __restrict__ only_if,
+                                                          const uint32_t* __restrict__ some)
 {
-    constexpr int M = 4 * MW, ROWS = CN * M, WAVES = THREADS / 64, MINE = (ROWS + WAVES - 1) / WAVES;
+    constexpr int M = 4 * MW, ROWS = CN * M, THREADS = 256, WAVES = THREADS / 64, MINE = (ROWS + WAVES - 1) / WAVES;
     __shared__ float row_s[ROWS * L];                                // row i * M + m: subspace m for the subcode of code i
     __shared__ NearRecord rec[WAVES][CN];
     const int64_t n0 = (int64_t)blockIdx.x * CN;
@@ -798,113 +799,69 @@ __global__ __launch_bounds__(THREADS) void assign_rows_kernel(const uint8_t* __r
     }
 }
 
-template <int MW, int CN, bool ROWS>
-__global__ __launch_bounds__(256) void assign_gather_kernel(const uint8_t* __restrict__ codes, int64_t N, int Mrt,
+// ROWS: byte by byte only; the look-ups of words through LDS are assign_rows_kernel's
+template <int MW, bool ROWS>
+__global__ __launch_bounds__(256) void assign_gather_kernel(const uint8_t* __restrict__ codes, int Mrt,
                                                             const uint8_t* __restrict__ centers, int K,
                                                             const float* __restrict__ tables,
                                                             int32_t* __restrict__ assign, float* __restrict__ dist,
                                                             NearRecord* __restrict__ part, int per)
 {
+    static_assert(!(MW && ROWS), "rows of words: assign_rows_kernel");
     const int M = MW ? 4 * MW : Mrt;
-    __shared__ float row_s[ROWS ? (MW ? CN * 4 * MW : 64) * L : 1];
-    const int64_t n0 = (int64_t)blockIdx.x * CN;
+    __shared__ float row_s[ROWS ? 64 * L : 1];
+    const int64_t n = blockIdx.x;
+    const uint8_t* x = codes + n * M;
     const int k_begin = (int)blockIdx.y * per;
     const int k_end = K - k_begin < per ? K : k_begin + per;
-    // row i * M + m: the entries of subspace m for the subcode of code i
+    // row m: the entries of subspace m for the code's subcode
     if (ROWS && ((uintptr_t)tables & 15) == 0) {
-        for (int e = threadIdx.x; e < CN * M * (L / 4); e += 256) {
-            const int r = e / (L / 4), i = r / M, m = r % M;
-            const int64_t n = n0 + i < N ? n0 + i : N - 1;
-            const uint32_t x = codes[n * M + m];
-            reinterpret_cast<float4*>(row_s)[e] = reinterpret_cast<const float4*>(tables + ((size_t)m * L + x) * L)[e % (L / 4)];
+        for (int e = threadIdx.x; e < M * (L / 4); e += 256) {
+            const int m = e / (L / 4);
+            reinterpret_cast<float4*>(row_s)[e] = reinterpret_cast<const float4*>(tables + ((size_t)m * L + x[m]) * L)[e % (L / 4)];
         }
     } else if (ROWS) {
-        for (int e = threadIdx.x; e < CN * M * L; e += 256) {
-            const int r = e / L, i = r / M, m = r % M;
-            const int64_t n = n0 + i < N ? n0 + i : N - 1;
-            row_s[e] = tables[((size_t)m * L + codes[n * M + m]) * L + e % L];
-        }
+        for (int e = threadIdx.x; e < M * L; e += 256) row_s[e] = tables[((size_t)(e / L) * L + x[e / L]) * L + e % L];
     }
     if (ROWS) __syncthreads();
-    float best[CN];
-    int bk[CN];
-#pragma unroll
-    for (int i = 0; i < CN; ++i) { best[i] = INFINITY; bk[i] = IDX_NONE; }
+    float best = INFINITY;
+    int bk = IDX_NONE;
     for (int64_t k64 = k_begin + (int)threadIdx.x; k64 < k_end; k64 += 256) {
         const int k = (int)k64;
-        float s[CN];
-        if (!ROWS) {
-            uint32_t c[MW ? MW : 1];
+        float s;
+        if constexpr (MW > 0) {
+            uint32_t c[MW];
 #pragma unroll
             for (int w = 0; w < MW; ++w) c[w] = reinterpret_cast<const uint32_t*>(centers)[(size_t)k * MW + w];
+            float a[4 * MW];
 #pragma unroll
-            for (int i = 0; i < CN; ++i) {
-                const int64_t n = n0 + i < N ? n0 + i : N - 1;                        // the same for all lanes
-                const uint8_t* x = codes + n * M;
-                float a[MW ? 4 * MW : 1];
-                if (MW) {
-#pragma unroll
-                    for (int m = 0; m < 4 * MW; ++m) {
-                        const uint32_t xm = (reinterpret_cast<const uint32_t*>(x)[m / 4] >> (8 * (m % 4))) & 255u;
-                        a[m] = tables[((size_t)m * L + xm) * L + ((c[m / 4] >> (8 * (m % 4))) & 255u)];
-                    }
-                    s[i] = a[0];
-#pragma unroll
-                    for (int m = 1; m < 4 * MW; ++m) s[i] = s[i] + a[m];
-                } else {
-                    const uint8_t* cb = centers + (size_t)k * M;
-                    s[i] = tables[(size_t)x[0] * L + cb[0]];
-#pragma unroll 4
-                    for (int m = 1; m < M; ++m) s[i] = s[i] + tables[((size_t)m * L + x[m]) * L + cb[m]];
-                }
+            for (int m = 0; m < 4 * MW; ++m) {
+                const uint32_t xm = (reinterpret_cast<const uint32_t*>(x)[m / 4] >> (8 * (m % 4))) & 255u;       // the same for all lanes
+                a[m] = tables[((size_t)m * L + xm) * L + ((c[m / 4] >> (8 * (m % 4))) & 255u)];
             }
-        } else if (MW) {
-            const float* at[MW ? 4 * MW : 1];
+            s = a[0];
 #pragma unroll
-            for (int w = 0; w < MW; ++w) {
-                const uint32_t c = reinterpret_cast<const uint32_t*>(centers)[(size_t)k * MW + w];
-                at[4 * w] = row_s + (c & 255u);
-                at[4 * w + 1] = row_s + ((c >> 8) & 255u);
-                at[4 * w + 2] = row_s + ((c >> 16) & 255u);
-                at[4 * w + 3] = row_s + (c >> 24);
-            }
-#pragma unroll
-            for (int m = 0; m < 4 * MW; ++m)
-#pragma unroll
-                for (int i = 0; i < CN; ++i) {
-                    const float a = at[m][(i * 4 * MW + m) * L];
-                    s[i] = m == 0 ? a : s[i] + a;
-                }
+            for (int m = 1; m < 4 * MW; ++m) s = s + a[m];
         } else {
             const uint8_t* c = centers + (size_t)k * M;
-            s[0] = row_s[c[0]];
+            s = ROWS ? row_s[c[0]] : tables[(size_t)x[0] * L + c[0]];
 #pragma unroll 4
-            for (int m = 1; m < M; ++m) s[0] = s[0] + row_s[m * L + c[m]];
+            for (int m = 1; m < M; ++m) s = s + (ROWS ? row_s[m * L + c[m]] : tables[((size_t)m * L + x[m]) * L + c[m]]);
         }
-#pragma unroll
-        for (int i = 0; i < CN; ++i)
-            if (s[i] < best[i]) { best[i] = s[i]; bk[i] = k; }
+        if (s < best) { best = s; bk = k; }
     }
-    static_assert(MW > 0 || CN == 1, "any M: one code");
-    __shared__ NearRecord rec[4][CN];
+    __shared__ NearRecord rec[4];
 #pragma unroll
-    for (int i = 0; i < CN; ++i) {
-#pragma unroll
-        for (int off = 32; off; off >>= 1) near_merge(best[i], bk[i], __shfl_xor(best[i], off), __shfl_xor(bk[i], off));
-        if ((threadIdx.x & 63) == 0) rec[threadIdx.x >> 6][i] = NearRecord{best[i], bk[i]};
-    }
+    for (int off = 32; off; off >>= 1) near_merge(best, bk, __shfl_xor(best, off), __shfl_xor(bk, off));
+    if ((threadIdx.x & 63) == 0) rec[threadIdx.x >> 6] = NearRecord{best, bk};
     __syncthreads();
-    if (threadIdx.x < CN && n0 + threadIdx.x < N) {
-        const int i = threadIdx.x;
-        float s = rec[0][i].dist;
-        int k = rec[0][i].index;
-        for (int w = 1; w < 4; ++w) near_merge(s, k, rec[w][i].dist, rec[w][i].index);
-        const int64_t n = n0 + i;
+    if (threadIdx.x == 0) {
+        for (int w = 1; w < 4; ++w) near_merge(best, bk, rec[w].dist, rec[w].index);
         if (part) {
-            part[n * gridDim.y + blockIdx.y] = NearRecord{s, k};
+            part[n * gridDim.y + blockIdx.y] = NearRecord{best, bk};
         } else {
-            assign[n] = k == IDX_NONE ? 0 : k;
-            if (dist) dist[n] = s;
+            assign[n] = bk == IDX_NONE ? 0 : bk;
+            if (dist) dist[n] = best;
         }
     }
 }
