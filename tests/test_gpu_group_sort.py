@@ -2,6 +2,7 @@
 ragged last one, heavy groups that several workgroups share, one cluster per group, and more groups than a block can count."""
 from __future__ import annotations
 
+import numpy as np
 import pytest
 
 pytestmark = pytest.mark.gpu
@@ -14,6 +15,7 @@ pytestmark = pytest.mark.gpu
 def test_histograms(N, M, K, uneven):
     import torch
 
+    import oracle
     import paper_1709_03708_amd as pq
 
     g = torch.Generator(device="cuda")
@@ -24,6 +26,7 @@ def test_histograms(N, M, K, uneven):
         a = torch.where(torch.rand(N, generator=g, device="cuda") < 0.6, torch.full_like(a, K // 2), a)
     t = torch.rand(M, 256, 256, generator=g, device="cuda")
     c = torch.randint(0, 256, (K, M), generator=g, device="cuda", dtype=torch.uint8)
+    before = c.cpu().numpy()
     pq.set_option("hist_kernel", 3)
     try:
         _, h, n = pq.update(x, a, t, c)
@@ -36,3 +39,33 @@ def test_histograms(N, M, K, uneven):
     for m in range(M):
         ref = torch.bincount(k * 256 + xv[:, m].long(), minlength=K * 256)
         assert torch.equal(h[:, m].reshape(-1).long(), ref)
+    if K * M <= 300_000:                                                          # (their histograms: 300 MB on the host)
+        want = oracle.vote(h.reshape(K, M, 256).cpu().numpy().view(np.uint32), n.cpu().numpy().view(np.uint32), t.cpu().numpy(), before)
+        np.testing.assert_array_equal(c.cpu().numpy(), want)
+
+
+# the smallest sizes at which the iterations of a fit sort by group, too few groups for the line that holds where scans keep their keys
+@pytest.mark.parametrize("M,N,K", [(16, 100_000, 500), (16, 131_077, 641), (32, 100_003, 150), (32, 140_001, 399)])
+@pytest.mark.parametrize("uneven", [False, True])
+def test_fit(M, N, K, uneven):
+    import torch
+
+    import oracle
+    import paper_1709_03708_amd as pq
+    from _util import rand_tables
+
+    assert pq.call_plan(N, M, K)["count"] == "sorted" and pq.call_plan(99_999, M, K)["count"] != "sorted"
+    rng = np.random.default_rng(M + K)
+    tables = rand_tables(rng, M)
+    centers = rng.integers(0, 256, (K, M), dtype=np.uint8)
+    of = rng.integers(0, K, N)
+    if uneven:
+        of[rng.random(N) < 0.6] = K // 2
+    codes = centers[of]
+    other = rng.random((N, M)) < 0.3
+    codes[other] = rng.integers(0, 256, int(other.sum()), dtype=np.uint8)
+    c = torch.from_numpy(centers).cuda()
+    _, a = pq.fit(torch.from_numpy(codes).cuda(), torch.from_numpy(tables).cuda(), c, 2)
+    want, ra, _, _ = oracle.fit(codes, tables, centers, 2)
+    np.testing.assert_array_equal(a.cpu().numpy(), ra)
+    np.testing.assert_array_equal(c.cpu().numpy(), want)
