@@ -107,6 +107,8 @@ inline int64_t group_alloc(int64_t n) { return (n + 30) & ~(int64_t)15; }  // re
 constexpr int SW_C_MAX = 256 * 16;          // most codes a workgroup of the sliding-window scan takes
 inline int64_t sw_alloc(int64_t n) { return ((n + SW_C_MAX - 1) / SW_C_MAX + 1) * SW_C_MAX; }   // whole workgroups of any shape
 
+int cu_count();
+
 // Shape of the LDS-privatised histogram pass: KT clusters per workgroup, `groups` cluster groups, S code slices.
 struct HistPlan { int KT; int64_t groups; int S; bool cheap; };
 
@@ -134,16 +136,28 @@ HistPlan hist_plan(int64_t N, int M, int K)
 // which any was slower, up to 9 %); M = 4: 230 / 192 at 2e6, 5000; M = 8: 179 / 176 at 1e6, 4000, 214 / 202 at 3e6, 2000; M = 16: 241 /
 // 198 at 3e6, 1000; M = 24: 251 / 245 at 1e6, 1200; M = 48: 250 / 204 at 1e6, 500.  Uneven clusters: 640 / 165, 598 / 171, 788 / 181,
 // 1187 / 210, 2052 / 214, 1975 / 240, 3254 / 227.  Tight ones: M = 4: 355 / 164; M = 8: 415 / 159; M = 16: 1076 / 222.
-// Sorted by group, which came later, the line lies lower, from 1e5 codes and 8000 histograms of a subspace on (4800 from M = 16 on).  Even
-// clusters, owner / sorted: M = 4: 113 / 96 at 1e6, 3000, 104 / 102 at 2e6, 2000, but 79 / 88 at 1e6, 1200; M = 8: 66 / 63 at 3e5, 1000, 88 / 87
-// at 1e6, 1000, but 134 / 139 at 3e6, 600; M = 12: 70 / 76 at 3e5, 500; M = 16: 61 / 63 at 1e5, 300, 96 / 94 at 1e6, 300, 152 / 136 at 1e6,
-// 1000, but 51 / 67 at 6e5, 100; M = 32: 119 / 101 at 3e5, 300, 116 / 108 at 1e6, 150; byte by byte M = 6: 99 / 119 at 1e6, 800.  Uneven
-// ones at the same sizes: 174 / 95, 290 / 111 (157 / 87); 107 / 75, 221 / 94 (573 / 165); (118 / 87); 77 / 65, 346 / 104, 599 / 138 (184 /
-// 81); 221 / 107, 563 / 128; (272 / 144).  Not in the fits whose lower-bound scans keep their keys in the sorted indices' room (`keys`).
+// Sorted by group, which came later, it pays from 1e5 codes on where the owner path's workgroups need a second round (it then leaves half of the
+// last one idle) and, in one round, where 64 KB of counters divide by M: from 12000 histograms of a subspace on at M = 4 and 8, 8000 at M =
+// 16, 4800 at M = 32 and 64.  Clusters of even / of uneven size (the cube of a random number), owner : sorted.  Two rounds: M = 4, K = 3000: 49.7 :
+// 39.6 / 50.9 : 41.2 at 1e5, 143 : 110 / 150 : 123 at 2e6; M = 8, 1500: 61 : 50 / 65 : 56 at 1e5; M = 12, 1333: 169 : 137 / 163 : 150 at 1e6; M = 24,
+// 333: 98 : 85 / 91 : 97 at 4e5; M = 40, 400: 101 : 90 / 108 : 108 at 1e5.  One round: M = 4, K = 4000: 44.5 : 45.1 / 46.0 : 46.9 at 1e5, 102 : 92 / 117 :
+// 107 at 1e6; K = 2000: 37.8 : 36.0 / 40.0 : 37.5 at 1e5, but 53.8 : 56.4 / 59.4 : 61.8 at 4e5; M = 8, K = 1000: 53.3 : 52.3 / 60.3 : 60.1 at 2e5, but 63.4 :
+// 62.2 / 67.8 : 71.3 at 4e5; M = 16, K = 500: 53.5 : 51.0 / 60.3 : 60.3 at 1e5; K = 300: 98.8 : 94.0 / 133 : 105 at 1e6, but 52.7 : 54.5 / 57.9 : 59.7 at
+// 1e5; M = 32, K = 150: 65.5 : 65.6 / 69.7 : 69.7 at 1e5.  Not where M leaves counters unused: M = 12, K = 1000: 65.0 : 71.4 / 74.1 : 77.9 at 2e5, K = 2000:
+// 56.4 : 66.7 at 1e5; M = 24, 200: 60.4 : 65.3; M = 48, 500: 89.5 : 97.2; M = 20 (K = 400: 94 : 88 / 94 : 104 at 4e5); nor where one round without slices
+// has little to do: M = 8, K = 4060: 73 : 77 / 79 : 83 at 2e5, M = 16, K = 1737: 94 : 97 at 2.2e5, but M = 32, K = 805: 144 : 138 at 3e5.  A power law gains
+// more (M = 16, K = 1000, 1e6: 599 : 138).  Not in the fits whose lower-bound scans keep their keys in the sorted indices' room (`keys`).
 inline bool sorted_histogram_pays(const HistPlan& hp, int64_t N, int M, int K, bool keys)
 {
     if (N > (int64_t)0xffffffff) return false;
-    if (!keys && N >= 100000 && (M & 3) == 0 && (int64_t)K * M >= (M < 16 ? 8000 : 4800)) return true;
+    const bool two_rounds = hp.groups * hp.S > cu_count();
+    if (!keys && N >= 100000 && (M == 4 || M == 12 || (M % 8 == 0 && M != 56)) && (two_rounds || hp.S > 1 || N * M >= 4000000)) {
+        const int64_t bins = (int64_t)K * M;
+        if (bins >= 6000 && two_rounds) return true;
+        if (M <= 8 && (bins >= 12000 || (bins >= 8000 && (N < 300000 || N >= 1500000)))) return true;
+        if (M == 16 && bins >= (N >= 800000 ? 4800 : 8000)) return true;
+        if ((M == 32 || M == 64) && bins >= 4800) return true;
+    }
     return hp.groups > 100 && (double)hp.groups * (double)N > 2.2e8;
 }
 

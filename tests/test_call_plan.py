@@ -122,3 +122,15 @@ def test_partial_histograms_of_subspaces_have_a_vote_that_adds_them(pq):
             assert p["vote_per_cluster"], (M, N, K)
         assert p["slices"] <= (64 if p["vote_per_cluster"] else 16)
     assert seen > 1000
+
+
+@pytest.mark.parametrize("M,N,K,by_group", [(4, 100_000, 3000, True), (12, 1_000_000, 1333, True), (24, 400_000, 333, True), (40, 100_000, 400, True), (48, 100_000, 166, True),
+                                            (4, 100_000, 2000, True), (4, 299_999, 2000, True), (4, 1_500_000, 2000, True), (8, 2_000_000, 5000, True), (16, 100_000, 500, True),
+                                            (16, 800_000, 300, True), (32, 100_000, 150, True), (64, 100_000, 75, True),
+                                            (4, 99_999, 3000, False), (4, 300_000, 2000, False), (8, 1_000_000, 1000, False), (16, 100_000, 300, False), (12, 200_000, 1000, False),
+                                            (12, 100_000, 2000, False), (20, 400_000, 400, False), (24, 100_000, 200, False), (48, 100_000, 100, False),
+                                            (48, 100_000, 500, False), (6, 300_000, 1000, False), (8, 201_135, 4060, False), (16, 224_433, 1737, False),
+                                            (32, 299_108, 805, True), (56, 232_257, 133, False)])
+def test_sort_by_group(pq, M, N, K, by_group):
+    """Not where clusters of nearly even size lose by it: a last round of the owner path that is full, and groups that leave counters unused."""
+    assert pq.call_plan(N, M, K)["count"] == ("sorted" if by_group else "cluster_groups")
