@@ -1686,8 +1686,10 @@ double rows_us(int64_t N, int M, int K)
 // smallest workgroups: a fixed part and about 2.45 us (M = 4) per tile of 128 / M centers.  Where the scan on the matrix cores takes
 // over from the tiled ones (dot_scan_dims) that is the limit.  With distances, tiled / one lane per center, us, on either side: M = 4, K = 1000:
 // 87 / 64 at N = 7e4, 90 / 98 at 1.1e5; K = 300: 32.6 / 22.5 at 4e4, 33 / 36 at 7e4; M = 8, K = 300: 50 / 37 at 4e4, 51 / 59 at 7e4; M = 16, K =
-// 160: 55 / 33 at 2e4, 55 / 60 at 4e4; M = 32, K = 160: 136 / 73 at 2e4, 134 / 138 at 4e4.  Fewer than 160 centers, without the rows: 7 us +
-// 0.6 ns N against 7 us + 2.8 us for every 32 centers at M = 4, 4.7 us at M = 8 and 7 us at M = 16 (with rows it is faster beyond that).
+// 160: 55 / 33 at 2e4, 55 / 60 at 4e4; M = 32, K = 160: 136 / 73 at 2e4, 134 / 138 at 4e4.  Fewer than 160 centers: 7 us + 0.6 ns N against 7 us + 2.8 us
+// for every 32 centers at M = 4, 4.7 us at M = 8 and 7 us at M = 16, the line of the rows through the caches, which hold for M = 16 below 96 centers and M =
+// 32; with the rows in LDS the two are even at twice to three times as many codes: M = 4: 10.3 / 10.5 at 2e4, K = 16; 17.3 / 18.8 at 4e4, K = 100 (12.5 /
+// 7.3 at 1e4, K = 64); M = 8: 13.3 / 13.5 at 16384, K = 32; 28.5 / 31.6 at 4e4, K = 130; M = 16: 39.3 / 29.8 at 2e4, K = 100.
 // Centers that are not aligned are read byte by byte, one code per block, several times as slowly, and the line stays lower.  Tiled / so, us:
 // M = 4, K = 1000: 88 / 431 at 9e4, K = 300: 32 / 88 at 4.6e4; M = 8, K = 1000: 145 / 562 at 7e4; M = 32, K = 300: 223 / 365 at 2.5e4.
 int64_t gather_max_codes(int M, int K, bool aligned)
