@@ -1675,12 +1675,24 @@ bool lane_per_code(int64_t N, int M, int K)
 }
 
 // us of the scan with one lane per center and its rows in LDS (many codes): measured at K = 160, 300, 1000 and 4000, ns per code: M = 4:
-// 0.40, 0.44, 0.85, 2.8; M = 8: 0.68, 0.79, 1.6, 5.6; M = 16: 1.35, 1.6, 3.3, 10.8; M = 32: 3.35, 3.9, 5.9, 21.
+// 0.40, 0.44, 0.85, 2.8; M = 8: 0.68, 0.79, 1.6, 5.6; M = 16: 1.35, 1.6, 3.3, 10.8; M = 32: 3.35, 3.9, 5.9, 21.  A block's only pass takes hardly less with
+// fewer than 256 centers (K = 180, 200, 230: M = 4: 0.39, 0.41, 0.41; M = 8: 0.70, 0.72, 0.73).
 double rows_us(int64_t N, int M, int K)
 {
     const double base = M == 4 ? 0.26 : M == 8 ? 0.43 : M == 16 ? 1.0 : 2.4, pass = M == 4 ? 0.164 : M == 8 ? 0.33 : M == 16 ? 0.61 : 1.15;
-    return 3.6 + 0.001 * (double)N * (base + pass * ((double)K / 256.0));
+    const double least = M == 4 ? 0.405 : M == 8 ? 0.725 : 0.0, code = base + pass * ((double)K / 256.0);
+    return 3.6 + 0.001 * (double)N * (code > least ? code : least);
 }
+
+// us of the tiled scans while one round of their smallest workgroups covers the codes: a fixed part and the tiles of 128 / M centers
+double one_round_tiled_us(int M, int K)
+{
+    const double tiles = (double)(((int64_t)K * M + 127) / 128);
+    return M == 4 ? 8.0 + 2.45 * tiles : M == 8 ? 9.5 + 2.12 * tiles : M == 16 ? 11.8 + 2.13 * tiles : 19.5 + 2.63 * tiles;
+}
+
+// Codes up to which one lane per center is the faster one whatever the alignment
+inline int64_t gather_codes_any(int K) { return (int64_t)120000 * K / (1550 + (int64_t)K); }
 
 // Most codes for which it is faster than the tiled scans (M = 4, 8, 16, 32), whose time does not depend on N below one round of their
 // smallest workgroups: a fixed part and about 2.45 us (M = 4) per tile of 128 / M centers.  Where the scan on the matrix cores takes
@@ -1694,12 +1706,10 @@ double rows_us(int64_t N, int M, int K)
 // M = 4, K = 1000: 88 / 431 at 9e4, K = 300: 32 / 88 at 4.6e4; M = 8, K = 1000: 145 / 562 at 7e4; M = 32, K = 300: 223 / 365 at 2.5e4.
 int64_t gather_max_codes(int M, int K, bool aligned)
 {
-    const int64_t least = (int64_t)120000 * K / (1550 + (int64_t)K);
+    const int64_t least = gather_codes_any(K);
     if (K >= 160 && !aligned) return least;
     if (K >= 160) {
-        const int64_t tiles = ((int64_t)K * M + 127) / 128;
-        const double tiled = M == 4 ? 8.0 + 2.45 * (double)tiles : M == 8 ? 9.5 + 2.12 * (double)tiles : M == 16 ? 11.8 + 2.13 * (double)tiles : 19.5 + 2.63 * (double)tiles;
-        int64_t most = (int64_t)((tiled - 3.6) / (rows_us(1000000, M, K) - 3.6) * 1e6);
+        int64_t most = (int64_t)((one_round_tiled_us(M, K) - 3.6) / (rows_us(1000000, M, K) - 3.6) * 1e6);
         const int64_t dot_from = M == 8 ? 90000000 / K : M == 16 && 9000000 / K < 25000 ? 25000 : 9000000 / K;
         if (M > 4 && (M > 8 || K >= 500) && most >= dot_from) most = dot_from - 1;
         if (most > 512 * (int64_t)cu_count()) most = 512 * (int64_t)cu_count();
@@ -1717,6 +1727,9 @@ int64_t gather_max_codes(int M, int K, bool aligned)
 // 2.5e4; K = 1000: 63 (49 / 71 / 73) at 1.8e4, 152 (65 / 75 / 159) at 4.6e4; K = 4000: 201 (92 / 138 / 208) at 1.8e4; M = 32, K = 160: 90 (53 / 59 /
 // 99) at 2.5e4; K = 1000: 78 (61 / 77 / 86) at 1.2e4, 279 (69 / 95 / 290) at 4.6e4.  More centers than codes lie close together, and a scan that then leaves them
 // all was for nothing (M = 16, N = 8000, K = 50000 of 500 components: 1060 and 1590): it has to promise more.
+// Nor where tables that it is not for would take longer than by the tiled scans, us, tiled / 128 dimensions / left to one lane per center: M = 8, K = 300: 50
+// (44 / 59) at 5.6e4; K = 400: 63 (47 / 71) at 6.2e4, but K = 512: 80 (48 / 77) at 6e4; M = 16, K = 160: 55 (40 / 66) at 3.7e4; K = 200: 66 (42 / 75) at 4.2e4,
+// but K = 256: 84 (40 / 67) at 3.5e4; M = 32, K = 160: 134 (51 / 147) at 3.9e4.  (rows_us is a tenth too long at M = 8 between 256 and 700 centers.)
 int dot_before_rows(int M, const Options& opt, int64_t N, int K, const uint8_t* codes, const uint8_t* centers, const Carve& c)
 {
     if (M < 8 || !tiled_M(M) || K < 160 || K > (1 << 22) || opt.assign_kernel == 1 || c.dot_off == 0 ||
@@ -1725,6 +1738,7 @@ int dot_before_rows(int M, const Options& opt, int64_t N, int K, const uint8_t* 
     const int64_t round = 256 * (int64_t)cu_count(), rounds = (N + round - 1) / round;
     const double few = M == 8 ? 35.0 : M == 16 ? 32.0 : 45.0, many = M == 8 ? 49.0 : M == 16 ? 37.0 : 51.0, rows = rows_us(N, M, K);
     auto dot = [&](double fixed, double center) { return fixed + center * K * (double)rounds + 10.0 * (double)(rounds - 1); };
+    if (N > gather_codes_any(K) && rows + (M == 8 ? 14.0 : 10.0) > (M == 8 ? 1.12 : 1.0) * one_round_tiled_us(M, K)) return 0;
     return rows > (K > N ? 1.6 : 1.25) * dot(many, 0.025) ? 256 : rows > (K > N ? 1.5 : 1.2) * dot(few, 0.015) ? 128 : 0;
 }
 

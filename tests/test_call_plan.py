@@ -134,3 +134,17 @@ def test_partial_histograms_of_subspaces_have_a_vote_that_adds_them(pq):
 def test_sort_by_group(pq, M, N, K, by_group):
     """Not where clusters of nearly even size lose by it: a last round of the owner path that is full, and groups that leave counters unused."""
     assert pq.call_plan(N, M, K)["count"] == ("sorted" if by_group else "cluster_groups")
+
+
+@pytest.mark.parametrize("M,N,K,dims", [(8, 56_000, 300, 0), (8, 50_000, 400, 128), (8, 62_000, 400, 0), (8, 60_000, 512, 128), (16, 28_000, 160, 128), (16, 36_000, 160, 0),
+                                        (16, 41_000, 200, 0), (16, 35_000, 256, 256), (32, 34_000, 160, 256), (32, 38_000, 160, 0), (32, 39_000, 230, 256)])
+def test_matrix_cores_where_being_left_costs_no_more_than_tiles(pq, M, N, K, dims):
+    """Tables they are not for pay 10 to 14 us to be told so, in front of one lane per center."""
+    p = pq.call_plan(N, M, K)
+    assert p["scan"] == "one_lane_per_center" and p["dot"] == dims
+
+
+@pytest.mark.parametrize("M,K,most", [(4, 160, 41_111), (4, 200, 53_209), (4, 300, 63_911), (8, 160, 37_379), (8, 200, 46_151), (8, 300, 56_543)])
+def test_limit_of_rows_with_one_pass(pq, M, K, most):
+    """A block's only pass takes hardly less with fewer centers."""
+    assert pq.call_plan(most, M, K)["scan"] == "one_lane_per_center" and pq.call_plan(most + 1, M, K)["scan"] == "tiled"
