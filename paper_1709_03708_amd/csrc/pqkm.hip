@@ -1184,13 +1184,14 @@ SubspaceHist subspace_hist(int64_t N, int M, int K, const Carve& c)
 {
     SubspaceHist p{0, 1, false};
     // Every workgroup reads a word of every code of its slice, whatever M is, and leaves K G KB for the vote to add; the owner
-    // path reads a byte per code and group, but a heavy cluster is the work of one of its workgroups.  Clusters of even size, whole
-    // update, owner / this, us: M = 4, K = 100: 42 / 54 at N = 5e5, 54 / 57 at 1e6, 104 / 87 at 3e6; M = 8, K = 100: 60 / 72 at
-    // 1e6, 120 / 90 at 3e6; M = 16, K = 100: 72 / 110 at 1e6, 150 / 145 at 3e6; M = 32, K = 100: 96 / 285 at 1e6, 208 / 412 at
-    // 3e6; M = 4, K = 10: 82 / 113 at 3e6; M = 16, K = 10: 68 / 63 at 1e6.  Uneven clusters (a power law): M = 4, K = 100, 1e6:
-    // 150 / 58, M = 8, 3e6: 666 / 91.  Taken where it does not cost even clusters more than a few per cent.
+    // path reads a byte per code and group, but a heavy cluster is the work of one of its workgroups.  Clusters of even / of uneven size (the cube of a
+    // random number), whole update, owner : this, us: M = 4, K = 100: 28.5 : 31.4 / 39.8 : 31.2 at N = 4e5, 37.5 : 31.5 / 57.7 : 31.2 at 8e5, 89.7 : 40.0 / 184 :
+    // 39.8 at 3.2e6; M = 8, K = 48: 49.8 : 34.8 / 100 : 34.9 at 8e5; K = 100: 66.7 : 50.4 / 151 : 50 at 1.6e6; M = 16, K = 48: 67 : 44 / 161 : 44 at 8e5; M = 32, K =
+    // 20: 104 : 64 / 177 : 65 at 8e5.  32 clusters of four subspaces per workgroup are fewer workgroups: M = 4: 32.6 : 34.3 at 8e5, 47.0 : 39.6 at 1.6e6; M = 12: 33.3
+    // : 36.5 at 1e6 where members share subcodes.  Taken where it does not cost even clusters more than a few per cent.
     if (N > (int64_t)0xffffffff || (int64_t)K * L > SUBSPACE_HIST_WORDS) return p;
-    if (!(K >= 32 && M >= 4 && M <= 16 && N >= (int64_t)300000 * M) && !(K < 32 && M >= 16 && N >= 1000000)) return p;
+    const int64_t least = K == 32 ? (M == 4 ? 1200000 : 1500000) : 1000000;
+    if (N < least || !(K >= 32 ? M >= 4 && M <= 16 : M >= 16)) return p;
     p.G = 1;
     while (p.G < 4 && p.G * 2 <= M && (int64_t)K * L * p.G * 2 <= SUBSPACE_HIST_WORDS) p.G *= 2;
     const int64_t groups = (M + p.G - 1) / p.G;
@@ -1204,7 +1205,8 @@ SubspaceHist subspace_hist(int64_t N, int M, int K, const Carve& c)
     p.S = slices((size_t)K * M * L * sizeof(uint16_t));
     p.halves = p.S > 1 && ((N + p.S - 1) / p.S + 1023) / 1024 * 1024 <= SUBSPACE_HALF_CODES;
     if (!p.halves) p.S = slices((size_t)K * M * L * sizeof(uint32_t));
-    // with fewer slices (no room for their arrays) the chip is half idle: M = 4, K = 128, N = 1e6: 70 us with 8
+    // With fewer slices (no room for their arrays) the chip is half idle, owner : this: M = 8, K = 128: 41.5 : 60.6 with 6 at 8e5, 62.2 : 61.3 with 12 at 1.6e6; M =
+    // 16, K = 64: 55.3 : 73.6 with 6; with 12, where all codes are alike, 123 : 136.
     if (K >= 32 && p.S < 16) p.G = 0;
     return p;
 }

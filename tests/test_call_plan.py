@@ -148,3 +148,12 @@ def test_matrix_cores_where_being_left_costs_no_more_than_tiles(pq, M, N, K, dim
 def test_limit_of_rows_with_one_pass(pq, M, K, most):
     """A block's only pass takes hardly less with fewer centers."""
     assert pq.call_plan(most, M, K)["scan"] == "one_lane_per_center" and pq.call_plan(most + 1, M, K)["scan"] == "tiled"
+
+
+@pytest.mark.parametrize("M,N,K,taken", [(4, 1_000_000, 100, True), (4, 999_999, 100, False), (4, 1_200_000, 32, True), (4, 1_199_999, 32, False), (8, 1_000_000, 48, True),
+                                         (12, 1_499_999, 32, False), (12, 1_500_000, 32, True), (8, 1_700_000, 100, True), (8, 1_600_000, 128, False), (8, 2_200_000, 128, True),
+                                         (16, 1_600_000, 64, False), (16, 2_200_000, 64, True), (17, 4_000_000, 33, False), (32, 1_000_000, 20, True),
+                                         (4, 2_000_000, 31, False)])
+def test_histograms_by_subspace(pq, M, N, K, taken):
+    """Enough slices to fill the chip, and codes to pay for adding their arrays."""
+    assert (pq.call_plan(N, M, K)["count"] == "subspaces") == taken

@@ -120,3 +120,23 @@ def test_vote_counts_heavy_clusters(env, M, N, K, codes_are):
     np.testing.assert_array_equal(h.cpu().numpy().view(np.uint32), rh)
     np.testing.assert_array_equal(n.cpu().numpy().view(np.uint32), rn)
     np.testing.assert_array_equal(c.cpu().numpy(), rc)
+
+
+# histograms by subspace from their smallest sizes on, codes off their alignment
+@pytest.mark.parametrize("M,N,K", [(4, 1_000_000, 33), (5, 1_500_000, 32), (4, 1_000_003, 100), (7, 1_000_001, 48), (16, 2_200_001, 64), (8, 1_700_000, 100)])
+@pytest.mark.parametrize("off", [0, 1])
+def test_histograms_by_subspace(env, M, N, K, off):
+    pq, oracle, torch = env
+    rng = np.random.default_rng(N + M)
+    codes = rng.integers(0, 256, (N, M), dtype=np.uint8)
+    codes[:, 0] &= 3                                                             # many members in few bins
+    assign = rng.integers(0, K, N).astype(np.int32)
+    assign[: N // 2] = K - 1
+    centers, tables = rng.integers(0, 256, (K, M), dtype=np.uint8), rand_tables(rng, M)
+    assert pq.call_plan(N, M, K, codes_aligned=not off)["count"] == "subspaces"
+    c = torch.from_numpy(centers.copy()).cuda()
+    _, h, n = pq.update(_off(torch, codes, off), torch.from_numpy(assign).cuda(), torch.from_numpy(tables).cuda(), c)
+    rc, rh, rn = oracle.update(codes, assign, tables, centers)
+    np.testing.assert_array_equal(h.cpu().numpy().view(np.uint32), rh)
+    np.testing.assert_array_equal(n.cpu().numpy().view(np.uint32), rn)
+    np.testing.assert_array_equal(c.cpu().numpy(), rc)
