@@ -2020,8 +2020,10 @@ inline bool vote_counts_codes(int64_t N, int M, int K)
     return N >= 1 && N <= 40000 && blocks <= (N <= 20000 ? 512 : 256);
 }
 
-// Few clusters: rows straight from the L2 (vote_few_kernel), while they are fewer than 550000 in all (a cluster has at most 256 non-zero bins
-// per subspace, and no more than it has members; a workgroup's waves beyond M are idle but there).  vote_kernel / this, us: M = 4: 13.1 / 6.9 at N =
+// Few clusters: rows straight from the L2 (vote_few_kernel), while they are fewer than 550000 in all, from M = 4 on 524288 (a cluster has at most 256 non-zero
+// bins per subspace, and no more than it has members; a workgroup's waves beyond M are idle but there).  Whole update at 4e5 codes, vote_kernel / this, us, on
+// either side: M = 4: 40.3 / 36.4 at K = 488, 40.6 / 41.3 at 536; M = 5: 45.8 / 42.6 at 244, 46.2 / 49.4 at 268; M = 8: 44.4 / 41.0 and 45.1 / 47.5; M = 3: 40.5 /
+// 37.5 at 714.  The vote alone, vote_kernel / this, us: M = 4: 13.1 / 6.9 at N =
 // 1e4, K = 100, 23.4 / 13.5 at 1.28e6, 100, 21.0 / 17.8 at 2e5, 300, but 16.8 / 20.7 at 2e5, 1000; M = 8: 23.5 / 21.8 at 1e6, 256, but 21.2 / 24.1
 // at 2e5, 300; M = 16: 19.6 / 15.8 at 4e4, 100; M = 32: 45 / 32 at 1e4, 1000.  Whole update: M = 6: 45 / 49 at 3e5, 300.
 // Many rows with few bins each: where vote_kernel's workgroups of sixteen clusters are one round that is nearly full, it is the better one
@@ -2034,7 +2036,8 @@ inline bool vote_few(int64_t N, int M, int K)
     const int64_t rows = (int64_t)K * waves * L < N * waves ? (int64_t)K * waves * L : N * waves;
     const int64_t kept = (int64_t)K * M / 16;                      // workgroups of vote_kernel
     if (kept > cu_count() * 2 / 3 && kept <= cu_count() && rows > 190000) return false;
-    return N >= 1 && rows <= 550000 && (int64_t)K * quads <= (M <= 4 ? 10000 : M % 4 ? 6000 : M <= 8 ? 10000 : M < 40 ? 9000 : 250 * M);
+    const int64_t most = M <= 3 ? 550000 : (int64_t)2 * cu_count() * 4 * L;       // two rounds of its workgroups with all bins
+    return N >= 1 && rows <= most && (int64_t)K * quads <= (M <= 4 ? 10000 : M % 4 ? 6000 : M <= 8 ? 10000 : M < 40 ? 9000 : 250 * M);
 }
 
 // Few codes as well: each of its workgroups counts its cluster from all codes, as few subspaces as one round of them allows.  Whole update, us,

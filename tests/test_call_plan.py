@@ -103,7 +103,8 @@ def test_vote_that_counts_a_cluster_per_workgroup(pq, M, N, K, aligned, few):
 @pytest.mark.parametrize("M,N,K,few", [(4, 47_500, 1000, True), (4, 100_000, 1000, False), (8, 50_000, 500, False), (8, 50_000, 300, True), (6, 300_000, 300, False),
                                        (6, 300_000, 200, True), (6, 60_000, 3000, True), (6, 10_000, 3001, False), (4, 100_000, 10_000, True), (8, 20_000, 5000, True),
                                        (8, 20_000, 5001, False), (16, 20_000, 2250, True), (16, 20_000, 2251, False), (32, 10_000, 5000, False), (64, 5000, 1000, True),
-                                       (64, 5000, 1001, False), (2, 200_000, 1000, True), (3, 500_000, 700, True)])
+                                       (64, 5000, 1001, False), (2, 200_000, 1000, True), (3, 500_000, 700, True), (4, 500_000, 512, True), (4, 500_000, 513, False),
+                                       (8, 500_000, 256, True), (8, 500_000, 257, False), (5, 400_000, 257, False)])
 def test_vote_with_a_workgroup_per_cluster(pq, M, N, K, few):
     assert pq.call_plan(N, M, K)["vote_per_cluster"] == few
 
