@@ -78,29 +78,36 @@ def workspace_bytes(N: int, M: int, K: int) -> int:
 # A call of a few codes takes as long as this marshalling: the kernel of 48 codes and 1000 centers 3.4 us, the call 9.3 us with a
 # c_void_p made per pointer (argtypes convert plain integers and None by themselves), a Stream object per call, an import of
 # torch per operand and shapes copied to compare them, 6.4 without.
-_tensor = None
+_torch = None
 
 
 def _ptr(t):
     return t.data_ptr() if t is not None else None
 
 
-def _stream():
+def _load_torch():
+    global _torch
     import torch
 
-    raw = getattr(torch._C, "_cuda_getCurrentRawStream", None)        # not public: a torch without it pays for a Stream object
-    return raw(torch.cuda.current_device()) if raw is not None else torch.cuda.current_stream().cuda_stream
+    _torch = torch
+
+
+def _stream():
+    if _torch is None:
+        _load_torch()
+    try:
+        raw = _torch._C._cuda_getCurrentRawStream
+    except AttributeError:                    # not public: a torch without it pays for a Stream object
+        return _torch.cuda.current_stream().cuda_stream
+    return raw(_torch.cuda.current_device())
 
 
 def _need(t, dtype, shape, name):
-    global _tensor
     if t is None:
         return
-    if _tensor is None:
-        import torch
-
-        _tensor = torch.Tensor
-    if not isinstance(t, _tensor) or not t.is_cuda or not t.is_contiguous():
+    if _torch is None:
+        _load_torch()
+    if not isinstance(t, _torch.Tensor) or not t.is_cuda or not t.is_contiguous():
         raise TypeError(f"{name}: expected a contiguous CUDA tensor")
     if t.dtype != dtype or t.shape != shape:
         raise TypeError(f"{name}: expected {dtype} {tuple(shape)}, got {t.dtype} {tuple(t.shape)}")

@@ -1773,7 +1773,7 @@ GatherPlan gather_plan(int64_t N, int M, int K, bool aligned, size_t room, bool 
         return p;
     }
     const int64_t passes = ((int64_t)K + 255) / 256;               // of a block over its centers
-    const int64_t ncu = cu_count(), most = N > 0 ? (int64_t)(room / sizeof(NearRecord)) / N : 0;      // whose records fit their room
+    const int64_t ncu = cu_count(), records = (int64_t)(room / sizeof(NearRecord));
     if (p.words && p.rows) {
         // Codes per block and parts of the centers by the time they take: a compute unit has k blocks, and a block's pass takes 10 ns M per
         // code of it where they share the unit, and 20 ns more by itself; beside its passes a block costs 50 ns + 4.5 ns M per code,
@@ -1782,17 +1782,20 @@ GatherPlan gather_plan(int64_t N, int M, int K, bool aligned, size_t room, bool 
         // 1000: 4.2 (1 x 1) / 4.3 (2 x 1) / 4.9 (4 x 1), N = 8000: 12.6 / 10.6 / 10.0; M = 8, N = 257, K = 300000: 196 / 110 (1 x 24);
         // M = 16, N = 257, K = 50000: 69 / 42 (2 x 16), N = 8000, K = 1000: 30.1 (1 x 1) / 28.6 (2 x 1) / 33.5 (4 x 1); M = 32, N =
         // 257, K = 50000: 134 / 79 (1 x 24).  Two codes of M = 16 leave room for fewer blocks, which few passes show: K = 300, N = 1e4: 19.4 / 21.7.
+        // (A block of one code per unit and too few passes for parts: nothing to choose, and the call waits for this arithmetic.)
+        if (N <= ncu && (double)passes * (M < 8 ? 0.09 : 0.0104 * M + 0.02) < 2.8) return p;
         double best = 1e300;
         const int widest = N < 2 || M == 32 || (M == 16 && passes <= 2) ? 1 : M == 4 ? 4 : 2;
-        for (int codes = 1; codes <= widest; codes *= 2) {
-            const int64_t blocks = (N + codes - 1) / codes;
+        for (int log = 0; 1 << log <= widest; ++log) {
+            const int codes = 1 << log;
+            const int64_t blocks = (N + codes - 1) >> log;
             const double code = 0.0104 * M * codes, pass = code + (codes == 1 ? 0.005 : 0.0), lone = code + 0.02 < 0.09 ? 0.09 : code + 0.02;
             const double beside = 0.05 + 0.0045 * M * codes;
             const int64_t parts_of[] = {1, 2, 3, 4, 6, 8, 12, 16, 24, 32, 64, 128, passes};
             for (int64_t parts : parts_of) {
                 if (parts > 1 && (whole || (double)passes * lone < 2.8)) break;
-                if (parts > 1 && (parts > passes || parts > most || parts > 128)) continue;
-                const double mine = (double)((passes + parts - 1) / parts), k = (double)((blocks * parts + ncu - 1) / ncu);
+                if (parts > 1 && (parts > passes || parts * N > records || parts > 128)) continue;
+                const double mine = (double)(parts == 1 ? passes : (passes + parts - 1) / parts), k = (double)((blocks * parts + ncu - 1) / ncu);
                 const double one = mine * lone + beside, all = k * (mine * pass + beside);
                 const double us = (one > all ? one : all) + (parts > 1 ? 2.8 + 0.0006 * (double)N : 0.0);
                 if (us < best) { best = us; p.codes = codes; p.parts = parts; }
@@ -1804,7 +1807,7 @@ GatherPlan gather_plan(int64_t N, int M, int K, bool aligned, size_t room, bool 
     if (whole || N < 1) return p;
     p.parts = 8 * ncu / N;
     if (p.parts > passes) p.parts = passes;
-    if (p.parts > most) p.parts = most;
+    if (p.parts * N > records) p.parts = records / N;
     if (p.parts < 1) p.parts = 1;
     return p;
 }

@@ -158,3 +158,12 @@ def test_limit_of_rows_with_one_pass(pq, M, K, most):
 def test_histograms_by_subspace(pq, M, N, K, taken):
     """Enough slices to fill the chip, and codes to pay for adding their arrays."""
     assert (pq.call_plan(N, M, K)["count"] == "subspaces") == taken
+
+
+@pytest.mark.parametrize("M,N,K,codes,parts", [(4, 48, 7936, 1, 1), (4, 48, 15_872, 2, 32), (4, 256, 15_872, 1, 1), (4, 256, 63_488, 2, 4), (4, 257, 63_488, 2, 16),
+                                               (8, 1, 6913, 1, 1), (8, 1, 13_824, 1, 54), (8, 256, 13_824, 1, 1), (8, 257, 13_824, 1, 6), (16, 48, 3841, 1, 1),
+                                               (16, 48, 7680, 1, 16), (16, 257, 7680, 1, 6), (32, 48, 1793, 1, 1), (32, 48, 3584, 1, 14), (32, 257, 14_336, 1, 8)])
+def test_blocks_of_a_code_per_unit(pq, M, N, K, codes, parts):
+    """Up to a block per compute unit there is nothing to choose until the centers take long enough to split."""
+    p = pq.call_plan(N, M, K)
+    assert (p["codes"], p["parts"]) == (codes, parts)
