@@ -1328,9 +1328,9 @@ int dot_scan_dims(int M, const Options& opt, int64_t N, int K, bool dist, const 
     return K < 16 ? 0 : 256;
 }
 
-template <int M>
+template <int M, bool MARKS>
 void launch_dot(const uint8_t* codes, int64_t N, const uint8_t* centers, int K, const float* tables, int32_t* assign, float* dist,
-                const Carve& c, char* ws, const Carried& carried, const Options& opt, int most_dims, bool marks, hipStream_t st)
+                const Carve& c, char* ws, const Carried& carried, const Options& opt, int most_dims, hipStream_t st)
 {
     const DotCarve d = dot_carve(M, K);
     char* room = ws + c.img_off;
@@ -1345,15 +1345,15 @@ void launch_dot(const uint8_t* codes, int64_t N, const uint8_t* centers, int K, 
                        check, emb, lost, state, room + d.img_off, carried.iteration, !carried.dot);
     EventPair ev{};
     const bool prof = (opt.profile & 1) && log_begin(g_scan_log, st, &ev);
-    const DotIn in{codes, centers, tables, stat, emb, lost, room + d.img_off, state, N, K, carried.iteration, marks};
+    const DotIn in{codes, centers, tables, stat, emb, lost, room + d.img_off, state, N, K, carried.iteration};
     const int64_t ncu = cu_count();
     // one or two columns of codes per wave, by the time of the rounds: about 20 tiles' worth for what a round costs beside its tiles
     auto cost = [&](int64_t ct) { return (double)(((N + 256 * ct - 1) / (256 * ct) + ncu - 1) / ncu) * ((double)K / DOT_TILE * (double)ct + 20.0); };
     const int ct = cost(2) <= cost(1) ? 2 : 1;
     const int64_t blocks = (N + 256 * ct - 1) / (256 * ct);
     const dim3 grid((unsigned)(blocks < ncu ? blocks : ncu));
-    if (ct == 2) hipLaunchKernelGGL((assign_dot_kernel<M, 2>), grid, dim3(512), 0, st, in, assign, dist);
-    else hipLaunchKernelGGL((assign_dot_kernel<M, 1>), grid, dim3(512), 0, st, in, assign, dist);
+    if (ct == 2) hipLaunchKernelGGL((assign_dot_kernel<M, 2, MARKS>), grid, dim3(512), 0, st, in, assign, dist);
+    else hipLaunchKernelGGL((assign_dot_kernel<M, 1, MARKS>), grid, dim3(512), 0, st, in, assign, dist);
     if (prof) {
         hipEventRecord(ev.b, st);
         std::lock_guard<std::mutex> lk(g_mu);
@@ -1453,7 +1453,7 @@ pqkm_status assign_tiled(const uint8_t* codes, int64_t N, const uint8_t* centers
     const uint32_t* left = nullptr;
     if constexpr (M != 4) {
         if (plan_of.dot) {
-            launch_dot<M>(codes, N, centers, K, tables, assign, dist, c, ws, carried, opt, plan_of.dot, false, st);
+            launch_dot<M, false>(codes, N, centers, K, tables, assign, dist, c, ws, carried, opt, plan_of.dot, st);
             if (launched() != PQKM_OK) return PQKM_ERR_DEVICE;
             left = &reinterpret_cast<const DotState*>(ws + c.dot_off)->left;
         }
@@ -1889,9 +1889,9 @@ pqkm_status assign_core(const Options& opt, const Carve& c, const uint8_t* codes
         const DotState* state = nullptr;
         if (dims) {
             char* wsc = static_cast<char*>(ws);
-            if (M == 8) launch_dot<8>(codes, N, centers, K, tables, assign, dist, c, wsc, carried, opt, dims, true, st);
-            else if (M == 16) launch_dot<16>(codes, N, centers, K, tables, assign, dist, c, wsc, carried, opt, dims, true, st);
-            else launch_dot<32>(codes, N, centers, K, tables, assign, dist, c, wsc, carried, opt, dims, true, st);
+            if (M == 8) launch_dot<8, true>(codes, N, centers, K, tables, assign, dist, c, wsc, carried, opt, dims, st);
+            else if (M == 16) launch_dot<16, true>(codes, N, centers, K, tables, assign, dist, c, wsc, carried, opt, dims, st);
+            else launch_dot<32, true>(codes, N, centers, K, tables, assign, dist, c, wsc, carried, opt, dims, st);
             if (launched() != PQKM_OK) return PQKM_ERR_DEVICE;
             state = reinterpret_cast<const DotState*>(wsc + c.dot_off);
             ++carried.iteration;

@@ -43,7 +43,7 @@ struct DotState {
     float scale;                                  // power of two: units of the rounded points
     uint32_t dc2[2], nc2[2];                      // per parity of the iteration: max |u_c - u'_c|^2, max |u'_c|^2, as bits
     unsigned long long formed[2];                 // likewise: fp32 distances formed
-    uint32_t some;                                // not zero: the codes whose assignment is -1 are left (DotIn::marks)
+    uint32_t some;                                // not zero: the codes whose assignment is -1 are left (MARKS)
 };
 struct DotStat { int rank; float spread; };       // per subspace: columns found (more than 256 / M: too many), see DOT_COARSE
 struct DotCheck { float e0, sum; };               // per part of a subspace: largest difference, sum of the entries
@@ -498,7 +498,6 @@ struct DotIn {
     DotState* state;
     int64_t N;
     int K, iteration;
-    bool marks;                                   // the scan behind looks for single codes that are left
 };
 
 // the fp32 distance of Eq. 3
@@ -548,7 +547,7 @@ __device__ __forceinline__ float dot_distance(const float* __restrict__ tables, 
 // M = 8, N = 1e6, K = 1000: 574 -> 342; M = 16, N = 4e5, K = 5000: 1752 -> 680; M = 32, N = 3e5, K = 6000: 6850 -> 719.  The kernel
 // itself at M = 8, N = 5e5, K = 5000, without distances: 670 to 730 us, 3.4 to 3.7e12 pairs per second.
 // ---------------------------------------------------------------------------------------------
-template <int M, int DIMS, int CT>
+template <int M, int DIMS, int CT, bool MARKS>
 __device__ __forceinline__ void dot_scan(const DotIn& f, int32_t* __restrict__ assign, float* __restrict__ dist, float4* tab,
                                          float* lost_s, char* buf, unsigned long long* key_s, uint32_t* list_s,
                                          uint32_t* over_s, uint32_t* code_s, uint32_t* misc)
@@ -823,8 +822,8 @@ __device__ __forceinline__ void dot_scan(const DotIn& f, int32_t* __restrict__ a
         const uint32_t listed = misc[2], overs = misc[3];
         // far more than the plain scan of these codes would cost: the same verdict in all threads
         const float cost = (float)listed + (float)overs * (float)f.K;
-        const bool beyond = overs > (uint32_t)DOT_OVER || cost > most;
-        if (beyond && !f.marks) {
+        const bool over = overs > (uint32_t)DOT_OVER || cost > most, beyond = MARKS && over;
+        if (over && !MARKS) {
             if (tid == 0) leave();
             break;
         }
@@ -875,7 +874,9 @@ __device__ __forceinline__ void dot_scan(const DotIn& f, int32_t* __restrict__ a
     wait_vector_loads();                                         // nothing may land in LDS after the workgroup has ended
 }
 
-template <int M, int CT>
+// MARKS: the scan behind looks for single codes that are left.  Decided at run time it cost seven more spilled scalars and 0.7 of 114 us where the scan
+// behind takes all codes or none (M = 16, N = 250007, K = 999).
+template <int M, int CT, bool MARKS>
 __global__ __launch_bounds__(512) void assign_dot_kernel(DotIn f, int32_t* __restrict__ assign, float* __restrict__ dist)
 {
     __shared__ float4 tab[4096];
@@ -893,9 +894,9 @@ __global__ __launch_bounds__(512) void assign_dot_kernel(DotIn f, int32_t* __res
     __syncthreads();
     if (misc[1]) return;
     if (dot_dims<M>(f.st) == 128)
-        dot_scan<M, 128, CT>(f, assign, dist, tab, lost_s, reinterpret_cast<char*>(buf), key_s, list_s, over_s, reinterpret_cast<uint32_t*>(code_s), misc);
+        dot_scan<M, 128, CT, MARKS>(f, assign, dist, tab, lost_s, reinterpret_cast<char*>(buf), key_s, list_s, over_s, reinterpret_cast<uint32_t*>(code_s), misc);
     else
-        dot_scan<M, 256, 1>(f, assign, dist, tab, lost_s, reinterpret_cast<char*>(buf), key_s, list_s, over_s, reinterpret_cast<uint32_t*>(code_s), misc);
+        dot_scan<M, 256, 1, MARKS>(f, assign, dist, tab, lost_s, reinterpret_cast<char*>(buf), key_s, list_s, over_s, reinterpret_cast<uint32_t*>(code_s), misc);
 }
 
 }  // namespace pqkm
