@@ -1188,7 +1188,9 @@ SubspaceHist subspace_hist(int64_t N, int M, int K, const Carve& c)
     // random number), whole update, owner : this, us: M = 4, K = 100: 28.5 : 31.4 / 39.8 : 31.2 at N = 4e5, 37.5 : 31.5 / 57.7 : 31.2 at 8e5, 89.7 : 40.0 / 184 :
     // 39.8 at 3.2e6; M = 8, K = 48: 49.8 : 34.8 / 100 : 34.9 at 8e5; K = 100: 66.7 : 50.4 / 151 : 50 at 1.6e6; M = 16, K = 48: 67 : 44 / 161 : 44 at 8e5; M = 32, K =
     // 20: 104 : 64 / 177 : 65 at 8e5.  32 clusters of four subspaces per workgroup are fewer workgroups: M = 4: 32.6 : 34.3 at 8e5, 47.0 : 39.6 at 1.6e6; M = 12: 33.3
-    // : 36.5 at 1e6 where members share subcodes.  Taken where it does not cost even clusters more than a few per cent.
+    // : 36.5 at 1e6 where members share subcodes.  Taken where it does not cost even clusters more than a few per cent.  With fewer than 32 centers that was
+    // so until the owner path formed its adds in line (M = 32, K = 28, 1.25e6: 73 : 111 / 280 : 111; M = 64, K = 16, 1.6e6: 117 : 149 / 378 : 147): kept for the
+    // uneven ones.  From 32 centers on, where the owner path's figures above are of before too, none of 800 random sizes loses more than 3 % by the rule.
     if (N > (int64_t)0xffffffff || (int64_t)K * L > SUBSPACE_HIST_WORDS) return p;
     const int64_t least = K == 32 ? (M == 4 ? 1200000 : 1500000) : 1000000;
     if (N < least || !(K >= 32 ? M >= 4 && M <= 16 : M >= 16)) return p;
@@ -1200,6 +1202,9 @@ SubspaceHist subspace_hist(int64_t N, int M, int K, const Carve& c)
         const int64_t most[] = {room, cu_count() / groups, N / 2048, 64};
         int64_t S = most[0];
         for (int64_t x : most) S = x < S ? x : S;
+        // Workgroup (g, s) runs on die s mod 8 where S is a multiple of eight, so that the groups of a slice share one L2's copy of its codes: M = 48, K = 7,
+        // 2.5e6 codes: 93 us with 16 slices, 174 with 21.
+        if (groups > 1 && S > 8) S &= ~(int64_t)7;
         return (int)(S < 1 ? 1 : S);
     };
     p.S = slices((size_t)K * M * L * sizeof(uint16_t));

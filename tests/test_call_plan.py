@@ -167,3 +167,13 @@ def test_blocks_of_a_code_per_unit(pq, M, N, K, codes, parts):
     """Up to a block per compute unit there is nothing to choose until the centers take long enough to split."""
     p = pq.call_plan(N, M, K)
     assert (p["codes"], p["parts"]) == (codes, parts)
+
+
+@pytest.mark.parametrize("M,N,K", [(48, 1_050_287, 1), (48, 2_501_840, 7), (40, 1_928_309, 2), (40, 2_036_211, 20), (20, 2_000_000, 20), (12, 2_000_000, 40), (5, 1_500_000, 40),
+                                   (4, 1_000_000, 100)])
+def test_slices_of_subspace_groups_share_a_die(pq, M, N, K):
+    """Workgroups of different subspaces read the same codes: through one L2 only where the slices are a multiple of eight."""
+    p = pq.call_plan(N, M, K)
+    assert p["count"] == "subspaces" and p["slices"] > 8
+    width = next(g for g in (4, 2, 1) if g == 1 or (g <= M and K * 256 * g <= 32768))
+    assert p["slices"] % 8 == 0 or width >= M
