@@ -4224,24 +4224,31 @@ constexpr int HIST_LDS_WORDS_SMALL = 4096;   // 16 KB (small instantiation: seve
 constexpr int HIST_QCAP = 4096;         // queue entries (16 KB)
 constexpr int SEG_HIST_WORDS = 16384;   // 64 KB: the histogram over indices sorted by cluster
 
-// One code into the private histograms of its cluster (LDS atomics).  Kept out of line: it is called
-// from many places of the scan loop, most of them cold.
-__device__ __noinline__ void hist_add_code(uint32_t* lh, const uint8_t* __restrict__ codes,
-                                           const int32_t* __restrict__ assign, int64_t n, int M, int k0, int kt,
-                                           bool wide)
+// One code into the private histograms of its cluster (LDS atomics).  Out of line, where lh is a pointer to any memory, the adds are flat ones and the
+// loop's time depends on where the linker places it: N = 721812, M = 20, K = 2, 80 per cent in one cluster: 108 us, 123 once other
+// kernels had grown, 82 so with four words' loads together; M = 40, K = 28, 21539 codes: 67, 76, 41.
+__device__ __forceinline__ void hist_add_code(uint32_t* lh, const uint8_t* __restrict__ codes, const int32_t* __restrict__ assign, int64_t n, int M,
+                                              int k0, int kt, bool wide)
 {
-    int kk = assign[n] - k0;
+    const int kk = assign[n] - k0;
     if ((unsigned)kk >= (unsigned)kt) return;
-    uint32_t* h = lh + (size_t)kk * M * L;
+    uint32_t* h = lh + kk * M * L;
     const uint8_t* x = codes + n * M;
     if (wide) {
         const uint32_t* xw = reinterpret_cast<const uint32_t*>(x);
-        for (int w = 0; w < M / 4; ++w) {
-            uint32_t p = xw[w];
-            atomicAdd(&h[(4 * w + 0) * L + (p & 255u)], 1u);
-            atomicAdd(&h[(4 * w + 1) * L + ((p >> 8) & 255u)], 1u);
-            atomicAdd(&h[(4 * w + 2) * L + ((p >> 16) & 255u)], 1u);
-            atomicAdd(&h[(4 * w + 3) * L + (p >> 24)], 1u);
+        for (int w0 = 0; w0 < M / 4; w0 += 4) {
+            uint32_t p[4];                                   // loads that travel together
+#pragma unroll
+            for (int i = 0; i < 4; ++i) p[i] = w0 + i < M / 4 ? xw[w0 + i] : 0u;
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                if (w0 + i >= M / 4) break;
+                uint32_t* hw = h + (w0 + i) * 4 * L;
+                atomicAdd(&hw[p[i] & 255u], 1u);
+                atomicAdd(&hw[L + ((p[i] >> 8) & 255u)], 1u);
+                atomicAdd(&hw[2 * L + ((p[i] >> 16) & 255u)], 1u);
+                atomicAdd(&hw[3 * L + (p[i] >> 24)], 1u);
+            }
         }
     } else {
         for (int m = 0; m < M; ++m) atomicAdd(&h[m * L + x[m]], 1u);

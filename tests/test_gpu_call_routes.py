@@ -140,3 +140,25 @@ def test_histograms_by_subspace(env, M, N, K, off):
     np.testing.assert_array_equal(h.cpu().numpy().view(np.uint32), rh)
     np.testing.assert_array_equal(n.cpu().numpy().view(np.uint32), rn)
     np.testing.assert_array_equal(c.cpu().numpy(), rc)
+
+
+# the owner path's adds: chunks of four words and what is left over, its queue full (nearly all codes in one group), codes byte by byte
+@pytest.mark.parametrize("M,N,K", [(4, 150_000, 3), (8, 150_000, 2), (12, 100_003, 5), (16, 100_000, 17), (20, 150_001, 2), (28, 70_000, 9), (40, 60_000, 130), (64, 50_000, 2), (5, 100_000, 7)])
+def test_owner_histograms_of_heavy_clusters(env, M, N, K):
+    pq, oracle, torch = env
+    rng = np.random.default_rng(N + M)
+    codes = rng.integers(0, 256, (N, M), dtype=np.uint8)
+    assign = np.where(rng.random(N) < 0.9, K - 1, rng.integers(-1, K + 1, N)).astype(np.int32)
+    centers, tables = rng.integers(0, 256, (K, M), dtype=np.uint8), rand_tables(rng, M)
+    c = torch.from_numpy(centers.copy()).cuda()
+    pq.set_option("hist_kernel", 2)
+    try:
+        assert pq.call_plan(N, M, K)["count"] == "cluster_groups"
+        _, h, n = pq.update(torch.from_numpy(codes).cuda(), torch.from_numpy(assign).cuda(), torch.from_numpy(tables).cuda(), c)
+    finally:
+        pq.set_option("hist_kernel", 0)
+    inside = (assign >= 0) & (assign < K)
+    rc, rh, rn = oracle.update(codes[inside], assign[inside], tables, centers)
+    np.testing.assert_array_equal(h.cpu().numpy().view(np.uint32), rh)
+    np.testing.assert_array_equal(n.cpu().numpy().view(np.uint32), rn)
+    np.testing.assert_array_equal(c.cpu().numpy(), rc)
