@@ -162,3 +162,20 @@ def test_owner_histograms_of_heavy_clusters(env, M, N, K):
     np.testing.assert_array_equal(h.cpu().numpy().view(np.uint32), rh)
     np.testing.assert_array_equal(n.cpu().numpy().view(np.uint32), rn)
     np.testing.assert_array_equal(c.cpu().numpy(), rc)
+
+
+# the vote with a workgroup per cluster: grids that the eight dies do not divide, more subspaces than clusters and the other way round
+@pytest.mark.parametrize("M,N,K", [(1, 50_000, 1), (4, 50_000, 9), (5, 50_000, 3), (20, 46_000, 8), (24, 46_000, 4), (40, 41_000, 28), (40, 41_000, 1), (60, 41_000, 17), (12, 60_000, 3)])
+def test_vote_per_cluster_by_dies(env, M, N, K):
+    pq, oracle, torch = env
+    rng = np.random.default_rng(N + M)
+    codes = rng.integers(0, 256, (N, M), dtype=np.uint8)
+    assign = rng.integers(0, K, N).astype(np.int32)
+    centers, tables = rng.integers(0, 256, (K, M), dtype=np.uint8), rand_tables(rng, M)
+    assert pq.call_plan(N, M, K)["vote_per_cluster"]
+    c = torch.from_numpy(centers.copy()).cuda()
+    _, h, n = pq.update(torch.from_numpy(codes).cuda(), torch.from_numpy(assign).cuda(), torch.from_numpy(tables).cuda(), c)
+    rc, rh, rn = oracle.update(codes, assign, tables, centers)
+    np.testing.assert_array_equal(h.cpu().numpy().view(np.uint32), rh)
+    np.testing.assert_array_equal(n.cpu().numpy().view(np.uint32), rn)
+    np.testing.assert_array_equal(c.cpu().numpy(), rc)
