@@ -2108,7 +2108,7 @@ pqkm_status update_impl(const Options& opt, const Carve& c, const uint8_t* codes
     const UpdateRoute route = update_route(path, force, N, M, K, codes);
     if (route == UPDATE_IN_VOTE_FEW) {
         const int G = vote_few_counts_codes(N, M, K, codes);
-        const dim3 grid((unsigned)(((int64_t)K * ((M + G - 1) / G) + 7) / 8 * 8));
+        const dim3 grid((unsigned)((int64_t)K * ((M + G - 1) / G)));
         const VoteRecords all{nullptr, nullptr, 0, codes, assign, N};
         if (G == 1)
             hipLaunchKernelGGL((vote_few_kernel<VOTE_CODES, 1>), grid, dim3(VOTE_FEW_THREADS), 0, st, hist, hist, 1, (size_t)0, false, counts, K, M, tables, centers, all);
@@ -2213,7 +2213,7 @@ pqkm_status update_impl(const Options& opt, const Carve& c, const uint8_t* codes
     }
     // vote_kernel adds at most 16 partial arrays, of 32-bit counters
     if (path == HIST_SUBSPACE || vote_few(N, M, K)) {
-        hipLaunchKernelGGL((vote_few_kernel<VOTE_PARTS>), dim3((unsigned)(((int64_t)K * ((M + 3) / 4) + 7) / 8 * 8)), dim3(256), 0, st, hist, parts, S, part_stride,
+        hipLaunchKernelGGL((vote_few_kernel<VOTE_PARTS>), dim3((unsigned)(((int64_t)K + 7) / 8 * 8 * ((M + 3) / 4))), dim3(256), 0, st, hist, parts, S, part_stride,
                            halves, counts, K, M, tables, centers, VoteRecords{});
         return launched();
     }

@@ -4664,11 +4664,18 @@ __global__ __launch_bounds__(FROM == VOTE_CODES ? VOTE_FEW_THREADS : 256) void v
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int quads = (M + G - 1) / G;
-    // A die takes consecutive clusters of the same subspaces, so that its L2 holds few tables: 280 workgroups of M = 40, K = 28 took 24 us with the
-    // subspaces side by side and take 20 (vote_kernel: 18); M = 20, K = 8: 16.9 and 14.1 (17.6).  The grid is rounded up to the eight dies.
-    const int w = (int)(blockIdx.x & 7u) * (int)(gridDim.x >> 3) + (int)(blockIdx.x >> 3);
-    if (w >= K * quads) return;
-    const int k = w % K, m0 = w / K * G;
+    // A die takes every eighth cluster of the same subspaces, so that its L2 holds few tables: 280 workgroups of M = 40, K = 28 took 24 us with the
+    // subspaces side by side and take 20 (vote_kernel: 18); M = 20, K = 8: 16.9 and 14.1 (17.6).  Every
+    // eighth, because clusters often come in the order of their sizes: M = 2, K = 3785, 171697 codes, uneven: 37 us where they were consecutive, 24 now (vote_kernel: 27).  The grid is
+    // for K rounded up to eight; not with VOTE_CODES, whose grid would not be one round any more.
+    int k = (int)blockIdx.x / quads, m0 = (int)blockIdx.x % quads * G;
+    if (FROM == VOTE_PARTS) {
+        const int each = (int)(gridDim.x >> 3) / quads;                      // clusters of a die and subspaces
+        const int at = (int)(blockIdx.x & 7u) * (int)(gridDim.x >> 3) + (int)(blockIdx.x >> 3), j = at % (8 * each);
+        k = j % each * 8 + j / each;
+        m0 = at / (8 * each) * G;
+        if (k >= K) return;
+    }
     uint32_t h[4];                           // bins chunk * 64 + lane
     if (FROM == VOTE_CODES) {
         constexpr int PER = 20;                                              // codes per thread whose loads travel together
