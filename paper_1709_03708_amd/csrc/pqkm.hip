@@ -2052,13 +2052,13 @@ inline bool vote_few(int64_t N, int M, int K)
 // where vote_kernel counts or a histogram is formed first / so: M = 4: 17 / 10 at N = 1e4, K = 100, 27.3 / 18.2 at 2e4, 32, 18.0 / 13.2 at 2e4, 256,
 // 31.0 / 24.3 at 4e4, 64, 24.7 / 20.3 at 4e4, 256, but 31.8 / 35.0 at 8e4, 100; M = 8: 20.9 / 16.5 at 2e4, 128, 31.1 / 27.2 at 4e4, 64; M = 16: 34.3 /
 // 29.1 at 4e4, 64.  A workgroup with a large share of the codes takes longer: 23.4 / 22.8 at 3e4, 8, but 25.2 / 26.6 at 4e4, 8 and 37.8 / 46.2 at
-// M = 64.  Byte by byte, four subspaces are too many: M = 6: 20.4 / 16.5 at 12000, 64, but 17.0 / 17.9 at 12000, 128.  All codes in one cluster:
+// M = 64; the vote itself 19.8 / 18.8 at 19084, 2, but 20.3 / 21.5 at 24550, 3.  Byte by byte, four subspaces are too many: M = 6: 20.4 / 16.5 at 12000, 64, but 17.0 / 17.9 at 12000, 128.  All codes in one cluster:
 // M = 4: 19.6 / 18.3 at 2e4, 64, 19.8 / 21.4 at 2e4, 256, 23.1 / 26.0 at 4e4, 64; all of them alike: 26 / 17 at 2e4, 64 (70 in one copy of the bins).
 // Returns the subspaces per workgroup, 0: not.
 inline int vote_few_counts_codes(int64_t N, int M, int K, const uint8_t* codes)
 {
     const bool words = (M & 3) == 0 && ((uintptr_t)codes & 3) == 0;
-    if (N < 1 || N > (!words ? 12000 : K < 16 ? 28000 : 40000)) return 0;
+    if (N < 1 || N > (!words ? 12000 : K < 4 ? 20000 : K < 16 ? 28000 : 40000)) return 0;
     for (int G = 1; G <= (words || N < 1500 ? 4 : 2); G *= 2)
         if ((int64_t)K * ((M + G - 1) / G) <= cu_count()) return G;
     return 0;

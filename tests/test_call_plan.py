@@ -92,7 +92,7 @@ def test_rows_of_sixteen_subspaces(pq):
     assert pq.call_plan(2000, 16, 95)["variant"] == 0 and pq.call_plan(2000, 16, 96)["variant"] == 1
 
 
-@pytest.mark.parametrize("M,N,K,aligned,few", [(4, 40_000, 16, True, True), (4, 40_001, 16, True, False), (4, 28_000, 8, True, True), (4, 28_001, 8, True, False),
+@pytest.mark.parametrize("M,N,K,aligned,few", [(4, 40_000, 16, True, True), (4, 40_001, 16, True, False), (4, 28_000, 8, True, True), (4, 28_001, 8, True, False), (8, 20_000, 3, True, True), (8, 20_001, 3, True, False),
                                                (4, 40_000, 256, True, True), (4, 40_000, 257, True, False), (64, 40_000, 8, True, False),
                                                (6, 12_000, 85, True, True), (6, 12_000, 86, True, False), (6, 1499, 128, True, True), (4, 12_001, 16, False, False)])
 def test_vote_that_counts_a_cluster_per_workgroup(pq, M, N, K, aligned, few):
